@@ -1,7 +1,7 @@
 """SepAttention (SepLLM, arXiv 2412.12094) for AMD MI355X: hand-written HIP kernels behind a C ABI.
 
 `csrc/` holds the kernels and the C entry points declared in include/sepattn.h; `binding.py` is the
-ctypes binding with the same names; `build.py` compiles libsepattn.so in-tree with hipcc for gfx950.
+binding with the same names (its calls go through csrc/native_binding.cpp); `build.py` compiles both in-tree.
 """
 from .binding import (  # noqa: F401
     EXPORTS,

@@ -1,10 +1,15 @@
-"""Thin ctypes binding of libsepattn.so: argument marshalling only.
+"""Thin binding of libsepattn.so: argument marshalling only.
 
 Each function has the name and the semantics of the C entry point declared in include/sepattn.h and
 takes torch tensors that already live on the GPU (torch is used for device memory and streams,
-nothing else).  Workspaces are allocated here with torch and handed to the library, which never
+nothing else).  Workspaces are allocated with torch and handed to the library, which never
 allocates.  Every step of the computation runs in the library's HIP kernels; if the library is
 missing this module raises at load time: there is no fallback.
+
+The calls that enqueue work go through the extension module `_native` (csrc/native_binding.cpp), which
+checks the tensors, allocates what the caller did not pass and calls the library: in Python those steps
+took longer than a small kernel.  `load()` gives the library itself through ctypes, for the queries, the
+measurement hooks and callers of the C interface.
 """
 from __future__ import annotations
 
@@ -161,6 +166,21 @@ def load(path: Optional[str] = None):
     return lib
 
 
+_calls = None
+
+
+def _native():
+    """The extension module whose calls go to the library at LIB_PATH (bound once)."""
+    global _calls
+    if _calls is None:
+        load()
+        from . import _native as mod
+
+        mod.bind(LIB_PATH, _raise_status)
+        _calls = mod
+    return _calls
+
+
 def status_string(status: int) -> str:
     return load().sepattn_status_string(int(status)).decode()
 
@@ -207,16 +227,16 @@ def _check(fn: str, rc: int) -> None:
         raise SepattnError(fn, rc)
 
 
+def _raise_status(fn: str, rc: int) -> None:
+    raise SepattnError(fn, rc)
+
+
 def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
 def _stream(t: torch.Tensor):
     return ctypes.c_void_p(torch.cuda.current_stream(t.device).cuda_stream)
-
-
-def _ws(nbytes: int, device) -> torch.Tensor:
-    return torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
 
 
 def _dtype_code(t: torch.Tensor) -> int:
@@ -240,16 +260,7 @@ def _dev(*ts: torch.Tensor) -> None:
 # ------------------------------------------------------------------------------------------------
 def sepattn_mark_separators(token_ids: torch.Tensor, sep_ids, out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """token_ids int32 [B,L] (GPU), sep_ids: host sequence of ints -> is_sep uint8 [B,L]."""
-    _dev(token_ids, out)
-    assert token_ids.dtype == torch.int32 and token_ids.dim() == 2
-    B, L = token_ids.shape
-    ids = (ctypes.c_int32 * len(sep_ids))(*[int(x) for x in sep_ids])
-    if out is None:
-        out = torch.empty((B, L), dtype=torch.uint8, device=token_ids.device)
-    _check("sepattn_mark_separators",
-           load().sepattn_mark_separators(_ptr(token_ids), B, L, ctypes.cast(ids, ctypes.c_void_p),
-                                          len(sep_ids), _ptr(out), _stream(token_ids)))
-    return out
+    return _native().mark_separators(token_ids, sep_ids, out)
 
 
 def sepattn_mark_interval(B: int, L: int, delta: int, phase: int, device, out: Optional[torch.Tensor] = None) -> torch.Tensor:
@@ -270,26 +281,7 @@ def sepattn_compact_indices(is_sep: torch.Tensor, cap: Optional[int] = None, wan
     Unless `out` = (sep_idx, sep_count, sep_prefix) is given, sep_idx is allocated and pre-filled
     with `fill` by torch; the library leaves entries beyond the count untouched.
     """
-    _dev(is_sep)
-    assert is_sep.dtype == torch.uint8 and is_sep.dim() == 2
-    B, L = is_sep.shape
-    dev = is_sep.device
-    if out is None:
-        cap = L if cap is None else int(cap)
-        idx = torch.full((B, max(cap, 1)), fill, dtype=torch.int32, device=dev)
-        cnt = torch.empty((B,), dtype=torch.int32, device=dev)
-        pre = torch.empty((B, L + 1), dtype=torch.int32, device=dev) if want_prefix else None
-    else:
-        idx, cnt, pre = out
-        _dev(idx, cnt, pre)
-        cap = idx.shape[1]
-    lib = load()
-    if ws is None:
-        ws = _ws(lib.sepattn_compact_workspace_bytes(B, L), dev)
-    _check("sepattn_compact_indices",
-           lib.sepattn_compact_indices(_ptr(is_sep), B, L, _ptr(idx), cap, _ptr(cnt), _ptr(pre), _ptr(ws),
-                                       ws.numel(), _stream(is_sep)))
-    return idx, cnt, pre
+    return _native().compact_indices(is_sep, cap, want_prefix, fill, out, ws)
 
 
 def sepattn_mark_compact(token_ids: torch.Tensor, sep_ids, cap: Optional[int] = None, want_prefix: bool = True,
@@ -300,28 +292,7 @@ def sepattn_mark_compact(token_ids: torch.Tensor, sep_ids, cap: Optional[int] = 
     Unless `out` = (is_sep, sep_idx, sep_count, sep_prefix) is given, the outputs are allocated and sep_idx is
     pre-filled with `fill` by torch; the library leaves entries beyond the count untouched.
     """
-    _dev(token_ids)
-    assert token_ids.dtype == torch.int32 and token_ids.dim() == 2
-    B, L = token_ids.shape
-    dev = token_ids.device
-    ids = (ctypes.c_int32 * len(sep_ids))(*[int(x) for x in sep_ids])
-    if out is None:
-        cap = L if cap is None else int(cap)
-        is_sep = torch.empty((B, L), dtype=torch.uint8, device=dev)
-        idx = torch.full((B, max(cap, 1)), fill, dtype=torch.int32, device=dev)
-        cnt = torch.empty((B,), dtype=torch.int32, device=dev)
-        pre = torch.empty((B, L + 1), dtype=torch.int32, device=dev) if want_prefix else None
-    else:
-        is_sep, idx, cnt, pre = out
-        _dev(is_sep, idx, cnt, pre)
-        cap = idx.shape[1]
-    lib = load()
-    if ws is None:
-        ws = _ws(lib.sepattn_compact_workspace_bytes(B, L), dev)
-    _check("sepattn_mark_compact",
-           lib.sepattn_mark_compact(_ptr(token_ids), B, L, ctypes.cast(ids, ctypes.c_void_p), len(sep_ids), _ptr(is_sep),
-                                    _ptr(idx), cap, _ptr(cnt), _ptr(pre), _ptr(ws), ws.numel(), _stream(token_ids)))
-    return is_sep, idx, cnt, pre
+    return _native().mark_compact(token_ids, sep_ids, cap, want_prefix, fill, out, ws)
 
 
 def _attn_params(Q, K, a, n, scale, cap) -> SepattnParams:
@@ -333,69 +304,20 @@ def _attn_params(Q, K, a, n, scale, cap) -> SepattnParams:
 def sepattn_forward(Q, K, V, sep_idx, sep_count, sep_prefix, a: int, n: int, scale: float,
                     out: Optional[Tuple[torch.Tensor, torch.Tensor]] = None, ws: Optional[torch.Tensor] = None):
     """Q [B,Hq,L,d], K,V [B,Hkv,L,d] -> (O like Q, LSE fp32 [B,Hq,L])."""
-    _dev(Q, K, V, sep_idx, sep_count, sep_prefix)
-    assert K.shape == V.shape and Q.dtype == K.dtype == V.dtype
-    p = _attn_params(Q, K, a, n, scale, sep_idx.shape[1])
-    lib = load()
-    if out is None:
-        O = torch.empty_like(Q)
-        LSE = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
-    else:
-        O, LSE = out
-    if ws is None:
-        ws = _ws(lib.sepattn_forward_workspace_bytes(ctypes.byref(p)), Q.device)
-    _check("sepattn_forward",
-           lib.sepattn_forward(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(sep_idx), _ptr(sep_count),
-                               _ptr(sep_prefix), _ptr(O), _ptr(LSE), _ptr(ws), ws.numel(), _stream(Q)))
-    return O, LSE
-
-
-def _head_windows(n_per_head, Hq: int):
-    arr = (ctypes.c_int32 * Hq)(*[int(v) for v in n_per_head])
-    assert len(n_per_head) == Hq
-    return arr
+    return _native().forward(Q, K, V, sep_idx, sep_count, sep_prefix, a, n, scale, out, ws)
 
 
 def sepattn_forward_headwise(Q, K, V, sep_idx, sep_count, sep_prefix, a: int, n_per_head, scale: float,
                              out: Optional[Tuple[torch.Tensor, torch.Tensor]] = None, ws: Optional[torch.Tensor] = None):
     """sepattn_forward with a neighbour window of its own for every query head (n_per_head: Hq ints, host)."""
-    _dev(Q, K, V, sep_idx, sep_count, sep_prefix)
-    assert K.shape == V.shape and Q.dtype == K.dtype == V.dtype
-    p = _attn_params(Q, K, a, 1, scale, sep_idx.shape[1])
-    nh = _head_windows(n_per_head, Q.shape[1])
-    lib = load()
-    if out is None:
-        O = torch.empty_like(Q)
-        LSE = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
-    else:
-        O, LSE = out
-    if ws is None:
-        ws = _ws(lib.sepattn_forward_workspace_bytes(ctypes.byref(p)), Q.device)
-    _check("sepattn_forward_headwise",
-           lib.sepattn_forward_headwise(ctypes.byref(p), nh, _ptr(Q), _ptr(K), _ptr(V), _ptr(sep_idx), _ptr(sep_count),
-                                        _ptr(sep_prefix), _ptr(O), _ptr(LSE), _ptr(ws), ws.numel(), _stream(Q)))
-    return O, LSE
+    return _native().forward_headwise(Q, K, V, sep_idx, sep_count, sep_prefix, a, n_per_head, scale, out, ws)
 
 
 def sepattn_backward_headwise(Q, K, V, O, LSE, dO, sep_idx, sep_count, sep_prefix, a: int, n_per_head, scale: float,
                               out: Optional[Tuple[torch.Tensor, torch.Tensor, torch.Tensor]] = None,
                               ws: Optional[torch.Tensor] = None):
     """sepattn_backward with per-head neighbour windows -> (dQ, dK, dV)."""
-    _dev(Q, K, V, O, LSE, dO, sep_idx, sep_count, sep_prefix)
-    p = _attn_params(Q, K, a, 1, scale, sep_idx.shape[1])
-    nh = _head_windows(n_per_head, Q.shape[1])
-    lib = load()
-    if out is None:
-        dQ, dK, dV = torch.empty_like(Q), torch.empty_like(K), torch.empty_like(V)
-    else:
-        dQ, dK, dV = out
-    if ws is None:
-        ws = _ws(lib.sepattn_backward_headwise_workspace_bytes(ctypes.byref(p), nh), Q.device)
-    _check("sepattn_backward_headwise",
-           lib.sepattn_backward_headwise(ctypes.byref(p), nh, _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), _ptr(dO),
-                                         _ptr(sep_idx), _ptr(sep_count), _ptr(sep_prefix), _ptr(dQ), _ptr(dK),
-                                         _ptr(dV), _ptr(ws), ws.numel(), _stream(Q)))
-    return dQ, dK, dV
+    return _native().backward_headwise(Q, K, V, O, LSE, dO, sep_idx, sep_count, sep_prefix, a, n_per_head, scale, out, ws)
 
 
 def sepattn_doc_bounds(cu_seqlens: torch.Tensor, L: int, a: int = 0, is_sep_row: Optional[torch.Tensor] = None,
@@ -403,39 +325,14 @@ def sepattn_doc_bounds(cu_seqlens: torch.Tensor, L: int, a: int = 0, is_sep_row:
     """One packed row: cu_seqlens int32 [n_docs+1] (GPU; cu[0] = 0, cu[-1] = L) -> (doc_start, doc_end) int32 [L].
     If is_sep_row (uint8 [L], one row of the marker bitmap) is given, the first a tokens of every
     document are marked in it, in place."""
-    _dev(cu_seqlens, is_sep_row)
-    assert cu_seqlens.dtype == torch.int32 and cu_seqlens.dim() == 1
-    if out is None:
-        out = (torch.empty((int(L),), dtype=torch.int32, device=cu_seqlens.device),
-               torch.empty((int(L),), dtype=torch.int32, device=cu_seqlens.device))
-    _dev(*out)
-    _check("sepattn_doc_bounds",
-           load().sepattn_doc_bounds(_ptr(cu_seqlens), int(cu_seqlens.numel()) - 1, int(L), int(a), _ptr(out[0]),
-                                     _ptr(out[1]), _ptr(is_sep_row), _stream(cu_seqlens)))
-    return out
+    return _native().doc_bounds(cu_seqlens, L, a, is_sep_row, out)
 
 
 def sepattn_forward_packed(Q, K, V, doc_start, doc_end, sep_idx, sep_count, sep_prefix, n: int, scale: float,
                            out: Optional[Tuple[torch.Tensor, torch.Tensor]] = None, ws: Optional[torch.Tensor] = None):
     """Forward over rows of packed documents: doc_start, doc_end int32 [B,L] per-position bounds;
     the index arrays come from a bitmap in which every document's initial tokens are marked (a = 0 here)."""
-    _dev(Q, K, V, doc_start, doc_end, sep_idx, sep_count, sep_prefix)
-    assert doc_start.dtype == torch.int32 and doc_end.dtype == torch.int32
-    assert tuple(doc_start.shape) == (Q.shape[0], Q.shape[2]) and doc_end.shape == doc_start.shape
-    p = _attn_params(Q, K, 0, n, scale, sep_idx.shape[1])
-    lib = load()
-    if out is None:
-        O = torch.empty_like(Q)
-        LSE = torch.empty(Q.shape[:3], dtype=torch.float32, device=Q.device)
-    else:
-        O, LSE = out
-    if ws is None:
-        ws = _ws(lib.sepattn_forward_workspace_bytes(ctypes.byref(p)), Q.device)
-    _check("sepattn_forward_packed",
-           lib.sepattn_forward_packed(ctypes.byref(p), _ptr(doc_start), _ptr(doc_end), _ptr(Q), _ptr(K), _ptr(V),
-                                      _ptr(sep_idx), _ptr(sep_count), _ptr(sep_prefix), _ptr(O), _ptr(LSE), _ptr(ws),
-                                      ws.numel(), _stream(Q)))
-    return O, LSE
+    return _native().forward_packed(Q, K, V, sep_idx, sep_count, sep_prefix, 0, n, scale, out, ws, doc_start, doc_end)
 
 
 def sepattn_backward_workspace_bytes(Q, K, a: int, n: int, scale: float, cap: int) -> int:
@@ -447,41 +344,13 @@ def sepattn_backward(Q, K, V, O, LSE, dO, sep_idx, sep_count, sep_prefix, a: int
                      out: Optional[Tuple[torch.Tensor, torch.Tensor, torch.Tensor]] = None,
                      ws: Optional[torch.Tensor] = None):
     """-> (dQ like Q, dK like K, dV like V)."""
-    _dev(Q, K, V, O, LSE, dO, sep_idx, sep_count, sep_prefix)
-    p = _attn_params(Q, K, a, n, scale, sep_idx.shape[1])
-    lib = load()
-    if out is None:
-        dQ, dK, dV = torch.empty_like(Q), torch.empty_like(K), torch.empty_like(V)
-    else:
-        dQ, dK, dV = out
-    if ws is None:
-        ws = _ws(lib.sepattn_backward_workspace_bytes(ctypes.byref(p)), Q.device)
-    _check("sepattn_backward",
-           lib.sepattn_backward(ctypes.byref(p), _ptr(Q), _ptr(K), _ptr(V), _ptr(O), _ptr(LSE), _ptr(dO),
-                                _ptr(sep_idx), _ptr(sep_count), _ptr(sep_prefix), _ptr(dQ), _ptr(dK),
-                                _ptr(dV), _ptr(ws), ws.numel(), _stream(Q)))
-    return dQ, dK, dV
+    return _native().backward(Q, K, V, O, LSE, dO, sep_idx, sep_count, sep_prefix, a, n, scale, out, ws)
 
 
 def sepattn_backward_packed(Q, K, V, O, LSE, dO, doc_start, doc_end, sep_idx, sep_count, sep_prefix, n: int,
                             scale: float, out=None, ws: Optional[torch.Tensor] = None):
     """Backward over rows of packed documents -> (dQ, dK, dV); arguments as sepattn_forward_packed."""
-    _dev(Q, K, V, O, LSE, dO, doc_start, doc_end, sep_idx, sep_count, sep_prefix)
-    assert doc_start.dtype == torch.int32 and doc_end.dtype == torch.int32
-    assert tuple(doc_start.shape) == (Q.shape[0], Q.shape[2]) and doc_end.shape == doc_start.shape
-    p = _attn_params(Q, K, 0, n, scale, sep_idx.shape[1])
-    lib = load()
-    if out is None:
-        dQ, dK, dV = torch.empty_like(Q), torch.empty_like(K), torch.empty_like(V)
-    else:
-        dQ, dK, dV = out
-    if ws is None:
-        ws = _ws(lib.sepattn_backward_workspace_bytes(ctypes.byref(p)), Q.device)
-    _check("sepattn_backward_packed",
-           lib.sepattn_backward_packed(ctypes.byref(p), _ptr(doc_start), _ptr(doc_end), _ptr(Q), _ptr(K), _ptr(V),
-                                       _ptr(O), _ptr(LSE), _ptr(dO), _ptr(sep_idx), _ptr(sep_count), _ptr(sep_prefix),
-                                       _ptr(dQ), _ptr(dK), _ptr(dV), _ptr(ws), ws.numel(), _stream(Q)))
-    return dQ, dK, dV
+    return _native().backward_packed(Q, K, V, O, LSE, dO, sep_idx, sep_count, sep_prefix, 0, n, scale, out, ws, doc_start, doc_end)
 
 
 def _kv_params(q, Kc, a, s, w, scale) -> SepkvParams:
@@ -493,35 +362,14 @@ def _kv_params(q, Kc, a, s, w, scale) -> SepkvParams:
 def sepattn_decode(q, Kc, Vc, sizes, a: int, s: int, w: int, scale: float,
                    out: Optional[Tuple[torch.Tensor, torch.Tensor]] = None, ws: Optional[torch.Tensor] = None):
     """q [S,Hq,d], Kc,Vc [S,Hkv,c,d], sizes int32 [S,6] -> (out [S,Hq,d], lse fp32 [S,Hq])."""
-    _dev(q, Kc, Vc, sizes)
-    assert sizes.dtype == torch.int32 and sizes.dim() == 2 and sizes.shape[1] == 6 and sizes.is_contiguous()
-    p = _kv_params(q, Kc, a, s, w, scale)
-    lib = load()
-    if out is None:
-        o = torch.empty_like(q)
-        lse = torch.empty(q.shape[:2], dtype=torch.float32, device=q.device)
-    else:
-        o, lse = out
-    if ws is None:
-        ws = _ws(lib.sepattn_decode_workspace_bytes(ctypes.byref(p)), q.device)
-    _check("sepattn_decode",
-           lib.sepattn_decode(ctypes.byref(p), _ptr(q), _ptr(Kc), _ptr(Vc), _ptr(sizes), _ptr(o), _ptr(lse),
-                              _ptr(ws), ws.numel(), _stream(q)))
-    return o, lse
+    return _native().decode(q, Kc, Vc, sizes, None, a, s, w, scale, out, ws)
 
 
 def sepattn_decode_noalloc(q, Kc, Vc, sizes, a: int, s: int, w: int, scale: float,
                            out: Tuple[torch.Tensor, torch.Tensor]):
     """sepattn_decode without a workspace (the library's fixed scratch array is used); the caller passes
     the outputs (out [S,Hq,d], lse fp32 [S,Hq]), so nothing at all is allocated by the call."""
-    _dev(q, Kc, Vc, sizes)
-    assert sizes.dtype == torch.int32 and sizes.dim() == 2 and sizes.shape[1] == 6 and sizes.is_contiguous()
-    p = _kv_params(q, Kc, a, s, w, scale)
-    o, lse = out
-    _check("sepattn_decode_noalloc",
-           load().sepattn_decode_noalloc(ctypes.byref(p), _ptr(q), _ptr(Kc), _ptr(Vc), _ptr(sizes), _ptr(o), _ptr(lse),
-                                         _stream(q)))
-    return o, lse
+    return _native().decode_noalloc(q, Kc, Vc, sizes, None, a, s, w, scale, out, None)
 
 
 def sepkv_rope_table(n_pos: int, d: int, base: float, device, out: Optional[torch.Tensor] = None) -> torch.Tensor:
@@ -537,70 +385,22 @@ def sepattn_decode_rope(q, Kc, Vc, sizes, rope_table, a: int, s: int, w: int, sc
                         out: Optional[Tuple[torch.Tensor, torch.Tensor]] = None, ws: Optional[torch.Tensor] = None):
     """As sepattn_decode, with q and the cached keys stored without position encoding and turned by
     their positions within the cache inside the kernel; rope_table from sepkv_rope_table."""
-    _dev(q, Kc, Vc, sizes, rope_table)
-    assert sizes.dtype == torch.int32 and sizes.dim() == 2 and sizes.shape[1] == 6 and sizes.is_contiguous()
-    assert rope_table.dtype == torch.float32
-    assert rope_table.dim() == 3 and rope_table.shape[1] == 2 and rope_table.shape[2] * 2 == q.shape[2]
-    p = _kv_params(q, Kc, a, s, w, scale)
-    lib = load()
-    if out is None:
-        o = torch.empty_like(q)
-        lse = torch.empty(q.shape[:2], dtype=torch.float32, device=q.device)
-    else:
-        o, lse = out
-    if ws is None:
-        ws = _ws(lib.sepattn_decode_workspace_bytes(ctypes.byref(p)), q.device)
-    _check("sepattn_decode_rope",
-           lib.sepattn_decode_rope(ctypes.byref(p), _ptr(q), _ptr(Kc), _ptr(Vc), _ptr(sizes), _ptr(rope_table),
-                                   int(rope_table.shape[0]), _ptr(o), _ptr(lse), _ptr(ws), ws.numel(), _stream(q)))
-    return o, lse
+    return _native().decode(q, Kc, Vc, sizes, rope_table, a, s, w, scale, out, ws)
 
 
 def sepkv_append(k_new, v_new, is_sep_new, Kc, Vc, win_is_sep, sizes, Hq: int, a: int, s: int, w: int) -> None:
     """In place: k_new, v_new [S,Hkv,d] and is_sep_new uint8 [S] enter Kc, Vc [S,Hkv,c,d], win_is_sep, sizes."""
-    _dev(k_new, v_new, is_sep_new, Kc, Vc, win_is_sep, sizes)
-    assert sizes.dtype == torch.int32 and sizes.dim() == 2 and sizes.shape[1] == 6 and sizes.is_contiguous()
-    assert is_sep_new.dtype == torch.uint8 and win_is_sep.dtype == torch.uint8
-    S, Hkv, c, d = Kc.shape
-    assert tuple(k_new.shape) == (S, Hkv, d) and tuple(v_new.shape) == (S, Hkv, d) and k_new.dtype == Kc.dtype
-    p = SepkvParams(S, int(Hq), Hkv, d, int(a), int(s), int(w), c, 1.0, _dtype_code(Kc))
-    _check("sepkv_append",
-           load().sepkv_append(ctypes.byref(p), _ptr(k_new), _ptr(v_new), _ptr(is_sep_new), _ptr(Kc), _ptr(Vc),
-                               _ptr(win_is_sep), _ptr(sizes), _stream(Kc)))
+    _native().append(k_new, v_new, is_sep_new, Kc, Vc, win_is_sep, sizes, Hq, a, s, w)
 
 
 def sepkv_evict_window(Kc, Vc, win_is_sep, sizes, Hq: int, a: int, s: int, w: int,
                        ws: Optional[torch.Tensor] = None) -> None:
     """In place on Kc, Vc [S,Hkv,c,d], win_is_sep uint8 [S,c-a-s], sizes int32 [S,6]."""
-    _dev(Kc, Vc, win_is_sep, sizes)
-    assert sizes.dtype == torch.int32 and sizes.dim() == 2 and sizes.shape[1] == 6 and sizes.is_contiguous()
-    S, Hkv, c, d = Kc.shape
-    p = SepkvParams(S, int(Hq), Hkv, d, int(a), int(s), int(w), c, 1.0, _dtype_code(Kc))
-    lib = load()
-    # the step needs no scratch memory: a workspace is passed on if the caller has one, NULL otherwise
-    _check("sepkv_evict_window",
-           lib.sepkv_evict_window(ctypes.byref(p), _ptr(Kc), _ptr(Vc), _ptr(win_is_sep), _ptr(sizes), _ptr(ws),
-                                  0 if ws is None else ws.numel(), _stream(Kc)))
+    _native().evict_window(Kc, Vc, win_is_sep, sizes, Hq, a, s, w, ws)
 
 
 def sepkv_fill_from_prefill(K, V, is_sep, sep_idx, sep_prefix, Hq: int, a: int, s: int, w: int, c: int, nw: int,
                             out=None):
     """Prefill K, V [S,Hkv,L,d] -> (Kc, Vc [S,Hkv,c,d], win_is_sep uint8 [S,c-a-s], sizes int32 [S,6]).
     Freshly allocated outputs are zero-filled (the call leaves slots beyond the sizes untouched)."""
-    _dev(K, V, is_sep, sep_idx, sep_prefix)
-    S, Hkv, L, d = K.shape
-    p = SepkvParams(S, int(Hq), Hkv, d, int(a), int(s), int(w), int(c), 1.0, _dtype_code(K))
-    if out is None:
-        Kc = torch.zeros((S, Hkv, c, d), dtype=K.dtype, device=K.device)
-        Vc = torch.zeros_like(Kc)
-        flags = torch.zeros((S, c - a - s), dtype=torch.uint8, device=K.device)
-        sizes = torch.zeros((S, 6), dtype=torch.int32, device=K.device)
-    else:
-        Kc, Vc, flags, sizes = out
-        _dev(Kc, Vc, flags, sizes)
-        assert sizes.dtype == torch.int32 and tuple(sizes.shape) == (S, 6) and sizes.is_contiguous()
-    _check("sepkv_fill_from_prefill",
-           load().sepkv_fill_from_prefill(ctypes.byref(p), int(L), int(nw), _ptr(K), _ptr(V), _ptr(is_sep),
-                                          _ptr(sep_idx), int(sep_idx.shape[1]), _ptr(sep_prefix), _ptr(Kc), _ptr(Vc),
-                                          _ptr(flags), _ptr(sizes), _stream(K)))
-    return Kc, Vc, flags, sizes
+    return _native().fill_from_prefill(K, V, is_sep, sep_idx, sep_prefix, Hq, a, s, w, c, nw, out)

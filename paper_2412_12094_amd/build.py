@@ -1,9 +1,11 @@
-"""Build libsepattn.so (HIP, gfx950) in-tree with hipcc.  Run as `python -m paper_2412_12094_amd.build`."""
+"""Build libsepattn.so (HIP, gfx950, with hipcc) and the binding's extension module _native.so (host code, with g++)
+in-tree.  Run as `python -m paper_2412_12094_amd.build`."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -11,6 +13,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsepattn.so")
+NATIVE = os.path.join(HERE, "_native.so")  # imported as paper_2412_12094_amd._native
 SOURCES = ["api.hip", "mark_compact.hip", "attn_fp32.hip", "fwd_bf16.hip", "bwd_bf16.hip", "bwd_dkv_bf16.hip", "decode.hip", "decode_mfma.hip", "decode_noalloc.hip",
            "evict.hip", "cache_fill.hip", "rope_table.hip", "cache_append.hip", "doc_bounds.hip"]
 # packed fp32 VALU instructions are switched off (some of their forms have miscomputed on
@@ -31,10 +34,32 @@ def _compile(src: str, extra) -> str:
     return obj
 
 
+def build_native(path: str = NATIVE) -> str:
+    """The binding's extension module: host code only, against torch's C++ interface."""
+    import torch
+    from torch.utils import cpp_extension
+
+    inc = [f for p in cpp_extension.include_paths() for f in ("-isystem", p)]
+    libdir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", *inc,
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", "/opt/rocm/include", "-I" + os.path.join(ROOT, "include"),
+           os.path.join(CSRC, "native_binding.cpp"), "-o", path, "-L" + libdir, "-lc10", "-lc10_hip", "-ltorch_cpu",
+           "-ltorch_hip", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on native_binding.cpp:\n{r.stderr}")
+    if r.stderr.strip():
+        sys.stderr.write(r.stderr)
+    return path
+
+
 def build(extra_flags=(), lib_path: str = LIB) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        native = ex.submit(build_native)
         objs = list(ex.map(lambda s: _compile(s, list(extra_flags)), SOURCES))
+        native.result()
     cmd = ["hipcc", "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", lib_path]
     subprocess.run(cmd, check=True)
     return lib_path

@@ -1,0 +1,605 @@
+// The binding's host path in native code: what happens between a Python call and the C entry point.
+//
+// The functions of binding.py that enqueue work take torch tensors and pass device pointers, sizes
+// and the current stream to libsepattn.  At the small end of the range (one conversation, one decode
+// step) the kernels last a few microseconds, so what a call costs on the host decides how fast a
+// generation loop runs: in Python (ctypes argument objects, current_stream(), torch.empty) it was
+// about 5.5 us per call on top of the kernel launches, here it is well under 1 us.  Nothing is
+// computed here: checks on the tensors, allocation of outputs and workspaces that the caller did not
+// pass (through torch's allocator), one call into the library.
+//
+// The module does not link libsepattn: bind(path) opens the library the binding uses and looks the
+// entry points up, so that SEPATTN_LIB selects another build for this path as well.
+#include <Python.h>
+
+#include <ATen/ATen.h>
+#include <ATen/hip/EmptyTensor.h>
+#include <c10/hip/HIPStream.h>
+#include <dlfcn.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include <vector>
+
+#include "sepattn.h"
+
+namespace {
+
+#define LIB_FUNCTIONS(X)                                                                                               \
+    X(sepattn_mark_separators) X(sepattn_compact_workspace_bytes) X(sepattn_compact_indices)  \
+    X(sepattn_mark_compact) X(sepattn_forward_workspace_bytes) X(sepattn_forward) X(sepattn_forward_headwise)          \
+    X(sepattn_backward_headwise_workspace_bytes) X(sepattn_backward_headwise) X(sepattn_doc_bounds)                    \
+    X(sepattn_forward_packed) X(sepattn_backward_packed) X(sepattn_backward_workspace_bytes) X(sepattn_backward)       \
+    X(sepattn_decode_workspace_bytes) X(sepattn_decode) X(sepattn_decode_noalloc) X(sepkv_evict_window)                \
+    X(sepkv_fill_from_prefill) X(sepattn_decode_rope) X(sepkv_append)
+struct Lib {
+#define X(name) decltype(&::name) name;
+    LIB_FUNCTIONS(X)
+#undef X
+} lib;
+PyObject *g_raise = nullptr;  // Python callable: raises SepattnError(function, status)
+
+// A failed check: the Python error is set, the caller returns nullptr.
+struct Failed {};
+[[noreturn]] void fail(PyObject *type, const char *msg) {
+    PyErr_SetString(type, msg);
+    throw Failed{};
+}
+void require(bool ok, const char *msg) {
+    if (!ok) fail(PyExc_AssertionError, msg);
+}
+
+// a tensor argument (borrowed from the caller for the duration of the call)
+const at::Tensor &tensor(PyObject *o) {
+    if (!THPVariable_Check(o)) fail(PyExc_TypeError, "a torch tensor is expected");
+    return THPVariable_Unpack(o);
+}
+// ... that must live on the GPU and be contiguous
+const at::Tensor &dev(PyObject *o) {
+    const at::Tensor &t = tensor(o);
+    if (!t.is_cuda()) fail(PyExc_ValueError, "libsepattn works on GPU tensors only");
+    if (!t.is_contiguous()) fail(PyExc_ValueError, "tensors must be contiguous");
+    return t;
+}
+void *ptr(const at::Tensor &t) { return t.data_ptr(); }
+void *ptr(PyObject *o) { return o == Py_None ? nullptr : tensor(o).data_ptr(); }
+const int32_t *i32(const at::Tensor &t) { return static_cast<const int32_t *>(t.data_ptr()); }
+
+void *stream_of(const at::Tensor &t) { return c10::hip::getCurrentHIPStream(t.device().index()).stream(); }
+
+int dtype_code(const at::Tensor &t) {
+    const auto s = t.scalar_type();
+    if (s == at::kBFloat16) return SEPATTN_BF16;
+    if (s == at::kFloat) return SEPATTN_FP32;
+    fail(PyExc_TypeError, "unsupported dtype: bf16 or fp32 expected");
+}
+at::Tensor empty(c10::IntArrayRef shape, at::ScalarType type, const at::Device &device) {
+    return at::detail::empty_cuda(shape, type, device, std::nullopt);
+}
+at::Tensor fresh_like(const at::Tensor &t) { return empty(t.sizes(), t.scalar_type(), t.device()); }
+
+long as_long(PyObject *o) {
+    if (PyLong_CheckExact(o)) {
+        const long v = PyLong_AsLong(o);
+        if (v == -1 && PyErr_Occurred()) throw Failed{};
+        return v;
+    }
+    PyObject *n = PyNumber_Long(o);  // what int(o) gives
+    if (!n) throw Failed{};
+    const long v = PyLong_AsLong(n);
+    Py_DECREF(n);
+    if (v == -1 && PyErr_Occurred()) throw Failed{};
+    return v;
+}
+int as_int(PyObject *o) {
+    const long v = as_long(o);
+    if (v < INT32_MIN || v > INT32_MAX) fail(PyExc_OverflowError, "argument does not fit 32 bits");
+    return (int)v;
+}
+float as_float(PyObject *o) {
+    const double v = PyFloat_AsDouble(o);
+    if (v == -1.0 && PyErr_Occurred()) throw Failed{};
+    return (float)v;
+}
+std::vector<int32_t> int_list(PyObject *o) {
+    PyObject *seq = PySequence_Fast(o, "a sequence of integers is expected");
+    if (!seq) throw Failed{};
+    const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq);
+    std::vector<int32_t> v((size_t)n);
+    try {
+        for (Py_ssize_t k = 0; k < n; ++k) v[(size_t)k] = (int32_t)as_long(PySequence_Fast_GET_ITEM(seq, k));
+    } catch (...) {
+        Py_DECREF(seq);
+        throw;
+    }
+    Py_DECREF(seq);
+    return v;
+}
+// the N tensors of an `out` argument
+template <int N>
+struct Out {
+    PyObject *o[N];
+    explicit Out(PyObject *seq) {
+        PyObject *fast = PySequence_Fast(seq, "out: a tuple of tensors is expected");
+        if (!fast) throw Failed{};
+        const bool ok = PySequence_Fast_GET_SIZE(fast) == N;
+        for (int k = 0; ok && k < N; ++k) o[k] = PySequence_Fast_GET_ITEM(fast, k);  // kept alive by the caller's sequence
+        Py_DECREF(fast);
+        if (!ok) fail(PyExc_ValueError, "out: wrong number of tensors");
+    }
+    PyObject *operator[](int k) const { return o[k]; }
+};
+void check(const char *fn, int rc) {
+    if (rc == SEPATTN_OK) return;
+    PyObject *r = PyObject_CallFunction(g_raise, "si", fn, rc);
+    Py_XDECREF(r);
+    throw Failed{};
+}
+// the caller's workspace, or one from torch's allocator that goes back when the call returns (the
+// allocator hands it out again in stream order)
+struct Workspace {
+    at::Tensor own;
+    void *p;
+    size_t bytes;
+    Workspace(PyObject *ws, size_t need, const at::Device &device) {
+        if (ws != Py_None) {
+            const at::Tensor &t = tensor(ws);
+            p = t.data_ptr();
+            bytes = (size_t)t.numel();
+        } else {
+            bytes = need < 256 ? 256 : need;
+            own = empty({(int64_t)bytes}, at::kByte, device);
+            p = own.data_ptr();
+        }
+    }
+};
+PyObject *wrap(at::Tensor t) { return THPVariable_Wrap(std::move(t)); }
+PyObject *keep(PyObject *o) {
+    Py_INCREF(o);
+    return o;
+}
+template <typename... P>
+PyObject *tuple_of(P *...items) {  // takes over the references
+    PyObject *t = PyTuple_New(sizeof...(items));
+    Py_ssize_t k = 0;
+    (PyTuple_SET_ITEM(t, k++, items), ...);
+    return t;
+}
+
+sepattn_params attn_params(const at::Tensor &Q, const at::Tensor &K, int a, int n, float scale, const at::Tensor &idx) {
+    if (Q.dim() != 4 || K.dim() < 2) fail(PyExc_ValueError, "Q [B,Hq,L,d] and K [B,Hkv,L,d] are expected");
+    sepattn_params p;
+    p.B = (int)Q.size(0);
+    p.Hq = (int)Q.size(1);
+    p.Hkv = (int)K.size(1);
+    p.L = (int)Q.size(2);
+    p.d = (int)Q.size(3);
+    p.a = a;
+    p.n = n;
+    p.scale = scale;
+    p.dtype = dtype_code(Q);
+    p.cap = (int)idx.size(1);
+    return p;
+}
+
+// ---- marking and compaction ----------------------------------------------------------------------
+// mark_separators(token_ids, sep_ids, out)
+PyObject *mark_separators(PyObject *const *a) {
+    const at::Tensor &tok = dev(a[0]);
+    if (a[2] != Py_None) dev(a[2]);
+    require(tok.scalar_type() == at::kInt && tok.dim() == 2, "token_ids: int32 [B, L]");
+    const int B = (int)tok.size(0), L = (int)tok.size(1);
+    const std::vector<int32_t> ids = int_list(a[1]);
+    at::Tensor out = a[2] == Py_None ? empty({B, L}, at::kByte, tok.device()) : tensor(a[2]);
+    check("sepattn_mark_separators", lib.sepattn_mark_separators(i32(tok), B, L, ids.data(), (int)ids.size(),
+                                                                 (uint8_t *)ptr(out), stream_of(tok)));
+    return a[2] == Py_None ? wrap(std::move(out)) : keep(a[2]);
+}
+
+// index arrays of a call that allocates its own: every entry of the list that is not written is `fill`
+struct IndexOut {
+    at::Tensor idx, cnt, pre;
+    int cap;
+    IndexOut(int B, int L, PyObject *cap_o, bool want_prefix, int fill, const at::Device &device) {
+        cap = cap_o == Py_None ? L : as_int(cap_o);
+        const int64_t pitch = cap > 1 ? cap : 1;
+        idx = empty({B, pitch}, at::kInt, device);
+        idx.fill_(fill);
+        cnt = empty({B}, at::kInt, device);
+        if (want_prefix) pre = empty({B, L + 1}, at::kInt, device);
+    }
+    int32_t *prefix() const { return pre.defined() ? (int32_t *)pre.data_ptr() : nullptr; }
+    PyObject *prefix_object() const { return pre.defined() ? wrap(pre) : keep(Py_None); }
+};
+
+// compact_indices(is_sep, cap, want_prefix, fill, out, ws)
+PyObject *compact_indices(PyObject *const *a) {
+    const at::Tensor &sep = dev(a[0]);
+    require(sep.scalar_type() == at::kByte && sep.dim() == 2, "is_sep: uint8 [B, L]");
+    const int B = (int)sep.size(0), L = (int)sep.size(1);
+    const Workspace ws(a[5], lib.sepattn_compact_workspace_bytes(B, L), sep.device());
+    void *st = stream_of(sep);
+    if (a[4] == Py_None) {
+        const IndexOut o(B, L, a[1], PyObject_IsTrue(a[2]) == 1, as_int(a[3]), sep.device());
+        check("sepattn_compact_indices",
+              lib.sepattn_compact_indices((const uint8_t *)ptr(sep), B, L, (int32_t *)ptr(o.idx), o.cap, (int32_t *)ptr(o.cnt),
+                                          o.prefix(), ws.p, ws.bytes, st));
+        return tuple_of(wrap(o.idx), wrap(o.cnt), o.prefix_object());
+    }
+    const Out<3> out(a[4]);
+    const at::Tensor &idx = dev(out[0]);
+    dev(out[1]);
+    if (out[2] != Py_None) dev(out[2]);
+    check("sepattn_compact_indices",
+          lib.sepattn_compact_indices((const uint8_t *)ptr(sep), B, L, (int32_t *)ptr(idx), (int)idx.size(1),
+                                      (int32_t *)ptr(out[1]), (int32_t *)ptr(out[2]), ws.p, ws.bytes, st));
+    return tuple_of(keep(out[0]), keep(out[1]), keep(out[2]));
+}
+
+// mark_compact(token_ids, sep_ids, cap, want_prefix, fill, out, ws)
+PyObject *mark_compact(PyObject *const *a) {
+    const at::Tensor &tok = dev(a[0]);
+    require(tok.scalar_type() == at::kInt && tok.dim() == 2, "token_ids: int32 [B, L]");
+    const int B = (int)tok.size(0), L = (int)tok.size(1);
+    const std::vector<int32_t> ids = int_list(a[1]);
+    const Workspace ws(a[6], lib.sepattn_compact_workspace_bytes(B, L), tok.device());
+    void *st = stream_of(tok);
+    if (a[5] == Py_None) {
+        at::Tensor sep = empty({B, L}, at::kByte, tok.device());
+        const IndexOut o(B, L, a[2], PyObject_IsTrue(a[3]) == 1, as_int(a[4]), tok.device());
+        check("sepattn_mark_compact",
+              lib.sepattn_mark_compact(i32(tok), B, L, ids.data(), (int)ids.size(), (uint8_t *)ptr(sep), (int32_t *)ptr(o.idx),
+                                       o.cap, (int32_t *)ptr(o.cnt), o.prefix(), ws.p, ws.bytes, st));
+        return tuple_of(wrap(std::move(sep)), wrap(o.idx), wrap(o.cnt), o.prefix_object());
+    }
+    const Out<4> out(a[5]);
+    dev(out[0]);
+    const at::Tensor &idx = dev(out[1]);
+    dev(out[2]);
+    if (out[3] != Py_None) dev(out[3]);
+    check("sepattn_mark_compact",
+          lib.sepattn_mark_compact(i32(tok), B, L, ids.data(), (int)ids.size(), (uint8_t *)ptr(out[0]), (int32_t *)ptr(idx),
+                                   (int)idx.size(1), (int32_t *)ptr(out[2]), (int32_t *)ptr(out[3]), ws.p, ws.bytes, st));
+    return tuple_of(keep(out[0]), keep(out[1]), keep(out[2]), keep(out[3]));
+}
+
+// doc_bounds(cu_seqlens, L, a, is_sep_row, out)
+PyObject *doc_bounds(PyObject *const *a) {
+    const at::Tensor &cu = dev(a[0]);
+    if (a[3] != Py_None) dev(a[3]);
+    require(cu.scalar_type() == at::kInt && cu.dim() == 1, "cu_seqlens: int32 [n_docs + 1]");
+    const int L = as_int(a[1]);
+    PyObject *res;
+    void *ds, *de;
+    if (a[4] == Py_None) {
+        at::Tensor s = empty({L}, at::kInt, cu.device()), e = empty({L}, at::kInt, cu.device());
+        ds = ptr(s);
+        de = ptr(e);
+        res = tuple_of(wrap(std::move(s)), wrap(std::move(e)));
+    } else {
+        const Out<2> out(a[4]);
+        ds = ptr(dev(out[0]));
+        de = ptr(dev(out[1]));
+        res = keep(a[4]);
+    }
+    try {
+        check("sepattn_doc_bounds", lib.sepattn_doc_bounds(i32(cu), (int)cu.numel() - 1, L, as_int(a[2]), (int32_t *)ds,
+                                                           (int32_t *)de, (uint8_t *)ptr(a[3]), stream_of(cu)));
+    } catch (...) {
+        Py_DECREF(res);
+        throw;
+    }
+    return res;
+}
+
+// ---- attention -------------------------------------------------------------------------------------
+// The three forms of a call differ in what stands between the sizes and the tensors: nothing, the
+// heads' windows, or the documents' bounds (nh / ds, de).
+enum Form { kPlain, kHeadwise, kPacked };
+
+// forward(Q, K, V, sep_idx, sep_count, sep_prefix, a, n | n_per_head, scale, out, ws [, doc_start, doc_end])
+template <Form F>
+PyObject *forward(PyObject *const *a) {
+    const at::Tensor &Q = dev(a[0]), &K = dev(a[1]), &V = dev(a[2]), &idx = dev(a[3]), &cnt = dev(a[4]), &pre = dev(a[5]);
+    require(K.sizes() == V.sizes() && Q.scalar_type() == K.scalar_type() && K.scalar_type() == V.scalar_type(),
+            "K and V of one shape, Q, K, V of one dtype");
+    const sepattn_params p = attn_params(Q, K, as_int(a[6]), F == kHeadwise ? 1 : as_int(a[7]), as_float(a[8]), idx);
+    std::vector<int32_t> nh;
+    const int32_t *ds = nullptr, *de = nullptr;
+    if constexpr (F == kHeadwise) {
+        nh = int_list(a[7]);
+        require((int)nh.size() == p.Hq, "n_per_head: one window per query head");
+    }
+    if constexpr (F == kPacked) {
+        const at::Tensor &s = dev(a[11]), &e = dev(a[12]);
+        require(s.scalar_type() == at::kInt && e.scalar_type() == at::kInt && s.dim() == 2 && s.size(0) == p.B &&
+                    s.size(1) == p.L && e.sizes() == s.sizes(), "doc_start, doc_end: int32 [B, L]");
+        ds = i32(s);
+        de = i32(e);
+    }
+    at::Tensor O, LSE;
+    PyObject *po = nullptr, *pl = nullptr;
+    void *optr;
+    float *lse;
+    if (a[9] == Py_None) {
+        O = fresh_like(Q);
+        LSE = empty({p.B, p.Hq, p.L}, at::kFloat, Q.device());
+        optr = ptr(O);
+        lse = (float *)ptr(LSE);
+    } else {
+        const Out<2> out(a[9]);
+        po = out[0], pl = out[1];
+        optr = ptr(po);
+        lse = (float *)ptr(pl);
+    }
+    // (the bf16 forward needs no workspace; the query keeps this right if that changes)
+    const size_t need = lib.sepattn_forward_workspace_bytes(&p);
+    at::Tensor own;
+    void *wp = nullptr;
+    size_t wb = 0;
+    if (a[10] != Py_None || need > 0) {
+        const Workspace ws(a[10], need, Q.device());
+        own = ws.own;
+        wp = ws.p;
+        wb = ws.bytes;
+    }
+    void *st = stream_of(Q);
+    if constexpr (F == kPlain)
+        check("sepattn_forward", lib.sepattn_forward(&p, ptr(Q), ptr(K), ptr(V), i32(idx), i32(cnt), i32(pre), optr, lse, wp, wb, st));
+    else if constexpr (F == kHeadwise)
+        check("sepattn_forward_headwise", lib.sepattn_forward_headwise(&p, nh.data(), ptr(Q), ptr(K), ptr(V), i32(idx), i32(cnt),
+                                                                       i32(pre), optr, lse, wp, wb, st));
+    else
+        check("sepattn_forward_packed", lib.sepattn_forward_packed(&p, ds, de, ptr(Q), ptr(K), ptr(V), i32(idx), i32(cnt), i32(pre),
+                                                                   optr, lse, wp, wb, st));
+    if (po) return tuple_of(keep(po), keep(pl));
+    return tuple_of(wrap(std::move(O)), wrap(std::move(LSE)));
+}
+
+// backward(Q, K, V, O, LSE, dO, sep_idx, sep_count, sep_prefix, a, n | n_per_head, scale, out, ws [, doc_start, doc_end])
+template <Form F>
+PyObject *backward(PyObject *const *a) {
+    const at::Tensor &Q = dev(a[0]), &K = dev(a[1]), &V = dev(a[2]), &O = dev(a[3]), &LSE = dev(a[4]), &dO = dev(a[5]),
+                     &idx = dev(a[6]), &cnt = dev(a[7]), &pre = dev(a[8]);
+    const sepattn_params p = attn_params(Q, K, as_int(a[9]), F == kHeadwise ? 1 : as_int(a[10]), as_float(a[11]), idx);
+    std::vector<int32_t> nh;
+    const int32_t *ds = nullptr, *de = nullptr;
+    if constexpr (F == kHeadwise) {
+        nh = int_list(a[10]);
+        require((int)nh.size() == p.Hq, "n_per_head: one window per query head");
+    }
+    if constexpr (F == kPacked) {
+        const at::Tensor &s = dev(a[14]), &e = dev(a[15]);
+        require(s.scalar_type() == at::kInt && e.scalar_type() == at::kInt, "doc_start, doc_end: int32 [B, L]");
+        ds = i32(s);
+        de = i32(e);
+    }
+    at::Tensor g[3];
+    PyObject *po[3] = {nullptr, nullptr, nullptr};
+    void *gp[3];
+    if (a[12] == Py_None) {
+        g[0] = fresh_like(Q);
+        g[1] = fresh_like(K);
+        g[2] = fresh_like(V);
+        for (int k = 0; k < 3; ++k) gp[k] = ptr(g[k]);
+    } else {
+        const Out<3> out(a[12]);
+        for (int k = 0; k < 3; ++k) {
+            po[k] = out[k];
+            gp[k] = ptr(po[k]);
+        }
+    }
+    size_t need = 0;
+    if (a[13] == Py_None)
+        need = F == kHeadwise ? lib.sepattn_backward_headwise_workspace_bytes(&p, nh.data()) : lib.sepattn_backward_workspace_bytes(&p);
+    const Workspace ws(a[13], need, Q.device());
+    const float *lse = (const float *)ptr(LSE);
+    void *st = stream_of(Q);
+    if constexpr (F == kPlain)
+        check("sepattn_backward", lib.sepattn_backward(&p, ptr(Q), ptr(K), ptr(V), ptr(O), lse, ptr(dO), i32(idx), i32(cnt), i32(pre),
+                                                       gp[0], gp[1], gp[2], ws.p, ws.bytes, st));
+    else if constexpr (F == kHeadwise)
+        check("sepattn_backward_headwise",
+              lib.sepattn_backward_headwise(&p, nh.data(), ptr(Q), ptr(K), ptr(V), ptr(O), lse, ptr(dO), i32(idx), i32(cnt), i32(pre),
+                                            gp[0], gp[1], gp[2], ws.p, ws.bytes, st));
+    else
+        check("sepattn_backward_packed",
+              lib.sepattn_backward_packed(&p, ds, de, ptr(Q), ptr(K), ptr(V), ptr(O), lse, ptr(dO), i32(idx), i32(cnt), i32(pre),
+                                          gp[0], gp[1], gp[2], ws.p, ws.bytes, st));
+    if (po[0]) return tuple_of(keep(po[0]), keep(po[1]), keep(po[2]));
+    return tuple_of(wrap(std::move(g[0])), wrap(std::move(g[1])), wrap(std::move(g[2])));
+}
+
+// ---- the streaming cache ---------------------------------------------------------------------------
+const at::Tensor &sizes_arg(PyObject *o) {
+    const at::Tensor &t = dev(o);
+    require(t.scalar_type() == at::kInt && t.dim() == 2 && t.size(1) == SEPKV_SIZES_COLS, "sizes: int32 [S, 6]");
+    return t;
+}
+sepkv_params kv_params(const at::Tensor &Kc, int S, int Hq, int a, int s, int w, float scale) {
+    if (Kc.dim() != 4) fail(PyExc_ValueError, "Kc [S,Hkv,c,d] is expected");
+    sepkv_params p;
+    p.S = S;
+    p.Hq = Hq;
+    p.Hkv = (int)Kc.size(1);
+    p.d = (int)Kc.size(3);
+    p.a = a;
+    p.s = s;
+    p.w = w;
+    p.c = (int)Kc.size(2);
+    p.scale = scale;
+    p.dtype = dtype_code(Kc);
+    return p;
+}
+
+// decode(q, Kc, Vc, sizes, rope_table | None, a, s, w, scale, out, ws); NOALLOC: out is required, ws unused
+template <bool NOALLOC>
+PyObject *decode(PyObject *const *a) {
+    const at::Tensor &q = dev(a[0]), &Kc = dev(a[1]), &Vc = dev(a[2]);
+    const bool rope = a[4] != Py_None;
+    const at::Tensor *table = rope ? &dev(a[4]) : nullptr;
+    const at::Tensor &sizes = sizes_arg(a[3]);
+    if (q.dim() != 3) fail(PyExc_ValueError, "q [S,Hq,d] is expected");
+    if (rope)
+        require(table->scalar_type() == at::kFloat && table->dim() == 3 && table->size(1) == 2 && table->size(2) * 2 == q.size(2),
+                "rope_table: fp32 [n_pos, 2, d/2]");
+    sepkv_params p = kv_params(Kc, (int)q.size(0), (int)q.size(1), as_int(a[5]), as_int(a[6]), as_int(a[7]), as_float(a[8]));
+    p.d = (int)q.size(2);
+    at::Tensor o, lse;
+    PyObject *po = nullptr, *pl = nullptr;
+    void *optr;
+    float *lptr;
+    if (a[9] == Py_None) {
+        if (NOALLOC) fail(PyExc_TypeError, "out is required");
+        o = fresh_like(q);
+        lse = empty({p.S, p.Hq}, at::kFloat, q.device());
+        optr = ptr(o);
+        lptr = (float *)ptr(lse);
+    } else {
+        const Out<2> out(a[9]);
+        po = out[0], pl = out[1];
+        optr = ptr(po);
+        lptr = (float *)ptr(pl);  // None: no LSE wanted
+    }
+    void *st = stream_of(q);
+    if constexpr (NOALLOC) {
+        check("sepattn_decode_noalloc",
+              lib.sepattn_decode_noalloc(&p, ptr(q), ptr(Kc), ptr(Vc), i32(sizes), optr, lptr, st));
+    } else {
+        const Workspace ws(a[10], a[10] == Py_None ? lib.sepattn_decode_workspace_bytes(&p) : 0, q.device());
+        if (rope)
+            check("sepattn_decode_rope",
+                  lib.sepattn_decode_rope(&p, ptr(q), ptr(Kc), ptr(Vc), i32(sizes), (const float *)ptr(*table), (int)table->size(0),
+                                          optr, lptr, ws.p, ws.bytes, st));
+        else
+            check("sepattn_decode",
+                  lib.sepattn_decode(&p, ptr(q), ptr(Kc), ptr(Vc), i32(sizes), optr, lptr, ws.p, ws.bytes, st));
+    }
+    if (po) return tuple_of(keep(po), keep(pl));
+    return tuple_of(wrap(std::move(o)), wrap(std::move(lse)));
+}
+
+// append(k_new, v_new, is_sep_new, Kc, Vc, win_is_sep, sizes, Hq, a, s, w)
+PyObject *append(PyObject *const *a) {
+    const at::Tensor &k = dev(a[0]), &v = dev(a[1]), &sep = dev(a[2]), &Kc = dev(a[3]), &Vc = dev(a[4]), &flags = dev(a[5]);
+    const at::Tensor &sizes = sizes_arg(a[6]);
+    require(sep.scalar_type() == at::kByte && flags.scalar_type() == at::kByte, "is_sep_new, win_is_sep: uint8");
+    const sepkv_params p = kv_params(Kc, (int)Kc.size(0), as_int(a[7]), as_int(a[8]), as_int(a[9]), as_int(a[10]), 1.0f);
+    const int64_t want[3] = {p.S, p.Hkv, p.d};
+    require(k.sizes() == c10::IntArrayRef(want, 3) && v.sizes() == k.sizes() && k.scalar_type() == Kc.scalar_type(),
+            "k_new, v_new: [S, Hkv, d] in the cache's dtype");
+    check("sepkv_append", lib.sepkv_append(&p, ptr(k), ptr(v), (const uint8_t *)ptr(sep), ptr(Kc), ptr(Vc), (uint8_t *)ptr(flags),
+                                           (int32_t *)ptr(sizes), stream_of(Kc)));
+    return keep(Py_None);
+}
+
+// evict_window(Kc, Vc, win_is_sep, sizes, Hq, a, s, w, ws)
+PyObject *evict_window(PyObject *const *a) {
+    const at::Tensor &Kc = dev(a[0]), &Vc = dev(a[1]), &flags = dev(a[2]);
+    const at::Tensor &sizes = sizes_arg(a[3]);
+    const sepkv_params p = kv_params(Kc, (int)Kc.size(0), as_int(a[4]), as_int(a[5]), as_int(a[6]), as_int(a[7]), 1.0f);
+    // the step needs no scratch memory: a workspace is passed on if the caller has one, NULL otherwise
+    check("sepkv_evict_window", lib.sepkv_evict_window(&p, ptr(Kc), ptr(Vc), (const uint8_t *)ptr(flags), (int32_t *)ptr(sizes),
+                                                       ptr(a[8]), a[8] == Py_None ? 0 : (size_t)tensor(a[8]).numel(), stream_of(Kc)));
+    return keep(Py_None);
+}
+
+// fill_from_prefill(K, V, is_sep, sep_idx, sep_prefix, Hq, a, s, w, c, nw, out)
+PyObject *fill_from_prefill(PyObject *const *a) {
+    const at::Tensor &K = dev(a[0]), &V = dev(a[1]), &sep = dev(a[2]), &idx = dev(a[3]), &pre = dev(a[4]);
+    const int L = K.dim() == 4 ? (int)K.size(2) : 0, nw = as_int(a[10]);
+    sepkv_params p = kv_params(K, (int)K.size(0), as_int(a[5]), as_int(a[6]), as_int(a[7]), as_int(a[8]), 1.0f);
+    p.c = as_int(a[9]);
+    at::Tensor Kc, Vc, flags, sizes;
+    PyObject *po[4] = {nullptr, nullptr, nullptr, nullptr};
+    if (a[11] == Py_None) {
+        // freshly allocated outputs are zero where the call leaves them alone
+        Kc = empty({p.S, p.Hkv, p.c, p.d}, K.scalar_type(), K.device()).zero_();
+        Vc = empty({p.S, p.Hkv, p.c, p.d}, K.scalar_type(), K.device()).zero_();
+        flags = empty({p.S, p.c - p.a - p.s}, at::kByte, K.device()).zero_();
+        sizes = empty({p.S, SEPKV_SIZES_COLS}, at::kInt, K.device()).zero_();
+    } else {
+        const Out<4> out(a[11]);
+        for (int k = 0; k < 4; ++k) po[k] = out[k];
+        Kc = dev(po[0]);
+        Vc = dev(po[1]);
+        flags = dev(po[2]);
+        sizes = dev(po[3]);
+        require(sizes.scalar_type() == at::kInt && sizes.dim() == 2 && sizes.size(0) == p.S && sizes.size(1) == SEPKV_SIZES_COLS,
+                "sizes: int32 [S, 6]");
+    }
+    check("sepkv_fill_from_prefill",
+          lib.sepkv_fill_from_prefill(&p, L, nw, ptr(K), ptr(V), (const uint8_t *)ptr(sep), i32(idx), (int)idx.size(1), i32(pre),
+                                      ptr(Kc), ptr(Vc), (uint8_t *)ptr(flags), (int32_t *)ptr(sizes), stream_of(K)));
+    if (po[0]) return tuple_of(keep(po[0]), keep(po[1]), keep(po[2]), keep(po[3]));
+    return tuple_of(wrap(std::move(Kc)), wrap(std::move(Vc)), wrap(std::move(flags)), wrap(std::move(sizes)));
+}
+
+// ---- module ------------------------------------------------------------------------------------------
+typedef PyObject *(*Body)(PyObject *const *);
+template <Body F, int N>
+PyObject *entry(PyObject *, PyObject *const *args, Py_ssize_t n) {
+    if (n != N) {
+        PyErr_Format(PyExc_TypeError, "%d arguments expected, got %zd", N, n);
+        return nullptr;
+    }
+    try {
+        return F(args);
+    } catch (const Failed &) {
+        return nullptr;
+    } catch (const std::exception &e) {  // torch's own errors (an allocation that fails)
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+        return nullptr;
+    }
+}
+
+// bind(path, raise_error): open the library and look its entry points up
+PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t n) {
+    if (n != 2) {
+        PyErr_SetString(PyExc_TypeError, "bind(path, raise_error)");
+        return nullptr;
+    }
+    const char *path = PyUnicode_AsUTF8(args[0]);
+    if (!path) return nullptr;
+    void *h = dlopen(path, RTLD_NOW | RTLD_LOCAL);
+    if (!h) {
+        PyErr_SetString(PyExc_OSError, dlerror());
+        return nullptr;
+    }
+#define X(name)                                                            \
+    lib.name = reinterpret_cast<decltype(lib.name)>(dlsym(h, #name));      \
+    if (!lib.name) {                                                       \
+        PyErr_SetString(PyExc_OSError, #name " is missing in the library"); \
+        return nullptr;                                                    \
+    }
+    LIB_FUNCTIONS(X)
+#undef X
+    Py_INCREF(args[1]);
+    Py_XSETREF(g_raise, args[1]);
+    Py_RETURN_NONE;
+}
+
+#define METHOD(name, body, count) \
+    {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(&entry<body, count>)), METH_FASTCALL, nullptr}
+PyMethodDef methods[] = {
+    {"bind", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(&bind)), METH_FASTCALL, nullptr},
+    METHOD("mark_separators", mark_separators, 3),
+    METHOD("compact_indices", compact_indices, 6),
+    METHOD("mark_compact", mark_compact, 7),
+    METHOD("doc_bounds", doc_bounds, 5),
+    METHOD("forward", forward<kPlain>, 11),
+    METHOD("forward_headwise", forward<kHeadwise>, 11),
+    METHOD("forward_packed", forward<kPacked>, 13),
+    METHOD("backward", backward<kPlain>, 14),
+    METHOD("backward_headwise", backward<kHeadwise>, 14),
+    METHOD("backward_packed", backward<kPacked>, 16),
+    METHOD("decode", decode<false>, 11),
+    METHOD("decode_noalloc", decode<true>, 11),
+    METHOD("append", append, 11),
+    METHOD("evict_window", evict_window, 9),
+    METHOD("fill_from_prefill", fill_from_prefill, 12),
+    {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__native(void) { return PyModule_Create(&module); }
