@@ -245,14 +245,32 @@ __global__ void decode_merge_kernel(int nsplit, const float *__restrict__ part, 
     long sh = blockIdx.x;
     int col = threadIdx.x;
     const float *r = part + sh * nsplit * PF;
-    float M = -INFINITY;
-    for (int s = 0; s < nsplit; ++s) M = fmaxf(M, r[s * PF]);
-    float lsum = 0.f, o = 0.f;
-    for (int s = 0; s < nsplit; ++s) {
-        float ms = r[s * PF];
-        float wgt = (ms == -INFINITY) ? 0.f : exp2f(ms - M);
-        lsum = fmaf(wgt, r[s * PF + 1], lsum);
-        o = fmaf(wgt, r[s * PF + 2 + col], o);
+    // the records of eight slices are requested together (one memory round trip); slices past the last
+    // repeat it with weight 0
+    constexpr int NB = 8;
+    float M = -INFINITY, lsum = 0.f, o = 0.f;
+    for (int s0 = 0; s0 < nsplit; s0 += NB) {
+        float ms[NB], ls[NB], os[NB];
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const float *rec = r + min(s0 + k, nsplit - 1) * PF;
+            ms[k] = s0 + k < nsplit ? rec[0] : -INFINITY;
+            ls[k] = rec[1];
+            os[k] = rec[2 + col];
+        }
+        float Mn = M;
+#pragma unroll
+        for (int k = 0; k < NB; ++k) Mn = fmaxf(Mn, ms[k]);
+        const float keep = (M == -INFINITY) ? 0.f : exp2f(M - Mn);
+        lsum *= keep;
+        o *= keep;
+        M = Mn;
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const float wgt = (ms[k] == -INFINITY) ? 0.f : exp2f(ms[k] - M);
+            lsum = fmaf(wgt, ls[k], lsum);
+            o = fmaf(wgt, os[k], o);
+        }
     }
     float val = (lsum > 0.f) ? o / lsum : 0.f;
     if constexpr (sizeof(T) == 2)
@@ -297,6 +315,11 @@ int launch_decode_t(const sepkv_params &p, const T *q, const T *Kc, const T *Vc,
 
 size_t decode_workspace(const sepkv_params &p) {
     int nsplit = decode_mfma_applicable(p) ? decode_mfma_nsplit(p) : pick_nsplit(p);
+    if (decode_wide_applicable(p)) {
+        const int a = decode_wide_nsplit(p, false), b = decode_wide_nsplit(p, true);
+        nsplit = nsplit > a ? nsplit : a;
+        nsplit = nsplit > b ? nsplit : b;
+    }
     return align_up((size_t)p.S * p.Hq * nsplit * (p.d + 2) * sizeof(float), 256);
 }
 
@@ -316,8 +339,10 @@ int launch_decode(const sepkv_params &p, const void *q, const void *Kc, const vo
     float *part = static_cast<float *>(ws);
     if (decode_mfma_applicable(p)) {
         using T = uint16_t;
-        const int nsplit = decode_mfma_nsplit(p);
-        int rc = launch_decode_mfma(p, nsplit, (const T *)q, (const T *)Kc, (const T *)Vc, sizes, rope, n_pos, (T *)out, lse, part, st);
+        const bool wide = decode_wide_applicable(p);
+        const int nsplit = wide ? decode_wide_nsplit(p, rope != nullptr) : decode_mfma_nsplit(p);
+        int rc = (wide ? launch_decode_wide : launch_decode_mfma)(p, nsplit, (const T *)q, (const T *)Kc, (const T *)Vc, sizes,
+                                                                  rope, n_pos, (T *)out, lse, part, st);
         if (rc != SEPATTN_OK || nsplit == 1) return rc;
         ProfScope prof(SEPATTN_K_DECODE_MERGE, st);
         if (p.d == 64)

@@ -55,4 +55,10 @@ int launch_decode_mfma(const sepkv_params &p, int nsplit, const uint16_t *q, con
                        const int32_t *sizes, const float *rope, int n_pos, uint16_t *out, float *lse, float *part,
                        hipStream_t st);
 
+bool decode_wide_applicable(const sepkv_params &p);
+int decode_wide_nsplit(const sepkv_params &p, bool rope);
+int launch_decode_wide(const sepkv_params &p, int nsplit, const uint16_t *q, const uint16_t *Kc, const uint16_t *Vc,
+                       const int32_t *sizes, const float *rope, int n_pos, uint16_t *out, float *lse, float *part,
+                       hipStream_t st);
+
 }  // namespace sepattn

@@ -1,5 +1,5 @@
 // Single-query attention over the four-block KV cache (Sec. 3.2 "Generation", Sec. 3.3), bf16,
-// as a stream through the matrix cores.
+// as a stream through the matrix cores, for 17 to 32 query heads per KV head (up to 16: decode_wide.hip).
 //
 // Every valid cache entry is visible, so this is Eq. 1 with one query row per head and M = 1.  The
 // work is HBM-bound: K and V are read once (2 * entries * d * 2 bytes per (sequence, KV head)) and

@@ -1,0 +1,384 @@
+// Single-query attention over the four-block KV cache (Sec. 3.2 "Generation", Sec. 3.3), bf16, up to 16
+// query heads per KV head: the decode kernel of every such call (more heads: decode_mfma.hip).
+//
+// A short cache, or one of few, is bound by the chain  sizes -> slots -> rows -> scores -> softmax -> output
+// -> merge and by the instructions a wave issues along it; many long ones by the rate of the memory.  A
+// workgroup owns one (sequence, KV head) and one of `nsplit` slices of its valid entries:
+//   - eight waves (four where more workgroups than compute units wait, see launch_decode_wide), one block of
+//     32 entries each at a time.  A wave has one LDS stage of K and V rows, filled with direct global->LDS
+//     loads; the K half is refilled as soon as the scores' operands sit in registers, the V half one step
+//     later, so 128 KB per compute unit are in flight nearly all the time and no workgroup barrier is needed;
+//   - v_mfma_f32_16x16x32_bf16: a block's scores are 8 values per lane (16 with 32-column operands), the
+//     output 4 registers per 16 dimensions, the merge records half as many;
+//   - a row's slot is worked out once per row (lane r has row r's) and handed to the lanes that fetch it with
+//     ds_bpermute, instead of once per 16-byte piece;
+//   - positions within the cache (ROPE, Sec. 3.3 "Positional Encoding", Sec. 4.6): every key is turned by its
+//     distance to the query, so that the query needs no turning.  Row r of a block is r entries closer than the
+//     block's first, so its angle is that of the first entry's distance (one table row per block, read by all
+//     lanes alike) minus that of r (rows 0 .. 31 of the table, fetched once per workgroup into LDS, kept in
+//     registers); dimension i pairs with i + D/2 in another fragment of the same lane.  (Reading each row's own
+//     table row from memory is 64 separate 16-byte pieces per instruction: 3.5 us per round of eight blocks.)
+// Measured (MI355X, 32/8 heads, d = 128, one call of a stream of calls, us without / with ROPE; before: four
+// waves, 32-column operands, two stages per wave, the angle carried from block to block in registers):
+//   1 sequence, 64 entries 5.1 / 6.7 -> 4.1 / 4.9; 800 entries 8.8 / 12.0 -> 7.4 / 8.8
+//   32 sequences, 300 entries 9.5 / 13.5 -> 6.9 / 8.4; 3332 entries (436.7 MB) 67.7 / 73.1 -> 64.6 / 65.8 (6.8 TB/s)
+//
+// Operand layouts of 16x16x32 (lane l, g = l / 16): A row l%16, k = 8g..8g+7; B column l%16, same k; C
+// column l%16, rows 4g..4g+3.  Row 4g+i of score tile t (t = 0, 1) is row 8g+4t+i of the block, so that
+// the two tiles' registers of lane group g are rows 8g..8g+7, exactly the k-slots the group holds of the
+// probabilities as B operand of the output contraction: no exchange between lanes.
+#include "common.h"
+#include "mfma_common.h"
+#include "decode_common.h"
+
+namespace sepattn {
+
+namespace {
+
+constexpr int kDwRows = 32;  // entries per block (one stage of a wave)
+
+__device__ inline f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+
+// XOR permutation of the 16-byte chunks of a row (row = 8a + 4t + i): the 16 rows (a, i) of a row-major
+// A fragment hit 16 different 16-byte slots of 256 bytes, and the 8 rows (a%2, i) of half a transposed
+// read 8 different 32-byte slots
+template <int D>
+__device__ inline int dw_swz(int row) {
+    const int i = row & 3, a = row >> 3;
+    if (D == 128) return (i << 1) | ((a & 1) << 3) | (a >> 1);
+    return (i & 2) | ((a & 1) << 2) | (a >> 1);  // two rows per 256 bytes: row bit 0 already separates them
+}
+
+// maximum / sum over the four lane groups (lanes l, l^16, l^32, l^48)
+__device__ inline float groups_max(float x) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return pair_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ inline float groups_sum(float x) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return pair_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Wint-to-pointer-cast"
+__device__ inline f32x4 lds_read_f4(uint32_t addr) { return *(const f32x4 __attribute__((address_space(3))) *)addr; }
+#pragma clang diagnostic pop
+
+template <int D, bool ROPE, int NW>
+__global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
+    sepkv_params p, int G, const uint16_t *__restrict__ q, const uint16_t *__restrict__ Kc,
+    const uint16_t *__restrict__ Vc, const int32_t *__restrict__ sizes, const float *__restrict__ rope, int n_pos,
+    float *__restrict__ part, uint16_t *__restrict__ out, float *__restrict__ lse) {
+    constexpr int CH = D / 8;           // 16-byte chunks per row
+    constexpr int RPL = 64 / CH;        // rows covered by one wave-wide 1 KB load
+    constexpr int NLD = kDwRows / RPL;  // wave-wide loads per tensor per stage
+    constexpr int KSTEPS = D / 32;
+    constexpr int KS2 = KSTEPS / 2;     // dimensions of k-step ks pair with those of k-step ks + KS2
+    constexpr int DB = D / 16;          // output blocks of 16 dimensions
+    constexpr int TILE = kDwRows * D;
+    constexpr int PF = D + 2;           // partial record: max (log2 domain), sum, D unnormalised outputs
+    constexpr int RF = D + 4;           // the same in LDS, padded to whole 16-byte pieces
+
+    __shared__ __attribute__((aligned(1024))) uint16_t smem[2][NW][TILE];  // K rows, V rows of every wave's stage
+    static_assert(sizeof(smem) >= 16 * NW * RF * sizeof(float), "merge records overlay the stages");
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, g = lane >> 4;
+    const int nsplit = gridDim.x, split = blockIdx.x, kv = blockIdx.y, sq = blockIdx.z;
+    const int h0 = kv * G;
+    const uint16_t *Kh = Kc + ((long)sq * p.Hkv + kv) * (long)p.c * D;
+    const uint16_t *Vh = Vc + ((long)sq * p.Hkv + kv) * (long)p.c * D;
+
+    // queries: B operand, column = head of the group (zero beyond G)
+    u32x4 qraw[KSTEPS];
+    {
+        const uint16_t *qrow = q + ((long)sq * p.Hq + h0 + min(col, G - 1)) * D + 8 * g;
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) qraw[ks] = *reinterpret_cast<const u32x4 *>(qrow + 32 * ks);
+    }
+    // ROPE: the table rows 0 .. 31 (cos, sin of a row's place within a block), shared by the waves, with the chunks
+    // of a row permuted; and per wave the table row of the block's first entry (two, in turn)
+    // four waves: the table lies over the V stages, whose first rows are requested once it has been read, so that
+    // two workgroups fit a compute unit
+    constexpr bool OVER = NW == 4;
+    __shared__ __attribute__((aligned(1024))) float tab_s[ROPE && !OVER ? kDwRows * D : 4];
+    __shared__ __attribute__((aligned(1024))) float base_s[ROPE ? NW : 1][ROPE ? 2 * D : 4];
+    const uint32_t t_lds = OVER ? lds_addr(&smem[1][0][0]) : lds_addr(&tab_s[0]), b_lds = lds_addr(&base_s[ROPE ? wave : 0][0]);
+    if constexpr (ROPE) {
+        constexpr int TCH = D / 4, TRPL = 64 / TCH, TLD = kDwRows / TRPL / NW;  // chunks per row, rows and loads per wave
+        static_assert(TLD >= 1 && TLD * TRPL * NW == kDwRows, "the table rows must divide among the waves");
+        static_for<TLD>([&](auto U) {
+            const int r = (wave * TLD + U) * TRPL + lane / TCH;
+            dma_to_lds_16(rope, (uint32_t)(min(r, n_pos - 1) * D * 4) + (uint32_t)(((lane % TCH) ^ dw_swz<128>(r)) * 16),
+                          t_lds + (wave * TLD + U) * 1024);
+        });
+    }
+    const CacheMap cm = cache_map(p, sizes + SEPKV_SIZES_COLS * sq);
+    const int nv = cm.n_init + cm.n_sep + cm.n_past + cm.n_loc;
+    // slices of whole blocks; wave w takes blocks w, w + NW, ... of the slice
+    const int nb = (nv + kDwRows - 1) / kDwRows;
+    const int per = (nsplit == 1 ? nb : (nb + nsplit - 1) / nsplit) * kDwRows;
+    const int e0 = min(split * per, nv), e1 = min(nv, e0 + per);
+
+    const uint32_t k_lds = lds_addr(&smem[0][wave][0]), v_lds = lds_addr(&smem[1][wave][0]);
+    const int my_pc = lane % CH, my_sub = lane / CH;
+    // The rows of one block, in two steps (the K rows' half of the stage is free as soon as the scores' operands
+    // sit in registers, the V rows' half one step later): byte offsets of the rows, the K rows (with ROPE after the
+    // table row of the first entry's distance, D fp32 unpermuted: all lanes of a group read the same pieces), the V rows.
+    uint32_t off[NLD];
+    auto issue_keys = [&](int eb, int par) __attribute__((always_inline)) {
+        const int slot = decode_slot_of(cm, min(eb + (lane & 31), e1 - 1));  // entries past the end: the last one (masked)
+        static_for<NLD>([&](auto U) {
+            constexpr int u = U;
+            const int r = u * RPL + my_sub;
+            const int sl = __builtin_amdgcn_ds_bpermute(r * 4, slot);
+            off[u] = (uint32_t)sl * (uint32_t)(D * 2) + (uint32_t)((my_pc ^ dw_swz<D>(r)) * 16);
+        });
+        if constexpr (ROPE) {
+            if (lane < D / 4) dma_to_lds_16(rope + (long)(nv - 1 - eb) * D, lane * 16, b_lds + par * D * 4);
+        }
+        static_for<NLD>([&](auto U) { dma_to_lds_16_nt(Kh, off[U], k_lds + U * RPL * D * 2); });
+    };
+    auto issue_values = [&]() __attribute__((always_inline)) {
+        static_for<NLD>([&](auto U) { dma_to_lds_16_nt(Vh, off[U], v_lds + U * RPL * D * 2); });
+    };
+    auto wait_loads = [&](auto N) __attribute__((always_inline)) {  // at most N loads are still in flight
+        constexpr int n = decltype(N)::value;
+        static_assert(n == 4 || n == 5 || n == 8 || n == 9 || n == 17, "wait counts are written for d = 64 and 128");
+        if constexpr (n == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        if constexpr (n == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
+        if constexpr (n == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        if constexpr (n == 9) asm volatile("s_waitcnt vmcnt(9)" ::: "memory");
+        if constexpr (n == 17) asm volatile("s_waitcnt vmcnt(17)" ::: "memory");
+    };
+
+    const float sl2 = p.scale * kLog2e_f;
+    f32x4 oacc[DB];
+#pragma unroll
+    for (int db = 0; db < DB; ++db) oacc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m_run = -INFINITY, l_run = 0.f;
+    bf16x8 qreg[KSTEPS];
+
+    // byte offsets of this lane's fragments in a stage: K row 8 (col/4) + col%4 (+ 4t), chunk 4 ks + g;
+    // V rows 8g + p/4 (+ 4), columns 16 db + 4 (p%4) with p = lane % 16
+    const int krow = 8 * (col >> 2) + (col & 3), vrow = 8 * g + (col >> 2);
+    const uint32_t kswz = dw_swz<D>(krow), vswz = dw_swz<D>(vrow);  // the same for rows + 4
+    const uint32_t kbase = k_lds + krow * D * 2, vbase = v_lds + vrow * D * 2 + ((col & 1) << 3);
+
+    int eb = e0 + wave * kDwRows;
+    const bool any = eb < e1;
+    if (any) {
+        issue_keys(eb, 0);
+        if (!(ROPE && OVER)) issue_values();
+    }
+    // cos / sin of the lane's two rows r = krow + 4t within a block, 8 frequencies per k-step
+    f32x4 rc[2][KS2][2], rs[2][KS2][2];
+    if constexpr (ROPE) {
+        // this wave's share of the table (requested before its first stage) has landed
+        if (any) wait_loads(IntC<(OVER ? 1 : 2) * NLD + 1>{});
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int ks = 0; ks < KS2; ++ks)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const uint32_t row = t_lds + (krow + 4 * t) * D * 4, tswz = dw_swz<128>(krow);
+                    rc[t][ks][h] = lds_read_f4(row + (((uint32_t)(8 * ks + 2 * g + h) ^ tswz) << 4));
+                    rs[t][ks][h] = lds_read_f4(row + (((uint32_t)(D / 8 + 8 * ks + 2 * g + h) ^ tswz) << 4));
+                }
+        if constexpr (OVER) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (any) issue_values();
+        }
+    }
+#pragma unroll
+    for (int ks = 0; ks < KSTEPS; ++ks) qreg[ks] = as_bf16x8(col < G ? qraw[ks] : u32x4{0u, 0u, 0u, 0u});
+
+    for (int par = 0; eb < e1; eb += NW * kDwRows, par ^= 1) {
+        wait_loads(IntC<NLD>{});  // the K rows (and the block's table row); the V rows may be in flight
+        bf16x8 ka[2][KSTEPS];
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int ks = 0; ks < KSTEPS; ++ks)
+                ka[t][ks] = lds_read_b128_at(kbase + 4 * t * D * 2 + (((uint32_t)(4 * ks + g) ^ kswz) << 4));
+        const bool more = eb + NW * kDwRows < e1;
+        if (more) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            issue_keys(eb + NW * kDwRows, par ^ 1);
+        }
+        if constexpr (ROPE) {
+            // R(-distance): (x, y) -> (x cos + y sin, y cos - x sin), dimension i with i + D/2; the distance of row r
+            // is that of the block's first entry minus r
+#pragma unroll
+            for (int ks = 0; ks < KS2; ++ks) {
+                f32x4 bc[2], bs[2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    bc[h] = lds_read_f4(b_lds + par * D * 4 + (8 * ks + 2 * g + h) * 16);
+                    bs[h] = lds_read_f4(b_lds + par * D * 4 + (D / 8 + 8 * ks + 2 * g + h) * 16);
+                }
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const f32x8 x = __builtin_convertvector(ka[t][ks], f32x8), y = __builtin_convertvector(ka[t][ks + KS2], f32x8);
+                    f32x8 u, v;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float c0 = bc[e >> 2][e & 3], s0 = bs[e >> 2][e & 3];
+                        const float cr = rc[t][ks][e >> 2][e & 3], sr = rs[t][ks][e >> 2][e & 3];
+                        const float c = fmaf(s0, sr, c0 * cr), s = fmaf(-c0, sr, s0 * cr);
+                        u[e] = fmaf(y[e], s, x[e] * c);
+                        v[e] = fmaf(-x[e], s, y[e] * c);
+                    }
+                    ka[t][ks] = __builtin_convertvector(u, bf16x8);
+                    ka[t][ks + KS2] = __builtin_convertvector(v, bf16x8);
+                }
+            }
+        }
+        f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) {
+            s0 = mfma16(ka[0][ks], qreg[ks], s0);
+            s1 = mfma16(ka[1][ks], qreg[ks], s1);
+        }
+        if (more) wait_loads(IntC<NLD + (ROPE ? 1 : 0)>{});  // the V rows (only the next block's K rows are in flight)
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        bf16x8 va[DB];
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            const uint32_t a0 = vbase + (((uint32_t)(2 * db + ((col & 3) >> 1)) ^ vswz) << 4);
+            va[db] = lds_read_tr_at(a0, 4 * D * 2);
+        }
+        if (more) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+            issue_values();
+        }
+        float s[8] = {s0[0], s0[1], s0[2], s0[3], s1[0], s1[1], s1[2], s1[3]};  // rows 8g .. 8g+7 of the block
+        const int n_valid = e1 - eb;  // >= 1
+        if (n_valid < kDwRows) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) s[i] = 8 * g + i < n_valid ? s[i] : -INFINITY;
+        }
+        float m_loc = fmaxf(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3])), fmaxf(fmaxf(s[4], s[5]), fmaxf(s[6], s[7])));
+        const float m_new = fmaxf(m_run, groups_max(m_loc) * sl2);  // finite: row 0 of a block is valid
+        const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+        m_run = m_new;
+        float psum = 0.f;
+        f32x8 pr;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            pr[i] = __builtin_amdgcn_exp2f(fmaf(s[i], sl2, -m_new));
+            psum += pr[i];
+        }
+        l_run = l_run * alpha + psum;
+        const bf16x8 pb = __builtin_convertvector(pr, bf16x8);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+            oacc[db] *= alpha;
+            oacc[db] = mfma16(va[db], pb, oacc[db]);
+        }
+    }
+
+    // ---- merge the waves' states through LDS: every wave's record overlays the stages
+    const float l_tot = groups_sum(l_run);
+    float *red = reinterpret_cast<float *>(&smem[0][0][0]);  // [G][NW][RF]: D outputs, max, sum
+    __syncthreads();
+    if (col < G) {
+        float *r = red + (col * NW + wave) * RF;
+        if (g == 0) {
+            r[D] = m_run;
+            r[D + 1] = l_tot;
+        }
+#pragma unroll
+        for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4 *>(r + 16 * db + 4 * g) = oacc[db];
+    }
+    __syncthreads();
+    for (int item = tid; item < G * (D / 2); item += 64 * NW) {  // two columns per thread
+        const int h = item / (D / 2), c2 = item % (D / 2);
+        const float *r = red + h * NW * RF;
+        float M = -INFINITY, ms[NW];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            ms[w] = r[w * RF + D];
+            M = fmaxf(M, ms[w]);
+        }
+        float lsum = 0.f, o0 = 0.f, o1 = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float wgt = (ms[w] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ms[w] - M);
+            const float2 o = *reinterpret_cast<const float2 *>(r + w * RF + 2 * c2);
+            lsum = fmaf(wgt, r[w * RF + D + 1], lsum);
+            o0 = fmaf(wgt, o.x, o0);
+            o1 = fmaf(wgt, o.y, o1);
+        }
+        const long sh = (long)sq * p.Hq + h0 + h;
+        if (nsplit == 1) {
+            const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
+            typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+            typedef float f32x2 __attribute__((ext_vector_type(2)));
+            const f32x2 v = {lsum > 0.f ? o0 * inv : 0.f, lsum > 0.f ? o1 * inv : 0.f};
+            *reinterpret_cast<bf16x2 *>(out + sh * D + 2 * c2) = __builtin_convertvector(v, bf16x2);
+            if (lse && c2 == 0) lse[sh] = (lsum > 0.f) ? (M + __builtin_amdgcn_logf(lsum)) * kLn2_f : -INFINITY;
+        } else {
+            float *dst = part + (sh * nsplit + split) * PF;
+            *reinterpret_cast<float2 *>(dst + 2 + 2 * c2) = float2{o0, o1};
+            if (c2 == 0) *reinterpret_cast<float2 *>(dst) = float2{M, lsum};
+        }
+    }
+}
+
+// workgroups of eight waves that a compute unit holds (by LDS)
+int decode_wide_per_cu(const sepkv_params &p) { return p.d == 64 ? 2 : 1; }
+
+}  // namespace
+
+bool decode_wide_applicable(const sepkv_params &p) {
+    return p.dtype == SEPATTN_BF16 && (p.d == 64 || p.d == 128) && p.Hq / p.Hkv <= 16;
+}
+
+// Slices per cache.  One slice needs no second launch; a wave then works through ceil(blocks / 8) blocks one
+// after the other.  More slices pay when the blocks a workgroup is spared take longer than the merge
+// launch (about 3 us): measured 0.22 us per block of a lone workgroup at d = 128, 0.38 us with ROPE, half
+// of that at d = 64, hence the thresholds below.  Never more slices than give every wave one block, nor
+// more workgroups than the compute units hold at once.
+int decode_wide_nsplit(const sepkv_params &p, bool rope) {
+    const int nb = (p.c + kDwRows - 1) / kDwRows;
+    const long fit = (long)compute_units() * decode_wide_per_cu(p) / ((long)p.S * p.Hkv);
+    int ns = (nb + 7) / 8;
+    if (ns > fit) ns = fit < 1 ? 1 : (int)fit;
+    if (ns > 64) ns = 64;
+    const int spared = nb - (nb + ns - 1) / ns;
+    const int pays = (rope ? 8 : 14) * (p.d == 64 ? 2 : 1);
+    return spared > pays ? ns : 1;
+}
+
+int launch_decode_wide(const sepkv_params &p, int nsplit, const uint16_t *q, const uint16_t *Kc, const uint16_t *Vc,
+                       const int32_t *sizes, const float *rope, int n_pos, uint16_t *out, float *lse, float *part,
+                       hipStream_t st) {
+    if (p.Hkv > 65535 || p.S > 65535) return SEPATTN_ERR_SHAPE;
+    const int G = p.Hq / p.Hkv;
+    ProfScope prof(SEPATTN_K_DECODE_SPLIT, st);
+    auto go = [&](auto D_, auto NW_) {
+        constexpr int D = decltype(D_)::value, NW = decltype(NW_)::value;
+        const dim3 grid(nsplit, p.Hkv, p.S), block(64 * NW);
+        if (rope)
+            hipLaunchKernelGGL((decode_wide_kernel<D, true, NW>), grid, block, 0, st, p, G, q, Kc, Vc, sizes, rope, n_pos, part, out, lse);
+        else
+            hipLaunchKernelGGL((decode_wide_kernel<D, false, NW>), grid, block, 0, st, p, G, q, Kc, Vc, sizes, rope, n_pos, part, out, lse);
+    };
+    // eight waves, unless there are more workgroups than the compute units hold at once: then four waves and
+    // half the LDS, two (d = 64: four) workgroups per compute unit, so that one's start and merge overlap
+    // another's stream (64 sequences x 8 heads of 100 entries 8.9 -> 5.4 us, of 1000 entries 40.7 -> 39.2)
+    const bool many = (long)p.S * p.Hkv * nsplit > (long)compute_units() * decode_wide_per_cu(p);
+    if (p.d == 64) many ? go(IntC<64>{}, IntC<4>{}) : go(IntC<64>{}, IntC<8>{});
+    else many ? go(IntC<128>{}, IntC<4>{}) : go(IntC<128>{}, IntC<8>{});
+    return launch_status();
+}
+
+}  // namespace sepattn

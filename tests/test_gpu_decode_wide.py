@@ -1,0 +1,59 @@
+"""The eight- and four-wave decode kernel at the edges of its dispatch, against the oracle: one block of
+entries, one more than a round of its waves, several slices, more workgroups than compute units, and the
+smallest and largest head groups.  Needs an MI355X."""
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    (2, 16, 1, 128, 0, 8, 4, 24),     # one block; 16 heads per KV head; fewer table rows than a block has entries
+    (2, 8, 4, 64, 4, 100, 60, 256),   # exactly one block per wave
+    (2, 8, 8, 64, 4, 100, 60, 257),   # one wave has a second block
+    (2, 14, 2, 128, 4, 64, 256, 800), # 7 heads per KV head; several slices with ROPE
+    (1, 4, 1, 128, 4, 300, 256, 1100),# several slices with and without ROPE
+    (3, 6, 2, 64, 3, 700, 300, 1999), # the same at d = 64
+    (33, 16, 8, 128, 2, 20, 10, 75),  # 264 pairs: four waves, two workgroups per compute unit
+    (65, 8, 8, 64, 2, 150, 50, 290),  # 520 pairs, several blocks per wave
+]
+
+
+@pytest.mark.parametrize("rope", [False, True])
+@pytest.mark.parametrize("S,Hq,Hkv,d,a,s,w,c", CASES)
+def test_decode_dispatch_edges(S, Hq, Hkv, d, a, s, w, c, rope):
+    import paper_2412_12094_amd as sp
+
+    rng = np.random.default_rng(c + S)
+    wcap = c - a - s
+    sizes = np.zeros((S, 4), dtype=np.int32)
+    for q in range(S):
+        tot = int(rng.integers(1, wcap + 1))
+        loc = min(w, tot)
+        sizes[q] = (int(rng.integers(0, a + 1)), int(rng.integers(0, s + 1)), tot - loc, loc)
+    sizes[0] = (a, s, wcap - w, w)  # one full cache
+    if S > 1:
+        sizes[1] = (0, 0, 0, 1)     # and one with a single entry
+    cfg = wl.CacheConfig("wide", S, Hq, Hkv, d, a, s, w, c, 0.1, "bf16", seed=900 + c)
+    data = wl.make_cache(cfg, sizes)
+    heads = np.stack([rng.integers(0, s, size=S), rng.integers(0, wcap, size=S)], axis=1)
+    # slots without a valid entry hold NaN
+    Kp, Vp, _, sz6 = wl.cache_to_ring(data["Kc"], data["Vc"], data["win_is_sep"], sizes, heads, a, s, fill=np.nan)
+    bf = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda().to(torch.bfloat16)
+    q, Kc, Vc, sz = bf(data["q"]), bf(Kp), bf(Vp), torch.from_numpy(sz6).cuda()
+    scale = 1.0 / math.sqrt(d)
+    if rope:
+        table = sp.sepkv_rope_table(c, d, 10000.0, "cuda")
+        out, lse = sp.sepattn_decode_rope(q, Kc, Vc, sz, table, a, s, w, scale)
+        ref, lref = oracle.decode_rope(data["q"], data["Kc"], data["Vc"], sizes, a, s, scale, 10000.0)
+    else:
+        out, lse = sp.sepattn_decode(q, Kc, Vc, sz, a, s, w, scale)
+        ref, lref = oracle.decode(data["q"], data["Kc"], data["Vc"], sizes, a, s, scale)
+    torch.cuda.synchronize()
+    assert np.abs(out.float().cpu().numpy() - ref).max() <= 2e-2
+    assert np.abs(lse.cpu().numpy() - lref).max() <= (1e-2 if rope else 2e-3)
