@@ -284,7 +284,7 @@ int sepattn_forward(const sepattn_params *p, const void *Q, const void *K, const
     discard_stale_hip_error();
     if (q.dtype == SEPATTN_FP32)
         return launch_forward_fp32(q, kNoHeadWin, (const float *)Q, (const float *)K, (const float *)V, sep_idx,
-                                   sep_prefix, nullptr, (float *)O, LSE, st);
+                                   sep_prefix, nullptr, nullptr, (float *)O, LSE, st);
     return launch_forward_bf16(q, kNoHeadWin, Q, K, V, sep_idx, sep_prefix, nullptr, nullptr, O, LSE, ws, st);
 }
 
@@ -312,14 +312,14 @@ int sepattn_forward_packed(const sepattn_params *p, const int32_t *doc_start, co
     discard_stale_hip_error();
     if (p->dtype == SEPATTN_FP32)
         return launch_forward_fp32(normalised(p), kNoHeadWin, (const float *)Q, (const float *)K, (const float *)V, sep_idx,
-                                   sep_prefix, doc_start, (float *)O, LSE, static_cast<hipStream_t>(stream));
+                                   sep_prefix, doc_start, doc_end, (float *)O, LSE, static_cast<hipStream_t>(stream));
     return launch_forward_bf16(normalised(p), kNoHeadWin, Q, K, V, sep_idx, sep_prefix, doc_start, doc_end, O, LSE, ws,
                                static_cast<hipStream_t>(stream));
 }
 
 size_t sepattn_backward_workspace_bytes(const sepattn_params *p) {
     if (check_attn(p) != SEPATTN_OK) return 0;
-    if (p->dtype == SEPATTN_FP32) return align_up((size_t)p->B * p->Hq * p->L * sizeof(float), 256);
+    if (p->dtype == SEPATTN_FP32) return backward_fp32_workspace(normalised(p));
     return backward_bf16_workspace(normalised(p));
 }
 
@@ -342,7 +342,7 @@ int sepattn_backward(const sepattn_params *p, const void *Q, const void *K, cons
     if (q.dtype == SEPATTN_FP32)
         return launch_backward_fp32(q, kNoHeadWin, (const float *)Q, (const float *)K, (const float *)V,
                                     (const float *)O, LSE, (const float *)dO, sep_idx, sep_prefix, nullptr, nullptr,
-                                    (float *)dQ, (float *)dK, (float *)dV, (float *)ws, st);
+                                    (float *)dQ, (float *)dK, (float *)dV, ws, st);
     return launch_backward_bf16(q, kNoHeadWin, Q, K, V, O, LSE, dO, sep_idx, sep_count, sep_prefix, nullptr, nullptr, dQ, dK, dV,
                                 ws, st);
 }
@@ -365,7 +365,7 @@ int sepattn_forward_headwise(const sepattn_params *p, const int32_t *n_per_head,
     discard_stale_hip_error();
     if (q.dtype == SEPATTN_FP32)
         return launch_forward_fp32(q, hw, (const float *)Q, (const float *)K, (const float *)V, sep_idx, sep_prefix,
-                                   nullptr, (float *)O, LSE, st);
+                                   nullptr, nullptr, (float *)O, LSE, st);
     return launch_forward_bf16(q, hw, Q, K, V, sep_idx, sep_prefix, nullptr, nullptr, O, LSE, ws, st);
 }
 
@@ -399,7 +399,7 @@ int sepattn_backward_headwise(const sepattn_params *p, const int32_t *n_per_head
     if (q.dtype == SEPATTN_FP32)
         return launch_backward_fp32(q, hw, (const float *)Q, (const float *)K, (const float *)V, (const float *)O, LSE,
                                     (const float *)dO, sep_idx, sep_prefix, nullptr, nullptr, (float *)dQ, (float *)dK,
-                                    (float *)dV, (float *)ws, st);
+                                    (float *)dV, ws, st);
     return launch_backward_bf16(q, hw, Q, K, V, O, LSE, dO, sep_idx, sep_count, sep_prefix, nullptr, nullptr, dQ, dK, dV,
                                 ws, st);
 }
@@ -424,7 +424,7 @@ int sepattn_backward_packed(const sepattn_params *p, const int32_t *doc_start, c
     if (p->dtype == SEPATTN_FP32)
         return launch_backward_fp32(normalised(p), kNoHeadWin, (const float *)Q, (const float *)K, (const float *)V,
                                     (const float *)O, LSE, (const float *)dO, sep_idx, sep_prefix, doc_start, doc_end,
-                                    (float *)dQ, (float *)dK, (float *)dV, (float *)ws,
+                                    (float *)dQ, (float *)dK, (float *)dV, ws,
                                     static_cast<hipStream_t>(stream));
     return launch_backward_bf16(normalised(p), kNoHeadWin, Q, K, V, O, LSE, dO, sep_idx, sep_count, sep_prefix, doc_start,
                                 doc_end, dQ, dK, dV, ws, static_cast<hipStream_t>(stream));

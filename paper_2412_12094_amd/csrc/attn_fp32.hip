@@ -1,284 +1,524 @@
-// fp32 debug path of SepAttention forward and backward (Eq. 1 with the mask of Eq. 2).
+// fp32 path of SepAttention forward and backward (Eq. 1 with the mask of Eq. 2): the path that a bf16
+// run is checked against.
 //
-// Slow and simple on purpose: one wavefront per query row (forward, dQ) or per key row (dK/dV),
-// plain fp32 FMA arithmetic, no matrix cores.  It exists to validate the decomposition of a row's
-// visible keys into  [initial tokens | separators older than the window | window]  (Sec. 3.1)
-// against the oracle at tight tolerance, independently of the bf16 MFMA kernels.
+// All contractions run on v_mfma_f32_16x16x4_f32 (fp32 operands, fp32 accumulation: a fused
+// multiply-add per product, no reduced precision anywhere) in blocks of 16 queries x 16 keys of one query head.  Operand layouts
+// (lane l, m = l%16, g = l/16):
+//   A (16 x 4): row m, k = g          B (4 x 16): column m, k = g
+//   C (16 x 16): column m, register i holds row 4 g + i
+// The k slots of a contraction may be dealt in any order as long as both operands agree, so a row
+// operand is read as 16-byte pieces (piece c of a lane: elements 16 c + 4 g .. +3 of its row, one
+// element per matrix instruction), and a lane's four accumulator registers of one contraction are,
+// as they stand, its B operand of the next one (step i: k slot g is accumulator row 4 g + i).
 //
-// Row i sees: j < min(a, ws) (initial), separators in [min(a, ws), ws) (taken from the compacted
-// index list), and the window ws <= j <= i with ws = max(0, i-n+1).  The three ranges are disjoint,
-// so every visible pair is visited exactly once and no mask test is needed.
-// Key j is seen by the contiguous query range [j, j+n) and, if it is an initial token or a
-// separator, by every later query as well.
-// Packed documents (doc_start / doc_end given, per position; the documents' initial tokens are
-// marked in the bitmap and a = 0): the three ranges of a row start at its document's first position
-// instead of 0, and a key's query range ends with its document.
-#include "common.h"
+// At the sizes this path is used at, a call lasts about as long as its chain of memory latencies, so
+// the work of a tile is spread over the four waves of a workgroup (16-key blocks, or query blocks, dealt round-robin; the waves'
+// partial results meet once in LDS), operands go straight from memory to registers, and what can
+// share a launch does: D_i is formed by the dQ kernel, and the far keys' partial sums are added by the
+// last workgroup to finish a list tile instead of by a kernel of their own.
+// B=1, 2 heads per KV head, L=512, d=64, n=64: forward 22 -> 7 us, D_i and dQ 5 + 23 -> 8, dK/dV 168 -> 20, against one
+// wave per row on the vector ALU.
+#include "bwd_common.h"
+#include "key_stream.h"
+#include "mfma_common.h"
 
 namespace sepattn {
 
 namespace {
 
+constexpr int kT = 16;      // queries / keys per block
+constexpr int kWaves = 4;   // waves per workgroup
+// (query block, head) items per far slice: two per wave.  An item costs a wave about 1.3 us, sharing a
+// list tile among slices about 3 us once: with 4 or 16 items the same call is 1 and 2.5 us slower.
+constexpr int kMinItems = 8;
+
+__device__ inline f32x4 mfma_f32(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+
 template <int D>
-__device__ inline float dot_row(const float *__restrict__ x, const float *__restrict__ y) {
-    float s = 0.f;
-#pragma unroll 8
-    for (int k = 0; k < D; k += 4) {
-        float4 a = *reinterpret_cast<const float4 *>(x + k);
-        float4 b = *reinterpret_cast<const float4 *>(y + k);
-        s = fmaf(a.x, b.x, s);
-        s = fmaf(a.y, b.y, s);
-        s = fmaf(a.z, b.z, s);
-        s = fmaf(a.w, b.w, s);
+__device__ inline void load_row(f32x4 (&f)[D / 16], const float *__restrict__ row, int g) {
+#pragma unroll
+    for (int c = 0; c < D / 16; ++c) f[c] = *reinterpret_cast<const f32x4 *>(row + 16 * c + 4 * g);
+}
+// x = A B over D, two interleaved accumulators
+template <int D>
+__device__ inline f32x4 row_product(const f32x4 (&a)[D / 16], const f32x4 (&b)[D / 16]) {
+    f32x4 x = {0.f, 0.f, 0.f, 0.f}, y = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < D / 16; ++c) {
+        x = mfma_f32(a[c][0], b[c][0], x);
+        y = mfma_f32(a[c][1], b[c][1], y);
+        x = mfma_f32(a[c][2], b[c][2], x);
+        y = mfma_f32(a[c][3], b[c][3], y);
     }
-    return s;
+    return x + y;
+}
+__device__ inline float group_max(float v) {
+    v = fmaxf(v, __shfl_xor(v, 16));
+    return fmaxf(v, __shfl_xor(v, 32));
+}
+__device__ inline float group_sum(float v) {
+    v += __shfl_xor(v, 16);
+    return v + __shfl_xor(v, 32);
 }
 
-__device__ inline float wave_max(float v) {
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-    return v;
-}
-__device__ inline float wave_sum(float v) {
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    return v;
-}
-
-struct RowKeys {
-    int n_init, n_sep, sep_lo, ws, total, ds;
+// A query tile: 16 positions from i0 on of one query head, and its key stream (key_stream.h).
+struct QueryTile {
+    int b, h, kv, i0;
+    long row0;  // first row of the head in [B, Hq, L]
+    sepattn_params p;  // p.n: the head's own window
+    const int32_t *prefix, *idx, *dend;
+    Stream st;
+    int de;
 };
-
-// ds: first position of the row's document (0 without packing)
-__device__ inline RowKeys row_keys(int i, int a, int n, const int32_t *__restrict__ prefix, int ds) {
-    RowKeys r;
-    r.ds = ds;
-    r.ws = max(ds, i - n + 1);
-    r.n_init = min(a, r.ws - ds);
-    r.sep_lo = prefix[ds + r.n_init];
-    r.n_sep = prefix[r.ws] - r.sep_lo;
-    r.total = r.n_init + r.n_sep + (i - r.ws + 1);
-    return r;
+__device__ inline QueryTile query_tile(const sepattn_params &p, const HeadWin &hw, const int32_t *sep_idx,
+                                       const int32_t *sep_prefix, const int32_t *doc_start, const int32_t *doc_end) {
+    QueryTile t;
+    const int n_tiles = (p.L + kT - 1) / kT;
+    const int bh = blockIdx.x / n_tiles;
+    t.b = bh / p.Hq, t.h = bh % p.Hq, t.kv = t.h / (p.Hq / p.Hkv);
+    t.i0 = (blockIdx.x % n_tiles) * kT;
+    t.row0 = (long)bh * p.L;
+    t.p = p;
+    t.p.n = p.n - head_delta(hw, t.h);
+    t.prefix = sep_prefix + (long)t.b * (p.L + 1);
+    t.idx = sep_idx + (long)t.b * p.cap;
+    t.dend = doc_end ? doc_end + (long)t.b * p.L : nullptr;
+    if (doc_start) {
+        // the clamps keep inconsistent bounds (caller error) from faulting
+        t.st = make_stream_docs(t.p, t.prefix, t.i0, kT, min(max(doc_start[(long)t.b * p.L + t.i0], 0), t.i0));
+        t.de = min(max(t.dend[t.i0], t.i0 + 1), p.L);
+    } else {
+        t.st = make_stream(t.p, t.prefix, t.i0, kT);
+        t.de = kIntMax;
+    }
+    return t;
 }
-
-// cap and L bound the index read and the position it yields, so that a caller breaking
-// sep_count <= cap (stale list tail) gets wrong numbers rather than a fault
-__device__ inline int key_at(const RowKeys &r, int t, const int32_t *__restrict__ sep_idx, int cap, int L) {
-    if (t < r.n_init) return r.ds + t;
-    if (t < r.n_init + r.n_sep)
-        return min(max(sep_idx[min(r.sep_lo + t - r.n_init, cap - 1)], 0), L - 1);
-    return r.ws + (t - r.n_init - r.n_sep);
+// position and visible query range of stream element k
+__device__ inline int tile_key(const QueryTile &t, int k, int &lo, int &hi) {
+    const int j = stream_key(t.st, k, t.p, t.idx, t.prefix, lo, hi);
+    if (t.dend) hi = min(hi, (k < t.st.n_dense ? t.de : t.dend[j]) - 1);
+    return j;
 }
-
-// ---- forward: one wave per (b, h, i) ---------------------------------------------------------
+// the four keys whose scores this lane holds: element 4 g + i of a block, described by lane 4 g + i
+struct Keys4 {
+    int j[4];
+    bool vis[4];
+};
+__device__ inline Keys4 keys_of_lane(int j, int lo, int hi, int g, int iq) {
+    Keys4 k;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int src = 4 * g + i;
+        k.j[i] = __shfl(j, src);
+        const int l = __shfl(lo, src), h = __shfl(hi, src);  // every lane takes part in both
+        k.vis[i] = l <= iq && iq <= h;
+    }
+    return k;
+}
+// element (column block cb * 16 + m, streamed row i of the lane's four) of a row-major matrix, transposed operand
 template <int D>
-__global__ __launch_bounds__(256) void fwd_fp32_kernel(sepattn_params p, const float *__restrict__ Q,
-                                                       const float *__restrict__ K,
-                                                       const float *__restrict__ V,
-                                                       const int32_t *__restrict__ sep_idx,
-                                                       const int32_t *__restrict__ sep_prefix,
-                                                       const int32_t *__restrict__ doc_start,
-                                                       float *__restrict__ O, float *__restrict__ LSE, HeadWin hw) {
-    constexpr int R = D / kWave;  // output values per lane
-    int lane = threadIdx.x % kWave;
-    long row = (long)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-    long n_rows = (long)p.B * p.Hq * p.L;
-    if (row >= n_rows) return;
-    int i = (int)(row % p.L);
-    int h = (int)((row / p.L) % p.Hq);
-    int b = (int)(row / ((long)p.L * p.Hq));
-    int kv = h / (p.Hq / p.Hkv);
-    const float *q = Q + row * D;
-    const float *Kh = K + ((long)b * p.Hkv + kv) * (long)p.L * D;
-    const float *Vh = V + ((long)b * p.Hkv + kv) * (long)p.L * D;
+__device__ inline void load_columns(float (&f)[D / 16][4], const float *__restrict__ base, const int (&row)[4], int m) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int cb = 0; cb < D / 16; ++cb) f[cb][i] = base[(long)row[i] * D + 16 * cb + m];
+}
+
+// ---- forward -----------------------------------------------------------------------------------
+template <int D>
+__global__ __launch_bounds__(64 * kWaves) void fwd_fp32_kernel(sepattn_params p, const float *__restrict__ Q,
+                                                               const float *__restrict__ K, const float *__restrict__ V,
+                                                               const int32_t *__restrict__ sep_idx,
+                                                               const int32_t *__restrict__ sep_prefix,
+                                                               const int32_t *__restrict__ doc_start,
+                                                               const int32_t *__restrict__ doc_end,
+                                                               float *__restrict__ O, float *__restrict__ LSE, HeadWin hw) {
+    constexpr int C = D / 16;
+    __shared__ float os[kWaves][kT][D + 4];
+    __shared__ float ms[kWaves][kT], ls[kWaves][kT];
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: scalar loads and branches
+    const QueryTile t = query_tile(p, hw, sep_idx, sep_prefix, doc_start, doc_end);
+    const long kv0 = ((long)t.b * p.Hkv + t.kv) * (long)p.L * D;
+    const float *Kh = K + kv0, *Vh = V + kv0;
+    const int iq = t.i0 + m;
+    f32x4 qf[C], o[C];
+    load_row<D>(qf, Q + (t.row0 + min(iq, p.L - 1)) * D, g);
+#pragma unroll
+    for (int c = 0; c < C; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float mx = -INFINITY, l = 0.f;
+    for (int k0 = wave * kT; k0 < t.st.n_total; k0 += kWaves * kT) {
+        int lo, hi;
+        const int j = tile_key(t, k0 + m, lo, hi);
+        f32x4 kf[C];
+        load_row<D>(kf, Kh + (long)j * D, g);
+        const Keys4 kk = keys_of_lane(j, lo, hi, g, iq);
+        float vf[C][4];
+        load_columns<D>(vf, Vh, kk.j, m);
+        f32x4 s = row_product<D>(kf, qf);
+        float mb = -INFINITY;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            s[i] = kk.vis[i] ? s[i] * p.scale : -INFINITY;
+            mb = fmaxf(mb, s[i]);
+        }
+        const float m_new = fmaxf(mx, group_max(mb));
+        const float ref = m_new == -INFINITY ? 0.f : m_new;  // a row that has seen no key yet
+        const float alpha = expf(mx - ref);
+        float ps = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            s[i] = expf(s[i] - ref);
+            ps += s[i];
+        }
+        l = l * alpha + group_sum(ps);
+        mx = m_new;
+#pragma unroll
+        for (int c = 0; c < C; ++c) o[c] *= alpha;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int c = 0; c < C; ++c) o[c] = mfma_f32(vf[c][i], s[i], o[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) *reinterpret_cast<f32x4 *>(&os[wave][m][16 * c + 4 * g]) = o[c];
+    if (g == 0) ms[wave][m] = mx, ls[wave][m] = l;
+    __syncthreads();
+    for (int e = threadIdx.x; e < kT * D / 4; e += 64 * kWaves) {
+        const int r = e / (D / 4), col = (e % (D / 4)) * 4;
+        float mt = ms[0][r], lt = 0.f;
+        for (int w = 1; w < kWaves; ++w) mt = fmaxf(mt, ms[w][r]);
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            const float f = expf(ms[w][r] - mt);
+            lt += ls[w][r] * f;
+            x += *reinterpret_cast<const f32x4 *>(&os[w][r][col]) * f;
+        }
+        if (t.i0 + r < p.L) {
+            *reinterpret_cast<f32x4 *>(O + (t.row0 + t.i0 + r) * D + col) = x / lt;
+            if (col == 0) LSE[t.row0 + t.i0 + r] = mt + logf(lt);
+        }
+    }
+}
+
+// ---- dQ, and D_i = <dO_i, O_i> for the dK/dV kernel, whose counters it clears too ---------------------
+template <int D>
+__global__ __launch_bounds__(64 * kWaves) void dq_fp32_kernel(sepattn_params p, const float *__restrict__ Q,
+                                                              const float *__restrict__ K, const float *__restrict__ V,
+                                                              const float *__restrict__ O, const float *__restrict__ LSE,
+                                                              const float *__restrict__ dO,
+                                                              const int32_t *__restrict__ sep_idx,
+                                                              const int32_t *__restrict__ sep_prefix,
+                                                              const int32_t *__restrict__ doc_start,
+                                                              const int32_t *__restrict__ doc_end,
+                                                              float *__restrict__ dQ, float *__restrict__ Dws,
+                                                              int32_t *__restrict__ counters, long n_counters, HeadWin hw) {
+    constexpr int C = D / 16;
+    __shared__ float xs[kWaves][kT][D + 4];
+    for (long c = (long)blockIdx.x * (64 * kWaves) + threadIdx.x; c < n_counters; c += (long)gridDim.x * (64 * kWaves)) counters[c] = 0;
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: scalar loads and branches
+    const QueryTile t = query_tile(p, hw, sep_idx, sep_prefix, doc_start, doc_end);
+    const long kv0 = ((long)t.b * p.Hkv + t.kv) * (long)p.L * D;
+    const float *Kh = K + kv0, *Vh = V + kv0;
+    const int iq = t.i0 + m;
+    const long row = t.row0 + min(iq, p.L - 1);
+    f32x4 qf[C], gf[C], acc[C];
+    load_row<D>(qf, Q + row * D, g);
+    load_row<D>(gf, dO + row * D, g);
+    float Di = 0.f;
+    {
+        f32x4 of[C];
+        load_row<D>(of, O + row * D, g);
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) Di = fmaf(gf[c][e], of[c][e], Di);
+        Di = group_sum(Di);
+    }
+    const float lse = LSE[row];
+    if (wave == 0 && g == 0 && iq < p.L) Dws[row] = Di;
+#pragma unroll
+    for (int c = 0; c < C; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = wave * kT; k0 < t.st.n_total; k0 += kWaves * kT) {
+        int lo, hi;
+        const int j = tile_key(t, k0 + m, lo, hi);
+        f32x4 kf[C], vf[C];
+        load_row<D>(kf, Kh + (long)j * D, g);
+        load_row<D>(vf, Vh + (long)j * D, g);
+        const Keys4 kk = keys_of_lane(j, lo, hi, g, iq);
+        float kt[C][4];
+        load_columns<D>(kt, Kh, kk.j, m);
+        const f32x4 s = row_product<D>(kf, qf), dp = row_product<D>(vf, gf);
+        f32x4 ds;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ds[i] = kk.vis[i] ? expf(s[i] * p.scale - lse) * (dp[i] - Di) : 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int c = 0; c < C; ++c) acc[c] = mfma_f32(kt[c][i], ds[i], acc[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) *reinterpret_cast<f32x4 *>(&xs[wave][m][16 * c + 4 * g]) = acc[c];
+    __syncthreads();
+    for (int e = threadIdx.x; e < kT * D / 4; e += 64 * kWaves) {
+        const int r = e / (D / 4), col = (e % (D / 4)) * 4;
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) x += *reinterpret_cast<const f32x4 *>(&xs[w][r][col]);
+        if (t.i0 + r < p.L) *reinterpret_cast<f32x4 *>(dQ + (t.row0 + t.i0 + r) * D + col) = x * p.scale;
+    }
+}
+
+// ---- dK, dV ------------------------------------------------------------------------------------
+// Keys come in two kinds of tiles of 16: consecutive positions, of which only those that are neither
+// initial tokens nor separators count (a band unit: the queries of their window), and consecutive
+// entries of the far list (every query from the tile's first key to the end of the sequence or
+// document).  The items (query block, head) of all list tiles of a (batch, KV head), in order, are
+// cut into equal slices, one per workgroup, at most `wpg` of them and none shorter than kMinItems; a
+// list tile that lies in one slice is finished there, otherwise each slice writes a partial (slot
+// slice + tile) and the workgroup that is the last to count itself in adds them in slice order.
+// Every wave of a workgroup keeps the tile's K and V rows and its own dK and dV sums in registers.
+template <int D>
+__global__ __launch_bounds__(64 * kWaves) void dkv_fp32_kernel(sepattn_params p, const float *__restrict__ Q,
+                                                               const float *__restrict__ K, const float *__restrict__ V,
+                                                               const float *__restrict__ LSE, const float *__restrict__ dO,
+                                                               const float *__restrict__ Drow,
+                                                               const int32_t *__restrict__ sep_idx,
+                                                               const int32_t *__restrict__ sep_prefix,
+                                                               const int32_t *__restrict__ doc_end, float *__restrict__ dK,
+                                                               float *__restrict__ dV, float *__restrict__ partials,
+                                                               int32_t *__restrict__ counters, int n_far_tiles, int wpg,
+                                                               HeadWin hw) {
+    constexpr int C = D / 16;
+    __shared__ float xs[kWaves][kT][D + 4];
+    __shared__ int last_s;
+    const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: scalar loads and branches
+    const int G = p.Hq / p.Hkv, n_bkv = p.B * p.Hkv;
+    const int bkv = blockIdx.x % n_bkv, unit = blockIdx.x / n_bkv;  // units: wpg far slices, then the band units
+    const int kv = bkv % p.Hkv, b = bkv / p.Hkv;
     const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
     const int32_t *idx = sep_idx + (long)b * p.cap;
-    // (the clamp keeps inconsistent bounds from faulting)
-    RowKeys rk = row_keys(i, p.a, p.n - head_delta(hw, h), prefix, doc_start ? min(max(doc_start[(long)b * p.L + i], 0), i) : 0);
+    const int32_t *dend = doc_end ? doc_end + (long)b * p.L : nullptr;
+    const long kvrow0 = (long)bkv * p.L;
+    const FarList fl = far_list(p, prefix);
+    f32x4 kf[C], vf[C], ak[C], av[C];
 
-    float m = -INFINITY, l = 0.f;
-    float acc[R];
-    for (int r = 0; r < R; ++r) acc[r] = 0.f;
-    for (int t0 = 0; t0 < rk.total; t0 += kWave) {
-        int t = t0 + lane;
-        int j = (t < rk.total) ? key_at(rk, t, idx, p.cap, p.L) : 0;
-        float s = (t < rk.total) ? p.scale * dot_row<D>(q, Kh + (long)j * D) : -INFINITY;
-        float m_new = fmaxf(m, wave_max(s));  // finite: the chunk holds at least one key
-        float alpha = expf(m - m_new);
-        float pr = expf(s - m_new);
-        l = l * alpha + wave_sum(pr);
-        for (int r = 0; r < R; ++r) acc[r] *= alpha;
-        int cnt = min(kWave, rk.total - t0);
-        for (int k = 0; k < cnt; ++k) {
-            float pk = __shfl(pr, k);
-            int jk = __shfl(j, k);
-            for (int r = 0; r < R; ++r) acc[r] = fmaf(pk, Vh[(long)jk * D + lane + r * kWave], acc[r]);
-        }
-        m = m_new;
-    }
-    for (int r = 0; r < R; ++r) O[row * D + lane + r * kWave] = acc[r] / l;
-    if (lane == 0) LSE[row] = m + logf(l);
-}
-
-// ---- backward pre-pass: D_i = <dO_i, O_i>, one wave per row -----------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void rowdot_fp32_kernel(long n_rows, const float *__restrict__ dO,
-                                                          const float *__restrict__ O,
-                                                          float *__restrict__ Dout) {
-    int lane = threadIdx.x % kWave;
-    long row = (long)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-    if (row >= n_rows) return;
-    float s = 0.f;
-    for (int k = lane; k < D; k += kWave) s = fmaf(dO[row * D + k], O[row * D + k], s);
-    s = wave_sum(s);
-    if (lane == 0) Dout[row] = s;
-}
-
-// ---- dQ: one wave per (b, h, i) -----------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void dq_fp32_kernel(sepattn_params p, const float *__restrict__ Q,
-                                                      const float *__restrict__ K,
-                                                      const float *__restrict__ V,
-                                                      const float *__restrict__ LSE,
-                                                      const float *__restrict__ dO,
-                                                      const float *__restrict__ Drow,
-                                                      const int32_t *__restrict__ sep_idx,
-                                                      const int32_t *__restrict__ sep_prefix,
-                                                      const int32_t *__restrict__ doc_start,
-                                                      float *__restrict__ dQ, HeadWin hw) {
-    constexpr int R = D / kWave;
-    int lane = threadIdx.x % kWave;
-    long row = (long)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-    long n_rows = (long)p.B * p.Hq * p.L;
-    if (row >= n_rows) return;
-    int i = (int)(row % p.L);
-    int h = (int)((row / p.L) % p.Hq);
-    int b = (int)(row / ((long)p.L * p.Hq));
-    int kv = h / (p.Hq / p.Hkv);
-    const float *q = Q + row * D;
-    const float *go = dO + row * D;
-    const float *Kh = K + ((long)b * p.Hkv + kv) * (long)p.L * D;
-    const float *Vh = V + ((long)b * p.Hkv + kv) * (long)p.L * D;
-    const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
-    const int32_t *idx = sep_idx + (long)b * p.cap;
-    // (the clamp keeps inconsistent bounds from faulting)
-    RowKeys rk = row_keys(i, p.a, p.n - head_delta(hw, h), prefix, doc_start ? min(max(doc_start[(long)b * p.L + i], 0), i) : 0);
-    float lse = LSE[row], Di = Drow[row];
-    float acc[R];
-    for (int r = 0; r < R; ++r) acc[r] = 0.f;
-    for (int t0 = 0; t0 < rk.total; t0 += kWave) {
-        int t = t0 + lane;
-        int j = 0;
-        float ds = 0.f;
-        if (t < rk.total) {
-            j = key_at(rk, t, idx, p.cap, p.L);
-            float s = p.scale * dot_row<D>(q, Kh + (long)j * D);
-            float pr = expf(s - lse);
-            float dp = dot_row<D>(go, Vh + (long)j * D);
-            ds = pr * (dp - Di);
-        }
-        int cnt = min(kWave, rk.total - t0);
-        for (int k = 0; k < cnt; ++k) {
-            float dsk = __shfl(ds, k);
-            int jk = __shfl(j, k);
-            for (int r = 0; r < R; ++r) acc[r] = fmaf(dsk, Kh[(long)jk * D + lane + r * kWave], acc[r]);
-        }
-    }
-    for (int r = 0; r < R; ++r) dQ[row * D + lane + r * kWave] = p.scale * acc[r];
-}
-
-// ---- dK, dV: one wave per (b, kv, j), loops over the query heads of the group and the queries
-// that see key j ------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256) void dkv_fp32_kernel(sepattn_params p, const float *__restrict__ Q,
-                                                       const float *__restrict__ K,
-                                                       const float *__restrict__ V,
-                                                       const float *__restrict__ LSE,
-                                                       const float *__restrict__ dO,
-                                                       const float *__restrict__ Drow,
-                                                       const int32_t *__restrict__ sep_prefix,
-                                                       const int32_t *__restrict__ doc_end,
-                                                       float *__restrict__ dK, float *__restrict__ dV, HeadWin hw) {
-    constexpr int R = D / kWave;
-    int lane = threadIdx.x % kWave;
-    long row = (long)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
-    long n_rows = (long)p.B * p.Hkv * p.L;
-    if (row >= n_rows) return;
-    int j = (int)(row % p.L);
-    int kv = (int)((row / p.L) % p.Hkv);
-    int b = (int)(row / ((long)p.L * p.Hkv));
-    int G = p.Hq / p.Hkv;
-    const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
-    bool always = (j < p.a) || (prefix[j + 1] != prefix[j]);
-    const float *kj = K + row * D;
-    const float *vj = V + row * D;
-    float accK[R], accV[R];
-    for (int r = 0; r < R; ++r) accK[r] = accV[r] = 0.f;
-    for (int g = 0; g < G; ++g) {
-        int h = kv * G + g;
-        // the queries that see key j: up to the end of the sequence (document), or of head h's window
-        long i_end_l = always ? (long)p.L : min((long)p.L, (long)j + p.n - head_delta(hw, h));
-        if (doc_end) i_end_l = min(i_end_l, (long)doc_end[(long)b * p.L + j]);
-        int i_end = (int)i_end_l;
-        long hrow = ((long)b * p.Hq + h) * p.L;
-        const float *Qh = Q + hrow * D;
-        const float *dOh = dO + hrow * D;
-        for (int i0 = j; i0 < i_end; i0 += kWave) {
-            int i = i0 + lane;
-            float pr = 0.f, ds = 0.f;
-            if (i < i_end) {
-                float s = p.scale * dot_row<D>(Qh + (long)i * D, kj);
-                pr = expf(s - LSE[hrow + i]);
-                float dp = dot_row<D>(dOh + (long)i * D, vj);
-                ds = pr * (dp - Drow[hrow + i]);
+    // items [first, last) of the tile's keys, item i = (query block i % n_qb from q_lo on, head i / n_qb), added to ak, av
+    auto run_items = [&](int first, int last, int q_lo, int n_qb, int j, bool valid, int end, bool far) __attribute__((always_inline)) {
+        const int jr = valid ? j : 0;
+        load_row<D>(kf, K + (kvrow0 + jr) * D, g);
+        load_row<D>(vf, V + (kvrow0 + jr) * D, g);
+#pragma unroll
+        for (int c = 0; c < C; ++c) ak[c] = av[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int it = first + wave; it < last; it += kWaves) {
+            const int h = kv * G + it / n_qb, q0 = q_lo + (it % n_qb) * kT;
+            // last query that sees the key: end of the sequence (document), or of head h's window
+            const int hi = valid ? (far ? end : (int)min((long)end, (long)j + p.n - head_delta(hw, h))) - 1 : -1;
+            if (__ballot(hi >= q0) == 0ull) continue;
+            const long hrow = ((long)b * p.Hq + h) * p.L;
+            f32x4 qf[C], gf[C];
+            const long qrow = hrow + min(q0 + m, p.L - 1);
+            load_row<D>(qf, Q + qrow * D, g);
+            load_row<D>(gf, dO + qrow * D, g);
+            int qi[4];
+            float lse[4], Dq[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                qi[i] = min(q0 + 4 * g + i, p.L - 1);
+                lse[i] = LSE[hrow + qi[i]];
+                Dq[i] = Drow[hrow + qi[i]];
             }
-            int cnt = min(kWave, i_end - i0);
-            for (int k = 0; k < cnt; ++k) {
-                float pk = __shfl(pr, k);
-                float dsk = __shfl(ds, k);
-                long ik = i0 + k;
-                for (int r = 0; r < R; ++r) {
-                    accV[r] = fmaf(pk, dOh[ik * D + lane + r * kWave], accV[r]);
-                    accK[r] = fmaf(dsk, Qh[ik * D + lane + r * kWave], accK[r]);
-                }
+            // requested with the rows: one memory round trip per item
+            float gt[C][4], qt[C][4];
+            load_columns<D>(gt, dO + hrow * D, qi, m);
+            load_columns<D>(qt, Q + hrow * D, qi, m);
+            const f32x4 s = row_product<D>(qf, kf), dp = row_product<D>(gf, vf);
+            f32x4 pr, ds;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int q = q0 + 4 * g + i;
+                pr[i] = j <= q && q <= hi ? expf(s[i] * p.scale - lse[i]) : 0.f;
+                ds[i] = pr[i] * (dp[i] - Dq[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int c = 0; c < C; ++c) av[c] = mfma_f32(gt[c][i], pr[i], av[c]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int c = 0; c < C; ++c) ak[c] = mfma_f32(qt[c][i], ds[i], ak[c]);
+        }
+    };
+    // sum over the waves of x (dK or dV of the tile's 16 keys), handed out as out(row, column, four values)
+    auto add_waves = [&](const f32x4 (&x)[C], auto out) __attribute__((always_inline)) {
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < C; ++c) *reinterpret_cast<f32x4 *>(&xs[wave][m][16 * c + 4 * g]) = x[c];
+        __syncthreads();
+        for (int e = threadIdx.x; e < kT * D / 4; e += 64 * kWaves) {
+            const int r = e / (D / 4), col = (e % (D / 4)) * 4;
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) v += *reinterpret_cast<const f32x4 *>(&xs[w][r][col]);
+            out(r, col, v);
+        }
+    };
+
+    if (unit >= wpg) {  // band unit
+        const int j0 = (unit - wpg) * kT, j = j0 + m, jc = min(j, p.L - 1);
+        const bool valid = j < p.L && far_index(fl, prefix, jc) < 0;
+        if (__ballot(valid) == 0ull) return;
+        const int end = dend ? min(dend[jc], p.L) : p.L;
+        const int n_qb = (min(p.L, j0 + kT + p.n - 1) - j0 + kT - 1) / kT;
+        run_items(0, G * n_qb, j0, n_qb, j, valid, end, false);
+        auto finish = [&](float *dst, float f) {
+            return [=](int r, int col, f32x4 v) {
+                if (j0 + r < p.L && far_index(fl, prefix, j0 + r) < 0)
+                    *reinterpret_cast<f32x4 *>(dst + (kvrow0 + j0 + r) * D + col) = v * f;
+            };
+        };
+        add_waves(ak, finish(dK, p.scale));
+        add_waves(av, finish(dV, 1.f));
+        return;
+    }
+
+    const int NFT = (fl.NF + kT - 1) / kT;
+    // lane t of a group of 64 list tiles: first query block and number of items of tile t
+    auto tile_items = [&](int t, int &fq) {
+        fq = 0;
+        if (t >= NFT) return 0;
+        fq = far_pos(fl, t * kT, idx, p.L) & ~(kT - 1);
+        return max(0, G * ((far_last_query(fl, t * kT, idx, p, dend, kT) - fq + kT - 1) / kT));
+    };
+    auto inclusive_scan = [&](int v) {
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int u = __shfl_up(v, off);
+            if (lane >= off) v += u;
+        }
+        return v;
+    };
+    // the first group of 64 list tiles (all of them up to 1024 list entries) is worked out once for both passes
+    int fq, nq = tile_items(lane, fq), inc = inclusive_scan(nq);
+    long total = __shfl(inc, 63);
+    for (int t0 = 64; t0 < NFT; t0 += 64) {
+        int unused;
+        total += __shfl(inclusive_scan(tile_items(t0 + lane, unused)), 63);
+    }
+    const long slices = min((long)wpg, max(1l, total / kMinItems));
+    if (unit >= slices || total == 0) return;
+    const long s0 = unit * total / slices, s1 = (unit + 1) * total / slices;
+    long cum = 0;
+    for (int t0 = 0; t0 < NFT && cum < s1; t0 += 64) {
+        if (t0 > 0) {
+            nq = tile_items(t0 + lane, fq);
+            inc = inclusive_scan(nq);
+        }
+        unsigned long long pend = __ballot(nq > 0 && cum + inc > s0 && cum + inc - nq < s1);
+        for (; pend; pend &= pend - 1) {
+            const int src = __ffsll(pend) - 1, ft = t0 + src, items = __shfl(nq, src), q_lo = __shfl(fq, src);
+            const long F = cum + __shfl(inc, src) - items;  // the tile's first item
+            const int f = ft * kT + m;
+            const bool valid = f < fl.NF;
+            const int j = valid ? far_pos(fl, f, idx, p.L) : 0;
+            const int end = dend ? min(dend[j], p.L) : p.L;
+            run_items((int)(max(s0, F) - F), (int)(min(s1, F + items) - F), q_lo, items / G, j, valid, end, true);
+            // slices w0 .. w1 hold the tile
+            const int w0 = (int)(((F + 1) * slices - 1) / total), w1 = (int)(((F + items) * slices - 1) / total);
+            auto to_row = [&](float *dst, float fac) {
+                return [=](int r, int col, f32x4 v) {
+                    if (ft * kT + r < fl.NF)
+                        *reinterpret_cast<f32x4 *>(dst + (kvrow0 + far_pos(fl, ft * kT + r, idx, p.L)) * D + col) = v * fac;
+                };
+            };
+            if (w0 == w1) {
+                add_waves(ak, to_row(dK, p.scale));
+                add_waves(av, to_row(dV, 1.f));
+                continue;
+            }
+            // slot: [dK rows | dV rows] of 16 keys
+            float *slots = partials + (long)bkv * (wpg + n_far_tiles) * (2 * kT * D);
+            auto slot_of = [=](int w, int which) { return slots + ((long)(w + ft) * 2 + which) * (kT * D); };
+            auto to_slot = [&](int which) {
+                float *dst = slot_of(unit, which);
+                return [=](int r, int col, f32x4 v) { *reinterpret_cast<f32x4 *>(dst + r * D + col) = v; };
+            };
+            add_waves(ak, to_slot(0));
+            add_waves(av, to_slot(1));
+            __threadfence();  // the slot is visible to every workgroup before the count is
+            __syncthreads();
+            if (threadIdx.x == 0) last_s = atomicAdd(&counters[(long)bkv * n_far_tiles + ft], 1) == w1 - w0;
+            __syncthreads();
+            if (!last_s) continue;
+            __threadfence();
+            for (int e = threadIdx.x; e < 2 * kT * D / 4; e += 64 * kWaves) {
+                const int which = e / (kT * D / 4), r = (e / (D / 4)) % kT, col = (e % (D / 4)) * 4;
+                f32x4 v = {0.f, 0.f, 0.f, 0.f};
+                for (int w = w0; w <= w1; ++w) v += *reinterpret_cast<const f32x4 *>(slot_of(w, which) + r * D + col);
+                if (which == 0) to_row(dK, p.scale)(r, col, v);
+                else to_row(dV, 1.f)(r, col, v);
             }
         }
-    }
-    for (int r = 0; r < R; ++r) {
-        dK[row * D + lane + r * kWave] = p.scale * accK[r];
-        dV[row * D + lane + r * kWave] = accV[r];
+        cum += __shfl(inc, 63);
     }
 }
 
-unsigned blocks_for_rows(long n_rows) { return (unsigned)((n_rows + 3) / 4); }
+// backward workspace: D_i [B,Hq,L] | one counter per list tile | the slots of the partial sums
+struct Fp32Workspace {
+    int wpg, n_far_tiles;
+    long n_counters;
+    size_t d_bytes, counter_bytes, total;
+};
+Fp32Workspace fp32_workspace(const sepattn_params &p) {
+    Fp32Workspace w;
+    const long n_bkv = (long)p.B * p.Hkv, wpg = 2 * (long)compute_units() / n_bkv;
+    w.wpg = (int)(wpg < 1 ? 1 : wpg);
+    w.n_far_tiles = (p.a + p.cap + kT - 1) / kT;
+    w.n_counters = n_bkv * w.n_far_tiles;
+    w.d_bytes = align_up((size_t)p.B * p.Hq * p.L * sizeof(float), 256);
+    w.counter_bytes = align_up((size_t)w.n_counters * sizeof(int32_t), 256);
+    w.total = w.d_bytes + w.counter_bytes + (size_t)n_bkv * (w.wpg + w.n_far_tiles) * (2 * kT * p.d) * sizeof(float);
+    return w;
+}
 
 }  // namespace
 
+size_t backward_fp32_workspace(const sepattn_params &p) { return fp32_workspace(p).total; }
+
 int launch_forward_fp32(const sepattn_params &p, const HeadWin &hw, const float *Q, const float *K, const float *V,
-                        const int32_t *sep_idx, const int32_t *sep_prefix, const int32_t *doc_start, float *O,
-                        float *LSE, hipStream_t st) {
-    long n_rows = (long)p.B * p.Hq * p.L;
-    dim3 grid(blocks_for_rows(n_rows)), block(256);
-    if (p.d == 64)
-        hipLaunchKernelGGL(fwd_fp32_kernel<64>, grid, block, 0, st, p, Q, K, V, sep_idx, sep_prefix, doc_start, O, LSE, hw);
-    else
-        hipLaunchKernelGGL(fwd_fp32_kernel<128>, grid, block, 0, st, p, Q, K, V, sep_idx, sep_prefix, doc_start, O, LSE, hw);
+                        const int32_t *sep_idx, const int32_t *sep_prefix, const int32_t *doc_start,
+                        const int32_t *doc_end, float *O, float *LSE, hipStream_t st) {
+    const long tiles = (long)p.B * p.Hq * ((p.L + kT - 1) / kT);
+    if (tiles > 0x7FFFFFFFL) return SEPATTN_ERR_SHAPE;
+    auto kernel = p.d == 64 ? fwd_fp32_kernel<64> : fwd_fp32_kernel<128>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * kWaves), 0, st, p, Q, K, V, sep_idx, sep_prefix, doc_start,
+                       doc_end, O, LSE, hw);
     return launch_status();
 }
 
 int launch_backward_fp32(const sepattn_params &p, const HeadWin &hw, const float *Q, const float *K, const float *V,
                          const float *O, const float *LSE, const float *dO, const int32_t *sep_idx,
                          const int32_t *sep_prefix, const int32_t *doc_start, const int32_t *doc_end, float *dQ,
-                         float *dK, float *dV, float *Dws, hipStream_t st) {
-    long q_rows = (long)p.B * p.Hq * p.L, k_rows = (long)p.B * p.Hkv * p.L;
-    dim3 block(256);
-    if (p.d == 64) {
-        hipLaunchKernelGGL(rowdot_fp32_kernel<64>, dim3(blocks_for_rows(q_rows)), block, 0, st, q_rows, dO, O, Dws);
-        hipLaunchKernelGGL(dq_fp32_kernel<64>, dim3(blocks_for_rows(q_rows)), block, 0, st, p, Q, K, V, LSE, dO, Dws, sep_idx, sep_prefix, doc_start, dQ, hw);
-        hipLaunchKernelGGL(dkv_fp32_kernel<64>, dim3(blocks_for_rows(k_rows)), block, 0, st, p, Q, K, V, LSE, dO, Dws, sep_prefix, doc_end, dK, dV, hw);
-    } else {
-        hipLaunchKernelGGL(rowdot_fp32_kernel<128>, dim3(blocks_for_rows(q_rows)), block, 0, st, q_rows, dO, O, Dws);
-        hipLaunchKernelGGL(dq_fp32_kernel<128>, dim3(blocks_for_rows(q_rows)), block, 0, st, p, Q, K, V, LSE, dO, Dws, sep_idx, sep_prefix, doc_start, dQ, hw);
-        hipLaunchKernelGGL(dkv_fp32_kernel<128>, dim3(blocks_for_rows(k_rows)), block, 0, st, p, Q, K, V, LSE, dO, Dws, sep_prefix, doc_end, dK, dV, hw);
-    }
+                         float *dK, float *dV, void *ws, hipStream_t st) {
+    const Fp32Workspace w = fp32_workspace(p);
+    char *base = static_cast<char *>(ws);
+    float *Dws = reinterpret_cast<float *>(base);
+    int32_t *counters = reinterpret_cast<int32_t *>(base + w.d_bytes);
+    float *partials = reinterpret_cast<float *>(base + w.d_bytes + w.counter_bytes);
+    const long tiles = (p.L + kT - 1) / kT, q_tiles = (long)p.B * p.Hq * tiles, k_units = (long)p.B * p.Hkv * (w.wpg + tiles);
+    if (q_tiles > 0x7FFFFFFFL || k_units > 0x7FFFFFFFL) return SEPATTN_ERR_SHAPE;
+    const dim3 block(64 * kWaves);
+    auto dq = p.d == 64 ? dq_fp32_kernel<64> : dq_fp32_kernel<128>;
+    hipLaunchKernelGGL(dq, dim3((unsigned)q_tiles), block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start,
+                       doc_end, dQ, Dws, counters, w.n_counters, hw);
+    if (hipGetLastError() != hipSuccess) return SEPATTN_ERR_HIP;
+    auto dkv = p.d == 64 ? dkv_fp32_kernel<64> : dkv_fp32_kernel<128>;
+    hipLaunchKernelGGL(dkv, dim3((unsigned)k_units), block, 0, st, p, Q, K, V, LSE, dO, Dws, sep_idx, sep_prefix, doc_end, dK,
+                       dV, partials, counters, w.n_far_tiles, w.wpg, hw);
     return launch_status();
 }
 

@@ -1,0 +1,45 @@
+"""Forward and backward at the edges of what the attention kernels' launchers decide (tiles, slices of the
+far keys' work, workgroup shapes), against the oracle.  Needs an MI355X."""
+import math
+
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+from test_gpu_parity import assert_close, assert_grads_close, dev, gpu_index, host, make_case
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def run(B, Hq, Hkv, L, d, a, n, p, dtype, seed=1):
+    """n: a window, or a list with one window per query head."""
+    import paper_2412_12094_amd as sp
+
+    tok, Q, K, V, dO = make_case(B, Hq, Hkv, L, d, p, dtype, seed)
+    scale = 1.0 / math.sqrt(d)
+    flags = oracle.mark_separators(tok, wl.SEPARATOR_IDS)
+    q, k, v, do = (dev(x, dtype) for x in (Q, K, V, dO))
+    _, idx, cnt, pre = gpu_index(sp, tok)
+    heads = isinstance(n, list)
+    fwd, bwd = (sp.sepattn_forward_headwise, sp.sepattn_backward_headwise) if heads else (sp.sepattn_forward, sp.sepattn_backward)
+    O, LSE = fwd(q, k, v, idx, cnt, pre, a, n, scale)
+    grads = bwd(q, k, v, O, LSE, do, idx, cnt, pre, a, n, scale)
+    torch.cuda.synchronize()
+    rO, rL = oracle.forward(Q, K, V, flags, a, n, scale)
+    refs = oracle.backward(Q, K, V, dO, flags, a, n, scale, return_term_rss=True)
+    assert_close(host(O), rO, dtype, "O")
+    assert np.abs(host(LSE) - rL).max() <= (1e-4 if dtype == "fp32" else 2e-3)
+    assert_grads_close(grads, refs, dtype)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,d,a,n,p", [
+    (1, 1, 1, 1, 64, 0, 1, 0.0),       # one query
+    (2, 2, 1, 16, 128, 3, 4, 0.3),     # exactly one tile
+    (1, 3, 1, 17, 64, 1, 40, 1.0),     # one row in the second tile; every key on the far list
+    (1, 8, 2, 600, 128, 4, 8, 0.15),   # list tiles spread over several slices
+    (3, 4, 4, 333, 64, 0, 16, 0.02),   # fewer items than one slice per list tile
+])
+def test_fp32_tiles_and_slices(B, Hq, Hkv, L, d, a, n, p):
+    run(B, Hq, Hkv, L, d, a, n, p, "fp32")
