@@ -35,6 +35,26 @@ __device__ inline TileGroup xcd_tile_group(int id, int n_tiles, int n_groups) {
     return r;
 }
 
+// Shape of a forward / dQ workgroup: nw waves of 32 query rows each, gp query heads of one KV head packed into
+// the rows, i.e. 32 nw / gp positions.  Fewer positions mean fewer keys that only some rows see (a tile
+// streams the window of its first row AND its own length), more heads mean fewer tiles.
+//   Four waves, so that two (d = 64: three) independent workgroups share a compute unit: one's segment change, row
+//     stores and barriers overlap the others' matrix work, and the split of a group is finer.
+//   Seven heads per KV head: seven waves, one head each (one head per workgroup streamed 456 band keys for a
+//     window of 200; seven stream 232: B=3, L=3077, d=128 forward 113 -> 72 us).
+//   Eight waves at d = 128 with four heads where the work is large (eight rounds of four-wave workgroups per compute
+//     unit and more): half the tile loads per matrix instruction (L = 64K: 3.67 ms against 4.0; level at L = 4096).
+struct QueryShape {
+    int gp, nw;
+};
+inline QueryShape query_shape(const sepattn_params &p) {
+    const int G = p.Hq / p.Hkv;
+    if (G % 7 == 0) return {7, 7};
+    const int gp = G % 4 == 0 ? 4 : (G % 2 == 0 ? 2 : 1);
+    const long tiles = (long)p.B * p.Hkv * (G / gp) * (((long)p.L * gp + 127) / 128);  // of four waves
+    return {gp, p.d == 128 && gp == 4 && tiles >= 8l * compute_units() ? 8 : 4};
+}
+
 struct Stream {
     int n_init, n_dense, n_total, sep_lo, bs;
 };
@@ -93,21 +113,7 @@ __device__ inline int stream_key(const Stream &s, int k, const sepattn_params &p
     return j;
 }
 
-// how a wave treats a block of 32 stream elements starting at k0, given its rows [pw, pw+31]:
-// 0 = skip (nothing visible), 1 = everything visible, 2 = test each pair
-__device__ inline int block_mode(const Stream &st, int k0, int pw, int n) {
-    int pmax = pw + 31;
-    if (k0 + 32 <= st.n_dense) return 1;
-    if (k0 >= st.n_dense) {
-        int jmin = st.bs + (k0 - st.n_dense), jmax = jmin + 31;
-        if (k0 >= st.n_total || jmin > pmax) return 0;
-        if (k0 + 32 <= st.n_total && jmax <= pw && jmin + n - 1 >= pmax) return 1;
-        return 2;
-    }
-    return 2;
-}
-
-// The same decision for "every pair of the block is visible" (mode 1), reduced to three comparisons
+// Whether every pair of a block of 32 stream elements is visible to a wave with rows [pw, pw+31], as three comparisons
 // against thresholds that are computed once per wave: a block of 32 stream elements starting at k0
 // needs no mask test iff it lies in the dense part (k0 <= dense_last) or is a band block whose keys
 // are inside every row's window and not in any row's future (band_first <= k0 <= band_last).

@@ -43,3 +43,16 @@ def run(B, Hq, Hkv, L, d, a, n, p, dtype, seed=1):
 ])
 def test_fp32_tiles_and_slices(B, Hq, Hkv, L, d, a, n, p):
     run(B, Hq, Hkv, L, d, a, n, p, "fp32")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,Hq,Hkv,L,a,n,p", [
+    (1, 7, 1, 33, 2, 5, 0.1),      # seven heads: one position in the second tile
+    (2, 14, 2, 450, 4, 100, 0.1),  # seven heads, several segments and tiles; an odd number of blocks
+    (1, 8, 1, 257, 0, 64, 0.2),    # eight heads: two groups of four
+    (1, 2, 1, 65, 3, 200, 0.0),    # two heads; the window covers everything
+    (1, 3, 3, 129, 1, 1, 0.3),     # one head; one position in the second tile; the smallest window
+    (4, 8, 2, 128, 4, 32, 0.1),    # streams that end with a full block
+])
+def test_bf16_workgroup_shapes(B, Hq, Hkv, L, d, a, n, p):
+    run(B, Hq, Hkv, L, d, a, n, p, "bf16")
