@@ -14,6 +14,7 @@
 #include "bwd_common.h"
 #include "mfma_common.h"
 #include "key_stream.h"
+#include "work_share.h"
 
 namespace sepattn {
 
@@ -56,7 +57,7 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     const uint16_t *__restrict__ dO, const int32_t *__restrict__ sep_idx,
     const int32_t *__restrict__ sep_prefix, const int32_t *__restrict__ doc_start,
     const int32_t *__restrict__ doc_end, uint16_t *__restrict__ dQ, float *__restrict__ Dws,
-    float *__restrict__ Lws, int wpg, HeadWin hw) {
+    float *__restrict__ Lws, int wpg, HeadWin hw, WorkShare share) {
     constexpr int TP = 32 * NW / GP;
     constexpr int CH = D / 8;
     constexpr int RPL = 64 / CH;
@@ -92,13 +93,23 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     // workgroups per group; rank 0 is the last tile, the one with the longest key stream.
     const int G = p.Hq / p.Hkv, groups = G / GP;
     const int n_pos_tiles = (p.L + TP - 1) / TP;
-    const TileGroup tg = xcd_tile_group(blockIdx.x, wpg, p.B * p.Hkv * groups);
+    TileGroup tg;
+    if (share.n) {  // head-wise windows: see work_share.h
+        const ShareOf s = share_of(share, blockIdx.x, p.B);
+        tg.rank = s.rank;
+        tg.group = s.b * p.Hkv * groups + share.group[s.pos];
+        wpg = s.count;
+    } else {
+        tg = xcd_tile_group(blockIdx.x, wpg, p.B * p.Hkv * groups);
+    }
     int y = tg.group;
     const int hg = y % groups;
     const int kv = (y / groups) % p.Hkv;
     const int b = y / (groups * p.Hkv);
     const int head = kv * G + hg * GP + (wave % GP);
-    const int hdelta = head_delta(hw, head);  // head-wise windows: see the forward kernel
+    const int gdelta = group_delta(hw, kv * G + hg * GP, GP);  // head-wise windows: see the forward kernel
+    p.n -= gdelta;
+    const int hdelta = head_delta(hw, head) - gdelta;
 
     const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
     const int32_t *idx = sep_idx + (long)b * p.cap;
@@ -538,17 +549,23 @@ int launch_bwd(const sepattn_params &p, const uint16_t *Q, const uint16_t *K, co
     int wpg = (int)((8 / NWr) * (long)compute_units() / n_groups);
     wpg = wpg < 1 ? 1 : (wpg > n_pos_tiles ? n_pos_tiles : wpg);
     if (n_groups * wpg > 0x7FFFFFFFL) return SEPATTN_ERR_SHAPE;
-    dim3 grid((unsigned)(n_groups * wpg)), block(64 * NWr);
+    WorkShare share = {};
+    long n_wg = n_groups * wpg;
+    if (any_delta(hw)) {
+        share = share_out(p, hw, GP, (8 / NWr) * compute_units() / p.B, n_pos_tiles, [&](int n, bool) { return query_cost(p, TP, n); });
+        n_wg = (long)p.B * share.first[share.n];
+    }
+    dim3 grid((unsigned)n_wg), block(64 * NWr);
     {
     ProfScope prof(SEPATTN_K_BWD_DQ, st);
     auto go = [&](auto NW_) {
         constexpr int NW = decltype(NW_)::value;
         if (GP == 4)
-            hipLaunchKernelGGL((dq_kernel<D, 4, DOCS, NW>), grid, block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, Lws, wpg, hw);
+            hipLaunchKernelGGL((dq_kernel<D, 4, DOCS, NW>), grid, block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, Lws, wpg, hw, share);
         else if (GP == 2)
-            hipLaunchKernelGGL((dq_kernel<D, 2, DOCS, NW>), grid, block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, Lws, wpg, hw);
+            hipLaunchKernelGGL((dq_kernel<D, 2, DOCS, NW>), grid, block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, Lws, wpg, hw, share);
         else
-            hipLaunchKernelGGL((dq_kernel<D, 1, DOCS, NW>), grid, block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, Lws, wpg, hw);
+            hipLaunchKernelGGL((dq_kernel<D, 1, DOCS, NW>), grid, block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, Lws, wpg, hw, share);
     };
     if constexpr (D == 64) {
         if (narrow) go(IntC<4>{});

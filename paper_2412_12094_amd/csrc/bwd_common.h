@@ -85,8 +85,14 @@ inline BwdWorkspace bwd_workspace(const sepattn_params &p) {
 struct FarList {
     int a_eff, sep_base, NF;
 };
-__device__ inline FarList far_list(const sepattn_params &p, const int32_t *__restrict__ prefix) {
+// every_key: the list of all keys (see dkv_kernel), which far_pos and far_index treat as initial tokens
+__device__ inline FarList far_list(const sepattn_params &p, const int32_t *__restrict__ prefix, bool every_key = false) {
     FarList f;
+    if (every_key) {
+        f.a_eff = f.NF = p.L;
+        f.sep_base = 0;
+        return f;
+    }
     f.a_eff = p.a;  // already clamped to L by the host
     f.sep_base = prefix[f.a_eff];
     int cnt = min(prefix[p.L], p.cap);

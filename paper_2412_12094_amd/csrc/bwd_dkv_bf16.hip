@@ -33,6 +33,7 @@
 // as many query tiles.
 #include "bwd_common.h"
 #include "mfma_common.h"
+#include "work_share.h"
 
 
 namespace sepattn {
@@ -48,12 +49,22 @@ __device__ inline int wave_max_i(int v) {
     return v;
 }
 
+// First partial row of a KV head whose workgroups are dealt by work: slots for its workgroups and list tiles, then one
+// band row per list entry, one KV head after the other.  The workgroups of a batch row are no more than with an
+// even deal, so this fits the same workspace.
+__device__ inline long shared_part_row(const FarGeom &even, const WorkShare &w, const ShareOf &s, const sepattn_params &p) {
+    return (long)s.b * p.Hkv * even.rows + (long)w.first[s.pos] * even.bk + (long)s.pos * ((long)even.NFTcap * even.bk + even.NFcap);
+}
+
 // DOCS: packed documents (doc_end [B, L]: one past the last position of each position's document;
 // p.a == 0, the documents' initial tokens are list entries): a key's query range ends with its
 // document, and the far pieces of a list tile end with the document of the tile's last entry.
-// HW: head-wise windows.  p.n is the largest window: it fixes the far / band split and the schedule;
-// in a band unit a key that is neither an initial token nor a separator is visible to query i of head
-// h only while i <= j + p.n - 1 - delta[h] (a third comparison in the blocks that need the mask test).
+// HW: head-wise windows.  p.n becomes the largest window of the KV head's query heads: it fixes the far / band
+// split and the schedule; in a band unit a key that is neither an initial token nor a separator is visible to
+// query i of head h only while i <= j + p.n - 1 - delta[h] (a third comparison in the blocks that need the mask
+// test).  A KV head whose heads all see every earlier key has no band: its list is that of ALL keys and its far
+// pairs are i >= j, so that this work is cut into equal slices too (as a
+// band unit the first keys' walk through the whole sequence is one workgroup's).  The workgroups are dealt to the KV heads by their work (work_share.h).
 template <int D, bool DOCS, bool HW, int KW>
 __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv_kernel(
     sepattn_params p, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
@@ -62,7 +73,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
     const int32_t *__restrict__ sep_prefix, const int32_t *__restrict__ doc_end,
     uint16_t *__restrict__ dK, uint16_t *__restrict__ dV,
     float *__restrict__ farK, float *__restrict__ farV, int32_t *__restrict__ piece_tab, int wpg, int n_band,
-    HeadWin hw) {
+    HeadWin hw, WorkShare share) {
     constexpr int NW = 2 * KW;               // waves per workgroup
     constexpr int BK = 32 * KW;              // keys per workgroup
     constexpr int CH = D / 8;                // 16-byte chunks per row
@@ -95,7 +106,21 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
     // 1-D grid: consecutive workgroups belong to consecutive (batch, KV head) pairs, so with 8 KV heads
     // each head's K, V, Q, dO rows stay in the L2 of one XCD.
     const int n_bkv = p.B * p.Hkv;
-    const int bkv = blockIdx.x % n_bkv, w_id = blockIdx.x / n_bkv;
+    int bkv = blockIdx.x % n_bkv, w_id = blockIdx.x / n_bkv;
+    long part0 = bkv * far_geom(p, wpg, KW).rows;  // first partial row of the (batch, KV head)
+    int gdelta = 0;
+    bool every_key = false;
+    if constexpr (HW) {
+        const ShareOf s = share_of(share, blockIdx.x, p.B);
+        bkv = s.b * p.Hkv + share.group[s.pos];
+        part0 = shared_part_row(far_geom(p, wpg, KW), share, s, p);
+        w_id = s.rank;
+        wpg = s.count;
+        gdelta = group_delta(hw, (bkv % p.Hkv) * G, G);
+        every_key = share.all[s.pos] != 0;
+        p.n = every_key ? 0 : p.n - gdelta;
+        if (every_key) n_band = 0;
+    }
     const int kv = bkv % p.Hkv, b = bkv / p.Hkv;
     const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
     const int32_t *idx = sep_idx + (long)b * p.cap;
@@ -103,7 +128,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
     const long kvrow0 = ((long)b * p.Hkv + kv) * (long)p.L;
     const float sl2 = p.scale * kLog2e_f;
     const FarGeom fg = far_geom(p, wpg, KW);
-    const FarList fl = far_list(p, prefix);
+    const FarList fl = far_list(p, prefix, every_key);
     const int a_row = pi_row(kj);
     const int my_pc = lane % CH, my_sub = lane / CH;
     // Per-lane byte offsets of the operand fragments inside a tile, computed once.  The first
@@ -392,7 +417,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
                 // the head's delta: the table is indexed with wave-uniform numbers only
                 const int hd = step_head;
                 for (int g = 0; g < G; ++g) {
-                    const int sd = head_delta(hw, kv * G + g);
+                    const int sd = head_delta(hw, kv * G + g) - gdelta;
                     dl = (!FAR && hd == g) ? sd : dl;
                 }
             }
@@ -675,7 +700,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         }
         if (valid) {
             if (to_partial) {
-                const long prow = ((long)bkv * fg.rows + part_row) * D;
+                const long prow = (part0 + part_row) * D;
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -710,13 +735,27 @@ __global__ __launch_bounds__(256) void dkv_combine_kernel(sepattn_params p, cons
                                                           uint16_t *__restrict__ dK, uint16_t *__restrict__ dV,
                                                           const float *__restrict__ farK,
                                                           const float *__restrict__ farV,
-                                                          const int32_t *__restrict__ piece_tab, int wpg, int kw) {
+                                                          const int32_t *__restrict__ piece_tab, int wpg, int kw,
+                                                          HeadWin hw, WorkShare share) {
     constexpr int TPR = D / 4;  // threads per row
-    const int bkv = blockIdx.y, kv = bkv % p.Hkv, b = bkv / p.Hkv;
+    int bkv = blockIdx.y;
+    long base = bkv * far_geom(p, wpg, kw).rows;
+    bool every_key = false;
+    if (share.n) {  // as in dkv_kernel
+        ShareOf s;
+        s.b = bkv / p.Hkv;
+        s.pos = bkv % p.Hkv;
+        bkv = s.b * p.Hkv + share.group[s.pos];
+        base = shared_part_row(far_geom(p, wpg, kw), share, s, p);
+        wpg = share.first[s.pos + 1] - share.first[s.pos];
+        every_key = share.all[s.pos] != 0;
+        p.n = every_key ? 0 : p.n - group_delta(hw, (bkv % p.Hkv) * (p.Hq / p.Hkv), p.Hq / p.Hkv);
+    }
+    const int kv = bkv % p.Hkv, b = bkv / p.Hkv;
     const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
     const int32_t *idx = sep_idx + (long)b * p.cap;
     const FarGeom fg = far_geom(p, wpg, kw);
-    const FarList fl = far_list(p, prefix);
+    const FarList fl = far_list(p, prefix, every_key);
     const int f = (blockIdx.x * 256 + threadIdx.x) / TPR, col = ((blockIdx.x * 256 + threadIdx.x) % TPR) * 4;
     if (f >= fl.NF) return;
     const int lt = fg.bk;  // entries per list tile
@@ -728,14 +767,16 @@ __global__ __launch_bounds__(256) void dkv_combine_kernel(sepattn_params p, cons
     const int32_t *tab = piece_tab + ((long)bkv * fg.NFTcap + ft) * 2;
     // the clamps keep a table that the far pass did not write (it always does) from faulting
     const int w0 = min(max(tab[0], 0), wpg - 1), w1 = min(max(tab[1], w0), wpg - 1);
-    const long base = (long)bkv * fg.rows;
     float4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
     // the band partial and eight pieces at a time (clamped slots) are requested together, so that a
     // list tile with up to eight pieces costs one memory round trip; the sum runs in slot order
     constexpr int NB = 8;
     const long brow = (base + (long)fg.NP * lt + f) * D + col;
-    const float4 bk = *reinterpret_cast<const float4 *>(farK + brow);
-    const float4 bv = *reinterpret_cast<const float4 *>(farV + brow);
+    float4 bk = {0.f, 0.f, 0.f, 0.f}, bv = {0.f, 0.f, 0.f, 0.f};
+    if (!every_key) {
+        bk = *reinterpret_cast<const float4 *>(farK + brow);
+        bv = *reinterpret_cast<const float4 *>(farV + brow);
+    }
     for (int w = w0; w <= w1; w += NB) {
         float4 pk[NB], pv[NB];
 #pragma unroll
@@ -764,18 +805,18 @@ template <int D, int KW>
 void launch_dkv_shape(const sepattn_params &p, const HeadWin &hw, bool headwise, const uint16_t *Q, const uint16_t *K,
                       const uint16_t *V, const float *lse2, const uint16_t *dO, const float *Dws, const int32_t *sep_idx,
                       const int32_t *sep_prefix, const int32_t *doc_end, uint16_t *dK, uint16_t *dV, float *farK,
-                      float *farV, int32_t *piece_tab, int wpg, hipStream_t st) {
+                      float *farV, int32_t *piece_tab, int wpg, const WorkShare &share, hipStream_t st) {
     const int band_grid = (p.L + 32 * KW - 1) / (32 * KW);
-    const dim3 grid((unsigned)((long)wpg * p.B * p.Hkv)), block(128 * KW);
+    const dim3 grid((unsigned)(headwise ? (long)p.B * share.first[share.n] : (long)wpg * p.B * p.Hkv)), block(128 * KW);
     if (doc_end)
         hipLaunchKernelGGL((dkv_kernel<D, true, false, KW>), grid, block, 0, st, p, Q, K, V, lse2, dO, Dws, sep_idx,
-                           sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, band_grid, hw);
+                           sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, band_grid, hw, share);
     else if (headwise)
         hipLaunchKernelGGL((dkv_kernel<D, false, true, KW>), grid, block, 0, st, p, Q, K, V, lse2, dO, Dws, sep_idx,
-                           sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, band_grid, hw);
+                           sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, band_grid, hw, share);
     else
         hipLaunchKernelGGL((dkv_kernel<D, false, false, KW>), grid, block, 0, st, p, Q, K, V, lse2, dO, Dws, sep_idx,
-                           sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, band_grid, hw);
+                           sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, band_grid, hw, share);
 }
 
 template <int D>
@@ -787,19 +828,31 @@ int launch_dkv(const sepattn_params &p, const HeadWin &hw, bool headwise, const 
     const int wpg = dkv_workgroups_per_head(p, kw);
     const FarGeom fg = far_geom(p, wpg, kw);
     if ((long)wpg * p.B * p.Hkv > 0x7FFFFFFFL) return SEPATTN_ERR_SHAPE;
+    WorkShare share = {};
+    if (headwise) {
+        const int G = p.Hq / p.Hkv;
+        // pairs multiplied, and the start of a piece as 320 / G queries
+        share = share_out(p, hw, G, wpg * p.Hkv, kIntMax, [&](int n, bool all) {
+            const double L = p.L, out = L - n;
+            return all ? L * L / 2 : L * (n + fg.bk + 320. / G) + kSepShare * out * out / 2;
+        });
+        // the list of all keys has to fit where the far list does
+        if (p.cap + p.a < p.L)
+            for (int i = 0; i < share.n; ++i) share.all[i] = 0;
+    }
     {
         ProfScope prof(SEPATTN_K_BWD_DKV, st);
         // the eight-wave shape exists for d = 128 only (dkv_key_blocks)
         if (D == 128 && kw == 4)
-            launch_dkv_shape<128, 4>(p, hw, headwise, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, st);
+            launch_dkv_shape<128, 4>(p, hw, headwise, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, share, st);
         else
-            launch_dkv_shape<D, 2>(p, hw, headwise, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, st);
+            launch_dkv_shape<D, 2>(p, hw, headwise, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, share, st);
     }
     if (hipGetLastError() != hipSuccess) return SEPATTN_ERR_HIP;
     ProfScope prof(SEPATTN_K_BWD_COMBINE, st);
     const int rows_per_block = 256 / (D / 4);
     hipLaunchKernelGGL((dkv_combine_kernel<D>), dim3((fg.NFcap + rows_per_block - 1) / rows_per_block, p.B * p.Hkv),
-                       dim3(256), 0, st, p, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, kw);
+                       dim3(256), 0, st, p, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, kw, hw, share);
     return launch_status();
 }
 
@@ -809,8 +862,7 @@ int launch_dkv_bf16(const sepattn_params &p, const HeadWin &hw, const uint16_t *
                     const float *lse2, const uint16_t *dO, const float *Dws, const int32_t *sep_idx,
                     const int32_t *sep_prefix, const int32_t *doc_end, uint16_t *dK, uint16_t *dV, float *farK,
                     float *farV, int32_t *piece_tab, hipStream_t st) {
-    bool headwise = false;
-    for (int h = 0; h < kMaxHeadwise; ++h) headwise = headwise || hw.delta[h] != 0;
+    const bool headwise = any_delta(hw);
     if (p.d == 64)
         return launch_dkv<64>(p, hw, headwise, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, st);
     return launch_dkv<128>(p, hw, headwise, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, st);

@@ -41,12 +41,12 @@ struct ProfScope {
     ~ProfScope() { profile_mark(kernel, st, true); }
 };
 
-// Head-wise neighbour windows (the head-wise variant of Sec. 4.6): every attention kernel runs with
-// p.n = the LARGEST window of the call and gets, by value, how much shorter each query head's own
-// window is.  The key streams and the far / band split are those of the largest window (so heads
-// that share K/V tiles still share them); only the visibility test of a band key uses the head's
-// own window:  key j, not an initial token or a separator, is visible to query i of head h iff
-// j <= i <= j + p.n - 1 - delta[h].  All zeros for an ordinary call.
+// Head-wise neighbour windows (the head-wise variant of Sec. 4.6): every attention kernel is given
+// p.n = the LARGEST window of the call and, by value, how much shorter each query head's own window
+// is.  The key streams and the far / band split of a group of heads that share K/V tiles are those of
+// the group's largest window (work_share.h); within it only the visibility test of a band key uses
+// the head's own window:  key j, not an initial token or a separator, is visible to query i of head
+// h iff j <= i <= j + p.n - 1 - delta[h].  All zeros for an ordinary call.
 constexpr int kMaxHeadwise = SEPATTN_MAX_HEADWISE_HEADS;
 struct HeadWin {
     int32_t delta[kMaxHeadwise];

@@ -25,6 +25,7 @@
 #include "common.h"
 #include "mfma_common.h"
 #include "key_stream.h"
+#include "work_share.h"
 
 
 namespace sepattn {
@@ -41,7 +42,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     sepattn_params p, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     const uint16_t *__restrict__ V, const int32_t *__restrict__ sep_idx,
     const int32_t *__restrict__ sep_prefix, const int32_t *__restrict__ doc_start,
-    const int32_t *__restrict__ doc_end, uint16_t *__restrict__ O, float *__restrict__ LSE, int wpg, HeadWin hw) {
+    const int32_t *__restrict__ doc_end, uint16_t *__restrict__ O, float *__restrict__ LSE, int wpg, HeadWin hw, WorkShare share) {
     constexpr int TP = 32 * NW / GP;  // query positions per workgroup
     constexpr int CH = D / 8;         // 16-byte chunks per row
     constexpr int RPL = 64 / CH;      // rows covered by one wave-wide 1 KB load
@@ -75,16 +76,26 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     // unequal workgroups and most of the per-tile start-up cost are paid once per workgroup.
     const int G = p.Hq / p.Hkv, groups = G / GP;
     const int n_pos_tiles = (p.L + TP - 1) / TP;
-    const TileGroup tg = xcd_tile_group(blockIdx.x, wpg, p.B * p.Hkv * groups);
+    TileGroup tg;
+    if (share.n) {  // head-wise windows: see work_share.h
+        const ShareOf s = share_of(share, blockIdx.x, p.B);
+        tg.rank = s.rank;
+        tg.group = s.b * p.Hkv * groups + share.group[s.pos];
+        wpg = s.count;
+    } else {
+        tg = xcd_tile_group(blockIdx.x, wpg, p.B * p.Hkv * groups);
+    }
     int y = tg.group;
     const int hg = y % groups;
     const int kv = (y / groups) % p.Hkv;
     const int b = y / (groups * p.Hkv);
     const int head = kv * G + hg * GP + (wave % GP);
-    // head-wise windows: the stream is that of the largest window p.n; this head's window is shorter by
-    // hdelta, which only enters the visibility test of band keys (hi was computed with p.n) and the
-    // decision which blocks need no test
-    const int hdelta = head_delta(hw, head);
+    // head-wise windows: the stream is that of the largest window of the group's heads (p.n from here on); this
+    // head's window is shorter by hdelta, which only enters the visibility test of band keys (hi was computed
+    // with p.n) and the decision which blocks need no test
+    const int gdelta = group_delta(hw, kv * G + hg * GP, GP);
+    p.n -= gdelta;
+    const int hdelta = head_delta(hw, head) - gdelta;
 
     const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
     const int32_t *idx = sep_idx + (long)b * p.cap;
@@ -536,11 +547,18 @@ int launch_fwd(const sepattn_params &p, const uint16_t *Q, const uint16_t *K, co
     int wpg = (int)((shape.nw > 4 ? 1 : D == 64 ? 3 : 2) * (long)compute_units() / n_groups);
     wpg = wpg < 1 ? 1 : (wpg > n_pos_tiles ? n_pos_tiles : wpg);
     if (n_groups * wpg > 0x7FFFFFFFL) return SEPATTN_ERR_SHAPE;
-    dim3 grid((unsigned)(n_groups * wpg)), block(64 * shape.nw);
+    WorkShare share = {};
+    long n_wg = n_groups * wpg;
+    if (any_delta(hw)) {
+        share = share_out(p, hw, shape.gp, (shape.nw > 4 ? 1 : D == 64 ? 3 : 2) * compute_units() / p.B, n_pos_tiles,
+                          [&](int n, bool) { return query_cost(p, TP, n); });
+        n_wg = (long)p.B * share.first[share.n];
+    }
+    dim3 grid((unsigned)n_wg), block(64 * shape.nw);
     {
     ProfScope prof(SEPATTN_K_FORWARD, st);
     auto go = [&](auto NW_, auto GP_) {
-        hipLaunchKernelGGL((fwd_bf16_kernel<D, decltype(GP_)::value, DOCS, decltype(NW_)::value>), grid, block, 0, st, p, Q, K, V, sep_idx, sep_prefix, doc_start, doc_end, O, LSE, wpg, hw);
+        hipLaunchKernelGGL((fwd_bf16_kernel<D, decltype(GP_)::value, DOCS, decltype(NW_)::value>), grid, block, 0, st, p, Q, K, V, sep_idx, sep_prefix, doc_start, doc_end, O, LSE, wpg, hw, share);
     };
     if (shape.gp == 7) go(IntC<7>{}, IntC<7>{});
     else if (D == 128 && shape.nw == 8) go(IntC<D == 128 ? 8 : 4>{}, IntC<4>{});

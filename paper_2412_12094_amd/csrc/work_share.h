@@ -1,0 +1,104 @@
+// How the workgroups of a head-wise call are dealt out to its groups of heads (the heads that share K/V tiles).
+//
+// A group runs with the largest window among ITS heads, so the groups' work differs by up to L / n: with heads that
+// see everything next to heads with a window of 128, an even deal leaves all but the longest groups' workgroups
+// idle, and running every group with the call's largest window made each as long as the longest (32/8 heads,
+// d = 128, L = 4096, every fourth KV head full, the others 128: forward 180 -> 102 us, dQ 228 -> 170, dK/dV 581 -> 170,
+// what is left in the first two being the last query tile, whose stream no deal shortens).  Workgroups are dealt in proportion to the work instead, the longest groups first in dispatch order, so that two of them share a
+// compute unit only when there are more long workgroups than compute units.
+#pragma once
+
+#include "common.h"
+
+namespace sepattn {
+
+// groups of one batch row in order of falling work: `group[i]` owns the workgroups first[i] .. first[i+1]-1 of the row
+struct WorkShare {
+    int32_t n;  // number of groups; 0: an ordinary call, every group gets the same number
+    int32_t first[kMaxHeadwise + 1];
+    int32_t group[kMaxHeadwise];
+    int32_t all[kMaxHeadwise];  // every head of the group sees every earlier key
+};
+
+struct ShareOf {
+    int b, pos, rank, count;  // batch row, index into the tables, workgroup's number within its group and their number
+};
+__device__ inline ShareOf share_of(const WorkShare &w, int id, int B) {
+    ShareOf s;
+    s.b = id % B;
+    const int r = id / B;
+    int lo = 0, hi = w.n;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (w.first[mid] <= r) lo = mid;
+        else hi = mid;
+    }
+    s.pos = lo;
+    s.rank = r - w.first[lo];
+    s.count = w.first[lo + 1] - w.first[lo];
+    return s;
+}
+
+// how much shorter than p.n the largest window of the heads h0 .. h0 + n - 1 is
+__host__ __device__ inline int group_delta(const HeadWin &hw, int h0, int n) {
+    int d = head_delta(hw, h0);
+    for (int i = 1; i < n; ++i) d = head_delta(hw, h0 + i) < d ? head_delta(hw, h0 + i) : d;
+    return d;
+}
+
+inline bool any_delta(const HeadWin &hw) {
+    for (int h = 0; h < kMaxHeadwise; ++h)
+        if (hw.delta[h]) return true;
+    return false;
+}
+
+// share of the keys that are separators, for the estimate of a group's work only (the count is on the device): text
+// holds about one in ten
+constexpr double kSepShare = 0.1;
+
+// Deals `slots` workgroups of a batch row to n groups of `heads` query heads each, in proportion to cost(window) and
+// between 1 and cap per group (what a capped group leaves goes to those after it).  More groups than slots get one
+// each, the longest ones dispatched first.
+template <typename Cost>
+inline WorkShare share_out(const sepattn_params &p, const HeadWin &hw, int heads, int slots, int cap, Cost cost) {
+    WorkShare w;
+    w.n = p.Hq / heads;
+    double c[kMaxHeadwise], left_cost = 0.;
+    for (int g = 0; g < w.n; ++g) {
+        const int dmin = group_delta(hw, g * heads, heads);
+        bool all = p.n - dmin >= p.L;
+        for (int i = 0; i < heads; ++i) all = all && head_delta(hw, g * heads + i) == dmin;
+        const double x = cost(p.n - dmin, all);
+        left_cost += x;
+        int i = g;
+        for (; i > 0 && c[i - 1] < x; --i) {
+            c[i] = c[i - 1];
+            w.group[i] = w.group[i - 1];
+            w.all[i] = w.all[i - 1];
+        }
+        c[i] = x;
+        w.group[i] = g;
+        w.all[i] = all;
+    }
+    int left = slots > w.n ? slots : w.n;
+    w.first[0] = 0;
+    for (int i = 0; i < w.n; ++i) {
+        int k = (int)(left * (c[i] / left_cost) + 0.5);
+        const int most = left - (w.n - 1 - i);
+        k = k > most ? most : k;
+        k = k > cap ? cap : k;
+        k = k < 1 ? 1 : k;
+        w.first[i + 1] = w.first[i] + k;
+        left -= k;
+        left_cost -= c[i];
+    }
+    return w;
+}
+
+// keys streamed by the query tiles of TP positions of a forward or dQ group, and what its segments' starts cost
+inline double query_cost(const sepattn_params &p, int TP, int n) {
+    const double L = p.L, w = n < p.L ? n : p.L, out = L - w;
+    return w * (L - w / 2) + L * (TP + 128) + kSepShare * out * out / 2;
+}
+
+}  // namespace sepattn

@@ -27,8 +27,9 @@ def run(B, Hq, Hkv, L, d, a, n, p, dtype, seed=1):
     O, LSE = fwd(q, k, v, idx, cnt, pre, a, n, scale)
     grads = bwd(q, k, v, O, LSE, do, idx, cnt, pre, a, n, scale)
     torch.cuda.synchronize()
-    rO, rL = oracle.forward(Q, K, V, flags, a, n, scale)
-    refs = oracle.backward(Q, K, V, dO, flags, a, n, scale, return_term_rss=True)
+    n, n_head = (1, n) if heads else (n, None)
+    rO, rL = oracle.forward(Q, K, V, flags, a, n, scale, n_head=n_head)
+    refs = oracle.backward(Q, K, V, dO, flags, a, n, scale, return_term_rss=True, n_head=n_head)
     assert_close(host(O), rO, dtype, "O")
     assert np.abs(host(LSE) - rL).max() <= (1e-4 if dtype == "fp32" else 2e-3)
     assert_grads_close(grads, refs, dtype)
@@ -56,3 +57,15 @@ def test_fp32_tiles_and_slices(B, Hq, Hkv, L, d, a, n, p):
 ])
 def test_bf16_workgroup_shapes(B, Hq, Hkv, L, d, a, n, p):
     run(B, Hq, Hkv, L, d, a, n, p, "bf16")
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,d,a,p,nh", [
+    (1, 8, 2, 1100, 128, 4, 0.08, [1100] * 4 + [48] * 4),      # a KV head that sees everything next to a short window
+    (2, 12, 4, 700, 64, 3, 0.1, [33] * 6 + [700] * 3 + [1] * 3),  # three heads per KV head, two rows of the batch
+    (1, 8, 2, 513, 64, 0, 0.0, [513] * 4 + [512] * 4),         # one position from full; no separators
+    (2, 14, 2, 400, 128, 2, 0.1, [16] * 7 + [500] * 7),        # seven heads per tile; a window beyond the sequence
+    (8, 128, 128, 66, 64, 1, 0.1, [66, 5, 20, 1] * 32),        # more groups than workgroups fit the chip
+    (1, 4, 2, 31, 128, 1, 0.3, [31, 31, 2, 2]),                # less than one tile
+])
+def test_bf16_head_groups_by_work(B, Hq, Hkv, L, d, a, p, nh):
+    run(B, Hq, Hkv, L, d, a, nh, p, "bf16")
