@@ -35,19 +35,25 @@ __device__ inline float bf16_dot8(u32x4 a, u32x4 b) {
 // ---------------------------------------------------------------------------------------------
 // dQ
 //
-// Same workgroup shapes and key stream as the forward: NW = 8 or 4 waves, each with 32 query rows (one
-// head, 32 positions) whose Q and dO rows stay in registers as B operands; K/V tiles of 64 stream
-// elements pass through LDS (global->LDS loads two tiles ahead, one workgroup barrier per tile).
-// Per block of 32 keys a wave runs
-//     S^T = K Q^T,  dP^T = V dO^T   (16 matrix instructions, operands row-major from LDS)
+// Same workgroup shapes, key stream and load scheme as the forward (fwd_bf16.hip): every wave has 32 query rows (one
+// head, 32 positions) whose Q and dO rows stay in registers as B operands; K/V tiles of 64 stream elements
+// pass through LDS.  Per block of 32 keys a wave runs
+//     S^T = K Q^T,  dP^T = V dO^T   (2 D/16 matrix instructions, operands row-major from LDS)
 //     dS = exp2(S*scale*log2e - LSE*log2e) * (dP - D), masked pairs zero, rounded to bf16
-//     dQ^T += K^T dS^T              (8 matrix instructions, K read transposed from the same tile)
-// with the operand fragments requested a few matrix instructions ahead.  K tiles are stored with
-// the XOR permutation that serves both kinds of read (V tiles too, so that one set of per-lane
-// offsets addresses both); four stages each (tile X+2 is requested while tile X is multiplied, by
-// the first four waves only).  The two waves that share a SIMD (of one workgroup, or of the two
-// workgroups on the compute unit) drift apart by themselves, so that one wave's exponentials overlap
-// the other's matrix work.
+//     dQ^T += K^T dS^T              (2 D/32 matrix instructions, K read transposed from the same tile)
+// A tile is four straight runs of matrix instructions,
+//     S, dP of block 0 | S, dP of block 1 | dQ update of block 0 | dQ update of block 1,
+// with the dS arithmetic of block 0 issued between the matrix instructions of the second run and that of block 1
+// between those of the third (a fixed share after each, held there by scheduling fences), so that it executes
+// while the matrix pipe is busy; the row loads ride on the first run.  Nothing is carried from one tile to the
+// next, so two stages of K and V (AH = 1) are enough for four waves and two workgroups share a compute unit
+// (three at d = 64, with 168 registers, spill: 65 us against 50 at 12 heads, 8 x L=2048).  K and V tiles are stored
+// with the XOR permutation that serves row-major and transposed reads.
+// Bounds: the matrix pipe and issue slots on long streams, the start of a workgroup and of a segment on short ones.
+// Measured (us; before: dS between two runs with nothing beside it, eight waves at d = 128, one head per tile for
+// seven, loads and their index work on four waves): 32/8 heads, d = 128, L = 8192, n = 256 171 -> 158, packed from eight
+// documents 137 -> 124; 28/4 heads, 3 x L=3077 173 -> 127; 8/2 heads, L = 600 19 -> 14; 12 heads, d = 64, 8 x L=2048 54.6 -> 51;
+// every fourth KV head full at L = 4096 170 -> 133.
 // ---------------------------------------------------------------------------------------------
 // DOCS: packed documents, as in the forward kernel (doc_start / doc_end [B, L]; p.a == 0).
 template <int D, int GP, bool DOCS, int NW>
@@ -60,33 +66,27 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     float *__restrict__ Lws, int wpg, HeadWin hw, WorkShare share) {
     constexpr int TP = 32 * NW / GP;
     constexpr int CH = D / 8;
-    constexpr int RPL = 64 / CH;
-    // the tile loads are issued by the first NLW waves only (all of them when NW = 4): of the two waves
-    // of a workgroup that share a SIMD the older one (w < 4) is served first and reaches every barrier
-    // long before its partner
-    constexpr int NLW = 4;
-    constexpr int LOADS = kBN / (RPL * NLW);
+    constexpr int RPL = 64 / CH;      // rows covered by one wave-wide 1 KB load
+    constexpr int NLD = kBN / RPL;    // wave-wide loads per tensor per tile
+    constexpr int LOADS = (NLD + NW - 1) / NW;
     constexpr int KSTEPS = D / 16;
     constexpr int DB = D / 32;
-    // LDS stages of K, of V, and of the visibility ranges: powers of two, so that a stage number is
-    // a mask of the tile number (the kernels spend their time issuing instructions, scalar ones too)
-    constexpr int KST = 4, VST = 4, MKS = 4;
+    // tiles the rows are requested ahead, and tiles between two workgroup barriers (as in the forward)
+    constexpr int AH = NW == 4 ? 1 : 2;
+    constexpr int KST = 2 * AH, MKS = 8;
     constexpr int TILE = kBN * D;
-    static_assert(LOADS >= 1 && LOADS * RPL * NLW == kBN, "tile must divide among the loading waves");
 
     __shared__ __attribute__((aligned(1024))) uint16_t Ks[KST][TILE];
-    __shared__ __attribute__((aligned(1024))) uint16_t Vs[VST][TILE];
-    __shared__ __attribute__((aligned(16))) int lo_s[MKS][kBN];
-    __shared__ __attribute__((aligned(16))) int hi_s[MKS][kBN];
-    // staging of one 32-column block of a wave's 32 dQ rows (see the end of a segment)
+    __shared__ __attribute__((aligned(1024))) uint16_t Vs[KST][TILE];
+    __shared__ __attribute__((aligned(256))) int lo_s[MKS][kBN];
+    __shared__ __attribute__((aligned(256))) int hi_s[MKS][kBN];
+    __shared__ __attribute__((aligned(256))) uint32_t off_s[4][kBN];           // byte offset of a tile's rows in K and V
+    __shared__ __attribute__((aligned(256))) int ent_s[4][DOCS ? 3 : 2][kBN];  // index entries of a tile
+    // staging of one 32-column block of a wave's 32 rows (see the start and the end of a segment)
     __shared__ __attribute__((aligned(16))) uint16_t ostage[NW][32 * 32];
-    constexpr int MR = LOADS * RPL;  // rows per wave and tile
-    constexpr int MST = 4;           // ring stages of the index entries
-    __shared__ __attribute__((aligned(256))) int meta_s[MST][NLW][64];  // 3 * MR <= 48 entries per wave and stage
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool loader = NW == NLW || wave < NLW;
     const int qi = lane & 31, hh = lane >> 5;
     // Persistent workgroups as in the forward kernel: a workgroup belongs to one (batch, KV head, head
     // group) and walks through several query tiles of it ("segments") in zig-zag order, `wpg`
@@ -115,79 +115,19 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     const int32_t *idx = sep_idx + (long)b * p.cap;
     const int32_t *dstart = DOCS ? doc_start + (long)b * p.L : nullptr;
     const int32_t *dend = DOCS ? doc_end + (long)b * p.L : nullptr;
-    const uint16_t *Kh = K + ((long)b * p.Hkv + kv) * (long)p.L * D;
-    const uint16_t *Vh = V + ((long)b * p.Hkv + kv) * (long)p.L * D;
 
     // state of the segment being multiplied (the lambdas below refer to it)
     int iq = 0, iq_h = 0;
     FullBlocks fullb = {};
     bf16x8 qreg[KSTEPS], doreg[KSTEPS];
-    float Di = 0.f, lse2 = 0.f;
+    float Di = 0.f, neg_lse2 = 0.f;
     const float sl2 = p.scale * kLog2e_f;
     f32x16 acc[DB];
 
-    // ---- tile loads (see the forward kernel: same scheme, other LDS layouts)
-    const int my_pc = lane % CH, my_sub = lane / CH;
-    const int row0 = LOADS * wave * RPL + my_sub;  // first of the rows of a tile this lane helps to fill (+ u * RPL)
-    const char *Kb = reinterpret_cast<const char *>(Kh), *Vb = reinterpret_cast<const char *>(Vh);
-    auto tile_class = [&](const Stream &ss, int t) {
-        const int k0 = t * kBN;
-        return (k0 + kBN <= ss.n_dense) ? 0 : (k0 >= ss.n_dense ? 1 : 2);
-    };
-    // A tile is named by the stream of its segment (ss), its number in that stream (t) and its
-    // number in the concatenation of all segments of this workgroup (g), which selects the LDS stage.
-    const int m_part = lane / MR, m_row = wave * MR + lane % MR;  // lanes 0 .. 3*MR-1 are used
-    auto issue_meta = [&](const Stream &ss, int t, int g) __attribute__((always_inline)) {
-        const int k = t * kBN + m_row;
-        const int e = min(max(ss.sep_lo - ss.n_init + k, 0), p.cap - 1);
-        const int j = min(max(ss.bs - ss.n_dense + k, 0), p.L - 1);
-        const int32_t *src = m_part == 0 ? idx + e : prefix + j + (m_part - 1);
-        if constexpr (DOCS) src = m_part == 3 ? dend + j : src;  // fourth part: where the key's document ends
-        if (lane < (DOCS ? 4 : 3) * MR) dma_to_lds_4_addr(src, lds_addr(&meta_s[(unsigned)g % MST][wave % NLW][0]));
-    };
-    // One row of the tile at a time (the loading waves have time to spare, registers are scarce): read
-    // the row's index entries, work out its key position and visibility range, request the row.
-    // de: end of the document of the segment's first row; straddle: the segment's rows reach beyond it
-    auto load_row = [&](const Stream &ss, int de, bool straddle, int t, int g, auto U) __attribute__((always_inline)) {
-        constexpr int u = decltype(U)::value;
-        const int *mt = &meta_s[(unsigned)g % MST][wave % NLW][0];
-        const int rawi = mt[u * RPL + my_sub], raw0 = mt[MR + u * RPL + my_sub], raw1 = mt[2 * MR + u * RPL + my_sub];
-        const int ms_ = (unsigned)g % MKS;
-        const int r = row0 + u * RPL;
-        const int k = t * kBN + r;
-        // the clamp keeps a stale list tail (caller broke sep_count <= cap) from faulting
-        const int jl = min(max(rawi, 0), p.L - 1);
-        int jrow;
-        if (tile_class(ss, t) == 0 && !(DOCS && straddle)) {
-            jrow = k < ss.n_init ? k : jl;
-        } else {
-            const bool init = k < ss.n_init, dense = k < ss.n_dense, pad = k >= ss.n_total;
-            const int jb = ss.bs + (k - ss.n_dense);
-            const bool always = dense | (jb < p.a) | (raw1 != raw0);
-            int j = init ? k : (dense ? jl : jb);
-            j = pad ? 0 : j;
-            const int lo = pad ? kIntMax : j;
-            int hi = always ? kIntMax : jb + p.n - 1;
-            if constexpr (DOCS) hi = min(hi, (dense ? de : mt[3 * MR + u * RPL + my_sub]) - 1);
-            hi = pad ? -1 : hi;
-            if (my_pc == 0) {
-                lo_s[ms_][r] = lo;
-                hi_s[ms_][r] = hi;
-            }
-            jrow = j;
-        }
-        const uint32_t kst = lds_addr(&Ks[(unsigned)g % KST][0]), vst = lds_addr(&Vs[(unsigned)g % VST][0]);
-        const uint32_t wave_off = (uint32_t)((LOADS * wave + u) * RPL * D * 2);
-        const uint32_t off = (uint32_t)jrow * (uint32_t)(D * 2) + swz_chunk<kSwzBoth, D>(my_pc, r) * 16;
-        dma_to_lds_16(Kb, off, kst + wave_off);
-        dma_to_lds_16(Vb, off, vst + wave_off);
-    };
-
-    // ---- segments of this workgroup and the load cursor: the tiles of all segments form one stream
-    // of loads; the cursor (segment lcur, tile l_t, global number l_g) points at the next tile whose
-    // rows are to be requested, two tiles ahead of the tile being multiplied, also across segment
-    // borders.  Past the last segment the stream is empty: its tiles are "loaded" too (row 0, never
-    // visible), which keeps the count of outstanding loads exact.
+    // ---- segments and the look-ahead over the concatenation of their tiles, as in the forward kernel: what a tile
+    // holds is worked out four tiles ahead of the multiplications by wave 0 (even tiles) and wave 1 (odd
+    // tiles), one row per lane, from index entries requested two tiles before.  Past the last segment the stream
+    // is empty: its tiles are "loaded" too (row 0, never visible).
     struct Seg {
         Stream st;
         int n_tiles, i0, de;
@@ -215,46 +155,85 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
         }
         return g;
     };
-    Seg lcur = open_segment(0), lnext = open_segment(1);
-    int l_round = 0, l_t = 0, l_g = 0;
-    auto advance_cursor = [&]() __attribute__((always_inline)) {
-        ++l_g;
-        if (++l_t == lcur.n_tiles) {
-            lcur = lnext;
-            ++l_round;
-            l_t = 0;
-            lnext = open_segment(l_round + 1);
+    struct Cursor {
+        Seg cur, next;
+        int round, t;  // segment of this workgroup and tile of its stream
+    };
+    auto advance = [&](Cursor &c) __attribute__((always_inline)) {
+        if (++c.t == c.cur.n_tiles) {
+            c.cur = c.next;
+            ++c.round;
+            c.t = 0;
+            c.next = open_segment(c.round + 1);
         }
     };
-    auto issue_meta_after_cursor = [&]() __attribute__((always_inline)) {
-        if (l_t + 1 < lcur.n_tiles)
-            issue_meta(lcur.st, l_t + 1, l_g + 1);
-        else
-            issue_meta(lnext.st, 0, l_g + 1);
+    // entries of tile t (global number g) of stream ss
+    auto issue_entries = [&](const Stream &ss, int t, int g) __attribute__((always_inline)) {
+        const int k = t * kBN + lane;
+        const int e = min(max(ss.sep_lo - ss.n_init + k, 0), p.cap - 1);
+        const int j = min(max(ss.bs - ss.n_dense + k, 0), p.L - 1);
+        const uint32_t dst = lds_addr(&ent_s[g & 3][0][0]);
+        dma_to_lds_4_addr(k < ss.n_dense ? idx + e : prefix + j, dst);
+        dma_to_lds_4_addr(prefix + j + 1, dst + kBN * 4);
+        if constexpr (DOCS) dma_to_lds_4_addr(dend + j, dst + 2 * kBN * 4);  // where the key's document ends
     };
-    // a tile step issues [1 entry load][2*LOADS row loads], in this order; loads complete in order
-    auto wait_vmcnt = [&](auto N) __attribute__((always_inline)) {
-        constexpr int n = decltype(N)::value;
-        static_assert(n == 2 || n == 3 || n == 4 || n == 5 || n == 8 || n == 9, "add the count");
-        if constexpr (n == 2) asm volatile("s_waitcnt vmcnt(2)" ::: "memory");
-        if constexpr (n == 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
-        if constexpr (n == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
-        if constexpr (n == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
-        if constexpr (n == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
-        if constexpr (n == 9) asm volatile("s_waitcnt vmcnt(9)" ::: "memory");
+    auto write_rows = [&](const Cursor &c, int g) __attribute__((always_inline)) {
+        const Stream &ss = c.cur.st;
+        const int k = c.t * kBN + lane;
+        const int e0 = ent_s[g & 3][0][lane], e1 = ent_s[g & 3][1][lane];
+        const bool dense = k < ss.n_dense, pad = k >= ss.n_total;
+        const int jb = ss.bs + (k - ss.n_dense);
+        // the clamp keeps a stale list tail (caller broke sep_count <= cap) from faulting
+        int j = dense ? min(max(e0, 0), p.L - 1) : jb;
+        j = k < ss.n_init ? k : j;
+        int hi = (dense | (jb < p.a) | (e1 != e0)) ? kIntMax : jb + p.n - 1;
+        if constexpr (DOCS) hi = min(hi, (dense ? c.cur.de : ent_s[g & 3][2][lane]) - 1);
+        lo_s[g % MKS][lane] = pad ? kIntMax : j;
+        hi_s[g % MKS][lane] = pad ? -1 : hi;
+        off_s[g & 3][lane] = pad ? 0u : (uint32_t)j * (uint32_t)(D * 2);
     };
-    auto entries_landed = [&]() __attribute__((always_inline)) { wait_vmcnt(IntC<2 * LOADS>{}); };
-    // (a wave that loads nothing has nothing in flight: the wait falls through)
-    auto wait_older_loads = [&]() __attribute__((always_inline)) { wait_vmcnt(IntC<1 + 2 * LOADS>{}); };
+    // start of tile step g: positions of a tile four further on, entries of one six further on (AH = 2: of two
+    // tiles every other step)
+    Cursor lc;
+    auto look_ahead = [&](int g) __attribute__((always_inline)) {
+        if (AH == 1 ? wave == (g & 1) : ((g & 1) == 0 && wave < 2)) {
+            const int t = g + (AH == 1 ? 0 : wave);
+            write_rows(lc, t + 4);
+            advance(lc);
+            advance(lc);
+            issue_entries(lc.cur.st, lc.t, t + 6);
+        }
+    };
+
+    // ---- row loads: load n of a tile fills rows n*RPL .. +RPL-1 with one wave-wide direct global->LDS load per
+    // tensor; wave w issues loads LOADS*w + u (the last one again where the waves do not divide the tile)
+    const char *Kb = reinterpret_cast<const char *>(K + ((long)b * p.Hkv + kv) * (long)p.L * D);
+    const char *Vb = reinterpret_cast<const char *>(V + ((long)b * p.Hkv + kv) * (long)p.L * D);
+    const int my_pc = lane % CH, my_sub = lane / CH;
+    const uint32_t ks_base = lds_addr(&Ks[0][0]), vs_base = lds_addr(&Vs[0][0]);
+    uint32_t gofs[LOADS];  // byte offset of this lane's piece of the rows it helps to fill next
+    auto read_offsets = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < LOADS; ++u) {
+            const int r = min(LOADS * wave + u, NLD - 1) * RPL + my_sub;
+            gofs[u] = off_s[g & 3][r] + swz_chunk<kSwzBoth, D>(my_pc, r) * 16;
+        }
+    };
+    auto issue_row = [&](int g, auto N) __attribute__((always_inline)) {  // the K (even n) or V (odd n) rows of load n / 2
+        constexpr int n = decltype(N)::value, u = n / 2;
+        const uint32_t at = (unsigned)(g % KST) * (TILE * 2) + (uint32_t)min(LOADS * wave + u, NLD - 1) * 1024u;
+        if constexpr (n % 2 == 0) dma_to_lds_16(Kb, gofs[u], ks_base + at);
+        else dma_to_lds_16(Vb, gofs[u], vs_base + at);
+    };
+    // publishes every load and LDS write of the wave
     auto wg_barrier = [&]() __attribute__((always_inline)) {
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     };
 
     // per-lane byte offsets of the operand fragments inside a tile
     const int a_row = pi_row(qi);
-    const uint32_t ks_base = lds_addr(&Ks[0][0]), vs_base = lds_addr(&Vs[0][0]);
     // Row-major fragments: the XOR permutation acts on the 16-byte chunk index 2*ks + hh, and the
     // k-step only enters through bits 1..3 of it, so fragment ks sits at (fragment 0) ^ (32 * ks):
     // one register instead of KSTEPS.  (Tile bases are multiples of 1 KB, so the XOR commutes with
@@ -274,109 +253,131 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
             return first - ktr0[db] + ktr1[db];
     };
 
-    // ---- one block of 32 keys: tile X of the current segment (global number gbase + X), block HB
+    // ---- one straight run of tile X of the current segment (global number gbase + X).  SP: S and dP of block SP into
+    // s_new, p_new; DQ: dQ update with block DQ's keys and ds_old; DS: dS of block DS from s_old, p_old into
+    // ds_new (-1: not in this run); LD: the rows of tile X + AH are requested.
     int gbase = 0;
     constexpr int LA = 4;
-    constexpr int NS1 = 2 * KSTEPS, NS2 = 2 * DB;  // matrix instructions: scores, then the dQ update
-    auto block_step = [&](int X, auto HB_, auto LD_) __attribute__((always_inline)) {
-        constexpr int HB = decltype(HB_)::value;
+    auto run = [&](int X, auto SP_, auto DQ_, auto DS_, auto LD_, f32x16 &s_new, f32x16 &p_new, const bf16x8 (&ds_old)[2],
+                   f32x16 &s_old, f32x16 &p_old, bf16x8 (&ds_new)[2]) __attribute__((always_inline)) {
+        constexpr int SP = decltype(SP_)::value, DQ = decltype(DQ_)::value, DS = decltype(DS_)::value;
         constexpr bool DO_LD = decltype(LD_)::value != 0;
-        const uint32_t kst = ks_base + ((unsigned)(gbase + X) % KST) * (TILE * 2) + HB * 32 * D * 2;
-        const uint32_t vst = vs_base + ((unsigned)(gbase + X) % VST) * (TILE * 2) + HB * 32 * D * 2;
-        f32x16 sacc, pacc;
+        constexpr int NS = SP >= 0 ? 2 * KSTEPS : (DQ >= 0 ? 2 * DB : 0);
+        static_assert(SP < 0 || DQ < 0, "one kind of matrix work per run");
+        constexpr int E = NS ? 16 / (NS ? NS : 1) : 16;  // elements of dS per matrix instruction
+        const uint32_t stage = (unsigned)(gbase + X) % KST * (TILE * 2);
+        const uint32_t kst = ks_base + stage + max(SP, DQ) * 32 * D * 2, vst = vs_base + stage + max(SP, 0) * 32 * D * 2;
         bf16x8 frag[LA];
-        auto request1 = [&](auto S) __attribute__((always_inline)) {
+        auto request = [&](auto S) __attribute__((always_inline)) {
             constexpr int s = decltype(S)::value;
-            if constexpr (s < NS1) {
-                constexpr int ks = s / 2;
-                frag[s % LA] = lds_read_b128_at(((s % 2 == 0 ? kst : vst) + koff0) ^ (32u * ks));
+            if constexpr (s < NS) {
+                if constexpr (SP >= 0) {
+                    frag[s % LA] = lds_read_b128_at(((s % 2 == 0 ? kst : vst) + koff0) ^ (32u * (s / 2)));
+                } else {
+                    constexpr int stp = s / DB, db = s % DB;
+                    frag[s % LA] = lds_read_tr_at2(kst + ktr0[db] + stp * 16 * D * 2, tr_second(kst + ktr0[db], db) + stp * 16 * D * 2);
+                }
             }
         };
-        static_for<LA>([&](auto S) { request1(S); });
-        __builtin_amdgcn_sched_barrier(0);
-        static_for<NS1>([&](auto S) {
-            constexpr int s = decltype(S)::value, ks = s / 2;
-            const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-            if constexpr (s % 2 == 0)
-                sacc = mfma_bf16(frag[s % LA], qreg[ks], ks == 0 ? zero : sacc);
-            else
-                pacc = mfma_bf16(frag[s % LA], doreg[ks], ks == 0 ? zero : pacc);
-            request1(IntC<s + LA>{});
-            // the load path of the tile at the cursor (two tiles ahead) rides along with the first
-            // block of the tile
-            if constexpr (DO_LD) {
-                static_assert(NS1 / 4 + 2 * (LOADS - 1) < NS1 - 1, "the row slots must come before the cursor moves");
-                // order of the requests: [entries of the tile after the cursor] [rows of the tile at it]
-                if (loader) {
-                    if constexpr (s == 0) {
-                        entries_landed();
-                        issue_meta_after_cursor();
-                    } else if constexpr (s >= NS1 / 4 && (s - NS1 / 4) % 2 == 0 && (s - NS1 / 4) / 2 < LOADS) {
-                        load_row(lcur.st, lcur.de, lcur.i0 + TP > lcur.de, l_t, l_g, IntC<(s - NS1 / 4) / 2>{});
-                    } else if constexpr (s == NS1 - 1) {
-                        advance_cursor();
+        static_for<LA>([&](auto S) { request(S); });
+        if constexpr (DS >= 0) {
+            if (!block_is_full(fullb, X * kBN + DS * 32)) {
+                const int ms_ = (unsigned)(gbase + X) % MKS;
+#pragma unroll
+                for (int half = 0; half < 2; ++half) {
+                    const int base = DS * 32 + 16 * half + 8 * hh;
+                    const int4 lo0 = *reinterpret_cast<const int4 *>(&lo_s[ms_][base]);
+                    const int4 lo1 = *reinterpret_cast<const int4 *>(&lo_s[ms_][base + 4]);
+                    const int4 hi0 = *reinterpret_cast<const int4 *>(&hi_s[ms_][base]);
+                    const int4 hi1 = *reinterpret_cast<const int4 *>(&hi_s[ms_][base + 4]);
+                    const int los[8] = {lo0.x, lo0.y, lo0.z, lo0.w, lo1.x, lo1.y, lo1.z, lo1.w};
+                    const int his[8] = {hi0.x, hi0.y, hi0.z, hi0.w, hi1.x, hi1.y, hi1.z, hi1.w};
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        const bool vis = (los[k] <= iq) & (iq_h <= his[k]);
+                        s_old[8 * half + k] = vis ? s_old[8 * half + k] : -INFINITY;
                     }
                 }
             }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        // elements e0 .. e0+E-1 get their exponentials in a slot, and their factor dP - D in the next one, when the
+        // transcendental unit has delivered
+        auto exps = [&](int e0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = e0; i < e0 + E; ++i)
+                if (i < 16) s_old[i] = __builtin_amdgcn_exp2f(fmaf(s_old[i], sl2, neg_lse2));
+        };
+        auto products = [&](int e0) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = e0; i < e0 + E; ++i)
+                if (i >= 0 && i < 16) s_old[i] *= p_old[i] - Di;
+        };
+        static_for<NS>([&](auto S) {
+            constexpr int s = decltype(S)::value;
+            if constexpr (SP >= 0) {
+                const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                if constexpr (s % 2 == 0) s_new = mfma_bf16(frag[s % LA], qreg[s / 2], s == 0 ? zero : s_new);
+                else p_new = mfma_bf16(frag[s % LA], doreg[s / 2], s == 1 ? zero : p_new);
+            } else {
+                acc[s % DB] = mfma_bf16(frag[s % LA], ds_old[s / DB], acc[s % DB]);
+            }
+            request(IntC<s + LA>{});
+            if constexpr (DS >= 0) {
+                constexpr int e0 = E * s;
+                exps(e0);
+                products(e0 - E);
+                if constexpr (e0 - E < 8 && e0 >= 8) ds_new[0] = pack_bf16x8(s_old, 0);
+            }
+            if constexpr (DO_LD && s >= 1) {
+                constexpr int LPS = (2 * LOADS + NS - 2) / (NS - 1);  // row loads per slot
+                static_for<LPS>([&](auto J) {
+                    constexpr int n = (s - 1) * LPS + decltype(J)::value;
+                    if constexpr (n < 2 * LOADS) issue_row(gbase + X + AH, IntC<n>{});
+                });
+            }
             __builtin_amdgcn_sched_barrier(0);
         });
-        // transposed K fragments of the first half of the dQ update are requested before the dS
-        // arithmetic, those of the second half while the first half multiplies
-        bf16x8 tfr[DB];
-#pragma unroll
-        for (int db = 0; db < DB; ++db) tfr[db] = lds_read_tr_at2(kst + ktr0[db], tr_second(kst + ktr0[db], db));
-        // dS = P (dP - D), zero where masked
-        if (!block_is_full(fullb, X * kBN + HB * 32)) {
-            const int ms_ = (unsigned)(gbase + X) % MKS;
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                const int base = HB * 32 + 16 * half + 8 * hh;
-                const int4 lo0 = *reinterpret_cast<const int4 *>(&lo_s[ms_][base]);
-                const int4 lo1 = *reinterpret_cast<const int4 *>(&lo_s[ms_][base + 4]);
-                const int4 hi0 = *reinterpret_cast<const int4 *>(&hi_s[ms_][base]);
-                const int4 hi1 = *reinterpret_cast<const int4 *>(&hi_s[ms_][base + 4]);
-                const int los[8] = {lo0.x, lo0.y, lo0.z, lo0.w, lo1.x, lo1.y, lo1.z, lo1.w};
-                const int his[8] = {hi0.x, hi0.y, hi0.z, hi0.w, hi1.x, hi1.y, hi1.z, hi1.w};
-#pragma unroll
-                for (int k = 0; k < 8; ++k) {
-                    const bool vis = (los[k] <= iq) & (iq_h <= his[k]);
-                    sacc[8 * half + k] = vis ? sacc[8 * half + k] : -INFINITY;
-                }
-            }
+        if constexpr (DS >= 0) {
+            if constexpr (NS == 0) exps(0);
+            products(16 - E);
+            if constexpr (E > 8) ds_new[0] = pack_bf16x8(s_old, 0);
+            ds_new[1] = pack_bf16x8(s_old, 8);
+            u32x4 &x0 = reinterpret_cast<u32x4 &>(ds_new[0]), &x1 = reinterpret_cast<u32x4 &>(ds_new[1]);
+            asm volatile("" : "+v"(x0), "+v"(x1));
         }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const float pr = __builtin_amdgcn_exp2f(fmaf(sacc[i], sl2, -lse2));
-            sacc[i] = pr * (pacc[i] - Di);
-        }
-        const bf16x8 dsb0 = pack_bf16x8(sacc, 0), dsb1 = pack_bf16x8(sacc, 8);
-        // dQ^T += K^T dS^T
-        bf16x8 tfr2[DB];
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-            acc[db] = mfma_bf16(tfr[db], dsb0, acc[db]);
-            tfr2[db] = lds_read_tr_at2(kst + ktr0[db] + 16 * D * 2, tr_second(kst + ktr0[db], db) + 16 * D * 2);
-        }
-#pragma unroll
-        for (int db = 0; db < DB; ++db) acc[db] = mfma_bf16(tfr2[db], dsb1, acc[db]);
+        __builtin_amdgcn_sched_barrier(0);
     };
 
-    // ---- start-up, once per workgroup: the first two tiles of the concatenated stream on their way
-    // into LDS, the index entries of the third requested
-    if (loader) {
-        issue_meta(lcur.st, 0, 0);
+    // ---- start-up, once per workgroup: positions of tiles 0 .. 3, then the first rows (the entries of tiles 4
+    // and 5 are on their way)
+    if (wave < 2) {
+        lc.cur = open_segment(0);
+        lc.next = open_segment(1);
+        lc.round = lc.t = 0;
+        if (wave == 1) advance(lc);
+        issue_entries(lc.cur.st, lc.t, wave);
+        Cursor l2 = lc;
+        advance(l2);
+        advance(l2);
+        issue_entries(l2.cur.st, l2.t, 2 + wave);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-#pragma unroll
-        for (int rep = 0; rep < 2; ++rep) {
-            issue_meta_after_cursor();
-            static_for<LOADS>([&](auto U) { load_row(lcur.st, lcur.de, lcur.i0 + TP > lcur.de, l_t, l_g, U); });
-            advance_cursor();
-            entries_landed();  // the entries just requested (the rows after them may be in flight)
-        }
+        write_rows(lc, wave);
+        write_rows(l2, 2 + wave);
+        lc = l2;
+        advance(lc);
+        advance(lc);
+        issue_entries(lc.cur.st, lc.t, 4 + wave);
     }
+    wg_barrier();
+    static_for<AH>([&](auto T) {
+        read_offsets(decltype(T)::value);
+        static_for<2 * LOADS>([&](auto N) { issue_row(decltype(T)::value, N); });
+    });
 
-    const IntC<1> yes;
-    const IntC<0> no;
+    const IntC<0> first, off;
+    const IntC<1> second, on;
+    const IntC<-1> none;
     // The wave's 32 rows of Q, dO and O of a segment.  The operand layout wants, per lane, 16-byte pieces
     // of ONE row; fetched that way every load instruction is 64 scattered pieces, and their number (1536
     // per wave and segment) is what such loads cost.  They are fetched instead so that four consecutive
@@ -451,7 +452,8 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
                 });
             }
             const uint32_t soff = (uint32_t)min(iq, p.L - 1) * 4u;
-            lse2 = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(LSE + head_row0) + soff) * kLog2e_f;
+            const float lse2 = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(LSE + head_row0) + soff) * kLog2e_f;
+            neg_lse2 = -lse2;
             if (hh == 0 && iq < p.L) {
                 // stored negated: the dK/dV kernel starts its dP accumulator from -D
                 *reinterpret_cast<float *>(reinterpret_cast<char *>(Dws + head_row0) + soff) = -Di;
@@ -464,19 +466,30 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[db][i] = 0.f;
 
-        // Tile step X reads K and V of tile gbase+X (row-major and transposed) and requests the tile
-        // two further on, whose stages held tile gbase+X-1: last read in the previous step, which
-        // every wave has left when it passes the barrier.  The barrier publishes tile gbase+X: each
-        // wave has waited for everything older than the previous step's requests.
-        const int n_tiles = cseg.n_tiles;
-        // the second block of the last tile is skipped when it is all padding (the same decision in
-        // every wave; the tile loads ride on the first block)
-        const int n_keys = cseg.st.n_total;
-        for (int X = 0; X < n_tiles; ++X) {
-            wait_older_loads();
-            wg_barrier();
-            block_step(X, IntC<0>{}, yes);
-            if (X * kBN + 32 < n_keys) block_step(X, IntC<1>{}, no);
+        // Step X reads tile gbase+X and requests tile gbase+X+AH, whose stages held tile gbase+X-AH; barriers stand in
+        // front of every AH-th tile of the concatenated stream, where everything requested before has landed.  The
+        // second block of the last tile is left out when it is all padding (the same decision in every wave).
+        // (A tail after the loop: alternatives inside it would cost a copy of the accumulators per tile.)
+        const int n_tiles = cseg.n_tiles, n_whole = (cseg.st.n_total + 31) / kBN;
+        auto begin_tile = [&](int X) __attribute__((always_inline)) {
+            if ((gbase + X) % AH == 0) wg_barrier();
+            look_ahead(gbase + X);
+            read_offsets(gbase + X + AH);
+        };
+        f32x16 s0, p0, s1, p1;
+        bf16x8 ds0[2], ds1[2];
+        for (int X = 0; X < n_whole; ++X) {
+            begin_tile(X);
+            run(X, first, none, none, on, s0, p0, ds0, s0, p0, ds0);
+            run(X, second, none, first, off, s1, p1, ds0, s0, p0, ds0);
+            run(X, none, first, second, off, s0, p0, ds0, s1, p1, ds1);
+            run(X, none, second, none, off, s0, p0, ds1, s1, p1, ds1);
+        }
+        if (n_whole < n_tiles) {
+            begin_tile(n_whole);
+            run(n_whole, first, none, none, on, s0, p0, ds0, s0, p0, ds0);
+            run(n_whole, none, none, first, off, s1, p1, ds0, s0, p0, ds0);
+            run(n_whole, none, first, none, off, s1, p1, ds0, s0, p0, ds0);
         }
         gbase += n_tiles;
         const Seg nseg = open_segment(round + 1);
@@ -530,49 +543,32 @@ int launch_bwd(const sepattn_params &p, const uint16_t *Q, const uint16_t *K, co
     float *farV = reinterpret_cast<float *>(base + 2 * w.d_bytes + w.far_bytes);
     int32_t *piece_tab = reinterpret_cast<int32_t *>(base + 2 * w.d_bytes + 2 * w.far_bytes);
 
-    int G = p.Hq / p.Hkv;
-    int GP = (G % 4 == 0) ? 4 : (G % 2 == 0) ? 2 : 1;
-    // Workgroups of eight waves, one per compute unit (the LDS footprint allows no more).  At d = 64
-    // the K/V stages are half as large and two independent workgroups of four waves fit a compute
-    // unit: one's segment start and row stores overlap the other's matrix work, their barriers do not
-    // lock each other's phases, and the split of a group is twice as fine (it fills the chip where
-    // 256 / groups is not a whole number).  A four-wave workgroup has half the query rows per K/V
-    // tile, i.e. twice the tile loads per matrix instruction: where four grouped heads share the
-    // tile (32 positions per workgroup instead of 64) the eight-wave shape stays the better one
-    // (by 2-5 % at any length), with one or two heads per tile the four-wave shape wins (5-25 %).
-    const bool narrow = D == 64 && GP <= 2;
-    const int NWr = narrow ? 4 : 8;
-    int TP = 32 * NWr / GP;
+    const QueryShape shape = query_shape(p);
+    const int TP = 32 * shape.nw / shape.gp;
     const int n_pos_tiles = (p.L + TP - 1) / TP;
-    const long n_groups = (long)p.B * p.Hkv * (G / GP);
+    const long n_groups = (long)p.B * (p.Hq / shape.gp);
     // persistent workgroups, spread evenly over the groups; never more than a group has tiles
-    int wpg = (int)((8 / NWr) * (long)compute_units() / n_groups);
+    const int per_cu = shape.nw > 4 ? 1 : 2;
+    int wpg = (int)(per_cu * (long)compute_units() / n_groups);
     wpg = wpg < 1 ? 1 : (wpg > n_pos_tiles ? n_pos_tiles : wpg);
     if (n_groups * wpg > 0x7FFFFFFFL) return SEPATTN_ERR_SHAPE;
     WorkShare share = {};
     long n_wg = n_groups * wpg;
     if (any_delta(hw)) {
-        share = share_out(p, hw, GP, (8 / NWr) * compute_units() / p.B, n_pos_tiles, [&](int n, bool) { return query_cost(p, TP, n); });
+        share = share_out(p, hw, shape.gp, per_cu * compute_units() / p.B, n_pos_tiles, [&](int n, bool) { return query_cost(p, TP, n); });
         n_wg = (long)p.B * share.first[share.n];
     }
-    dim3 grid((unsigned)n_wg), block(64 * NWr);
+    dim3 grid((unsigned)n_wg), block(64 * shape.nw);
     {
     ProfScope prof(SEPATTN_K_BWD_DQ, st);
-    auto go = [&](auto NW_) {
-        constexpr int NW = decltype(NW_)::value;
-        if (GP == 4)
-            hipLaunchKernelGGL((dq_kernel<D, 4, DOCS, NW>), grid, block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, Lws, wpg, hw, share);
-        else if (GP == 2)
-            hipLaunchKernelGGL((dq_kernel<D, 2, DOCS, NW>), grid, block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, Lws, wpg, hw, share);
-        else
-            hipLaunchKernelGGL((dq_kernel<D, 1, DOCS, NW>), grid, block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, Lws, wpg, hw, share);
+    auto go = [&](auto NW_, auto GP_) {
+        hipLaunchKernelGGL((dq_kernel<D, decltype(GP_)::value, DOCS, decltype(NW_)::value>), grid, block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, Lws, wpg, hw, share);
     };
-    if constexpr (D == 64) {
-        if (narrow) go(IntC<4>{});
-        else go(IntC<8>{});
-    } else {
-        go(IntC<8>{});
-    }
+    if (shape.gp == 7) go(IntC<7>{}, IntC<7>{});
+    else if (D == 128 && shape.nw == 8) go(IntC<D == 128 ? 8 : 4>{}, IntC<4>{});
+    else if (shape.gp == 4) go(IntC<4>{}, IntC<4>{});
+    else if (shape.gp == 2) go(IntC<4>{}, IntC<2>{});
+    else go(IntC<4>{}, IntC<1>{});
     }
     if (hipGetLastError() != hipSuccess) return SEPATTN_ERR_HIP;
     return launch_dkv_bf16(p, hw, Q, K, V, Lws, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, st);
