@@ -8,16 +8,16 @@
 //   its far pieces: far pairs on the COMPACTED list of such keys.  For list tile ft (128 consecutive
 //              list entries, gathered K/V rows) the work is the sequence of items (query tile of 64
 //              rows, query head) from the first query that sees the tile's first key to the end of
-//              the sequence; the items of all list tiles, concatenated, are cut into wpg equal
-//              slices, and the part of a workgroup's slice inside one list tile is a piece.  A piece
+//              the sequence; the items of all list tiles, concatenated, are cut into slices, up to
+//              one per workgroup, and the part of a slice inside one list tile is a piece.  A piece
 //              writes an fp32 partial dK/dV of the tile's rows to the workspace (slot w + ft).
 //   its band units: 128 consecutive keys against the queries j <= i < j+n (units w, w+wpg, ...).
 //              Keys that are not on the far list are finished here (rounded once to bf16); for the
 //              others the band unit writes one more fp32 partial.
 // dkv_combine_kernel then adds, in fixed order, the partials of every far-list key and rounds once to
 // bf16.  One workgroup owns each partial row: no atomics, results are bit-reproducible.  Every
-// workgroup gets the same amount of far work and (up to one) the same number of band units, so the
-// compute units finish together.
+// workgroup gets (up to one) the same number of band units, and those with one less get more far work, so
+// the compute units finish together.
 // A workgroup is 8 waves = 4 key blocks of 32 keys x 2 roles.  The two waves of a key block split
 // the four contractions so that each keeps only one operand matrix and one accumulator resident:
 //   P-wave :  S = Q K^T   -> P = exp2(.)      -> dV^T += dO^T P     (holds K rows, dV^T)
@@ -172,11 +172,23 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         int fq;
         far_total += __builtin_amdgcn_readfirstlane(__shfl(inclusive_scan(tile_items(base + lane, fq)), 63));
     }
-    // no more slices than items, so that no slice is empty: the pieces of a list tile then belong to
-    // consecutive workgroups, which is what the combine kernel relies on
-    const long wfar = far_total < wpg ? (far_total > 0 ? far_total : 1) : wpg;
-    const long s0 = w_id < wfar ? w_id * far_total / wfar : far_total;
-    const long s1 = w_id < wfar ? (w_id + 1) * far_total / wfar : far_total;
+    // Slices.  Where the band units do not divide among the workgroups, the first `heavy` have one more than the others,
+    // and far work goes to those others first, as much as a band unit costs (in items, with its start).  Without that
+    // a workgroup with two units and a full slice sets the time where most have one unit (28/4 heads, 3 x L=3077,
+    // 49 units on 42 workgroups: 190 us, 174 with it).  No slice is shorter than kMinSlice steps: the start of a piece and the
+    // sum of many partials would cost more than the items (8/2 heads, L = 600: 29 + 12.6 us with slices of one
+    // item, 22 + 4 now).  The slices that are not empty belong to consecutive workgroups, which is what the combine
+    // kernel relies on.
+    constexpr int kMinSlice = 16, kUnitStart = 8;  // steps of 32 query rows
+    const int heavy = n_band % wpg, light = wpg - heavy;
+    const long unit_items = ((long)G * ((p.n + 30) / 32 + 1) + kUnitStart) / BPT;
+    long per_heavy = heavy ? max((far_total - unit_items * light) / wpg, 0l) : 0;
+    if (per_heavy < kMinSlice / BPT) per_heavy = 0;
+    const long far_light = far_total - per_heavy * heavy;
+    const long n_light = min(max(far_light / (kMinSlice / BPT), 1l), (long)light);
+    const int w_light = w_id - heavy;
+    const long s0 = w_light < 0 ? w_id * per_heavy : per_heavy * heavy + min((long)w_light, n_light) * far_light / n_light;
+    const long s1 = w_light < 0 ? s0 + per_heavy : per_heavy * heavy + min(w_light + 1l, n_light) * far_light / n_light;
 
     // iteration state over the pieces: first the far pieces of the slice (list tiles in groups of 64,
     // `pend` = tiles of the current group that overlap the slice and are still to be visited), then
