@@ -739,7 +739,10 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
 }
 
 // Sum of the partials of every far-list key (the far pieces of its list tile in ascending workgroup
-// order, then the band partial), rounded once to bf16.  One thread per (key, 4 consecutive columns).
+// order, then the band partial), rounded once to bf16.  One thread per (key, 4 consecutive columns).  Bounds: the chain
+// list length -> list entry -> piece table -> partials, then their bytes.  The list's length is on the device and
+// its capacity is that of all keys: a grid for an eighth of the capacity, which walks on where there are more
+// entries, starts an eighth of the workgroups that only find out that they have nothing to do.
 template <int D>
 __global__ __launch_bounds__(256) void dkv_combine_kernel(sepattn_params p, const int32_t *__restrict__ sep_idx,
                                                           const int32_t *__restrict__ sep_prefix,
@@ -749,7 +752,7 @@ __global__ __launch_bounds__(256) void dkv_combine_kernel(sepattn_params p, cons
                                                           const float *__restrict__ farV,
                                                           const int32_t *__restrict__ piece_tab, int wpg, int kw,
                                                           HeadWin hw, WorkShare share) {
-    constexpr int TPR = D / 4;  // threads per row
+    constexpr int TPR = D / 4, RPB = 256 / TPR;  // threads per row, rows per workgroup
     int bkv = blockIdx.y;
     long base = bkv * far_geom(p, wpg, kw).rows;
     bool every_key = false;
@@ -768,49 +771,51 @@ __global__ __launch_bounds__(256) void dkv_combine_kernel(sepattn_params p, cons
     const int32_t *idx = sep_idx + (long)b * p.cap;
     const FarGeom fg = far_geom(p, wpg, kw);
     const FarList fl = far_list(p, prefix, every_key);
-    const int f = (blockIdx.x * 256 + threadIdx.x) / TPR, col = ((blockIdx.x * 256 + threadIdx.x) % TPR) * 4;
-    if (f >= fl.NF) return;
-    const int lt = fg.bk;  // entries per list tile
-    const int A = far_first_query(fl, f, idx, p, lt);
-    // no far piece for this list tile: the band unit has written the row
-    if (A >= far_last_query(fl, f, idx, p, doc_end ? doc_end + (long)b * p.L : nullptr, lt)) return;
-    const int j = far_pos(fl, f, idx, p.L);
-    const int ft = f / lt;
-    const int32_t *tab = piece_tab + ((long)bkv * fg.NFTcap + ft) * 2;
-    // the clamps keep a table that the far pass did not write (it always does) from faulting
-    const int w0 = min(max(tab[0], 0), wpg - 1), w1 = min(max(tab[1], w0), wpg - 1);
-    float4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
-    // the band partial and eight pieces at a time (clamped slots) are requested together, so that a
-    // list tile with up to eight pieces costs one memory round trip; the sum runs in slot order
-    constexpr int NB = 8;
-    const long brow = (base + (long)fg.NP * lt + f) * D + col;
-    float4 bk = {0.f, 0.f, 0.f, 0.f}, bv = {0.f, 0.f, 0.f, 0.f};
-    if (!every_key) {
-        bk = *reinterpret_cast<const float4 *>(farK + brow);
-        bv = *reinterpret_cast<const float4 *>(farV + brow);
-    }
-    for (int w = w0; w <= w1; w += NB) {
-        float4 pk[NB], pv[NB];
-#pragma unroll
-        for (int c = 0; c < NB; ++c) {
-            const int ww = min(w + c, w1);
-            const long prow = (base + (long)(ww + ft) * lt + (f - ft * lt)) * D + col;
-            pk[c] = *reinterpret_cast<const float4 *>(farK + prow);
-            pv[c] = *reinterpret_cast<const float4 *>(farV + prow);
+    const int col = (threadIdx.x % TPR) * 4, lt = fg.bk;  // lt: entries per list tile
+    const int32_t *dend = doc_end ? doc_end + (long)b * p.L : nullptr;
+    for (int f = blockIdx.x * RPB + threadIdx.x / TPR; f < fl.NF; f += gridDim.x * RPB) {
+        // everything that does not depend on a loaded value is requested before the first use
+        const int ft = f / lt;
+        const int32_t *tab = piece_tab + ((long)bkv * fg.NFTcap + ft) * 2;
+        const int t0 = tab[0], t1 = tab[1];
+        const long brow = (base + (long)fg.NP * lt + f) * D + col;
+        float4 bk = {0.f, 0.f, 0.f, 0.f}, bv = {0.f, 0.f, 0.f, 0.f};
+        if (!every_key) {
+            bk = *reinterpret_cast<const float4 *>(farK + brow);
+            bv = *reinterpret_cast<const float4 *>(farV + brow);
         }
+        const int j = far_pos(fl, f, idx, p.L);
+        // no far piece for this list tile: the band unit has written the row
+        if (far_first_query(fl, f, idx, p, lt) >= far_last_query(fl, f, idx, p, dend, lt)) continue;
+        // the clamps keep a table that the far pass did not write (it always does) from faulting
+        const int w0 = min(max(t0, 0), wpg - 1), w1 = min(max(t1, w0), wpg - 1);
+        float4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
+        // eight pieces at a time (clamped slots) are requested together, so that a list tile with up to eight
+        // pieces costs one memory round trip; the sum runs in slot order
+        constexpr int NB = 8;
+        for (int w = w0; w <= w1; w += NB) {
+            float4 pk[NB], pv[NB];
 #pragma unroll
-        for (int c = 0; c < NB; ++c) {
-            if (w + c <= w1) {
-                sk.x += pk[c].x, sk.y += pk[c].y, sk.z += pk[c].z, sk.w += pk[c].w;
-                sv.x += pv[c].x, sv.y += pv[c].y, sv.z += pv[c].z, sv.w += pv[c].w;
+            for (int c = 0; c < NB; ++c) {
+                const int ww = min(w + c, w1);
+                const long prow = (base + (long)(ww + ft) * lt + (f - ft * lt)) * D + col;
+                pk[c] = *reinterpret_cast<const float4 *>(farK + prow);
+                pv[c] = *reinterpret_cast<const float4 *>(farV + prow);
+            }
+#pragma unroll
+            for (int c = 0; c < NB; ++c) {
+                if (w + c <= w1) {
+                    sk.x += pk[c].x, sk.y += pk[c].y, sk.z += pk[c].z, sk.w += pk[c].w;
+                    sv.x += pv[c].x, sv.y += pv[c].y, sv.z += pv[c].z, sv.w += pv[c].w;
+                }
             }
         }
+        sk.x += bk.x, sk.y += bk.y, sk.z += bk.z, sk.w += bk.w;
+        sv.x += bv.x, sv.y += bv.y, sv.z += bv.z, sv.w += bv.w;
+        const long orow = (((long)b * p.Hkv + kv) * (long)p.L + j) * D + col;
+        *reinterpret_cast<uint2 *>(dK + orow) = pack_bf16x4(sk.x, sk.y, sk.z, sk.w);
+        *reinterpret_cast<uint2 *>(dV + orow) = pack_bf16x4(sv.x, sv.y, sv.z, sv.w);
     }
-    sk.x += bk.x, sk.y += bk.y, sk.z += bk.z, sk.w += bk.w;
-    sv.x += bv.x, sv.y += bv.y, sv.z += bv.z, sv.w += bv.w;
-    const long orow = (((long)b * p.Hkv + kv) * (long)p.L + j) * D + col;
-    *reinterpret_cast<uint2 *>(dK + orow) = pack_bf16x4(sk.x, sk.y, sk.z, sk.w);
-    *reinterpret_cast<uint2 *>(dV + orow) = pack_bf16x4(sv.x, sv.y, sv.z, sv.w);
 }
 
 template <int D, int KW>
@@ -863,7 +868,10 @@ int launch_dkv(const sepattn_params &p, const HeadWin &hw, bool headwise, const 
     if (hipGetLastError() != hipSuccess) return SEPATTN_ERR_HIP;
     ProfScope prof(SEPATTN_K_BWD_COMBINE, st);
     const int rows_per_block = 256 / (D / 4);
-    hipLaunchKernelGGL((dkv_combine_kernel<D>), dim3((fg.NFcap + rows_per_block - 1) / rows_per_block, p.B * p.Hkv),
+    bool every_key = false;
+    for (int i = 0; i < share.n; ++i) every_key = every_key || share.all[i] != 0;
+    const int list_rows = every_key ? fg.NFcap : (fg.NFcap + 7) / 8;
+    hipLaunchKernelGGL((dkv_combine_kernel<D>), dim3((list_rows + rows_per_block - 1) / rows_per_block, p.B * p.Hkv),
                        dim3(256), 0, st, p, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, kw, hw, share);
     return launch_status();
 }
