@@ -62,9 +62,10 @@ __device__ inline long shared_part_row(const FarGeom &even, const WorkShare &w, 
 // HW: head-wise windows.  p.n becomes the largest window of the KV head's query heads: it fixes the far / band
 // split and the schedule; in a band unit a key that is neither an initial token nor a separator is visible to
 // query i of head h only while i <= j + p.n - 1 - delta[h] (a third comparison in the blocks that need the mask
-// test).  A KV head whose heads all see every earlier key has no band: its list is that of ALL keys and its far
-// pairs are i >= j, so that this work is cut into equal slices too (as a
-// band unit the first keys' walk through the whole sequence is one workgroup's).  The workgroups are dealt to the KV heads by their work (work_share.h).
+// test).  The workgroups are dealt to the KV heads by their work (work_share.h).
+// A KV head whose query heads all see every earlier key (n >= L) may have no band (`share.all`, see list_of_all_keys):
+// its list is then that of ALL keys and its far pairs are i >= j, so that this work is cut into equal slices too; as
+// a band unit the first keys' walk through the whole sequence is one workgroup's.
 template <int D, bool DOCS, bool HW, int KW>
 __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv_kernel(
     sepattn_params p, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
@@ -120,6 +121,11 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         every_key = share.all[s.pos] != 0;
         p.n = every_key ? 0 : p.n - gdelta;
         if (every_key) n_band = 0;
+    } else if constexpr (!DOCS) {
+        if (share.all[0]) {
+            every_key = true;
+            p.n = n_band = 0;
+        }
     }
     const int kv = bkv % p.Hkv, b = bkv / p.Hkv;
     const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
@@ -765,6 +771,9 @@ __global__ __launch_bounds__(256) void dkv_combine_kernel(sepattn_params p, cons
         wpg = share.first[s.pos + 1] - share.first[s.pos];
         every_key = share.all[s.pos] != 0;
         p.n = every_key ? 0 : p.n - group_delta(hw, (bkv % p.Hkv) * (p.Hq / p.Hkv), p.Hq / p.Hkv);
+    } else if (share.all[0]) {
+        every_key = true;
+        p.n = 0;
     }
     const int kv = bkv % p.Hkv, b = bkv / p.Hkv;
     const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
@@ -818,6 +827,16 @@ __global__ __launch_bounds__(256) void dkv_combine_kernel(sepattn_params p, cons
     }
 }
 
+// Whether KV heads that see every earlier key work through the list of all keys (see dkv_kernel).  As band units their
+// work is q = units / workgroups walks per workgroup, the longest about 1 + 1/q times the mean; as slices it is even, but
+// every key's gradients pass through fp32 partials, which short walks (G L queries) don't pay for.
+// Measured, a step with n = L in us, band units against slices: 32/8 heads, d = 128, L = 8192 2814 / 2357, L = 1024 178 /
+// 112; 8/1 heads, L = 1000 277 / 88; 8 x 12 heads, d = 64, L = 300, every other one full 54 / 82 (not taken).
+inline bool list_of_all_keys(const sepattn_params &p, int wpg, const FarGeom &fg) {
+    const long units = (p.L + fg.bk - 1) / fg.bk, G = p.Hq / p.Hkv;
+    return p.cap + p.a >= p.L /* the list has to fit where the far list does */ && units <= 2 * wpg && G * p.L >= 4096;
+}
+
 template <int D, int KW>
 void launch_dkv_shape(const sepattn_params &p, const HeadWin &hw, bool headwise, const uint16_t *Q, const uint16_t *K,
                       const uint16_t *V, const float *lse2, const uint16_t *dO, const float *Dws, const int32_t *sep_idx,
@@ -846,16 +865,18 @@ int launch_dkv(const sepattn_params &p, const HeadWin &hw, bool headwise, const 
     const FarGeom fg = far_geom(p, wpg, kw);
     if ((long)wpg * p.B * p.Hkv > 0x7FFFFFFFL) return SEPATTN_ERR_SHAPE;
     WorkShare share = {};
+    const bool list_all = !doc_end && list_of_all_keys(p, wpg, fg);
     if (headwise) {
         const int G = p.Hq / p.Hkv;
         // pairs multiplied, and the start of a piece as 320 / G queries
         share = share_out(p, hw, G, wpg * p.Hkv, kIntMax, [&](int n, bool all) {
             const double L = p.L, out = L - n;
-            return all ? L * L / 2 : L * (n + fg.bk + 320. / G) + kSepShare * out * out / 2;
+            return all && list_all ? L * L / 2 : n * (L - n / 2.) + L * (fg.bk + 320. / G) + kSepShare * out * out / 2;
         });
-        // the list of all keys has to fit where the far list does
-        if (p.cap + p.a < p.L)
+        if (!list_all)
             for (int i = 0; i < share.n; ++i) share.all[i] = 0;
+    } else {
+        share.all[0] = list_all && p.n >= p.L;
     }
     {
         ProfScope prof(SEPATTN_K_BWD_DKV, st);
@@ -868,8 +889,8 @@ int launch_dkv(const sepattn_params &p, const HeadWin &hw, bool headwise, const 
     if (hipGetLastError() != hipSuccess) return SEPATTN_ERR_HIP;
     ProfScope prof(SEPATTN_K_BWD_COMBINE, st);
     const int rows_per_block = 256 / (D / 4);
-    bool every_key = false;
-    for (int i = 0; i < share.n; ++i) every_key = every_key || share.all[i] != 0;
+    bool every_key = share.all[0] != 0;
+    for (int i = 1; i < share.n; ++i) every_key = every_key || share.all[i] != 0;
     const int list_rows = every_key ? fg.NFcap : (fg.NFcap + 7) / 8;
     hipLaunchKernelGGL((dkv_combine_kernel<D>), dim3((list_rows + rows_per_block - 1) / rows_per_block, p.B * p.Hkv),
                        dim3(256), 0, st, p, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, kw, hw, share);

@@ -69,3 +69,13 @@ def test_bf16_workgroup_shapes(B, Hq, Hkv, L, d, a, n, p):
 ])
 def test_bf16_head_groups_by_work(B, Hq, Hkv, L, d, a, p, nh):
     run(B, Hq, Hkv, L, d, a, nh, p, "bf16")
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,d,a,n,p", [
+    (1, 8, 1, 512, 128, 4, 512, 0.1),    # the shortest sequence whose keys are all listed
+    (1, 8, 1, 511, 128, 4, 511, 0.1),    # one key fewer: band units
+    (2, 8, 2, 1101, 64, 0, 4000, 0.0),   # a last list tile of 13 keys; no separators; a window beyond the sequence
+    (1, 4, 1, 8200, 128, 4, 8200, 0.05),  # eight-wave workgroups
+])
+def test_bf16_windows_of_the_whole_sequence(B, Hq, Hkv, L, d, a, n, p):
+    run(B, Hq, Hkv, L, d, a, n, p, "bf16")
