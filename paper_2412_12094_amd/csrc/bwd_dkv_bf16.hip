@@ -181,17 +181,19 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
     // Slices.  Where the band units do not divide among the workgroups, the first `heavy` have one more than the others,
     // and far work goes to those others first, as much as a band unit costs (in items, with its start).  Without that
     // a workgroup with two units and a full slice sets the time where most have one unit (28/4 heads, 3 x L=3077,
-    // 49 units on 42 workgroups: 190 us, 174 with it).  No slice is shorter than kMinSlice steps: the start of a piece and the
+    // 49 units on 42 workgroups: 190 us, 174 with it).  No slice is shorter than min_slice, the steps of a
+    // band unit up to 16: the start of a piece and the
     // sum of many partials would cost more than the items (8/2 heads, L = 600: 29 + 12.6 us with slices of one
     // item, 22 + 4 now).  The slices that are not empty belong to consecutive workgroups, which is what the combine
     // kernel relies on.
-    constexpr int kMinSlice = 16, kUnitStart = 8;  // steps of 32 query rows
+    constexpr int kUnitStart = 8;  // steps of 32 query rows
+    const int unit_steps = G * ((p.n + 30) / 32 + 1), min_slice = (every_key ? 16 : min(max(unit_steps, 4), 16)) / BPT;
     const int heavy = n_band % wpg, light = wpg - heavy;
-    const long unit_items = ((long)G * ((p.n + 30) / 32 + 1) + kUnitStart) / BPT;
+    const long unit_items = ((long)unit_steps + kUnitStart) / BPT;
     long per_heavy = heavy ? max((far_total - unit_items * light) / wpg, 0l) : 0;
-    if (per_heavy < kMinSlice / BPT) per_heavy = 0;
+    if (per_heavy < min_slice) per_heavy = 0;
     const long far_light = far_total - per_heavy * heavy;
-    const long n_light = min(max(far_light / (kMinSlice / BPT), 1l), (long)light);
+    const long n_light = min(max(far_light / min_slice, 1l), (long)light);
     const int w_light = w_id - heavy;
     const long s0 = w_light < 0 ? w_id * per_heavy : per_heavy * heavy + min((long)w_light, n_light) * far_light / n_light;
     const long s1 = w_light < 0 ? s0 + per_heavy : per_heavy * heavy + min(w_light + 1l, n_light) * far_light / n_light;
