@@ -296,6 +296,18 @@ PyObject *doc_bounds(PyObject *const *a) {
 // heads' windows, or the documents' bounds (nh / ds, de).
 enum Form { kPlain, kHeadwise, kPacked };
 
+// the documents' bounds of a packed call: the kernels read a row of L entries for every row of the batch
+struct DocBounds {
+    const int32_t *start, *end;
+    DocBounds(PyObject *so, PyObject *eo, const sepattn_params &p) {
+        const at::Tensor &s = dev(so), &e = dev(eo);
+        require(s.scalar_type() == at::kInt && e.scalar_type() == at::kInt && s.dim() == 2 && s.size(0) == p.B &&
+                    s.size(1) == p.L && e.sizes() == s.sizes(), "doc_start, doc_end: int32 [B, L]");
+        start = i32(s);
+        end = i32(e);
+    }
+};
+
 // forward(Q, K, V, sep_idx, sep_count, sep_prefix, a, n | n_per_head, scale, out, ws [, doc_start, doc_end])
 template <Form F>
 PyObject *forward(PyObject *const *a) {
@@ -310,11 +322,8 @@ PyObject *forward(PyObject *const *a) {
         require((int)nh.size() == p.Hq, "n_per_head: one window per query head");
     }
     if constexpr (F == kPacked) {
-        const at::Tensor &s = dev(a[11]), &e = dev(a[12]);
-        require(s.scalar_type() == at::kInt && e.scalar_type() == at::kInt && s.dim() == 2 && s.size(0) == p.B &&
-                    s.size(1) == p.L && e.sizes() == s.sizes(), "doc_start, doc_end: int32 [B, L]");
-        ds = i32(s);
-        de = i32(e);
+        const DocBounds d(a[11], a[12], p);
+        ds = d.start, de = d.end;
     }
     at::Tensor O, LSE;
     PyObject *po = nullptr, *pl = nullptr;
@@ -368,10 +377,8 @@ PyObject *backward(PyObject *const *a) {
         require((int)nh.size() == p.Hq, "n_per_head: one window per query head");
     }
     if constexpr (F == kPacked) {
-        const at::Tensor &s = dev(a[14]), &e = dev(a[15]);
-        require(s.scalar_type() == at::kInt && e.scalar_type() == at::kInt, "doc_start, doc_end: int32 [B, L]");
-        ds = i32(s);
-        de = i32(e);
+        const DocBounds d(a[14], a[15], p);
+        ds = d.start, de = d.end;
     }
     at::Tensor g[3];
     PyObject *po[3] = {nullptr, nullptr, nullptr};
