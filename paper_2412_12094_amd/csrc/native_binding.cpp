@@ -114,19 +114,32 @@ std::vector<int32_t> int_list(PyObject *o) {
     Py_DECREF(seq);
     return v;
 }
-// the N tensors of an `out` argument
+// The N tensors of an `out` argument, which may be any iterable; None: the call allocates its own.  The items
+// are held until the call has returned: an iterator that made them is no longer their owner.
 template <int N>
 struct Out {
-    PyObject *o[N];
-    explicit Out(PyObject *seq) {
-        PyObject *fast = PySequence_Fast(seq, "out: a tuple of tensors is expected");
-        if (!fast) throw Failed{};
-        const bool ok = PySequence_Fast_GET_SIZE(fast) == N;
-        for (int k = 0; ok && k < N; ++k) o[k] = PySequence_Fast_GET_ITEM(fast, k);  // kept alive by the caller's sequence
-        Py_DECREF(fast);
-        if (!ok) fail(PyExc_ValueError, "out: wrong number of tensors");
+    PyObject *items = nullptr;  // a tuple
+    explicit Out(PyObject *o) {
+        if (o == Py_None) return;
+        items = PySequence_Tuple(o);
+        if (!items) throw Failed{};
+        if (PyTuple_GET_SIZE(items) == N) return;
+        Py_DECREF(items);
+        fail(PyExc_ValueError, "out: wrong number of tensors");
     }
-    PyObject *operator[](int k) const { return o[k]; }
+    ~Out() { Py_XDECREF(items); }
+    Out(const Out &) = delete;
+    Out &operator=(const Out &) = delete;
+    bool given() const { return items != nullptr; }
+    PyObject *operator[](int k) const { return PyTuple_GET_ITEM(items, k); }
+};
+// a reference that this call owns
+struct Owned {
+    PyObject *o;
+    explicit Owned(PyObject *x) : o(x) {}
+    ~Owned() { Py_DECREF(o); }
+    Owned(const Owned &) = delete;
+    Owned &operator=(const Owned &) = delete;
 };
 void check(const char *fn, int rc) {
     if (rc == SEPATTN_OK) return;
@@ -218,14 +231,14 @@ PyObject *compact_indices(PyObject *const *a) {
     const int B = (int)sep.size(0), L = (int)sep.size(1);
     const Workspace ws(a[5], lib.sepattn_compact_workspace_bytes(B, L), sep.device());
     void *st = stream_of(sep);
-    if (a[4] == Py_None) {
+    const Out<3> out(a[4]);
+    if (!out.given()) {
         const IndexOut o(B, L, a[1], PyObject_IsTrue(a[2]) == 1, as_int(a[3]), sep.device());
         check("sepattn_compact_indices",
               lib.sepattn_compact_indices((const uint8_t *)ptr(sep), B, L, (int32_t *)ptr(o.idx), o.cap, (int32_t *)ptr(o.cnt),
                                           o.prefix(), ws.p, ws.bytes, st));
         return tuple_of(wrap(o.idx), wrap(o.cnt), o.prefix_object());
     }
-    const Out<3> out(a[4]);
     const at::Tensor &idx = dev(out[0]);
     dev(out[1]);
     if (out[2] != Py_None) dev(out[2]);
@@ -243,7 +256,8 @@ PyObject *mark_compact(PyObject *const *a) {
     const std::vector<int32_t> ids = int_list(a[1]);
     const Workspace ws(a[6], lib.sepattn_compact_workspace_bytes(B, L), tok.device());
     void *st = stream_of(tok);
-    if (a[5] == Py_None) {
+    const Out<4> out(a[5]);
+    if (!out.given()) {
         at::Tensor sep = empty({B, L}, at::kByte, tok.device());
         const IndexOut o(B, L, a[2], PyObject_IsTrue(a[3]) == 1, as_int(a[4]), tok.device());
         check("sepattn_mark_compact",
@@ -251,7 +265,6 @@ PyObject *mark_compact(PyObject *const *a) {
                                        o.cap, (int32_t *)ptr(o.cnt), o.prefix(), ws.p, ws.bytes, st));
         return tuple_of(wrap(std::move(sep)), wrap(o.idx), wrap(o.cnt), o.prefix_object());
     }
-    const Out<4> out(a[5]);
     dev(out[0]);
     const at::Tensor &idx = dev(out[1]);
     dev(out[2]);
@@ -268,27 +281,20 @@ PyObject *doc_bounds(PyObject *const *a) {
     if (a[3] != Py_None) dev(a[3]);
     require(cu.scalar_type() == at::kInt && cu.dim() == 1, "cu_seqlens: int32 [n_docs + 1]");
     const int L = as_int(a[1]);
-    PyObject *res;
-    void *ds, *de;
-    if (a[4] == Py_None) {
-        at::Tensor s = empty({L}, at::kInt, cu.device()), e = empty({L}, at::kInt, cu.device());
-        ds = ptr(s);
-        de = ptr(e);
-        res = tuple_of(wrap(std::move(s)), wrap(std::move(e)));
-    } else {
-        const Out<2> out(a[4]);
-        ds = ptr(dev(out[0]));
-        de = ptr(dev(out[1]));
-        res = keep(a[4]);
+    const int n_docs = (int)cu.numel() - 1, init = as_int(a[2]);
+    // `out` itself is returned, so it has to be a sequence; items beyond the two are left alone
+    PyObject *first = a[4] == Py_None ? keep(Py_None) : PySequence_GetSlice(a[4], 0, 2);
+    if (!first) throw Failed{};
+    const Out<2> out(Owned(first).o);
+    at::Tensor s, e;
+    if (!out.given()) {
+        s = empty({L}, at::kInt, cu.device());
+        e = empty({L}, at::kInt, cu.device());
     }
-    try {
-        check("sepattn_doc_bounds", lib.sepattn_doc_bounds(i32(cu), (int)cu.numel() - 1, L, as_int(a[2]), (int32_t *)ds,
-                                                           (int32_t *)de, (uint8_t *)ptr(a[3]), stream_of(cu)));
-    } catch (...) {
-        Py_DECREF(res);
-        throw;
-    }
-    return res;
+    int32_t *ds = (int32_t *)ptr(out.given() ? dev(out[0]) : s), *de = (int32_t *)ptr(out.given() ? dev(out[1]) : e);
+    check("sepattn_doc_bounds", lib.sepattn_doc_bounds(i32(cu), n_docs, L, init, ds, de, (uint8_t *)ptr(a[3]), stream_of(cu)));
+    if (out.given()) return keep(a[4]);
+    return tuple_of(wrap(std::move(s)), wrap(std::move(e)));
 }
 
 // ---- attention -------------------------------------------------------------------------------------
@@ -325,21 +331,14 @@ PyObject *forward(PyObject *const *a) {
         const DocBounds d(a[11], a[12], p);
         ds = d.start, de = d.end;
     }
+    const Out<2> out(a[9]);
     at::Tensor O, LSE;
-    PyObject *po = nullptr, *pl = nullptr;
-    void *optr;
-    float *lse;
-    if (a[9] == Py_None) {
+    if (!out.given()) {
         O = fresh_like(Q);
         LSE = empty({p.B, p.Hq, p.L}, at::kFloat, Q.device());
-        optr = ptr(O);
-        lse = (float *)ptr(LSE);
-    } else {
-        const Out<2> out(a[9]);
-        po = out[0], pl = out[1];
-        optr = ptr(po);
-        lse = (float *)ptr(pl);
     }
+    void *optr = out.given() ? ptr(out[0]) : ptr(O);
+    float *lse = (float *)(out.given() ? ptr(out[1]) : ptr(LSE));
     // (the bf16 forward needs no workspace; the query keeps this right if that changes)
     const size_t need = lib.sepattn_forward_workspace_bytes(&p);
     at::Tensor own;
@@ -360,7 +359,7 @@ PyObject *forward(PyObject *const *a) {
     else
         check("sepattn_forward_packed", lib.sepattn_forward_packed(&p, ds, de, ptr(Q), ptr(K), ptr(V), i32(idx), i32(cnt), i32(pre),
                                                                    optr, lse, wp, wb, st));
-    if (po) return tuple_of(keep(po), keep(pl));
+    if (out.given()) return tuple_of(keep(out[0]), keep(out[1]));
     return tuple_of(wrap(std::move(O)), wrap(std::move(LSE)));
 }
 
@@ -380,21 +379,15 @@ PyObject *backward(PyObject *const *a) {
         const DocBounds d(a[14], a[15], p);
         ds = d.start, de = d.end;
     }
+    const Out<3> out(a[12]);
     at::Tensor g[3];
-    PyObject *po[3] = {nullptr, nullptr, nullptr};
-    void *gp[3];
-    if (a[12] == Py_None) {
+    if (!out.given()) {
         g[0] = fresh_like(Q);
         g[1] = fresh_like(K);
         g[2] = fresh_like(V);
-        for (int k = 0; k < 3; ++k) gp[k] = ptr(g[k]);
-    } else {
-        const Out<3> out(a[12]);
-        for (int k = 0; k < 3; ++k) {
-            po[k] = out[k];
-            gp[k] = ptr(po[k]);
-        }
     }
+    void *gp[3];
+    for (int k = 0; k < 3; ++k) gp[k] = out.given() ? ptr(out[k]) : ptr(g[k]);
     size_t need = 0;
     if (a[13] == Py_None)
         need = F == kHeadwise ? lib.sepattn_backward_headwise_workspace_bytes(&p, nh.data()) : lib.sepattn_backward_workspace_bytes(&p);
@@ -412,7 +405,7 @@ PyObject *backward(PyObject *const *a) {
         check("sepattn_backward_packed",
               lib.sepattn_backward_packed(&p, ds, de, ptr(Q), ptr(K), ptr(V), ptr(O), lse, ptr(dO), i32(idx), i32(cnt), i32(pre),
                                           gp[0], gp[1], gp[2], ws.p, ws.bytes, st));
-    if (po[0]) return tuple_of(keep(po[0]), keep(po[1]), keep(po[2]));
+    if (out.given()) return tuple_of(keep(out[0]), keep(out[1]), keep(out[2]));
     return tuple_of(wrap(std::move(g[0])), wrap(std::move(g[1])), wrap(std::move(g[2])));
 }
 
@@ -451,22 +444,15 @@ PyObject *decode(PyObject *const *a) {
                 "rope_table: fp32 [n_pos, 2, d/2]");
     sepkv_params p = kv_params(Kc, (int)q.size(0), (int)q.size(1), as_int(a[5]), as_int(a[6]), as_int(a[7]), as_float(a[8]));
     p.d = (int)q.size(2);
+    const Out<2> out(a[9]);
     at::Tensor o, lse;
-    PyObject *po = nullptr, *pl = nullptr;
-    void *optr;
-    float *lptr;
-    if (a[9] == Py_None) {
+    if (!out.given()) {
         if (NOALLOC) fail(PyExc_TypeError, "out is required");
         o = fresh_like(q);
         lse = empty({p.S, p.Hq}, at::kFloat, q.device());
-        optr = ptr(o);
-        lptr = (float *)ptr(lse);
-    } else {
-        const Out<2> out(a[9]);
-        po = out[0], pl = out[1];
-        optr = ptr(po);
-        lptr = (float *)ptr(pl);  // None: no LSE wanted
     }
+    void *optr = out.given() ? ptr(out[0]) : ptr(o);
+    float *lptr = (float *)(out.given() ? ptr(out[1]) : ptr(lse));  // an item None: no LSE wanted
     void *st = stream_of(q);
     if constexpr (NOALLOC) {
         check("sepattn_decode_noalloc",
@@ -481,7 +467,7 @@ PyObject *decode(PyObject *const *a) {
             check("sepattn_decode",
                   lib.sepattn_decode(&p, ptr(q), ptr(Kc), ptr(Vc), i32(sizes), optr, lptr, ws.p, ws.bytes, st));
     }
-    if (po) return tuple_of(keep(po), keep(pl));
+    if (out.given()) return tuple_of(keep(out[0]), keep(out[1]));
     return tuple_of(wrap(std::move(o)), wrap(std::move(lse)));
 }
 
@@ -516,28 +502,26 @@ PyObject *fill_from_prefill(PyObject *const *a) {
     const int L = K.dim() == 4 ? (int)K.size(2) : 0, nw = as_int(a[10]);
     sepkv_params p = kv_params(K, (int)K.size(0), as_int(a[5]), as_int(a[6]), as_int(a[7]), as_int(a[8]), 1.0f);
     p.c = as_int(a[9]);
+    const Out<4> out(a[11]);
     at::Tensor Kc, Vc, flags, sizes;
-    PyObject *po[4] = {nullptr, nullptr, nullptr, nullptr};
-    if (a[11] == Py_None) {
+    if (!out.given()) {
         // freshly allocated outputs are zero where the call leaves them alone
         Kc = empty({p.S, p.Hkv, p.c, p.d}, K.scalar_type(), K.device()).zero_();
         Vc = empty({p.S, p.Hkv, p.c, p.d}, K.scalar_type(), K.device()).zero_();
         flags = empty({p.S, p.c - p.a - p.s}, at::kByte, K.device()).zero_();
         sizes = empty({p.S, SEPKV_SIZES_COLS}, at::kInt, K.device()).zero_();
     } else {
-        const Out<4> out(a[11]);
-        for (int k = 0; k < 4; ++k) po[k] = out[k];
-        Kc = dev(po[0]);
-        Vc = dev(po[1]);
-        flags = dev(po[2]);
-        sizes = dev(po[3]);
+        Kc = dev(out[0]);
+        Vc = dev(out[1]);
+        flags = dev(out[2]);
+        sizes = dev(out[3]);
         require(sizes.scalar_type() == at::kInt && sizes.dim() == 2 && sizes.size(0) == p.S && sizes.size(1) == SEPKV_SIZES_COLS,
                 "sizes: int32 [S, 6]");
     }
     check("sepkv_fill_from_prefill",
           lib.sepkv_fill_from_prefill(&p, L, nw, ptr(K), ptr(V), (const uint8_t *)ptr(sep), i32(idx), (int)idx.size(1), i32(pre),
                                       ptr(Kc), ptr(Vc), (uint8_t *)ptr(flags), (int32_t *)ptr(sizes), stream_of(K)));
-    if (po[0]) return tuple_of(keep(po[0]), keep(po[1]), keep(po[2]), keep(po[3]));
+    if (out.given()) return tuple_of(keep(out[0]), keep(out[1]), keep(out[2]), keep(out[3]));
     return tuple_of(wrap(std::move(Kc)), wrap(std::move(Vc)), wrap(std::move(flags)), wrap(std::move(sizes)));
 }
 

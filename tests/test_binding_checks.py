@@ -56,3 +56,53 @@ def test_packed_bounds_are_int32(bd, call):
             bd.sepattn_forward_packed(q, k, k, *bounds, *index, 4, 0.1, NEW, NEW)
         else:
             bd.sepattn_backward_packed(q, k, k, q, lse, q, *bounds, *index, 4, 0.1, NEW, NEW)
+
+
+class Watched:
+    """Not a tensor; logs when its type is looked at and when it is released."""
+
+    def __init__(self, log):
+        self.log = log
+
+    @property
+    def __class__(self):
+        self.log.append("looked at")
+        return object
+
+    def __del__(self):
+        self.log.append("released")
+
+
+def cache_call():
+    q, Kc = fake(1, HQ, D, dtype=torch.bfloat16), fake(1, HKV, 32, D, dtype=torch.bfloat16)
+    return q, Kc, Kc, fake(1, 6), 4, 8, 8, 0.1
+
+
+@pytest.mark.parametrize("make", [tuple, list, iter, lambda items: (x for x in items)])
+def test_outputs_live_until_the_call_returns(bd, make):
+    """`out` may be any iterable, and it may be the only owner of its items."""
+    log = []
+    with pytest.raises(TypeError, match="tensor") as err:
+        bd.sepattn_decode_noalloc(*cache_call(), make(Watched(log) for _ in range(2)))
+    assert log[0] == "looked at"
+    del err  # (the traceback's frames hold a tuple or a list)
+    assert log[-2:] == ["released"] * 2 and log.count("released") == 2
+
+
+@pytest.mark.parametrize("n", [0, 1, 3])
+def test_outputs_are_counted(bd, n):
+    q, k, lse, index = attention()
+    with pytest.raises(ValueError):
+        bd.sepattn_forward(q, k, k, *index, 1, 4, 0.1, (q,) * n)
+    with pytest.raises(TypeError):
+        bd.sepattn_forward(q, k, k, *index, 1, 4, 0.1, 3)
+
+
+def test_document_bounds_take_a_sequence(bd):
+    cu, row = fake(3), fake(L, dtype=torch.int64)
+    with pytest.raises(TypeError):  # an iterator would come back exhausted
+        bd.sepattn_doc_bounds(cu, L, 2, None, iter((row, row)))
+    with pytest.raises(ValueError, match="number of tensors"):
+        bd.sepattn_doc_bounds(cu, L, 2, None, (row,))
+    with pytest.raises(ValueError, match="GPU"):  # taken apart; refused for what the second item is
+        bd.sepattn_doc_bounds(cu, L, 2, None, [row, fake(L, device="cpu"), row])
