@@ -147,22 +147,34 @@ void check(const char *fn, int rc) {
     Py_XDECREF(r);
     throw Failed{};
 }
+// What a call allocates and enqueues runs without the interpreter lock: the allocator may wait for the device, a
+// launch for a place in a full queue, and other Python threads go on meanwhile.  Arguments are taken apart before
+// (no Python object is touched inside), results wrapped afterwards.
+template <typename F>
+auto unlocked(F f) {
+    struct Lock {
+        PyThreadState *state = PyEval_SaveThread();
+        ~Lock() { PyEval_RestoreThread(state); }
+    } lock;
+    return f();
+}
 // the caller's workspace, or one from torch's allocator that goes back when the call returns (the
 // allocator hands it out again in stream order)
 struct Workspace {
     at::Tensor own;
-    void *p;
-    size_t bytes;
-    Workspace(PyObject *ws, size_t need, const at::Device &device) {
-        if (ws != Py_None) {
-            const at::Tensor &t = tensor(ws);
-            p = t.data_ptr();
-            bytes = (size_t)t.numel();
-        } else {
-            bytes = need < 256 ? 256 : need;
-            own = empty({(int64_t)bytes}, at::kByte, device);
-            p = own.data_ptr();
-        }
+    void *p = nullptr;
+    size_t bytes = 0;
+    bool given;
+    explicit Workspace(PyObject *ws) : given(ws != Py_None) {
+        if (!given) return;
+        const at::Tensor &t = tensor(ws);
+        p = t.data_ptr();
+        bytes = (size_t)t.numel();
+    }
+    void allocate(size_t need, const at::Device &device) {
+        bytes = need < 256 ? 256 : need;
+        own = empty({(int64_t)bytes}, at::kByte, device);
+        p = own.data_ptr();
     }
 };
 PyObject *wrap(at::Tensor t) { return THPVariable_Wrap(std::move(t)); }
@@ -202,25 +214,45 @@ PyObject *mark_separators(PyObject *const *a) {
     require(tok.scalar_type() == at::kInt && tok.dim() == 2, "token_ids: int32 [B, L]");
     const int B = (int)tok.size(0), L = (int)tok.size(1);
     const std::vector<int32_t> ids = int_list(a[1]);
-    at::Tensor out = a[2] == Py_None ? empty({B, L}, at::kByte, tok.device()) : tensor(a[2]);
-    check("sepattn_mark_separators", lib.sepattn_mark_separators(i32(tok), B, L, ids.data(), (int)ids.size(),
-                                                                 (uint8_t *)ptr(out), stream_of(tok)));
+    at::Tensor out;
+    if (a[2] != Py_None) out = tensor(a[2]);
+    check("sepattn_mark_separators", unlocked([&] {
+              if (!out.defined()) out = empty({B, L}, at::kByte, tok.device());
+              return lib.sepattn_mark_separators(i32(tok), B, L, ids.data(), (int)ids.size(), (uint8_t *)ptr(out), stream_of(tok));
+          }));
     return a[2] == Py_None ? wrap(std::move(out)) : keep(a[2]);
 }
 
-// index arrays of a call that allocates its own: every entry of the list that is not written is `fill`
+// Index arrays, the caller's or (`allocate`) the call's own, where every entry of the list that is not written is
+// `fill`.  Arguments: the last three of `out`, cap, want_prefix, fill.
 struct IndexOut {
     at::Tensor idx, cnt, pre;
-    int cap;
-    IndexOut(int B, int L, PyObject *cap_o, bool want_prefix, int fill, const at::Device &device) {
-        cap = cap_o == Py_None ? L : as_int(cap_o);
-        const int64_t pitch = cap > 1 ? cap : 1;
-        idx = empty({B, pitch}, at::kInt, device);
+    int cap = 0, fill = 0;
+    bool want_prefix = false;
+    int32_t *idx_p = nullptr, *cnt_p = nullptr, *pre_p = nullptr;
+    template <int N>
+    IndexOut(const Out<N> &out, int L, PyObject *cap_o, PyObject *want_prefix_o, PyObject *fill_o) {
+        if (out.given()) {
+            const at::Tensor &i = dev(out[N - 3]);
+            cap = (int)i.size(1);
+            idx_p = (int32_t *)ptr(i);
+            cnt_p = (int32_t *)ptr(dev(out[N - 2]));
+            pre_p = out[N - 1] == Py_None ? nullptr : (int32_t *)ptr(dev(out[N - 1]));
+        } else {
+            cap = cap_o == Py_None ? L : as_int(cap_o);
+            want_prefix = PyObject_IsTrue(want_prefix_o) == 1;
+            fill = as_int(fill_o);
+        }
+    }
+    void allocate(int B, int L, const at::Device &device) {
+        idx = empty({B, cap > 1 ? cap : 1}, at::kInt, device);
         idx.fill_(fill);
         cnt = empty({B}, at::kInt, device);
-        if (want_prefix) pre = empty({B, L + 1}, at::kInt, device);
+        idx_p = (int32_t *)ptr(idx), cnt_p = (int32_t *)ptr(cnt);
+        if (!want_prefix) return;
+        pre = empty({B, L + 1}, at::kInt, device);
+        pre_p = (int32_t *)ptr(pre);
     }
-    int32_t *prefix() const { return pre.defined() ? (int32_t *)pre.data_ptr() : nullptr; }
     PyObject *prefix_object() const { return pre.defined() ? wrap(pre) : keep(Py_None); }
 };
 
@@ -229,23 +261,17 @@ PyObject *compact_indices(PyObject *const *a) {
     const at::Tensor &sep = dev(a[0]);
     require(sep.scalar_type() == at::kByte && sep.dim() == 2, "is_sep: uint8 [B, L]");
     const int B = (int)sep.size(0), L = (int)sep.size(1);
-    const Workspace ws(a[5], lib.sepattn_compact_workspace_bytes(B, L), sep.device());
-    void *st = stream_of(sep);
     const Out<3> out(a[4]);
-    if (!out.given()) {
-        const IndexOut o(B, L, a[1], PyObject_IsTrue(a[2]) == 1, as_int(a[3]), sep.device());
-        check("sepattn_compact_indices",
-              lib.sepattn_compact_indices((const uint8_t *)ptr(sep), B, L, (int32_t *)ptr(o.idx), o.cap, (int32_t *)ptr(o.cnt),
-                                          o.prefix(), ws.p, ws.bytes, st));
-        return tuple_of(wrap(o.idx), wrap(o.cnt), o.prefix_object());
-    }
-    const at::Tensor &idx = dev(out[0]);
-    dev(out[1]);
-    if (out[2] != Py_None) dev(out[2]);
-    check("sepattn_compact_indices",
-          lib.sepattn_compact_indices((const uint8_t *)ptr(sep), B, L, (int32_t *)ptr(idx), (int)idx.size(1),
-                                      (int32_t *)ptr(out[1]), (int32_t *)ptr(out[2]), ws.p, ws.bytes, st));
-    return tuple_of(keep(out[0]), keep(out[1]), keep(out[2]));
+    IndexOut o(out, L, a[1], a[2], a[3]);
+    Workspace ws(a[5]);
+    check("sepattn_compact_indices", unlocked([&] {
+              if (!ws.given) ws.allocate(lib.sepattn_compact_workspace_bytes(B, L), sep.device());
+              if (!out.given()) o.allocate(B, L, sep.device());
+              return lib.sepattn_compact_indices((const uint8_t *)ptr(sep), B, L, o.idx_p, o.cap, o.cnt_p, o.pre_p, ws.p, ws.bytes,
+                                                 stream_of(sep));
+          }));
+    if (out.given()) return tuple_of(keep(out[0]), keep(out[1]), keep(out[2]));
+    return tuple_of(wrap(o.idx), wrap(o.cnt), o.prefix_object());
 }
 
 // mark_compact(token_ids, sep_ids, cap, want_prefix, fill, out, ws)
@@ -254,25 +280,22 @@ PyObject *mark_compact(PyObject *const *a) {
     require(tok.scalar_type() == at::kInt && tok.dim() == 2, "token_ids: int32 [B, L]");
     const int B = (int)tok.size(0), L = (int)tok.size(1);
     const std::vector<int32_t> ids = int_list(a[1]);
-    const Workspace ws(a[6], lib.sepattn_compact_workspace_bytes(B, L), tok.device());
-    void *st = stream_of(tok);
     const Out<4> out(a[5]);
-    if (!out.given()) {
-        at::Tensor sep = empty({B, L}, at::kByte, tok.device());
-        const IndexOut o(B, L, a[2], PyObject_IsTrue(a[3]) == 1, as_int(a[4]), tok.device());
-        check("sepattn_mark_compact",
-              lib.sepattn_mark_compact(i32(tok), B, L, ids.data(), (int)ids.size(), (uint8_t *)ptr(sep), (int32_t *)ptr(o.idx),
-                                       o.cap, (int32_t *)ptr(o.cnt), o.prefix(), ws.p, ws.bytes, st));
-        return tuple_of(wrap(std::move(sep)), wrap(o.idx), wrap(o.cnt), o.prefix_object());
-    }
-    dev(out[0]);
-    const at::Tensor &idx = dev(out[1]);
-    dev(out[2]);
-    if (out[3] != Py_None) dev(out[3]);
-    check("sepattn_mark_compact",
-          lib.sepattn_mark_compact(i32(tok), B, L, ids.data(), (int)ids.size(), (uint8_t *)ptr(out[0]), (int32_t *)ptr(idx),
-                                   (int)idx.size(1), (int32_t *)ptr(out[2]), (int32_t *)ptr(out[3]), ws.p, ws.bytes, st));
-    return tuple_of(keep(out[0]), keep(out[1]), keep(out[2]), keep(out[3]));
+    at::Tensor sep;
+    if (out.given()) sep = dev(out[0]);
+    IndexOut o(out, L, a[2], a[3], a[4]);
+    Workspace ws(a[6]);
+    check("sepattn_mark_compact", unlocked([&] {
+              if (!ws.given) ws.allocate(lib.sepattn_compact_workspace_bytes(B, L), tok.device());
+              if (!out.given()) {
+                  sep = empty({B, L}, at::kByte, tok.device());
+                  o.allocate(B, L, tok.device());
+              }
+              return lib.sepattn_mark_compact(i32(tok), B, L, ids.data(), (int)ids.size(), (uint8_t *)ptr(sep), o.idx_p, o.cap,
+                                              o.cnt_p, o.pre_p, ws.p, ws.bytes, stream_of(tok));
+          }));
+    if (out.given()) return tuple_of(keep(out[0]), keep(out[1]), keep(out[2]), keep(out[3]));
+    return tuple_of(wrap(std::move(sep)), wrap(o.idx), wrap(o.cnt), o.prefix_object());
 }
 
 // doc_bounds(cu_seqlens, L, a, is_sep_row, out)
@@ -287,12 +310,18 @@ PyObject *doc_bounds(PyObject *const *a) {
     if (!first) throw Failed{};
     const Out<2> out(Owned(first).o);
     at::Tensor s, e;
-    if (!out.given()) {
-        s = empty({L}, at::kInt, cu.device());
-        e = empty({L}, at::kInt, cu.device());
+    if (out.given()) {
+        s = dev(out[0]);
+        e = dev(out[1]);
     }
-    int32_t *ds = (int32_t *)ptr(out.given() ? dev(out[0]) : s), *de = (int32_t *)ptr(out.given() ? dev(out[1]) : e);
-    check("sepattn_doc_bounds", lib.sepattn_doc_bounds(i32(cu), n_docs, L, init, ds, de, (uint8_t *)ptr(a[3]), stream_of(cu)));
+    uint8_t *row = (uint8_t *)ptr(a[3]);
+    check("sepattn_doc_bounds", unlocked([&] {
+              if (!out.given()) {
+                  s = empty({L}, at::kInt, cu.device());
+                  e = empty({L}, at::kInt, cu.device());
+              }
+              return lib.sepattn_doc_bounds(i32(cu), n_docs, L, init, (int32_t *)ptr(s), (int32_t *)ptr(e), row, stream_of(cu));
+          }));
     if (out.given()) return keep(a[4]);
     return tuple_of(wrap(std::move(s)), wrap(std::move(e)));
 }
@@ -333,32 +362,30 @@ PyObject *forward(PyObject *const *a) {
     }
     const Out<2> out(a[9]);
     at::Tensor O, LSE;
-    if (!out.given()) {
-        O = fresh_like(Q);
-        LSE = empty({p.B, p.Hq, p.L}, at::kFloat, Q.device());
-    }
-    void *optr = out.given() ? ptr(out[0]) : ptr(O);
-    float *lse = (float *)(out.given() ? ptr(out[1]) : ptr(LSE));
-    // (the bf16 forward needs no workspace; the query keeps this right if that changes)
-    const size_t need = lib.sepattn_forward_workspace_bytes(&p);
-    at::Tensor own;
-    void *wp = nullptr;
-    size_t wb = 0;
-    if (a[10] != Py_None || need > 0) {
-        const Workspace ws(a[10], need, Q.device());
-        own = ws.own;
-        wp = ws.p;
-        wb = ws.bytes;
-    }
-    void *st = stream_of(Q);
-    if constexpr (F == kPlain)
-        check("sepattn_forward", lib.sepattn_forward(&p, ptr(Q), ptr(K), ptr(V), i32(idx), i32(cnt), i32(pre), optr, lse, wp, wb, st));
-    else if constexpr (F == kHeadwise)
-        check("sepattn_forward_headwise", lib.sepattn_forward_headwise(&p, nh.data(), ptr(Q), ptr(K), ptr(V), i32(idx), i32(cnt),
-                                                                       i32(pre), optr, lse, wp, wb, st));
-    else
-        check("sepattn_forward_packed", lib.sepattn_forward_packed(&p, ds, de, ptr(Q), ptr(K), ptr(V), i32(idx), i32(cnt), i32(pre),
-                                                                   optr, lse, wp, wb, st));
+    void *optr = nullptr, *lptr = nullptr;
+    if (out.given()) optr = ptr(out[0]), lptr = ptr(out[1]);
+    Workspace ws(a[10]);
+    constexpr const char *name = F == kPlain ? "sepattn_forward" : (F == kHeadwise ? "sepattn_forward_headwise" : "sepattn_forward_packed");
+    check(name, unlocked([&] {
+              if (!out.given()) {
+                  O = fresh_like(Q);
+                  LSE = empty({p.B, p.Hq, p.L}, at::kFloat, Q.device());
+                  optr = ptr(O), lptr = ptr(LSE);
+              }
+              // (the forward needs no workspace; the query keeps this right if that changes)
+              const size_t need = lib.sepattn_forward_workspace_bytes(&p);
+              if (!ws.given && need > 0) ws.allocate(need, Q.device());
+              float *lse = (float *)lptr;
+              void *st = stream_of(Q);
+              if constexpr (F == kPlain)
+                  return lib.sepattn_forward(&p, ptr(Q), ptr(K), ptr(V), i32(idx), i32(cnt), i32(pre), optr, lse, ws.p, ws.bytes, st);
+              else if constexpr (F == kHeadwise)
+                  return lib.sepattn_forward_headwise(&p, nh.data(), ptr(Q), ptr(K), ptr(V), i32(idx), i32(cnt), i32(pre), optr, lse,
+                                                      ws.p, ws.bytes, st);
+              else
+                  return lib.sepattn_forward_packed(&p, ds, de, ptr(Q), ptr(K), ptr(V), i32(idx), i32(cnt), i32(pre), optr, lse, ws.p,
+                                                    ws.bytes, st);
+          }));
     if (out.given()) return tuple_of(keep(out[0]), keep(out[1]));
     return tuple_of(wrap(std::move(O)), wrap(std::move(LSE)));
 }
@@ -381,30 +408,32 @@ PyObject *backward(PyObject *const *a) {
     }
     const Out<3> out(a[12]);
     at::Tensor g[3];
-    if (!out.given()) {
-        g[0] = fresh_like(Q);
-        g[1] = fresh_like(K);
-        g[2] = fresh_like(V);
-    }
     void *gp[3];
-    for (int k = 0; k < 3; ++k) gp[k] = out.given() ? ptr(out[k]) : ptr(g[k]);
-    size_t need = 0;
-    if (a[13] == Py_None)
-        need = F == kHeadwise ? lib.sepattn_backward_headwise_workspace_bytes(&p, nh.data()) : lib.sepattn_backward_workspace_bytes(&p);
-    const Workspace ws(a[13], need, Q.device());
-    const float *lse = (const float *)ptr(LSE);
-    void *st = stream_of(Q);
-    if constexpr (F == kPlain)
-        check("sepattn_backward", lib.sepattn_backward(&p, ptr(Q), ptr(K), ptr(V), ptr(O), lse, ptr(dO), i32(idx), i32(cnt), i32(pre),
-                                                       gp[0], gp[1], gp[2], ws.p, ws.bytes, st));
-    else if constexpr (F == kHeadwise)
-        check("sepattn_backward_headwise",
-              lib.sepattn_backward_headwise(&p, nh.data(), ptr(Q), ptr(K), ptr(V), ptr(O), lse, ptr(dO), i32(idx), i32(cnt), i32(pre),
-                                            gp[0], gp[1], gp[2], ws.p, ws.bytes, st));
-    else
-        check("sepattn_backward_packed",
-              lib.sepattn_backward_packed(&p, ds, de, ptr(Q), ptr(K), ptr(V), ptr(O), lse, ptr(dO), i32(idx), i32(cnt), i32(pre),
-                                          gp[0], gp[1], gp[2], ws.p, ws.bytes, st));
+    for (int k = 0; out.given() && k < 3; ++k) gp[k] = ptr(out[k]);
+    Workspace ws(a[13]);
+    constexpr const char *name = F == kPlain ? "sepattn_backward" : (F == kHeadwise ? "sepattn_backward_headwise" : "sepattn_backward_packed");
+    check(name, unlocked([&] {
+              if (!out.given()) {
+                  g[0] = fresh_like(Q);
+                  g[1] = fresh_like(K);
+                  g[2] = fresh_like(V);
+                  for (int k = 0; k < 3; ++k) gp[k] = ptr(g[k]);
+              }
+              if (!ws.given)
+                  ws.allocate(F == kHeadwise ? lib.sepattn_backward_headwise_workspace_bytes(&p, nh.data())
+                                             : lib.sepattn_backward_workspace_bytes(&p), Q.device());
+              const float *lse = (const float *)ptr(LSE);
+              void *st = stream_of(Q);
+              if constexpr (F == kPlain)
+                  return lib.sepattn_backward(&p, ptr(Q), ptr(K), ptr(V), ptr(O), lse, ptr(dO), i32(idx), i32(cnt), i32(pre), gp[0],
+                                              gp[1], gp[2], ws.p, ws.bytes, st);
+              else if constexpr (F == kHeadwise)
+                  return lib.sepattn_backward_headwise(&p, nh.data(), ptr(Q), ptr(K), ptr(V), ptr(O), lse, ptr(dO), i32(idx), i32(cnt),
+                                                       i32(pre), gp[0], gp[1], gp[2], ws.p, ws.bytes, st);
+              else
+                  return lib.sepattn_backward_packed(&p, ds, de, ptr(Q), ptr(K), ptr(V), ptr(O), lse, ptr(dO), i32(idx), i32(cnt),
+                                                     i32(pre), gp[0], gp[1], gp[2], ws.p, ws.bytes, st);
+          }));
     if (out.given()) return tuple_of(keep(out[0]), keep(out[1]), keep(out[2]));
     return tuple_of(wrap(std::move(g[0])), wrap(std::move(g[1])), wrap(std::move(g[2])));
 }
@@ -445,28 +474,26 @@ PyObject *decode(PyObject *const *a) {
     sepkv_params p = kv_params(Kc, (int)q.size(0), (int)q.size(1), as_int(a[5]), as_int(a[6]), as_int(a[7]), as_float(a[8]));
     p.d = (int)q.size(2);
     const Out<2> out(a[9]);
+    if (NOALLOC && !out.given()) fail(PyExc_TypeError, "out is required");
     at::Tensor o, lse;
-    if (!out.given()) {
-        if (NOALLOC) fail(PyExc_TypeError, "out is required");
-        o = fresh_like(q);
-        lse = empty({p.S, p.Hq}, at::kFloat, q.device());
-    }
-    void *optr = out.given() ? ptr(out[0]) : ptr(o);
-    float *lptr = (float *)(out.given() ? ptr(out[1]) : ptr(lse));  // an item None: no LSE wanted
-    void *st = stream_of(q);
-    if constexpr (NOALLOC) {
-        check("sepattn_decode_noalloc",
-              lib.sepattn_decode_noalloc(&p, ptr(q), ptr(Kc), ptr(Vc), i32(sizes), optr, lptr, st));
-    } else {
-        const Workspace ws(a[10], a[10] == Py_None ? lib.sepattn_decode_workspace_bytes(&p) : 0, q.device());
-        if (rope)
-            check("sepattn_decode_rope",
-                  lib.sepattn_decode_rope(&p, ptr(q), ptr(Kc), ptr(Vc), i32(sizes), (const float *)ptr(*table), (int)table->size(0),
-                                          optr, lptr, ws.p, ws.bytes, st));
-        else
-            check("sepattn_decode",
-                  lib.sepattn_decode(&p, ptr(q), ptr(Kc), ptr(Vc), i32(sizes), optr, lptr, ws.p, ws.bytes, st));
-    }
+    void *optr = nullptr, *lptr = nullptr;
+    if (out.given()) optr = ptr(out[0]), lptr = ptr(out[1]);  // an item None: no LSE wanted
+    Workspace ws(NOALLOC ? Py_None : a[10]);
+    check(NOALLOC ? "sepattn_decode_noalloc" : (rope ? "sepattn_decode_rope" : "sepattn_decode"), unlocked([&] {
+              if (!out.given()) {
+                  o = fresh_like(q);
+                  lse = empty({p.S, p.Hq}, at::kFloat, q.device());
+                  optr = ptr(o), lptr = ptr(lse);
+              }
+              if (!NOALLOC && !ws.given) ws.allocate(lib.sepattn_decode_workspace_bytes(&p), q.device());
+              void *st = stream_of(q);
+              if constexpr (NOALLOC)
+                  return lib.sepattn_decode_noalloc(&p, ptr(q), ptr(Kc), ptr(Vc), i32(sizes), optr, (float *)lptr, st);
+              if (rope)
+                  return lib.sepattn_decode_rope(&p, ptr(q), ptr(Kc), ptr(Vc), i32(sizes), (const float *)ptr(*table),
+                                                 (int)table->size(0), optr, (float *)lptr, ws.p, ws.bytes, st);
+              return lib.sepattn_decode(&p, ptr(q), ptr(Kc), ptr(Vc), i32(sizes), optr, (float *)lptr, ws.p, ws.bytes, st);
+          }));
     if (out.given()) return tuple_of(keep(out[0]), keep(out[1]));
     return tuple_of(wrap(std::move(o)), wrap(std::move(lse)));
 }
@@ -480,8 +507,10 @@ PyObject *append(PyObject *const *a) {
     const int64_t want[3] = {p.S, p.Hkv, p.d};
     require(k.sizes() == c10::IntArrayRef(want, 3) && v.sizes() == k.sizes() && k.scalar_type() == Kc.scalar_type(),
             "k_new, v_new: [S, Hkv, d] in the cache's dtype");
-    check("sepkv_append", lib.sepkv_append(&p, ptr(k), ptr(v), (const uint8_t *)ptr(sep), ptr(Kc), ptr(Vc), (uint8_t *)ptr(flags),
-                                           (int32_t *)ptr(sizes), stream_of(Kc)));
+    check("sepkv_append", unlocked([&] {
+              return lib.sepkv_append(&p, ptr(k), ptr(v), (const uint8_t *)ptr(sep), ptr(Kc), ptr(Vc), (uint8_t *)ptr(flags),
+                                      (int32_t *)ptr(sizes), stream_of(Kc));
+          }));
     return keep(Py_None);
 }
 
@@ -491,8 +520,11 @@ PyObject *evict_window(PyObject *const *a) {
     const at::Tensor &sizes = sizes_arg(a[3]);
     const sepkv_params p = kv_params(Kc, (int)Kc.size(0), as_int(a[4]), as_int(a[5]), as_int(a[6]), as_int(a[7]), 1.0f);
     // the step needs no scratch memory: a workspace is passed on if the caller has one, NULL otherwise
-    check("sepkv_evict_window", lib.sepkv_evict_window(&p, ptr(Kc), ptr(Vc), (const uint8_t *)ptr(flags), (int32_t *)ptr(sizes),
-                                                       ptr(a[8]), a[8] == Py_None ? 0 : (size_t)tensor(a[8]).numel(), stream_of(Kc)));
+    const Workspace ws(a[8]);
+    check("sepkv_evict_window", unlocked([&] {
+              return lib.sepkv_evict_window(&p, ptr(Kc), ptr(Vc), (const uint8_t *)ptr(flags), (int32_t *)ptr(sizes), ws.p, ws.bytes,
+                                            stream_of(Kc));
+          }));
     return keep(Py_None);
 }
 
@@ -504,13 +536,7 @@ PyObject *fill_from_prefill(PyObject *const *a) {
     p.c = as_int(a[9]);
     const Out<4> out(a[11]);
     at::Tensor Kc, Vc, flags, sizes;
-    if (!out.given()) {
-        // freshly allocated outputs are zero where the call leaves them alone
-        Kc = empty({p.S, p.Hkv, p.c, p.d}, K.scalar_type(), K.device()).zero_();
-        Vc = empty({p.S, p.Hkv, p.c, p.d}, K.scalar_type(), K.device()).zero_();
-        flags = empty({p.S, p.c - p.a - p.s}, at::kByte, K.device()).zero_();
-        sizes = empty({p.S, SEPKV_SIZES_COLS}, at::kInt, K.device()).zero_();
-    } else {
+    if (out.given()) {
         Kc = dev(out[0]);
         Vc = dev(out[1]);
         flags = dev(out[2]);
@@ -518,9 +544,17 @@ PyObject *fill_from_prefill(PyObject *const *a) {
         require(sizes.scalar_type() == at::kInt && sizes.dim() == 2 && sizes.size(0) == p.S && sizes.size(1) == SEPKV_SIZES_COLS,
                 "sizes: int32 [S, 6]");
     }
-    check("sepkv_fill_from_prefill",
-          lib.sepkv_fill_from_prefill(&p, L, nw, ptr(K), ptr(V), (const uint8_t *)ptr(sep), i32(idx), (int)idx.size(1), i32(pre),
-                                      ptr(Kc), ptr(Vc), (uint8_t *)ptr(flags), (int32_t *)ptr(sizes), stream_of(K)));
+    check("sepkv_fill_from_prefill", unlocked([&] {
+              if (!out.given()) {  // zero where the call leaves them alone
+                  Kc = empty({p.S, p.Hkv, p.c, p.d}, K.scalar_type(), K.device()).zero_();
+                  Vc = empty({p.S, p.Hkv, p.c, p.d}, K.scalar_type(), K.device()).zero_();
+                  flags = empty({p.S, p.c - p.a - p.s}, at::kByte, K.device()).zero_();
+                  sizes = empty({p.S, SEPKV_SIZES_COLS}, at::kInt, K.device()).zero_();
+              }
+              return lib.sepkv_fill_from_prefill(&p, L, nw, ptr(K), ptr(V), (const uint8_t *)ptr(sep), i32(idx), (int)idx.size(1),
+                                                 i32(pre), ptr(Kc), ptr(Vc), (uint8_t *)ptr(flags), (int32_t *)ptr(sizes),
+                                                 stream_of(K));
+          }));
     if (out.given()) return tuple_of(keep(out[0]), keep(out[1]), keep(out[2]), keep(out[3]));
     return tuple_of(wrap(std::move(Kc)), wrap(std::move(Vc)), wrap(std::move(flags)), wrap(std::move(sizes)));
 }
