@@ -385,7 +385,7 @@ def sepattn_decode_rope(q, Kc, Vc, sizes, rope_table, a: int, s: int, w: int, sc
                         out: Optional[Tuple[torch.Tensor, torch.Tensor]] = None, ws: Optional[torch.Tensor] = None):
     """As sepattn_decode, with q and the cached keys stored without position encoding and turned by
     their positions within the cache inside the kernel; rope_table from sepkv_rope_table."""
-    return _native().decode(q, Kc, Vc, sizes, rope_table, a, s, w, scale, out, ws)
+    return _native().decode_rope(q, Kc, Vc, sizes, rope_table, a, s, w, scale, out, ws)
 
 
 def sepkv_append(k_new, v_new, is_sep_new, Kc, Vc, win_is_sep, sizes, Hq: int, a: int, s: int, w: int) -> None:

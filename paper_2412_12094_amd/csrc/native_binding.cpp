@@ -460,39 +460,42 @@ sepkv_params kv_params(const at::Tensor &Kc, int S, int Hq, int a, int s, int w,
     return p;
 }
 
-// decode(q, Kc, Vc, sizes, rope_table | None, a, s, w, scale, out, ws); NOALLOC: out is required, ws unused
-template <bool NOALLOC>
+enum Decode { kKept, kRope, kNoAlloc };  // positions as the keys hold them, by place in the cache; no allocation
+
+// decode(q, Kc, Vc, sizes, rope_table, a, s, w, scale, out, ws): the table is looked at with kRope only; kNoAlloc: out is
+// required, ws unused
+template <Decode F>
 PyObject *decode(PyObject *const *a) {
     const at::Tensor &q = dev(a[0]), &Kc = dev(a[1]), &Vc = dev(a[2]);
-    const bool rope = a[4] != Py_None;
-    const at::Tensor *table = rope ? &dev(a[4]) : nullptr;
+    const at::Tensor *table = F == kRope ? &dev(a[4]) : nullptr;
     const at::Tensor &sizes = sizes_arg(a[3]);
     if (q.dim() != 3) fail(PyExc_ValueError, "q [S,Hq,d] is expected");
-    if (rope)
+    if (F == kRope)
         require(table->scalar_type() == at::kFloat && table->dim() == 3 && table->size(1) == 2 && table->size(2) * 2 == q.size(2),
                 "rope_table: fp32 [n_pos, 2, d/2]");
     sepkv_params p = kv_params(Kc, (int)q.size(0), (int)q.size(1), as_int(a[5]), as_int(a[6]), as_int(a[7]), as_float(a[8]));
     p.d = (int)q.size(2);
     const Out<2> out(a[9]);
-    if (NOALLOC && !out.given()) fail(PyExc_TypeError, "out is required");
+    if (F == kNoAlloc && !out.given()) fail(PyExc_TypeError, "out is required");
     at::Tensor o, lse;
     void *optr = nullptr, *lptr = nullptr;
     if (out.given()) optr = ptr(out[0]), lptr = ptr(out[1]);  // an item None: no LSE wanted
-    Workspace ws(NOALLOC ? Py_None : a[10]);
-    check(NOALLOC ? "sepattn_decode_noalloc" : (rope ? "sepattn_decode_rope" : "sepattn_decode"), unlocked([&] {
+    Workspace ws(F == kNoAlloc ? Py_None : a[10]);
+    check(F == kNoAlloc ? "sepattn_decode_noalloc" : (F == kRope ? "sepattn_decode_rope" : "sepattn_decode"), unlocked([&] {
               if (!out.given()) {
                   o = fresh_like(q);
                   lse = empty({p.S, p.Hq}, at::kFloat, q.device());
                   optr = ptr(o), lptr = ptr(lse);
               }
-              if (!NOALLOC && !ws.given) ws.allocate(lib.sepattn_decode_workspace_bytes(&p), q.device());
+              if (F != kNoAlloc && !ws.given) ws.allocate(lib.sepattn_decode_workspace_bytes(&p), q.device());
               void *st = stream_of(q);
-              if constexpr (NOALLOC)
+              if constexpr (F == kNoAlloc)
                   return lib.sepattn_decode_noalloc(&p, ptr(q), ptr(Kc), ptr(Vc), i32(sizes), optr, (float *)lptr, st);
-              if (rope)
+              else if constexpr (F == kRope)
                   return lib.sepattn_decode_rope(&p, ptr(q), ptr(Kc), ptr(Vc), i32(sizes), (const float *)ptr(*table),
                                                  (int)table->size(0), optr, (float *)lptr, ws.p, ws.bytes, st);
-              return lib.sepattn_decode(&p, ptr(q), ptr(Kc), ptr(Vc), i32(sizes), optr, (float *)lptr, ws.p, ws.bytes, st);
+              else
+                  return lib.sepattn_decode(&p, ptr(q), ptr(Kc), ptr(Vc), i32(sizes), optr, (float *)lptr, ws.p, ws.bytes, st);
           }));
     if (out.given()) return tuple_of(keep(out[0]), keep(out[1]));
     return tuple_of(wrap(std::move(o)), wrap(std::move(lse)));
@@ -617,8 +620,9 @@ PyMethodDef methods[] = {
     METHOD("backward", backward<kPlain>, 14),
     METHOD("backward_headwise", backward<kHeadwise>, 14),
     METHOD("backward_packed", backward<kPacked>, 16),
-    METHOD("decode", decode<false>, 11),
-    METHOD("decode_noalloc", decode<true>, 11),
+    METHOD("decode", decode<kKept>, 11),
+    METHOD("decode_rope", decode<kRope>, 11),
+    METHOD("decode_noalloc", decode<kNoAlloc>, 11),
     METHOD("append", append, 11),
     METHOD("evict_window", evict_window, 9),
     METHOD("fill_from_prefill", fill_from_prefill, 12),

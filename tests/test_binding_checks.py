@@ -106,3 +106,12 @@ def test_document_bounds_take_a_sequence(bd):
         bd.sepattn_doc_bounds(cu, L, 2, None, (row,))
     with pytest.raises(ValueError, match="GPU"):  # taken apart; refused for what the second item is
         bd.sepattn_doc_bounds(cu, L, 2, None, [row, fake(L, device="cpu"), row])
+
+
+def test_decode_with_positions_needs_the_table(bd):
+    """Without one it would be the decode without positions."""
+    q, Kc, Vc, sizes, *kv = cache_call()
+    with pytest.raises(TypeError):
+        bd.sepattn_decode_rope(q, Kc, Vc, sizes, None, *kv, (q, fake(1, HQ, dtype=torch.float32)))
+    with pytest.raises(AssertionError, match="rope_table"):
+        bd.sepattn_decode_rope(q, Kc, Vc, sizes, fake(32, 2, D, dtype=torch.float32), *kv)
