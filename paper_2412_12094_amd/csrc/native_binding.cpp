@@ -96,22 +96,34 @@ int as_int(PyObject *o) {
     return (int)v;
 }
 float as_float(PyObject *o) {
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) throw Failed{};
+    if (PyFloat_CheckExact(o)) return (float)PyFloat_AS_DOUBLE(o);
+    PyObject *n = PyNumber_Float(o);  // what float(o) gives
+    if (!n) throw Failed{};
+    const double v = PyFloat_AS_DOUBLE(n);
+    Py_DECREF(n);
     return (float)v;
 }
-std::vector<int32_t> int_list(PyObject *o) {
-    PyObject *seq = PySequence_Fast(o, "a sequence of integers is expected");
-    if (!seq) throw Failed{};
-    const Py_ssize_t n = PySequence_Fast_GET_SIZE(seq);
-    std::vector<int32_t> v((size_t)n);
-    try {
-        for (Py_ssize_t k = 0; k < n; ++k) v[(size_t)k] = (int32_t)as_long(PySequence_Fast_GET_ITEM(seq, k));
-    } catch (...) {
-        Py_DECREF(seq);
-        throw;
+bool as_bool(PyObject *o) {
+    const int v = PyObject_IsTrue(o);
+    if (v < 0) throw Failed{};
+    return v != 0;
+}
+// a reference that this call owns
+struct Owned {
+    PyObject *o;
+    explicit Owned(PyObject *x) : o(x) {
+        if (!o) throw Failed{};
     }
-    Py_DECREF(seq);
+    ~Owned() { Py_DECREF(o); }
+    Owned(const Owned &) = delete;
+    Owned &operator=(const Owned &) = delete;
+};
+std::vector<int32_t> int_list(PyObject *o) {
+    if (PyObject_Size(o) < 0) throw Failed{};    // an iterator is refused
+    const Owned items(PySequence_Tuple(o));      // items of its own: int() of one may run code that changes the list
+    const Py_ssize_t n = PyTuple_GET_SIZE(items.o);
+    std::vector<int32_t> v((size_t)n);
+    for (Py_ssize_t k = 0; k < n; ++k) v[(size_t)k] = (int32_t)as_long(PyTuple_GET_ITEM(items.o, k));
     return v;
 }
 // The N tensors of an `out` argument, which may be any iterable; None: the call allocates its own.  The items
@@ -132,14 +144,6 @@ struct Out {
     Out &operator=(const Out &) = delete;
     bool given() const { return items != nullptr; }
     PyObject *operator[](int k) const { return PyTuple_GET_ITEM(items, k); }
-};
-// a reference that this call owns
-struct Owned {
-    PyObject *o;
-    explicit Owned(PyObject *x) : o(x) {}
-    ~Owned() { Py_DECREF(o); }
-    Owned(const Owned &) = delete;
-    Owned &operator=(const Owned &) = delete;
 };
 void check(const char *fn, int rc) {
     if (rc == SEPATTN_OK) return;
@@ -240,7 +244,7 @@ struct IndexOut {
             pre_p = out[N - 1] == Py_None ? nullptr : (int32_t *)ptr(dev(out[N - 1]));
         } else {
             cap = cap_o == Py_None ? L : as_int(cap_o);
-            want_prefix = PyObject_IsTrue(want_prefix_o) == 1;
+            want_prefix = as_bool(want_prefix_o);
             fill = as_int(fill_o);
         }
     }
@@ -306,9 +310,7 @@ PyObject *doc_bounds(PyObject *const *a) {
     const int L = as_int(a[1]);
     const int n_docs = (int)cu.numel() - 1, init = as_int(a[2]);
     // `out` itself is returned, so it has to be a sequence; items beyond the two are left alone
-    PyObject *first = a[4] == Py_None ? keep(Py_None) : PySequence_GetSlice(a[4], 0, 2);
-    if (!first) throw Failed{};
-    const Out<2> out(Owned(first).o);
+    const Out<2> out(Owned(a[4] == Py_None ? keep(Py_None) : PySequence_GetSlice(a[4], 0, 2)).o);
     at::Tensor s, e;
     if (out.given()) {
         s = dev(out[0]);

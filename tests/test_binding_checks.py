@@ -115,3 +115,24 @@ def test_decode_with_positions_needs_the_table(bd):
         bd.sepattn_decode_rope(q, Kc, Vc, sizes, None, *kv, (q, fake(1, HQ, dtype=torch.float32)))
     with pytest.raises(AssertionError, match="rope_table"):
         bd.sepattn_decode_rope(q, Kc, Vc, sizes, fake(32, 2, D, dtype=torch.float32), *kv)
+
+
+def test_flags_and_lists_are_read_as_python_does(bd):
+    tokens, flags = fake(B, L), fake(B, L, dtype=torch.uint8)
+    with pytest.raises(RuntimeError, match="ambiguous"):  # bool() of this raises
+        bd.sepattn_compact_indices(flags, want_prefix=torch.zeros(2))
+    with pytest.raises(TypeError):  # no length
+        bd.sepattn_mark_separators(tokens, (x for x in [1, 2]))
+    ids = [1, 2, 3]
+
+    class Clears:
+        def __int__(self):
+            ids.clear()
+            return 1
+
+    ids[0] = Clears()
+    q, k, _, index = attention()
+    with pytest.raises(AssertionError, match="n_per_head"):  # the three items that the list had
+        bd.sepattn_forward_headwise(q, k, k, *index, 1, ids, 0.1)
+    with pytest.raises(ValueError, match="wrong number"):  # float() takes the text, the outputs are looked at next
+        bd.sepattn_forward(q, k, k, *index, 1, 4, "0.1", ())
