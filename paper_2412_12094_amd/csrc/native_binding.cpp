@@ -16,6 +16,7 @@
 #include <ATen/hip/EmptyTensor.h>
 #include <c10/hip/HIPStream.h>
 #include <dlfcn.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <vector>
@@ -576,8 +577,8 @@ PyObject *entry(PyObject *, PyObject *const *args, Py_ssize_t n) {
         return F(args);
     } catch (const Failed &) {
         return nullptr;
-    } catch (const std::exception &e) {  // torch's own errors (an allocation that fails)
-        PyErr_SetString(PyExc_RuntimeError, e.what());
+    } catch (...) {  // torch's own errors as the Python classes it gives them (OutOfMemoryError, IndexError, ...)
+        torch::translate_exception_to_python(std::current_exception());
         return nullptr;
     }
 }

@@ -136,3 +136,9 @@ def test_flags_and_lists_are_read_as_python_does(bd):
         bd.sepattn_forward_headwise(q, k, k, *index, 1, ids, 0.1)
     with pytest.raises(ValueError, match="wrong number"):  # float() takes the text, the outputs are looked at next
         bd.sepattn_forward(q, k, k, *index, 1, 4, "0.1", ())
+
+
+def test_errors_of_torch_keep_their_class(bd):
+    q, k, _, (idx, cnt, pre) = attention()
+    with pytest.raises(IndexError):  # the list has no second dimension
+        bd.sepattn_forward(q, k, k, fake(L), cnt, pre, 1, 4, 0.1)

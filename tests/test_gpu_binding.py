@@ -92,3 +92,18 @@ def test_outputs_of_any_iterable_are_written(bd, make):
     filler += [torch.full_like(t, 7.0) for t in want_g for _ in range(2)]
     for a, b in zip((*want, *want_g), (*got, *got_g), strict=True):
         assert torch.equal(a, b)
+
+
+def test_a_failed_allocation_is_an_out_of_memory_error(bd):
+    """The class that programs catch to give memory back and try again."""
+    q, k = z(1, 64, 4096, 128, dtype=torch.bfloat16), z(1, 8, 4096, 128, dtype=torch.bfloat16)
+    index = z(1, 4096), z(1), z(1, 4097)
+    torch.cuda.empty_cache()
+    allowed = torch.cuda.memory_reserved() + (1 << 20)  # no room for the outputs (64 MiB)
+    torch.cuda.set_per_process_memory_fraction(allowed / torch.cuda.get_device_properties(0).total_memory)
+    try:
+        with pytest.raises(torch.OutOfMemoryError):
+            bd.sepattn_forward(q, k, k, *index, 4, 64, 0.1)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert bd.sepattn_forward(q, k, k, *index, 4, 64, 0.1)[0].shape == q.shape
