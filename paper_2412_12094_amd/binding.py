@@ -82,11 +82,12 @@ class SepattnError(RuntimeError):
 
 
 _lib = None
+_calls = None  # the extension module, once its calls are bound to _lib
 
 
 def load(path: Optional[str] = None):
     """Load the shared library (once).  Raises if it has not been built."""
-    global _lib
+    global _lib, _calls
     if _lib is not None and path is None:
         return _lib
     path = path or LIB_PATH
@@ -163,22 +164,21 @@ def load(path: Optional[str] = None):
     lib.sepattn_profile_destroy.argtypes = [vp]
     if path == LIB_PATH or _lib is None:
         _lib = lib
+        _calls = None
     return lib
 
 
-_calls = None
-
-
 def _native():
-    """The extension module whose calls go to the library at LIB_PATH (bound once)."""
+    """The extension module, its calls bound to the library that load() gives (once)."""
     global _calls
-    if _calls is None:
-        load()
-        from . import _native as mod
+    calls = _calls
+    if calls is None:
+        lib = load()
+        from . import _native as calls
 
-        mod.bind(LIB_PATH, _raise_status)
-        _calls = mod
-    return _calls
+        calls.bind(lib._name, _raise_status)
+        _calls = calls
+    return calls
 
 
 def status_string(status: int) -> str:

@@ -142,3 +142,24 @@ def test_errors_of_torch_keep_their_class(bd):
     q, k, _, (idx, cnt, pre) = attention()
     with pytest.raises(IndexError):  # the list has no second dimension
         bd.sepattn_forward(q, k, k, fake(L), cnt, pre, 1, 4, 0.1)
+
+
+def test_calls_go_to_the_library_that_was_loaded(bd, monkeypatch, tmp_path):
+    import shutil
+
+    from paper_2412_12094_amd import _native
+
+    other = str(tmp_path / "libsepattn.so")
+    shutil.copy(bd.LIB_PATH, other)
+    bound = []
+    monkeypatch.setattr(_native, "bind", lambda path, raise_error: bound.append(path))
+    monkeypatch.setattr(bd, "_lib", None)
+    monkeypatch.setattr(bd, "_calls", None)
+    bd.load(other)  # the first one loaded is the one in use
+    bd._native()
+    bd.load()
+    bd._native()
+    assert bound == [other]
+    bd.load(bd.LIB_PATH)  # ... until the usual one is asked for
+    bd._native()
+    assert bound == [other, bd.LIB_PATH]
