@@ -30,6 +30,11 @@
  *   - Return value: SEPATTN_OK (0) or a positive sepattn_status.  No call throws or exits.
  *   - Outputs must not alias inputs, except where a call is documented as in-place.
  *   - All results are bit-reproducible run to run (no floating-point atomics).
+ *   - Infinities and NaN in Q, K, V, dO: with SEPATTN_FP32 they reach the results of the rows that see
+ *     their position and no others.  With SEPATTN_BF16 a masked pair is multiplied with weight 0, and
+ *     0 times such a value is NaN: it may also reach rows that share a tile of queries or keys with
+ *     a row that sees it, so masked positions (padding) must hold finite numbers.  The decode calls
+ *     never read a slot without a valid entry.
  */
 #ifndef SEPATTN_H
 #define SEPATTN_H

@@ -16,6 +16,12 @@
 // partial results meet once in LDS), operands go straight from memory to registers, and what can
 // share a launch does: D_i is formed by the dQ kernel, and the far keys' partial sums are added by the
 // last workgroup to finish a list tile instead of by a kernel of their own.
+//
+// A masked pair enters the contractions over streamed rows with weight 0, and 0 times an infinity or a NaN is NaN: a
+// non-finite value in a row would reach every row of the other side that shares a block with it.  As all that such a
+// pair can do to a sum is to make it NaN, a wave looks at its finished sums and, if one is NaN, forms them once more
+// with vector arithmetic over the visible pairs only.  Finite inputs pay for the look: 43.9 -> 44.6 us for the call
+// below; B=1, 32/8 heads, L=4096, d=128, n=256 451 us forward and 1858 backward with it, 452 and 1866 without.
 // B=1, 2 heads per KV head, L=512, d=64, n=64: forward 22 -> 7 us, D_i and dQ 5 + 23 -> 8, dK/dV 168 -> 20, against one
 // wave per row on the vector ALU.
 #include "bwd_common.h"
@@ -124,9 +130,41 @@ __device__ inline void load_columns(float (&f)[D / 16][4], const float *__restri
         for (int cb = 0; cb < D / 16; ++cb) f[cb][i] = base[(long)row[i] * D + 16 * cb + m];
 }
 
+template <int C>
+__device__ inline bool any_nan(const f32x4 (&x)[C]) {
+    bool n = false;
+#pragma unroll
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) n |= x[c][e] != x[c][e];
+    return __ballot(n) != 0ull;
+}
+// acc (column m, rows 16 c + 4 g + e: dimensions) += sum over the 16 streamed rows of weight * row, visible pairs only:
+// what load_columns and the matrix instructions add where every value is finite.  w, vis, row: the lane's four.
+template <int D>
+__device__ inline void add_visible(f32x4 (&acc)[D / 16], const f32x4 &w, const bool (&vis)[4], const float *__restrict__ base,
+                                   const int (&row)[4], int m, int g) {
+#pragma unroll 1
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int src = 16 * s + m, r = __shfl(row[i], src);  // every lane takes part in all three
+            const float f = __shfl(w[i], src);
+            const bool v = __shfl((int)vis[i], src) != 0;
+            asm volatile("" ::: "memory");  // one row at a time: no more registers than the matrix path
+            f32x4 x[D / 16];
+            load_row<D>(x, base + (long)r * D, g);
+            if (!v) continue;
+#pragma unroll
+            for (int c = 0; c < D / 16; ++c)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[c][e] = fmaf(f, x[c][e], acc[c][e]);
+        }
+}
+
 // ---- forward -----------------------------------------------------------------------------------
 template <int D>
-__global__ __launch_bounds__(64 * kWaves) void fwd_fp32_kernel(sepattn_params p, const float *__restrict__ Q,
+__global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 3) void fwd_fp32_kernel(sepattn_params p, const float *__restrict__ Q,
                                                                const float *__restrict__ K, const float *__restrict__ V,
                                                                const int32_t *__restrict__ sep_idx,
                                                                const int32_t *__restrict__ sep_prefix,
@@ -144,42 +182,51 @@ __global__ __launch_bounds__(64 * kWaves) void fwd_fp32_kernel(sepattn_params p,
     const int iq = t.i0 + m;
     f32x4 qf[C], o[C];
     load_row<D>(qf, Q + (t.row0 + min(iq, p.L - 1)) * D, g);
+    float mx, l;
+    auto run = [&](auto VISIBLE_ONLY) __attribute__((always_inline)) {
 #pragma unroll
-    for (int c = 0; c < C; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float mx = -INFINITY, l = 0.f;
-    for (int k0 = wave * kT; k0 < t.st.n_total; k0 += kWaves * kT) {
-        int lo, hi;
-        const int j = tile_key(t, k0 + m, lo, hi);
-        f32x4 kf[C];
-        load_row<D>(kf, Kh + (long)j * D, g);
-        const Keys4 kk = keys_of_lane(j, lo, hi, g, iq);
-        float vf[C][4];
-        load_columns<D>(vf, Vh, kk.j, m);
-        f32x4 s = row_product<D>(kf, qf);
-        float mb = -INFINITY;
+        for (int c = 0; c < C; ++c) o[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        mx = -INFINITY, l = 0.f;
+        for (int k0 = wave * kT; k0 < t.st.n_total; k0 += kWaves * kT) {
+            int lo, hi;
+            const int j = tile_key(t, k0 + m, lo, hi);
+            f32x4 kf[C];
+            load_row<D>(kf, Kh + (long)j * D, g);
+            const Keys4 kk = keys_of_lane(j, lo, hi, g, iq);
+            float vf[C][4];
+            if constexpr (!VISIBLE_ONLY) load_columns<D>(vf, Vh, kk.j, m);
+            f32x4 s = row_product<D>(kf, qf);
+            float mb = -INFINITY;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            s[i] = kk.vis[i] ? s[i] * p.scale : -INFINITY;
-            mb = fmaxf(mb, s[i]);
+            for (int i = 0; i < 4; ++i) {
+                s[i] = kk.vis[i] ? s[i] * p.scale : -INFINITY;
+                mb = fmaxf(mb, s[i]);
+            }
+            const float m_new = fmaxf(mx, group_max(mb));
+            const float ref = m_new == -INFINITY ? 0.f : m_new;  // a row that has seen no key yet
+            const float alpha = expf(mx - ref);
+            float ps = 0.f;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                s[i] = expf(s[i] - ref);
+                ps += s[i];
+            }
+            l = l * alpha + group_sum(ps);
+            mx = m_new;
+#pragma unroll
+            for (int c = 0; c < C; ++c) o[c] *= alpha;
+            if constexpr (VISIBLE_ONLY) {
+                add_visible<D>(o, s, kk.vis, Vh, kk.j, m, g);
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int c = 0; c < C; ++c) o[c] = mfma_f32(vf[c][i], s[i], o[c]);
+            }
         }
-        const float m_new = fmaxf(mx, group_max(mb));
-        const float ref = m_new == -INFINITY ? 0.f : m_new;  // a row that has seen no key yet
-        const float alpha = expf(mx - ref);
-        float ps = 0.f;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            s[i] = expf(s[i] - ref);
-            ps += s[i];
-        }
-        l = l * alpha + group_sum(ps);
-        mx = m_new;
-#pragma unroll
-        for (int c = 0; c < C; ++c) o[c] *= alpha;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int c = 0; c < C; ++c) o[c] = mfma_f32(vf[c][i], s[i], o[c]);
-    }
+    };
+    run(IntC<0>{});
+    if (any_nan(o)) run(IntC<1>{});
 #pragma unroll
     for (int c = 0; c < C; ++c) *reinterpret_cast<f32x4 *>(&os[wave][m][16 * c + 4 * g]) = o[c];
     if (g == 0) ms[wave][m] = mx, ls[wave][m] = l;
@@ -204,7 +251,7 @@ __global__ __launch_bounds__(64 * kWaves) void fwd_fp32_kernel(sepattn_params p,
 
 // ---- dQ, and D_i = <dO_i, O_i> for the dK/dV kernel, whose counters it clears too ---------------------
 template <int D>
-__global__ __launch_bounds__(64 * kWaves) void dq_fp32_kernel(sepattn_params p, const float *__restrict__ Q,
+__global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void dq_fp32_kernel(sepattn_params p, const float *__restrict__ Q,
                                                               const float *__restrict__ K, const float *__restrict__ V,
                                                               const float *__restrict__ O, const float *__restrict__ LSE,
                                                               const float *__restrict__ dO,
@@ -239,26 +286,34 @@ __global__ __launch_bounds__(64 * kWaves) void dq_fp32_kernel(sepattn_params p, 
     }
     const float lse = LSE[row];
     if (wave == 0 && g == 0 && iq < p.L) Dws[row] = Di;
+    auto run = [&](auto VISIBLE_ONLY) __attribute__((always_inline)) {
 #pragma unroll
-    for (int c = 0; c < C; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = wave * kT; k0 < t.st.n_total; k0 += kWaves * kT) {
-        int lo, hi;
-        const int j = tile_key(t, k0 + m, lo, hi);
-        f32x4 kf[C], vf[C];
-        load_row<D>(kf, Kh + (long)j * D, g);
-        load_row<D>(vf, Vh + (long)j * D, g);
-        const Keys4 kk = keys_of_lane(j, lo, hi, g, iq);
-        float kt[C][4];
-        load_columns<D>(kt, Kh, kk.j, m);
-        const f32x4 s = row_product<D>(kf, qf), dp = row_product<D>(vf, gf);
-        f32x4 ds;
+        for (int c = 0; c < C; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int k0 = wave * kT; k0 < t.st.n_total; k0 += kWaves * kT) {
+            int lo, hi;
+            const int j = tile_key(t, k0 + m, lo, hi);
+            f32x4 kf[C], vf[C];
+            load_row<D>(kf, Kh + (long)j * D, g);
+            load_row<D>(vf, Vh + (long)j * D, g);
+            const Keys4 kk = keys_of_lane(j, lo, hi, g, iq);
+            float kt[C][4];
+            if constexpr (!VISIBLE_ONLY) load_columns<D>(kt, Kh, kk.j, m);
+            const f32x4 s = row_product<D>(kf, qf), dp = row_product<D>(vf, gf);
+            f32x4 ds;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) ds[i] = kk.vis[i] ? expf(s[i] * p.scale - lse) * (dp[i] - Di) : 0.f;
+            for (int i = 0; i < 4; ++i) ds[i] = kk.vis[i] ? expf(s[i] * p.scale - lse) * (dp[i] - Di) : 0.f;
+            if constexpr (VISIBLE_ONLY) {
+                add_visible<D>(acc, ds, kk.vis, Kh, kk.j, m, g);
+            } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+                for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int c = 0; c < C; ++c) acc[c] = mfma_f32(kt[c][i], ds[i], acc[c]);
-    }
+                    for (int c = 0; c < C; ++c) acc[c] = mfma_f32(kt[c][i], ds[i], acc[c]);
+            }
+        }
+    };
+    run(IntC<0>{});
+    if (any_nan(acc)) run(IntC<1>{});
 #pragma unroll
     for (int c = 0; c < C; ++c) *reinterpret_cast<f32x4 *>(&xs[wave][m][16 * c + 4 * g]) = acc[c];
     __syncthreads();
@@ -311,47 +366,60 @@ __global__ __launch_bounds__(64 * kWaves) void dkv_fp32_kernel(sepattn_params p,
         const int jr = valid ? j : 0;
         load_row<D>(kf, K + (kvrow0 + jr) * D, g);
         load_row<D>(vf, V + (kvrow0 + jr) * D, g);
+        auto run = [&](auto VISIBLE_ONLY) __attribute__((always_inline)) {
 #pragma unroll
-        for (int c = 0; c < C; ++c) ak[c] = av[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int it = first + wave; it < last; it += kWaves) {
-            const int h = kv * G + it / n_qb, q0 = q_lo + (it % n_qb) * kT;
-            // last query that sees the key: end of the sequence (document), or of head h's window
-            const int hi = valid ? (far ? end : (int)min((long)end, (long)j + p.n - head_delta(hw, h))) - 1 : -1;
-            if (__ballot(hi >= q0) == 0ull) continue;
-            const long hrow = ((long)b * p.Hq + h) * p.L;
-            f32x4 qf[C], gf[C];
-            const long qrow = hrow + min(q0 + m, p.L - 1);
-            load_row<D>(qf, Q + qrow * D, g);
-            load_row<D>(gf, dO + qrow * D, g);
-            int qi[4];
-            float lse[4], Dq[4];
+            for (int c = 0; c < C; ++c) ak[c] = av[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int it = first + wave; it < last; it += kWaves) {
+                const int h = kv * G + it / n_qb, q0 = q_lo + (it % n_qb) * kT;
+                // last query that sees the key: end of the sequence (document), or of head h's window
+                const int hi = valid ? (far ? end : (int)min((long)end, (long)j + p.n - head_delta(hw, h))) - 1 : -1;
+                if (__ballot(hi >= q0) == 0ull) continue;
+                const long hrow = ((long)b * p.Hq + h) * p.L;
+                f32x4 qf[C], gf[C];
+                const long qrow = hrow + min(q0 + m, p.L - 1);
+                load_row<D>(qf, Q + qrow * D, g);
+                load_row<D>(gf, dO + qrow * D, g);
+                int qi[4];
+                float lse[4], Dq[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                qi[i] = min(q0 + 4 * g + i, p.L - 1);
-                lse[i] = LSE[hrow + qi[i]];
-                Dq[i] = Drow[hrow + qi[i]];
+                for (int i = 0; i < 4; ++i) {
+                    qi[i] = min(q0 + 4 * g + i, p.L - 1);
+                    lse[i] = LSE[hrow + qi[i]];
+                    Dq[i] = Drow[hrow + qi[i]];
+                }
+                // requested with the rows: one memory round trip per item
+                float gt[C][4], qt[C][4];
+                if constexpr (!VISIBLE_ONLY) {
+                    load_columns<D>(gt, dO + hrow * D, qi, m);
+                    load_columns<D>(qt, Q + hrow * D, qi, m);
+                }
+                const f32x4 s = row_product<D>(qf, kf), dp = row_product<D>(gf, vf);
+                f32x4 pr, ds;
+                bool vis[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int q = q0 + 4 * g + i;
+                    vis[i] = j <= q && q <= hi;
+                    pr[i] = vis[i] ? expf(s[i] * p.scale - lse[i]) : 0.f;
+                    ds[i] = vis[i] ? pr[i] * (dp[i] - Dq[i]) : 0.f;
+                }
+                if constexpr (VISIBLE_ONLY) {
+                    add_visible<D>(av, pr, vis, dO + hrow * D, qi, m, g);
+                    add_visible<D>(ak, ds, vis, Q + hrow * D, qi, m, g);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int c = 0; c < C; ++c) av[c] = mfma_f32(gt[c][i], pr[i], av[c]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int c = 0; c < C; ++c) ak[c] = mfma_f32(qt[c][i], ds[i], ak[c]);
+                }
             }
-            // requested with the rows: one memory round trip per item
-            float gt[C][4], qt[C][4];
-            load_columns<D>(gt, dO + hrow * D, qi, m);
-            load_columns<D>(qt, Q + hrow * D, qi, m);
-            const f32x4 s = row_product<D>(qf, kf), dp = row_product<D>(gf, vf);
-            f32x4 pr, ds;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int q = q0 + 4 * g + i;
-                pr[i] = j <= q && q <= hi ? expf(s[i] * p.scale - lse[i]) : 0.f;
-                ds[i] = pr[i] * (dp[i] - Dq[i]);
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int c = 0; c < C; ++c) av[c] = mfma_f32(gt[c][i], pr[i], av[c]);
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int c = 0; c < C; ++c) ak[c] = mfma_f32(qt[c][i], ds[i], ak[c]);
-        }
+        };
+        run(IntC<0>{});
+        if (any_nan(av) || any_nan(ak)) run(IntC<1>{});
     };
     // sum over the waves of x (dK or dV of the tile's 16 keys), handed out as out(row, column, four values)
     auto add_waves = [&](const f32x4 (&x)[C], auto out) __attribute__((always_inline)) {
