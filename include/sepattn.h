@@ -32,9 +32,10 @@
  *   - All results are bit-reproducible run to run (no floating-point atomics).
  *   - Infinities and NaN in Q, K, V, dO: with SEPATTN_FP32 they reach the results of the rows that see
  *     their position and no others.  With SEPATTN_BF16 a masked pair is multiplied with weight 0, and
- *     0 times such a value is NaN: it may also reach rows that share a tile of queries or keys with
- *     a row that sees it, so masked positions (padding) must hold finite numbers.  The decode calls
- *     never read a slot without a valid entry.
+ *     0 times such a value is NaN: it may also reach rows that do not see it (those that share a
+ *     tile of queries or keys with one that does; from position 0, which fills up the last tile of
+ *     a row's keys, any), so that padding and other masked positions must hold finite numbers.  The
+ *     decode calls never read a slot without a valid entry.
  */
 #ifndef SEPATTN_H
 #define SEPATTN_H
@@ -60,7 +61,7 @@ typedef enum {
 
 typedef enum {
     SEPATTN_BF16 = 0, /* bfloat16 storage, fp32 softmax and accumulation, MFMA contractions    */
-    SEPATTN_FP32 = 1  /* fp32 storage and arithmetic: slow debug path                          */
+    SEPATTN_FP32 = 1  /* fp32 storage and arithmetic throughout: the path to check a bf16 run against */
 } sepattn_dtype;
 
 #define SEPATTN_MAX_SEP_IDS 64

@@ -314,11 +314,12 @@ int launch_decode_t(const sepkv_params &p, const T *q, const T *Kc, const T *Vc,
 }  // namespace
 
 size_t decode_workspace(const sepkv_params &p) {
-    int nsplit = decode_mfma_applicable(p) ? decode_mfma_nsplit(p) : pick_nsplit(p);
-    if (decode_wide_applicable(p)) {
+    int nsplit;
+    if (decode_wide_applicable(p)) {  // one size for calls with and without positions
         const int a = decode_wide_nsplit(p, false), b = decode_wide_nsplit(p, true);
-        nsplit = nsplit > a ? nsplit : a;
-        nsplit = nsplit > b ? nsplit : b;
+        nsplit = a > b ? a : b;
+    } else {
+        nsplit = decode_mfma_applicable(p) ? decode_mfma_nsplit(p) : pick_nsplit(p);
     }
     return align_up((size_t)p.S * p.Hq * nsplit * (p.d + 2) * sizeof(float), 256);
 }

@@ -206,3 +206,12 @@ def test_ring_layout_helpers_round_trip():
         assert np.array_equal(F2[q, :npast + nl], fl[q, :npast + nl])
     K0, V0, F0, _ = wl.cache_to_ring(Kc, Vc, fl, sizes, np.zeros((S, 2), np.int32), a, s)
     assert np.array_equal(K0, Kc) and np.array_equal(V0, Vc) and np.array_equal(F0, fl)
+
+
+def test_decode_workspace_holds_the_slices_of_the_kernel_that_runs(sp):
+    """300 entries and up to 16 query heads per KV head: one slice, with and without positions; 32 heads run on another
+    kernel, which cuts at 256 entries."""
+    need = lambda **kw: sp.load().sepattn_decode_workspace_bytes(ctypes.byref(kv_params(sp, c=300, **kw)))
+    record = lambda heads: (heads * (128 + 2) * 4 + 255) // 256 * 256
+    assert need(S=2, Hq=8, Hkv=2) == record(2 * 8)
+    assert need(S=2, Hq=64, Hkv=2) == record(2 * 64 * 2)

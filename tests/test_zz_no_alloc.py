@@ -43,7 +43,7 @@ def test_decode_noalloc_equals_decode_on_two_calls_in_a_row(sp):
     lib = bd.load()
     # several slices per cache, so that the partial results do go through the scratch array; the
     # second call is smaller in every dimension of the scratch layout (sequences, heads, slices)
-    shapes = [(2, 32, 1, 128, 4, 500, 64, 900), (1, 8, 1, 64, 2, 100, 16, 300)]
+    shapes = [(2, 32, 1, 128, 4, 500, 64, 2000), (1, 8, 1, 64, 2, 500, 16, 1300)]
     for i, (S, Hq, Hkv, d, a, s, w, c) in enumerate(shapes):
         cfg, q, Kc, Vc, sizes = _case(S, Hq, Hkv, d, a, s, w, c, 500 + i)
         p = bd._kv_params(q, Kc, a, s, w, cfg.scale)
