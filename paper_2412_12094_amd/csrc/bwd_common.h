@@ -33,9 +33,9 @@ __host__ __device__ inline int align_down32(int x) { return x & ~31; }
 
 // The far work of one (batch, KV head): for list tile ft (bk = 32 KW consecutive list entries) the
 // "items" (query tile, query head) from the first query that can see the tile's first key
-// to the end of the sequence.  The items of all list tiles, in this order, are cut into `wpg` slices
-// of equal length, one per workgroup; the part of a slice that lies in one list tile is a "piece" and
-// produces one fp32 partial of that tile's dK / dV rows.  Piece (w, ft) uses partial slot w + ft
+// to the end of the sequence.  The items of all list tiles, in this order, are cut into slices, at
+// most one per workgroup (`wpg` of them; workgroups with fewer band units get longer ones, see dkv_kernel); the
+// part of a slice that lies in one list tile is a "piece" and produces one fp32 partial of that tile's dK / dV rows.  Piece (w, ft) uses partial slot w + ft
 // (along the pieces either w or ft grows, so the slot numbers are distinct).
 struct FarGeom {
     int wpg;     // workgroups per (batch, KV head)

@@ -5,36 +5,35 @@
 // The visible pairs split into band pairs (i-j < n) and far pairs (i-j >= n, j an initial token or a
 // separator, Sec. 3.1).  dkv_kernel runs persistent workgroups, `wpg` per (batch, KV head), each of
 // which works through
-//   its far pieces: far pairs on the COMPACTED list of such keys.  For list tile ft (128 consecutive
-//              list entries, gathered K/V rows) the work is the sequence of items (query tile of 64
+//   its far pieces: far pairs on the COMPACTED list of such keys.  For list tile ft (128 or 64 consecutive
+//              list entries, gathered K/V rows) the work is the sequence of items (query tile of 64 or 32
 //              rows, query head) from the first query that sees the tile's first key to the end of
 //              the sequence; the items of all list tiles, concatenated, are cut into slices, up to
 //              one per workgroup, and the part of a slice inside one list tile is a piece.  A piece
 //              writes an fp32 partial dK/dV of the tile's rows to the workspace (slot w + ft).
-//   its band units: 128 consecutive keys against the queries j <= i < j+n (units w, w+wpg, ...).
+//   its band units: 128 or 64 consecutive keys against the queries j <= i < j+n (units w, w+wpg, ...).
 //              Keys that are not on the far list are finished here (rounded once to bf16); for the
 //              others the band unit writes one more fp32 partial.
 // dkv_combine_kernel then adds, in fixed order, the partials of every far-list key and rounds once to
 // bf16.  One workgroup owns each partial row: no atomics, results are bit-reproducible.  Every
 // workgroup gets (up to one) the same number of band units, and those with one less get more far work, so
 // the compute units finish together.
-// A workgroup is 8 waves = 4 key blocks of 32 keys x 2 roles.  The two waves of a key block split
+// A workgroup is KW = 4 or 2 (dkv_key_blocks) key blocks of 32 keys x 2 roles = 8 or 4 waves.  The two waves of a key block split
 // the four contractions so that each keeps only one operand matrix and one accumulator resident:
 //   P-wave :  S = Q K^T   -> P = exp2(.)      -> dV^T += dO^T P     (holds K rows, dV^T)
 //   dS-wave:  dP = dO V^T -> dS = P (dP - D)  -> dK^T += Q^T dS     (holds V rows, dK^T)
 // P travels from the first to the second through a small LDS buffer (same lane, same register:
 // both are 32x32 accumulator layouts), once per block of 32 queries, fenced by the block's
 // workgroup barrier (P is exchanged in bf16, the form it has in the second contraction anyway).  Query
-// tiles (64 rows of Q and dO, plus LSE*log2e and -D) stream through a ring of four LDS buffers filled
+// tiles (64 or 32 rows of Q and dO, plus LSE*log2e and -D) stream through a ring of four LDS buffers filled
 // by direct global->LDS loads issued as soon as a buffer is free; with the ring the block barriers
 // are the only barriers.  The tiles are stored unpadded with XOR-permuted 16-byte
 // chunks so that both the row-major reads (first contraction) and the transposed reads (second
-// contraction) are free of bank conflicts.  The four query heads of a GQA group are just four times
-// as many query tiles.
+// contraction) are free of bank conflicts.  The G query heads of a KV head are just G times as many
+// query tiles.
 #include "bwd_common.h"
 #include "mfma_common.h"
 #include "work_share.h"
-
 
 namespace sepattn {
 

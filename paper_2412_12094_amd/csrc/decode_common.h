@@ -1,5 +1,5 @@
-// Pieces shared by the two decode kernels (the vector-ALU one for fp32 / any group size and the
-// bf16 matrix-core one): the map from logical cache entries to slots, and the partial record merge.
+// Pieces shared by the decode kernels (decode_wide.hip: bf16, up to 16 query heads per KV head; decode_mfma.hip: bf16,
+// 17 to 32; decode.hip: fp32 and wider groups on the vector ALU): the map from logical cache entries to slots, and the partial record merge.
 #pragma once
 
 #include "common.h"

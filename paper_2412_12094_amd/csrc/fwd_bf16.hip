@@ -27,7 +27,6 @@
 #include "key_stream.h"
 #include "work_share.h"
 
-
 namespace sepattn {
 
 namespace {
@@ -36,7 +35,7 @@ constexpr float kRescaleThreshold = 8.f;  // log2 units
 
 // DOCS: packed documents (see make_stream_docs); doc_start / doc_end [B, L] give, per position, the
 // first position of its document and one past its last.  Requires p.a == 0.
-// NW: waves per workgroup (8 or 4); 2 waves per SIMD either way.
+// NW: waves per workgroup (4, 7 or 8, see query_shape); about two waves per SIMD in all shapes, three at d = 64 with four.
 template <int D, int GP, bool DOCS, int NW>
 __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_kernel(
     sepattn_params p, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,

@@ -41,7 +41,8 @@ __device__ inline TileGroup xcd_tile_group(int id, int n_tiles, int n_groups) {
 //   Four waves, so that two (d = 64: three) independent workgroups share a compute unit: one's segment change, row
 //     stores and barriers overlap the others' matrix work, and the split of a group is finer.
 //   Seven heads per KV head: seven waves, one head each (one head per workgroup streamed 456 band keys for a
-//     window of 200; seven stream 232: B=3, L=3077, d=128 forward 113 -> 72 us).
+//     window of 200; seven stream 232: B=3, L=3077, d=128 forward 113 -> 72 us).  Three, five and six heads per KV
+//     head run with one or two per tile; shapes with all of them in one tile have not been built or measured.
 //   Eight waves at d = 128 with four heads where the work is large (eight rounds of four-wave workgroups per compute
 //     unit and more): half the tile loads per matrix instruction (L = 64K: 3.67 ms against 4.0; level at L = 4096).
 struct QueryShape {

@@ -1,6 +1,6 @@
 // Device helpers shared by the bf16 MFMA kernels (gfx950 / CDNA4, wave64).
 //
-// All contractions use v_mfma_f32_32x32x16_bf16.  Operand layouts (lane l of the wave):
+// The contractions of the training kernels and of decode_mfma.hip use v_mfma_f32_32x32x16_bf16.  Operand layouts (lane l of the wave):
 //   A (32 x 16): row l%32, k = 8*(l/32) .. +7        B (16 x 32): column l%32, k = 8*(l/32) .. +7
 //   C (32 x 32): column l%32, register i holds row 8*(i/4) + 4*(l/32) + i%4
 // The kernels always put the "streamed" matrix (staged in LDS) in A and the wave's own 32 rows

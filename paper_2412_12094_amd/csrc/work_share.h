@@ -4,8 +4,9 @@
 // see everything next to heads with a window of 128, an even deal leaves all but the longest groups' workgroups
 // idle, and running every group with the call's largest window made each as long as the longest (32/8 heads,
 // d = 128, L = 4096, every fourth KV head full, the others 128: forward 180 -> 102 us, dQ 228 -> 170, dK/dV 581 -> 170,
-// what is left in the first two being the last query tile, whose stream no deal shortens).  Workgroups are dealt in proportion to the work instead, the longest groups first in dispatch order, so that two of them share a
-// compute unit only when there are more long workgroups than compute units.
+// what is left in the first two being the last query tile, whose stream no deal shortens).  Workgroups are dealt so that
+// the largest work of any one of them is least (share_out), the longest groups first in dispatch order, so that two
+// of them share a compute unit only when there are more long workgroups than compute units.
 #pragma once
 
 #include "common.h"
