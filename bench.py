@@ -39,17 +39,16 @@ PEAK_HBM_GBS = 8000.0      # MI355X HBM3E
 # The figures and the commands are in profiles/; None = not measured for the current kernels.
 CALIB_BYTES = 256 << 20
 MEASURED_TRAFFIC_BYTES = {
-    "forward": 190.5e6,      # cfg3: read 119.0 MB + written 71.5 MB   (algorithmic: 168.8 MB; the staged output rows leave as
-                             # 64-byte pieces, two store instructions per 128-byte line)
-    "bwd_dq": 346.7e6,       # cfg3: read 271.5 MB + written 75.1 MB
-    "bwd_dkv": 542.5e6,      # cfg3: read 468.1 MB (Q, dO tiles re-read by every list tile and band unit) + written 74.3 MB
-    "bwd_combine": 46.4e6,   # cfg3: read 43.6 MB + written 2.8 MB
-    "cfg2_step": 613.9e6,    # mark+compact 0.2 + forward 108.8 + dQ 167.9 + dK/dV 289.9 + combine 47.1 MB (algorithmic: 303.6 MB)
-    "cfg4_forward": 1895.8e6,  # read 1347.3 MB + written 548.5 MB    (algorithmic: 1351 MB)
+    "forward": 176.0e6,      # cfg3: read 107.8 MB + written 68.2 MB   (algorithmic: 168.8 MB)
+    "bwd_dq": 348.4e6,       # cfg3: read 272.8 MB + written 75.6 MB
+    "bwd_dkv": 542.7e6,      # cfg3: read 468.3 MB (Q, dO tiles re-read by every list tile and band unit) + written 74.3 MB
+    "bwd_combine": 46.6e6,   # cfg3: read 43.9 MB + written 2.8 MB
+    "cfg2_step": 610.8e6,    # mark+compact 0.2 + forward 108.1 + dQ 165.1 + dK/dV 290.3 + combine 47.1 MB (algorithmic: 303.6 MB)
+    "cfg4_forward": 1780.2e6,  # read 1235.0 MB + written 545.3 MB    (algorithmic: 1351 MB)
     "evict_move": 42.1e6,    # cfg5: read 21.3 MB + written 20.8 MB by the counters; the kernel loads and stores 10.4 MB each
                              # (a build that counts its stores: 40 704 rows of 256 B), i.e. the counters read twice the bytes of
                              # these scattered 256-byte rows
-    "cache_fill": 482.2e6,   # 32 prompts of 8K into cfg5 caches: read 241.5 MB + written 240.8 MB (algorithmic: 481.5 MB)
+    "cache_fill": 482.3e6,   # 32 prompts of 8K into cfg5 caches: read 241.5 MB + written 240.8 MB (algorithmic: 481.5 MB)
 }
 
 
