@@ -17,7 +17,7 @@ NATIVE = os.path.join(HERE, "_native.so")  # imported as paper_2412_12094_amd._n
 SOURCES = ["api.hip", "mark_compact.hip", "attn_fp32.hip", "fwd_bf16.hip", "bwd_bf16.hip", "bwd_dkv_bf16.hip", "decode.hip", "decode_mfma.hip", "decode_wide.hip", "decode_noalloc.hip",
            "evict.hip", "cache_fill.hip", "rope_table.hip", "cache_append.hip", "doc_bounds.hip"]
 # packed fp32 VALU instructions are switched off (some of their forms have miscomputed on
-# the test machines); the host pass does not know the feature and says so, which is harmless
+# this hardware); the host pass does not know the feature and says so, which is harmless
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
 
