@@ -59,6 +59,16 @@ def test_bf16_workgroup_shapes(B, Hq, Hkv, L, d, a, n, p):
     run(B, Hq, Hkv, L, d, a, n, p, "bf16")
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,L,a,n,p", [
+    (4, 128, 32, 513, 4, 33, 0.1),                   # one position in the last tile, two workgroups per group of heads
+    (16, 128, 32, 128, 1, 200, 0.1),                 # the fewest tiles for which eight waves are taken (2048 of four); more groups than compute units
+    (16, 128, 32, 96, 1, 20, 0.1),                   # fewer: four waves
+    (4, 128, 32, 513, 4, [33, 513, 1, 100] * 32, 0.1),  # a window per head
+])
+def test_bf16_eight_wave_forward_and_dq(B, Hq, Hkv, L, a, n, p):
+    run(B, Hq, Hkv, L, 128, a, n, p, "bf16")
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,L,d,a,p,nh", [
     (1, 8, 2, 1100, 128, 4, 0.08, [1100] * 4 + [48] * 4),      # a KV head that sees everything next to a short window
     (2, 12, 4, 700, 64, 3, 0.1, [33] * 6 + [700] * 3 + [1] * 3),  # three heads per KV head, two rows of the batch
@@ -75,7 +85,7 @@ def test_bf16_head_groups_by_work(B, Hq, Hkv, L, d, a, p, nh):
     (1, 8, 1, 512, 128, 4, 512, 0.1),    # the shortest sequence whose keys are all listed
     (1, 8, 1, 511, 128, 4, 511, 0.1),    # one key fewer: band units
     (2, 8, 2, 1101, 64, 0, 4000, 0.0),   # a last list tile of 13 keys; no separators; a window beyond the sequence
-    (1, 4, 1, 8200, 128, 4, 8200, 0.05),  # eight-wave workgroups
+    (1, 4, 1, 8200, 128, 4, 8200, 0.05),  # eight-wave dK/dV workgroups
 ])
 def test_bf16_windows_of_the_whole_sequence(B, Hq, Hkv, L, d, a, n, p):
     run(B, Hq, Hkv, L, d, a, n, p, "bf16")

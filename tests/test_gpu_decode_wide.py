@@ -16,7 +16,8 @@ CASES = [
     (2, 16, 1, 128, 0, 8, 4, 24),     # one block; 16 heads per KV head; fewer table rows than a block has entries
     (2, 8, 4, 64, 4, 100, 60, 256),   # exactly one block per wave
     (2, 8, 8, 64, 4, 100, 60, 257),   # one wave has a second block
-    (2, 14, 2, 128, 4, 64, 256, 800), # 7 heads per KV head; several slices with ROPE
+    (2, 14, 2, 128, 4, 64, 256, 800), # 7 heads per KV head; several slices
+    (1, 8, 2, 128, 4, 200, 100, 530), # several slices with ROPE, one without
     (1, 4, 1, 128, 4, 300, 256, 1100),# several slices with and without ROPE
     (3, 6, 2, 64, 3, 700, 300, 1999), # the same at d = 64
     (33, 16, 8, 128, 2, 20, 10, 75),  # 264 pairs: four waves, two workgroups per compute unit
