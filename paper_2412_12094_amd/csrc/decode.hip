@@ -315,13 +315,15 @@ int launch_decode_t(const sepkv_params &p, const T *q, const T *Kc, const T *Vc,
 
 size_t decode_workspace(const sepkv_params &p) {
     int nsplit;
+    size_t arrival = 0;
     if (decode_wide_applicable(p)) {  // one size for calls with and without positions
-        const int a = decode_wide_nsplit(p, false), b = decode_wide_nsplit(p, true);
+        const int a = decode_wide_shape(p, false).nsplit, b = decode_wide_shape(p, true).nsplit;
         nsplit = a > b ? a : b;
+        if (nsplit > 1) arrival = decode_wide_arrival_bytes(p);
     } else {
         nsplit = decode_mfma_applicable(p) ? decode_mfma_nsplit(p) : pick_nsplit(p);
     }
-    return align_up((size_t)p.S * p.Hq * nsplit * (p.d + 2) * sizeof(float), 256);
+    return arrival + align_up((size_t)p.S * p.Hq * nsplit * (p.d + 2) * sizeof(float), 256);
 }
 
 template <typename T>
@@ -341,10 +343,12 @@ int launch_decode(const sepkv_params &p, const void *q, const void *Kc, const vo
     if (decode_mfma_applicable(p)) {
         using T = uint16_t;
         const bool wide = decode_wide_applicable(p);
-        const int nsplit = wide ? decode_wide_nsplit(p, rope != nullptr) : decode_mfma_nsplit(p);
-        int rc = (wide ? launch_decode_wide : launch_decode_mfma)(p, nsplit, (const T *)q, (const T *)Kc, (const T *)Vc, sizes,
-                                                                  rope, n_pos, (T *)out, lse, part, st);
-        if (rc != SEPATTN_OK || nsplit == 1) return rc;
+        DecodeWideShape shape = {1, 0};
+        if (wide) shape = decode_wide_shape(p, rope != nullptr);
+        const int nsplit = wide ? shape.nsplit : decode_mfma_nsplit(p);
+        const int rc = wide ? launch_decode_wide(p, shape, (const T *)q, (const T *)Kc, (const T *)Vc, sizes, rope, n_pos, (T *)out, lse, part, st)
+                            : launch_decode_mfma(p, nsplit, (const T *)q, (const T *)Kc, (const T *)Vc, sizes, rope, n_pos, (T *)out, lse, part, st);
+        if (rc != SEPATTN_OK || nsplit == 1 || wide) return rc;
         ProfScope prof(SEPATTN_K_DECODE_MERGE, st);
         if (p.d == 64)
             hipLaunchKernelGGL((decode_merge_kernel<T, 64>), dim3(p.S * p.Hq), dim3(64), 0, st, nsplit, part, (T *)out, lse);

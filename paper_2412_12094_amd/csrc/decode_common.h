@@ -56,8 +56,13 @@ int launch_decode_mfma(const sepkv_params &p, int nsplit, const uint16_t *q, con
                        hipStream_t st);
 
 bool decode_wide_applicable(const sepkv_params &p);
-int decode_wide_nsplit(const sepkv_params &p, bool rope);
-int launch_decode_wide(const sepkv_params &p, int nsplit, const uint16_t *q, const uint16_t *Kc, const uint16_t *Vc,
+struct DecodeWideShape {
+    int nsplit, nw;  // slices per (sequence, KV head), waves per workgroup
+};
+DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope);
+// decode_wide_kernel adds its slices itself; the workspace begins with one word per (sequence, KV head) for that
+inline size_t decode_wide_arrival_bytes(const sepkv_params &p) { return align_up((size_t)p.S * p.Hkv * sizeof(uint64_t), 256); }
+int launch_decode_wide(const sepkv_params &p, const DecodeWideShape &shape, const uint16_t *q, const uint16_t *Kc, const uint16_t *Vc,
                        const int32_t *sizes, const float *rope, int n_pos, uint16_t *out, float *lse, float *part,
                        hipStream_t st);
 

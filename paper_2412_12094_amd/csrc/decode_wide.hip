@@ -2,9 +2,9 @@
 // query heads per KV head: the decode kernel of every such call (more heads: decode_mfma.hip).
 //
 // A short cache, or one of few, is bound by the chain  sizes -> slots -> rows -> scores -> softmax -> output
-// -> merge and by the instructions a wave issues along it; many long ones by the rate of the memory.  A
+// -> sum over the slices and by the instructions a wave issues along it; many long ones by the rate of the memory.  A
 // workgroup owns one (sequence, KV head) and one of `nsplit` slices of its valid entries:
-//   - eight waves (four where more workgroups than compute units wait, see launch_decode_wide), one block of
+//   - eight waves or four (see decode_wide_shape), one block of
 //     32 entries each at a time.  A wave has one LDS stage of K and V rows, filled with direct global->LDS
 //     loads; the K half is refilled as soon as the scores' operands sit in registers, the V half one step
 //     later, so 128 KB per compute unit are in flight nearly all the time and no workgroup barrier is needed;
@@ -18,9 +18,12 @@
 //     lanes alike) minus that of r (rows 0 .. 31 of the table, fetched once per workgroup into LDS, kept in
 //     registers); dimension i pairs with i + D/2 in another fragment of the same lane.  (Reading each row's own
 //     table row from memory is 64 separate 16-byte pieces per instruction: 3.5 us per round of eight blocks.)
+//   - the workgroup of a cache that finishes last adds the slices (arrives_last): about 2 us of device-scope round trips,
+//     as long as a merge launch takes on the device, but a launch less on the host, which costs 3.5 us there
+//     (append + decode of a streaming generation step, 4 sequences of 800 entries: 12.3 us -> 9.9).
 // Measured (MI355X, 32/8 heads, d = 128, one call of a stream of calls, us without / with ROPE; before: four
 // waves, 32-column operands, two stages per wave, the angle carried from block to block in registers):
-//   1 sequence, 64 entries 5.1 / 6.7 -> 4.1 / 4.9; 800 entries 8.8 / 12.0 -> 7.4 / 8.8
+//   1 sequence, 64 entries 5.1 / 6.7 -> 3.6 / 4.8; 800 entries 8.8 / 12.0 -> 6.1 / 7.3
 //   32 sequences, 300 entries 9.5 / 13.5 -> 6.9 / 8.4; 3332 entries (436.7 MB) 67.7 / 73.1 -> 64.6 / 65.8 (6.8 TB/s)
 //
 // Operand layouts of 16x16x32 (lane l, g = l / 16): A row l%16, k = 8g..8g+7; B column l%16, same k; C
@@ -64,11 +67,38 @@ __device__ inline float groups_sum(float x) {
 __device__ inline f32x4 lds_read_f4(uint32_t addr) { return *(const f32x4 __attribute__((address_space(3))) *)addr; }
 #pragma clang diagnostic pop
 
+// The slices' records pass between workgroups that may run on different XCDs, whose L2 caches are not coherent with
+// each other: they are stored and loaded as device-scope atomics of 8 bytes, which go past the L2.
+__device__ inline void publish(float *dst, float2 v) {
+    __hip_atomic_store(reinterpret_cast<uint64_t *>(dst), __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline float2 fetch_published(const float *src) {
+    return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const uint64_t *>(src), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
+// How many slices of a (sequence, KV head) have published their records: the low 8 bits of a word in the caller's
+// workspace, which nobody clears.  The word counts only while its upper 56 bits hold a fixed pattern.  Every slice looks
+// at it before its own work and, if it is anything else, replaces what it saw by "none"; a slice that sees the pattern,
+// or loses that exchange, finds the word in use by this call.  The last slice sets the count back to none, so that the
+// words of a workspace that has been used before need no exchange.  Nobody waits for another workgroup.
+constexpr uint64_t kArrivalPattern = 0xD1B54A32D192ED03ull & ~0xFFull;
+__device__ inline void arrival_ready(uint64_t *word) {
+    uint64_t seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((seen & ~0xFFull) != kArrivalPattern)
+        __hip_atomic_compare_exchange_strong(word, &seen, kArrivalPattern, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline bool arrives_last(uint64_t *word, int nsplit) {
+    const uint64_t before = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((int)(before & 0xFF) != nsplit - 1) return false;
+    __hip_atomic_store(word, kArrivalPattern, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return true;
+}
+
 template <int D, bool ROPE, int NW>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
     sepkv_params p, int G, const uint16_t *__restrict__ q, const uint16_t *__restrict__ Kc,
     const uint16_t *__restrict__ Vc, const int32_t *__restrict__ sizes, const float *__restrict__ rope, int n_pos,
-    float *__restrict__ part, uint16_t *__restrict__ out, float *__restrict__ lse) {
+    uint64_t *__restrict__ arrived, float *__restrict__ part, uint16_t *__restrict__ out, float *__restrict__ lse) {
     constexpr int CH = D / 8;           // 16-byte chunks per row
     constexpr int RPL = 64 / CH;        // rows covered by one wave-wide 1 KB load
     constexpr int NLD = kDwRows / RPL;  // wave-wide loads per tensor per stage
@@ -90,6 +120,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
     const uint16_t *Kh = Kc + ((long)sq * p.Hkv + kv) * (long)p.c * D;
     const uint16_t *Vh = Vc + ((long)sq * p.Hkv + kv) * (long)p.c * D;
 
+    arrived += (long)sq * p.Hkv + kv;
+    if (nsplit > 1 && tid == 64 * (NW - 1)) arrival_ready(arrived);
     // queries: B operand, column = head of the group (zero beyond G)
     u32x4 qraw[KSTEPS];
     {
@@ -327,14 +359,54 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
             if (lse && c2 == 0) lse[sh] = (lsum > 0.f) ? (M + __builtin_amdgcn_logf(lsum)) * kLn2_f : -INFINITY;
         } else {
             float *dst = part + (sh * nsplit + split) * PF;
-            *reinterpret_cast<float2 *>(dst + 2 + 2 * c2) = float2{o0, o1};
-            if (c2 == 0) *reinterpret_cast<float2 *>(dst) = float2{M, lsum};
+            publish(dst + 2 + 2 * c2, float2{o0, o1});
+            if (c2 == 0) publish(dst, float2{M, lsum});
         }
     }
-}
+    if (nsplit == 1) return;
 
-// workgroups of eight waves that a compute unit holds (by LDS)
-int decode_wide_per_cu(const sepkv_params &p) { return p.d == 64 ? 2 : 1; }
+    // ---- the workgroup that finishes last adds the slices' records, in slice order, whichever it is
+    __shared__ int last_s;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's part of the record is where every XCD sees it
+    __syncthreads();
+    if (tid == 0) last_s = arrives_last(arrived, nsplit);
+    __syncthreads();
+    if (!last_s) return;
+    for (int item = tid; item < G * (D / 2); item += 64 * NW) {
+        const int h = item / (D / 2), c2 = item % (D / 2);
+        const long sh = (long)sq * p.Hq + h0 + h;
+        const float *r = part + sh * nsplit * PF;
+        // eight records at a time are requested together; slices past the last repeat it with weight 0
+        constexpr int NB = 8;
+        float M = -INFINITY, lsum = 0.f, o0 = 0.f, o1 = 0.f;
+        for (int s0 = 0; s0 < nsplit; s0 += NB) {
+            float2 ml[NB], o[NB];
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const float *rec = r + min(s0 + k, nsplit - 1) * PF;
+                ml[k] = fetch_published(rec);
+                o[k] = fetch_published(rec + 2 + 2 * c2);
+                if (s0 + k >= nsplit) ml[k].x = -INFINITY;
+            }
+            float Mn = M;
+#pragma unroll
+            for (int k = 0; k < NB; ++k) Mn = fmaxf(Mn, ml[k].x);
+            const float keep = (M == -INFINITY) ? 0.f : exp2f(M - Mn);
+            lsum *= keep, o0 *= keep, o1 *= keep;
+            M = Mn;
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                const float wgt = (ml[k].x == -INFINITY) ? 0.f : exp2f(ml[k].x - M);
+                lsum = fmaf(wgt, ml[k].y, lsum);
+                o0 = fmaf(wgt, o[k].x, o0);
+                o1 = fmaf(wgt, o[k].y, o1);
+            }
+        }
+        const uint32_t b0 = decode_f32_to_bf16(lsum > 0.f ? o0 / lsum : 0.f), b1 = decode_f32_to_bf16(lsum > 0.f ? o1 / lsum : 0.f);
+        *reinterpret_cast<uint32_t *>(out + sh * D + 2 * c2) = b0 | (b1 << 16);
+        if (lse && c2 == 0) lse[sh] = (lsum > 0.f) ? (M + log2f(lsum)) * kLn2_f : -INFINITY;
+    }
+}
 
 }  // namespace
 
@@ -342,42 +414,56 @@ bool decode_wide_applicable(const sepkv_params &p) {
     return p.dtype == SEPATTN_BF16 && (p.d == 64 || p.d == 128) && p.Hq / p.Hkv <= 16;
 }
 
-// Slices per cache.  One slice needs no second launch; a wave then works through ceil(blocks / 8) blocks one
-// after the other.  More slices pay when the blocks a workgroup is spared take longer than the merge
-// launch (about 3 us): measured 0.22 us per block of a lone workgroup at d = 128, 0.38 us with ROPE, half
-// of that at d = 64, hence the thresholds below.  Never more slices than give every wave one block, nor
-// more workgroups than the compute units hold at once.
-int decode_wide_nsplit(const sepkv_params &p, bool rope) {
-    const int nb = (p.c + kDwRows - 1) / kDwRows;
-    const long fit = (long)compute_units() * decode_wide_per_cu(p) / ((long)p.S * p.Hkv);
-    int ns = (nb + 7) / 8;
-    if (ns > fit) ns = fit < 1 ? 1 : (int)fit;
-    if (ns > 64) ns = 64;
-    const int spared = nb - (nb + ns - 1) / ns;
-    const int pays = (rope ? 8 : 14) * (p.d == 64 ? 2 : 1);
-    return spared > pays ? ns : 1;
+// Slices per cache and waves per workgroup.  Times below: one call of a stream of calls in us, 32/8 heads, d = 128
+// unless noted, without / with ROPE.
+//   Slices are at most one workgroup per compute unit, four blocks each (one per wave; d = 64 with more than 32 blocks:
+//     eight): the rows that one compute unit has to fetch are what a short call waits for.  1 sequence of 800 entries
+//     (25 blocks): seven slices of four waves 6.1 / 7.3, four of eight with a merge launch 7.0 / 8.4; 4 sequences
+//     6.7 / 7.8 against 8.2 / 9.3.  Never two workgroups on some compute units: d = 64, 32 sequences of 2300 entries,
+//     one slice 22.5 / 23.0, two 24.4 / 25.1.
+//   Eight slices, whose records are fetched in one round trip (1 sequence of 1400 entries: 6.7 / 8.6, eleven 7.7 / 8.8);
+//     sixteen where a slice would be longer than ten blocks (1 sequence of 3332 entries 8.9 / 10.0, eight 9.9 / 11.7).
+//   Slices pay when the blocks that a workgroup is spared take longer than adding the records (about 2 us).  A block
+//     costs a lone workgroup 0.2 us, with ROPE 0.3 us, half of that at d = 64: 13 blocks in one slice 5.8 / 8.4, in four
+//     5.8 / 6.9; 16 blocks 6.0 / 8.6 and 6.0 / 7.0.
+//   Four waves per slice at d = 128 (two slices for 16 sequences of 2300 entries 24.6 / 25.6, of eight waves 24.8 / 25.6)
+//     and where each has one block; eight at d = 64 (8 sequences of 2300 entries 8.2 / 8.8 against 8.7 / 9.5).
+//   One slice: eight waves (more bytes in flight); four for caches of up to eight blocks (1 sequence of 128 entries
+//     3.6 / 4.8 against 4.2 / 5.1), and where more workgroups wait than the compute units hold at once: half the LDS, so
+//     that two (d = 64: four) share a compute unit and one's start and merge overlap another's stream (64 sequences x
+//     8 heads of 100 entries 8.9 -> 5.4, of 1000 entries 40.7 -> 39.2).
+DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope) {
+    const long pairs = (long)p.S * p.Hkv, fit = compute_units() / pairs;
+    const int nb = (p.c + kDwRows - 1) / kDwRows, d64 = p.d == 64 ? 2 : 1;
+    const int want = d64 == 2 && nb > 32 ? 8 : 4, most = nb > 80 ? 16 : 8;  // blocks per slice, slices
+    int ns = (nb + want - 1) / want;
+    if (ns > most) ns = most;
+    if (ns > fit) ns = (int)fit;
+    if (ns > 1) {
+        const int per = (nb + ns - 1) / ns;
+        if (nb - per >= (rope ? 9 : 11) * d64) return {ns, d64 == 1 || per <= 4 ? 4 : 8};
+    }
+    return {1, nb <= 8 || pairs > (long)compute_units() * d64 ? 4 : 8};
 }
 
-int launch_decode_wide(const sepkv_params &p, int nsplit, const uint16_t *q, const uint16_t *Kc, const uint16_t *Vc,
+int launch_decode_wide(const sepkv_params &p, const DecodeWideShape &shape, const uint16_t *q, const uint16_t *Kc, const uint16_t *Vc,
                        const int32_t *sizes, const float *rope, int n_pos, uint16_t *out, float *lse, float *part,
                        hipStream_t st) {
+    uint64_t *arrived = reinterpret_cast<uint64_t *>(part);  // one word per (sequence, KV head), then the records
+    part += decode_wide_arrival_bytes(p) / sizeof(float);
     if (p.Hkv > 65535 || p.S > 65535) return SEPATTN_ERR_SHAPE;
     const int G = p.Hq / p.Hkv;
     ProfScope prof(SEPATTN_K_DECODE_SPLIT, st);
     auto go = [&](auto D_, auto NW_) {
         constexpr int D = decltype(D_)::value, NW = decltype(NW_)::value;
-        const dim3 grid(nsplit, p.Hkv, p.S), block(64 * NW);
+        const dim3 grid(shape.nsplit, p.Hkv, p.S), block(64 * NW);
         if (rope)
-            hipLaunchKernelGGL((decode_wide_kernel<D, true, NW>), grid, block, 0, st, p, G, q, Kc, Vc, sizes, rope, n_pos, part, out, lse);
+            hipLaunchKernelGGL((decode_wide_kernel<D, true, NW>), grid, block, 0, st, p, G, q, Kc, Vc, sizes, rope, n_pos, arrived, part, out, lse);
         else
-            hipLaunchKernelGGL((decode_wide_kernel<D, false, NW>), grid, block, 0, st, p, G, q, Kc, Vc, sizes, rope, n_pos, part, out, lse);
+            hipLaunchKernelGGL((decode_wide_kernel<D, false, NW>), grid, block, 0, st, p, G, q, Kc, Vc, sizes, rope, n_pos, arrived, part, out, lse);
     };
-    // eight waves, unless there are more workgroups than the compute units hold at once: then four waves and
-    // half the LDS, two (d = 64: four) workgroups per compute unit, so that one's start and merge overlap
-    // another's stream (64 sequences x 8 heads of 100 entries 8.9 -> 5.4 us, of 1000 entries 40.7 -> 39.2)
-    const bool many = (long)p.S * p.Hkv * nsplit > (long)compute_units() * decode_wide_per_cu(p);
-    if (p.d == 64) many ? go(IntC<64>{}, IntC<4>{}) : go(IntC<64>{}, IntC<8>{});
-    else many ? go(IntC<128>{}, IntC<4>{}) : go(IntC<128>{}, IntC<8>{});
+    if (p.d == 64) shape.nw == 4 ? go(IntC<64>{}, IntC<4>{}) : go(IntC<64>{}, IntC<8>{});
+    else shape.nw == 4 ? go(IntC<128>{}, IntC<4>{}) : go(IntC<128>{}, IntC<8>{});
     return launch_status();
 }
 

@@ -58,3 +58,45 @@ def test_decode_dispatch_edges(S, Hq, Hkv, d, a, s, w, c, rope):
     torch.cuda.synchronize()
     assert np.abs(out.float().cpu().numpy() - ref).max() <= 2e-2
     assert np.abs(lse.cpu().numpy() - lref).max() <= (1e-2 if rope else 2e-3)
+
+
+# slices and waves per workgroup: the edges of decode_wide_shape's rules on a chip of 256 compute units
+SHAPE_CASES = [
+    (1, 8, 2, 128, 4, 100, 60, 256),    # eight blocks: one slice of four waves
+    (1, 8, 2, 128, 4, 100, 60, 385),    # 13 blocks: one slice of eight waves without ROPE, four of four with
+    (4, 32, 8, 128, 4, 64, 256, 800),   # 25 blocks in seven slices, the last of one block
+    (2, 8, 1, 128, 0, 1100, 256, 2600), # 82 blocks in sixteen slices
+    (9, 56, 8, 128, 4, 500, 100, 1600), # 72 pairs of seven heads: three slices
+    (16, 128, 8, 128, 4, 200, 100, 800),# 128 pairs of sixteen heads: two slices
+    (2, 12, 12, 64, 3, 64, 256, 800),   # d = 64: one slice without ROPE, seven of four waves with
+    (4, 8, 8, 64, 4, 900, 256, 2300),   # nine blocks per slice: eight waves
+    (33, 8, 8, 64, 4, 500, 100, 1100),  # 264 pairs at d = 64: one slice of eight waves
+]
+
+
+@pytest.mark.parametrize("rope", [False, True])
+@pytest.mark.parametrize("S,Hq,Hkv,d,a,s,w,c", SHAPE_CASES)
+def test_decode_slices_and_waves(S, Hq, Hkv, d, a, s, w, c, rope):
+    test_decode_dispatch_edges(S, Hq, Hkv, d, a, s, w, c, rope)
+
+
+def test_decode_workspace_needs_no_clearing():
+    """The slices are counted in the workspace, whatever it holds: the same bits from any of it, call after call and
+    with calls of other shapes, which lay the workspace out differently, in between."""
+    import paper_2412_12094_amd as sp
+
+    def call(S, c, seed, ws):
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        q = torch.randn((S, 32, 128), device="cuda", generator=g).bfloat16()
+        K, V = (torch.randn((S, 8, c, 128), device="cuda", generator=g).bfloat16() for _ in range(2))
+        sizes = torch.tensor([[4, 64, c - 4 - 64 - 256, 256, 3, 5]] * S, dtype=torch.int32, device="cuda")
+        return [t.clone() for t in sp.sepattn_decode(q, K, V, sizes, 4, 64, 256, 0.09, ws=ws)]
+
+    shapes = [(4, 800, 1), (1, 2600, 2), (9, 700, 3)]
+    fresh = [call(*s, torch.zeros(4 << 20, dtype=torch.uint8, device="cuda")) for s in shapes]
+    g = torch.Generator(device="cuda").manual_seed(9)
+    noise = torch.randint(0, 256, (4 << 20,), dtype=torch.uint8, device="cuda", generator=g)
+    for ws in (noise, torch.full_like(noise, 255), torch.full_like(noise, 0x7F)):
+        for k in (0, 0, 1, 2, 0, 2, 1):
+            for got, ref in zip(call(*shapes[k], ws), fresh[k]):
+                assert torch.equal(got, ref)
