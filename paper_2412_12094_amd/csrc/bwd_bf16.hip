@@ -144,8 +144,8 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
             g.i0 = (n_pos_tiles - 1 - rank) * TP;
             if constexpr (DOCS) {
                 // the clamps keep inconsistent bounds (caller error) from faulting
-                const int ds = min(max(dstart[g.i0], 0), g.i0);
-                g.de = min(max(dend[g.i0], g.i0 + 1), p.L);
+                const int ds = min(max(load_uniform(dstart, g.i0), 0), g.i0);
+                g.de = min(max(load_uniform(dend, g.i0), g.i0 + 1), p.L);
                 g.st = make_stream_docs(p, prefix, g.i0, TP, ds);
             } else {
                 g.de = kIntMax;

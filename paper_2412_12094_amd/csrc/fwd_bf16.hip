@@ -133,8 +133,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
             g.i0 = (n_pos_tiles - 1 - rank) * TP;
             if constexpr (DOCS) {
                 // the clamps keep inconsistent bounds (caller error) from faulting
-                const int ds = min(max(dstart[g.i0], 0), g.i0);
-                g.de = min(max(dend[g.i0], g.i0 + 1), p.L);
+                const int ds = min(max(load_uniform(dstart, g.i0), 0), g.i0);
+                g.de = min(max(load_uniform(dend, g.i0), g.i0 + 1), p.L);
                 g.st = make_stream_docs(p, prefix, g.i0, TP, ds);
             } else {
                 g.de = kIntMax;
@@ -320,40 +320,48 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     // one half of a tile step.  HB: which block of the tile (0 or 1).  DO_QK: S(2X+HB) of tile X into
     // s_new; DO_PV: O^T += V_{X-1}[32 HB ..]^T p_old^T; DO_SM: softmax of the block whose scores are
     // s_old (tile sm_tile, block sm_kb) into p_new; DO_LD: V rows of tile X+AH-1 and K rows of tile X+AH are requested.
+    // NEXT: the last LA slots request the first operands of the tile's second block, which the following half then finds on
+    // their way (READY) instead of waiting for them.
     int gbase = 0;  // global number of tile 0 of the segment being multiplied
-    auto half_step = [&](int X, auto HB_, auto DO_QK_, auto DO_PV_, auto DO_SM_, auto DO_LD_, f32x16 &s_new,
+    bf16x8 frag[LA];
+    auto half_step = [&](int X, auto HB_, auto DO_QK_, auto DO_PV_, auto DO_SM_, auto DO_LD_, auto READY_, auto NEXT_, f32x16 &s_new,
                          const bf16x8 (&p_old)[2], f32x16 &s_old, bf16x8 (&p_new)[2], int sm_tile,
                          int sm_kb) __attribute__((always_inline)) {
         constexpr int HB = decltype(HB_)::value;
         constexpr bool DO_QK = decltype(DO_QK_)::value != 0, DO_PV = decltype(DO_PV_)::value != 0;
         constexpr bool DO_SM = decltype(DO_SM_)::value != 0, DO_LD = decltype(DO_LD_)::value != 0;
+        constexpr bool READY = decltype(READY_)::value != 0, NEXT = decltype(NEXT_)::value != 0;
         constexpr int N1 = DO_QK ? NQK : 0, N2 = DO_PV ? NPV : 0, NS = N1 + N2;
         constexpr int E = (16 + NS - 1) / NS;              // elements of the softmax per matrix instruction
-        constexpr int M0 = N1 + 2, EM = (16 + NS - M0 - 1) / (NS - M0 > 0 ? NS - M0 : 1);  // of the maximum, from slot M0 on
+        constexpr int M0 = N1 + 2, NM = NS > M0 ? NS - M0 : 1;  // pairs of the maximum, from slot M0 on
         const uint32_t vst = vs_base + ((unsigned)(gbase + X + VST - 1) % VST) * (TILE * 2) + HB * 32 * D * 2;
         const uint32_t kst = ks_base + ((unsigned)(gbase + X) % KST) * (TILE * 2) + HB * 32 * D * 2;
-        bf16x8 frag[LA];
+        constexpr int OFF = READY ? (NQK + NPV) % LA : 0;  // where the half before put the first operand
         auto request = [&](auto S) __attribute__((always_inline)) {
             constexpr int s = decltype(S)::value;
             if constexpr (s < N1) {
-                frag[s % LA] = lds_read_b128_at((kst + koff0) ^ (32u * s));
+                frag[(s + OFF) % LA] = lds_read_b128_at((kst + koff0) ^ (32u * s));
             } else if constexpr (s < NS) {
                 constexpr int q_ = s - N1, stp = q_ / DB, db = q_ % DB;
-                frag[s % LA] = lds_read_tr_at(vst + voff[db] + stp * 16 * D * 2, 4 * D * 2);
+                frag[(s + OFF) % LA] = lds_read_tr_at(vst + voff[db] + stp * 16 * D * 2, 4 * D * 2);
+            } else if constexpr (NEXT) {
+                static_assert(HB == 0 && DO_QK && LA <= NQK, "the next half begins with K rows 32 .. 63 of the same tile");
+                constexpr int n = s - NS;
+                frag[s % LA] = lds_read_b128_at((kst + 32 * D * 2 + koff0) ^ (32u * n));
             }
         };
         auto multiply = [&](auto S) __attribute__((always_inline)) {
             constexpr int s = decltype(S)::value;
             if constexpr (s < N1) {
                 const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                s_new = mfma_bf16(frag[s % LA], qreg[s], s == 0 ? zero : s_new);
+                s_new = mfma_bf16(frag[(s + OFF) % LA], qreg[s], s == 0 ? zero : s_new);
             } else {
                 constexpr int q_ = s - N1, stp = q_ / DB, db = q_ % DB;
-                oacc[db] = mfma_bf16(frag[s % LA], p_old[stp], oacc[db]);
+                oacc[db] = mfma_bf16(frag[(s + OFF) % LA], p_old[stp], oacc[db]);
             }
         };
         if constexpr (DO_LD) read_offsets(gbase + X + AH);
-        static_for<(LA < NS ? LA : NS)>([&](auto S) { request(S); });
+        if constexpr (!READY) static_for<(LA < NS ? LA : NS)>([&](auto S) { request(S); });
         if constexpr (DO_PV) apply_rescale();
         if constexpr (DO_SM) softmax_head(s_old, sm_tile, gbase + sm_tile, sm_kb);
         float psum = 0.f, mx = -INFINITY;
@@ -374,7 +382,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
             }
             if constexpr (DO_QK && s_ >= M0) {
 #pragma unroll
-                for (int i = EM * (s_ - M0); i < EM * (s_ - M0 + 1) && i < 16; ++i) mx = fmaxf(mx, s_new[i]);
+                for (int i = 8 * (s_ - M0) / NM * 2; i < 8 * (s_ - M0 + 1) / NM * 2; i += 2) mx = fmaxf(fmaxf(mx, s_new[i]), s_new[i + 1]);
+                asm volatile("" : "+v"(mx));  // here, not in a chain after the run
             }
             if constexpr (DO_LD && s_ >= 1) {
                 constexpr int LPS = (2 * LOADS + NS - 2) / (NS - 1), n0 = (s_ - 1) * LPS;  // row loads per slot
@@ -401,6 +410,16 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
         }
         __builtin_amdgcn_sched_barrier(0);
     };
+
+    Seg cseg = open_segment(0), cnext = open_segment(1);
+    auto load_queries = [&](int seg_i0) __attribute__((always_inline)) {
+        const int row = min(seg_i0 + 32 * (wave / GP) + qi, p.L - 1);
+        const uint16_t *qrow = Q + (((long)b * p.Hq + head) * p.L + row) * D;
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks)
+            qreg[ks] = as_bf16x8(*reinterpret_cast<const u32x4 *>(qrow + ks * 16 + 8 * hh));
+    };
+    load_queries(cseg.i0);  // in flight during the start-up
 
     // ---- start-up, once per workgroup: positions of tiles 0 .. 3, then the first rows (the entries of tiles 4
     // and 5 are on their way)
@@ -446,15 +465,6 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     const IntC<0> no;
     const IntC<0> first_block;
     const IntC<1> second_block;
-    Seg cseg = open_segment(0), cnext = open_segment(1);
-    auto load_queries = [&](int seg_i0) __attribute__((always_inline)) {
-        const int row = min(seg_i0 + 32 * (wave / GP) + qi, p.L - 1);
-        const uint16_t *qrow = Q + (((long)b * p.Hq + head) * p.L + row) * D;
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks)
-            qreg[ks] = as_bf16x8(*reinterpret_cast<const u32x4 *>(qrow + ks * 16 + 8 * hh));
-    };
-    load_queries(cseg.i0);
     for (int round = 0; cseg.i0 >= 0; ++round) {
     i0 = cseg.i0;
     pw = i0 + 32 * (wave / GP);  // first position of this wave
@@ -476,20 +486,20 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     // step 0: no output update yet, no softmax in the first half.  Its barrier was that of the start-up or
     // of the previous segment's last step.
     look_ahead(gbase);
-    half_step(0, first_block, yes, no, no, yes, s_a, p_a, s_b, p_b, 0, 0);
-    half_step(0, second_block, yes, no, yes, no, s_b, p_b, s_a, p_a, 0, 0);
+    half_step(0, first_block, yes, no, no, yes, no, no, s_a, p_a, s_b, p_b, 0, 0);
+    half_step(0, second_block, yes, no, yes, no, no, no, s_b, p_b, s_a, p_a, 0, 0);
     for (int X = 1; X < n_tiles; ++X) {
         if ((gbase + X) % AH == 0) wg_barrier();
         look_ahead(gbase + X);
-        half_step(X, first_block, yes, yes, yes, yes, s_a, p_a, s_b, p_b, X - 1, 1);
-        half_step(X, second_block, yes, yes, yes, no, s_b, p_b, s_a, p_a, X, 0);
+        half_step(X, first_block, yes, yes, yes, yes, no, yes, s_a, p_a, s_b, p_b, X - 1, 1);
+        half_step(X, second_block, yes, yes, yes, no, yes, no, s_b, p_b, s_a, p_a, X, 0);
     }
     // last step: output updates of the last tile, softmax of its second block; the queries of the
     // next segment are fetched meanwhile (the registers are free: no score block in this step)
     if ((gbase + n_tiles) % AH == 0) wg_barrier();
     if (cnext.i0 >= 0) load_queries(cnext.i0);
-    half_step(n_tiles, first_block, no, yes, yes, no, s_a, p_a, s_b, p_b, n_tiles - 1, 1);
-    half_step(n_tiles, second_block, no, yes, no, no, s_b, p_b, s_a, p_a, n_tiles, 0);
+    half_step(n_tiles, first_block, no, yes, yes, no, no, no, s_a, p_a, s_b, p_b, n_tiles - 1, 1);
+    half_step(n_tiles, second_block, no, yes, no, no, no, no, s_b, p_b, s_a, p_a, n_tiles, 0);
     gbase += n_tiles;
 
     // epilogue: normalise, store O (bf16) and LSE (natural log)

@@ -60,13 +60,20 @@ struct Stream {
     int n_init, n_dense, n_total, sep_lo, bs;
 };
 
+// Element i (the same in every lane) of an array that no running kernel writes, through the scalar cache.  As an ordinary
+// load it would be a vector load here (the statements that write LDS behind the compiler's back keep it from
+// proving that nothing has changed), whose result is waited for behind every row load and row store in flight.
+__device__ inline int load_uniform(const int32_t *__restrict__ a, int i) {
+    return ((const __attribute__((address_space(4))) int32_t *)(uintptr_t)a)[__builtin_amdgcn_readfirstlane(i)];
+}
+
 __device__ inline Stream make_stream(const sepattn_params &p, const int32_t *__restrict__ prefix, int i0,
                                      int tile_positions) {
     Stream st;
     st.bs = max(0, i0 - p.n + 1);
     st.n_init = min(p.a, st.bs);
-    st.sep_lo = prefix[st.n_init];
-    st.n_dense = st.n_init + (prefix[st.bs] - st.sep_lo);
+    st.sep_lo = load_uniform(prefix, st.n_init);
+    st.n_dense = st.n_init + (load_uniform(prefix, st.bs) - st.sep_lo);
     st.n_total = st.n_dense + (min(p.L, i0 + tile_positions) - st.bs);
     return st;
 }
@@ -83,8 +90,8 @@ __device__ inline Stream make_stream_docs(const sepattn_params &p, const int32_t
     Stream st;
     st.bs = max(ds, i0 - p.n + 1);
     st.n_init = 0;
-    st.sep_lo = prefix[ds];
-    st.n_dense = prefix[st.bs] - st.sep_lo;
+    st.sep_lo = load_uniform(prefix, ds);
+    st.n_dense = load_uniform(prefix, st.bs) - st.sep_lo;
     st.n_total = st.n_dense + (min(p.L, i0 + tile_positions) - st.bs);
     return st;
 }
