@@ -32,6 +32,7 @@ namespace sepattn {
 namespace {
 
 constexpr float kRescaleThreshold = 8.f;  // log2 units
+constexpr float kMaxTerm = 256.f;         // 2^kRescaleThreshold
 
 // DOCS: packed documents (see make_stream_docs); doc_start / doc_end [B, L] give, per position, the
 // first position of its document and one past its last.  Requires p.a == 0.
@@ -113,6 +114,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     float neg_m = 0.f;                     // -m_run, 0 as long as no key has been seen
     float alpha_pending = 1.f;             // rescale of oacc decided by a softmax, applied before the next output update
     bool rescale = false;                  // alpha_pending != 1 in some lane (wave-uniform)
+    bool no_max = true;                    // some lane has seen no key yet (wave-uniform)
 
     // ---- segments of this workgroup, as the loads see them.  The tiles of all segments form ONE stream
     // of loads that runs ahead of the multiplications also across segment borders, so that only the
@@ -265,15 +267,27 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     constexpr int LA = D == 128 ? 6 : 4;
     constexpr int NQK = KSTEPS, NPV = 2 * DB;  // matrix instructions per half
 
-    // largest score of a block for each of the wave's queries (log2 domain), from the scores at hand
-    float m_cand = 0.f;
+    // largest score of a block for each of the wave's queries (log2 domain)
     auto block_max = [&](const f32x16 &s) __attribute__((always_inline)) {
         float m = fmaxf(fmaxf(s[0], s[1]), s[2]);
 #pragma unroll
         for (int i = 3; i < 15; i += 2) m = fmaxf(fmaxf(m, s[i]), s[i + 1]);
-        return fmaxf(m, s[15]);
+        return pair_max(fmaxf(m, s[15]) * sl2);
     };
-    // softmax of a block, the part that branches: mask, running maximum
+    // Raises the running maximum to that of a block where it has grown.  This happens where a query has no maximum yet
+    // (before the block's exponentials), and afterwards only where the exponentials turn out too large (their sum
+    // over a lane says so): the maximum of every block need not be known then.
+    auto raise_max = [&](const f32x16 &s) __attribute__((always_inline)) {
+        const float m = block_max(s);
+        const bool grow = m > m_run + kRescaleThreshold;
+        const float alpha = grow ? __builtin_amdgcn_exp2f(m_run - m) : 1.f;
+        alpha_pending = rescale ? alpha_pending * alpha : alpha;
+        m_run = grow ? m : m_run;
+        neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
+        l_run *= alpha;
+        rescale = true;
+    };
+    // softmax of a block, the part that branches: mask, first maximum
     auto softmax_head = [&](f32x16 &s, int tile, int gtile, int kb) __attribute__((always_inline)) {
         if (!block_is_full(fullb, tile * kBN + kb * 32)) {
             const int vs_ = (unsigned)gtile % MKS;
@@ -292,15 +306,10 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
                     s[8 * half + k] = vis ? s[8 * half + k] : -INFINITY;
                 }
             }
-            m_cand = pair_max(block_max(s) * sl2);
         }
-        const bool grow = m_cand > m_run + kRescaleThreshold;
-        if (__builtin_amdgcn_ballot_w64(grow) != 0ull) {
-            alpha_pending = grow ? __builtin_amdgcn_exp2f(m_run - m_cand) : 1.f;
-            m_run = grow ? m_cand : m_run;
-            neg_m = (m_run == -INFINITY) ? 0.f : -m_run;
-            l_run *= alpha_pending;
-            rescale = true;
+        if (no_max) {
+            raise_max(s);
+            no_max = __builtin_amdgcn_ballot_w64(m_run == -INFINITY) != 0ull;
         }
     };
     auto apply_rescale = [&]() __attribute__((always_inline)) {
@@ -333,21 +342,22 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
         constexpr bool READY = decltype(READY_)::value != 0, NEXT = decltype(NEXT_)::value != 0;
         constexpr int N1 = DO_QK ? NQK : 0, N2 = DO_PV ? NPV : 0, NS = N1 + N2;
         constexpr int E = (16 + NS - 1) / NS;              // elements of the softmax per matrix instruction
-        constexpr int M0 = N1 + 2, NM = NS > M0 ? NS - M0 : 1;  // pairs of the maximum, from slot M0 on
-        const uint32_t vst = vs_base + ((unsigned)(gbase + X + VST - 1) % VST) * (TILE * 2) + HB * 32 * D * 2;
-        const uint32_t kst = ks_base + ((unsigned)(gbase + X) % KST) * (TILE * 2) + HB * 32 * D * 2;
+        // (which half is added after the XOR, so that it becomes the instruction's offset and both halves share the addresses)
+        const uint32_t vst = vs_base + ((unsigned)(gbase + X + VST - 1) % VST) * (TILE * 2);
+        const uint32_t kst = ks_base + ((unsigned)(gbase + X) % KST) * (TILE * 2) + koff0;
+        constexpr uint32_t HO = HB * 32 * D * 2;
         constexpr int OFF = READY ? (NQK + NPV) % LA : 0;  // where the half before put the first operand
         auto request = [&](auto S) __attribute__((always_inline)) {
             constexpr int s = decltype(S)::value;
             if constexpr (s < N1) {
-                frag[(s + OFF) % LA] = lds_read_b128_at((kst + koff0) ^ (32u * s));
+                frag[(s + OFF) % LA] = lds_read_b128_at((kst ^ (32u * s)) + HO);
             } else if constexpr (s < NS) {
                 constexpr int q_ = s - N1, stp = q_ / DB, db = q_ % DB;
-                frag[(s + OFF) % LA] = lds_read_tr_at(vst + voff[db] + stp * 16 * D * 2, 4 * D * 2);
+                frag[(s + OFF) % LA] = lds_read_tr_at(vst + voff[db] + (HO + stp * 16 * D * 2), 4 * D * 2);
             } else if constexpr (NEXT) {
                 static_assert(HB == 0 && DO_QK && LA <= NQK, "the next half begins with K rows 32 .. 63 of the same tile");
                 constexpr int n = s - NS;
-                frag[s % LA] = lds_read_b128_at((kst + 32 * D * 2 + koff0) ^ (32u * n));
+                frag[s % LA] = lds_read_b128_at((kst ^ (32u * n)) + 32 * D * 2);
             }
         };
         auto multiply = [&](auto S) __attribute__((always_inline)) {
@@ -364,7 +374,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
         if constexpr (!READY) static_for<(LA < NS ? LA : NS)>([&](auto S) { request(S); });
         if constexpr (DO_PV) apply_rescale();
         if constexpr (DO_SM) softmax_head(s_old, sm_tile, gbase + sm_tile, sm_kb);
-        float psum = 0.f, mx = -INFINITY;
+        float psum = 0.f;
+        f32x16 pe;  // exponentials; the scores stay, in case they turn out too large
         __builtin_amdgcn_sched_barrier(0);
         static_for<NS>([&](auto S) {
             constexpr int s_ = decltype(S)::value;
@@ -374,16 +385,11 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
                 // the sum takes an element one slot later, when the transcendental unit has delivered
                 constexpr int e0 = E * s_;
 #pragma unroll
-                for (int i = e0; i < e0 + E && i < 16; ++i) s_old[i] = __builtin_amdgcn_exp2f(fmaf(s_old[i], sl2, neg_m));
+                for (int i = e0; i < e0 + E && i < 16; ++i) pe[i] = __builtin_amdgcn_exp2f(fmaf(s_old[i], sl2, neg_m));
 #pragma unroll
                 for (int i = e0 - E; i < e0; ++i)
-                    if (i >= 0) psum += s_old[i];
-                if constexpr (e0 - E < 8 && e0 >= 8) p_new[0] = pack_bf16x8(s_old, 0);
-            }
-            if constexpr (DO_QK && s_ >= M0) {
-#pragma unroll
-                for (int i = 8 * (s_ - M0) / NM * 2; i < 8 * (s_ - M0 + 1) / NM * 2; i += 2) mx = fmaxf(fmaxf(mx, s_new[i]), s_new[i + 1]);
-                asm volatile("" : "+v"(mx));  // here, not in a chain after the run
+                    if (i >= 0) psum += pe[i];
+                if constexpr (e0 - E < 8 && e0 >= 8) p_new[0] = pack_bf16x8(pe, 0);
             }
             if constexpr (DO_LD && s_ >= 1) {
                 constexpr int LPS = (2 * LOADS + NS - 2) / (NS - 1), n0 = (s_ - 1) * LPS;  // row loads per slot
@@ -397,16 +403,22 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
         });
         if constexpr (DO_SM) {
 #pragma unroll
-            for (int i = 16 - E; i < 16; ++i) psum += s_old[i];
-            p_new[1] = pack_bf16x8(s_old, 8);
+            for (int i = 16 - E; i < 16; ++i) psum += pe[i];
+            p_new[1] = pack_bf16x8(pe, 8);
+            if (__builtin_amdgcn_ballot_w64(psum > 16.f * kMaxTerm) != 0ull) {
+                raise_max(s_old);
+                psum = 0.f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    pe[i] = __builtin_amdgcn_exp2f(fmaf(s_old[i], sl2, neg_m));
+                    psum += pe[i];
+                }
+                p_new[0] = pack_bf16x8(pe, 0);
+                p_new[1] = pack_bf16x8(pe, 8);
+            }
             l_run += psum;
             pin(p_new);
             asm volatile("" : "+v"(l_run));
-        }
-        if constexpr (DO_QK) {
-            if constexpr (!DO_PV) mx = block_max(s_new);
-            m_cand = pair_max(mx * sl2);
-            asm volatile("" : "+v"(m_cand));
         }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -482,6 +494,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     l_run = 0.f;
     neg_m = 0.f;
     rescale = false;
+    no_max = true;
 
     // step 0: no output update yet, no softmax in the first half.  Its barrier was that of the start-up or
     // of the previous segment's last step.
