@@ -477,6 +477,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     const IntC<0> no;
     const IntC<0> first_block;
     const IntC<1> second_block;
+    const IntC<(D == 128 || NW > 4) ? 1 : 0> ahead;  // not with the 168 registers of three workgroups per compute unit
     for (int round = 0; cseg.i0 >= 0; ++round) {
     i0 = cseg.i0;
     pw = i0 + 32 * (wave / GP);  // first position of this wave
@@ -504,8 +505,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     for (int X = 1; X < n_tiles; ++X) {
         if ((gbase + X) % AH == 0) wg_barrier();
         look_ahead(gbase + X);
-        half_step(X, first_block, yes, yes, yes, yes, no, yes, s_a, p_a, s_b, p_b, X - 1, 1);
-        half_step(X, second_block, yes, yes, yes, no, yes, no, s_b, p_b, s_a, p_a, X, 0);
+        half_step(X, first_block, yes, yes, yes, yes, no, ahead, s_a, p_a, s_b, p_b, X - 1, 1);
+        half_step(X, second_block, yes, yes, yes, no, ahead, no, s_b, p_b, s_a, p_a, X, 0);
     }
     // last step: output updates of the last tile, softmax of its second block; the queries of the
     // next segment are fetched meanwhile (the registers are free: no score block in this step)
