@@ -76,8 +76,7 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     constexpr int KST = 2 * AH, MKS = 8;
     constexpr int TILE = kBN * D;
 
-    __shared__ __attribute__((aligned(1024))) uint16_t Ks[KST][TILE];
-    __shared__ __attribute__((aligned(1024))) uint16_t Vs[KST][TILE];
+    __shared__ __attribute__((aligned(1024))) uint16_t KVs[KST][2][TILE];  // K and V rows of a tile, a constant apart
     __shared__ __attribute__((aligned(256))) int lo_s[MKS][kBN];
     __shared__ __attribute__((aligned(256))) int hi_s[MKS][kBN];
     __shared__ __attribute__((aligned(256))) uint32_t off_s[4][kBN];           // byte offset of a tile's rows in K and V
@@ -210,7 +209,7 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     const char *Kb = reinterpret_cast<const char *>(K + ((long)b * p.Hkv + kv) * (long)p.L * D);
     const char *Vb = reinterpret_cast<const char *>(V + ((long)b * p.Hkv + kv) * (long)p.L * D);
     const int my_pc = lane % CH, my_sub = lane / CH;
-    const uint32_t ks_base = lds_addr(&Ks[0][0]), vs_base = lds_addr(&Vs[0][0]);
+    const uint32_t kv_base = lds_addr(&KVs[0][0][0]);
     uint32_t gofs[LOADS];  // byte offset of this lane's piece of the rows it helps to fill next
     auto read_offsets = [&](int g) __attribute__((always_inline)) {
 #pragma unroll
@@ -221,9 +220,9 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     };
     auto issue_row = [&](int g, auto N) __attribute__((always_inline)) {  // the K (even n) or V (odd n) rows of load n / 2
         constexpr int n = decltype(N)::value, u = n / 2;
-        const uint32_t at = (unsigned)(g % KST) * (TILE * 2) + (uint32_t)min(LOADS * wave + u, NLD - 1) * 1024u;
-        if constexpr (n % 2 == 0) dma_to_lds_16(Kb, gofs[u], ks_base + at);
-        else dma_to_lds_16(Vb, gofs[u], vs_base + at);
+        const uint32_t at = kv_base + (unsigned)(g % KST) * (TILE * 4) + (uint32_t)min(LOADS * wave + u, NLD - 1) * 1024u;
+        if constexpr (n % 2 == 0) dma_to_lds_16(Kb, gofs[u], at);
+        else dma_to_lds_16(Vb, gofs[u], at + TILE * 2);
     };
     // publishes every load and LDS write of the wave
     auto wg_barrier = [&]() __attribute__((always_inline)) {
@@ -258,6 +257,9 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     // ds_new (-1: not in this run); LD: the rows of tile X + AH are requested.
     int gbase = 0;
     constexpr int LA = 4;
+    // d = 64 has the registers to start every dP accumulator from -D: no subtraction per element
+    constexpr bool FROM_D = D == 64;
+    f32x16 d_start;
     auto run = [&](int X, auto SP_, auto DQ_, auto DS_, auto LD_, f32x16 &s_new, f32x16 &p_new, const bf16x8 (&ds_old)[2],
                    f32x16 &s_old, f32x16 &p_old, bf16x8 (&ds_new)[2]) __attribute__((always_inline)) {
         constexpr int SP = decltype(SP_)::value, DQ = decltype(DQ_)::value, DS = decltype(DS_)::value;
@@ -265,17 +267,20 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
         constexpr int NS = SP >= 0 ? 2 * KSTEPS : (DQ >= 0 ? 2 * DB : 0);
         static_assert(SP < 0 || DQ < 0, "one kind of matrix work per run");
         constexpr int E = NS ? 16 / (NS ? NS : 1) : 16;  // elements of dS per matrix instruction
-        const uint32_t stage = (unsigned)(gbase + X) % KST * (TILE * 2);
-        const uint32_t kst = ks_base + stage + max(SP, DQ) * 32 * D * 2, vst = vs_base + stage + max(SP, 0) * 32 * D * 2;
+        // Block and matrix (K or V) are added after the XOR: they become the instructions' offsets, and a K and a V fragment, or
+        // those of both blocks, share an address.
+        const uint32_t stage = kv_base + (unsigned)(gbase + X) % KST * (TILE * 4);
+        constexpr uint32_t BO = (SP >= 0 ? SP : (DQ >= 0 ? DQ : 0)) * 32 * D * 2;
         bf16x8 frag[LA];
         auto request = [&](auto S) __attribute__((always_inline)) {
             constexpr int s = decltype(S)::value;
             if constexpr (s < NS) {
                 if constexpr (SP >= 0) {
-                    frag[s % LA] = lds_read_b128_at(((s % 2 == 0 ? kst : vst) + koff0) ^ (32u * (s / 2)));
+                    frag[s % LA] = lds_read_b128_at(((stage + koff0) ^ (32u * (s / 2))) + (BO + (s % 2) * TILE * 2));
                 } else {
                     constexpr int stp = s / DB, db = s % DB;
-                    frag[s % LA] = lds_read_tr_at2(kst + ktr0[db] + stp * 16 * D * 2, tr_second(kst + ktr0[db], db) + stp * 16 * D * 2);
+                    frag[s % LA] = lds_read_tr_at2(stage + ktr0[db] + (BO + stp * 16 * D * 2),
+                                                   tr_second(stage + ktr0[db], db) + (BO + stp * 16 * D * 2));
                 }
             }
         };
@@ -311,14 +316,14 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
         auto products = [&](int e0) __attribute__((always_inline)) {
 #pragma unroll
             for (int i = e0; i < e0 + E; ++i)
-                if (i >= 0 && i < 16) s_old[i] *= p_old[i] - Di;
+                if (i >= 0 && i < 16) s_old[i] *= FROM_D ? p_old[i] : p_old[i] - Di;
         };
         static_for<NS>([&](auto S) {
             constexpr int s = decltype(S)::value;
             if constexpr (SP >= 0) {
                 const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
                 if constexpr (s % 2 == 0) s_new = mfma_bf16(frag[s % LA], qreg[s / 2], s == 0 ? zero : s_new);
-                else p_new = mfma_bf16(frag[s % LA], doreg[s / 2], s == 1 ? zero : p_new);
+                else p_new = mfma_bf16(frag[s % LA], doreg[s / 2], s == 1 ? (FROM_D ? d_start : zero) : p_new);
             } else {
                 acc[s % DB] = mfma_bf16(frag[s % LA], ds_old[s / DB], acc[s % DB]);
             }
@@ -431,6 +436,8 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
             {
                 const float d0 = __shfl(part[0], 4 * (qi & 15)), d1 = __shfl(part[1], 4 * (qi & 15));
                 Di = qi < 16 ? d0 : d1;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) d_start[i] = -Di;
             }
             uint16_t *stg = &ostage[wave][0];
             const int wr0 = (lane >> 2), wc = lane & 3;
