@@ -94,8 +94,8 @@ __device__ inline FarList far_list(const sepattn_params &p, const int32_t *__res
         return f;
     }
     f.a_eff = p.a;  // already clamped to L by the host
-    f.sep_base = prefix[f.a_eff];
-    int cnt = min(prefix[p.L], p.cap);
+    f.sep_base = load_uniform(prefix, f.a_eff);
+    int cnt = min(load_uniform(prefix, p.L), p.cap);
     f.NF = f.a_eff + max(cnt - f.sep_base, 0);
     return f;
 }

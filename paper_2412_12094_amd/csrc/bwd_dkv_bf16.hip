@@ -39,15 +39,6 @@ namespace sepattn {
 
 namespace {
 
-__device__ inline int wave_min_i(int v) {
-    for (int off = 32; off > 0; off >>= 1) v = min(v, __shfl_xor(v, off));
-    return v;
-}
-__device__ inline int wave_max_i(int v) {
-    for (int off = 32; off > 0; off >>= 1) v = max(v, __shfl_xor(v, off));
-    return v;
-}
-
 // First partial row of a KV head whose workgroups are dealt by work: slots for its workgroups and list tiles, then one
 // band row per list entry, one KV head after the other.  The workgroups of a batch row are no more than with an
 // even deal, so this fits the same workspace.
@@ -172,10 +163,12 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         }
         return v;
     };
-    long far_total = 0;
-    for (int base = 0; base < NFT; base += 64) {
+    // the first group of 64 list tiles is worked out once, for the total and for the pieces
+    int first_fq, first_nq = tile_items(lane, first_fq), first_inc = inclusive_scan(first_nq);
+    long far_total = __builtin_amdgcn_readlane(first_inc, 63);
+    for (int base = 64; base < NFT; base += 64) {
         int fq;
-        far_total += __builtin_amdgcn_readfirstlane(__shfl(inclusive_scan(tile_items(base + lane, fq)), 63));
+        far_total += __builtin_amdgcn_readlane(inclusive_scan(tile_items(base + lane, fq)), 63);
     }
     // Slices.  Where the band units do not divide among the workgroups, the first `heavy` have one more than the others,
     // and far work goes to those others first, as much as a band unit costs (in items, with its start).  Without that
@@ -189,13 +182,15 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
     const int unit_steps = G * ((p.n + 30) / 32 + 1), min_slice = (every_key ? 16 : min(max(unit_steps, 4), 16)) / BPT;
     const int heavy = n_band % wpg, light = wpg - heavy;
     const long unit_items = ((long)unit_steps + kUnitStart) / BPT;
-    long per_heavy = heavy ? max((far_total - unit_items * light) / wpg, 0l) : 0;
+    // (quotients of numbers >= 0; a 64-bit division is some 150 instructions, and five of them stood at the start)
+    auto quotient = [](long x, long y) { return ((x | y) >> 31) ? x / y : (long)((uint32_t)x / (uint32_t)y); };
+    long per_heavy = heavy ? quotient(max(far_total - unit_items * light, 0l), wpg) : 0;
     if (per_heavy < min_slice) per_heavy = 0;
     const long far_light = far_total - per_heavy * heavy;
-    const long n_light = min(max(far_light / min_slice, 1l), (long)light);
+    const long n_light = min(max(quotient(far_light, min_slice), 1l), (long)light);
     const int w_light = w_id - heavy;
-    const long s0 = w_light < 0 ? w_id * per_heavy : per_heavy * heavy + min((long)w_light, n_light) * far_light / n_light;
-    const long s1 = w_light < 0 ? s0 + per_heavy : per_heavy * heavy + min(w_light + 1l, n_light) * far_light / n_light;
+    const long s0 = w_light < 0 ? w_id * per_heavy : per_heavy * heavy + quotient(min((long)w_light, n_light) * far_light, n_light);
+    const long s1 = w_light < 0 ? s0 + per_heavy : per_heavy * heavy + quotient(min(w_light + 1l, n_light) * far_light, n_light);
 
     // iteration state over the pieces: first the far pieces of the slice (list tiles in groups of 64,
     // `pend` = tiles of the current group that overlap the slice and are still to be visited), then
@@ -216,21 +211,26 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
                     }
                     grp_base = grp_next;
                     grp_cum = cum_next;
-                    g_nq = tile_items(grp_base + lane, g_fq);
-                    const int inc = inclusive_scan(g_nq);
+                    int inc = first_inc;
+                    g_nq = first_nq;
+                    g_fq = first_fq;
+                    if (grp_base > 0) {
+                        g_nq = tile_items(grp_base + lane, g_fq);
+                        inc = inclusive_scan(g_nq);
+                    }
                     g_excl = inc - g_nq;
                     pend = __ballot(g_nq > 0 && grp_cum + inc > s0 && grp_cum + g_excl < s1);
-                    cum_next = grp_cum + __builtin_amdgcn_readfirstlane(__shfl(inc, 63));
+                    cum_next = grp_cum + __builtin_amdgcn_readlane(inc, 63);
                     grp_next = grp_base + 64;
                     continue;
                 }
                 const int l = __ffsll(pend) - 1;
                 pend &= pend - 1;
-                const long first = grp_cum + __builtin_amdgcn_readfirstlane(__shfl(g_excl, l));
-                const int nq = __builtin_amdgcn_readfirstlane(__shfl(g_nq, l));
+                const long first = grp_cum + __builtin_amdgcn_readlane(g_excl, l);
+                const int nq = __builtin_amdgcn_readlane(g_nq, l);
                 const long lo_i = s0 > first ? s0 : first, hi_i = s1 < first + nq ? s1 : first + nq;
                 ft = grp_base + l;
-                fq0 = __builtin_amdgcn_readfirstlane(__shfl(g_fq, l));
+                fq0 = __builtin_amdgcn_readlane(g_fq, l);
                 item0 = (int)(lo_i - first);
                 n_items = (int)(hi_i - lo_i);
                 n_qt = nq / G;
@@ -296,18 +296,30 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         const uint32_t span_m = hi >= lo ? (uint32_t)(hi - lo) : 0u;
         // wave-uniform bounds of the keys' query ranges, in scalar registers so that the per-block
         // decisions below are scalar branches
-        const int lo_max = __builtin_amdgcn_readfirstlane(wave_max_i(lo));
-        const int hi_min = __builtin_amdgcn_readfirstlane(wave_min_i(hi));
-        const int hi2_min = HW ? __builtin_amdgcn_readfirstlane(wave_min_i(hi2)) : 0;
-
-        // resident B operand: K rows for the P-wave, V rows for the dS-wave
-        bf16x8 breg[KSTEPS];
-        {
-            const uint16_t *brow = (role == 0 ? K : V) + (kvrow0 + j) * D;
-#pragma unroll
-            for (int ks = 0; ks < KSTEPS; ++ks)
-                breg[ks] = as_bf16x8(*reinterpret_cast<const u32x4 *>(brow + ks * 16 + 8 * hh));
+        // (the keys ascend with the lane, invalid ones come last: the extremes sit in the first and the last lane, that of
+        // hi2 in the first key that is neither an initial token nor a separator)
+        const int lo_max = __builtin_amdgcn_readlane(lo, 31);
+        const int hi_min = min(__builtin_amdgcn_readlane(hi, 0), __builtin_amdgcn_readlane(hi, 31));
+        int hi2_min = 1 << 29;
+        if constexpr (HW) {
+            const unsigned long long near = __ballot(hi2 < (1 << 29));
+            if (near) hi2_min = __builtin_amdgcn_readlane(hi2, __ffsll(near) - 1);
         }
+
+        // Resident B operand: K rows for the P-wave, V rows for the dS-wave.  They come through LDS, into the half of the ring
+        // that the piece's third and fourth tile will take (8 KB per wave at d = 128, its own): a load straight into the
+        // operand layout is 64 scattered 16-byte pieces per instruction, and the number of such pieces is what it
+        // costs (with them, the start of a piece spent 7000 to 11000 cycles issuing its loads).
+        const uint32_t row_lds = (role == 0 ? q_base : do_base) + 2 * (TILE * 2) + kbw * (32 * D * 2);
+        {
+            const char *rows = reinterpret_cast<const char *>((role == 0 ? K : V) + kvrow0 * D);
+            static_for<32 / RPL>([&](auto U) {
+                const int r = decltype(U)::value * RPL + my_sub;
+                const uint32_t off = (uint32_t)__shfl(j, r) * (uint32_t)(D * 2) + swz_chunk<kSwzRow, D>(my_pc, r) * 16;
+                dma_to_lds_16(rows, off, row_lds + decltype(U)::value * 1024);
+            });
+        }
+        bf16x8 breg[KSTEPS];
         f32x16 acc[DB];  // dV^T (P-wave) or dK^T (dS-wave) of the wave's keys
 #pragma unroll
         for (int db = 0; db < DB; ++db)
@@ -630,10 +642,17 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
             while (iss_tt < n_tiles && iss_tt - NBUF < lo_cur) issue_tile();
         };
 
-        // start-up: the ring is filled, step 0 needs tile 0 only
-        while (iss_tt < n_tiles && iss_tt < NBUF) issue_tile();
+        // start-up: two tiles, the resident rows (requested before them) out of the other half of the ring, and when every
+        // wave has those, the rest of the ring.  Step 0 needs tile 0 only.
+        while (iss_tt < n_tiles && iss_tt < 2) issue_tile();
+        wait_tiles(iss_tt);
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks)
+            breg[ks] = lds_read_b128_at(row_lds + lds_off_a<kSwzRow, D>(kj, 2 * ks + hh));
         wait_tiles(iss_tt - 1);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
+        while (iss_tt < n_tiles && iss_tt < NBUF) issue_tile();
 
         // ---- software pipeline over the steps.  Between the barriers of steps s and s+1 a wave runs
         // the second contraction of its block of step s and the first of its block of step s+1, with

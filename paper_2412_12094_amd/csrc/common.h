@@ -29,6 +29,13 @@ __device__ inline void nt_store(uint4 v, uint4 *p) {
     __builtin_nontemporal_store(t, reinterpret_cast<nt_u32x4 *>(p));
 }
 
+// Element i (the same in every lane) of an array that no running kernel writes, through the scalar cache.  As an ordinary
+// load it would be a vector load here (the statements that write LDS behind the compiler's back keep it from
+// proving that nothing has changed), whose result is waited for behind every row load and row store in flight.
+__device__ inline int load_uniform(const int32_t *__restrict__ a, int i) {
+    return ((const __attribute__((address_space(4))) int32_t *)(uintptr_t)a)[__builtin_amdgcn_readfirstlane(i)];
+}
+
 // number of compute units of the current device (queried once per device; 256 if the query fails)
 int compute_units();
 

@@ -60,13 +60,6 @@ struct Stream {
     int n_init, n_dense, n_total, sep_lo, bs;
 };
 
-// Element i (the same in every lane) of an array that no running kernel writes, through the scalar cache.  As an ordinary
-// load it would be a vector load here (the statements that write LDS behind the compiler's back keep it from
-// proving that nothing has changed), whose result is waited for behind every row load and row store in flight.
-__device__ inline int load_uniform(const int32_t *__restrict__ a, int i) {
-    return ((const __attribute__((address_space(4))) int32_t *)(uintptr_t)a)[__builtin_amdgcn_readfirstlane(i)];
-}
-
 __device__ inline Stream make_stream(const sepattn_params &p, const int32_t *__restrict__ prefix, int i0,
                                      int tile_positions) {
     Stream st;
