@@ -392,7 +392,15 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     constexpr int CB = D / 32;  // column blocks of 32 columns (64 bytes of a row)
     const long head_row0 = ((long)b * p.Hq + head) * p.L;  // rows of this wave's head
     u32x4 q4[CB][2], do4[CB][2], o4[CB][2];
+    // What the start and the end of a segment derive from the lane's number is worked out anew each time: kept over the loop
+    // between them, where no register is free, it went to scratch memory.
+    auto lane_anew = [&]() __attribute__((always_inline)) {
+        int l = lane;
+        asm volatile("" : "+v"(l));
+        return l;
+    };
     auto fetch_rows = [&](const Seg &sg) __attribute__((always_inline)) {
+        const int lane = lane_anew();
         const char *qb = reinterpret_cast<const char *>(Q + head_row0 * D);
         const char *dob = reinterpret_cast<const char *>(dO + head_row0 * D);
         const char *ob = reinterpret_cast<const char *>(O + head_row0 * D);
@@ -417,6 +425,7 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
         fullb = full_blocks(cseg.st, pw, p.n - hdelta);
         if (DOCS && pw + 31 >= cseg.de) fullb = no_full_blocks();
         {
+            const int lane = lane_anew(), qi = lane & 31, hh = lane >> 5;
             // Q and dO reach their operand layout through the wave's 2 KB staging area, one column block
             // at a time (16-byte piece c of row r at piece position c ^ ((r / 4) % 4); the LDS operations
             // of a wave execute in order).  D_i = sum_k dO_ik O_ik needs no particular layout: partial
@@ -510,6 +519,7 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
         // row.  8-byte chunk ch of row r sits at chunk position ch ^ (2 * ((r / 4) % 4)); the LDS
         // operations of a wave execute in order, so a block's reads precede the next block's writes.
         {
+            const int lane = lane_anew(), qi = lane & 31, hh = lane >> 5;
             uint16_t *stg = &ostage[wave][0];
             const int wsw = ((qi >> 2) & 3) << 1;
 #pragma unroll

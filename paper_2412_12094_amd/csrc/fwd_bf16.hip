@@ -477,7 +477,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     const IntC<0> no;
     const IntC<0> first_block;
     const IntC<1> second_block;
-    const IntC<(D == 128 || NW > 4) ? 1 : 0> ahead;  // not with the 168 registers of three workgroups per compute unit
+    const IntC<1> ahead;
     for (int round = 0; cseg.i0 >= 0; ++round) {
     i0 = cseg.i0;
     pw = i0 + 32 * (wave / GP);  // first position of this wave
@@ -528,6 +528,10 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     // writes (one chunk of 32 rows) spread over the banks.  The LDS operations of a wave execute in
     // order, so a block's reads are issued before the next block's writes without a wait in between.
     {
+        // d = 64: worked out anew from the lane's number each time (kept over the loop it would go to scratch memory there)
+        int ln = lane;
+        if constexpr (D == 64) asm volatile("" : "+v"(ln));
+        const int lane = ln, qi = lane & 31, hh = lane >> 5;
         uint16_t *stg = &ostage[wave][0];
         const long orow0 = ((long)b * p.Hq + head) * p.L + pw;  // output row of the wave's first query
         const int wsw = ((qi >> 2) & 3) << 1;
