@@ -348,7 +348,7 @@ __global__ __launch_bounds__(64 * kWaves) void dkv_fp32_kernel(sepattn_params p,
                                                                HeadWin hw) {
     constexpr int C = D / 16;
     __shared__ float xs[kWaves][kT][D + 4];
-    __shared__ int last_s;
+    __shared__ int last_s, js[kT];  // js: the keys of a list tile
     const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: scalar loads and branches
     const int G = p.Hq / p.Hkv, n_bkv = p.B * p.Hkv;
@@ -494,13 +494,15 @@ __global__ __launch_bounds__(64 * kWaves) void dkv_fp32_kernel(sepattn_params p,
             const bool valid = f < fl.NF;
             const int j = valid ? far_pos(fl, f, idx, p.L) : 0;
             const int end = dend ? min(dend[j], p.L) : p.L;
+            __syncthreads();  // the tile before has been written out
+            if (threadIdx.x < kT) js[m] = j;
             run_items((int)(max(s0, F) - F), (int)(min(s1, F + items) - F), q_lo, items / G, j, valid, end, true);
             // slices w0 .. w1 hold the tile
             const int w0 = (int)(((F + 1) * slices - 1) / total), w1 = (int)(((F + items) * slices - 1) / total);
             auto to_row = [&](float *dst, float fac) {
                 return [=](int r, int col, f32x4 v) {
                     if (ft * kT + r < fl.NF)
-                        *reinterpret_cast<f32x4 *>(dst + (kvrow0 + far_pos(fl, ft * kT + r, idx, p.L)) * D + col) = v * fac;
+                        *reinterpret_cast<f32x4 *>(dst + (kvrow0 + js[r]) * D + col) = v * fac;
                 };
             };
             if (w0 == w1) {
@@ -513,20 +515,33 @@ __global__ __launch_bounds__(64 * kWaves) void dkv_fp32_kernel(sepattn_params p,
             auto slot_of = [=](int w, int which) { return slots + ((long)(w + ft) * 2 + which) * (kT * D); };
             auto to_slot = [&](int which) {
                 float *dst = slot_of(unit, which);
-                return [=](int r, int col, f32x4 v) { *reinterpret_cast<f32x4 *>(dst + r * D + col) = v; };
+                return [=](int r, int col, f32x4 v) {
+                    publish(dst + r * D + col, float2{v[0], v[1]});
+                    publish(dst + r * D + col + 2, float2{v[2], v[3]});
+                };
             };
             add_waves(ak, to_slot(0));
             add_waves(av, to_slot(1));
-            __threadfence();  // the slot is visible to every workgroup before the count is
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's part of the slot is where every XCD sees it
             __syncthreads();
             if (threadIdx.x == 0) last_s = atomicAdd(&counters[(long)bkv * n_far_tiles + ft], 1) == w1 - w0;
             __syncthreads();
             if (!last_s) continue;
-            __threadfence();
             for (int e = threadIdx.x; e < 2 * kT * D / 4; e += 64 * kWaves) {
                 const int which = e / (kT * D / 4), r = (e / (D / 4)) % kT, col = (e % (D / 4)) * 4;
                 f32x4 v = {0.f, 0.f, 0.f, 0.f};
-                for (int w = w0; w <= w1; ++w) v += *reinterpret_cast<const f32x4 *>(slot_of(w, which) + r * D + col);
+                constexpr int NB = 4;  // slots requested together
+                for (int w = w0; w <= w1; w += NB) {
+                    float2 x[NB], y[NB];
+#pragma unroll
+                    for (int k = 0; k < NB; ++k) {
+                        const float *src = slot_of(min(w + k, w1), which) + r * D + col;
+                        x[k] = fetch_published(src), y[k] = fetch_published(src + 2);
+                    }
+#pragma unroll
+                    for (int k = 0; k < NB; ++k)
+                        if (w + k <= w1) v += f32x4{x[k].x, x[k].y, y[k].x, y[k].y};
+                }
                 if (which == 0) to_row(dK, p.scale)(r, col, v);
                 else to_row(dV, 1.f)(r, col, v);
             }

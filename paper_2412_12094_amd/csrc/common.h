@@ -36,6 +36,16 @@ __device__ inline int load_uniform(const int32_t *__restrict__ a, int i) {
     return ((const __attribute__((address_space(4))) int32_t *)(uintptr_t)a)[__builtin_amdgcn_readfirstlane(i)];
 }
 
+// Values that pass between workgroups of one launch, which may run on different XCDs, whose L2 caches are not coherent with
+// each other: stored and loaded as device-scope atomics of 8 bytes, which go past the L2 (a fence would write back all of
+// it).  The publisher waits for its stores (s_waitcnt vmcnt(0)) before it counts itself in.
+__device__ inline void publish(float *dst, float2 v) {
+    __hip_atomic_store(reinterpret_cast<uint64_t *>(dst), __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline float2 fetch_published(const float *src) {
+    return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const uint64_t *>(src), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+
 // number of compute units of the current device (queried once per device; 256 if the query fails)
 int compute_units();
 

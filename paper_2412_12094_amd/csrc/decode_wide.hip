@@ -67,15 +67,6 @@ __device__ inline float groups_sum(float x) {
 __device__ inline f32x4 lds_read_f4(uint32_t addr) { return *(const f32x4 __attribute__((address_space(3))) *)addr; }
 #pragma clang diagnostic pop
 
-// The slices' records pass between workgroups that may run on different XCDs, whose L2 caches are not coherent with
-// each other: they are stored and loaded as device-scope atomics of 8 bytes, which go past the L2.
-__device__ inline void publish(float *dst, float2 v) {
-    __hip_atomic_store(reinterpret_cast<uint64_t *>(dst), __builtin_bit_cast(uint64_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline float2 fetch_published(const float *src) {
-    return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const uint64_t *>(src), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-}
-
 // How many slices of a (sequence, KV head) have published their records: the low 8 bits of a word in the caller's
 // workspace, which nobody clears.  The word counts only while its upper 56 bits hold a fixed pattern.  Every slice looks
 // at it before its own work and, if it is anything else, replaces what it saw by "none"; a slice that sees the pattern,
