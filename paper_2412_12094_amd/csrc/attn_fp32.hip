@@ -22,7 +22,7 @@
 // pair can do to a sum is to make it NaN, a wave looks at its finished sums and, if one is NaN, forms them once more
 // with vector arithmetic over the visible pairs only.  Finite inputs pay for the look: 43.9 -> 44.6 us for the call
 // below; B=1, 32/8 heads, L=4096, d=128, n=256 451 us forward and 1858 backward with it, 452 and 1866 without.
-// B=1, 2 heads per KV head, L=512, d=64, n=64: forward 22 -> 7 us, D_i and dQ 5 + 23 -> 8, dK/dV 168 -> 20, against one
+// B=1, 2 heads per KV head, L=512, d=64, n=64: forward 22 -> 7 us, D_i and dQ 5 + 23 -> 8, dK/dV 168 -> 16, against one
 // wave per row on the vector ALU.
 #include "bwd_common.h"
 #include "key_stream.h"
@@ -34,9 +34,11 @@ namespace {
 
 constexpr int kT = 16;      // queries / keys per block
 constexpr int kWaves = 4;   // waves per workgroup
-// (query block, head) items per far slice: two per wave.  An item costs a wave about 1.3 us, sharing a
-// list tile among slices about 3 us once: with 4 or 16 items the same call is 1 and 2.5 us slower.
-constexpr int kMinItems = 8;
+// (query block, head) items per far slice: one per wave, more where a list tile of the whole sequence would be shared among
+// more than kMaxShare slices, whose sums one workgroup adds.  Backward, us, with 4 / 8 / the rule: 2 heads per KV head,
+// L=512, d=64 23.0 / 23.9 / 23.0; 4 and 4 heads, 2 x L=300, d=128 32.7 / 36.4 / 32.7; 4 heads per KV head, 2 x L=1000, d=64
+// 34.0 / 30.7 / 30.7.
+constexpr int kMinItems = 4, kMaxShare = 32;
 
 __device__ inline f32x4 mfma_f32(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
@@ -331,7 +333,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void dq_fp32_kernel(s
 // initial tokens nor separators count (a band unit: the queries of their window), and consecutive
 // entries of the far list (every query from the tile's first key to the end of the sequence or
 // document).  The items (query block, head) of all list tiles of a (batch, KV head), in order, are
-// cut into equal slices, one per workgroup, at most `wpg` of them and none shorter than kMinItems; a
+// cut into equal slices, one per workgroup, at most `wpg` of them and none shorter than kMinItems (and see kMaxShare); a
 // list tile that lies in one slice is finished there, otherwise each slice writes a partial (slot
 // slice + tile) and the workgroup that is the last to count itself in adds them in slice order.
 // Every wave of a workgroup keeps the tile's K and V rows and its own dK and dV sums in registers.
@@ -477,9 +479,9 @@ __global__ __launch_bounds__(64 * kWaves) void dkv_fp32_kernel(sepattn_params p,
         int unused;
         total += __shfl(inclusive_scan(tile_items(t0 + lane, unused)), 63);
     }
-    const long slices = min((long)wpg, max(1l, total / kMinItems));
+    const long slices = min((long)wpg, max(1l, quotient(total, max(kMinItems, G * ((p.L + kT - 1) / kT) / kMaxShare))));
     if (unit >= slices || total == 0) return;
-    const long s0 = unit * total / slices, s1 = (unit + 1) * total / slices;
+    const long s0 = quotient(unit * total, slices), s1 = quotient((unit + 1) * total, slices);
     long cum = 0;
     for (int t0 = 0; t0 < NFT && cum < s1; t0 += 64) {
         if (t0 > 0) {
@@ -498,7 +500,7 @@ __global__ __launch_bounds__(64 * kWaves) void dkv_fp32_kernel(sepattn_params p,
             if (threadIdx.x < kT) js[m] = j;
             run_items((int)(max(s0, F) - F), (int)(min(s1, F + items) - F), q_lo, items / G, j, valid, end, true);
             // slices w0 .. w1 hold the tile
-            const int w0 = (int)(((F + 1) * slices - 1) / total), w1 = (int)(((F + items) * slices - 1) / total);
+            const int w0 = (int)quotient((F + 1) * slices - 1, total), w1 = (int)quotient((F + items) * slices - 1, total);
             auto to_row = [&](float *dst, float fac) {
                 return [=](int r, int col, f32x4 v) {
                     if (ft * kT + r < fl.NF)
@@ -530,7 +532,7 @@ __global__ __launch_bounds__(64 * kWaves) void dkv_fp32_kernel(sepattn_params p,
             for (int e = threadIdx.x; e < 2 * kT * D / 4; e += 64 * kWaves) {
                 const int which = e / (kT * D / 4), r = (e / (D / 4)) % kT, col = (e % (D / 4)) * 4;
                 f32x4 v = {0.f, 0.f, 0.f, 0.f};
-                constexpr int NB = 4;  // slots requested together
+                constexpr int NB = 8;  // slots requested together
                 for (int w = w0; w <= w1; w += NB) {
                     float2 x[NB], y[NB];
 #pragma unroll

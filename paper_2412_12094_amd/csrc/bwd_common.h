@@ -31,6 +31,10 @@ inline int dkv_workgroups_per_cu(const sepattn_params &p, int kw) { return kw ==
 
 __host__ __device__ inline int align_down32(int x) { return x & ~31; }
 
+// x / y of numbers >= 0: a 64-bit division is some 150 instructions, and four or five of them stand at the start of a
+// dK/dV kernel
+__device__ inline long quotient(long x, long y) { return ((x | y) >> 31) ? x / y : (long)((uint32_t)x / (uint32_t)y); }
+
 // The far work of one (batch, KV head): for list tile ft (bk = 32 KW consecutive list entries) the
 // "items" (query tile, query head) from the first query that can see the tile's first key
 // to the end of the sequence.  The items of all list tiles, in this order, are cut into slices, at

@@ -182,8 +182,6 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
     const int unit_steps = G * ((p.n + 30) / 32 + 1), min_slice = (every_key ? 16 : min(max(unit_steps, 4), 16)) / BPT;
     const int heavy = n_band % wpg, light = wpg - heavy;
     const long unit_items = ((long)unit_steps + kUnitStart) / BPT;
-    // (quotients of numbers >= 0; a 64-bit division is some 150 instructions, and five of them stood at the start)
-    auto quotient = [](long x, long y) { return ((x | y) >> 31) ? x / y : (long)((uint32_t)x / (uint32_t)y); };
     long per_heavy = heavy ? quotient(max(far_total - unit_items * light, 0l), wpg) : 0;
     if (per_heavy < min_slice) per_heavy = 0;
     const long far_light = far_total - per_heavy * heavy;
