@@ -47,14 +47,29 @@ struct FarGeom {
     int NFcap;   // capacity of the far list, a multiple of bk
     int NFTcap;  // list tiles at full capacity
     int NP;      // partial slots per (batch, KV head)
-    long rows;   // fp32 partial rows per (batch, KV head): NP slots of bk rows, then one band row per list entry
+    long rows;   // fp32 partial rows per (batch, KV head): NP slots of bk rows, then one band row per list entry (band units
+                 // that are split among workgroups, see band_split: bk rows per part)
 };
 inline int dkv_workgroups_per_head(const sepattn_params &p, int kw) {
     const long n_bkv = (long)p.B * p.Hkv;
     const long w = dkv_workgroups_per_cu(p, kw) * (long)compute_units() / n_bkv;
     return (int)(w < 1 ? 1 : w);
 }
-__host__ __device__ inline FarGeom far_geom(const sepattn_params &p, int wpg, int kw) {
+// Among how many workgroups a band unit (32 KW keys and their windows, all query heads of the KV head) is split, by query
+// heads.  A unit is a chain of G ((n + 30) / 32 + 1) steps of 0.7 us on one workgroup; where there are fewer units than
+// workgroups it sets the time of the kernel.  Split, every key's sums pass through fp32 partials and the combine
+// kernel.  The largest number that divides the heads, gives no workgroup two parts, leaves a part four steps and
+// spares eight: 8/2 heads, d = 128, L = 600, n = 96 (20 steps) dK/dV and combine 22.3 + 4.5 -> 13.6 + 5.3 us.
+// (any_n: for the workspace, whose size does not depend on the window: the largest split of any window.)
+inline int band_split(const sepattn_params &p, int wpg, int kw, bool any_n = false) {
+    const int G = p.Hq / p.Hkv, steps = any_n ? 1 << 20 : ((p.n < p.L ? p.n : p.L) + 30) / 32 + 1;
+    const long units = ((long)p.L + 32 * kw - 1) / (32 * kw);
+    int split = 1;
+    for (int s = 2; s <= G; ++s)
+        if (G % s == 0 && units * s <= wpg && (long)G / s * steps >= 4 && (long)(G - G / s) * steps >= 8) split = s;
+    return split;
+}
+__host__ __device__ inline FarGeom far_geom(const sepattn_params &p, int wpg, int kw, int split = 1) {
     FarGeom g;
     g.wpg = wpg;
     g.bk = 32 * kw;
@@ -62,6 +77,10 @@ __host__ __device__ inline FarGeom far_geom(const sepattn_params &p, int wpg, in
     g.NFTcap = g.NFcap / g.bk;
     g.NP = wpg + g.NFTcap;
     g.rows = (long)g.NP * g.bk + g.NFcap;
+    if (split > 1) {
+        const long band = ((long)p.L + g.bk - 1) / g.bk * g.bk * split;
+        if (band > g.NFcap) g.rows = (long)g.NP * g.bk + band;
+    }
     return g;
 }
 
@@ -76,7 +95,8 @@ inline BwdWorkspace bwd_workspace(const sepattn_params &p) {
     w.far_bytes = w.tab_bytes = 0;
     // the eight-wave shape exists at d = 128 only
     for (int kw = 2; kw <= (p.d == 128 ? 4 : 2); kw += 2) {
-        const FarGeom fg = far_geom(p, dkv_workgroups_per_head(p, kw), kw);
+        const int wpg = dkv_workgroups_per_head(p, kw);
+        const FarGeom fg = far_geom(p, wpg, kw, band_split(p, wpg, kw, true));
         const size_t far = align_up((size_t)p.B * p.Hkv * fg.rows * p.d * sizeof(float), 256);
         const size_t tab = align_up((size_t)p.B * p.Hkv * fg.NFTcap * 2 * sizeof(int32_t), 256);
         w.far_bytes = far > w.far_bytes ? far : w.far_bytes;

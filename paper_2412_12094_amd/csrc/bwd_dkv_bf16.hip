@@ -56,7 +56,7 @@ __device__ inline long shared_part_row(const FarGeom &even, const WorkShare &w, 
 // A KV head whose query heads all see every earlier key (n >= L) may have no band (`share.all`, see list_of_all_keys):
 // its list is then that of ALL keys and its far pairs are i >= j, so that this work is cut into equal slices too; as
 // a band unit the first keys' walk through the whole sequence is one workgroup's.
-template <int D, bool DOCS, bool HW, int KW>
+template <int D, bool DOCS, bool HW, int KW, bool PARTS>
 __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv_kernel(
     sepattn_params p, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     const uint16_t *__restrict__ V, const float *__restrict__ LSE2, const uint16_t *__restrict__ dO,
@@ -64,7 +64,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
     const int32_t *__restrict__ sep_prefix, const int32_t *__restrict__ doc_end,
     uint16_t *__restrict__ dK, uint16_t *__restrict__ dV,
     float *__restrict__ farK, float *__restrict__ farV, int32_t *__restrict__ piece_tab, int wpg, int n_band,
-    HeadWin hw, WorkShare share) {
+    int split, HeadWin hw, WorkShare share) {
     constexpr int NW = 2 * KW;               // waves per workgroup
     constexpr int BK = 32 * KW;              // keys per workgroup
     constexpr int CH = D / 8;                // 16-byte chunks per row
@@ -94,11 +94,13 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
     const int kbw = wave % KW;   // key block of the wave
     const int kj = lane & 31, hh = lane >> 5;
     const int G = p.Hq / p.Hkv;
+    if constexpr (!PARTS) split = 1;
+    const int Gs = G / split;  // query heads per part of a band unit (see band_split); n_band counts the parts
     // 1-D grid: consecutive workgroups belong to consecutive (batch, KV head) pairs, so with 8 KV heads
     // each head's K, V, Q, dO rows stay in the L2 of one XCD.
     const int n_bkv = p.B * p.Hkv;
     int bkv = blockIdx.x % n_bkv, w_id = blockIdx.x / n_bkv;
-    long part0 = bkv * far_geom(p, wpg, KW).rows;  // first partial row of the (batch, KV head)
+    long part0 = bkv * far_geom(p, wpg, KW, split).rows;  // first partial row of the (batch, KV head)
     int gdelta = 0;
     bool every_key = false;
     if constexpr (HW) {
@@ -179,7 +181,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
     // item, 22 + 4 now).  The slices that are not empty belong to consecutive workgroups, which is what the combine
     // kernel relies on.
     constexpr int kUnitStart = 8;  // steps of 32 query rows
-    const int unit_steps = G * ((p.n + 30) / 32 + 1), min_slice = (every_key ? 16 : min(max(unit_steps, 4), 16)) / BPT;
+    const int unit_steps = Gs * ((p.n + 30) / 32 + 1), min_slice = (every_key ? 16 : min(max(unit_steps, 4), 16)) / BPT;
     const int heavy = n_band % wpg, light = wpg - heavy;
     const long unit_items = ((long)unit_steps + kUnitStart) / BPT;
     long per_heavy = heavy ? quotient(max(far_total - unit_items * light, 0l), wpg) : 0;
@@ -209,10 +211,10 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
                     }
                     grp_base = grp_next;
                     grp_cum = cum_next;
-                    int inc = first_inc;
                     g_nq = first_nq;
                     g_fq = first_fq;
-                    if (grp_base > 0) {
+                    int inc = first_inc;
+                    if (HW || grp_base > 0) {  // head-wise: once more, rather than registers that d = 64 does not have
                         g_nq = tile_items(grp_base + lane, g_fq);
                         inc = inclusive_scan(g_nq);
                     }
@@ -267,7 +269,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
             hi = q_hi - 1;
             if constexpr (DOCS) hi = min(hi, dend[j] - 1);
         } else {
-            int j0 = unit * BK;
+            int j0 = unit / split * BK;
             j = j0 + 32 * kbw + kj;
             valid = j < p.L;
             q_lo = j0;
@@ -282,7 +284,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
             if constexpr (DOCS) hi = min(hi, dend[j] - 1);
             item0 = 0;
             n_qt = (q_hi - q_lo + BQ - 1) / BQ;
-            n_items = G * n_qt;
+            n_items = Gs * n_qt;
         }
         if (!valid) {
             lo = kIntMax;
@@ -346,7 +348,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         if (BPT == 1 && st_P < 3) st_P = 3;
         if (FAR || st_P > nbh) st_P = nbh;
         const int st_ov = nbh - st_P;                            // 0 .. KW-1
-        const int st_G = FAR ? 1 : G;
+        const int st_G = FAR ? 1 : Gs;
         const int n_blocks = (st_G - 1) * st_P + nbh;            // steps of the piece
         const int tiles_per_head = FAR ? 0 : n_qt;
 
@@ -356,6 +358,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         // masked by the [lo, hi] test: hi <= L-1).  Tiles are issued in order; (iss_g, iss_qt) is the
         // (head, query tile) of the next one.
         int iss_tt = 0, iss_g = item0 / n_qt, iss_qt = item0 % n_qt;
+        if (PARTS && !FAR) iss_g = unit % split * Gs;  // the part's first head
         auto issue_tile = [&]() {
             const int buf = iss_tt % NBUF;
             const long hrow0 = ((long)b * p.Hq + kv * G + iss_g) * (long)p.L;
@@ -727,7 +730,10 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         float *farX = role == 0 ? farV : farK;
         long part_row = (long)(w_id + ft) * BK + 32 * kbw + kj;
         bool to_partial = FAR;
-        if (!FAR && valid) {
+        if (PARTS && !FAR) {
+            to_partial = true;
+            part_row = (long)fg.NP * BK + (long)unit * BK + 32 * kbw + kj;
+        } else if (!FAR && valid) {
             const int f = far_index(fl, prefix, j);
             if (f >= 0 && far_first_query(fl, f, idx, p, BK) < far_last_query(fl, f, idx, p, dend, BK)) {
                 to_partial = true;
@@ -845,6 +851,78 @@ __global__ __launch_bounds__(256) void dkv_combine_kernel(sepattn_params p, cons
     }
 }
 
+// The same where band units are split among workgroups (band_split): every key is finished here, from the parts of its band
+// unit and, if it is on the list, its far pieces.
+template <int D>
+__global__ __launch_bounds__(256) void dkv_combine_parts_kernel(sepattn_params p, const int32_t *__restrict__ sep_idx,
+                                                                const int32_t *__restrict__ sep_prefix,
+                                                                const int32_t *__restrict__ doc_end,
+                                                                uint16_t *__restrict__ dK, uint16_t *__restrict__ dV,
+                                                                const float *__restrict__ farK,
+                                                                const float *__restrict__ farV,
+                                                                const int32_t *__restrict__ piece_tab, int wpg, int kw,
+                                                                int split) {
+    constexpr int TPR = D / 4, RPB = 256 / TPR;  // threads per row, rows per workgroup
+    const int bkv = blockIdx.y, b = bkv / p.Hkv;
+    const FarGeom fg = far_geom(p, wpg, kw, split);
+    const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
+    const int32_t *idx = sep_idx + (long)b * p.cap;
+    const int32_t *dend = doc_end ? doc_end + (long)b * p.L : nullptr;
+    const int lt = fg.bk, j = blockIdx.x * RPB + threadIdx.x / TPR, col = (threadIdx.x % TPR) * 4;
+    if (j >= p.L) return;
+    const long row0 = bkv * fg.rows;
+    float4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
+    // `count` partial rows `step` rows apart from `first` on, NB at a time (the last one again past the end), in order
+    auto request = [&](auto NB_, long first, long step, int h, int count, auto &x, auto &y) __attribute__((always_inline)) {
+        constexpr int NB = decltype(NB_)::value;
+#pragma unroll
+        for (int c = 0; c < NB; ++c) {
+            const long at = (first + min(h + c, count - 1) * step) * D + col;
+            x[c] = *reinterpret_cast<const float4 *>(farK + at);
+            y[c] = *reinterpret_cast<const float4 *>(farV + at);
+        }
+    };
+    auto add = [&](auto NB_, int h, int count, const auto &x, const auto &y) __attribute__((always_inline)) {
+        constexpr int NB = decltype(NB_)::value;
+#pragma unroll
+        for (int c = 0; c < NB; ++c) {
+            if (h + c < count) {
+                sk.x += x[c].x, sk.y += x[c].y, sk.z += x[c].z, sk.w += x[c].w;
+                sv.x += y[c].x, sv.y += y[c].y, sv.z += y[c].z, sv.w += y[c].w;
+            }
+        }
+    };
+    // the parts are in flight while the far pieces are found (two more round trips)
+    const long part0 = row0 + (long)(fg.NP + j / lt * split) * lt + j % lt;
+    const IntC<4> four;
+    const IntC<8> eight;
+    float4 bk[4], bv[4], x[8], y[8];
+    request(four, part0, lt, 0, split, bk, bv);
+    const FarList fl = far_list(p, prefix);
+    const int f = far_index(fl, prefix, j);
+    if (f >= 0) {
+        const int ft = f / lt;
+        const int32_t *tab = piece_tab + ((long)bkv * fg.NFTcap + ft) * 2;
+        const int t0 = tab[0], t1 = tab[1];
+        if (far_first_query(fl, f, idx, p, lt) < far_last_query(fl, f, idx, p, dend, lt)) {
+            // the clamps keep a table that the far pass did not write (it always does) from faulting
+            const int w0 = min(max(t0, 0), wpg - 1), n = min(max(t1, w0), wpg - 1) - w0 + 1;
+            for (int h = 0; h < n; h += 8) {
+                request(eight, row0 + (long)(w0 + ft) * lt + (f - ft * lt), lt, h, n, x, y);
+                add(eight, h, n, x, y);
+            }
+        }
+    }
+    add(four, 0, split, bk, bv);
+    for (int h = 4; h < split; h += 4) {
+        request(four, part0, lt, h, split, bk, bv);
+        add(four, h, split, bk, bv);
+    }
+    const long orow = ((long)bkv * p.L + j) * D + col;
+    *reinterpret_cast<uint2 *>(dK + orow) = pack_bf16x4(sk.x, sk.y, sk.z, sk.w);
+    *reinterpret_cast<uint2 *>(dV + orow) = pack_bf16x4(sv.x, sv.y, sv.z, sv.w);
+}
+
 // Whether KV heads that see every earlier key work through the list of all keys (see dkv_kernel).  As band units their
 // work is q = units / workgroups walks per workgroup, the longest about 1 + 1/q times the mean; as slices it is even, but
 // every key's gradients pass through fp32 partials.  That pays where a workgroup has about one unit (eight waves,
@@ -864,18 +942,18 @@ template <int D, int KW>
 void launch_dkv_shape(const sepattn_params &p, const HeadWin &hw, bool headwise, const uint16_t *Q, const uint16_t *K,
                       const uint16_t *V, const float *lse2, const uint16_t *dO, const float *Dws, const int32_t *sep_idx,
                       const int32_t *sep_prefix, const int32_t *doc_end, uint16_t *dK, uint16_t *dV, float *farK,
-                      float *farV, int32_t *piece_tab, int wpg, const WorkShare &share, hipStream_t st) {
-    const int band_grid = (p.L + 32 * KW - 1) / (32 * KW);
+                      float *farV, int32_t *piece_tab, int wpg, int split, const WorkShare &share, hipStream_t st) {
+    const int band_grid = (p.L + 32 * KW - 1) / (32 * KW) * split;
     const dim3 grid((unsigned)(headwise ? (long)p.B * share.first[share.n] : (long)wpg * p.B * p.Hkv)), block(128 * KW);
-    if (doc_end)
-        hipLaunchKernelGGL((dkv_kernel<D, true, false, KW>), grid, block, 0, st, p, Q, K, V, lse2, dO, Dws, sep_idx,
-                           sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, band_grid, hw, share);
-    else if (headwise)
-        hipLaunchKernelGGL((dkv_kernel<D, false, true, KW>), grid, block, 0, st, p, Q, K, V, lse2, dO, Dws, sep_idx,
-                           sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, band_grid, hw, share);
-    else
-        hipLaunchKernelGGL((dkv_kernel<D, false, false, KW>), grid, block, 0, st, p, Q, K, V, lse2, dO, Dws, sep_idx,
-                           sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, band_grid, hw, share);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, st, p, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg,
+                           band_grid, split, hw, share);
+    };
+    if (doc_end && split == 1) go(dkv_kernel<D, true, false, KW, false>);
+    else if (headwise) go(dkv_kernel<D, false, true, KW, false>);
+    else if (split == 1) go(dkv_kernel<D, false, false, KW, false>);
+    else if (doc_end) go(dkv_kernel<D, true, false, KW, true>);
+    else go(dkv_kernel<D, false, false, KW, true>);
 }
 
 template <int D>
@@ -901,22 +979,27 @@ int launch_dkv(const sepattn_params &p, const HeadWin &hw, bool headwise, const 
     } else {
         share.all[0] = list_all && p.n >= p.L;
     }
+    const int split = headwise || share.all[0] ? 1 : band_split(p, wpg, kw);
     {
         ProfScope prof(SEPATTN_K_BWD_DKV, st);
         // the eight-wave shape exists for d = 128 only (dkv_key_blocks)
         if (D == 128 && kw == 4)
-            launch_dkv_shape<128, 4>(p, hw, headwise, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, share, st);
+            launch_dkv_shape<128, 4>(p, hw, headwise, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, split, share, st);
         else
-            launch_dkv_shape<D, 2>(p, hw, headwise, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, share, st);
+            launch_dkv_shape<D, 2>(p, hw, headwise, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, split, share, st);
     }
     if (hipGetLastError() != hipSuccess) return SEPATTN_ERR_HIP;
     ProfScope prof(SEPATTN_K_BWD_COMBINE, st);
     const int rows_per_block = 256 / (D / 4);
     bool every_key = share.all[0] != 0;
     for (int i = 1; i < share.n; ++i) every_key = every_key || share.all[i] != 0;
-    const int list_rows = every_key ? fg.NFcap : (fg.NFcap + 7) / 8;
-    hipLaunchKernelGGL((dkv_combine_kernel<D>), dim3((list_rows + rows_per_block - 1) / rows_per_block, p.B * p.Hkv),
-                       dim3(256), 0, st, p, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, kw, hw, share);
+    const bool split_rows = split > 1 && !every_key;
+    const int list_rows = split_rows ? p.L : every_key ? fg.NFcap : (fg.NFcap + 7) / 8;
+    const dim3 grid((list_rows + rows_per_block - 1) / rows_per_block, p.B * p.Hkv);
+    if (split_rows)
+        hipLaunchKernelGGL((dkv_combine_parts_kernel<D>), grid, dim3(256), 0, st, p, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, kw, split);
+    else
+        hipLaunchKernelGGL((dkv_combine_kernel<D>), grid, dim3(256), 0, st, p, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, kw, hw, share);
     return launch_status();
 }
 

@@ -89,3 +89,16 @@ def test_bf16_head_groups_by_work(B, Hq, Hkv, L, d, a, p, nh):
 ])
 def test_bf16_windows_of_the_whole_sequence(B, Hq, Hkv, L, d, a, n, p):
     run(B, Hq, Hkv, L, d, a, n, p, "bf16")
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,d,a,n,p", [
+    (1, 8, 2, 600, 128, 4, 96, 0.1),    # a band unit in four parts of one head
+    (1, 8, 2, 600, 64, 4, 96, 0.1),
+    (1, 7, 1, 130, 64, 2, 100, 0.1),    # seven parts
+    (2, 12, 2, 333, 128, 0, 64, 0.0),   # three parts of two heads; nothing on the list
+    (4, 32, 8, 256, 128, 4, 128, 0.1),  # as many parts as workgroups
+    (4, 32, 8, 257, 128, 4, 128, 0.1),  # one key more: two parts
+    (1, 8, 1, 8200, 128, 4, 40, 0.05),  # eight-wave workgroups
+])
+def test_bf16_band_units_in_parts(B, Hq, Hkv, L, d, a, n, p):
+    run(B, Hq, Hkv, L, d, a, n, p, "bf16")
