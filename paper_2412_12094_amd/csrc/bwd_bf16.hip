@@ -65,6 +65,7 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     const int32_t *__restrict__ doc_end, uint16_t *__restrict__ dQ, float *__restrict__ Dws,
     float *__restrict__ Lws, int wpg, HeadWin hw, WorkShare share) {
     constexpr int TP = 32 * NW / GP;
+    constexpr bool OWN_END = TP > 32;  // the waves' streams end at different tiles (as in the forward)
     constexpr int CH = D / 8;
     constexpr int RPL = 64 / CH;      // rows covered by one wave-wide 1 KB load
     constexpr int NLD = kBN / RPL;    // wave-wide loads per tensor per tile
@@ -484,9 +485,12 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
 
         // Step X reads tile gbase+X and requests tile gbase+X+AH, whose stages held tile gbase+X-AH; barriers stand in
         // front of every AH-th tile of the concatenated stream, where everything requested before has landed.  The
-        // second block of the last tile is left out when it is all padding (the same decision in every wave).
+        // second block of the wave's last tile is left out when it is all padding or beyond the wave's last position; in
+        // tiles beyond that (OWN_END) the wave only takes part in the loads.
         // (A tail after the loop: alternatives inside it would cost a copy of the accumulators per tile.)
-        const int n_tiles = cseg.n_tiles, n_whole = (cseg.st.n_total + 31) / kBN;
+        const int n_tiles = cseg.n_tiles;
+        const int my_total = OWN_END ? min(cseg.st.n_total, cseg.st.n_dense + pw + 32 - cseg.st.bs) : cseg.st.n_total;
+        const int n_whole = (my_total + 31) / kBN, my_tiles = OWN_END ? (my_total + kBN - 1) / kBN : n_tiles;
         auto begin_tile = [&](int X) __attribute__((always_inline)) {
             if ((gbase + X) % AH == 0) wg_barrier();
             look_ahead(gbase + X);
@@ -501,11 +505,17 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
             run(X, none, first, second, off, s0, p0, ds0, s1, p1, ds1);
             run(X, none, second, none, off, s0, p0, ds1, s1, p1, ds1);
         }
-        if (n_whole < n_tiles) {
+        if (n_whole < my_tiles) {
             begin_tile(n_whole);
             run(n_whole, first, none, none, on, s0, p0, ds0, s0, p0, ds0);
             run(n_whole, none, none, first, off, s1, p1, ds0, s0, p0, ds0);
             run(n_whole, none, first, none, off, s1, p1, ds0, s0, p0, ds0);
+        }
+        if constexpr (OWN_END) {
+            for (int X = my_tiles; X < n_tiles; ++X) {
+                begin_tile(X);
+                static_for<2 * LOADS>([&](auto N) { issue_row(gbase + X + AH, N); });
+            }
         }
         gbase += n_tiles;
         const Seg nseg = open_segment(round + 1);

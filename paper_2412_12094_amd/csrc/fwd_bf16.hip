@@ -44,6 +44,10 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     const int32_t *__restrict__ sep_prefix, const int32_t *__restrict__ doc_start,
     const int32_t *__restrict__ doc_end, uint16_t *__restrict__ O, float *__restrict__ LSE, int wpg, HeadWin hw, WorkShare share) {
     constexpr int TP = 32 * NW / GP;  // query positions per workgroup
+    // The waves' streams end at different tiles: a wave that is past its last position leaves the arithmetic of the rest out
+    // (12 heads, d = 64, 8 x L = 2048, n = 64, four waves of 32 positions each: forward and backward 170.0 -> 165.1 us, of
+    // which the forward 2.6; with TP = 32 there is nothing to leave out, and the code for it is not there).
+    constexpr bool OWN_END = TP > 32;
     constexpr int CH = D / 8;         // 16-byte chunks per row
     constexpr int RPL = 64 / CH;      // rows covered by one wave-wide 1 KB load
     constexpr int NLD = kBN / RPL;    // wave-wide loads per tensor per tile
@@ -477,7 +481,13 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     const IntC<0> no;
     const IntC<0> first_block;
     const IntC<1> second_block;
-    const IntC<1> ahead;
+    // a tile step of a wave that is through with its own blocks
+    auto loads_only = [&](int X) __attribute__((always_inline)) {
+        look_ahead(gbase + X);
+        read_offsets(gbase + X + AH);
+        static_for<LOADS>([&](auto U) { issue_v(gbase + X + AH - 1, U); });
+        static_for<LOADS>([&](auto U) { issue_k(gbase + X + AH, U); });
+    };
     for (int round = 0; cseg.i0 >= 0; ++round) {
     i0 = cseg.i0;
     pw = i0 + 32 * (wave / GP);  // first position of this wave
@@ -485,6 +495,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     iq_h = iq + hdelta;          // ... as the upper ends of the keys' query ranges (computed with p.n) see it
     st = cseg.st;
     n_tiles = cseg.n_tiles;
+    // tiles up to the wave's last position; in those beyond it only takes part in the loads
+    const int my_tiles = OWN_END ? (min(st.n_total, st.n_dense + pw + 32 - st.bs) + kBN - 1) / kBN : n_tiles;
     fullb = full_blocks(st, pw, p.n - hdelta);
     if (DOCS && pw + 31 >= cseg.de) fullb = no_full_blocks();
 #pragma unroll
@@ -502,18 +514,26 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     look_ahead(gbase);
     half_step(0, first_block, yes, no, no, yes, no, no, s_a, p_a, s_b, p_b, 0, 0);
     half_step(0, second_block, yes, no, yes, no, no, no, s_b, p_b, s_a, p_a, 0, 0);
-    for (int X = 1; X < n_tiles; ++X) {
+    int X = 1;
+    for (; X < my_tiles; ++X) {
         if ((gbase + X) % AH == 0) wg_barrier();
         look_ahead(gbase + X);
-        half_step(X, first_block, yes, yes, yes, yes, no, ahead, s_a, p_a, s_b, p_b, X - 1, 1);
-        half_step(X, second_block, yes, yes, yes, no, ahead, no, s_b, p_b, s_a, p_a, X, 0);
+        half_step(X, first_block, yes, yes, yes, yes, no, yes, s_a, p_a, s_b, p_b, X - 1, 1);
+        half_step(X, second_block, yes, yes, yes, no, yes, no, s_b, p_b, s_a, p_a, X, 0);
     }
     // last step: output updates of the last tile, softmax of its second block; the queries of the
     // next segment are fetched meanwhile (the registers are free: no score block in this step)
-    if ((gbase + n_tiles) % AH == 0) wg_barrier();
+    if ((gbase + X) % AH == 0) wg_barrier();
+    if (OWN_END && X < n_tiles) loads_only(X);
     if (cnext.i0 >= 0) load_queries(cnext.i0);
-    half_step(n_tiles, first_block, no, yes, yes, no, no, no, s_a, p_a, s_b, p_b, n_tiles - 1, 1);
-    half_step(n_tiles, second_block, no, yes, no, no, no, no, s_b, p_b, s_a, p_a, n_tiles, 0);
+    half_step(X, first_block, no, yes, yes, no, no, no, s_a, p_a, s_b, p_b, X - 1, 1);
+    half_step(X, second_block, no, yes, no, no, no, no, s_b, p_b, s_a, p_a, X, 0);
+    if constexpr (OWN_END) {
+        while (++X <= n_tiles) {
+            if ((gbase + X) % AH == 0) wg_barrier();
+            if (X < n_tiles) loads_only(X);
+        }
+    }
     gbase += n_tiles;
 
     // epilogue: normalise, store O (bf16) and LSE (natural log)

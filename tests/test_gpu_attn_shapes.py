@@ -91,6 +91,18 @@ def test_bf16_windows_of_the_whole_sequence(B, Hq, Hkv, L, d, a, n, p):
     run(B, Hq, Hkv, L, d, a, n, p, "bf16")
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,Hq,Hkv,L,a,n,p", [
+    (1, 2, 2, 128, 0, 1, 0.0),     # one head: the waves' streams end with one key each, half a tile apart
+    (2, 3, 3, 300, 4, 40, 0.1),    # the last tile's waves 2 and 3 lie past the sequence
+    (1, 1, 1, 97, 0, 500, 0.0),    # one position in the last wave; the window covers everything
+    (1, 4, 2, 191, 2, 33, 0.2),    # two heads: two position blocks per workgroup
+    (1, 2, 1, 224, 100, 8, 0.05),  # more initial tokens than window
+])
+def test_bf16_waves_whose_streams_end_apart(B, Hq, Hkv, L, d, a, n, p):
+    run(B, Hq, Hkv, L, d, a, n, p, "bf16")
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,L,d,a,n,p", [
     (1, 8, 2, 600, 128, 4, 96, 0.1),    # a band unit in four parts of one head
     (1, 8, 2, 600, 64, 4, 96, 0.1),
