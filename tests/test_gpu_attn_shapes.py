@@ -114,3 +114,29 @@ def test_bf16_waves_whose_streams_end_apart(B, Hq, Hkv, L, d, a, n, p):
 ])
 def test_bf16_band_units_in_parts(B, Hq, Hkv, L, d, a, n, p):
     run(B, Hq, Hkv, L, d, a, n, p, "bf16")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv", [(4, 1), (2, 2), (7, 1)])
+@pytest.mark.parametrize("shape", ["grow", "jump"])
+def test_bf16_forward_raises_its_maximum(Hq, Hkv, d, shape):
+    """Scores that grow along the keys, from -s to s, steadily (every few blocks outgrow the maximum before them) or at
+    once (the first exponential after the jump overflows); half the heads see them fall instead.  |V| <= 2: rounding P and O
+    to bf16 gives at most 2 * 2^-9 + 2^-8 < 0.008 in O; 2e-3 in LSE is the other tests' bound, |LSE| stays below 110."""
+    import paper_2412_12094_amd as sp
+
+    L, a, n, p, top = 700, 4, 300, 0.1, 100.0
+    scale = 1.0 / math.sqrt(d)
+    tok, Q, K, V, _ = make_case(1, Hq, Hkv, L, d, p, "bf16", 5)
+    ramp = np.linspace(-1, 1, L) if shape == "grow" else np.where(np.arange(L) < L // 2, -1.0, 1.0)
+    u = np.where(np.arange(d) % 2, 1.0, -1.0)
+    sign = np.where(np.arange(Hq) % 2, -1.0, 1.0)
+    Q = (0.05 * Q + sign[None, :, None, None] * u).astype(np.float32)
+    K = (0.05 * K + (top / math.sqrt(d) * ramp)[None, None, :, None] * u).astype(np.float32)
+    q, k, v = (dev(x, "bf16") for x in (Q, K, np.clip(V, -2, 2)))
+    _, idx, cnt, pre = gpu_index(sp, tok)
+    O, LSE = sp.sepattn_forward(q, k, v, idx, cnt, pre, a, n, scale)
+    torch.cuda.synchronize()
+    rO, rL = oracle.forward(host(q), host(k), host(v), oracle.mark_separators(tok, wl.SEPARATOR_IDS), a, n, scale)
+    assert np.abs(host(O) - rO).max() <= 8e-3
+    assert np.abs(host(LSE) - rL).max() <= 2e-3
