@@ -7,6 +7,8 @@
 // Three launches, no floating-point atomics (results are bit-reproducible):
 //  1. dq_kernel (this file): persistent workgroups over the query tiles, same dense key stream as the forward
 //     [initial | separators older than the window | band].  Also writes -D_i and LSE_i*log2(e).
+//     (Where few tiles have long streams, these go in two parts to two workgroups and dq_parts_kernel adds their
+//     fp32 sums: see split_tiles.)
 //  2. dkv_kernel (bwd_dkv_bf16.hip): the visible pairs split into band pairs (i-j < n) and far
 //     pairs (i-j >= n, j an initial token or a separator); far units work on the COMPACTED list of
 //     such keys and write fp32 partials, band units finish the keys that are not on that list.
@@ -56,14 +58,16 @@ __device__ inline float bf16_dot8(u32x4 a, u32x4 b) {
 // every fourth KV head full at L = 4096 170 -> 133.
 // ---------------------------------------------------------------------------------------------
 // DOCS: packed documents, as in the forward kernel (doc_start / doc_end [B, L]; p.a == 0).
-template <int D, int GP, bool DOCS, int NW>
+// PARTS: streams of windows of part_keys and more keys go in two parts (split_tiles), whose sums go to `parts`
+// [group][split tile][part][wave][32 D].
+template <int D, int GP, bool DOCS, int NW, bool PARTS>
 __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     sepattn_params p, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     const uint16_t *__restrict__ V, const uint16_t *__restrict__ O, const float *__restrict__ LSE,
     const uint16_t *__restrict__ dO, const int32_t *__restrict__ sep_idx,
     const int32_t *__restrict__ sep_prefix, const int32_t *__restrict__ doc_start,
     const int32_t *__restrict__ doc_end, uint16_t *__restrict__ dQ, float *__restrict__ Dws,
-    float *__restrict__ Lws, int wpg, HeadWin hw, WorkShare share) {
+    float *__restrict__ Lws, float *__restrict__ parts, int part_keys, int wpg, HeadWin hw, WorkShare share) {
     constexpr int TP = 32 * NW / GP;
     constexpr bool OWN_END = TP > 32;  // the waves' streams end at different tiles (as in the forward)
     constexpr int CH = D / 8;
@@ -130,18 +134,24 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     // is empty: its tiles are "loaded" too (row 0, never visible).
     struct Seg {
         Stream st;
-        int n_tiles, i0, de;
+        int t0, n_tiles, i0, de;  // tiles t0 .. n_tiles-1 of the stream
+        int slot;                 // where the sums of a part go, -1: not a part
     };
+    const SplitTiles split = split_tiles(n_pos_tiles, TP, p.n, PARTS ? part_keys : 0);  // of this group (its p.n)
     auto open_segment = [&](int round) {
         Seg g;
         const int rank = round * wpg + ((round & 1) ? wpg - 1 - tg.rank : tg.rank);
-        if (rank >= n_pos_tiles) {
+        g.t0 = 0;
+        g.slot = -1;
+        if (rank >= n_pos_tiles + split.n) {
             g.st = Stream{0, 0, 0, 0, 0};
             g.n_tiles = kIntMax;
             g.i0 = -1;
             g.de = kIntMax;
         } else {
-            g.i0 = (n_pos_tiles - 1 - rank) * TP;
+            int tile = rank, part = -1;
+            if constexpr (PARTS) split.find(rank, tile, part);
+            g.i0 = (n_pos_tiles - 1 - tile) * TP;
             if constexpr (DOCS) {
                 // the clamps keep inconsistent bounds (caller error) from faulting
                 const int ds = min(max(load_uniform(dstart, g.i0), 0), g.i0);
@@ -152,6 +162,11 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
                 g.st = make_stream(p, prefix, g.i0, TP);
             }
             g.n_tiles = (g.st.n_total + kBN - 1) / kBN;
+            if (PARTS && part >= 0) {
+                g.slot = (y * split.most + tile) * 2 + part;
+                if (part) g.t0 = g.n_tiles / 2;
+                else g.n_tiles /= 2;
+            }
         }
         return g;
     };
@@ -163,7 +178,7 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
         if (++c.t == c.cur.n_tiles) {
             c.cur = c.next;
             ++c.round;
-            c.t = 0;
+            c.t = PARTS ? c.cur.t0 : 0;
             c.next = open_segment(c.round + 1);
         }
     };
@@ -360,7 +375,8 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     if (wave < 2) {
         lc.cur = open_segment(0);
         lc.next = open_segment(1);
-        lc.round = lc.t = 0;
+        lc.round = 0;
+        lc.t = lc.cur.t0;
         if (wave == 1) advance(lc);
         issue_entries(lc.cur.st, lc.t, wave);
         Cursor l2 = lc;
@@ -471,7 +487,7 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
             const uint32_t soff = (uint32_t)min(iq, p.L - 1) * 4u;
             const float lse2 = *reinterpret_cast<const float *>(reinterpret_cast<const char *>(LSE + head_row0) + soff) * kLog2e_f;
             neg_lse2 = -lse2;
-            if (hh == 0 && iq < p.L) {
+            if (hh == 0 && iq < p.L && (!PARTS || cseg.t0 == 0)) {
                 // stored negated: the dK/dV kernel starts its dP accumulator from -D
                 *reinterpret_cast<float *>(reinterpret_cast<char *>(Dws + head_row0) + soff) = -Di;
                 // the dK/dV kernels work in the log2 domain too
@@ -488,8 +504,10 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
         // second block of the wave's last tile is left out when it is all padding or beyond the wave's last position; in
         // tiles beyond that (OWN_END) the wave only takes part in the loads.
         // (A tail after the loop: alternatives inside it would cost a copy of the accumulators per tile.)
-        const int n_tiles = cseg.n_tiles;
-        const int my_total = OWN_END ? min(cseg.st.n_total, cseg.st.n_dense + pw + 32 - cseg.st.bs) : cseg.st.n_total;
+        const int t0 = PARTS ? cseg.t0 : 0, n_tiles = cseg.n_tiles;
+        gbase -= t0;
+        int my_total = OWN_END ? min(cseg.st.n_total, cseg.st.n_dense + pw + 32 - cseg.st.bs) : cseg.st.n_total;
+        if constexpr (PARTS) my_total = max(min(my_total, n_tiles * kBN), t0 * kBN);
         const int n_whole = (my_total + 31) / kBN, my_tiles = OWN_END ? (my_total + kBN - 1) / kBN : n_tiles;
         auto begin_tile = [&](int X) __attribute__((always_inline)) {
             if ((gbase + X) % AH == 0) wg_barrier();
@@ -498,7 +516,7 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
         };
         f32x16 s0, p0, s1, p1;
         bf16x8 ds0[2], ds1[2];
-        for (int X = 0; X < n_whole; ++X) {
+        for (int X = t0; X < n_whole; ++X) {
             begin_tile(X);
             run(X, first, none, none, on, s0, p0, ds0, s0, p0, ds0);
             run(X, second, none, first, off, s1, p1, ds0, s0, p0, ds0);
@@ -528,7 +546,19 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
         // and leaves as 16-byte pieces of which four consecutive lanes cover 64 contiguous bytes of a
         // row.  8-byte chunk ch of row r sits at chunk position ch ^ (2 * ((r / 4) % 4)); the LDS
         // operations of a wave execute in order, so a block's reads precede the next block's writes.
-        {
+        if (PARTS && cseg.slot >= 0) {
+            // fp32 sums of a part, in the accumulators' own order: every store covers 1 KB
+            const int lane = lane_anew();
+            float *out = parts + ((long)cseg.slot * NW + wave) * (32 * D) + lane * 4;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    const float4 v = {acc[db][4 * i4] * p.scale, acc[db][4 * i4 + 1] * p.scale,
+                                      acc[db][4 * i4 + 2] * p.scale, acc[db][4 * i4 + 3] * p.scale};
+                    *reinterpret_cast<float4 *>(out + (db * 4 + i4) * 256) = v;
+                }
+        } else {
             const int lane = lane_anew(), qi = lane & 31, hh = lane >> 5;
             uint16_t *stg = &ostage[wave][0];
             const int wsw = ((qi >> 2) & 3) << 1;
@@ -557,6 +587,33 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+// dQ of the query tiles whose streams went in two parts (see split_tiles): the sum of the parts, rounded once.  One workgroup
+// per tile and column block; thread = lane of the dq kernel's wave.  Bounds: the bytes of the parts.
+template <int D, int GP, int NW>
+__global__ __launch_bounds__(64 * NW) void dq_parts_kernel(sepattn_params p, const float *__restrict__ parts, uint16_t *__restrict__ dQ,
+                                                           int part_keys, HeadWin hw) {
+    constexpr int TP = 32 * NW / GP, DB = D / 32;
+    const int G = p.Hq / p.Hkv, groups = G / GP, n_pos_tiles = (p.L + TP - 1) / TP;
+    const int tile = blockIdx.x / DB, db = blockIdx.x % DB, y = blockIdx.y;
+    const int hg = y % groups, kv = (y / groups) % p.Hkv, b = y / (groups * p.Hkv);
+    const SplitTiles split = split_tiles(n_pos_tiles, TP, p.n - group_delta(hw, kv * G + hg * GP, GP), part_keys);
+    if (tile >= split.n) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, qi = lane & 31, hh = lane >> 5;
+    const float *src = parts + (((long)y * split.most + tile) * 2 * NW + wave) * (32 * D) + db * 1024 + lane * 4;
+    const int row = (n_pos_tiles - 1 - tile) * TP + 32 * (wave / GP) + qi;
+    float4 u[4], v[4];
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+        u[i4] = *reinterpret_cast<const float4 *>(src + i4 * 256);
+        v[i4] = *reinterpret_cast<const float4 *>(src + (long)NW * (32 * D) + i4 * 256);
+    }
+    if (row >= p.L) return;
+    uint16_t *out = dQ + (((long)b * p.Hq + kv * G + hg * GP + wave % GP) * p.L + row) * D + db * 32 + 4 * hh;
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4)
+        *reinterpret_cast<uint2 *>(out + 8 * i4) = pack_bf16x4(u[i4].x + v[i4].x, u[i4].y + v[i4].y, u[i4].z + v[i4].z, u[i4].w + v[i4].w);
+}
+
 template <int D, bool DOCS>
 int launch_bwd(const sepattn_params &p, const uint16_t *Q, const uint16_t *K, const uint16_t *V,
                const uint16_t *O, const float *LSE, const uint16_t *dO, const int32_t *sep_idx,
@@ -576,26 +633,40 @@ int launch_bwd(const sepattn_params &p, const uint16_t *Q, const uint16_t *K, co
     const long n_groups = (long)p.B * (p.Hq / shape.gp);
     // persistent workgroups, spread evenly over the groups; never more than a group has tiles
     const int per_cu = shape.nw > 4 ? 1 : 2;
-    int wpg = (int)(per_cu * (long)compute_units() / n_groups);
-    wpg = wpg < 1 ? 1 : (wpg > n_pos_tiles ? n_pos_tiles : wpg);
+    const long slots = per_cu * (long)compute_units();
+    // the parts' sums lie where the dK/dV kernel puts its partials later
+    const int part_keys = DOCS || shape.nw != 4 ? 0 : split_keys(p, hw, shape.gp, TP, slots, 2 * w.far_bytes / (2 * TP * shape.gp * D * sizeof(float)));
+    const int n_ranks = n_pos_tiles + split_tiles(n_pos_tiles, TP, p.n, part_keys).n;
+    int wpg = (int)(slots / n_groups);
+    wpg = wpg < 1 ? 1 : (wpg > n_ranks ? n_ranks : wpg);
     if (n_groups * wpg > 0x7FFFFFFFL) return SEPATTN_ERR_SHAPE;
     WorkShare share = {};
     long n_wg = n_groups * wpg;
     if (any_delta(hw)) {
-        share = share_out(p, hw, shape.gp, per_cu * compute_units() / p.B, n_pos_tiles, [&](int n, bool) { return query_cost(p, TP, n); });
+        share = share_out(p, hw, shape.gp, slots / p.B, n_ranks, [&](int n, bool) { return query_cost(p, TP, n); });
         n_wg = (long)p.B * share.first[share.n];
     }
     dim3 grid((unsigned)n_wg), block(64 * shape.nw);
     {
     ProfScope prof(SEPATTN_K_BWD_DQ, st);
-    auto go = [&](auto NW_, auto GP_) {
-        hipLaunchKernelGGL((dq_kernel<D, decltype(GP_)::value, DOCS, decltype(NW_)::value>), grid, block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, Lws, wpg, hw, share);
+    auto go = [&](auto NW_, auto GP_, auto PARTS_) {
+        constexpr int GP = decltype(GP_)::value, NW = decltype(NW_)::value;
+        constexpr bool PARTS = decltype(PARTS_)::value != 0;
+        hipLaunchKernelGGL((dq_kernel<D, GP, DOCS, NW, PARTS>), grid, block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, Lws, farK, part_keys, wpg, hw, share);
+        if constexpr (PARTS)
+            hipLaunchKernelGGL((dq_parts_kernel<D, GP, NW>), dim3((n_ranks - n_pos_tiles) * (D / 32), (unsigned)n_groups), block, 0, st, p, farK, dQ, part_keys, hw);
     };
-    if (shape.gp == 7) go(IntC<7>{}, IntC<7>{});
-    else if (D == 128 && shape.nw == 8) go(IntC<D == 128 ? 8 : 4>{}, IntC<4>{});
-    else if (shape.gp == 4) go(IntC<4>{}, IntC<4>{});
-    else if (shape.gp == 2) go(IntC<4>{}, IntC<2>{});
-    else go(IntC<4>{}, IntC<1>{});
+    auto go4 = [&](auto GP_) {
+        if constexpr (!DOCS) {
+            if (part_keys) return go(IntC<4>{}, GP_, IntC<1>{});
+        }
+        go(IntC<4>{}, GP_, IntC<0>{});
+    };
+    if (shape.gp == 7) go(IntC<7>{}, IntC<7>{}, IntC<0>{});
+    else if (D == 128 && shape.nw == 8) go(IntC<D == 128 ? 8 : 4>{}, IntC<4>{}, IntC<0>{});
+    else if (shape.gp == 4) go4(IntC<4>{});
+    else if (shape.gp == 2) go4(IntC<2>{});
+    else go4(IntC<1>{});
     }
     if (hipGetLastError() != hipSuccess) return SEPATTN_ERR_HIP;
     return launch_dkv_bf16(p, hw, Q, K, V, Lws, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, st);

@@ -105,4 +105,52 @@ inline double query_cost(const sepattn_params &p, int TP, int n) {
     return w * (L - w / 2) + L * (TP + 128) + kSepShare * out * out / 2;
 }
 
+// Query tiles whose key streams go in two halves to two workgroups.  A tile's stream is a serial chain of one workgroup,
+// and where windows are long and tiles few it is what the kernel waits for.  Of the tiles, longest first, the first `n`
+// are split: those whose first row has at least `keys` keys in its window (0: none).
+struct SplitTiles {
+    int n, most, tiles;  // split tiles of the group; of any group; all tiles
+    // rank in the order of falling work -> tile and part (-1: whole).  Lengths fall linearly from the longest to its half over
+    // the split tiles and from there to nothing, so four halves (two tiles) go with one whole tile.
+    __host__ __device__ void find(int rank, int &tile, int &part) const {
+        const int fives = n / 2 < tiles - n ? n / 2 : tiles - n;
+        int half = -1;
+        tile = rank - n;
+        if (rank < 5 * fives) {
+            if (rank % 5) half = rank / 5 * 4 + rank % 5 - 1;
+            else tile = n + rank / 5;
+        } else if (rank < 2 * n + fives) {
+            half = rank - fives;
+        }
+        part = half < 0 ? -1 : half & 1;
+        if (half >= 0) tile = half >> 1;
+    }
+};
+__host__ __device__ inline SplitTiles split_tiles(int tiles, int TP, int window, int keys) {
+    SplitTiles s;
+    s.tiles = tiles;
+    s.most = keys && tiles > keys / TP ? tiles - keys / TP : 0;
+    s.n = keys && window >= keys ? s.most : 0;
+    return s;
+}
+
+// From which window length on tiles are split, 0: none are.  Half of the longest (p.n is that of the call), if that shortens the
+// longest chain by kWorthSplitting keys, given the workgroups' mean work, and there is `room` for the parts of so many
+// tiles.  A split costs the second part's start, fp32 sums and a launch that adds them (6 us for 128 tiles at
+// d = 128).  Measured, forward and backward in us, whole / split streams.  Above the line: every fourth KV head full, the others 128 (32/8
+// heads, d = 128, L = 4096) 384 / 377, of which dQ 114.5 / 97.6 + 5.6, the same with 8/8 heads 249 / 217; 8/1 heads, L = 3000, n = L
+// 198 / 182; 8/2 heads, L = 4096, n = L 277 / 261.  Below it: 32/8 heads, L = n = 1024 106 / 108, 2048 231 / 234; 16/4 heads, 2 x L = 1500,
+// n = 1100 157 / 166; 12 heads, d = 64, L = n = 2048 125 / 117, but every fourth of them full, 4 x L = 2048 154 / 158.
+constexpr int kWorthSplitting = 1280;
+inline int split_keys(const sepattn_params &p, const HeadWin &hw, int gp, int TP, long slots, size_t room) {
+    const int longest = p.n < p.L ? p.n : p.L, start = TP + 128;
+    if (longest < 2 * kWorthSplitting) return 0;
+    double sum = 0.;
+    for (int h = 0; h < p.Hq; h += gp) sum += query_cost(p, TP, p.n - group_delta(hw, h, gp)) / TP * p.B;
+    const int keys = (longest / 2 + TP - 1) / TP * TP;
+    if (longest + start - sum / slots < kWorthSplitting) return 0;
+    const SplitTiles s = split_tiles((p.L + TP - 1) / TP, TP, p.n, keys);
+    return (size_t)p.B * (p.Hq / gp) * s.most <= room ? keys : 0;
+}
+
 }  // namespace sepattn

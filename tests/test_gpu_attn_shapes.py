@@ -117,6 +117,18 @@ def test_bf16_band_units_in_parts(B, Hq, Hkv, L, d, a, n, p):
 
 
 @pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,Hq,Hkv,L,a,n,p", [
+    (1, 4, 1, 2560, 4, 2560, 0.1),                         # the shortest sequence with split streams
+    (1, 2, 1, 2627, 0, 1 << 20, 0.0),                      # two heads, ragged; windows longer than any sequence
+    (2, 1, 1, 2689, 4, 2570, 0.1),                         # one head: waves that end before the second half
+    (1, 4, 2, 4000, 2, 2600, 0.3),                         # windows that end: many split tiles equally long
+    (1, 8, 2, 2600, 4, [2600] * 4 + [40, 7, 1, 64], 0.1),  # one group split, the other not
+])
+def test_bf16_streams_in_two_parts(B, Hq, Hkv, L, d, a, n, p):
+    run(B, Hq, Hkv, L, d, a, n, p, "bf16")
+
+
+@pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("Hq,Hkv", [(4, 1), (2, 2), (7, 1)])
 @pytest.mark.parametrize("shape", ["grow", "jump"])
 def test_bf16_forward_raises_its_maximum(Hq, Hkv, d, shape):
