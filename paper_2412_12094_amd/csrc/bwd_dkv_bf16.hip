@@ -26,7 +26,7 @@
 // both are 32x32 accumulator layouts), once per block of 32 queries, fenced by the block's
 // workgroup barrier (P is exchanged in bf16, the form it has in the second contraction anyway).  Query
 // tiles (64 or 32 rows of Q and dO, plus LSE*log2e and -D) stream through a ring of four LDS buffers filled
-// by direct global->LDS loads issued as soon as a buffer is free; with the ring the block barriers
+// by direct global->LDS loads, issued in the step in which a buffer becomes free; with the ring the block barriers
 // are the only barriers.  The tiles are stored unpadded with XOR-permuted 16-byte
 // chunks so that both the row-major reads (first contraction) and the transposed reads (second
 // contraction) are free of bank conflicts.  The G query heads of a KV head are just G times as many
@@ -74,13 +74,21 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
     // ring of four, the single workgroup tiles of 64 rows (two blocks).
     constexpr int BQ = KW == 2 ? 32 : 64;
     constexpr int BPT = BQ / 32;             // blocks of 32 query rows per tile
-    constexpr int LOADS = BQ / (RPL * NW);   // wave-wide loads per wave per tensor per tile
-    constexpr int RVL = (2 * BQ / 16) / NW;  // loads of sixteen row values (LSE*log2e or -D) per wave per tile
+    // The loads of a tile (40 wave-wide ones per compute unit, 16 cycles each, and the waves that issue them stand still
+    // meanwhile) are issued by the waves of one role, and where these have time to spare: with eight waves by the P-waves
+    // in front of their softmax, while the dS-waves multiply; with four, where the P-waves come last to the barrier, by
+    // the dS-waves in front of it (see refill).  By all waves right behind the barrier, where every wave has the longest way
+    // to go, they cost 325 - 590 of 2400 cycles per step.  dK/dV, us, before / now: 32/8 heads, d = 128, L = 8192,
+    // n = 256 (eight waves) 227 / 213, with the dS-waves loading 222; four waves: every fourth KV head full at L = 4096 167 / 158
+    // (dS-waves behind the barrier 163, P-waves 169); 28/4 heads, 3 x L = 3077 152 / 152 (154, 160); packed 163 / 162.
+    constexpr int LOADER = KW == 4 ? 0 : 1;
+    constexpr int LOADS = BQ / (RPL * KW);   // wave-wide loads per loading wave per tensor per tile
+    constexpr int RVL = (2 * BQ / 16) / KW;  // loads of sixteen row values (LSE*log2e or -D) per loading wave per tile
     constexpr int KSTEPS = D / 16;
     constexpr int DB = D / 32;
     constexpr int TILE = BQ * D;
     constexpr int NBUF = 4;
-    static_assert(LOADS >= 1 && LOADS * RPL * NW == BQ && RVL >= 1 && RVL * 16 * NW == 2 * BQ, "tile must divide among the waves");
+    static_assert(LOADS >= 1 && LOADS * RPL * KW == BQ && RVL >= 1 && RVL * 16 * KW == 2 * BQ, "tile must divide among the waves");
 
     __shared__ __attribute__((aligned(1024))) uint16_t Qs[NBUF][TILE];
     __shared__ __attribute__((aligned(1024))) uint16_t dOs[NBUF][TILE];
@@ -129,6 +137,11 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
     const FarList fl = far_list(p, prefix, every_key);
     const int a_row = pi_row(kj);
     const int my_pc = lane % CH, my_sub = lane / CH;
+    // byte offset within a tile of Q or dO of what this lane fetches of the wave's first rows; those RPL rows on differ by
+    // them and by a chunk bit each (kSwzBoth; the wave's rows start at a multiple of 16)
+    constexpr uint32_t ROWB = D * 2;
+    static_assert(LOADS * RPL == 16, "a loading wave's rows");
+    const uint32_t my_off = (uint32_t)(16 * kbw + my_sub) * ROWB + swz_chunk<kSwzBoth, D>(my_pc, my_sub) * 16;
     // Per-lane byte offsets of the operand fragments inside a tile, computed once.  The first
     // contraction reads rows of T1 (Q for the P-wave, dO for the dS-wave), the second reads the other
     // tensor (T2) transposed.  Row-major fragments: the XOR permutation acts on the 16-byte chunk
@@ -359,56 +372,56 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         // (head, query tile) of the next one.
         int iss_tt = 0, iss_g = item0 / n_qt, iss_qt = item0 % n_qt;
         if (PARTS && !FAR) iss_g = unit % split * Gs;  // the part's first head
+        size_t iss_head = (((long)b * p.Hq + kv * G + iss_g) * (long)p.L) * ROWB;  // byte offset of the head's rows in Q and dO
         auto issue_tile = [&]() {
-            const int buf = iss_tt % NBUF;
-            const long hrow0 = ((long)b * p.Hq + kv * G + iss_g) * (long)p.L;
-            const int qbase = q_lo + iss_qt * BQ;
-            static_for<LOADS>([&](auto U) {
-                constexpr int u = U;
-                const int r = (LOADS * wave + u) * RPL + my_sub;
-                // (uniform base of the head) + 32-bit byte offset; the loads go through inline assembly
-                // so that the compiler does not make every LDS read wait for all of them
-                const uint32_t off = (uint32_t)min(qbase + r, p.L - 1) * (uint32_t)(D * 2) + swz_chunk<kSwzBoth, D>(my_pc, r) * 16;
-                const int wave_off = (LOADS * wave + u) * RPL * D;
-                dma_to_lds_16(Q + hrow0 * D, off, lds_addr(&Qs[buf][wave_off]));
-                dma_to_lds_16(dO + hrow0 * D, off, lds_addr(&dOs[buf][wave_off]));
-            });
-            // the BQ + BQ row values (LSE*log2e, -D) in groups of sixteen, dealt to the waves so that every
-            // wave issues the same number of loads per tile: group g holds rows 16 (g % (BQ/16)) .. +15
-            // of LSE*log2e (g < BQ/16) or of -D
+            if (role == LOADER) {
+                const int buf = iss_tt % NBUF;
+                const int qbase = q_lo + iss_qt * BQ;
+                static_for<LOADS>([&](auto U) {
+                    constexpr int u = U;
+                    // (uniform base of the head) + 32-bit byte offset; the loads go through inline assembly
+                    // so that the compiler does not make every LDS read wait for all of them
+                    uint32_t off = my_off;
+                    asm volatile("" : "+v"(off));  // one register for all rows, not one each
+                    off = (uint32_t)qbase * ROWB + ((off ^ (u * (D == 128 ? 16u : 32u))) + u * RPL * ROWB);
+                    off = min(off, ((uint32_t)(p.L - 1) * ROWB) | (off & (ROWB - 1)));
+                    const int wave_off = (LOADS * kbw + u) * RPL * D;
+                    dma_to_lds_16(reinterpret_cast<const char *>(Q) + iss_head, off, lds_addr(&Qs[buf][wave_off]));
+                    dma_to_lds_16(reinterpret_cast<const char *>(dO) + iss_head, off, lds_addr(&dOs[buf][wave_off]));
+                });
+                // the BQ + BQ row values (LSE*log2e, -D) in groups of sixteen: group g holds rows
+                // 16 (g % (BQ/16)) .. +15 of LSE*log2e (g < BQ/16) or of -D
 #pragma unroll
-            for (int v = 0; v < RVL; ++v) {
-                constexpr int GPT = BQ / 16;  // groups per tensor
-                const int g = wave * RVL + v, part = g % GPT;
-                const float *src = (g < GPT ? LSE2 : Dws) + hrow0;
-                float *dst = g < GPT ? &lse_s[buf][16 * part] : &d_s[buf][16 * part];
-                if (lane < 16) dma_to_lds_4(src, (uint32_t)min(qbase + 16 * part + lane, p.L - 1) * 4u, lds_addr(dst));
+                for (int v = 0; v < RVL; ++v) {
+                    constexpr int GPT = BQ / 16;  // groups per tensor
+                    const int g = kbw * RVL + v, part = g % GPT;
+                    const char *src = reinterpret_cast<const char *>(g < GPT ? LSE2 : Dws) + iss_head / (ROWB / 4);
+                    float *dst = g < GPT ? &lse_s[buf][16 * part] : &d_s[buf][16 * part];
+                    if (lane < 16) dma_to_lds_4(src, (uint32_t)min(qbase + 16 * part + lane, p.L - 1) * 4u, lds_addr(dst));
+                }
             }
             ++iss_tt;
             if (++iss_qt == n_qt) {
                 iss_qt = 0;
-                ++iss_g;
+                iss_head += (size_t)p.L * ROWB;
             }
         };
         // wait until at most the loads of the n_out newest tiles are still in flight (loads complete in
         // the order they were issued; every wave issues 2*LOADS + 1 loads per tile)
         auto wait_tiles = [&](int n_out) __attribute__((always_inline)) {
             constexpr int LW = 2 * LOADS + RVL;
-            static_assert(LW == 3 || LW == 5 || LW == 6, "wait counts below are written for 3, 5 or 6 loads per wave and tile");
-            if (n_out <= 0) {
+            static_assert(LW == 6 || LW == 10, "wait counts below are written for 6 or 10 loads per wave and tile");
+            if (n_out <= 0 || role != LOADER) {
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             } else if (n_out == 1) {
-                if constexpr (LW == 3) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
-                else if constexpr (LW == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
-                else asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+                if constexpr (LW == 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
             } else if (n_out == 2) {
-                if constexpr (LW == 3) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-                else if constexpr (LW == 5) asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
-                else asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+                if constexpr (LW == 6) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(20)" ::: "memory");
             } else {
-                if constexpr (LW == 3) asm volatile("s_waitcnt vmcnt(9)" ::: "memory");
-                else if constexpr (LW == 5) asm volatile("s_waitcnt vmcnt(15)" ::: "memory");
-                else asm volatile("s_waitcnt vmcnt(18)" ::: "memory");
+                if constexpr (LW == 6) asm volatile("s_waitcnt vmcnt(18)" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(30)" ::: "memory");
             }
         };
 
@@ -466,6 +479,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         };
         int st_n = -1;                            // number of the step handed out last
         int lo_cur = 0, hi_next = 0;              // lowest tile of that step; highest tile of the step after it
+        int lo_free = 0;                          // tiles below this one are read by no wave any more
         int hi_landed = 0;                        // highest tile this wave has waited for
         auto next_block = [&]() __attribute__((always_inline)) {
             ++st_n;
@@ -632,7 +646,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         // Barrier after the first contraction (and publication of P) of the step handed out last.  The
         // interval after it reads the blocks of that step (second contraction) and of the next one
         // (first contraction): every wave first waits for its share of the tiles the next step needs,
-        // and after the barrier the buffers of the tiles below the lowest one still in use are refilled.
+        // and in that interval the buffers of the tiles below the lowest one still in use are refilled.
         auto block_barrier = [&]() __attribute__((always_inline)) {
             if (hi_next != hi_landed) {
                 wait_tiles(iss_tt - 1 - hi_next);
@@ -640,7 +654,11 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
-            while (iss_tt < n_tiles && iss_tt - NBUF < lo_cur) issue_tile();
+            lo_free = lo_cur;
+        };
+        auto refill = [&]() __attribute__((always_inline)) {
+            while (iss_tt < n_tiles && iss_tt - NBUF < lo_free) issue_tile();
+            __builtin_amdgcn_sched_barrier(0);
         };
 
         // start-up: two tiles, the resident rows (requested before them) out of the other half of the ring, and when every
@@ -687,6 +705,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
                 fetch_p_and_form_ds(cur, xc, xb);
                 __builtin_amdgcn_sched_barrier(0);
                 gemm1_then_gemm2(nxt, a0, a1, xn, cur, xb);
+                refill();
                 block_barrier();
                 cur = nxt;
             };
@@ -694,6 +713,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
                 for (int gb = 0; gb + 1 < n_blocks; ++gb) {
                     const Blk nxt = next_block();
                     gemm2_then_gemm1(cur, xb, nxt, x);
+                    refill();
                     softmax_and_publish(nxt, x, xb);
                     block_barrier();
                     cur = nxt;
