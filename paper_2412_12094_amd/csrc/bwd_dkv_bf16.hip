@@ -628,11 +628,15 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         };
         // dS-wave: dS = P (dP - D); x holds dP - D (the accumulator started from -D), the result is
         // rounded to bf16 in the form the second contraction needs
-        auto fetch_p_and_form_ds = [&](const Blk &k, const f32x16 &x, bf16x8 (&xb)[2]) __attribute__((always_inline)) {
+        auto fetch_p = [&](const Blk &k, u32x4 (&pw2)[2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) pw2[h] = *reinterpret_cast<const u32x4 *>(&Pex[kbw][k.ps][h][lane * 8]);
+        };
+        auto form_ds = [&](const u32x4 (&pw2)[2], const f32x16 &x, bf16x8 (&xb)[2]) __attribute__((always_inline)) {
             f32x16 ds;
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
-                const u32x4 pw = *reinterpret_cast<const u32x4 *>(&Pex[kbw][k.ps][h][lane * 8]);
+                const u32x4 pw = pw2[h];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const float p_lo = __uint_as_float(pw[e] << 16), p_hi = __uint_as_float(pw[e] & 0xFFFF0000u);
@@ -700,9 +704,19 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
             auto ds_step = [&](f32x16 &xc, f32x16 &xn) __attribute__((always_inline)) {
                 const Blk nxt = next_block();
                 bf16x8 a0[KSTEPS / 2], a1[KSTEPS / 2];
+                // LDS reads return in the order they were requested, and behind the barrier all waves request theirs: P first,
+                // because the dS arithmetic needs nothing else (last: dK/dV 216 us instead of 212 at 32/8 heads, d = 128,
+                // L = 8192, 28/4 heads, 3 x L = 3077 153 instead of 150; at d = 64, with half the reads, level or slower)
+                u32x4 pw[2];
+                if constexpr (D == 128) {
+                    fetch_p(cur, pw);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
                 read_rows_halves(nxt, a0, a1);  // in flight during the dS arithmetic
                 read_rowvals(nxt, xn);
-                fetch_p_and_form_ds(cur, xc, xb);
+                if constexpr (D == 128) __builtin_amdgcn_sched_barrier(0);
+                else fetch_p(cur, pw);
+                form_ds(pw, xc, xb);
                 __builtin_amdgcn_sched_barrier(0);
                 gemm1_then_gemm2(nxt, a0, a1, xn, cur, xb);
                 refill();
@@ -733,7 +747,11 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
             {
                 bf16x8 tfr[2][DB];
                 read_transposed(cur, tfr);
-                if constexpr (R == 1) fetch_p_and_form_ds(cur, x, xb);
+                if constexpr (R == 1) {
+                    u32x4 pw[2];
+                    fetch_p(cur, pw);
+                    form_ds(pw, x, xb);
+                }
                 gemm2(tfr, xb);
             }
         };
