@@ -55,7 +55,9 @@ __device__ inline float bf16_dot8(u32x4 a, u32x4 b) {
 // Measured (us; before: dS between two runs with nothing beside it, eight waves at d = 128, one head per tile for
 // seven, loads and their index work on four waves): 32/8 heads, d = 128, L = 8192, n = 256 171 -> 158, packed from eight
 // documents 137 -> 124; 28/4 heads, 3 x L=3077 173 -> 127; 8/2 heads, L = 600 19 -> 14; 12 heads, d = 64, 8 x L=2048 54.6 -> 51;
-// every fourth KV head full at L = 4096 170 -> 133.
+// every fourth KV head full at L = 4096 170 -> 133.  Since then (K and V tiles interleaved with shared operand addresses, nothing in
+// scratch memory, waves that end with their own stream, split streams), in the same order: 158 -> 131, 124 -> 102, 127 -> 104,
+// 14 -> 12, 51 -> 44, 133 -> 96 + 6.
 // ---------------------------------------------------------------------------------------------
 // DOCS: packed documents, as in the forward kernel (doc_start / doc_end [B, L]; p.a == 0).
 // PARTS: streams of windows of part_keys and more keys go in two parts (split_tiles), whose sums go to `parts`

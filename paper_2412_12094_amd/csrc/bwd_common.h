@@ -11,8 +11,9 @@ namespace sepattn {
 // of two shapes:
 //   KW = 4: 8 waves, one workgroup per compute unit.  Fewest tile loads per matrix instruction; the
 //           better shape when a workgroup's pieces are long: d = 128, sequences from 8K on with
-//           grouped heads (by 3-5 % there; at L = 4096, or with one head per KV head at 8K, the other
-//           shape is 1-13 % ahead, at 16K with one head per KV head the two are level).
+//           grouped heads (a step with 32/8 heads, us, KW = 4 / 2: L = 8192, n = 256 442 / 443, n = 1024 779 / 805; 16K 1241 / 1268,
+//           32K 3998 / 4282; at L = 4096, or with one head per KV head at 8K, the other shape is 1-13 % ahead, at 16K
+//           with one head per KV head the two are level).
 //   KW = 2: 4 waves, two workgroups per compute unit (three at d = 64, where the registers and the ring
 //           of query tiles allow it) that run independently: one's piece start-up and partial stores
 //           overlap the others' matrix work, the split of a (batch, KV head) is finer (it fills the

@@ -18,10 +18,13 @@
 // 16-byte chunks (see mfma_common.h).  V^T operands are read with ds_read_b64_tr_b16.  A wave drops
 // the mask test on blocks every one of its rows sees in full.  The running maximum is only raised
 // when it grows by more than 2^8 (all terms carry the same stale maximum, so the result is
-// unchanged), which removes almost every rescale of the output accumulators.
+// unchanged), which removes almost every rescale of the output accumulators; whether it has is seen from
+// the exponentials, so that a block's maximum is not formed at all unless they are too large (raise_max).
 // Measured (forward call with its index step, us; before: eight waves, vector work outside the shadow of the matrix
 // instructions, loads and index work on four of the waves): 32/8 heads, d = 128: L=8192 n=256 109 -> 98, L=64K
-// n=1024 3990 -> 3650, 4 x L=1531 n=256 84 -> 75; 28/4 heads, 3 x L=3077 119 -> 78; 12 heads, d = 64, 8 x L=2048 51 -> 40.
+// n=1024 3990 -> 3650, 4 x L=1531 n=256 84 -> 75; 28/4 heads, 3 x L=3077 119 -> 78; 12 heads, d = 64, 8 x L=2048 51 -> 40.  The kernel alone (scalar
+// loads of a segment's bounds, no maximum per block, operands of a tile's second half requested in its first): 113 -> 94 (L=8192),
+// 3625 -> 3385 (64K), 88 -> 76 (3 x 3077), 38 -> 34 (d = 64), 86 -> 76 (8192 packed from eight documents).
 #include "common.h"
 #include "mfma_common.h"
 #include "key_stream.h"
@@ -257,7 +260,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     //   half 2:  S(2X+1) = K_X[32..63] Q^T      O^T += V_{X-1}[32..63]^T P(2X-1)^T    softmax of block 2X
     // A half begins with what branches (mask, rescaling) and then is ONE straight run of matrix
     // instructions, after each of which a fixed share of the rest (exponentials, row sum and rounding to
-    // bf16 of one block, maximum of the next, row loads, operand requests LA matrix instructions ahead) is
+    // bf16 of one block, row loads, operand requests LA matrix instructions ahead) is
     // issued and executes while the matrix pipe is busy.  Branches inside the run, or results that are only
     // used beyond it, let the compiler move the vector work out of the shadow of the matrix
     // instructions: hence the scheduling fences and the empty asm statements that use the results in place.
