@@ -416,7 +416,8 @@ bool decode_wide_applicable(const sepkv_params &p) {
 //     sixteen where a slice would be longer than ten blocks (1 sequence of 3332 entries 8.9 / 10.0, eight 9.9 / 11.7).
 //   Slices pay when the blocks that a workgroup is spared take longer than adding the records (about 2 us).  A block
 //     costs a lone workgroup 0.2 us, with ROPE 0.3 us, half of that at d = 64: 13 blocks in one slice 5.8 / 8.4, in four
-//     5.8 / 6.9; 16 blocks 6.0 / 8.6 and 6.0 / 7.0.
+//     5.8 / 6.9; 16 blocks 6.0 / 8.6 and 6.0 / 7.0; a cache of 16 that holds 12 to 16 (28/4 heads, 2 sequences) 6.9 in one,
+//     7.9 in four.
 //   Four waves per slice at d = 128 (two slices for 16 sequences of 2300 entries 24.6 / 25.6, of eight waves 24.8 / 25.6)
 //     and where each has one block; eight at d = 64 (8 sequences of 2300 entries 8.2 / 8.8 against 8.7 / 9.5).
 //   One slice: eight waves (more bytes in flight); four for caches of up to eight blocks (1 sequence of 128 entries
@@ -432,7 +433,7 @@ DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope) {
     if (ns > fit) ns = (int)fit;
     if (ns > 1) {
         const int per = (nb + ns - 1) / ns;
-        if (nb - per >= (rope ? 9 : 11) * d64) return {ns, d64 == 1 || per <= 4 ? 4 : 8};
+        if (nb - per >= (rope ? 9 * d64 : d64 == 1 ? 13 : 22)) return {ns, d64 == 1 || per <= 4 ? 4 : 8};
     }
     return {1, nb <= 8 || pairs > (long)compute_units() * d64 ? 4 : 8};
 }
