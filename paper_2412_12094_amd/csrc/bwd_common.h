@@ -4,6 +4,7 @@
 #pragma once
 
 #include "common.h"
+#include "work_share.h"
 
 namespace sepattn {
 
@@ -59,13 +60,17 @@ inline int dkv_workgroups_per_head(const sepattn_params &p, int kw) {
 // Among how many workgroups a band unit (32 KW keys and their windows, all query heads of the KV head) is split, by query
 // heads.  A unit is a chain of G ((n + 30) / 32 + 1) steps of 0.7 us on one workgroup; where there are fewer units than
 // workgroups it sets the time of the kernel.  Split, every key's sums pass through fp32 partials and the combine
-// kernel.  The largest number that divides the heads, gives no workgroup two parts, leaves a part four steps and
-// spares eight: 8/2 heads, d = 128, L = 600, n = 96 (20 steps) dK/dV and combine 22.3 + 4.5 -> 13.6 + 5.3 us.
+// kernel.  Not where the far work keeps the workgroups busy as long (a unit shorter than three times their mean work: 8/1 heads,
+// 3 x L = 2648, d = 64, n = 18, dK/dV 28.0 us, with four parts 30.2); else the largest number that divides the heads, gives no
+// workgroup two parts, leaves a part four steps and spares eight: 8/2 heads, d = 128, L = 600, n = 96 (20 steps) dK/dV and combine 22.3 + 4.5 -> 13.6 + 5.3 us.
 // (any_n: for the workspace, whose size does not depend on the window: the largest split of any window.)
 inline int band_split(const sepattn_params &p, int wpg, int kw, bool any_n = false) {
     const int G = p.Hq / p.Hkv, steps = any_n ? 1 << 20 : ((p.n < p.L ? p.n : p.L) + 30) / 32 + 1;
     const long units = ((long)p.L + 32 * kw - 1) / (32 * kw);
+    // far work in steps of 32 query rows, from the share of separators that work_share.h assumes
+    const double out = any_n || p.n >= p.L ? 0. : p.L - p.n, far = (p.a + kSepShare * out / 2) * out / (1024. * kw) * G;
     int split = 1;
+    if (3. * (far + (double)units * G * steps) > (double)wpg * G * steps) return 1;
     for (int s = 2; s <= G; ++s)
         if (G % s == 0 && units * s <= wpg && (long)G / s * steps >= 4 && (long)(G - G / s) * steps >= 8) split = s;
     return split;

@@ -110,7 +110,7 @@ def test_bf16_waves_whose_streams_end_apart(B, Hq, Hkv, L, d, a, n, p):
     (2, 12, 2, 333, 128, 0, 64, 0.0),   # three parts of two heads; nothing on the list
     (4, 32, 8, 256, 128, 4, 128, 0.1),  # as many parts as workgroups
     (4, 32, 8, 257, 128, 4, 128, 0.1),  # one key more: two parts
-    (1, 8, 1, 8200, 128, 4, 40, 0.05),  # eight-wave workgroups
+    (1, 8, 1, 8200, 128, 4, 2000, 0.05),  # eight-wave workgroups
 ])
 def test_bf16_band_units_in_parts(B, Hq, Hkv, L, d, a, n, p):
     run(B, Hq, Hkv, L, d, a, n, p, "bf16")
