@@ -420,8 +420,8 @@ bool decode_wide_applicable(const sepkv_params &p) {
 //     7.9 in four.
 //   Four waves per slice at d = 128 (two slices for 16 sequences of 2300 entries 24.6 / 25.6, of eight waves 24.8 / 25.6)
 //     and where each has one block; eight at d = 64 (8 sequences of 2300 entries 8.2 / 8.8 against 8.7 / 9.5).
-//   One slice: eight waves (more bytes in flight); four for caches of up to eight blocks (1 sequence of 128 entries
-//     3.6 / 4.8 against 4.2 / 5.1), and where more workgroups wait than the compute units hold at once: half the LDS, so
+//   One slice: eight waves (more bytes in flight); four for caches of up to four blocks (1 sequence of 128 entries
+//     3.6 / 4.8 against 4.2 / 5.1; of eight blocks, which four waves take in two rounds, 0.14 us slower), and where more workgroups wait than the compute units hold at once: half the LDS, so
 //     that two (d = 64: four) share a compute unit and one's start and merge overlap another's stream (64 sequences x
 //     8 heads of 100 entries 8.9 -> 5.4, of 1000 entries 40.7 -> 39.2).
 DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope) {
@@ -435,7 +435,7 @@ DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope) {
         const int per = (nb + ns - 1) / ns;
         if (nb - per >= (rope ? 9 * d64 : d64 == 1 ? 13 : 22)) return {ns, d64 == 1 || per <= 4 ? 4 : 8};
     }
-    return {1, nb <= 8 || pairs > (long)compute_units() * d64 ? 4 : 8};
+    return {1, nb <= 4 || pairs > (long)compute_units() * d64 ? 4 : 8};
 }
 
 int launch_decode_wide(const sepkv_params &p, const DecodeWideShape &shape, const uint16_t *q, const uint16_t *Kc, const uint16_t *Vc,
