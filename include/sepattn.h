@@ -260,7 +260,11 @@ typedef struct {
  *   sizes    DEVICE int32 [S, 6]; a sequence with no valid entry yields out = 0, lse = -inf
  *   out      DEVICE dtype [S, Hq, d]  out
  *   lse      DEVICE fp32  [S, Hq]     out, may be NULL
- *   ws       DEVICE, >= sepattn_decode_workspace_bytes(p) bytes, 256-byte aligned
+ *   ws       DEVICE, >= sepattn_decode_workspace_bytes(p) bytes, 256-byte aligned.  It may hold
+ *            anything before the call and need not be cleared; the call leaves words in it by
+ *            which a later call on it saves work, and no later result depends on them.  Calls that
+ *            overlap in time need a workspace each: sharing one makes the results of the
+ *            overlapping calls wrong, and of none after them
  */
 size_t sepattn_decode_workspace_bytes(const sepkv_params *p);
 int sepattn_decode(const sepkv_params *p, const void *q, const void *Kc, const void *Vc,
@@ -291,13 +295,13 @@ int sepattn_decode_rope(const sepkv_params *p, const void *q, const void *Kc, co
  * arguments, kernels and results as sepattn_decode, without ws / ws_bytes: the partial results of
  * the cache slices live in a fixed array of SEPATTN_DECODE_NOALLOC_SCRATCH_BYTES inside the library
  * (one copy per GPU the library runs on, held until the process ends).  The call allocates and
- * frees nothing and clears nothing.
+ * frees nothing, and nothing that an earlier call left in the array has to be cleared.
  *   - SEPATTN_ERR_WORKSPACE if the shape needs more than the fixed array, i.e. if
  *     sepattn_decode_noalloc_scratch_bytes(p) (= sepattn_decode_workspace_bytes(p)) exceeds
  *     SEPATTN_DECODE_NOALLOC_SCRATCH_BYTES; nothing is enqueued then.
  *   - All calls on one GPU share that GPU's array: two calls that overlap in time on one GPU (on
- *     different streams, or from different threads) race on it.  Calls on one stream are ordered
- *     and safe.
+ *     different streams, or from different threads) race on it, and their results are wrong.
+ *     Calls on one stream are ordered and safe, also after others have overlapped.
  */
 #define SEPATTN_DECODE_NOALLOC_SCRATCH_BYTES (4u << 20)
 size_t sepattn_decode_noalloc_scratch_bytes(const sepkv_params *p);

@@ -16,7 +16,7 @@ inline int launch_status() { return hipGetLastError() == hipSuccess ? SEPATTN_OK
 // (and blamed on this call) by the first launch_status(): every entry point discards it first.
 inline void discard_stale_hip_error() { (void)hipGetLastError(); }
 
-inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+__host__ __device__ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // 16-byte loads and stores with the non-temporal hint, for rows that are touched once
 typedef unsigned int nt_u32x4 __attribute__((ext_vector_type(4)));

@@ -326,6 +326,15 @@ size_t decode_workspace(const sepkv_params &p) {
     return arrival + align_up((size_t)p.S * p.Hq * nsplit * (p.d + 2) * sizeof(float), 256);
 }
 
+// A captured launch runs with the same arguments at every replay, so it has no number of its own to count its slices under
+// (decode_wide.hip); its slices are added by a merge launch.
+static bool being_captured(hipStream_t st) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    discard_stale_hip_error();  // the null stream while another stream is being captured: the launch reports that
+    return false;
+}
+
 template <typename T>
 int launch_decode_valu(const sepkv_params &p, const void *q, const void *Kc, const void *Vc, const int32_t *sizes,
                        const float *rope, int n_pos, void *out, float *lse, float *part, hipStream_t st) {
@@ -343,12 +352,16 @@ int launch_decode(const sepkv_params &p, const void *q, const void *Kc, const vo
     if (decode_mfma_applicable(p)) {
         using T = uint16_t;
         const bool wide = decode_wide_applicable(p);
-        DecodeWideShape shape = {1, 0};
-        if (wide) shape = decode_wide_shape(p, rope != nullptr);
+        DecodeWideShape shape = {1, 0, false};
+        if (wide) {
+            shape = decode_wide_shape(p, rope != nullptr);
+            shape.add = shape.add && !being_captured(st);
+        }
         const int nsplit = wide ? shape.nsplit : decode_mfma_nsplit(p);
         const int rc = wide ? launch_decode_wide(p, shape, (const T *)q, (const T *)Kc, (const T *)Vc, sizes, rope, n_pos, (T *)out, lse, part, st)
                             : launch_decode_mfma(p, nsplit, (const T *)q, (const T *)Kc, (const T *)Vc, sizes, rope, n_pos, (T *)out, lse, part, st);
-        if (rc != SEPATTN_OK || nsplit == 1 || wide) return rc;
+        if (rc != SEPATTN_OK || nsplit == 1 || shape.add) return rc;
+        if (wide) part += decode_wide_arrival_bytes(p) / sizeof(float);
         ProfScope prof(SEPATTN_K_DECODE_MERGE, st);
         if (p.d == 64)
             hipLaunchKernelGGL((decode_merge_kernel<T, 64>), dim3(p.S * p.Hq), dim3(64), 0, st, nsplit, part, (T *)out, lse);

@@ -19,12 +19,13 @@ __device__ inline CacheMap cache_map(const sepkv_params &p, const int32_t *__res
     m.a = p.a;
     m.s = p.s;
     m.wcap = p.c - p.a - p.s;
-    m.n_init = min(max(sz[0], 0), p.a);
-    m.n_sep = min(max(sz[1], 0), p.s);
-    m.n_past = min(max(sz[2], 0), m.wcap);
-    m.n_loc = min(max(sz[3], 0), m.wcap - m.n_past);
-    m.sep_head = p.s > 0 ? min(max(sz[4], 0), p.s - 1) : 0;
-    m.win_head = min(max(sz[5], 0), m.wcap - 1);
+    const int init = sz[0], sep = sz[1], past = sz[2], loc = sz[3], sep_head = sz[4], win_head = sz[5];
+    m.n_init = min(max(init, 0), p.a);
+    m.n_sep = min(max(sep, 0), p.s);
+    m.n_past = min(max(past, 0), m.wcap);
+    m.n_loc = min(max(loc, 0), m.wcap - m.n_past);
+    m.sep_head = max(min(max(sep_head, 0), p.s - 1), 0);
+    m.win_head = min(max(win_head, 0), m.wcap - 1);
     return m;
 }
 __device__ inline int sep_slot(const CacheMap &m, int k) {
@@ -58,10 +59,12 @@ int launch_decode_mfma(const sepkv_params &p, int nsplit, const uint16_t *q, con
 bool decode_wide_applicable(const sepkv_params &p);
 struct DecodeWideShape {
     int nsplit, nw;  // slices per (sequence, KV head), waves per workgroup
+    bool add;        // the slices are added by decode_wide_kernel itself, not by a merge launch
 };
 DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope);
-// decode_wide_kernel adds its slices itself; the workspace begins with one word per (sequence, KV head) for that
-inline size_t decode_wide_arrival_bytes(const sepkv_params &p) { return align_up((size_t)p.S * p.Hkv * sizeof(uint64_t), 256); }
+// where decode_wide_kernel has several slices the workspace begins with one word per (sequence, KV head), in which they are
+// counted
+__host__ __device__ inline size_t decode_wide_arrival_bytes(const sepkv_params &p) { return align_up((size_t)p.S * p.Hkv * sizeof(uint64_t), 256); }
 int launch_decode_wide(const sepkv_params &p, const DecodeWideShape &shape, const uint16_t *q, const uint16_t *Kc, const uint16_t *Vc,
                        const int32_t *sizes, const float *rope, int n_pos, uint16_t *out, float *lse, float *part,
                        hipStream_t st);

@@ -51,8 +51,9 @@ int sepattn_decode_noalloc(const sepkv_params *p, const void *q, const void *Kc,
     void *ptr = scratch_of_current_device();
     if (!ptr) return SEPATTN_ERR_HIP;
     sepattn::discard_stale_hip_error();
-    // every slot of the partials that the merge step reads is written by this call's first kernel, so
-    // nothing has to be cleared between calls
+    // every record that is added was written by this call's first kernel, and the words in which its slices are counted
+    // (decode_wide.hip) may hold whatever an earlier call, or calls that overlapped, left in them: nothing has to
+    // be cleared between calls
     return sepattn::launch_decode(*p, q, Kc, Vc, sizes, nullptr, 0, out, lse, ptr, static_cast<hipStream_t>(stream));
 }
 

@@ -30,6 +30,9 @@
 // column l%16, rows 4g..4g+3.  Row 4g+i of score tile t (t = 0, 1) is row 8g+4t+i of the block, so that
 // the two tiles' registers of lane group g are rows 8g..8g+7, exactly the k-slots the group holds of the
 // probabilities as B operand of the output contraction: no exchange between lanes.
+#include <atomic>
+#include <chrono>
+
 #include "common.h"
 #include "mfma_common.h"
 #include "decode_common.h"
@@ -67,29 +70,33 @@ __device__ inline float groups_sum(float x) {
 __device__ inline f32x4 lds_read_f4(uint32_t addr) { return *(const f32x4 __attribute__((address_space(3))) *)addr; }
 #pragma clang diagnostic pop
 
-// How many slices of a (sequence, KV head) have published their records: the low 8 bits of a word in the caller's
-// workspace, which nobody clears.  The word counts only while its upper 56 bits hold a fixed pattern.  Every slice looks
-// at it before its own work and, if it is anything else, replaces what it saw by "none"; a slice that sees the pattern,
-// or loses that exchange, finds the word in use by this call.  The last slice sets the count back to none, so that the
-// words of a workspace that has been used before need no exchange.  Nobody waits for another workgroup.
-constexpr uint64_t kArrivalPattern = 0xD1B54A32D192ED03ull & ~0xFFull;
-__device__ inline void arrival_ready(uint64_t *word) {
+// How many slices of a (sequence, KV head) have published their records: a word in the caller's workspace, which nobody
+// clears.  Each slice adds `one`, the number of this launch in the upper 56 bits and 1 in the lower 8; the last one finds
+// (slices - 1) of them and sets the word to 0, so that the next launch finds it so.  Whatever else may stand there
+// (memory never used for this, the sum that calls left which overlapped on one workspace) is no multiple of this
+// launch's `one`: every slice looks at the word before its own work and, if it sees such a value, replaces that by 0;
+// if the exchange fails, another slice of this launch has done so.  Nobody waits for another workgroup.  (A word that
+// every launch has to set first: 0.1 to 0.2 us more.)
+__device__ inline void arrival_ready(uint64_t *word, uint64_t one, int nsplit) {
     uint64_t seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((seen & ~0xFFull) != kArrivalPattern)
-        __hip_atomic_compare_exchange_strong(word, &seen, kArrivalPattern, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t n = seen & 0xFF;
+    if (n >= (uint64_t)nsplit || seen != n * one)
+        __hip_atomic_compare_exchange_strong(word, &seen, 0ull, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ inline bool arrives_last(uint64_t *word, int nsplit) {
-    const uint64_t before = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((int)(before & 0xFF) != nsplit - 1) return false;
-    __hip_atomic_store(word, kArrivalPattern, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ inline bool arrives_last(uint64_t *word, uint64_t one, int nsplit) {
+    if (__hip_atomic_fetch_add(word, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (uint64_t)(nsplit - 1) * one) return false;
+    __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     return true;
 }
 
-template <int D, bool ROPE, int NW>
+// ADD: several slices, added by the workgroup that finishes last.  Otherwise one slice, or the records are left to a merge launch.
+// The arguments fill 120 bytes, so that what the kernel reads of them, the grid's size behind them included, is two cache
+// lines: a third one costs a short eager call 0.1 us.
+template <int D, bool ROPE, int NW, bool ADD>
 __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
-    sepkv_params p, int G, const uint16_t *__restrict__ q, const uint16_t *__restrict__ Kc,
-    const uint16_t *__restrict__ Vc, const int32_t *__restrict__ sizes, const float *__restrict__ rope, int n_pos,
-    uint64_t *__restrict__ arrived, float *__restrict__ part, uint16_t *__restrict__ out, float *__restrict__ lse) {
+    sepkv_params p, int G, int n_pos, const uint16_t *__restrict__ q, const uint16_t *__restrict__ Kc,
+    const uint16_t *__restrict__ Vc, const int32_t *__restrict__ sizes, const float *__restrict__ rope, uint64_t one,
+    float *__restrict__ part, uint16_t *__restrict__ out, float *__restrict__ lse) {
     constexpr int CH = D / 8;           // 16-byte chunks per row
     constexpr int RPL = 64 / CH;        // rows covered by one wave-wide 1 KB load
     constexpr int NLD = kDwRows / RPL;  // wave-wide loads per tensor per stage
@@ -111,8 +118,16 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
     const uint16_t *Kh = Kc + ((long)sq * p.Hkv + kv) * (long)p.c * D;
     const uint16_t *Vh = Vc + ((long)sq * p.Hkv + kv) * (long)p.c * D;
 
-    arrived += (long)sq * p.Hkv + kv;
-    if (nsplit > 1 && tid == 64 * (NW - 1)) arrival_ready(arrived);
+    const CacheMap cm = cache_map(p, sizes + SEPKV_SIZES_COLS * sq);
+    // one word per (sequence, KV head), then the records
+    uint64_t *const arrived = reinterpret_cast<uint64_t *>(part) + (long)sq * p.Hkv + kv;
+    part += decode_wide_arrival_bytes(p) / sizeof(float);
+    // by the wave with the fewest blocks, in front of everything else: behind the queries 0.1 to 0.3 us slower with ROPE (2
+    // sequences of 400 entries 7.4 -> 7.7), put off until the rows have been used 0.4 us without (2 sequences, 32/32 heads, 937
+    // entries 9.1 -> 9.6)
+    if constexpr (ADD) {
+        if (tid == 64 * (NW - 1)) arrival_ready(arrived, one, nsplit);
+    }
     // queries: B operand, column = head of the group (zero beyond G)
     u32x4 qraw[KSTEPS];
     {
@@ -137,7 +152,6 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
                           t_lds + (wave * TLD + U) * 1024);
         });
     }
-    const CacheMap cm = cache_map(p, sizes + SEPKV_SIZES_COLS * sq);
     const int nv = cm.n_init + cm.n_sep + cm.n_past + cm.n_loc;
     // slices of whole blocks; wave w takes blocks w, w + NW, ... of the slice
     const int nb = (nv + kDwRows - 1) / kDwRows;
@@ -341,7 +355,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
             o1 = fmaf(wgt, o.y, o1);
         }
         const long sh = (long)sq * p.Hq + h0 + h;
-        if (nsplit == 1) {
+        if (!ADD && nsplit == 1) {
             const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
             typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
             typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -350,17 +364,22 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
             if (lse && c2 == 0) lse[sh] = (lsum > 0.f) ? (M + __builtin_amdgcn_logf(lsum)) * kLn2_f : -INFINITY;
         } else {
             float *dst = part + (sh * nsplit + split) * PF;
-            publish(dst + 2 + 2 * c2, float2{o0, o1});
-            if (c2 == 0) publish(dst, float2{M, lsum});
+            if constexpr (ADD) {
+                publish(dst + 2 + 2 * c2, float2{o0, o1});
+                if (c2 == 0) publish(dst, float2{M, lsum});
+            } else {
+                *reinterpret_cast<float2 *>(dst + 2 + 2 * c2) = float2{o0, o1};
+                if (c2 == 0) *reinterpret_cast<float2 *>(dst) = float2{M, lsum};
+            }
         }
     }
-    if (nsplit == 1) return;
+    if constexpr (!ADD) return;
 
     // ---- the workgroup that finishes last adds the slices' records, in slice order, whichever it is
     __shared__ int last_s;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's part of the record is where every XCD sees it
     __syncthreads();
-    if (tid == 0) last_s = arrives_last(arrived, nsplit);
+    if (tid == 0) last_s = arrives_last(arrived, one, nsplit);
     __syncthreads();
     if (!last_s) return;
     for (int item = tid; item < G * (D / 2); item += 64 * NW) {
@@ -433,29 +452,37 @@ DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope) {
     if (ns > fit) ns = (int)fit;
     if (ns > 1) {
         const int per = (nb + ns - 1) / ns;
-        if (nb - per >= (rope ? 9 * d64 : d64 == 1 ? 13 : 22)) return {ns, d64 == 1 || per <= 4 ? 4 : 8};
+        if (nb - per >= (rope ? 9 * d64 : d64 == 1 ? 13 : 22)) return {ns, d64 == 1 || per <= 4 ? 4 : 8, true};
     }
-    return {1, nb <= 4 || pairs > (long)compute_units() * d64 ? 4 : 8};
+    return {1, nb <= 4 || pairs > (long)compute_units() * d64 ? 4 : 8, false};
+}
+
+// What each slice of one launch adds to its word: a number in the upper 56 bits that no two launches of a process share (those of
+// another process, or whatever else memory may hold, meet it with probability 2^-56), and 1.
+static uint64_t launch_number() {
+    static std::atomic<uint64_t> number{(uint64_t)std::chrono::system_clock::now().time_since_epoch().count()};
+    return (number.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull) << 8 | 1;
 }
 
 int launch_decode_wide(const sepkv_params &p, const DecodeWideShape &shape, const uint16_t *q, const uint16_t *Kc, const uint16_t *Vc,
                        const int32_t *sizes, const float *rope, int n_pos, uint16_t *out, float *lse, float *part,
                        hipStream_t st) {
-    uint64_t *arrived = reinterpret_cast<uint64_t *>(part);  // one word per (sequence, KV head), then the records
-    part += decode_wide_arrival_bytes(p) / sizeof(float);
     if (p.Hkv > 65535 || p.S > 65535) return SEPATTN_ERR_SHAPE;
     const int G = p.Hq / p.Hkv;
     ProfScope prof(SEPATTN_K_DECODE_SPLIT, st);
-    auto go = [&](auto D_, auto NW_) {
+    const uint64_t one = shape.add ? launch_number() : 0;
+    auto go = [&](auto D_, auto NW_, auto ADD_) {
         constexpr int D = decltype(D_)::value, NW = decltype(NW_)::value;
+        constexpr bool ADD = decltype(ADD_)::value;
         const dim3 grid(shape.nsplit, p.Hkv, p.S), block(64 * NW);
         if (rope)
-            hipLaunchKernelGGL((decode_wide_kernel<D, true, NW>), grid, block, 0, st, p, G, q, Kc, Vc, sizes, rope, n_pos, arrived, part, out, lse);
+            hipLaunchKernelGGL((decode_wide_kernel<D, true, NW, ADD>), grid, block, 0, st, p, G, n_pos, q, Kc, Vc, sizes, rope, one, part, out, lse);
         else
-            hipLaunchKernelGGL((decode_wide_kernel<D, false, NW>), grid, block, 0, st, p, G, q, Kc, Vc, sizes, rope, n_pos, arrived, part, out, lse);
+            hipLaunchKernelGGL((decode_wide_kernel<D, false, NW, ADD>), grid, block, 0, st, p, G, n_pos, q, Kc, Vc, sizes, rope, one, part, out, lse);
     };
-    if (p.d == 64) shape.nw == 4 ? go(IntC<64>{}, IntC<4>{}) : go(IntC<64>{}, IntC<8>{});
-    else shape.nw == 4 ? go(IntC<128>{}, IntC<4>{}) : go(IntC<128>{}, IntC<8>{});
+    auto pick = [&](auto D_, auto NW_) { shape.add ? go(D_, NW_, IntC<1>{}) : go(D_, NW_, IntC<0>{}); };
+    if (p.d == 64) shape.nw == 4 ? pick(IntC<64>{}, IntC<4>{}) : pick(IntC<64>{}, IntC<8>{});
+    else shape.nw == 4 ? pick(IntC<128>{}, IntC<4>{}) : pick(IntC<128>{}, IntC<8>{});
     return launch_status();
 }
 

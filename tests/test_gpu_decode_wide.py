@@ -100,3 +100,78 @@ def test_decode_workspace_needs_no_clearing():
         for k in (0, 0, 1, 2, 0, 2, 1):
             for got, ref in zip(call(*shapes[k], ws), fresh[k]):
                 assert torch.equal(got, ref)
+
+
+@pytest.mark.parametrize("left", [1, 3, 6])
+def test_decode_heals_from_counts_that_overlapping_calls_left(left):
+    """Two calls that overlap on one workspace may leave any count in the words that count the slices.  That spoils
+    those calls, and none after them."""
+    import paper_2412_12094_amd as sp
+
+    S, Hkv, c, sizes = 4, 8, 800, [[4, 64, 476, 256, 3, 5]]
+    ws = torch.zeros(4 << 20, dtype=torch.uint8, device="cuda")
+    words = ws[: 8 * S * Hkv].view(torch.int64)
+    g = torch.Generator(device="cuda").manual_seed(left)
+    sz = torch.tensor(sizes * S, dtype=torch.int32, device="cuda")
+    for call in range(4):
+        q = torch.randn((S, 32, 128), device="cuda", generator=g).bfloat16()
+        K, V = (torch.randn((S, Hkv, c, 128), device="cuda", generator=g).bfloat16() for _ in range(2))
+        ref = sp.sepattn_decode(q, K, V, sz, 4, 64, 256, 0.09, ws=torch.zeros_like(ws))
+        got = sp.sepattn_decode(q, K, V, sz, 4, 64, 256, 0.09, ws=ws)
+        for x, y in zip(got, ref):
+            assert torch.equal(x, y), call
+        words += left + (call << 40)  # the lower 8 bits count, the upper ones tell launches apart
+
+
+def test_decode_alone_after_calls_that_overlapped():
+    """The same with an overlap: whatever two streams leave in a workspace that they share, later calls are right."""
+    import paper_2412_12094_amd as sp
+
+    g = torch.Generator(device="cuda").manual_seed(21)
+    q = torch.randn((4, 32, 128), device="cuda", generator=g).bfloat16()
+    K, V = (torch.randn((4, 8, 800, 128), device="cuda", generator=g).bfloat16() for _ in range(2))
+    sz = torch.tensor([[4, 64, 476, 256, 3, 5]] * 4, dtype=torch.int32, device="cuda")
+    ws = torch.zeros(4 << 20, dtype=torch.uint8, device="cuda")
+    ref = sp.sepattn_decode(q, K, V, sz, 4, 64, 256, 0.09, ws=torch.zeros_like(ws))
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    outs = [(torch.empty_like(q), torch.empty((4, 32), device="cuda")) for _ in streams]
+    torch.cuda.synchronize()
+    for _ in range(16):
+        for st, out in zip(streams, outs):
+            with torch.cuda.stream(st):
+                sp.sepattn_decode(q, K, V, sz, 4, 64, 256, 0.09, out=out, ws=ws)
+    torch.cuda.synchronize()
+    for call in range(3):
+        got = sp.sepattn_decode(q, K, V, sz, 4, 64, 256, 0.09, ws=ws)
+        for x, y in zip(got, ref):
+            assert torch.equal(x, y), call
+
+
+def test_decode_captured_slices_replay():
+    """A captured call has several slices too; whatever the workspace holds before a replay, the outputs are those of the
+    eager call, bit for bit."""
+    import paper_2412_12094_amd as sp
+
+    g = torch.Generator(device="cuda").manual_seed(11)
+    q = torch.empty((4, 32, 128), dtype=torch.bfloat16, device="cuda")
+    K, V = (torch.randn((4, 8, 800, 128), device="cuda", generator=g).bfloat16() for _ in range(2))
+    sz = torch.tensor([[4, 64, 476, 256, 3, 5]] * 4, dtype=torch.int32, device="cuda")
+    out = (torch.empty_like(q), torch.empty((4, 32), device="cuda"))
+    ws, other = (torch.zeros(4 << 20, dtype=torch.uint8, device="cuda") for _ in range(2))
+    call = lambda w, o: sp.sepattn_decode(q, K, V, sz, 4, 64, 256, 0.09, out=o, ws=w)
+    side = torch.cuda.Stream()
+    q.normal_(generator=g)
+    with torch.cuda.stream(side):
+        call(ws, out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(ws, out)
+    for k in range(5):
+        q.normal_(generator=g)
+        ref = [t.clone() for t in call(other, None)]
+        ws.random_(0, 256, generator=g) if k % 2 else ws.fill_(k)
+        graph.replay()
+        torch.cuda.synchronize()
+        for x, y in zip(out, ref):
+            assert torch.equal(x, y), k
