@@ -431,8 +431,16 @@ bool decode_wide_applicable(const sepkv_params &p) {
 //     (25 blocks): seven slices of four waves 6.1 / 7.3, four of eight with a merge launch 7.0 / 8.4; 4 sequences
 //     6.7 / 7.8 against 8.2 / 9.3.  Never two workgroups on some compute units: d = 64, 32 sequences of 2300 entries,
 //     one slice 22.5 / 23.0, two 24.4 / 25.1.
-//   Eight slices, whose records are fetched in one round trip (1 sequence of 1400 entries: 6.7 / 8.6, eleven 7.7 / 8.8);
-//     sixteen where a slice would be longer than ten blocks (1 sequence of 3332 entries 8.9 / 10.0, eight 9.9 / 11.7).
+//   Eight slices, whose records are fetched in one round trip (1 sequence of 1400 entries: 6.7 / 8.6, eleven 7.7 / 8.8); more
+//     for long caches, in proportion to the root of their length, because what a slice more costs does not depend on
+//     the length and what it spares does.  16/4 heads, 3332 entries: sixteen 8.8 / 10.1, eight 9.5 / 11.7 (d = 64, whose blocks take
+//     half the time: fourteen 8.2 / 8.7, eight 7.1 / 7.8); 16/2 heads, 8192 entries: thirty-two 11.2 / 12.0, sixteen 11.6 / 13.3; 16384: 13.7 /
+//     14.9 and 16.4 / 18.9; 65536: sixty-four 22.8 / 24.2, thirty-two 27.8 / 31.5, sixteen 44 / 48.  With more than four pairs, whose
+//     sixteen slices are half a chip, the second line lies later: 32/8 heads, 8192 entries: thirty-two 13.3 / 13.8, sixteen
+//     12.4 / 13.4; 16384: 17.7 / 18.3 and 18.1 / 19.1.
+//   More than sixteen are added by a merge launch: a workgroup alone fetches their records, past the L2, in longer than that takes
+//     (32/8 heads, 16384 entries, thirty-two: 18.9 / 19.4, with a merge launch 17.8 / 18.3; up to sixteen level on the device, and
+//     a launch less on the host).
 //   Slices pay when the blocks that a workgroup is spared take longer than adding the records (about 2 us).  A block
 //     costs a lone workgroup 0.2 us, with ROPE 0.3 us, half of that at d = 64: 13 blocks in one slice 5.8 / 8.4, in four
 //     5.8 / 6.9; 16 blocks 6.0 / 8.6 and 6.0 / 7.0; a cache of 16 that holds 12 to 16 (28/4 heads, 2 sequences) 6.9 in one,
@@ -446,13 +454,14 @@ bool decode_wide_applicable(const sepkv_params &p) {
 DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope) {
     const long pairs = (long)p.S * p.Hkv, fit = compute_units() / pairs;
     const int nb = (p.c + kDwRows - 1) / kDwRows, d64 = p.d == 64 ? 2 : 1;
-    const int want = d64 == 2 && nb > 32 ? 8 : 4, most = nb > 80 ? 16 : 8;  // blocks per slice, slices
+    const int want = d64 == 2 && nb > 32 ? 8 : 4;  // blocks per slice
+    const int most = nb <= (d64 == 1 ? 80 : 128) ? 8 : nb <= (pairs > 4 ? 400 : 200) * d64 ? 16 : nb <= 800 * d64 ? 32 : 64;
     int ns = (nb + want - 1) / want;
     if (ns > most) ns = most;
     if (ns > fit) ns = (int)fit;
     if (ns > 1) {
         const int per = (nb + ns - 1) / ns;
-        if (nb - per >= (rope ? 9 * d64 : d64 == 1 ? 13 : 22)) return {ns, d64 == 1 || per <= 4 ? 4 : 8, true};
+        if (nb - per >= (rope ? 9 * d64 : d64 == 1 ? 13 : 22)) return {ns, d64 == 1 || per <= 4 ? 4 : 8, ns <= 16};
     }
     return {1, nb <= 4 || pairs > (long)compute_units() * d64 ? 4 : 8, false};
 }

@@ -62,7 +62,7 @@ def test_decode_dispatch_edges(S, Hq, Hkv, d, a, s, w, c, rope):
 
 # slices and waves per workgroup: the edges of decode_wide_shape's rules on a chip of 256 compute units
 SHAPE_CASES = [
-    (1, 8, 2, 128, 4, 100, 60, 256),    # eight blocks: one slice of four waves
+    (1, 8, 2, 128, 4, 100, 60, 256),    # eight blocks: one slice of eight waves
     (1, 8, 2, 128, 4, 100, 60, 385),    # 13 blocks: one slice of eight waves without ROPE, four of four with
     (4, 32, 8, 128, 4, 64, 256, 800),   # 25 blocks in seven slices, the last of one block
     (2, 8, 1, 128, 0, 1100, 256, 2600), # 82 blocks in sixteen slices
@@ -70,6 +70,10 @@ SHAPE_CASES = [
     (16, 128, 8, 128, 4, 200, 100, 800),# 128 pairs of sixteen heads: two slices
     (2, 12, 12, 64, 3, 64, 256, 800),   # d = 64: one slice without ROPE, seven of four waves with
     (4, 8, 8, 64, 4, 900, 256, 2300),   # nine blocks per slice: eight waves
+    (1, 4, 2, 64, 4, 2500, 256, 5200),  # d = 64, 163 blocks: sixteen slices, two fetches of records
+    (1, 2, 1, 128, 4, 4000, 256, 6500), # 204 blocks, one pair: thirty-two slices, merge launch
+    (1, 5, 5, 128, 4, 4000, 256, 6500), # 204 blocks, five pairs: sixteen
+    (1, 2, 1, 64, 4, 30000, 256, 51300),# 1604 blocks: sixty-four
     (33, 8, 8, 64, 4, 500, 100, 1100),  # 264 pairs at d = 64: one slice of eight waves
 ]
 
