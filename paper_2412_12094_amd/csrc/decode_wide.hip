@@ -18,9 +18,9 @@
 //     lanes alike) minus that of r (rows 0 .. 31 of the table, fetched once per workgroup into LDS, kept in
 //     registers); dimension i pairs with i + D/2 in another fragment of the same lane.  (Reading each row's own
 //     table row from memory is 64 separate 16-byte pieces per instruction: 3.5 us per round of eight blocks.)
-//   - the workgroup of a cache that finishes last adds the slices (arrives_last): about 2 us of device-scope round trips,
-//     as long as a merge launch takes on the device, but a launch less on the host, which costs 3.5 us there
-//     (append + decode of a streaming generation step, 4 sequences of 800 entries: 12.3 us -> 9.9).
+//   - where the slices' records are few, the workgroup of a cache that finishes last adds them (arrives_last): 1 to 2 us of
+//     device-scope round trips, as long as a merge launch takes on the device, but a launch less on the host, which
+//     costs 3 us there (append + decode of a streaming generation step, 32/8 heads, 4 sequences of 800 entries: 12.3 us -> 9.9).
 // Measured (MI355X, 32/8 heads, d = 128, one call of a stream of calls, us without / with ROPE; before: four
 // waves, 32-column operands, two stages per wave, the angle carried from block to block in registers):
 //   1 sequence, 64 entries 5.1 / 6.7 -> 3.6 / 4.8; 800 entries 8.8 / 12.0 -> 6.1 / 7.3
@@ -438,9 +438,12 @@ bool decode_wide_applicable(const sepkv_params &p) {
 //     14.9 and 16.4 / 18.9; 65536: sixty-four 22.8 / 24.2, thirty-two 27.8 / 31.5, sixteen 44 / 48.  With more than four pairs, whose
 //     sixteen slices are half a chip, the second line lies later: 32/8 heads, 8192 entries: thirty-two 13.3 / 13.8, sixteen
 //     12.4 / 13.4; 16384: 17.7 / 18.3 and 18.1 / 19.1.
-//   More than sixteen are added by a merge launch: a workgroup alone fetches their records, past the L2, in longer than that takes
-//     (32/8 heads, 16384 entries, thirty-two: 18.9 / 19.4, with a merge launch 17.8 / 18.3; up to sixteen level on the device, and
-//     a launch less on the host).
+//   The kernel adds the slices where their records are few, as one workgroup fetches them all, past the L2: 33 KB at the line.
+//     A merge launch takes the device 0.6 us longer for three records of 4 x 128, as long for twelve, 2 us less for eight of
+//     16 x 128 and 1.6 for thirty-two of 4 x 128.  16/1 heads, 3332 entries, sixteen: 14.6 / 15.9, with a merge launch 9.5 / 10.8; 16/2
+//     heads 10.8 / 12.1 and 9.2 / 10.4; 32/8 heads, 16384 entries, thirty-two: 18.9 / 19.4 and 17.8 / 18.3.  It also costs the host 3 us, which
+//     append + decode per token wait for: 28/4 heads, 4 sequences, caches of 1600, 13.3 us per token with eight slices added in
+//     the kernel, 14.7 with a merge launch.
 //   Slices pay when the blocks that a workgroup is spared take longer than adding the records (about 2 us).  A block
 //     costs a lone workgroup 0.2 us, with ROPE 0.3 us, half of that at d = 64: 13 blocks in one slice 5.8 / 8.4, in four
 //     5.8 / 6.9; 16 blocks 6.0 / 8.6 and 6.0 / 7.0; a cache of 16 that holds 12 to 16 (28/4 heads, 2 sequences) 6.9 in one,
@@ -453,7 +456,7 @@ bool decode_wide_applicable(const sepkv_params &p) {
 //     8 heads of 100 entries 8.9 -> 5.4, of 1000 entries 40.7 -> 39.2).
 DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope) {
     const long pairs = (long)p.S * p.Hkv, fit = compute_units() / pairs;
-    const int nb = (p.c + kDwRows - 1) / kDwRows, d64 = p.d == 64 ? 2 : 1;
+    const int nb = (p.c + kDwRows - 1) / kDwRows, d64 = p.d == 64 ? 2 : 1, row = p.Hq / p.Hkv * p.d;
     const int want = d64 == 2 && nb > 32 ? 8 : 4;  // blocks per slice
     const int most = nb <= (d64 == 1 ? 80 : 128) ? 8 : nb <= (pairs > 4 ? 400 : 200) * d64 ? 16 : nb <= 800 * d64 ? 32 : 64;
     int ns = (nb + want - 1) / want;
@@ -461,7 +464,7 @@ DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope) {
     if (ns > fit) ns = (int)fit;
     if (ns > 1) {
         const int per = (nb + ns - 1) / ns;
-        if (nb - per >= (rope ? 9 * d64 : d64 == 1 ? 13 : 22)) return {ns, d64 == 1 || per <= 4 ? 4 : 8, ns <= 16};
+        if (nb - per >= (rope ? 9 * d64 : d64 == 1 ? 13 : 22)) return {ns, d64 == 1 || per <= 4 ? 4 : 8, ns <= 16 && row <= 1024 && ns * row <= 8192};
     }
     return {1, nb <= 4 || pairs > (long)compute_units() * d64 ? 4 : 8, false};
 }

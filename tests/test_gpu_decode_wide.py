@@ -70,6 +70,8 @@ SHAPE_CASES = [
     (16, 128, 8, 128, 4, 200, 100, 800),# 128 pairs of sixteen heads: two slices
     (2, 12, 12, 64, 3, 64, 256, 800),   # d = 64: one slice without ROPE, seven of four waves with
     (4, 8, 8, 64, 4, 900, 256, 2300),   # nine blocks per slice: eight waves
+    (2, 14, 2, 128, 4, 500, 256, 1400), # seven heads: eight slices added in the kernel
+    (2, 14, 2, 128, 4, 1100, 256, 2600),# seven heads: sixteen slices, merge launch
     (1, 4, 2, 64, 4, 2500, 256, 5200),  # d = 64, 163 blocks: sixteen slices, two fetches of records
     (1, 2, 1, 128, 4, 4000, 256, 6500), # 204 blocks, one pair: thirty-two slices, merge launch
     (1, 5, 5, 128, 4, 4000, 256, 6500), # 204 blocks, five pairs: sixteen
