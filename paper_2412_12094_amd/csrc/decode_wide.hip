@@ -424,12 +424,12 @@ bool decode_wide_applicable(const sepkv_params &p) {
     return p.dtype == SEPATTN_BF16 && (p.d == 64 || p.d == 128) && p.Hq / p.Hkv <= 16;
 }
 
-// Slices per cache and waves per workgroup.  Times below: one call of a stream of calls in us, 32/8 heads, d = 128
-// unless noted, without / with ROPE.
+// Slices per cache, waves per workgroup, and who adds the slices.  Times below: one call of a stream of calls in us, 32/8 heads,
+// d = 128, caches that are full, without / with ROPE, unless noted.
 //   Slices are at most one workgroup per compute unit, four blocks each (one per wave; d = 64 with more than 32 blocks:
 //     eight): the rows that one compute unit has to fetch are what a short call waits for.  1 sequence of 800 entries
-//     (25 blocks): seven slices of four waves 6.1 / 7.3, four of eight with a merge launch 7.0 / 8.4; 4 sequences
-//     6.7 / 7.8 against 8.2 / 9.3.  Never two workgroups on some compute units: d = 64, 32 sequences of 2300 entries,
+//     (25 blocks): seven slices of four waves 6.8 / 7.7, four of eight with a merge launch 8.3 / 9.4; 4 sequences
+//     8.0 / 8.8 against 9.0 / 10.0.  Never two workgroups on some compute units: d = 64, 32 sequences of 2300 entries,
 //     one slice 22.5 / 23.0, two 24.4 / 25.1.
 //   Eight slices, whose records are fetched in one round trip (1 sequence of 1400 entries: 6.7 / 8.6, eleven 7.7 / 8.8); more
 //     for long caches, in proportion to the root of their length, because what a slice more costs does not depend on
@@ -444,10 +444,14 @@ bool decode_wide_applicable(const sepkv_params &p) {
 //     heads 10.8 / 12.1 and 9.2 / 10.4; 32/8 heads, 16384 entries, thirty-two: 18.9 / 19.4 and 17.8 / 18.3.  It also costs the host 3 us, which
 //     append + decode per token wait for: 28/4 heads, 4 sequences, caches of 1600, 13.3 us per token with eight slices added in
 //     the kernel, 14.7 with a merge launch.
-//   Slices pay when the blocks that a workgroup is spared take longer than adding the records (about 2 us).  A block
-//     costs a lone workgroup 0.2 us, with ROPE 0.3 us, half of that at d = 64: 13 blocks in one slice 5.8 / 8.4, in four
-//     5.8 / 6.9; 16 blocks 6.0 / 8.6 and 6.0 / 7.0; a cache of 16 that holds 12 to 16 (28/4 heads, 2 sequences) 6.9 in one,
-//     7.9 in four.
+//   Slices pay when the blocks that a workgroup is spared take longer than adding the records (1 to 2 us; a block costs
+//     a lone workgroup 0.2 us, with ROPE 0.3 us, half of that at d = 64).  The slices follow the capacity c, as only the
+//     device knows how much of it is in use.  One slice / sliced, 32/8 and 28/4 heads, 1 to 6 sequences, full caches and half-full
+//     ones: without ROPE 13 blocks 6.7 / 6.4 and 5.3 / 5.8, 16 blocks 7.5 / 6.5 and 5.6 / 5.9 (28/4 heads, 12 to 16 of them in use, 6.9 / 7.9), 20 blocks 8.6 / 6.6 and 6.0 / 6.0;
+//     with ROPE 13 blocks 9.1 / 7.3 and 6.6 / 7.0, 20 blocks 10.1 / 7.5 and 7.8 / 7.2; d = 64: 20 blocks 5.7 / 5.4 and 4.1 / 5.1, 25 blocks
+//     6.4 / 5.6 and 4.8 / 5.3.  Two or three slices of four waves have hardly more waves than the one of eight, and have to spare
+//     more: two, 16 sequences of 28 blocks 13.2 / 13.9 and (0.6 full) 9.5 / 11.1, with ROPE 14.8 / 14.8 and 11.1 / 12.1, of 38 blocks with
+//     ROPE 19.2 / 17.5 and 13.2 / 12.9; three, 10 sequences of 15 blocks with ROPE 9.8 / 10.1, of 19 blocks 10.9 / 10.2.
 //   Four waves per slice at d = 128 (two slices for 16 sequences of 2300 entries 24.6 / 25.6, of eight waves 24.8 / 25.6)
 //     and where each has one block; eight at d = 64 (8 sequences of 2300 entries 8.2 / 8.8 against 8.7 / 9.5).
 //   One slice: eight waves (more bytes in flight); four for caches of up to four blocks (1 sequence of 128 entries
@@ -464,7 +468,8 @@ DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope) {
     if (ns > fit) ns = (int)fit;
     if (ns > 1) {
         const int per = (nb + ns - 1) / ns;
-        if (nb - per >= (rope ? 9 * d64 : d64 == 1 ? 13 : 22)) return {ns, d64 == 1 || per <= 4 ? 4 : 8, ns <= 16 && row <= 1024 && ns * row <= 8192};
+        const int pays = (rope ? 9 * d64 : d64 == 1 ? 13 : 22) + (ns == 2 ? 8 : ns == 3 ? 3 : 0) * d64;
+        if (nb - per >= pays) return {ns, d64 == 1 || per <= 4 ? 4 : 8, ns <= 16 && row <= 1024 && ns * row <= 8192};
     }
     return {1, nb <= 4 || pairs > (long)compute_units() * d64 ? 4 : 8, false};
 }

@@ -67,7 +67,9 @@ SHAPE_CASES = [
     (4, 32, 8, 128, 4, 64, 256, 800),   # 25 blocks in seven slices, the last of one block
     (2, 8, 1, 128, 0, 1100, 256, 2600), # 82 blocks in sixteen slices
     (9, 56, 8, 128, 4, 500, 100, 1600), # 72 pairs of seven heads: three slices
-    (16, 128, 8, 128, 4, 200, 100, 800),# 128 pairs of sixteen heads: two slices
+    (16, 128, 8, 128, 4, 200, 100, 800),# 128 pairs of sixteen heads, 25 blocks: one slice
+    (16, 32, 8, 128, 4, 200, 100, 1100),# 128 pairs, 35 blocks: one slice without ROPE, two with
+    (16, 128, 8, 128, 4, 800, 100, 1400),# 128 pairs of sixteen heads, 44 blocks: two slices, merge launch
     (2, 12, 12, 64, 3, 64, 256, 800),   # d = 64: one slice without ROPE, seven of four waves with
     (4, 8, 8, 64, 4, 900, 256, 2300),   # nine blocks per slice: eight waves
     (2, 14, 2, 128, 4, 500, 256, 1400), # seven heads: eight slices added in the kernel
