@@ -137,14 +137,17 @@ __host__ __device__ inline SplitTiles split_tiles(int tiles, int TP, int window,
 // From which window length on tiles are split, 0: none are.  Half of the longest (p.n is that of the call), if that shortens the
 // longest chain by kWorthSplitting keys, given the workgroups' mean work, and there is `room` for the parts of so many
 // tiles.  A split costs the second part's start, fp32 sums and a launch that adds them (6 us for 128 tiles at
-// d = 128).  Measured, forward and backward in us, whole / split streams.  Above the line: every fourth KV head full, the others 128 (32/8
-// heads, d = 128, L = 4096) 384 / 377, of which dQ 114.5 / 97.6 + 5.6, the same with 8/8 heads 249 / 217; 8/1 heads, L = 3000, n = L
-// 198 / 182; 8/2 heads, L = 4096, n = L 277 / 261.  Below it: 32/8 heads, L = n = 1024 106 / 108, 2048 231 / 234; 16/4 heads, 2 x L = 1500,
-// n = 1100 157 / 166; 12 heads, d = 64, L = n = 2048 125 / 117, but every fourth of them full, 4 x L = 2048 154 / 158.
+// d = 128).  Over 270 calls with full windows of 1300 to 2500 positions the step is, by what a split saves, 1.00 times as fast at 800 to
+// 1200 keys (0.96 to 1.06), 1.04 at 1200 to 1600 (0.97 to 1.10), 1.07 above (1.01 to 1.12).  Forward and backward in us, whole / split
+// streams.  Above the line: every fourth KV head full, the others 128 (32/8 heads, d = 128, L = 4096) 363 / 352, the same with 8/8 heads
+// 245 / 213; 8/1 heads, L = 3000, n = L 193 / 179; 12/12 heads, d = 64, L = n = 2048 123 / 116, 1300 91 / 88; 8/2 heads, L = 4096, n = L 273 / 254.
+// Below it: 32/8 heads, L = n = 2048 225 / 228; 12/12 heads, d = 64, 4 x L = 2048 194 / 207.  Windows that end before the sequence and
+// are shorter than twice the line stay whole: from there on all tiles are equally long, and it is half of them or more that
+// are split (8/2 heads, L = 4096, n = 2048, 1330 keys saved, 201 / 208; 6/3 heads, 1570 keys, 222 / 221).
 constexpr int kWorthSplitting = 1280;
 inline int split_keys(const sepattn_params &p, const HeadWin &hw, int gp, int TP, long slots, size_t room) {
     const int longest = p.n < p.L ? p.n : p.L, start = TP + 128;
-    if (longest < 2 * kWorthSplitting) return 0;
+    if (p.n < p.L && longest < 2 * kWorthSplitting) return 0;
     double sum = 0.;
     for (int h = 0; h < p.Hq; h += gp) sum += query_cost(p, TP, p.n - group_delta(hw, h, gp)) / TP * p.B;
     const int keys = (longest / 2 + TP - 1) / TP * TP;

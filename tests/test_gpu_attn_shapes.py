@@ -118,7 +118,11 @@ def test_bf16_band_units_in_parts(B, Hq, Hkv, L, d, a, n, p):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("B,Hq,Hkv,L,a,n,p", [
-    (1, 4, 1, 2560, 4, 2560, 0.1),                         # the shortest sequence with split streams
+    (1, 4, 1, 2560, 4, 2560, 0.1),                         # four heads; the shortest window that may end before the sequence
+    (1, 3, 3, 1301, 0, 1301, 0.05),                        # full windows are split from some 1300 positions on
+    (1, 4, 2, 1500, 4, 1500, 0.1),                         # two heads
+    (1, 4, 2, 1500, 4, 1499, 0.1),                         # a position short of full: whole
+    (1, 8, 2, 1430, 4, [1430] * 4 + [30, 7, 1, 64], 0.1),  # one group full and split, the other not
     (1, 2, 1, 2627, 0, 1 << 20, 0.0),                      # two heads, ragged; windows longer than any sequence
     (2, 1, 1, 2689, 4, 2570, 0.1),                         # one head: waves that end before the second half
     (1, 4, 2, 4000, 2, 2600, 0.3),                         # windows that end: many split tiles equally long
