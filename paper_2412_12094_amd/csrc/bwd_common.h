@@ -12,9 +12,11 @@ namespace sepattn {
 // of two shapes:
 //   KW = 4: 8 waves, one workgroup per compute unit.  Fewest tile loads per matrix instruction; the
 //           better shape when a workgroup's pieces are long: d = 128, sequences from 8K on with
-//           grouped heads (a step with 32/8 heads, us, KW = 4 / 2: L = 8192, n = 256 442 / 443, n = 1024 779 / 805; 16K 1241 / 1268,
-//           32K 3998 / 4282; at L = 4096, or with one head per KV head at 8K, the other shape is 1-13 % ahead, at 16K
-//           with one head per KV head the two are level).
+//           grouped heads.  A step in us, KW = 4 / 2 (two runs of one side differ by up to 0.5 %): 32/8 heads, n = 256, L = 8192
+//           430.8 / 433.7, two of them 884 / 906, L = 12000 783 / 801; 28/4 heads, L = 8192, n = 256 380 / 386, n = 1024 688 / 719;
+//           8/2 heads, L = 16384, n = 256 331 / 346, n = 1024 516 / 540.  Short windows at 8K, where pieces are shorter, are on the wrong side of
+//           the line: 32/8 heads, n = 64 351 / 346 (28/4 heads 307 / 310).  Beyond it: 16/4 heads, L = 4096, n = 64 102.6 / 96.6, n = 256 119.7 /
+//           115.4; 32/8 heads 196.8 / 197.4, but n = 1024 360 / 377; 32/32 heads, L = 8192, n = 64 465 / 459, n = 256 556 / 559.
 //   KW = 2: 4 waves, two workgroups per compute unit (three at d = 64, where the registers and the ring
 //           of query tiles allow it) that run independently: one's piece start-up and partial stores
 //           overlap the others' matrix work, the split of a (batch, KV head) is finer (it fills the
