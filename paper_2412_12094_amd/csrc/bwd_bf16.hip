@@ -633,19 +633,19 @@ int launch_bwd(const sepattn_params &p, const uint16_t *Q, const uint16_t *K, co
     const int TP = 32 * shape.nw / shape.gp;
     const int n_pos_tiles = (p.L + TP - 1) / TP;
     const long n_groups = (long)p.B * (p.Hq / shape.gp);
-    // persistent workgroups, spread evenly over the groups; never more than a group has tiles
+    // persistent workgroups, spread evenly over the groups; never more than a group has tiles, or parts of tiles
     const int per_cu = shape.nw > 4 ? 1 : 2;
     const long slots = per_cu * (long)compute_units();
     // the parts' sums lie where the dK/dV kernel puts its partials later
     const int part_keys = DOCS || shape.nw != 4 ? 0 : split_keys(p, hw, shape.gp, TP, slots, 2 * w.far_bytes / (2 * TP * shape.gp * D * sizeof(float)));
-    const int n_ranks = n_pos_tiles + split_tiles(n_pos_tiles, TP, p.n, part_keys).n;
+    const int n_pieces = query_pieces(p, TP, p.n, part_keys);  // of the group with the longest window
     int wpg = (int)(slots / n_groups);
-    wpg = wpg < 1 ? 1 : (wpg > n_ranks ? n_ranks : wpg);
+    wpg = wpg < 1 ? 1 : (wpg > n_pieces ? n_pieces : wpg);
     if (n_groups * wpg > 0x7FFFFFFFL) return SEPATTN_ERR_SHAPE;
     WorkShare share = {};
     long n_wg = n_groups * wpg;
     if (any_delta(hw)) {
-        share = share_out(p, hw, shape.gp, slots / p.B, n_ranks, [&](int n, bool) { return query_cost(p, TP, n); });
+        share = share_queries(p, hw, shape.gp, TP, (int)(slots / p.B), part_keys);
         n_wg = (long)p.B * share.first[share.n];
     }
     dim3 grid((unsigned)n_wg), block(64 * shape.nw);
@@ -656,7 +656,7 @@ int launch_bwd(const sepattn_params &p, const uint16_t *Q, const uint16_t *K, co
         constexpr bool PARTS = decltype(PARTS_)::value != 0;
         hipLaunchKernelGGL((dq_kernel<D, GP, DOCS, NW, PARTS>), grid, block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, Lws, farK, part_keys, wpg, hw, share);
         if constexpr (PARTS)
-            hipLaunchKernelGGL((dq_parts_kernel<D, GP, NW>), dim3((n_ranks - n_pos_tiles) * (D / 32), (unsigned)n_groups), block, 0, st, p, farK, dQ, part_keys, hw);
+            hipLaunchKernelGGL((dq_parts_kernel<D, GP, NW>), dim3((n_pieces - n_pos_tiles) * (D / 32), (unsigned)n_groups), block, 0, st, p, farK, dQ, part_keys, hw);
     };
     auto go4 = [&](auto GP_) {
         if constexpr (!DOCS) {

@@ -1008,7 +1008,7 @@ int launch_dkv(const sepattn_params &p, const HeadWin &hw, bool headwise, const 
     if (headwise) {
         const int G = p.Hq / p.Hkv;
         // pairs multiplied, and the start of a piece as 320 / G queries
-        share = share_out(p, hw, G, wpg * p.Hkv, kIntMax, [&](int n, bool all) {
+        share = share_out(p, hw, G, wpg * p.Hkv, [](int) { return kIntMax; }, [&](int n, bool all) {
             const double L = p.L, out = L - n;
             return all && list_all ? L * L / 2 : n * (L - n / 2.) + L * (fg.bk + 320. / G) + kSepShare * out * out / 2;
         });

@@ -600,8 +600,7 @@ int launch_fwd(const sepattn_params &p, const uint16_t *Q, const uint16_t *K, co
     WorkShare share = {};
     long n_wg = n_groups * wpg;
     if (any_delta(hw)) {
-        share = share_out(p, hw, shape.gp, (shape.nw > 4 ? 1 : D == 64 ? 3 : 2) * compute_units() / p.B, n_pos_tiles,
-                          [&](int n, bool) { return query_cost(p, TP, n); });
+        share = share_queries(p, hw, shape.gp, TP, (shape.nw > 4 ? 1 : D == 64 ? 3 : 2) * compute_units() / p.B, 0);
         n_wg = (long)p.B * share.first[share.n];
     }
     dim3 grid((unsigned)n_wg), block(64 * shape.nw);

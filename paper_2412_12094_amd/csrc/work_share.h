@@ -57,14 +57,15 @@ inline bool any_delta(const HeadWin &hw) {
 // holds about one in ten
 constexpr double kSepShare = 0.1;
 
-// Deals at most `slots` workgroups of a batch row to the groups of `heads` query heads each, between 1 and cap per group,
-// so that the largest cost(window, all) per workgroup is as small as it can be (bisection over that value; dealing by
+// Deals at most `slots` workgroups of a batch row to the groups of `heads` query heads each, between 1 and cap(window) per
+// group, so that the largest cost(window, all) per workgroup is as small as it can be (bisection over that value; dealing by
 // rounded shares left groups with one workgroup where two per group were to be had: 219 -> 274 us at 8 x 32
 // heads, L = 512).  More groups than slots get one each, the longest ones dispatched first.
-template <typename Cost>
-inline WorkShare share_out(const sepattn_params &p, const HeadWin &hw, int heads, int slots, int cap, Cost cost) {
+template <typename Cap, typename Cost>
+inline WorkShare share_out(const sepattn_params &p, const HeadWin &hw, int heads, int slots, Cap cap, Cost cost) {
     WorkShare w;
     w.n = p.Hq / heads;
+    int limit[kMaxHeadwise];
     double c[kMaxHeadwise], sum = 0.;
     for (int g = 0; g < w.n; ++g) {
         const int dmin = group_delta(hw, g * heads, heads);
@@ -75,16 +76,18 @@ inline WorkShare share_out(const sepattn_params &p, const HeadWin &hw, int heads
         int i = g;
         for (; i > 0 && c[i - 1] < x; --i) {
             c[i] = c[i - 1];
+            limit[i] = limit[i - 1];
             w.group[i] = w.group[i - 1];
             w.all[i] = w.all[i - 1];
         }
         c[i] = x;
+        limit[i] = cap(p.n - dmin);
         w.group[i] = g;
         w.all[i] = all;
     }
     auto wanted = [&](int i, double most) {
         const double k = c[i] / most + 0.999;
-        return k >= cap ? cap : (k < 1. ? 1 : (int)k);
+        return k >= limit[i] ? limit[i] : (k < 1. ? 1 : (int)k);
     };
     double lo = sum / (slots > 0 ? slots : 1) / 2, hi = c[0];  // hi: one workgroup each
     for (int it = 0; it < 12; ++it) {
@@ -154,6 +157,16 @@ inline int split_keys(const sepattn_params &p, const HeadWin &hw, int gp, int TP
     if (longest + start - sum / slots < kWorthSplitting) return 0;
     const SplitTiles s = split_tiles((p.L + TP - 1) / TP, TP, p.n, keys);
     return (size_t)p.B * (p.Hq / gp) * s.most <= room ? keys : 0;
+}
+
+// pieces of work of a forward or dQ group whose largest window is `n`: its query tiles, split ones twice
+inline int query_pieces(const sepattn_params &p, int TP, int n, int part_keys) {
+    const int tiles = (p.L + TP - 1) / TP;
+    return tiles + split_tiles(tiles, TP, n, part_keys).n;
+}
+// the workgroups of a head-wise forward or dQ: no group gets more than it has pieces
+inline WorkShare share_queries(const sepattn_params &p, const HeadWin &hw, int gp, int TP, int slots, int part_keys) {
+    return share_out(p, hw, gp, slots, [&](int n) { return query_pieces(p, TP, n, part_keys); }, [&](int n, bool) { return query_cost(p, TP, n); });
 }
 
 }  // namespace sepattn
