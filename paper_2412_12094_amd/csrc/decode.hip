@@ -317,7 +317,8 @@ size_t decode_workspace(const sepkv_params &p) {
     int nsplit;
     size_t arrival = 0;
     if (decode_wide_applicable(p)) {  // one size for calls with and without positions
-        const int a = decode_wide_shape(p, false).nsplit, b = decode_wide_shape(p, true).nsplit;
+        const int units = compute_units();  // asks the runtime for the current device: once
+        const int a = decode_wide_shape(p, false, units).nsplit, b = decode_wide_shape(p, true, units).nsplit;
         nsplit = a > b ? a : b;
         if (nsplit > 1) arrival = decode_wide_arrival_bytes(p);
     } else {
@@ -354,7 +355,7 @@ int launch_decode(const sepkv_params &p, const void *q, const void *Kc, const vo
         const bool wide = decode_wide_applicable(p);
         DecodeWideShape shape = {1, 0, false};
         if (wide) {
-            shape = decode_wide_shape(p, rope != nullptr);
+            shape = decode_wide_shape(p, rope != nullptr, compute_units());
             shape.add = shape.add && !being_captured(st);
         }
         const int nsplit = wide ? shape.nsplit : decode_mfma_nsplit(p);

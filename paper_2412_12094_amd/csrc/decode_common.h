@@ -61,7 +61,7 @@ struct DecodeWideShape {
     int nsplit, nw;  // slices per (sequence, KV head), waves per workgroup
     bool add;        // the slices are added by decode_wide_kernel itself, not by a merge launch
 };
-DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope);
+DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope, int units);  // units: compute_units()
 // where decode_wide_kernel has several slices the workspace begins with one word per (sequence, KV head), in which they are
 // counted
 __host__ __device__ inline size_t decode_wide_arrival_bytes(const sepkv_params &p) { return align_up((size_t)p.S * p.Hkv * sizeof(uint64_t), 256); }

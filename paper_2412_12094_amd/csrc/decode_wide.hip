@@ -465,8 +465,8 @@ bool decode_wide_applicable(const sepkv_params &p) {
 //     3.6 / 4.8 against 4.2 / 5.1; of eight blocks, which four waves take in two rounds, 0.14 us slower), and where more workgroups wait than the compute units hold at once: half the LDS, so
 //     that two (d = 64: four) share a compute unit and one's start and merge overlap another's stream (64 sequences x
 //     8 heads of 100 entries 8.9 -> 5.4, of 1000 entries 40.7 -> 39.2).
-DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope) {
-    const long pairs = (long)p.S * p.Hkv, fit = compute_units() / pairs;
+DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope, int units) {
+    const long pairs = (long)p.S * p.Hkv, fit = units / pairs;
     const int nb = (p.c + kDwRows - 1) / kDwRows, d64 = p.d == 64 ? 2 : 1, row = p.Hq / p.Hkv * p.d;
     const int want = d64 == 2 && nb > 32 ? 8 : 4;  // blocks per slice
     const int most = nb <= (d64 == 1 ? 80 : 128) ? 8 : nb <= (pairs > 4 ? 400 : 200) * d64 ? 16 : nb <= 800 * d64 ? 32 : 64;
@@ -478,7 +478,7 @@ DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope) {
         const int pays = (rope ? 9 * d64 : d64 == 1 ? 13 : 22) + (ns == 2 ? 8 : ns == 3 ? 3 : 0) * d64;
         if (nb - per >= pays) return {ns, d64 == 1 || per <= 4 ? 4 : 8, ns <= 16 && row <= 1024 && ns * row <= 8192};
     }
-    return {1, nb <= 4 || pairs > (long)compute_units() * d64 ? 4 : 8, false};
+    return {1, nb <= 4 || pairs > (long)units * d64 ? 4 : 8, false};
 }
 
 // What each slice of one launch adds to its word: a number in the upper 56 bits that no two launches of a process share (those of
