@@ -64,7 +64,7 @@ inline int dkv_workgroups_per_head(const sepattn_params &p, int kw) {
 // workgroups it sets the time of the kernel.  Split, every key's sums pass through fp32 partials and the combine
 // kernel.  Not where the far work keeps the workgroups busy as long (a unit shorter than three times their mean work: 8/1 heads,
 // 3 x L = 2648, d = 64, n = 18, dK/dV 28.0 us, with four parts 30.2); else the largest number that divides the heads, gives no
-// workgroup two parts, leaves a part four steps and spares eight: 8/2 heads, d = 128, L = 600, n = 96 (20 steps) dK/dV and combine 22.3 + 4.5 -> 13.6 + 5.3 us.
+// workgroup two parts, leaves a part four steps and spares eight: 8/2 heads, d = 128, L = 600, n = 96 (16 steps) dK/dV and combine 22.3 + 4.5 -> 13.6 + 5.3 us.
 // (any_n: for the workspace, whose size does not depend on the window: the largest split of any window.)
 inline int band_split(const sepattn_params &p, int wpg, int kw, bool any_n = false) {
     const int G = p.Hq / p.Hkv, steps = any_n ? 1 << 20 : ((p.n < p.L ? p.n : p.L) + 30) / 32 + 1;

@@ -365,11 +365,11 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         const int n_blocks = (st_G - 1) * st_P + nbh;            // steps of the piece
         const int tiles_per_head = FAR ? 0 : n_qt;
 
-        // tile tt -> LDS buffer tt%4: wave w fills rows (LOADS*w + u)*RPL .. +RPL-1 with one wave-wide
-        // direct load per tensor; a lane owns physical chunk lane%CH of its row and fetches the
-        // logical chunk the permutation maps there.  Rows past the sequence end are clamped (they are
-        // masked by the [lo, hi] test: hi <= L-1).  Tiles are issued in order; (iss_g, iss_qt) is the
-        // (head, query tile) of the next one.
+        // tile tt -> LDS buffer tt%4: the loading wave of key block kbw fills rows (LOADS*kbw + u)*RPL ..
+        // +RPL-1 with one wave-wide direct load per tensor; a lane owns physical chunk lane%CH of its row and
+        // fetches the logical chunk the permutation maps there.  Rows past the sequence end are clamped (they
+        // are masked by the [lo, hi] test: hi <= L-1).  Tiles are issued in order, head by head: the next one
+        // is query tile iss_qt of the head whose rows begin at iss_head (iss_g: the head of the first).
         int iss_tt = 0, iss_g = item0 / n_qt, iss_qt = item0 % n_qt;
         if (PARTS && !FAR) iss_g = unit % split * Gs;  // the part's first head
         size_t iss_head = (((long)b * p.Hq + kv * G + iss_g) * (long)p.L) * ROWB;  // byte offset of the head's rows in Q and dO
@@ -406,8 +406,9 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
                 iss_head += (size_t)p.L * ROWB;
             }
         };
-        // wait until at most the loads of the n_out newest tiles are still in flight (loads complete in
-        // the order they were issued; every wave issues 2*LOADS + 1 loads per tile)
+        // wait until at most the wave's loads of the n_out newest tiles are still in flight: loads complete in the
+        // order they were issued, and a wave of the loading role issues LW = 2*LOADS + RVL of them per tile.  The
+        // other waves issue none (at the start of a piece they wait for their resident rows here).
         auto wait_tiles = [&](int n_out) __attribute__((always_inline)) {
             constexpr int LW = 2 * LOADS + RVL;
             static_assert(LW == 6 || LW == 10, "wait counts below are written for 6 or 10 loads per wave and tile");
