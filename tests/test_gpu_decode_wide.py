@@ -1,6 +1,7 @@
 """The eight- and four-wave decode kernel at the edges of its dispatch, against the oracle: one block of
 entries, one more than a round of its waves, several slices, more workgroups than compute units, and the
 smallest and largest head groups.  Needs an MI355X."""
+import ctypes
 import math
 
 import numpy as np
@@ -60,31 +61,43 @@ def test_decode_dispatch_edges(S, Hq, Hkv, d, a, s, w, c, rope):
     assert np.abs(lse.cpu().numpy() - lref).max() <= (1e-2 if rope else 2e-3)
 
 
-# slices and waves per workgroup: the edges of decode_wide_shape's rules on a chip of 256 compute units
+# slices and waves per workgroup: the edges of decode_wide_shape's rules on a chip of 256 compute units.  `slices`: without and
+# with ROPE
 SHAPE_CASES = [
-    (1, 8, 2, 128, 4, 100, 60, 256),    # eight blocks: one slice of eight waves
-    (1, 8, 2, 128, 4, 100, 60, 385),    # 13 blocks: one slice of eight waves without ROPE, four of four with
-    (4, 32, 8, 128, 4, 64, 256, 800),   # 25 blocks in seven slices, the last of one block
-    (2, 8, 1, 128, 0, 1100, 256, 2600), # 82 blocks in sixteen slices
-    (9, 56, 8, 128, 4, 500, 100, 1600), # 72 pairs of seven heads: three slices
-    (16, 128, 8, 128, 4, 200, 100, 800),# 128 pairs of sixteen heads, 25 blocks: one slice
-    (16, 32, 8, 128, 4, 200, 100, 1100),# 128 pairs, 35 blocks: one slice without ROPE, two with
-    (16, 128, 8, 128, 4, 800, 100, 1400),# 128 pairs of sixteen heads, 44 blocks: two slices, merge launch
-    (2, 12, 12, 64, 3, 64, 256, 800),   # d = 64: one slice without ROPE, seven of four waves with
-    (4, 8, 8, 64, 4, 900, 256, 2300),   # nine blocks per slice: eight waves
-    (2, 14, 2, 128, 4, 500, 256, 1400), # seven heads: eight slices added in the kernel
-    (2, 14, 2, 128, 4, 1100, 256, 2600),# seven heads: sixteen slices, merge launch
-    (1, 4, 2, 64, 4, 2500, 256, 5200),  # d = 64, 163 blocks: sixteen slices, two fetches of records
-    (1, 2, 1, 128, 4, 4000, 256, 6500), # 204 blocks, one pair: thirty-two slices, merge launch
-    (1, 5, 5, 128, 4, 4000, 256, 6500), # 204 blocks, five pairs: sixteen
-    (1, 2, 1, 64, 4, 30000, 256, 51300),# 1604 blocks: sixty-four
-    (33, 8, 8, 64, 4, 500, 100, 1100),  # 264 pairs at d = 64: one slice of eight waves
+    (1, 8, 2, 128, 4, 50, 30, 128, (1, 1)),         # four blocks: four waves
+    (1, 8, 2, 128, 4, 50, 30, 129, (1, 1)),         # five: eight waves
+    (1, 8, 2, 128, 4, 100, 60, 256, (1, 1)),        # eight blocks: one slice of eight waves
+    (1, 8, 2, 128, 4, 100, 60, 385, (1, 4)),        # 13 blocks: one slice of eight waves without ROPE, four of four with
+    (4, 32, 8, 128, 4, 64, 256, 800, (7, 7)),       # 25 blocks in seven slices, the last of one block
+    (2, 8, 1, 128, 0, 1100, 256, 2600, (16, 16)),   # 82 blocks in sixteen slices
+    (9, 56, 8, 128, 4, 500, 100, 1600, (3, 3)),     # 72 pairs of seven heads: three slices
+    (16, 128, 8, 128, 4, 200, 100, 800, (1, 1)),    # 128 pairs of sixteen heads, 25 blocks: one slice
+    (16, 32, 8, 128, 4, 200, 100, 1100, (1, 2)),    # 128 pairs, 35 blocks: one slice without ROPE, two with
+    (16, 32, 8, 128, 4, 800, 100, 1312, (1, 2)),    # 41 blocks: 20 spared, one without
+    (16, 32, 8, 128, 4, 800, 100, 1340, (2, 2)),    # 42 blocks: 21 spared, two slices without ROPE too, added in the kernel
+    (16, 128, 8, 128, 4, 800, 100, 1400, (2, 2)),   # 128 pairs of sixteen heads, 44 blocks: two slices, merge launch
+    (2, 12, 12, 64, 3, 64, 256, 800, (1, 7)),       # d = 64: one slice without ROPE, seven of four waves with
+    (4, 8, 8, 64, 4, 900, 256, 2300, (8, 8)),       # nine blocks per slice: eight waves
+    (2, 14, 2, 128, 4, 500, 256, 1400, (8, 8)),     # seven heads: eight slices added in the kernel
+    (2, 14, 2, 128, 4, 1100, 256, 2600, (16, 16)),  # seven heads: sixteen slices, merge launch
+    (1, 4, 2, 64, 4, 2500, 256, 5200, (16, 16)),    # d = 64, 163 blocks: sixteen slices, two fetches of records
+    (1, 2, 1, 128, 4, 4000, 256, 6500, (32, 32)),   # 204 blocks, one pair: thirty-two slices, merge launch
+    (1, 5, 5, 128, 4, 4000, 256, 6500, (16, 16)),   # 204 blocks, five pairs: sixteen
+    (1, 2, 1, 64, 4, 30000, 256, 51300, (64, 64)),  # 1604 blocks: sixty-four
+    (33, 8, 8, 64, 4, 500, 100, 1100, (1, 1)),      # 264 pairs at d = 64: one slice of eight waves
 ]
 
 
 @pytest.mark.parametrize("rope", [False, True])
-@pytest.mark.parametrize("S,Hq,Hkv,d,a,s,w,c", SHAPE_CASES)
-def test_decode_slices_and_waves(S, Hq, Hkv, d, a, s, w, c, rope):
+@pytest.mark.parametrize("S,Hq,Hkv,d,a,s,w,c,slices", SHAPE_CASES)
+def test_decode_slices_and_waves(S, Hq, Hkv, d, a, s, w, c, slices, rope):
+    import paper_2412_12094_amd as sp
+
+    # the workspace holds the records of the larger number of slices, and words to count them if there are several
+    up = lambda x: -(-x // 256) * 256
+    p = sp.binding.SepkvParams(S, Hq, Hkv, d, a, s, w, c, 1.0, 0)
+    words = up(S * Hkv * 8) if max(slices) > 1 else 0
+    assert sp.load().sepattn_decode_workspace_bytes(ctypes.byref(p)) == words + up(S * Hq * max(slices) * (d + 2) * 4)
     test_decode_dispatch_edges(S, Hq, Hkv, d, a, s, w, c, rope)
 
 
