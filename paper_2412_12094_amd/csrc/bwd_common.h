@@ -62,19 +62,30 @@ inline int dkv_workgroups_per_head(const sepattn_params &p, int kw) {
 // Among how many workgroups a band unit (32 KW keys and their windows, all query heads of the KV head) is split, by query
 // heads.  A unit is a chain of G ((n + 30) / 32 + 1) steps of 0.7 us on one workgroup; where there are fewer units than
 // workgroups it sets the time of the kernel.  Split, every key's sums pass through fp32 partials and the combine
-// kernel.  Not where the far work keeps the workgroups busy as long (a unit shorter than three times their mean work: 8/1 heads,
-// 3 x L = 2648, d = 64, n = 18, dK/dV 28.0 us, with four parts 30.2); else the largest number that divides the heads, gives no
-// workgroup two parts, leaves a part four steps and spares eight: 8/2 heads, d = 128, L = 600, n = 96 (16 steps) dK/dV and combine 22.3 + 4.5 -> 13.6 + 5.3 us.
+// kernel, and the parts, with the slices of far work, which are cut as short as they are (see min_slice), share the compute units.
+// Only units longer than three times the workgroups' mean work are split, into a number that divides the heads, gives no
+// workgroup two parts, leaves a part four steps and spares eight: the number for which the steps of a part, 12 for each part and 6
+// for each far slice that a compute unit gets, and 3 for the combine kernel where there is a split, are fewest together.
+// Over 1760 calls with grouped heads and room for parts, 668 are split; of these 17 take more than 2 % longer than whole (at most 11 %), and
+// the backward of all takes 0.87 of the time.  By the largest divisor alone it was 65 of 703, at most 44 %.  Backward in us, whole / 2 / 4 / 8
+// parts, and what is chosen: 8/1 heads, d = 64, L = 3803, n = 32 45.3 / 47.8 / 65.2 / 54.3 (whole); L = 3662, n = 36 49.2 / 44.8 / 56.4 / 55.7
+// (two); L = 527, n = 32 32.3 / 26.1 / 25.4 / 26.8 (four); d = 128, L = 2921, n = 19 51.7 / 52.0 / 64.8 / 55.4 (two); 32/8 heads, d = 128, L = 869,
+// n = 86 43.7 / 47.6 / 54.7 (whole); 8/2 heads, L = 600, n = 96 dK/dV and combine 22.3 + 4.5 whole, 13.6 + 5.3 in four.
 // (any_n: for the workspace, whose size does not depend on the window: the largest split of any window.)
 inline int band_split(const sepattn_params &p, int wpg, int kw, bool any_n = false) {
     const int G = p.Hq / p.Hkv, steps = any_n ? 1 << 20 : ((p.n < p.L ? p.n : p.L) + 30) / 32 + 1;
     const long units = ((long)p.L + 32 * kw - 1) / (32 * kw);
     // far work in steps of 32 query rows, from the share of separators that work_share.h assumes
     const double out = any_n || p.n >= p.L ? 0. : p.L - p.n, far = (p.a + kSepShare * out / 2) * out / (1024. * kw) * G;
-    int split = 1;
     if (3. * (far + (double)units * G * steps) > (double)wpg * G * steps) return 1;
+    const double share = (double)p.B * p.Hkv / compute_units();  // of the workgroups of a (batch, KV head), per compute unit
+    auto cost = [&](int s) {
+        const long part = (long)G / s * steps, slice = part < 4 ? 4 : (part > 16 ? 16 : part), left = wpg - units * s;
+        return part + (12. * units * s + 6. * (far / slice < left ? far / slice : left)) * share + (s > 1 ? 3. : 0.);
+    };
+    int split = 1;
     for (int s = 2; s <= G; ++s)
-        if (G % s == 0 && units * s <= wpg && (long)G / s * steps >= 4 && (long)(G - G / s) * steps >= 8) split = s;
+        if (G % s == 0 && units * s <= wpg && (long)G / s * steps >= 4 && (long)(G - G / s) * steps >= 8 && cost(s) < cost(split)) split = s;
     return split;
 }
 __host__ __device__ inline FarGeom far_geom(const sepattn_params &p, int wpg, int kw, int split = 1) {

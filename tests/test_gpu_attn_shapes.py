@@ -108,8 +108,10 @@ def test_bf16_waves_whose_streams_end_apart(B, Hq, Hkv, L, d, a, n, p):
     (1, 8, 2, 600, 64, 4, 96, 0.1),
     (1, 7, 1, 130, 64, 2, 100, 0.1),    # seven parts
     (2, 12, 2, 333, 128, 0, 64, 0.0),   # three parts of two heads; nothing on the list
-    (4, 32, 8, 256, 128, 4, 128, 0.1),  # as many parts as workgroups
-    (4, 32, 8, 257, 128, 4, 128, 0.1),  # one key more: two parts
+    (4, 32, 8, 256, 128, 4, 128, 0.1),  # two parts of two heads
+    (4, 32, 8, 257, 128, 4, 128, 0.1),  # one key more: whole units
+    (21, 4, 1, 384, 128, 4, 360, 0.1),  # as many parts as workgroups
+    (21, 4, 1, 385, 128, 4, 360, 0.1),  # one key more: two parts
     (1, 8, 1, 8200, 128, 4, 2000, 0.05),  # eight-wave workgroups
 ])
 def test_bf16_band_units_in_parts(B, Hq, Hkv, L, d, a, n, p):

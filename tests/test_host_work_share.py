@@ -1,4 +1,5 @@
-"""How the workgroups of a head-wise call are dealt to its groups of heads (csrc/work_share.h), in a host build, no GPU."""
+"""How the workgroups of a head-wise call are dealt to its groups of heads (csrc/work_share.h), and into how many parts the band units
+of the backward are split (csrc/bwd_common.h), in a host build, no GPU."""
 import shutil
 import subprocess
 
@@ -32,17 +33,42 @@ int main(int argc, char **argv) {
 """
 
 
-@pytest.fixture(scope="module")
-def dealt(tmp_path_factory):
+PARTS_PROGRAM = r"""
+#include <stdio.h>
+#include <stdlib.h>
+#include "bwd_common.h"
+using namespace sepattn;
+int sepattn::compute_units() { return 256; }
+// B Hq Hkv L d a n: parts of a band unit, workgroups per (batch, KV head), parts that the workspace has room for
+int main(int, char **argv) {
+    auto arg = [&](int i) { return atoi(argv[i]); };
+    sepattn_params p = {};
+    p.B = arg(1), p.Hq = arg(2), p.Hkv = arg(3), p.L = arg(4), p.d = arg(5), p.a = arg(6), p.n = arg(7);
+    const int wpg = dkv_workgroups_per_head(p, 2);
+    printf("%d %d %d\n", band_split(p, wpg, 2), wpg, band_split(p, wpg, 2, true));
+}
+"""
+
+
+def host_program(d, source):
     if shutil.which("hipcc") is None:
         pytest.skip("hipcc not available")
-    d = tmp_path_factory.mktemp("work_share")
-    (d / "share.hip").write_text(PROGRAM)
+    (d / "share.hip").write_text(source)
     cmd = ["hipcc", *build.FLAGS, "--offload-host-only", "-c", str(d / "share.hip"), "-o", str(d / "share.o")]
     subprocess.run(cmd, check=True, capture_output=True)
     subprocess.run(["g++", str(d / "share.o"), "-o", str(d / "share")], check=True)
     return lambda *args: [list(map(int, line.split())) for line in
                           subprocess.run([str(d / "share"), *map(str, args)], check=True, capture_output=True, text=True).stdout.splitlines()]
+
+
+@pytest.fixture(scope="module")
+def dealt(tmp_path_factory):
+    return host_program(tmp_path_factory.mktemp("work_share"), PROGRAM)
+
+
+@pytest.fixture(scope="module")
+def parts(tmp_path_factory):
+    return host_program(tmp_path_factory.mktemp("band_parts"), PARTS_PROGRAM)
 
 
 @pytest.mark.parametrize("L,d,gp,TP,slots,windows,is_split", [
@@ -65,3 +91,22 @@ def test_no_group_gets_more_workgroups_than_it_has_pieces(dealt, L, d, gp, TP, s
     # what one group cannot use goes to the others
     if slots >= sum(pieces for _, _, pieces in groups):
         assert all(count == pieces for _, count, pieces in groups)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,d,a,n,want", [
+    (1, 8, 2, 600, 128, 4, 96, 4),     # few units, nothing beside them: as many parts as there are heads
+    (1, 8, 1, 527, 64, 8, 32, 4),      # a part has four steps at least
+    (1, 28, 4, 600, 128, 4, 96, 7),
+    (1, 8, 1, 3803, 64, 0, 32, 1),     # far work, whose slices get as short as the parts: four parts took 1.44 times as long
+    (2, 8, 1, 2820, 64, 8, 58, 2),     # 1.05 times
+    (1, 8, 1, 2921, 128, 3, 19, 2),    # 1.25 times
+    (1, 32, 8, 869, 128, 3, 86, 1),    # more parts than compute units: four took 1.25 times as long
+    (1, 8, 2, 600, 128, 4, 600, 4),    # the whole sequence in the window: no far work
+    (21, 4, 1, 384, 128, 4, 360, 4),   # as many parts as workgroups
+    (21, 4, 1, 385, 128, 4, 360, 2),   # one key more
+    (1, 8, 8, 600, 128, 4, 96, 1),     # one head per KV head
+])
+def test_band_units_are_split_where_the_parts_have_room(parts, B, Hq, Hkv, L, d, a, n, want):
+    ((split, wpg, room),) = parts(B, Hq, Hkv, L, d, a, n)
+    assert split == want and split <= room
+    assert split == 1 or -(-L // 64) * split <= wpg
