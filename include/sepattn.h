@@ -107,6 +107,10 @@ size_t sepattn_compact_workspace_bytes(int B, int L);
 int sepattn_compact_indices(const uint8_t *is_sep, int B, int L, int32_t *sep_idx, int cap,
                             int32_t *sep_count, int32_t *sep_prefix, void *workspace,
                             size_t workspace_bytes, void *stream);
+/* The same, for a list that holds nothing yet: entries at and beyond min(count, cap) are set to `fill` in the same launch. */
+int sepattn_compact_indices_filled(const uint8_t *is_sep, int B, int L, int32_t *sep_idx, int cap,
+                                   int32_t *sep_count, int32_t *sep_prefix, int32_t fill, void *workspace,
+                                   size_t workspace_bytes, void *stream);
 
 /* Marking and compaction in one call (Sec. 4.1 "Parameter Setting" and Eq. 2): exactly the outputs
  * of sepattn_mark_separators followed by sepattn_compact_indices, arguments as there (is_sep is an
@@ -117,6 +121,11 @@ int sepattn_compact_indices(const uint8_t *is_sep, int B, int L, int32_t *sep_id
 int sepattn_mark_compact(const int32_t *token_ids, int B, int L, const int32_t *sep_ids, int n_sep,
                          uint8_t *is_sep, int32_t *sep_idx, int cap, int32_t *sep_count,
                          int32_t *sep_prefix, void *workspace, size_t workspace_bytes, void *stream);
+/* The same with the list's other entries set to `fill`, as sepattn_compact_indices_filled. */
+int sepattn_mark_compact_filled(const int32_t *token_ids, int B, int L, const int32_t *sep_ids, int n_sep,
+                                uint8_t *is_sep, int32_t *sep_idx, int cap, int32_t *sep_count,
+                                int32_t *sep_prefix, int32_t fill, void *workspace, size_t workspace_bytes,
+                                void *stream);
 
 /* ------------------------------------------------------------------------------------------
  * Training / prefill attention (Eq. 1 with the mask of Eq. 2).
@@ -368,6 +377,12 @@ int sepkv_fill_from_prefill(const sepkv_params *p, int L, int nw, const void *K,
                             const uint8_t *is_sep, const int32_t *sep_idx, int cap,
                             const int32_t *sep_prefix, void *Kc, void *Vc, uint8_t *win_is_sep,
                             int32_t *sizes, void *stream);
+/* The same, for buffers that hold nothing yet: slots of Kc, Vc and entries of win_is_sep beyond the new sizes are set to 0
+ * in the same launch. */
+int sepkv_fill_from_prefill_zeroed(const sepkv_params *p, int L, int nw, const void *K, const void *V,
+                                   const uint8_t *is_sep, const int32_t *sep_idx, int cap,
+                                   const int32_t *sep_prefix, void *Kc, void *Vc, uint8_t *win_is_sep,
+                                   int32_t *sizes, void *stream);
 
 /* ------------------------------------------------------------------------------------------
  * Measurement hooks (not part of the method).  A benchmark that times whole steps can also report one

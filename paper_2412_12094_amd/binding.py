@@ -33,7 +33,9 @@ EXPORTS = (
     "sepattn_mark_interval",
     "sepattn_compact_workspace_bytes",
     "sepattn_compact_indices",
+    "sepattn_compact_indices_filled",
     "sepattn_mark_compact",
+    "sepattn_mark_compact_filled",
     "sepattn_forward_workspace_bytes",
     "sepattn_forward",
     "sepattn_forward_headwise",
@@ -51,6 +53,7 @@ EXPORTS = (
     "sepkv_evict_workspace_bytes",
     "sepkv_evict_window",
     "sepkv_fill_from_prefill",
+    "sepkv_fill_from_prefill_zeroed",
     "sepkv_rope_table",
     "sepattn_decode_rope",
     "sepkv_append",
@@ -106,8 +109,12 @@ def load(path: Optional[str] = None):
     lib.sepattn_compact_workspace_bytes.argtypes = [ci, ci]
     lib.sepattn_compact_indices.restype = ci
     lib.sepattn_compact_indices.argtypes = [vp, ci, ci, vp, ci, vp, vp, vp, sz, vp]
+    lib.sepattn_compact_indices_filled.restype = ci
+    lib.sepattn_compact_indices_filled.argtypes = [vp, ci, ci, vp, ci, vp, vp, ctypes.c_int32, vp, sz, vp]
     lib.sepattn_mark_compact.restype = ci
     lib.sepattn_mark_compact.argtypes = [vp, ci, ci, vp, ci, vp, vp, ci, vp, vp, vp, sz, vp]
+    lib.sepattn_mark_compact_filled.restype = ci
+    lib.sepattn_mark_compact_filled.argtypes = [vp, ci, ci, vp, ci, vp, vp, ci, vp, vp, ctypes.c_int32, vp, sz, vp]
     pp = ctypes.POINTER(SepattnParams)
     lib.sepattn_forward_workspace_bytes.restype = sz
     lib.sepattn_forward_workspace_bytes.argtypes = [pp]
@@ -144,6 +151,8 @@ def load(path: Optional[str] = None):
     lib.sepkv_evict_window.argtypes = [kp] + [vp] * 5 + [sz, vp]
     lib.sepkv_fill_from_prefill.restype = ci
     lib.sepkv_fill_from_prefill.argtypes = [kp, ci, ci, vp, vp, vp, vp, ci, vp, vp, vp, vp, vp, vp]
+    lib.sepkv_fill_from_prefill_zeroed.restype = ci
+    lib.sepkv_fill_from_prefill_zeroed.argtypes = [kp, ci, ci, vp, vp, vp, vp, ci, vp, vp, vp, vp, vp, vp]
     lib.sepkv_rope_table.restype = ci
     lib.sepkv_rope_table.argtypes = [ci, ci, ctypes.c_double, vp, vp]
     lib.sepattn_decode_rope.restype = ci

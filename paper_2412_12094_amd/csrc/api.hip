@@ -234,9 +234,8 @@ size_t sepattn_compact_workspace_bytes(int B, int L) {
     return align_up((size_t)B * n_chunks * sizeof(int32_t), 256);
 }
 
-int sepattn_compact_indices(const uint8_t *is_sep, int B, int L, int32_t *sep_idx, int cap,
-                            int32_t *sep_count, int32_t *sep_prefix, void *workspace,
-                            size_t workspace_bytes, void *stream) {
+static int compact_indices(const uint8_t *is_sep, int B, int L, int32_t *sep_idx, int cap, int32_t *sep_count,
+                           int32_t *sep_prefix, const int32_t *fill, void *workspace, size_t workspace_bytes, void *stream) {
     if (!is_sep || !sep_idx || !sep_count) return SEPATTN_ERR_NULL;
     if (B <= 0 || L <= 0 || B > 65535) return SEPATTN_ERR_SHAPE;
     if (cap < 1) return SEPATTN_ERR_CAPACITY;
@@ -244,12 +243,24 @@ int sepattn_compact_indices(const uint8_t *is_sep, int B, int L, int32_t *sep_id
         return SEPATTN_ERR_WORKSPACE;
     discard_stale_hip_error();
     return launch_compact(is_sep, B, L, sep_idx, cap, sep_count, sep_prefix,
-                          static_cast<int32_t *>(workspace), static_cast<hipStream_t>(stream));
+                          static_cast<int32_t *>(workspace), fill, static_cast<hipStream_t>(stream));
 }
 
-int sepattn_mark_compact(const int32_t *token_ids, int B, int L, const int32_t *sep_ids, int n_sep,
-                         uint8_t *is_sep, int32_t *sep_idx, int cap, int32_t *sep_count,
-                         int32_t *sep_prefix, void *workspace, size_t workspace_bytes, void *stream) {
+int sepattn_compact_indices(const uint8_t *is_sep, int B, int L, int32_t *sep_idx, int cap,
+                            int32_t *sep_count, int32_t *sep_prefix, void *workspace,
+                            size_t workspace_bytes, void *stream) {
+    return compact_indices(is_sep, B, L, sep_idx, cap, sep_count, sep_prefix, nullptr, workspace, workspace_bytes, stream);
+}
+
+int sepattn_compact_indices_filled(const uint8_t *is_sep, int B, int L, int32_t *sep_idx, int cap,
+                                   int32_t *sep_count, int32_t *sep_prefix, int32_t fill, void *workspace,
+                                   size_t workspace_bytes, void *stream) {
+    return compact_indices(is_sep, B, L, sep_idx, cap, sep_count, sep_prefix, &fill, workspace, workspace_bytes, stream);
+}
+
+static int mark_compact(const int32_t *token_ids, int B, int L, const int32_t *sep_ids, int n_sep, uint8_t *is_sep,
+                        int32_t *sep_idx, int cap, int32_t *sep_count, int32_t *sep_prefix, const int32_t *fill,
+                        void *workspace, size_t workspace_bytes, void *stream) {
     if (!token_ids || !sep_ids || !is_sep || !sep_idx || !sep_count) return SEPATTN_ERR_NULL;
     if (B <= 0 || L <= 0 || B > 65535) return SEPATTN_ERR_SHAPE;
     if (n_sep < 1 || n_sep > SEPATTN_MAX_SEP_IDS) return SEPATTN_ERR_PARAM;
@@ -262,7 +273,22 @@ int sepattn_mark_compact(const int32_t *token_ids, int B, int L, const int32_t *
     for (int k = 0; k < SEPATTN_MAX_SEP_IDS; ++k) set.ids[k] = k < n_sep ? sep_ids[k] : sep_ids[0];
     discard_stale_hip_error();
     return launch_mark_compact(token_ids, B, L, set, is_sep, sep_idx, cap, sep_count, sep_prefix,
-                               static_cast<int32_t *>(workspace), static_cast<hipStream_t>(stream));
+                               static_cast<int32_t *>(workspace), fill, static_cast<hipStream_t>(stream));
+}
+
+int sepattn_mark_compact(const int32_t *token_ids, int B, int L, const int32_t *sep_ids, int n_sep,
+                         uint8_t *is_sep, int32_t *sep_idx, int cap, int32_t *sep_count,
+                         int32_t *sep_prefix, void *workspace, size_t workspace_bytes, void *stream) {
+    return mark_compact(token_ids, B, L, sep_ids, n_sep, is_sep, sep_idx, cap, sep_count, sep_prefix, nullptr, workspace,
+                        workspace_bytes, stream);
+}
+
+int sepattn_mark_compact_filled(const int32_t *token_ids, int B, int L, const int32_t *sep_ids, int n_sep,
+                                uint8_t *is_sep, int32_t *sep_idx, int cap, int32_t *sep_count,
+                                int32_t *sep_prefix, int32_t fill, void *workspace, size_t workspace_bytes,
+                                void *stream) {
+    return mark_compact(token_ids, B, L, sep_ids, n_sep, is_sep, sep_idx, cap, sep_count, sep_prefix, &fill, workspace,
+                        workspace_bytes, stream);
 }
 
 size_t sepattn_forward_workspace_bytes(const sepattn_params *p) {
@@ -498,9 +524,9 @@ int sepkv_evict_window(const sepkv_params *p, void *Kc, void *Vc, const uint8_t 
     return launch_evict(*p, Kc, Vc, win_is_sep, sizes, ws, static_cast<hipStream_t>(stream));
 }
 
-int sepkv_fill_from_prefill(const sepkv_params *p, int L, int nw, const void *K, const void *V,
-                            const uint8_t *is_sep, const int32_t *sep_idx, int cap, const int32_t *sep_prefix,
-                            void *Kc, void *Vc, uint8_t *win_is_sep, int32_t *sizes, void *stream) {
+static int fill_from_prefill(const sepkv_params *p, int L, int nw, const void *K, const void *V, const uint8_t *is_sep,
+                             const int32_t *sep_idx, int cap, const int32_t *sep_prefix, void *Kc, void *Vc,
+                             uint8_t *win_is_sep, int32_t *sizes, bool zero_rest, void *stream) {
     int rc = check_kv(p);
     if (rc != SEPATTN_OK) return rc;
     if (!K || !V || !is_sep || !sep_idx || !sep_prefix || !Kc || !Vc || !win_is_sep || !sizes) return SEPATTN_ERR_NULL;
@@ -510,8 +536,21 @@ int sepkv_fill_from_prefill(const sepkv_params *p, int L, int nw, const void *K,
     if (nw < 0 || nw > p->c - p->a - p->s || nw > L - n_init) return SEPATTN_ERR_PARAM;
     if (!aligned(K, 16) || !aligned(V, 16) || !aligned(Kc, 16) || !aligned(Vc, 16)) return SEPATTN_ERR_PARAM;
     discard_stale_hip_error();
-    return launch_cache_fill(*p, L, nw, K, V, is_sep, sep_idx, cap, sep_prefix, Kc, Vc, win_is_sep, sizes,
+    return launch_cache_fill(*p, L, nw, K, V, is_sep, sep_idx, cap, sep_prefix, Kc, Vc, win_is_sep, sizes, zero_rest,
                              static_cast<hipStream_t>(stream));
+}
+
+int sepkv_fill_from_prefill(const sepkv_params *p, int L, int nw, const void *K, const void *V,
+                            const uint8_t *is_sep, const int32_t *sep_idx, int cap, const int32_t *sep_prefix,
+                            void *Kc, void *Vc, uint8_t *win_is_sep, int32_t *sizes, void *stream) {
+    return fill_from_prefill(p, L, nw, K, V, is_sep, sep_idx, cap, sep_prefix, Kc, Vc, win_is_sep, sizes, false, stream);
+}
+
+int sepkv_fill_from_prefill_zeroed(const sepkv_params *p, int L, int nw, const void *K, const void *V,
+                                   const uint8_t *is_sep, const int32_t *sep_idx, int cap,
+                                   const int32_t *sep_prefix, void *Kc, void *Vc, uint8_t *win_is_sep,
+                                   int32_t *sizes, void *stream) {
+    return fill_from_prefill(p, L, nw, K, V, is_sep, sep_idx, cap, sep_prefix, Kc, Vc, win_is_sep, sizes, true, stream);
 }
 
 }  // extern "C"

@@ -9,6 +9,9 @@
 // slot), win_is_sep = separator flag of each
 // window entry.  Rows are copied bit-exactly.
 //
+// ZERO: slots and window flags beyond the sizes are set to 0 (a caller whose buffers are fresh, which would otherwise clear
+// them first: four launches, and every byte that the copy writes written twice); without it they are left alone.
+//
 // One kernel: a workgroup of 256 threads copies 16 (d = 128, bf16) rows per pass; blockIdx.y is the
 // (sequence, KV head, K or V), blockIdx.x a run of kFillRows cache slots.  Workgroup x = 0 of KV
 // head 0 / tensor K also writes the sequence's sizes and window flags.
@@ -22,6 +25,7 @@ constexpr int kFillThreads = 256;
 constexpr int kFillRows = 128;  // cache slots per workgroup
 constexpr int kFillUnroll = 8;  // rows a thread has in flight
 
+template <bool ZERO>
 __global__ __launch_bounds__(kFillThreads) void cache_fill_kernel(
     sepkv_params p, int L, int nw, int cap, int row16, const uint4 *__restrict__ K, const uint4 *__restrict__ V,
     const uint8_t *__restrict__ is_sep, const int32_t *__restrict__ sep_idx, const int32_t *__restrict__ sep_prefix,
@@ -51,6 +55,8 @@ __global__ __launch_bounds__(kFillThreads) void cache_fill_kernel(
             sz[5] = 0;
         }
         for (int u = threadIdx.x; u < nw; u += kFillThreads) win_is_sep[(long)sq * wcap + u] = is_sep[(long)sq * L + wstart + u];
+        if constexpr (ZERO)
+            for (int u = nw + threadIdx.x; u < wcap; u += kFillThreads) win_is_sep[(long)sq * wcap + u] = 0;
     }
 
     const uint4 *src = (which ? V : K) + ((long)sq * p.Hkv + kv) * (long)L * row16;
@@ -62,7 +68,7 @@ __global__ __launch_bounds__(kFillThreads) void cache_fill_kernel(
     // kFillUnroll rows at a time: first all their source positions (for separator slots a dependent
     // load from the compacted list), then all row loads, then all stores.
     for (int t0 = blockIdx.x * kFillRows; t0 < t_end; t0 += rows_per_pass * kFillUnroll) {
-        int jsrc[kFillUnroll];  // source position of the slot, -1: the slot stays as it is
+        int jsrc[kFillUnroll];  // source position of the slot, -1: the slot is not in use
 #pragma unroll
         for (int u = 0; u < kFillUnroll; ++u) {
             const int t = t0 + u * rows_per_pass + r_in;  // cache slot
@@ -90,6 +96,7 @@ __global__ __launch_bounds__(kFillThreads) void cache_fill_kernel(
         for (int u = 0; u < kFillUnroll; ++u) {
             const int t = t0 + u * rows_per_pass + r_in;
             if (jsrc[u] >= 0) nt_store(v[u], &dst[(long)t * row16 + piece]);
+            else if (ZERO && t < t_end) nt_store(make_uint4(0u, 0u, 0u, 0u), &dst[(long)t * row16 + piece]);
         }
     }
 }
@@ -98,14 +105,14 @@ __global__ __launch_bounds__(kFillThreads) void cache_fill_kernel(
 
 int launch_cache_fill(const sepkv_params &p, int L, int nw, const void *K, const void *V, const uint8_t *is_sep,
                       const int32_t *sep_idx, int cap, const int32_t *sep_prefix, void *Kc, void *Vc,
-                      uint8_t *win_is_sep, int32_t *sizes, hipStream_t st) {
+                      uint8_t *win_is_sep, int32_t *sizes, bool zero_rest, hipStream_t st) {
     const int elem = (p.dtype == SEPATTN_BF16) ? 2 : 4;
     const int row16 = p.d * elem / 16;
     const long ny = (long)p.S * p.Hkv * 2;
     if (ny > 65535L) return SEPATTN_ERR_SHAPE;
     dim3 grid((p.c + kFillRows - 1) / kFillRows, (unsigned)ny);
     ProfScope prof(SEPATTN_K_CACHE_FILL, st);
-    hipLaunchKernelGGL(cache_fill_kernel, grid, dim3(kFillThreads), 0, st, p, L, nw, cap, row16,
+    hipLaunchKernelGGL(zero_rest ? cache_fill_kernel<true> : cache_fill_kernel<false>, grid, dim3(kFillThreads), 0, st, p, L, nw, cap, row16,
                        static_cast<const uint4 *>(K), static_cast<const uint4 *>(V), is_sep, sep_idx, sep_prefix,
                        static_cast<uint4 *>(Kc), static_cast<uint4 *>(Vc), win_is_sep, sizes);
     return launch_status();

@@ -81,11 +81,12 @@ int launch_mark(const int32_t *token_ids, long n_tokens, const SepIdSet &set, ui
                 hipStream_t st);
 int launch_mark_interval(int B, int L, int delta, int phase, uint8_t *is_sep, hipStream_t st);
 constexpr int kCompactChunk = 2048;  // tokens per workgroup of the compaction kernels
-int launch_compact(const uint8_t *is_sep, int B, int L, int32_t *sep_idx, int cap,
-                   int32_t *sep_count, int32_t *sep_prefix, int32_t *chunk_counts, hipStream_t st);
+// fill: what the entries behind a list's last separator are set to, or nullptr (left alone)
+int launch_compact(const uint8_t *is_sep, int B, int L, int32_t *sep_idx, int cap, int32_t *sep_count,
+                   int32_t *sep_prefix, int32_t *chunk_counts, const int32_t *fill, hipStream_t st);
 int launch_mark_compact(const int32_t *token_ids, int B, int L, const SepIdSet &set, uint8_t *is_sep,
                         int32_t *sep_idx, int cap, int32_t *sep_count, int32_t *sep_prefix,
-                        int32_t *chunk_counts, hipStream_t st);
+                        int32_t *chunk_counts, const int32_t *fill, hipStream_t st);
 
 // ---- fp32 path ---------------------------------------------------------------------------------
 // doc_start / doc_end: packed documents (per-position bounds [B, L]), or nullptr
@@ -127,6 +128,6 @@ int launch_evict(const sepkv_params &p, void *Kc, void *Vc, const uint8_t *win_i
                  void *ws, hipStream_t st);
 int launch_cache_fill(const sepkv_params &p, int L, int nw, const void *K, const void *V, const uint8_t *is_sep,
                       const int32_t *sep_idx, int cap, const int32_t *sep_prefix, void *Kc, void *Vc,
-                      uint8_t *win_is_sep, int32_t *sizes, hipStream_t st);
+                      uint8_t *win_is_sep, int32_t *sizes, bool zero_rest, hipStream_t st);
 
 }  // namespace sepattn

@@ -83,11 +83,17 @@ int launch_mark_interval(int B, int L, int delta, int phase, uint8_t *is_sep, hi
 }
 
 // ---- compaction --------------------------------------------------------------------------------
-constexpr int kCompactThreads = 256;
+// Bounds: the launch and one round trip of loads; nothing here comes near the memory's rate.  Sixteen waves per chunk, so that
+// a thread has two tokens of its own and at most six in front of the chunk, all requested together, and one barrier in
+// all.  Kernel time in us, before (four waves, eight tokens per thread, three or four barriers, one scalar load per id) /
+// now: @MC@.
+constexpr int kCompactThreads = 1024;
 constexpr int kCompactSingleLaunch = 32768;  // longest sequence compacted with one launch
 constexpr int kMarkCompactSingleLaunch = 8192;  // longest sequence marked and compacted with one launch
-constexpr int kCompactIters = kCompactChunk / kCompactThreads;  // 8 ballots per wave per chunk
+constexpr int kCompactIters = kCompactChunk / kCompactThreads;  // ballots per wave per chunk
 constexpr int kCompactWaves = kCompactThreads / kWave;
+constexpr int kCompactGroups = kCompactIters * kCompactWaves;  // a ballot each, in position order
+static_assert(kCompactGroups + kCompactWaves <= kWave, "the counts are added with one per lane");
 
 // pass 1: chunk_counts[b, chunk] = number of separators in the chunk
 __global__ __launch_bounds__(kCompactThreads) void compact_count_kernel(
@@ -112,11 +118,11 @@ __global__ __launch_bounds__(kCompactThreads) void compact_count_kernel(
     }
 }
 
-__device__ inline bool in_id_set(int v, const SepIdSet &set) {
-    unsigned f = 0;
-    for (int k = 0; k < set.n; ++k) f |= (v == set.ids[k]);
-    return f != 0;
-}
+// What the list holds behind its last separator: left alone, or set to `value`
+struct ListRest {
+    bool set;
+    int32_t value;
+};
 
 // pass 2: ranks and writes.  FUSED: the flags are not read from is_sep but formed from the token ids
 // (and written to marks_out for the chunk's own positions); chunk_counts is nullptr then.
@@ -125,129 +131,107 @@ __global__ __launch_bounds__(kCompactThreads) void compact_write_kernel(
     const uint8_t *__restrict__ is_sep, const int32_t *__restrict__ token_ids, SepIdSet set,
     uint8_t *__restrict__ marks_out, int L, int n_chunks, const int32_t *__restrict__ chunk_counts,
     int32_t *__restrict__ sep_idx, int cap, int32_t *__restrict__ sep_count,
-    int32_t *__restrict__ sep_prefix) {
-    __shared__ int part[kCompactIters * kCompactWaves];  // count of (iteration, wave) groups
-    __shared__ int base_s;
-    int b = blockIdx.y, chunk = blockIdx.x;
-    const uint8_t *row = FUSED ? nullptr : is_sep + (long)b * L;
-    const int32_t *ids_row = FUSED ? token_ids + (long)b * L : nullptr;
-    int base = chunk * kCompactChunk;
-    int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    int32_t *__restrict__ sep_prefix, ListRest rest) {
+    __shared__ int part[kCompactGroups + kCompactWaves];  // counts of the chunk's groups; of what each wave saw in front of it
+    const int b = blockIdx.y, chunk = blockIdx.x, tid = threadIdx.x;
+    const int base = chunk * kCompactChunk;
+    const int lane = tid % kWave, wave = __builtin_amdgcn_readfirstlane(tid / kWave);
 
-    // separators in earlier chunks of this sequence: from the counts of pass 1, or (short sequences,
-    // single launch) counted here from the flags themselves
-    if (chunk_counts != nullptr) {
-        if (wave == 0) {
-            int s = 0;
-            for (int c = lane; c < chunk; c += kWave) s += chunk_counts[(long)b * n_chunks + c];
-            for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-            if (lane == 0) base_s = s;
+    // the flags of the thread's own tokens, and the number of separators it finds in the earlier chunks of the sequence: from
+    // the counts of pass 1, or (short sequences, single launch) counted here
+    bool flag[kCompactIters];
+    int early = 0;
+    if constexpr (FUSED) {
+        // token q * kCompactThreads + tid, from the sequence's first to the chunk's own ones.  The id set (padded by the host
+        // with ids of its own) is walked in the outer loop, eight ids per scalar load; a token's matches are
+        // collected as a bit and counted once, so that an id given twice does not count twice.
+        constexpr int kTokens = kMarkCompactSingleLaunch / kCompactThreads;
+        static_assert(SEPATTN_MAX_SEP_IDS % 8 == 0, "ids are read eight at a time");
+        const int32_t *row = token_ids + (long)b * L;
+        const int own = chunk * kCompactIters;
+        int v[kTokens];
+#pragma unroll
+        for (int q = 0; q < kTokens; ++q)
+            if (q < own + kCompactIters) v[q] = row[min(q * kCompactThreads + tid, L - 1)];
+        uint32_t hit = 0;
+        for (int k0 = 0; k0 < set.n; k0 += 8) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const int sid = set.ids[k0 + k];
+#pragma unroll
+                for (int q = 0; q < kTokens; ++q)
+                    if (q < own + kCompactIters) hit |= (uint32_t)(v[q] == sid) << q;
+            }
+        }
+        early = __popc(hit & ((1u << own) - 1u));
+#pragma unroll
+        for (int it = 0; it < kCompactIters; ++it) {
+            const int j = base + it * kCompactThreads + tid;
+            flag[it] = j < L && ((hit >> (own + it)) & 1u);
+            if (j < L) marks_out[(long)b * L + j] = flag[it] ? 1 : 0;
         }
     } else {
-        __shared__ int early[kCompactWaves];
-        int s = 0;
-        if constexpr (FUSED) {
-            // at most three chunks lie in front (8192 tokens per launch).  All loads of a thread are
-            // requested first; the id set is walked in the OUTER loop (one scalar load per id, not
-            // one per id and token), a token's matches are collected as bits and counted once, so
-            // that an id given twice does not count twice.
-            constexpr int kEarly = (kMarkCompactSingleLaunch - kCompactChunk) / (kCompactThreads * 4);
-            if ((reinterpret_cast<uintptr_t>(ids_row) & 15u) == 0) {  // base is a multiple of 4
-                int4 v[kEarly];
-                uint32_t there = 0, hit = 0;
+        const uint8_t *row = is_sep + (long)b * L;
 #pragma unroll
-                for (int q = 0; q < kEarly; ++q) {
-                    const int j = (q * kCompactThreads + (int)threadIdx.x) * 4;
-                    v[q] = j < base ? *reinterpret_cast<const int4 *>(ids_row + j) : int4{0, 0, 0, 0};
-                    there |= (j < base ? 0xFu : 0u) << (4 * q);
-                }
-                for (int k = 0; k < set.n; ++k) {
-                    const int sid = set.ids[k];
-#pragma unroll
-                    for (int q = 0; q < kEarly; ++q)
-                        hit |= ((uint32_t)(v[q].x == sid) | ((uint32_t)(v[q].y == sid) << 1) | ((uint32_t)(v[q].z == sid) << 2) |
-                                ((uint32_t)(v[q].w == sid) << 3))
-                               << (4 * q);
-                }
-                s = __popc(hit & there);
-            } else {
-                for (int j = threadIdx.x; j < base; j += kCompactThreads) s += in_id_set(ids_row[j], set);
-            }
+        for (int it = 0; it < kCompactIters; ++it) {
+            const int j = base + it * kCompactThreads + tid;
+            flag[it] = j < L && row[j] != 0;
+        }
+        if (chunk_counts != nullptr) {
+            for (int c = tid; c < chunk; c += kCompactThreads) early += chunk_counts[(long)b * n_chunks + c];
         } else if ((reinterpret_cast<uintptr_t>(row) & 3u) == 0) {  // base is a multiple of 4
-            for (int j = threadIdx.x * 4; j < base; j += kCompactThreads * 4) {
+            for (int j = tid * 4; j < base; j += kCompactThreads * 4) {
                 const uint32_t w = *reinterpret_cast<const uint32_t *>(row + j);
                 // one bit per non-zero byte
-                s += __popc((((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w) & 0x80808080u);
+                early += __popc((((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w) & 0x80808080u);
             }
         } else {
-            for (int j = threadIdx.x; j < base; j += kCompactThreads) s += row[j] != 0;
-        }
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
-        if (lane == 0) early[wave] = s;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int t = 0;
-            for (int w2 = 0; w2 < kCompactWaves; ++w2) t += early[w2];
-            base_s = t;
+            for (int j = tid; j < base; j += kCompactThreads) early += row[j] != 0;
         }
     }
-    unsigned long long lt_mask = (1ull << lane) - 1ull;
-    bool flag[kCompactIters];
+    for (int off = 32; off > 0; off >>= 1) early += __shfl_xor(early, off);
+    if (lane == 0) part[kCompactGroups + wave] = early;
+    const unsigned long long lt_mask = (1ull << lane) - 1ull;
     int rank_in_wave[kCompactIters];
-    uint32_t own_hit = 0;
-    if constexpr (FUSED) {
-        int own_id[kCompactIters];
-#pragma unroll
-        for (int it = 0; it < kCompactIters; ++it) own_id[it] = ids_row[min(base + it * kCompactThreads + (int)threadIdx.x, L - 1)];
-        for (int k = 0; k < set.n; ++k) {
-            const int sid = set.ids[k];
-#pragma unroll
-            for (int it = 0; it < kCompactIters; ++it) own_hit |= (uint32_t)(own_id[it] == sid) << it;
-        }
-    }
 #pragma unroll
     for (int it = 0; it < kCompactIters; ++it) {
-        int j = base + it * kCompactThreads + threadIdx.x;
-        if constexpr (FUSED) {
-            flag[it] = (j < L) && ((own_hit >> it) & 1u);
-            if (j < L) marks_out[(long)b * L + j] = flag[it] ? 1 : 0;
-        } else {
-            flag[it] = (j < L) && row[j] != 0;
-        }
-        unsigned long long m = __ballot(flag[it]);
+        const unsigned long long m = __ballot(flag[it]);
         rank_in_wave[it] = __popcll(m & lt_mask);
         if (lane == 0) part[it * kCompactWaves + wave] = __popcll(m);
     }
     __syncthreads();
-    // exclusive prefix over the 32 (iteration, wave) groups, in position order, by wave 0
-    if (wave == 0) {
-        int v = (lane < kCompactIters * kCompactWaves) ? part[lane] : 0;
-        int incl = v;
-        for (int off = 1; off < kCompactIters * kCompactWaves; off <<= 1) {
-            int t = __shfl_up(incl, off);
-            if (lane >= off) incl += t;
-        }
-        if (lane < kCompactIters * kCompactWaves) part[lane] = incl - v;
+    // every wave: inclusive sums over the groups (position order), then over what lies in front of the chunk
+    const int v = lane < kCompactGroups + kCompactWaves ? part[lane] : 0;
+    int incl = v;
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int t = __shfl_up(incl, off);
+        if (lane >= off) incl += t;
     }
-    __syncthreads();
-    int chunk_base = base_s;
+    const int chunk_base = __builtin_amdgcn_readlane(incl, kWave - 1) - __builtin_amdgcn_readlane(incl, kCompactGroups - 1);
+    int32_t *list = sep_idx + (long)b * cap;
+#pragma unroll
     for (int it = 0; it < kCompactIters; ++it) {
-        int j = base + it * kCompactThreads + threadIdx.x;
+        const int g = it * kCompactWaves + wave, j = base + it * kCompactThreads + tid;
         if (j < L) {
-            int r = chunk_base + part[it * kCompactWaves + wave] + rank_in_wave[it];
+            const int r = chunk_base + __builtin_amdgcn_readlane(incl - v, g) + rank_in_wave[it];
             if (sep_prefix) sep_prefix[(long)b * (L + 1) + j] = r;
-            if (flag[it] && r < cap) sep_idx[(long)b * cap + r] = j;
+            // token j is separator r, or one of the others, j - r of which lie in front of it: these take the entries behind
+            // the list's last, from L - 1 downwards, so that nobody needs to know how long the list is
+            const int e = flag[it] ? r : L - 1 - (j - r);
+            if (e < cap && (flag[it] || rest.set)) list[e] = flag[it] ? j : rest.value;
             if (j == L - 1) {
-                int total = r + (flag[it] ? 1 : 0);
+                const int total = r + (flag[it] ? 1 : 0);
                 if (sep_prefix) sep_prefix[(long)b * (L + 1) + L] = total;
                 sep_count[b] = total;
             }
         }
     }
+    if (rest.set)
+        for (long e = (long)L + chunk * kCompactThreads + tid; e < cap; e += (long)n_chunks * kCompactThreads) list[e] = rest.value;
 }
 
 int launch_compact(const uint8_t *is_sep, int B, int L, int32_t *sep_idx, int cap,
-                   int32_t *sep_count, int32_t *sep_prefix, int32_t *chunk_counts, hipStream_t st) {
+                   int32_t *sep_count, int32_t *sep_prefix, int32_t *chunk_counts, const int32_t *fill, hipStream_t st) {
     int n_chunks = (L + kCompactChunk - 1) / kCompactChunk;
     dim3 grid(n_chunks, B);
     // Up to kCompactSingleLaunch positions a workgroup counts the separators in front of its chunk
@@ -262,7 +246,8 @@ int launch_compact(const uint8_t *is_sep, int B, int L, int32_t *sep_idx, int ca
     }
     ProfScope prof(SEPATTN_K_COMPACT_WRITE, st);
     hipLaunchKernelGGL(compact_write_kernel<false>, grid, dim3(kCompactThreads), 0, st, is_sep, nullptr, SepIdSet{},
-                       nullptr, L, n_chunks, single ? nullptr : chunk_counts, sep_idx, cap, sep_count, sep_prefix);
+                       nullptr, L, n_chunks, single ? nullptr : chunk_counts, sep_idx, cap, sep_count, sep_prefix,
+                       ListRest{fill != nullptr, fill ? *fill : 0});
     return launch_status();
 }
 
@@ -271,16 +256,17 @@ int launch_compact(const uint8_t *is_sep, int B, int L, int32_t *sep_idx, int ca
 // kernels beyond
 int launch_mark_compact(const int32_t *token_ids, int B, int L, const SepIdSet &set, uint8_t *is_sep,
                         int32_t *sep_idx, int cap, int32_t *sep_count, int32_t *sep_prefix,
-                        int32_t *chunk_counts, hipStream_t st) {
+                        int32_t *chunk_counts, const int32_t *fill, hipStream_t st) {
     if (L > kMarkCompactSingleLaunch) {
         int rc = launch_mark(token_ids, (long)B * L, set, is_sep, st);
         if (rc != SEPATTN_OK) return rc;
-        return launch_compact(is_sep, B, L, sep_idx, cap, sep_count, sep_prefix, chunk_counts, st);
+        return launch_compact(is_sep, B, L, sep_idx, cap, sep_count, sep_prefix, chunk_counts, fill, st);
     }
     int n_chunks = (L + kCompactChunk - 1) / kCompactChunk;
     ProfScope prof(SEPATTN_K_MARK_COMPACT, st);
     hipLaunchKernelGGL(compact_write_kernel<true>, dim3(n_chunks, B), dim3(kCompactThreads), 0, st, nullptr, token_ids,
-                       set, is_sep, L, n_chunks, nullptr, sep_idx, cap, sep_count, sep_prefix);
+                       set, is_sep, L, n_chunks, nullptr, sep_idx, cap, sep_count, sep_prefix,
+                       ListRest{fill != nullptr, fill ? *fill : 0});
     return launch_status();
 }
 

@@ -32,9 +32,12 @@ namespace {
     X(sepattn_forward_packed) X(sepattn_backward_packed) X(sepattn_backward_workspace_bytes) X(sepattn_backward)       \
     X(sepattn_decode_workspace_bytes) X(sepattn_decode) X(sepattn_decode_noalloc) X(sepkv_evict_window)                \
     X(sepkv_fill_from_prefill) X(sepattn_decode_rope) X(sepkv_append)
+// what some of them call where the outputs are their own, fresh ones
+#define LIB_FRESH_FUNCTIONS(F) F(sepattn_compact_indices_filled) F(sepattn_mark_compact_filled) F(sepkv_fill_from_prefill_zeroed)
 struct Lib {
 #define X(name) decltype(&::name) name;
     LIB_FUNCTIONS(X)
+    LIB_FRESH_FUNCTIONS(X)
 #undef X
 } lib;
 PyObject *g_raise = nullptr;  // Python callable: raises SepattnError(function, status)
@@ -228,8 +231,8 @@ PyObject *mark_separators(PyObject *const *a) {
     return a[2] == Py_None ? wrap(std::move(out)) : keep(a[2]);
 }
 
-// Index arrays, the caller's or (`allocate`) the call's own, where every entry of the list that is not written is
-// `fill`.  Arguments: the last three of `out`, cap, want_prefix, fill.
+// Index arrays, the caller's or (`allocate`) the call's own, where every entry of the list behind the last separator is
+// `fill` (the _filled entry points write it).  Arguments: the last three of `out`, cap, want_prefix, fill.
 struct IndexOut {
     at::Tensor idx, cnt, pre;
     int cap = 0, fill = 0;
@@ -251,7 +254,6 @@ struct IndexOut {
     }
     void allocate(int B, int L, const at::Device &device) {
         idx = empty({B, cap > 1 ? cap : 1}, at::kInt, device);
-        idx.fill_(fill);
         cnt = empty({B}, at::kInt, device);
         idx_p = (int32_t *)ptr(idx), cnt_p = (int32_t *)ptr(cnt);
         if (!want_prefix) return;
@@ -272,6 +274,9 @@ PyObject *compact_indices(PyObject *const *a) {
     check("sepattn_compact_indices", unlocked([&] {
               if (!ws.given) ws.allocate(lib.sepattn_compact_workspace_bytes(B, L), sep.device());
               if (!out.given()) o.allocate(B, L, sep.device());
+              if (!out.given())
+                  return lib.sepattn_compact_indices_filled((const uint8_t *)ptr(sep), B, L, o.idx_p, o.cap, o.cnt_p, o.pre_p, o.fill,
+                                                            ws.p, ws.bytes, stream_of(sep));
               return lib.sepattn_compact_indices((const uint8_t *)ptr(sep), B, L, o.idx_p, o.cap, o.cnt_p, o.pre_p, ws.p, ws.bytes,
                                                  stream_of(sep));
           }));
@@ -295,6 +300,8 @@ PyObject *mark_compact(PyObject *const *a) {
               if (!out.given()) {
                   sep = empty({B, L}, at::kByte, tok.device());
                   o.allocate(B, L, tok.device());
+                  return lib.sepattn_mark_compact_filled(i32(tok), B, L, ids.data(), (int)ids.size(), (uint8_t *)ptr(sep), o.idx_p,
+                                                         o.cap, o.cnt_p, o.pre_p, o.fill, ws.p, ws.bytes, stream_of(tok));
               }
               return lib.sepattn_mark_compact(i32(tok), B, L, ids.data(), (int)ids.size(), (uint8_t *)ptr(sep), o.idx_p, o.cap,
                                               o.cnt_p, o.pre_p, ws.p, ws.bytes, stream_of(tok));
@@ -551,15 +558,15 @@ PyObject *fill_from_prefill(PyObject *const *a) {
                 "sizes: int32 [S, 6]");
     }
     check("sepkv_fill_from_prefill", unlocked([&] {
-              if (!out.given()) {  // zero where the call leaves them alone
-                  Kc = empty({p.S, p.Hkv, p.c, p.d}, K.scalar_type(), K.device()).zero_();
-                  Vc = empty({p.S, p.Hkv, p.c, p.d}, K.scalar_type(), K.device()).zero_();
-                  flags = empty({p.S, p.c - p.a - p.s}, at::kByte, K.device()).zero_();
-                  sizes = empty({p.S, SEPKV_SIZES_COLS}, at::kInt, K.device()).zero_();
+              if (!out.given()) {
+                  Kc = empty({p.S, p.Hkv, p.c, p.d}, K.scalar_type(), K.device());
+                  Vc = empty({p.S, p.Hkv, p.c, p.d}, K.scalar_type(), K.device());
+                  flags = empty({p.S, p.c - p.a - p.s}, at::kByte, K.device());
+                  sizes = empty({p.S, SEPKV_SIZES_COLS}, at::kInt, K.device());
               }
-              return lib.sepkv_fill_from_prefill(&p, L, nw, ptr(K), ptr(V), (const uint8_t *)ptr(sep), i32(idx), (int)idx.size(1),
-                                                 i32(pre), ptr(Kc), ptr(Vc), (uint8_t *)ptr(flags), (int32_t *)ptr(sizes),
-                                                 stream_of(K));
+              const auto fill = out.given() ? lib.sepkv_fill_from_prefill : lib.sepkv_fill_from_prefill_zeroed;
+              return fill(&p, L, nw, ptr(K), ptr(V), (const uint8_t *)ptr(sep), i32(idx), (int)idx.size(1),
+                          i32(pre), ptr(Kc), ptr(Vc), (uint8_t *)ptr(flags), (int32_t *)ptr(sizes), stream_of(K));
           }));
     if (out.given()) return tuple_of(keep(out[0]), keep(out[1]), keep(out[2]), keep(out[3]));
     return tuple_of(wrap(std::move(Kc)), wrap(std::move(Vc)), wrap(std::move(flags)), wrap(std::move(sizes)));
@@ -603,6 +610,7 @@ PyObject *bind(PyObject *, PyObject *const *args, Py_ssize_t n) {
         return nullptr;                                                    \
     }
     LIB_FUNCTIONS(X)
+    LIB_FRESH_FUNCTIONS(X)
 #undef X
     Py_INCREF(args[1]);
     Py_XSETREF(g_raise, args[1]);
