@@ -62,8 +62,7 @@ struct DecodeWideShape {
     bool add;        // the slices are added by decode_wide_kernel itself, not by a merge launch
 };
 DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope, int units);  // units: compute_units()
-// where decode_wide_kernel has several slices the workspace begins with one word per (sequence, KV head), in which they are
-// counted
+// where decode_wide_kernel has several slices the workspace holds one word per (sequence, KV head), in which they are counted
 __host__ __device__ inline size_t decode_wide_arrival_bytes(const sepkv_params &p) { return align_up((size_t)p.S * p.Hkv * sizeof(uint64_t), 256); }
 int launch_decode_wide(const sepkv_params &p, const DecodeWideShape &shape, const uint16_t *q, const uint16_t *Kc, const uint16_t *Vc,
                        const int32_t *sizes, const float *rope, int n_pos, uint16_t *out, float *lse, float *part,

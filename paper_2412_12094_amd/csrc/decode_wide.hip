@@ -19,12 +19,17 @@
 //     registers); dimension i pairs with i + D/2 in another fragment of the same lane.  (Reading each row's own
 //     table row from memory is 64 separate 16-byte pieces per instruction: 3.5 us per round of eight blocks.)
 //   - where the slices' records are few, the workgroup of a cache that finishes last adds them (arrives_last): 1 to 2 us of
-//     device-scope round trips, as long as a merge launch takes on the device, but a launch less on the host, which
+//     device-scope round trips (the records stored, the count, the records fetched: 0.4 us each), as long as a merge launch takes on the device, but a launch less on the host, which
 //     costs 3 us there (append + decode of a streaming generation step, 32/8 heads, 4 sequences of 800 entries: 12.3 us -> 9.9).
 // Measured (MI355X, 32/8 heads, d = 128, one call of a stream of calls, us without / with ROPE; before: four
 // waves, 32-column operands, two stages per wave, the angle carried from block to block in registers):
 //   1 sequence, 64 entries 5.1 / 6.7 -> 3.6 / 4.8; 800 entries 8.8 / 12.0 -> 6.1 / 7.3
 //   32 sequences, 300 entries 9.5 / 13.5 -> 6.9 / 8.4; 3332 entries (436.7 MB) 67.7 / 73.1 -> 64.6 / 65.8 (6.8 TB/s)
+// Since then (angles formed while the K rows are on their way, queries through LDS with ROPE, a word per cache line, records of the
+// waves in their own stages): 1 sequence, 800 entries 6.5 / 7.5 -> 5.9 / 6.9; 4 sequences 6.8 / 7.8 -> 6.0 / 7.0; 3588 entries 8.7 /
+// 10.5 -> 7.6 / 9.0.  Where the 13100 cycles of such a workgroup with ROPE go that adds (one block per wave, 4 sequences): sizes and
+// table's requests 1050, rows' requests 700, table in registers 1200, K rows 900, turned and multiplied 1800, V 800,
+// waves' records 1400, slices' records published 900, counted 1000, added 2700.
 //
 // Operand layouts of 16x16x32 (lane l, g = l / 16): A row l%16, k = 8g..8g+7; B column l%16, same k; C
 // column l%16, rows 4g..4g+3.  Row 4g+i of score tile t (t = 0, 1) is row 8g+4t+i of the block, so that
@@ -42,6 +47,7 @@ namespace sepattn {
 namespace {
 
 constexpr int kDwRows = 32;  // entries per block (one stage of a wave)
+constexpr int kDwMostAdded = 16;  // slices that the kernel itself adds, at most
 
 __device__ inline f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
 
@@ -65,6 +71,17 @@ __device__ inline float groups_sum(float x) {
     return pair_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 
+// maximum over the eight lanes of half a row of sixteen
+__device__ inline float half_row_max(float x) {
+    auto with = [&](auto CTRL) {
+        x = fmaxf(x, __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), decltype(CTRL)::value, 0xF, 0xF, true)));
+    };
+    with(IntC<0xB1>{});   // quad_perm [1, 0, 3, 2]
+    with(IntC<0x4E>{});   // quad_perm [2, 3, 0, 1]
+    with(IntC<0x141>{});  // row_half_mirror
+    return x;
+}
+
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Wint-to-pointer-cast"
 __device__ inline f32x4 lds_read_f4(uint32_t addr) { return *(const f32x4 __attribute__((address_space(3))) *)addr; }
@@ -74,20 +91,19 @@ __device__ inline f32x4 lds_read_f4(uint32_t addr) { return *(const f32x4 __attr
 // clears.  Each slice adds `one`, the number of this launch in the upper 56 bits and 1 in the lower 8; the last one finds
 // (slices - 1) of them and sets the word to 0, so that the next launch finds it so.  Whatever else may stand there
 // (memory never used for this, the sum that calls left which overlapped on one workspace) is no multiple of this
-// launch's `one`: every slice looks at the word before its own work and, if it sees such a value, replaces that by 0;
+// launch's `one`: every slice looks at the word before it counts itself in and, if it saw such a value, replaces that by 0;
 // if the exchange fails, another slice of this launch has done so.  Nobody waits for another workgroup.  (A word that
 // every launch has to set first: 0.1 to 0.2 us more.)
-__device__ inline void arrival_ready(uint64_t *word, uint64_t one, int nsplit) {
-    uint64_t seen = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ inline uint64_t arrival_seen(uint64_t *word) { return __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void arrival_ready(uint64_t *word, uint64_t seen, uint64_t one, int nsplit) {
     const uint64_t n = seen & 0xFF;
     if (n >= (uint64_t)nsplit || seen != n * one)
         __hip_atomic_compare_exchange_strong(word, &seen, 0ull, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ inline bool arrives_last(uint64_t *word, uint64_t one, int nsplit) {
-    if (__hip_atomic_fetch_add(word, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (uint64_t)(nsplit - 1) * one) return false;
-    __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
+    return __hip_atomic_fetch_add(word, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint64_t)(nsplit - 1) * one;
 }
+__device__ inline void arrival_reset(uint64_t *word) { __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // ADD: several slices, added by the workgroup that finishes last.  Otherwise one slice, or the records are left to a merge launch.
 // The arguments fill 120 bytes, so that what the kernel reads of them, the grid's size behind them included, is two cache
@@ -108,7 +124,6 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
     constexpr int RF = D + 4;           // the same in LDS, padded to whole 16-byte pieces
 
     __shared__ __attribute__((aligned(1024))) uint16_t smem[2][NW][TILE];  // K rows, V rows of every wave's stage
-    static_assert(sizeof(smem) >= 16 * NW * RF * sizeof(float), "merge records overlay the stages");
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -118,34 +133,33 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
     const uint16_t *Kh = Kc + ((long)sq * p.Hkv + kv) * (long)p.c * D;
     const uint16_t *Vh = Vc + ((long)sq * p.Hkv + kv) * (long)p.c * D;
 
-    // Waited for only when the queries have been requested: those requests are up to 256 scattered pieces of 16 bytes per
+    // Waited for only when the queries and the table's rows have been requested: those requests are up to 256 scattered pieces of 16 bytes per
     // wave, which go out during this round trip; behind it the rows queue up behind them (28/4 heads, 1 sequence of 447
     // entries 6.46 -> 6.35 us, 16/1 heads 7.75 -> 7.66)
     int32_t sz[SEPKV_SIZES_COLS];
 #pragma unroll
     for (int i = 0; i < SEPKV_SIZES_COLS; ++i) sz[i] = sizes[SEPKV_SIZES_COLS * sq + i];
-    // one word per (sequence, KV head), then the records
-    uint64_t *const arrived = reinterpret_cast<uint64_t *>(part) + (long)sq * p.Hkv + kv;
-    part += decode_wide_arrival_bytes(p) / sizeof(float);
-    // by the wave with the fewest blocks, in front of everything else: behind the queries 0.1 to 0.3 us slower with ROPE (2
-    // sequences of 400 entries 7.4 -> 7.7), put off until the rows have been used 0.4 us without (2 sequences, 32/32 heads, 937
-    // entries 9.1 -> 9.6)
-    if constexpr (ADD) {
-        if (tid == 64 * (NW - 1)) arrival_ready(arrived, one, nsplit);
-    }
-    // queries: B operand, column = head of the group (zero beyond G)
+    // queries: B operand, column = head of the group (zero beyond G).  With ROPE fragment ks is fetched by wave ks for all waves,
+    // through LDS, every lane's 16 bytes to the lane's own place: loads into registers are waited for by the compiler, which
+    // does not see the row loads behind them, with all of those, while the angles could be formed.  Without ROPE there
+    // is nothing to do meanwhile, and the barrier costs more than the wait (1 sequence of 384 entries 5.7 -> 6.1 us).
+    const uint16_t *const qh = q + ((long)sq * p.Hq + h0) * D;
+    const uint32_t q_off = (uint32_t)(min(col, G - 1) * D + 8 * g) * 2;  // of fragment 0; the next one is 64 bytes on
+    __shared__ __attribute__((aligned(1024))) uint16_t q_s[ROPE ? KSTEPS : 1][ROPE ? 64 * 8 : 8];
     u32x4 qraw[KSTEPS];
-    {
-        const uint16_t *qrow = q + ((long)sq * p.Hq + h0 + min(col, G - 1)) * D + 8 * g;
+    if constexpr (ROPE) {
+        static_assert(KSTEPS <= NW, "one fragment per wave");
+        if (wave < KSTEPS)
+            dma_to_lds_16(qh, q_off + 64u * wave, lds_addr(&q_s[wave][0]));
+    } else {
 #pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) qraw[ks] = *reinterpret_cast<const u32x4 *>(qrow + 32 * ks);
+        for (int ks = 0; ks < KSTEPS; ++ks) qraw[ks] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(qh) + (q_off + 64u * ks));
     }
     __builtin_amdgcn_sched_barrier(0);
-    const CacheMap cm = cache_map(p, sz);
     // ROPE: the table rows 0 .. 31 (cos, sin of a row's place within a block), shared by the waves, with the chunks
     // of a row permuted; and per wave the table row of the block's first entry (two, in turn)
     // four waves: the table lies over the V stages, whose first rows are requested once it has been read, so that
-    // two workgroups fit a compute unit
+    // two workgroups fit a compute unit (where each has one to itself, V rows requested at once bring nothing: 6.66 us against 6.63)
     constexpr bool OVER = NW == 4;
     __shared__ __attribute__((aligned(1024))) float tab_s[ROPE && !OVER ? kDwRows * D : 4];
     __shared__ __attribute__((aligned(1024))) float base_s[ROPE ? NW : 1][ROPE ? 2 * D : 4];
@@ -158,11 +172,28 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
             dma_to_lds_16(rope, (uint32_t)(min(r, n_pos - 1) * D * 4) + (uint32_t)(((lane % TCH) ^ dw_swz<128>(r)) * 16),
                           t_lds + (wave * TLD + U) * 1024);
         });
+        __builtin_amdgcn_sched_barrier(0);
     }
+    // the word of the (sequence, KV head), and its records [head][slice].  Every word stands in front of its own records: side by
+    // side the words share a few cache lines, and the counting of all caches waits in one queue (4 sequences x 8 KV heads, seven
+    // slices: 0.9 to 1.4 us for the count, 0.4 now).  Records that a merge launch adds lie in one piece, behind where as many words would stand.
+    const long pair = (long)sq * p.Hkv + kv, pair_bytes = (long)G * nsplit * (PF * 4);
+    char *const arrived_at = reinterpret_cast<char *>(part) + pair * ((long)sizeof(uint64_t) + pair_bytes);
+    uint64_t *const arrived = reinterpret_cast<uint64_t *>(arrived_at);
+    char *const recs = ADD ? arrived_at + sizeof(uint64_t) : reinterpret_cast<char *>(part) + decode_wide_arrival_bytes(p) + pair * pair_bytes;
+    // requested in front of the rows, looked at when the wave's blocks are done
+    uint64_t seen = 0;
+    if constexpr (ADD) {
+        if (tid == 0) seen = arrival_seen(arrived);
+    }
+    const CacheMap cm = cache_map(p, sz);
     const int nv = cm.n_init + cm.n_sep + cm.n_past + cm.n_loc;
     // slices of whole blocks; wave w takes blocks w, w + NW, ... of the slice
     const int nb = (nv + kDwRows - 1) / kDwRows;
-    const int per = (nsplit == 1 ? nb : (nb + nsplit - 1) / nsplit) * kDwRows;
+    // blocks per slice, rounded up.  (The quotient of x < 2^21 by n: x + 1/2 is at least 1/(2n) of a whole number off, and the
+    // product's relative error is below 2^-22.  c d < 2^30, so nb < 2^19.  An integer division is on the way to the first row.)
+    const int share = (int)(((float)(nb + nsplit - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)nsplit));
+    const int per = (nsplit == 1 ? nb : __builtin_amdgcn_readfirstlane(share)) * kDwRows;
     const int e0 = min(split * per, nv), e1 = min(nv, e0 + per);
 
     const uint32_t k_lds = lds_addr(&smem[0][wave][0]), v_lds = lds_addr(&smem[1][wave][0]);
@@ -189,11 +220,12 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
     };
     auto wait_loads = [&](auto N) __attribute__((always_inline)) {  // at most N loads are still in flight
         constexpr int n = decltype(N)::value;
-        static_assert(n == 4 || n == 5 || n == 8 || n == 9 || n == 17, "wait counts are written for d = 64 and 128");
+        static_assert(n == 4 || n == 5 || n == 8 || n == 9 || n == 16 || n == 17, "wait counts are written for d = 64 and 128");
         if constexpr (n == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
         if constexpr (n == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
         if constexpr (n == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
         if constexpr (n == 9) asm volatile("s_waitcnt vmcnt(9)" ::: "memory");
+        if constexpr (n == 16) asm volatile("s_waitcnt vmcnt(16)" ::: "memory");
         if constexpr (n == 17) asm volatile("s_waitcnt vmcnt(17)" ::: "memory");
     };
 
@@ -219,7 +251,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
     // cos / sin of the lane's two rows r = krow + 4t within a block, 8 frequencies per k-step
     f32x4 rc[2][KS2][2], rs[2][KS2][2];
     if constexpr (ROPE) {
-        // this wave's share of the table (requested before its first stage) has landed
+        // this wave's share of the queries and of the table (requested before its first stage) has landed
         if (any) wait_loads(IntC<(OVER ? 1 : 2) * NLD + 1>{});
         else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
@@ -242,10 +274,44 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
         }
     }
 #pragma unroll
-    for (int ks = 0; ks < KSTEPS; ++ks) qreg[ks] = as_bf16x8(col < G ? qraw[ks] : u32x4{0u, 0u, 0u, 0u});
+    for (int ks = 0; ks < KSTEPS; ++ks) {
+        if constexpr (ROPE) qraw[ks] = *reinterpret_cast<const u32x4 *>(&q_s[ks][lane * 8]);
+        qreg[ks] = as_bf16x8(col < G ? qraw[ks] : u32x4{0u, 0u, 0u, 0u});
+    }
 
     for (int par = 0; eb < e1; eb += NW * kDwRows, par ^= 1) {
-        wait_loads(IntC<NLD>{});  // the K rows (and the block's table row); the V rows may be in flight
+        // R(-distance): (x, y) -> (x cos + y sin, y cos - x sin), dimension i with i + D/2; the distance of row r
+        // is that of the block's first entry minus r.  The angles need the block's table row only, which arrives in front of the K
+        // rows, and are formed while these are on their way (d = 64 has no registers for that).
+        auto base_row = [&](int ks, f32x4 (&bc)[2], f32x4 (&bs)[2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                bc[h] = lds_read_f4(b_lds + par * D * 4 + (8 * ks + 2 * g + h) * 16);
+                bs[h] = lds_read_f4(b_lds + par * D * 4 + (D / 8 + 8 * ks + 2 * g + h) * 16);
+            }
+        };
+        auto angle = [&](int t, int ks, int e, const f32x4 (&bc)[2], const f32x4 (&bs)[2], float &c, float &s) __attribute__((always_inline)) {
+            const float c0 = bc[e >> 2][e & 3], s0 = bs[e >> 2][e & 3];
+            const float cr = rc[t][ks][e >> 2][e & 3], sr = rs[t][ks][e >> 2][e & 3];
+            c = fmaf(s0, sr, c0 * cr);
+            s = fmaf(-c0, sr, s0 * cr);
+        };
+        constexpr bool EARLY = D == 128;
+        float ac[2][KS2][8], as[2][KS2][8];
+        if constexpr (ROPE && EARLY) {
+            wait_loads(IntC<2 * NLD>{});
+#pragma unroll
+            for (int ks = 0; ks < KS2; ++ks) {
+                f32x4 bc[2], bs[2];
+                base_row(ks, bc, bs);
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) angle(t, ks, e, bc, bs, ac[t][ks][e], as[t][ks][e]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        wait_loads(IntC<NLD>{});  // the K rows; the V rows may be in flight
         bf16x8 ka[2][KSTEPS];
 #pragma unroll
         for (int t = 0; t < 2; ++t)
@@ -258,25 +324,19 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
             issue_keys(eb + NW * kDwRows, par ^ 1);
         }
         if constexpr (ROPE) {
-            // R(-distance): (x, y) -> (x cos + y sin, y cos - x sin), dimension i with i + D/2; the distance of row r
-            // is that of the block's first entry minus r
 #pragma unroll
             for (int ks = 0; ks < KS2; ++ks) {
                 f32x4 bc[2], bs[2];
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    bc[h] = lds_read_f4(b_lds + par * D * 4 + (8 * ks + 2 * g + h) * 16);
-                    bs[h] = lds_read_f4(b_lds + par * D * 4 + (D / 8 + 8 * ks + 2 * g + h) * 16);
-                }
+                if constexpr (!EARLY) base_row(ks, bc, bs);
 #pragma unroll
                 for (int t = 0; t < 2; ++t) {
                     const f32x8 x = __builtin_convertvector(ka[t][ks], f32x8), y = __builtin_convertvector(ka[t][ks + KS2], f32x8);
                     f32x8 u, v;
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
-                        const float c0 = bc[e >> 2][e & 3], s0 = bs[e >> 2][e & 3];
-                        const float cr = rc[t][ks][e >> 2][e & 3], sr = rs[t][ks][e >> 2][e & 3];
-                        const float c = fmaf(s0, sr, c0 * cr), s = fmaf(-c0, sr, s0 * cr);
+                        float c, s;
+                        if constexpr (EARLY) c = ac[t][ks][e], s = as[t][ks][e];
+                        else angle(t, ks, e, bc, bs, c, s);
                         u[e] = fmaf(y[e], s, x[e] * c);
                         v[e] = fmaf(-x[e], s, y[e] * c);
                     }
@@ -329,37 +389,40 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
         }
     }
 
-    // ---- merge the waves' states through LDS: every wave's record overlays the stages
+    if constexpr (ADD) {
+        if (tid == 0) arrival_ready(arrived, seen, one, nsplit);
+    }
+    // ---- merge the waves' states through LDS: D outputs, max, sum of a head.  A wave's records lie in its own stage, whose rows
+    // nobody else reads: heads 0 .. 7 in the K half, the others in the V half
     const float l_tot = groups_sum(l_run);
-    float *red = reinterpret_cast<float *>(&smem[0][0][0]);  // [G][NW][RF]: D outputs, max, sum
-    __syncthreads();
+    static_assert(8 * RF * sizeof(float) <= TILE * sizeof(uint16_t), "the records of eight heads in half a stage");
+    auto record = [&](int h, int w) __attribute__((always_inline)) { return reinterpret_cast<float *>(&smem[h >> 3][w][0]) + (h & 7) * RF; };
     if (col < G) {
-        float *r = red + (col * NW + wave) * RF;
-        if (g == 0) {
-            r[D] = m_run;
-            r[D + 1] = l_tot;
-        }
+        float *r = record(col, wave);
+        if (g == 0) *reinterpret_cast<float2 *>(r + D) = float2{m_run, l_tot};
 #pragma unroll
         for (int db = 0; db < DB; ++db) *reinterpret_cast<f32x4 *>(r + 16 * db + 4 * g) = oacc[db];
     }
     __syncthreads();
     for (int item = tid; item < G * (D / 2); item += 64 * NW) {  // two columns per thread
         const int h = item / (D / 2), c2 = item % (D / 2);
-        const float *r = red + h * NW * RF;
-        float M = -INFINITY, ms[NW];
+        float2 ml[NW], o[NW];
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            ms[w] = r[w * RF + D];
-            M = fmaxf(M, ms[w]);
+            const float *r = record(h, w);
+            ml[w] = *reinterpret_cast<const float2 *>(r + D);
+            o[w] = *reinterpret_cast<const float2 *>(r + 2 * c2);
         }
+        float M = -INFINITY;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) M = fmaxf(M, ml[w].x);
         float lsum = 0.f, o0 = 0.f, o1 = 0.f;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            const float wgt = (ms[w] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ms[w] - M);
-            const float2 o = *reinterpret_cast<const float2 *>(r + w * RF + 2 * c2);
-            lsum = fmaf(wgt, r[w * RF + D + 1], lsum);
-            o0 = fmaf(wgt, o.x, o0);
-            o1 = fmaf(wgt, o.y, o1);
+            const float wgt = (ml[w].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml[w].x - M);
+            lsum = fmaf(wgt, ml[w].y, lsum);
+            o0 = fmaf(wgt, o[w].x, o0);
+            o1 = fmaf(wgt, o[w].y, o1);
         }
         const long sh = (long)sq * p.Hq + h0 + h;
         if (!ADD && nsplit == 1) {
@@ -370,7 +433,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
             *reinterpret_cast<bf16x2 *>(out + sh * D + 2 * c2) = __builtin_convertvector(v, bf16x2);
             if (lse && c2 == 0) lse[sh] = (lsum > 0.f) ? (M + __builtin_amdgcn_logf(lsum)) * kLn2_f : -INFINITY;
         } else {
-            float *dst = part + (sh * nsplit + split) * PF;
+            float *dst = reinterpret_cast<float *>(recs + (uint32_t)(h * nsplit + split) * (PF * 4));
             if constexpr (ADD) {
                 publish(dst + 2 + 2 * c2, float2{o0, o1});
                 if (c2 == 0) publish(dst, float2{M, lsum});
@@ -387,41 +450,56 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's part of the record is where every XCD sees it
     __syncthreads();
     if (tid == 0) last_s = arrives_last(arrived, one, nsplit);
-    __syncthreads();
+    // (a __syncthreads would also wait for stores)
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
     if (!last_s) return;
+    // The lanes of a head (64, or 32 at d = 64) have two columns each.  Maximum and sum of slice k are fetched by the head's lane k
+    // and handed around as scalars: fetched by every lane, they are half of the requests, whose number is what the
+    // fetch costs.  The arithmetic, and so every bit, is that of decode_merge_kernel: eight records at a time, in slice order.
+    static_assert(kDwMostAdded <= 16 && kDwMostAdded <= D / 2, "a slice per lane of a row of sixteen");
+    const int lk = lane % (D / 2);
     for (int item = tid; item < G * (D / 2); item += 64 * NW) {
         const int h = item / (D / 2), c2 = item % (D / 2);
-        const long sh = (long)sq * p.Hq + h0 + h;
-        const float *r = part + sh * nsplit * PF;
-        // eight records at a time are requested together; slices past the last repeat it with weight 0
-        constexpr int NB = 8;
+        const uint32_t at = (uint32_t)(h * nsplit) * (PF * 4);
+        float2 ml = {-INFINITY, 0.f};
         float M = -INFINITY, lsum = 0.f, o0 = 0.f, o1 = 0.f;
-        for (int s0 = 0; s0 < nsplit; s0 += NB) {
-            float2 ml[NB], o[NB];
+        for (int s0 = 0; s0 < nsplit; s0 += 8) {
+            float2 o[8];
 #pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                const float *rec = r + min(s0 + k, nsplit - 1) * PF;
-                ml[k] = fetch_published(rec);
-                o[k] = fetch_published(rec + 2 + 2 * c2);
-                if (s0 + k >= nsplit) ml[k].x = -INFINITY;
+            for (int k = 0; k < 8; ++k)  // slices past the last repeat it with weight 0
+                o[k] = fetch_published(reinterpret_cast<const float *>(recs + (at + 8u + 8u * c2 + (uint32_t)(min(s0 + k, nsplit - 1) * (PF * 4)))));
+            __builtin_amdgcn_sched_barrier(0);
+            if (s0 == 0) {  // the last of the requests, because its answer is waited for first
+                ml = fetch_published(reinterpret_cast<const float *>(recs + (at + (uint32_t)(min(lk, nsplit - 1) * (PF * 4)))));
+                if (lk >= nsplit) ml = float2{-INFINITY, 0.f};
             }
-            float Mn = M;
-#pragma unroll
-            for (int k = 0; k < NB; ++k) Mn = fmaxf(Mn, ml[k].x);
-            const float keep = (M == -INFINITY) ? 0.f : exp2f(M - Mn);
+            if (s0 == 0 && tid == 0) arrival_reset(arrived);
+            // the largest of the batch, in all of its eight lanes
+            const float m8 = half_row_max(ml.x);
+            auto of_head = [&](float x, int k) __attribute__((always_inline)) {  // lane k of this lane's head
+                const float a = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), k));
+                if constexpr (D == 128) return a;
+                else return lane < 32 ? a : __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), 32 + k));
+            };
+            const float Mn = fmaxf(M, of_head(m8, s0));
+            const float keep = (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
             lsum *= keep, o0 *= keep, o1 *= keep;
             M = Mn;
+            const float wgt = (ml.x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml.x - M);  // used of the batch's lanes
 #pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                const float wgt = (ml[k].x == -INFINITY) ? 0.f : exp2f(ml[k].x - M);
-                lsum = fmaf(wgt, ml[k].y, lsum);
-                o0 = fmaf(wgt, o[k].x, o0);
-                o1 = fmaf(wgt, o[k].y, o1);
+            for (int k = 0; k < 8; ++k) {
+                const float w = of_head(wgt, s0 + k);
+                lsum = fmaf(w, of_head(ml.y, s0 + k), lsum);
+                o0 = fmaf(w, o[k].x, o0);
+                o1 = fmaf(w, o[k].y, o1);
             }
         }
+        const long sh = (long)sq * p.Hq + h0 + h;
         const uint32_t b0 = decode_f32_to_bf16(lsum > 0.f ? o0 / lsum : 0.f), b1 = decode_f32_to_bf16(lsum > 0.f ? o1 / lsum : 0.f);
         *reinterpret_cast<uint32_t *>(out + sh * D + 2 * c2) = b0 | (b1 << 16);
-        if (lse && c2 == 0) lse[sh] = (lsum > 0.f) ? (M + log2f(lsum)) * kLn2_f : -INFINITY;
+        if (lse && c2 == 0) lse[sh] = (lsum > 0.f) ? (M + __builtin_amdgcn_logf(lsum)) * kLn2_f : -INFINITY;
     }
 }
 
@@ -476,7 +554,7 @@ DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope, int units) {
     if (ns > 1) {
         const int per = (nb + ns - 1) / ns;
         const int pays = (rope ? 9 * d64 : d64 == 1 ? 13 : 22) + (ns == 2 ? 8 : ns == 3 ? 3 : 0) * d64;
-        if (nb - per >= pays) return {ns, d64 == 1 || per <= 4 ? 4 : 8, ns <= 16 && row <= 1024 && ns * row <= 8192};
+        if (nb - per >= pays) return {ns, d64 == 1 || per <= 4 ? 4 : 8, ns <= kDwMostAdded && row <= 1024 && ns * row <= 8192};
     }
     return {1, nb <= 4 || pairs > (long)units * d64 ? 4 : 8, false};
 }
