@@ -62,14 +62,15 @@ __device__ inline float bf16_dot8(u32x4 a, u32x4 b) {
 // DOCS: packed documents, as in the forward kernel (doc_start / doc_end [B, L]; p.a == 0).
 // PARTS: streams of windows of part_keys and more keys go in two parts (split_tiles), whose sums go to `parts`
 // [group][split tile][part][wave][32 D].
-template <int D, int GP, bool DOCS, int NW, bool PARTS>
+// HW: head-wise windows.
+template <int D, int GP, bool DOCS, int NW, bool PARTS, bool HW>
 __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     sepattn_params p, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     const uint16_t *__restrict__ V, const uint16_t *__restrict__ O, const float *__restrict__ LSE,
     const uint16_t *__restrict__ dO, const int32_t *__restrict__ sep_idx,
     const int32_t *__restrict__ sep_prefix, const int32_t *__restrict__ doc_start,
     const int32_t *__restrict__ doc_end, uint16_t *__restrict__ dQ, float *__restrict__ Dws,
-    float *__restrict__ Lws, float *__restrict__ parts, int part_keys, int wpg, HeadWin hw, WorkShare share) {
+    float *__restrict__ Lws, float *__restrict__ parts, int part_keys, int wpg, QueryGrid qg, HeadArgs<HW> ha) {
     constexpr int TP = 32 * NW / GP;
     constexpr bool OWN_END = TP > 32;  // the waves' streams end at different tiles (as in the forward)
     constexpr int CH = D / 8;
@@ -97,25 +98,24 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
     // Persistent workgroups as in the forward kernel: a workgroup belongs to one (batch, KV head, head
     // group) and walks through several query tiles of it ("segments") in zig-zag order, `wpg`
     // workgroups per group; rank 0 is the last tile, the one with the longest key stream.
-    const int G = p.Hq / p.Hkv, groups = G / GP;
     const int n_pos_tiles = (p.L + TP - 1) / TP;
-    TileGroup tg;
-    if (share.n) {  // head-wise windows: see work_share.h
-        const ShareOf s = share_of(share, blockIdx.x, p.B);
-        tg.rank = s.rank;
-        tg.group = s.b * p.Hkv * groups + share.group[s.pos];
+    int rank0 = blockIdx.y, y = blockIdx.x + qg.gx * blockIdx.z;
+    GroupOf at;
+    if constexpr (HW) {  // see work_share.h
+        const ShareOf s = share_of(ha.share, blockIdx.x, p.B);
+        rank0 = s.rank;
         wpg = s.count;
+        const int g = ha.share.group[s.pos], k = quotient(g, qg.by_groups);
+        at = {g - k * qg.groups, k, s.b};
+        y = s.b * p.Hkv * qg.groups + g;
     } else {
-        tg = xcd_tile_group(blockIdx.x, wpg, p.B * p.Hkv * groups);
+        at = group_of(qg, y, p.Hkv);
     }
-    int y = tg.group;
-    const int hg = y % groups;
-    const int kv = (y / groups) % p.Hkv;
-    const int b = y / (groups * p.Hkv);
-    const int head = kv * G + hg * GP + (wave % GP);
-    const int gdelta = group_delta(hw, kv * G + hg * GP, GP);  // head-wise windows: see the forward kernel
+    const int kv = at.kv, b = at.b, head0 = (kv * qg.groups + at.hg) * GP;
+    const int head = head0 + (wave % GP);
+    const int gdelta = ha.of_group(head0, GP);  // head-wise windows: see the forward kernel
     p.n -= gdelta;
-    const int hdelta = head_delta(hw, head) - gdelta;
+    const int hdelta = ha.of_head(head) - gdelta;
 
     const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
     const int32_t *idx = sep_idx + (long)b * p.cap;
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
 
     // ---- segments and the look-ahead over the concatenation of their tiles, as in the forward kernel: what a tile
     // holds is worked out four tiles ahead of the multiplications by wave 0 (even tiles) and wave 1 (odd
-    // tiles), one row per lane, from index entries requested two tiles before.  Past the last segment the stream
+    // tiles; tiles 0 .. 3 by the first four waves), one row per lane, from index entries requested two tiles before.  Past the last segment the stream
     // is empty: its tiles are "loaded" too (row 0, never visible).
     struct Seg {
         Stream st;
@@ -140,37 +140,36 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
         int slot;                 // where the sums of a part go, -1: not a part
     };
     const SplitTiles split = split_tiles(n_pos_tiles, TP, p.n, PARTS ? part_keys : 0);  // of this group (its p.n)
-    auto open_segment = [&](int round) {
+    auto rank_of = [&](int round) { return round * wpg + ((round & 1) ? wpg - 1 - rank0 : rank0); };
+    const int n_pieces = n_pos_tiles + split.n;
+    auto segment_at = [&](int rank) {  // rank < n_pieces; no branches, as in the forward
         Seg g;
-        const int rank = round * wpg + ((round & 1) ? wpg - 1 - tg.rank : tg.rank);
+        int tile = rank, part = -1;
+        if constexpr (PARTS) split.find(rank, tile, part);
+        g.i0 = (n_pos_tiles - 1 - tile) * TP;
+        if constexpr (DOCS) {
+            // the clamps keep inconsistent bounds (caller error) from faulting
+            const int ds = min(max(load_uniform(dstart, g.i0), 0), g.i0);
+            g.de = min(max(load_uniform(dend, g.i0), g.i0 + 1), p.L);
+            g.st = make_stream_docs(p, prefix, g.i0, TP, ds);
+        } else {
+            g.de = kIntMax;
+            g.st = make_stream(p, prefix, g.i0, TP);
+        }
+        g.n_tiles = (g.st.n_total + kBN - 1) / kBN;
         g.t0 = 0;
         g.slot = -1;
-        if (rank >= n_pos_tiles + split.n) {
-            g.st = Stream{0, 0, 0, 0, 0};
-            g.n_tiles = kIntMax;
-            g.i0 = -1;
-            g.de = kIntMax;
-        } else {
-            int tile = rank, part = -1;
-            if constexpr (PARTS) split.find(rank, tile, part);
-            g.i0 = (n_pos_tiles - 1 - tile) * TP;
-            if constexpr (DOCS) {
-                // the clamps keep inconsistent bounds (caller error) from faulting
-                const int ds = min(max(load_uniform(dstart, g.i0), 0), g.i0);
-                g.de = min(max(load_uniform(dend, g.i0), g.i0 + 1), p.L);
-                g.st = make_stream_docs(p, prefix, g.i0, TP, ds);
-            } else {
-                g.de = kIntMax;
-                g.st = make_stream(p, prefix, g.i0, TP);
-            }
-            g.n_tiles = (g.st.n_total + kBN - 1) / kBN;
-            if (PARTS && part >= 0) {
-                g.slot = (y * split.most + tile) * 2 + part;
-                if (part) g.t0 = g.n_tiles / 2;
-                else g.n_tiles /= 2;
-            }
+        if (PARTS && part >= 0) {
+            g.slot = (y * split.most + tile) * 2 + part;
+            if (part) g.t0 = g.n_tiles / 2;
+            else g.n_tiles /= 2;
         }
         return g;
+    };
+    auto past_the_last = []() { return Seg{Stream{0, 0, 0, 0, 0}, 0, kIntMax, -1, kIntMax, -1}; };
+    auto open_segment = [&](int round) {
+        const int rank = rank_of(round);
+        return rank >= n_pieces ? past_the_last() : segment_at(rank);
     };
     struct Cursor {
         Seg cur, next;
@@ -372,33 +371,6 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    // ---- start-up, once per workgroup: positions of tiles 0 .. 3, then the first rows (the entries of tiles 4
-    // and 5 are on their way)
-    if (wave < 2) {
-        lc.cur = open_segment(0);
-        lc.next = open_segment(1);
-        lc.round = 0;
-        lc.t = lc.cur.t0;
-        if (wave == 1) advance(lc);
-        issue_entries(lc.cur.st, lc.t, wave);
-        Cursor l2 = lc;
-        advance(l2);
-        advance(l2);
-        issue_entries(l2.cur.st, l2.t, 2 + wave);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        write_rows(lc, wave);
-        write_rows(l2, 2 + wave);
-        lc = l2;
-        advance(lc);
-        advance(lc);
-        issue_entries(lc.cur.st, lc.t, 4 + wave);
-    }
-    wg_barrier();
-    static_for<AH>([&](auto T) {
-        read_offsets(decltype(T)::value);
-        static_for<2 * LOADS>([&](auto N) { issue_row(decltype(T)::value, N); });
-    });
-
     const IntC<0> first, off;
     const IntC<1> second, on;
     const IntC<-1> none;
@@ -435,8 +407,39 @@ __global__ __launch_bounds__(64 * NW, 2) void dq_kernel(
             }
         }
     };
-    Seg cseg = open_segment(0);
+    // ---- start-up, once per workgroup, as in the forward: positions of tiles 0 .. 3, a wave each, then the first rows (the entries
+    // of tiles 4 and 5 are on their way).  The first segment's rows of Q, dO and O are requested behind the entries,
+    // which are waited for alone.
+    Seg cseg = segment_at(rank0);
+    {
+        Seg next = segment_at(min(rank_of(1), n_pieces - 1));
+        if (rank_of(1) >= n_pieces) next = past_the_last();
+        lc = {cseg, next, 0, cseg.t0};
+    }
+    if (wave < 4) {
+        for (int t = 0; t < wave; ++t) advance(lc);
+        issue_entries(lc.cur.st, lc.t, wave);
+    }
+    __builtin_amdgcn_sched_barrier(0);
     fetch_rows(cseg);
+    __builtin_amdgcn_sched_barrier(0);
+    if (wave < 4) {
+        const Cursor own = lc;
+        if (wave < 2)
+            for (int t = 0; t < 4; ++t) advance(lc);
+        static_assert(CB == 2 || CB == 4, "all but the loads of fetch_rows are waited for");
+        if constexpr (CB == 2) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
+        if constexpr (CB == 4) asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
+        write_rows(own, wave);
+        if (wave < 2) issue_entries(lc.cur.st, lc.t, 4 + wave);  // where those of tile `wave` have just been read
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // only what write_rows wrote is published here
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    static_for<AH>([&](auto T) {
+        read_offsets(decltype(T)::value);
+        static_for<2 * LOADS>([&](auto N) { issue_row(decltype(T)::value, N); });
+    });
     for (int round = 0; cseg.i0 >= 0; ++round) {
         const int pw = cseg.i0 + 32 * (wave / GP);
         iq = pw + qi;
@@ -644,17 +647,25 @@ int launch_bwd(const sepattn_params &p, const uint16_t *Q, const uint16_t *K, co
     if (n_groups * wpg > 0x7FFFFFFFL) return SEPATTN_ERR_SHAPE;
     WorkShare share = {};
     long n_wg = n_groups * wpg;
-    if (any_delta(hw)) {
+    const bool headwise = !DOCS && any_delta(hw);  // (packed calls have no windows per head)
+    if (headwise) {
         share = share_queries(p, hw, shape.gp, TP, (int)(slots / p.B), part_keys);
         n_wg = (long)p.B * share.first[share.n];
     }
-    dim3 grid((unsigned)n_wg), block(64 * shape.nw);
+    const QueryGrid qg = query_grid(p, shape.gp, n_groups);
+    const dim3 block(64 * shape.nw), grid = headwise ? dim3((unsigned)n_wg) : dim3((unsigned)qg.gx, (unsigned)wpg, (unsigned)(n_groups / qg.gx));
     {
     ProfScope prof(SEPATTN_K_BWD_DQ, st);
     auto go = [&](auto NW_, auto GP_, auto PARTS_) {
         constexpr int GP = decltype(GP_)::value, NW = decltype(NW_)::value;
         constexpr bool PARTS = decltype(PARTS_)::value != 0;
-        hipLaunchKernelGGL((dq_kernel<D, GP, DOCS, NW, PARTS>), grid, block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, Lws, farK, part_keys, wpg, hw, share);
+        auto run = [&](auto kernel, auto ha) {
+            hipLaunchKernelGGL(kernel, grid, block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, Lws, farK, part_keys, wpg, qg, ha);
+        };
+        if constexpr (!DOCS) {
+            if (headwise) run(dq_kernel<D, GP, false, NW, PARTS, true>, HeadArgs<true>{hw, share});
+        }
+        if (!headwise) run(dq_kernel<D, GP, DOCS, NW, PARTS, false>, HeadArgs<false>{});
         if constexpr (PARTS)
             hipLaunchKernelGGL((dq_parts_kernel<D, GP, NW>), dim3((n_pieces - n_pos_tiles) * (D / 32), (unsigned)n_groups), block, 0, st, p, farK, dQ, part_keys, hw);
     };

@@ -58,6 +58,20 @@ struct ProfScope {
     ~ProfScope() { profile_mark(kernel, st, true); }
 };
 
+// Division of 0 <= x < 2^31 by a number known on the host: x / d = x m >> s with s = 31 + l, l = ceil(log2 d), m = ceil(2^s / d) (m d
+// exceeds 2^s by less than d <= 2^l).  Four scalar instructions; a division on the device is forty, and the start of a
+// workgroup had up to eight of them.
+struct FastDiv {
+    uint32_t m;
+    int32_t s;
+};
+inline FastDiv fast_div(uint32_t d) {
+    int l = 0;
+    while ((1ull << l) < d) ++l;
+    return {(uint32_t)(((1ull << (31 + l)) + d - 1) / d), 31 + l};
+}
+__device__ inline int quotient(int x, FastDiv f) { return (int)(((uint64_t)(uint32_t)x * f.m) >> f.s); }
+
 // Head-wise neighbour windows (the head-wise variant of Sec. 4.6): every attention kernel is given
 // p.n = the LARGEST window of the call and, by value, how much shorter each query head's own window
 // is.  The key streams and the far / band split of a group of heads that share K/V tiles are those of

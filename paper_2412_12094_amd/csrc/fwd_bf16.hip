@@ -25,6 +25,10 @@
 // n=1024 3990 -> 3650, 4 x L=1531 n=256 84 -> 75; 28/4 heads, 3 x L=3077 119 -> 78; 12 heads, d = 64, 8 x L=2048 51 -> 40.  The kernel alone (scalar
 // loads of a segment's bounds, no maximum per block, operands of a tile's second half requested in its first): 113 -> 94 (L=8192),
 // 3625 -> 3385 (64K), 88 -> 76 (3 x 3077), 38 -> 34 (d = 64), 86 -> 76 (8192 packed from eight documents).
+// The start of a workgroup (arguments -> bounds of its segments -> index entries -> rows) lasted 6800 cycles in a small call and 14000
+// where all compute units start at once; with the tables of head-wise calls left to these, divisions by multiplication, both
+// segments' bounds in one round trip and four waves for the first tiles' entries, here and in dQ, a step in us: 8/2 heads, L = 600
+// 47.3 -> 45.4, 8 x L = 2048 157 -> 154, 4 prompts of 1531 65.5 -> 62.2.
 #include "common.h"
 #include "mfma_common.h"
 #include "key_stream.h"
@@ -40,12 +44,13 @@ constexpr float kMaxTerm = 256.f;         // 2^kRescaleThreshold
 // DOCS: packed documents (see make_stream_docs); doc_start / doc_end [B, L] give, per position, the
 // first position of its document and one past its last.  Requires p.a == 0.
 // NW: waves per workgroup (4, 7 or 8, see query_shape); about two waves per SIMD in all shapes, three at d = 64 with four.
-template <int D, int GP, bool DOCS, int NW>
+// HW: head-wise windows (see below); the workgroups are dealt to the groups by their work (work_share.h).
+template <int D, int GP, bool DOCS, int NW, bool HW>
 __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_kernel(
     sepattn_params p, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
     const uint16_t *__restrict__ V, const int32_t *__restrict__ sep_idx,
     const int32_t *__restrict__ sep_prefix, const int32_t *__restrict__ doc_start,
-    const int32_t *__restrict__ doc_end, uint16_t *__restrict__ O, float *__restrict__ LSE, int wpg, HeadWin hw, WorkShare share) {
+    const int32_t *__restrict__ doc_end, uint16_t *__restrict__ O, float *__restrict__ LSE, int wpg, QueryGrid qg, HeadArgs<HW> ha) {
     constexpr int TP = 32 * NW / GP;  // query positions per workgroup
     // The waves' streams end at different tiles: a wave that is past its last position leaves the arithmetic of the rest out
     // (12 heads, d = 64, 8 x L = 2048, n = 64, four waves of 32 positions each: forward and backward 170.0 -> 165.1 us, of
@@ -81,28 +86,26 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     // the one with the longest key stream), so that with an even spread of separators every
     // workgroup gets about the same number of stream tiles.  Launch gaps, the tail of a grid of
     // unequal workgroups and most of the per-tile start-up cost are paid once per workgroup.
-    const int G = p.Hq / p.Hkv, groups = G / GP;
     const int n_pos_tiles = (p.L + TP - 1) / TP;
-    TileGroup tg;
-    if (share.n) {  // head-wise windows: see work_share.h
-        const ShareOf s = share_of(share, blockIdx.x, p.B);
-        tg.rank = s.rank;
-        tg.group = s.b * p.Hkv * groups + share.group[s.pos];
+    int rank0 = blockIdx.y;
+    GroupOf at;
+    if constexpr (HW) {
+        const ShareOf s = share_of(ha.share, blockIdx.x, p.B);
+        rank0 = s.rank;
         wpg = s.count;
+        const int g = ha.share.group[s.pos], k = quotient(g, qg.by_groups);
+        at = {g - k * qg.groups, k, s.b};
     } else {
-        tg = xcd_tile_group(blockIdx.x, wpg, p.B * p.Hkv * groups);
+        at = group_of(qg, blockIdx.x + qg.gx * blockIdx.z, p.Hkv);
     }
-    int y = tg.group;
-    const int hg = y % groups;
-    const int kv = (y / groups) % p.Hkv;
-    const int b = y / (groups * p.Hkv);
-    const int head = kv * G + hg * GP + (wave % GP);
+    const int kv = at.kv, b = at.b, head0 = (kv * qg.groups + at.hg) * GP;
+    const int head = head0 + (wave % GP);
     // head-wise windows: the stream is that of the largest window of the group's heads (p.n from here on); this
     // head's window is shorter by hdelta, which only enters the visibility test of band keys (hi was computed
     // with p.n) and the decision which blocks need no test
-    const int gdelta = group_delta(hw, kv * G + hg * GP, GP);
+    const int gdelta = ha.of_group(head0, GP);
     p.n -= gdelta;
-    const int hdelta = head_delta(hw, head) - gdelta;
+    const int hdelta = ha.of_head(head) - gdelta;
 
     const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
     const int32_t *idx = sep_idx + (long)b * p.cap;
@@ -130,32 +133,31 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
         Stream st;
         int n_tiles, i0, de;
     };
-    auto open_segment = [&](int round) {
+    auto rank_of = [&](int round) { return round * wpg + ((round & 1) ? wpg - 1 - rank0 : rank0); };
+    auto segment_at = [&](int rank) {  // rank < n_pos_tiles; no branches, so that the loads of two segments go out together
         Seg g;
-        const int rank = round * wpg + ((round & 1) ? wpg - 1 - tg.rank : tg.rank);
-        if (rank >= n_pos_tiles) {  // no more work: an empty stream of padding tiles
-            g.st = Stream{0, 0, 0, 0, 0};
-            g.n_tiles = kIntMax;
-            g.i0 = -1;
-            g.de = kIntMax;
+        g.i0 = (n_pos_tiles - 1 - rank) * TP;
+        if constexpr (DOCS) {
+            // the clamps keep inconsistent bounds (caller error) from faulting
+            const int ds = min(max(load_uniform(dstart, g.i0), 0), g.i0);
+            g.de = min(max(load_uniform(dend, g.i0), g.i0 + 1), p.L);
+            g.st = make_stream_docs(p, prefix, g.i0, TP, ds);
         } else {
-            g.i0 = (n_pos_tiles - 1 - rank) * TP;
-            if constexpr (DOCS) {
-                // the clamps keep inconsistent bounds (caller error) from faulting
-                const int ds = min(max(load_uniform(dstart, g.i0), 0), g.i0);
-                g.de = min(max(load_uniform(dend, g.i0), g.i0 + 1), p.L);
-                g.st = make_stream_docs(p, prefix, g.i0, TP, ds);
-            } else {
-                g.de = kIntMax;
-                g.st = make_stream(p, prefix, g.i0, TP);
-            }
-            g.n_tiles = (g.st.n_total + kBN - 1) / kBN;
+            g.de = kIntMax;
+            g.st = make_stream(p, prefix, g.i0, TP);
         }
+        g.n_tiles = (g.st.n_total + kBN - 1) / kBN;
         return g;
+    };
+    // no more work: an empty stream of padding tiles
+    auto past_the_last = []() { return Seg{Stream{0, 0, 0, 0, 0}, kIntMax, -1, kIntMax}; };
+    auto open_segment = [&](int round) {
+        const int rank = rank_of(round);
+        return rank >= n_pos_tiles ? past_the_last() : segment_at(rank);
     };
 
     // ---- what a tile holds: worked out four tiles ahead of the multiplications, one row per lane, by wave
-    // 0 (even tiles) and wave 1 (odd tiles) for all waves, which only read the rows' byte offsets back.  Two
+    // 0 (even tiles) and wave 1 (odd tiles; tiles 0 .. 3 by the first four waves) for all waves, which only read the rows' byte offsets back.  Two
     // steps: the index entries of the rows (issue_entries: list entry or prefix count of the row's
     // position, and the next prefix count) are requested with 4-byte global->LDS loads, and two tiles
     // later turned into key position and visibility range (write_rows).  Past the last segment the
@@ -163,13 +165,6 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
     struct Cursor {
         Seg cur, next;
         int round, t;  // segment of this workgroup and tile of its stream
-    };
-    auto cursor_at_start = [&]() {
-        Cursor c;
-        c.cur = open_segment(0);
-        c.next = open_segment(1);
-        c.round = c.t = 0;
-        return c;
     };
     auto advance = [&](Cursor &c) __attribute__((always_inline)) {
         if (++c.t == c.cur.n_tiles) {
@@ -430,7 +425,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    Seg cseg = open_segment(0), cnext = open_segment(1);
+    Seg cseg = segment_at(rank0), cnext = segment_at(min(rank_of(1), n_pos_tiles - 1));
+    if (rank_of(1) >= n_pos_tiles) cnext = past_the_last();
     auto load_queries = [&](int seg_i0) __attribute__((always_inline)) {
         const int row = min(seg_i0 + 32 * (wave / GP) + qi, p.L - 1);
         const uint16_t *qrow = Q + (((long)b * p.Hq + head) * p.L + row) * D;
@@ -438,26 +434,26 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
         for (int ks = 0; ks < KSTEPS; ++ks)
             qreg[ks] = as_bf16x8(*reinterpret_cast<const u32x4 *>(qrow + ks * 16 + 8 * hh));
     };
-    load_queries(cseg.i0);  // in flight during the start-up
 
-    // ---- start-up, once per workgroup: positions of tiles 0 .. 3, then the first rows (the entries of tiles 4
-    // and 5 are on their way)
-    Cursor lc;
-    if (wave < 2) {
-        lc = cursor_at_start();
-        if (wave == 1) advance(lc);
+    // ---- start-up, once per workgroup: positions of tiles 0 .. 3, a wave each, then the first rows (the entries of tiles 4
+    // and 5 are on their way).  The queries are requested behind the entries, which are waited for alone.
+    Cursor lc = {cseg, cnext, 0, 0};
+    if (wave < 4) {
+        for (int t = 0; t < wave; ++t) advance(lc);
         issue_entries(lc.cur.st, lc.t, wave);
-        Cursor l2 = lc;
-        advance(l2);
-        advance(l2);
-        issue_entries(l2.cur.st, l2.t, 2 + wave);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        write_rows(lc, wave);
-        write_rows(l2, 2 + wave);
-        lc = l2;
-        advance(lc);
-        advance(lc);
-        issue_entries(lc.cur.st, lc.t, 4 + wave);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    load_queries(cseg.i0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (wave < 4) {
+        const Cursor own = lc;
+        if (wave < 2)
+            for (int t = 0; t < 4; ++t) advance(lc);
+        static_assert(KSTEPS == 4 || KSTEPS == 8, "all but the queries' loads are waited for");
+        if constexpr (KSTEPS == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+        if constexpr (KSTEPS == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+        write_rows(own, wave);
+        if (wave < 2) issue_entries(lc.cur.st, lc.t, 4 + wave);  // where those of tile `wave` have just been read
     }
     // start of tile step g: positions of a tile four further on, entries of one six further on (AH = 2: of two
     // tiles every other step)
@@ -470,7 +466,9 @@ __global__ __launch_bounds__(64 * NW, D == 64 && NW == 4 ? 3 : 2) void fwd_bf16_
             issue_entries(lc.cur.st, lc.t, t + 6);
         }
     };
-    wg_barrier();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // only what write_rows wrote is published here
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
     read_offsets(0);
     static_for<LOADS>([&](auto U) { issue_k(0, U); });
     if constexpr (AH == 2) {
@@ -599,15 +597,24 @@ int launch_fwd(const sepattn_params &p, const uint16_t *Q, const uint16_t *K, co
     if (n_groups * wpg > 0x7FFFFFFFL) return SEPATTN_ERR_SHAPE;
     WorkShare share = {};
     long n_wg = n_groups * wpg;
-    if (any_delta(hw)) {
+    const bool headwise = !DOCS && any_delta(hw);  // (packed calls have no windows per head)
+    if (headwise) {
         share = share_queries(p, hw, shape.gp, TP, (shape.nw > 4 ? 1 : D == 64 ? 3 : 2) * compute_units() / p.B, 0);
         n_wg = (long)p.B * share.first[share.n];
     }
-    dim3 grid((unsigned)n_wg), block(64 * shape.nw);
+    const QueryGrid qg = query_grid(p, shape.gp, n_groups);
+    const dim3 block(64 * shape.nw), grid = headwise ? dim3((unsigned)n_wg) : dim3((unsigned)qg.gx, (unsigned)wpg, (unsigned)(n_groups / qg.gx));
     {
     ProfScope prof(SEPATTN_K_FORWARD, st);
     auto go = [&](auto NW_, auto GP_) {
-        hipLaunchKernelGGL((fwd_bf16_kernel<D, decltype(GP_)::value, DOCS, decltype(NW_)::value>), grid, block, 0, st, p, Q, K, V, sep_idx, sep_prefix, doc_start, doc_end, O, LSE, wpg, hw, share);
+        constexpr int NW = decltype(NW_)::value, GP = decltype(GP_)::value;
+        if constexpr (!DOCS) {
+            if (headwise) {
+                hipLaunchKernelGGL((fwd_bf16_kernel<D, GP, false, NW, true>), grid, block, 0, st, p, Q, K, V, sep_idx, sep_prefix, doc_start, doc_end, O, LSE, wpg, qg, (HeadArgs<true>{hw, share}));
+                return;
+            }
+        }
+        hipLaunchKernelGGL((fwd_bf16_kernel<D, GP, DOCS, NW, false>), grid, block, 0, st, p, Q, K, V, sep_idx, sep_prefix, doc_start, doc_end, O, LSE, wpg, qg, HeadArgs<false>{});
     };
     if (shape.gp == 7) go(IntC<7>{}, IntC<7>{});
     else if (D == 128 && shape.nw == 8) go(IntC<D == 128 ? 8 : 4>{}, IntC<4>{});

@@ -15,24 +15,34 @@ namespace sepattn {
 
 constexpr int kBN = 64;  // keys per LDS tile
 
-// XCD-aware decomposition of a 1-D grid of n_tiles * n_groups workgroups into (tile rank, group),
-// where a group is one (batch, KV head, packed query-head group) and owns its own K/V rows.
-// Consecutive workgroup ids are dealt round-robin to the 8 XCDs, each with a private L2.  When the
-// number of groups is a multiple of 8, XCD x only ever sees groups congruent to x, so the K/V rows
-// of a group stay in one L2 instead of being streamed through all eight.
-struct TileGroup {
-    int rank, group;
+// The workgroups of a forward or dQ launch.  A group is one (batch, KV head, packed query heads) and owns its own K/V rows; `wpg`
+// workgroups share its query tiles.
+// Consecutive workgroup ids (x first) are dealt round-robin to the 8 XCDs, each with a private L2.  When the
+// number of groups is a multiple of 8, the grid is 8 x wpg x groups/8, so that XCD x only ever sees groups congruent to
+// x and the K/V rows of a group stay in one L2 instead of being streamed through all eight.  Otherwise groups x wpg.
+struct QueryGrid {
+    int gx;      // groups side by side in the grid
+    int groups;  // head groups per KV head
+    FastDiv by_groups, by_hkv;
 };
-__device__ inline TileGroup xcd_tile_group(int id, int n_tiles, int n_groups) {
-    TileGroup r;
-    if (n_groups % 8 == 0) {
-        r.group = (id % 8) + 8 * (id / (8 * n_tiles));
-        r.rank = (id / 8) % n_tiles;
-    } else {
-        r.group = id % n_groups;
-        r.rank = id / n_groups;
-    }
+struct GroupOf {
+    int hg, kv, b;  // head group, KV head, batch row
+};
+__device__ inline GroupOf group_of(const QueryGrid &g, int group, int Hkv) {
+    GroupOf r;
+    const int bkv = quotient(group, g.by_groups);
+    r.hg = group - bkv * g.groups;
+    r.b = quotient(bkv, g.by_hkv);
+    r.kv = bkv - r.b * Hkv;
     return r;
+}
+inline QueryGrid query_grid(const sepattn_params &p, int gp, long n_groups) {
+    QueryGrid g;
+    g.groups = p.Hq / p.Hkv / gp;
+    g.gx = n_groups % 8 == 0 && n_groups / 8 <= 65535 ? 8 : (int)n_groups;
+    g.by_groups = fast_div((uint32_t)g.groups);
+    g.by_hkv = fast_div((uint32_t)p.Hkv);
+    return g;
 }
 
 // Shape of a forward / dQ workgroup: nw waves of 32 query rows each, gp query heads of one KV head packed into

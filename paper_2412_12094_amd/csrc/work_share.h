@@ -47,6 +47,21 @@ __host__ __device__ inline int group_delta(const HeadWin &hw, int h0, int n) {
     return d;
 }
 
+// What a forward or dQ kernel is given about head-wise windows.  An ordinary call has nothing of it: reading the tables (a round
+// trip to the arguments, behind that for the group's number) would stand at the start of every workgroup.
+template <bool HW>
+struct HeadArgs {
+    HeadWin hw;
+    WorkShare share;
+    __device__ int of_group(int h0, int n) const { return group_delta(hw, h0, n); }
+    __device__ int of_head(int h) const { return head_delta(hw, h); }
+};
+template <>
+struct HeadArgs<false> {
+    __device__ static int of_group(int, int) { return 0; }
+    __device__ static int of_head(int) { return 0; }
+};
+
 inline bool any_delta(const HeadWin &hw) {
     for (int h = 0; h < kMaxHeadwise; ++h)
         if (hw.delta[h]) return true;
