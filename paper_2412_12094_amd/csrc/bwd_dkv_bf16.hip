@@ -56,6 +56,26 @@ __device__ inline long shared_part_row(const FarGeom &even, const WorkShare &w, 
 // A KV head whose query heads all see every earlier key (n >= L) may have no band (`share.all`, see list_of_all_keys):
 // its list is then that of ALL keys and its far pairs are i >= j, so that this work is cut into equal slices too; as
 // a band unit the first keys' walk through the whole sequence is one workgroup's.
+// What the slices of the far work depend on, per launch (head-wise windows: per KV head, worked out on the device).  The start of
+// a workgroup, from its arguments to its first piece, is in the way of every call: with these numbers from the host, divisions
+// by multiplication, sums over lanes in registers and the head-wise tables left to the head-wise kernel it takes 2900 cycles instead
+// of 4900 at 8/2 heads, L = 600 (the kernel 11.2 -> 9.4 us, the step 45.4 -> 44.4), 8 x L = 2048 a step 157 -> 155 us.
+struct DkvSlices {
+    int G, Gs;              // query heads per KV head, per part of a band unit
+    int every_key;
+    int heavy;              // workgroups with one band unit more than the others
+    int min_slice;          // items of the shortest slice
+    int unit_items;         // what a band unit costs, in items
+    FastDiv by_hkv, by_G, by_split, by_wpg, by_min_slice;
+    __host__ __device__ void set(int n_band, int wpg, int Gs, int n, bool every_key, int blocks_per_tile) {
+        constexpr int kUnitStart = 8;  // steps of 32 query rows
+        const int unit_steps = Gs * ((n + 30) / 32 + 1), least = unit_steps < 4 ? 4 : (unit_steps > 16 ? 16 : unit_steps);
+        heavy = n_band % wpg;
+        min_slice = (every_key ? 16 : least) / blocks_per_tile;
+        unit_items = (unit_steps + kUnitStart) / blocks_per_tile;
+    }
+};
+
 template <int D, bool DOCS, bool HW, int KW, bool PARTS>
 __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv_kernel(
     sepattn_params p, const uint16_t *__restrict__ Q, const uint16_t *__restrict__ K,
@@ -64,7 +84,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
     const int32_t *__restrict__ sep_prefix, const int32_t *__restrict__ doc_end,
     uint16_t *__restrict__ dK, uint16_t *__restrict__ dV,
     float *__restrict__ farK, float *__restrict__ farV, int32_t *__restrict__ piece_tab, int wpg, int n_band,
-    int split, HeadWin hw, WorkShare share) {
+    int split, DkvSlices sl, HeadArgs<HW> ha) {
     constexpr int NW = 2 * KW;               // waves per workgroup
     constexpr int BK = 32 * KW;              // keys per workgroup
     constexpr int CH = D / 8;                // 16-byte chunks per row
@@ -101,33 +121,31 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
     const int role = wave / KW;  // 0: P-wave (S, dV), 1: dS-wave (dP, dK)
     const int kbw = wave % KW;   // key block of the wave
     const int kj = lane & 31, hh = lane >> 5;
-    const int G = p.Hq / p.Hkv;
+    const int G = sl.G;
     if constexpr (!PARTS) split = 1;
-    const int Gs = G / split;  // query heads per part of a band unit (see band_split); n_band counts the parts
-    // 1-D grid: consecutive workgroups belong to consecutive (batch, KV head) pairs, so with 8 KV heads
+    const int Gs = PARTS ? sl.Gs : G;  // query heads per part of a band unit (see band_split); n_band counts the parts
+    // Consecutive workgroups belong to consecutive (batch, KV head) pairs (the grid's first dimension), so with 8 KV heads
     // each head's K, V, Q, dO rows stay in the L2 of one XCD.
-    const int n_bkv = p.B * p.Hkv;
-    int bkv = blockIdx.x % n_bkv, w_id = blockIdx.x / n_bkv;
+    int bkv = blockIdx.x, w_id = blockIdx.y;
     long part0 = bkv * far_geom(p, wpg, KW, split).rows;  // first partial row of the (batch, KV head)
     int gdelta = 0;
     bool every_key = false;
     if constexpr (HW) {
-        const ShareOf s = share_of(share, blockIdx.x, p.B);
-        bkv = s.b * p.Hkv + share.group[s.pos];
-        part0 = shared_part_row(far_geom(p, wpg, KW), share, s, p);
+        const ShareOf s = share_of(ha.share, blockIdx.x, p.B);
+        bkv = s.b * p.Hkv + ha.share.group[s.pos];
+        part0 = shared_part_row(far_geom(p, wpg, KW), ha.share, s, p);
         w_id = s.rank;
         wpg = s.count;
-        gdelta = group_delta(hw, (bkv % p.Hkv) * G, G);
-        every_key = share.all[s.pos] != 0;
+        gdelta = ha.of_group((bkv - s.b * p.Hkv) * G, G);
+        every_key = ha.share.all[s.pos] != 0;
         p.n = every_key ? 0 : p.n - gdelta;
         if (every_key) n_band = 0;
+        sl.set(n_band, wpg, Gs, p.n, every_key, BPT);
     } else if constexpr (!DOCS) {
-        if (share.all[0]) {
-            every_key = true;
-            p.n = n_band = 0;
-        }
+        every_key = sl.every_key != 0;
+        if (every_key) p.n = n_band = 0;
     }
-    const int kv = bkv % p.Hkv, b = bkv / p.Hkv;
+    const int b = quotient(bkv, sl.by_hkv), kv = bkv - b * p.Hkv;
     const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
     const int32_t *idx = sep_idx + (long)b * p.cap;
     const int32_t *dend = DOCS ? doc_end + (long)b * p.L : nullptr;
@@ -171,11 +189,9 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         return fq < qe ? G * ((qe - fq + BQ - 1) / BQ) : 0;
     };
     auto inclusive_scan = [&](int v) __attribute__((always_inline)) {
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int u = __shfl_up(v, off);
-            if (lane >= off) v += u;
-        }
+        static_for<4>([&](auto I) { v += __builtin_amdgcn_update_dpp(0, v, 0x110 | (1 << decltype(I)::value), 0xF, 0xF, false); });  // row_shr
+        v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15: rows 1, 3
+        v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31: rows 2, 3
         return v;
     };
     // the first group of 64 list tiles is worked out once, for the total and for the pieces
@@ -193,17 +209,26 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
     // sum of many partials would cost more than the items (8/2 heads, L = 600: 29 + 12.6 us with slices of one
     // item, 22 + 4 now).  The slices that are not empty belong to consecutive workgroups, which is what the combine
     // kernel relies on.
-    constexpr int kUnitStart = 8;  // steps of 32 query rows
-    const int unit_steps = Gs * ((p.n + 30) / 32 + 1), min_slice = (every_key ? 16 : min(max(unit_steps, 4), 16)) / BPT;
-    const int heavy = n_band % wpg, light = wpg - heavy;
-    const long unit_items = ((long)unit_steps + kUnitStart) / BPT;
-    long per_heavy = heavy ? quotient(max(far_total - unit_items * light, 0l), wpg) : 0;
+    auto by = [](long x, FastDiv f, int d) { return x >> 31 ? x / d : (long)quotient((int)x, f); };
+    const int heavy = sl.heavy, light = wpg - heavy, min_slice = sl.min_slice;
+    const long unit_items = sl.unit_items;
+    long per_heavy = 0;
+    if (heavy) {
+        const long rest = max(far_total - unit_items * light, 0l);
+        per_heavy = HW ? quotient(rest, wpg) : by(rest, sl.by_wpg, wpg);
+    }
     if (per_heavy < min_slice) per_heavy = 0;
     const long far_light = far_total - per_heavy * heavy;
-    const long n_light = min(max(quotient(far_light, min_slice), 1l), (long)light);
+    const long n_light = min(max(HW ? quotient(far_light, min_slice) : by(far_light, sl.by_min_slice, min_slice), 1l), (long)light);
     const int w_light = w_id - heavy;
-    const long s0 = w_light < 0 ? w_id * per_heavy : per_heavy * heavy + quotient(min((long)w_light, n_light) * far_light, n_light);
-    const long s1 = w_light < 0 ? s0 + per_heavy : per_heavy * heavy + quotient(min(w_light + 1l, n_light) * far_light, n_light);
+    // the first of the slices w of n_light equal ones: floor(w far_light / n_light), w <= n_light <= wpg, from one division
+    const long whole = quotient(far_light, n_light), over = far_light - whole * n_light;
+    auto slice_start = [&](long w) __attribute__((always_inline)) {
+        const long x = w * over;  // < n_light^2
+        return w * whole + (x < kSmallQuotient ? (long)small_quotient((int)x, reciprocal((int)n_light)) : x / n_light);
+    };
+    const long s0 = w_light < 0 ? w_id * per_heavy : per_heavy * heavy + slice_start(min((long)w_light, n_light));
+    const long s1 = w_light < 0 ? s0 + per_heavy : per_heavy * heavy + slice_start(min(w_light + 1l, n_light));
 
     // iteration state over the pieces: first the far pieces of the slice (list tiles in groups of 64,
     // `pend` = tiles of the current group that overlap the slice and are still to be visited), then
@@ -246,7 +271,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
                 fq0 = __builtin_amdgcn_readlane(g_fq, l);
                 item0 = (int)(lo_i - first);
                 n_items = (int)(hi_i - lo_i);
-                n_qt = nq / G;
+                n_qt = quotient(nq, sl.by_G);
                 // the combine kernel finds the pieces of a list tile through its first and last workgroup
                 if (tid == 0) {
                     int32_t *tab = piece_tab + ((long)bkv * fg.NFTcap + ft) * 2;
@@ -282,7 +307,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
             hi = q_hi - 1;
             if constexpr (DOCS) hi = min(hi, dend[j] - 1);
         } else {
-            int j0 = unit / split * BK;
+            const int j0 = (PARTS ? quotient(unit, sl.by_split) : unit) * BK;
             j = j0 + 32 * kbw + kj;
             valid = j < p.L;
             q_lo = j0;
@@ -370,8 +395,10 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         // fetches the logical chunk the permutation maps there.  Rows past the sequence end are clamped (they
         // are masked by the [lo, hi] test: hi <= L-1).  Tiles are issued in order, head by head: the next one
         // is query tile iss_qt of the head whose rows begin at iss_head (iss_g: the head of the first).
-        int iss_tt = 0, iss_g = item0 / n_qt, iss_qt = item0 % n_qt;
-        if (PARTS && !FAR) iss_g = unit % split * Gs;  // the part's first head
+        int iss_tt = 0, iss_g = item0 < kSmallQuotient ? __builtin_amdgcn_readfirstlane(small_quotient(item0, reciprocal(n_qt))) : item0 / n_qt;
+        const int q0_tile = item0 - iss_g * n_qt;
+        int iss_qt = q0_tile;
+        if (PARTS && !FAR) iss_g = (unit - quotient(unit, sl.by_split) * split) * Gs;  // the part's first head
         size_t iss_head = (((long)b * p.Hq + kv * G + iss_g) * (long)p.L) * ROWB;  // byte offset of the head's rows in Q and dO
         auto issue_tile = [&]() {
             if (role == LOADER) {
@@ -437,11 +464,12 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
             uint32_t off;    // byte offset of the block's first row from the start of the ring
             bool full;       // every (query, key) pair of the block is visible: no mask test needed
         };
-        const int q0_tile = item0 % n_qt;
         // step s: the tile and block this wave (key block kbw) works on, lowest / highest tile of any wave
         int step_head = 0;  // head (within the group) of the block step_of was last asked about (band units)
+        const bool few = n_blocks + n_qt < kSmallQuotient;  // steps and tiles are divided by reciprocals
+        const float by_P = reciprocal(st_P), by_qt = reciprocal(n_qt);
         auto step_of = [&](int s, int &tile, int &blk, int &lo_t, int &hi_t) __attribute__((always_inline)) {
-            const int g = s / st_P, b = s - g * st_P;
+            const int g = FAR ? 0 : few ? small_quotient(s, by_P) : s / st_P, b = s - g * st_P;
             const int base_t = g * tiles_per_head;
             const bool mg = g > 0 && b < st_ov;
             const int own = base_t + b / BPT, old = base_t - tiles_per_head + (b + st_P) / BPT;
@@ -463,14 +491,15 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
                 // the head's delta: the table is indexed with wave-uniform numbers only
                 const int hd = step_head;
                 for (int g = 0; g < G; ++g) {
-                    const int sd = head_delta(hw, kv * G + g) - gdelta;
+                    const int sd = ha.of_head(kv * G + g) - gdelta;
                     dl = (!FAR && hd == g) ? sd : dl;
                 }
             }
             step_of(sidx + 1, tile_n, blk_n, lo_n, hi_n);
             if (sidx + 1 >= n_blocks) hi_n = n_tiles - 1;
             const int buf = tile % NBUF, qb = blk % BPT;
-            const int r0 = q_lo + ((q0_tile + blk / BPT) % n_qt) * BQ + 32 * qb;
+            const int q = q0_tile + blk / BPT, q_head = few ? small_quotient(q, by_qt) : q / n_qt;
+            const int r0 = q_lo + (q - q_head * n_qt) * BQ + 32 * qb;
             bool full = (r0 >= lo_max) && (r0 + 31 <= hi_min);
             if constexpr (HW) full = full && (r0 + 31 + dl <= hi2_min);
             sch_d = dl;
@@ -812,38 +841,38 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
 // list length -> list entry -> piece table -> partials, then their bytes.  The list's length is on the device and
 // its capacity is that of all keys: a grid for an eighth of the capacity, which walks on where there are more
 // entries, starts an eighth of the workgroups that only find out that they have nothing to do.
-template <int D>
+template <int D, int KW, bool HW>
 __global__ __launch_bounds__(256) void dkv_combine_kernel(sepattn_params p, const int32_t *__restrict__ sep_idx,
                                                           const int32_t *__restrict__ sep_prefix,
                                                           const int32_t *__restrict__ doc_end,
                                                           uint16_t *__restrict__ dK, uint16_t *__restrict__ dV,
                                                           const float *__restrict__ farK,
                                                           const float *__restrict__ farV,
-                                                          const int32_t *__restrict__ piece_tab, int wpg, int kw,
-                                                          HeadWin hw, WorkShare share) {
+                                                          const int32_t *__restrict__ piece_tab, int wpg,
+                                                          DkvSlices sl, HeadArgs<HW> ha) {
     constexpr int TPR = D / 4, RPB = 256 / TPR;  // threads per row, rows per workgroup
+    constexpr int kw = KW;
     int bkv = blockIdx.y;
     long base = bkv * far_geom(p, wpg, kw).rows;
-    bool every_key = false;
-    if (share.n) {  // as in dkv_kernel
+    bool every_key = sl.every_key != 0;
+    if constexpr (HW) {  // as in dkv_kernel
         ShareOf s;
-        s.b = bkv / p.Hkv;
-        s.pos = bkv % p.Hkv;
-        bkv = s.b * p.Hkv + share.group[s.pos];
-        base = shared_part_row(far_geom(p, wpg, kw), share, s, p);
-        wpg = share.first[s.pos + 1] - share.first[s.pos];
-        every_key = share.all[s.pos] != 0;
-        p.n = every_key ? 0 : p.n - group_delta(hw, (bkv % p.Hkv) * (p.Hq / p.Hkv), p.Hq / p.Hkv);
-    } else if (share.all[0]) {
-        every_key = true;
-        p.n = 0;
+        s.b = quotient(bkv, sl.by_hkv);
+        s.pos = bkv - s.b * p.Hkv;
+        bkv = s.b * p.Hkv + ha.share.group[s.pos];
+        base = shared_part_row(far_geom(p, wpg, kw), ha.share, s, p);
+        wpg = ha.share.first[s.pos + 1] - ha.share.first[s.pos];
+        every_key = ha.share.all[s.pos] != 0;
+        p.n -= ha.of_group((bkv - s.b * p.Hkv) * sl.G, sl.G);
     }
-    const int kv = bkv % p.Hkv, b = bkv / p.Hkv;
+    if (every_key) p.n = 0;
+    const int b = quotient(bkv, sl.by_hkv), kv = bkv - b * p.Hkv;
     const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
     const int32_t *idx = sep_idx + (long)b * p.cap;
     const FarGeom fg = far_geom(p, wpg, kw);
     const FarList fl = far_list(p, prefix, every_key);
-    const int col = (threadIdx.x % TPR) * 4, lt = fg.bk;  // lt: entries per list tile
+    const int col = (threadIdx.x % TPR) * 4;
+    constexpr int lt = 32 * KW;  // entries per list tile
     const int32_t *dend = doc_end ? doc_end + (long)b * p.L : nullptr;
     for (int f = blockIdx.x * RPB + threadIdx.x / TPR; f < fl.NF; f += gridDim.x * RPB) {
         // everything that does not depend on a loaded value is requested before the first use
@@ -892,22 +921,24 @@ __global__ __launch_bounds__(256) void dkv_combine_kernel(sepattn_params p, cons
 
 // The same where band units are split among workgroups (band_split): every key is finished here, from the parts of its band
 // unit and, if it is on the list, its far pieces.
-template <int D>
+template <int D, int KW>
 __global__ __launch_bounds__(256) void dkv_combine_parts_kernel(sepattn_params p, const int32_t *__restrict__ sep_idx,
                                                                 const int32_t *__restrict__ sep_prefix,
                                                                 const int32_t *__restrict__ doc_end,
                                                                 uint16_t *__restrict__ dK, uint16_t *__restrict__ dV,
                                                                 const float *__restrict__ farK,
                                                                 const float *__restrict__ farV,
-                                                                const int32_t *__restrict__ piece_tab, int wpg, int kw,
-                                                                int split) {
+                                                                const int32_t *__restrict__ piece_tab, int wpg,
+                                                                int split, FastDiv by_hkv) {
     constexpr int TPR = D / 4, RPB = 256 / TPR;  // threads per row, rows per workgroup
-    const int bkv = blockIdx.y, b = bkv / p.Hkv;
+    constexpr int kw = KW;
+    const int bkv = blockIdx.y, b = quotient(bkv, by_hkv);
     const FarGeom fg = far_geom(p, wpg, kw, split);
     const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
     const int32_t *idx = sep_idx + (long)b * p.cap;
     const int32_t *dend = doc_end ? doc_end + (long)b * p.L : nullptr;
-    const int lt = fg.bk, j = blockIdx.x * RPB + threadIdx.x / TPR, col = (threadIdx.x % TPR) * 4;
+    constexpr int lt = 32 * KW;
+    const int j = blockIdx.x * RPB + threadIdx.x / TPR, col = (threadIdx.x % TPR) * 4;
     if (j >= p.L) return;
     const long row0 = bkv * fg.rows;
     float4 sk = {0.f, 0.f, 0.f, 0.f}, sv = {0.f, 0.f, 0.f, 0.f};
@@ -978,21 +1009,51 @@ inline bool list_of_all_keys(const sepattn_params &p, int kw, int wpg, const Far
 }
 
 template <int D, int KW>
-void launch_dkv_shape(const sepattn_params &p, const HeadWin &hw, bool headwise, const uint16_t *Q, const uint16_t *K,
-                      const uint16_t *V, const float *lse2, const uint16_t *dO, const float *Dws, const int32_t *sep_idx,
-                      const int32_t *sep_prefix, const int32_t *doc_end, uint16_t *dK, uint16_t *dV, float *farK,
-                      float *farV, int32_t *piece_tab, int wpg, int split, const WorkShare &share, hipStream_t st) {
-    const int band_grid = (p.L + 32 * KW - 1) / (32 * KW) * split;
-    const dim3 grid((unsigned)(headwise ? (long)p.B * share.first[share.n] : (long)wpg * p.B * p.Hkv)), block(128 * KW);
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, block, 0, st, p, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg,
-                           band_grid, split, hw, share);
+int launch_dkv_shape(const sepattn_params &p, const HeadWin &hw, bool headwise, const uint16_t *Q, const uint16_t *K,
+                     const uint16_t *V, const float *lse2, const uint16_t *dO, const float *Dws, const int32_t *sep_idx,
+                     const int32_t *sep_prefix, const int32_t *doc_end, uint16_t *dK, uint16_t *dV, float *farK,
+                     float *farV, int32_t *piece_tab, int wpg, int split, const WorkShare &share, hipStream_t st) {
+    const int n_band = (p.L + 32 * KW - 1) / (32 * KW) * split;
+    bool any_all = share.all[0] != 0;  // some KV head works through the list of all keys
+    for (int i = 1; i < share.n; ++i) any_all = any_all || share.all[i] != 0;
+    DkvSlices sl;
+    sl.G = p.Hq / p.Hkv;
+    sl.Gs = sl.G / split;
+    sl.every_key = !headwise && any_all;
+    sl.set(sl.every_key ? 0 : n_band, wpg, sl.Gs, sl.every_key ? 0 : p.n, sl.every_key, KW == 2 ? 1 : 2);
+    sl.by_hkv = fast_div((uint32_t)p.Hkv);
+    sl.by_G = fast_div((uint32_t)sl.G);
+    sl.by_split = fast_div((uint32_t)split);
+    sl.by_wpg = fast_div((uint32_t)wpg);
+    sl.by_min_slice = fast_div((uint32_t)sl.min_slice);
+    {
+        const dim3 block(128 * KW), grid = headwise ? dim3((unsigned)(p.B * share.first[share.n])) : dim3((unsigned)(p.B * p.Hkv), (unsigned)wpg);
+        ProfScope prof(SEPATTN_K_BWD_DKV, st);
+        auto go = [&](auto kernel, auto ha) {
+            hipLaunchKernelGGL(kernel, grid, block, 0, st, p, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg,
+                               n_band, split, sl, ha);
+        };
+        const HeadArgs<false> none;
+        if (doc_end && split == 1) go(dkv_kernel<D, true, false, KW, false>, none);
+        else if (headwise) go(dkv_kernel<D, false, true, KW, false>, HeadArgs<true>{hw, share});
+        else if (split == 1) go(dkv_kernel<D, false, false, KW, false>, none);
+        else if (doc_end) go(dkv_kernel<D, true, false, KW, true>, none);
+        else go(dkv_kernel<D, false, false, KW, true>, none);
+    }
+    if (hipGetLastError() != hipSuccess) return SEPATTN_ERR_HIP;
+    ProfScope prof(SEPATTN_K_BWD_COMBINE, st);
+    const FarGeom fg = far_geom(p, wpg, KW);
+    const int rows_per_block = 256 / (D / 4);
+    const int list_rows = split > 1 ? p.L : any_all ? fg.NFcap : (fg.NFcap + 7) / 8;
+    const dim3 grid((list_rows + rows_per_block - 1) / rows_per_block, p.B * p.Hkv);
+    auto combine = [&](auto kernel, auto ha) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, p, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, sl, ha);
     };
-    if (doc_end && split == 1) go(dkv_kernel<D, true, false, KW, false>);
-    else if (headwise) go(dkv_kernel<D, false, true, KW, false>);
-    else if (split == 1) go(dkv_kernel<D, false, false, KW, false>);
-    else if (doc_end) go(dkv_kernel<D, true, false, KW, true>);
-    else go(dkv_kernel<D, false, false, KW, true>);
+    if (split > 1)
+        hipLaunchKernelGGL((dkv_combine_parts_kernel<D, KW>), grid, dim3(256), 0, st, p, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, split, sl.by_hkv);
+    else if (headwise) combine(dkv_combine_kernel<D, KW, true>, HeadArgs<true>{hw, share});
+    else combine(dkv_combine_kernel<D, KW, false>, HeadArgs<false>{});
+    return launch_status();
 }
 
 template <int D>
@@ -1019,27 +1080,12 @@ int launch_dkv(const sepattn_params &p, const HeadWin &hw, bool headwise, const 
         share.all[0] = list_all && p.n >= p.L;
     }
     const int split = headwise || share.all[0] ? 1 : band_split(p, wpg, kw);
-    {
-        ProfScope prof(SEPATTN_K_BWD_DKV, st);
-        // the eight-wave shape exists for d = 128 only (dkv_key_blocks)
-        if (D == 128 && kw == 4)
-            launch_dkv_shape<128, 4>(p, hw, headwise, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, split, share, st);
-        else
-            launch_dkv_shape<D, 2>(p, hw, headwise, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, split, share, st);
-    }
-    if (hipGetLastError() != hipSuccess) return SEPATTN_ERR_HIP;
-    ProfScope prof(SEPATTN_K_BWD_COMBINE, st);
-    const int rows_per_block = 256 / (D / 4);
-    bool every_key = share.all[0] != 0;
-    for (int i = 1; i < share.n; ++i) every_key = every_key || share.all[i] != 0;
-    const bool split_rows = split > 1 && !every_key;
-    const int list_rows = split_rows ? p.L : every_key ? fg.NFcap : (fg.NFcap + 7) / 8;
-    const dim3 grid((list_rows + rows_per_block - 1) / rows_per_block, p.B * p.Hkv);
-    if (split_rows)
-        hipLaunchKernelGGL((dkv_combine_parts_kernel<D>), grid, dim3(256), 0, st, p, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, kw, split);
-    else
-        hipLaunchKernelGGL((dkv_combine_kernel<D>), grid, dim3(256), 0, st, p, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, kw, hw, share);
-    return launch_status();
+    // the eight-wave shape exists for d = 128 only (dkv_key_blocks)
+    auto go = [&](auto launch) {
+        return launch(p, hw, headwise, Q, K, V, lse2, dO, Dws, sep_idx, sep_prefix, doc_end, dK, dV, farK, farV, piece_tab, wpg, split, share, st);
+    };
+    if (D == 128 && kw == 4) return go(launch_dkv_shape<128, 4>);
+    return go(launch_dkv_shape<D, 2>);
 }
 
 }  // namespace

@@ -71,6 +71,11 @@ inline FastDiv fast_div(uint32_t d) {
     return {(uint32_t)(((1ull << (31 + l)) + d - 1) / d), 31 + l};
 }
 __device__ inline int quotient(int x, FastDiv f) { return (int)(((uint64_t)(uint32_t)x * f.m) >> f.s); }
+// The same with a divisor d that only the device knows, by its reciprocal (v_rcp_f32, one unit in the last place): x + 1/2 is at
+// least 1/(2d) of a whole number off, and the product's relative error is below 2^-22, so this holds for 0 <= x < 2^21.
+constexpr int kSmallQuotient = 1 << 21;
+__device__ inline float reciprocal(int d) { return __builtin_amdgcn_rcpf((float)d); }
+__device__ inline int small_quotient(int x, float rcp) { return (int)(((float)x + 0.5f) * rcp); }
 
 // Head-wise neighbour windows (the head-wise variant of Sec. 4.6): every attention kernel is given
 // p.n = the LARGEST window of the call and, by value, how much shorter each query head's own window

@@ -190,9 +190,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
     const int nv = cm.n_init + cm.n_sep + cm.n_past + cm.n_loc;
     // slices of whole blocks; wave w takes blocks w, w + NW, ... of the slice
     const int nb = (nv + kDwRows - 1) / kDwRows;
-    // blocks per slice, rounded up.  (The quotient of x < 2^21 by n: x + 1/2 is at least 1/(2n) of a whole number off, and the
-    // product's relative error is below 2^-22.  c d < 2^30, so nb < 2^19.  An integer division is on the way to the first row.)
-    const int share = (int)(((float)(nb + nsplit - 1) + 0.5f) * __builtin_amdgcn_rcpf((float)nsplit));
+    // blocks per slice, rounded up (c d < 2^30, so nb < 2^19; an integer division is on the way to the first row)
+    const int share = small_quotient(nb + nsplit - 1, reciprocal(nsplit));
     const int per = (nsplit == 1 ? nb : __builtin_amdgcn_readfirstlane(share)) * kDwRows;
     const int e0 = min(split * per, nv), e1 = min(nv, e0 + per);
 
