@@ -3,6 +3,8 @@
 // cover.
 #include "common.h"
 
+#include <atomic>
+#include <chrono>
 #include <new>
 #include <vector>
 
@@ -108,6 +110,20 @@ int check_kv(const sepkv_params *p) { return sepattn::check_kv_params(p); }
 }  // namespace
 
 namespace sepattn {
+// What each slice of one launch adds to its word: a number in the upper 56 bits that no two launches of a process share (those of
+// another process, or whatever else memory may hold, meet it with probability 2^-56), and 1.
+uint64_t launch_number() {
+    static std::atomic<uint64_t> number{(uint64_t)std::chrono::system_clock::now().time_since_epoch().count()};
+    return (number.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull) << 8 | 1;
+}
+
+bool being_captured(hipStream_t st) {
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    discard_stale_hip_error();  // the null stream while another stream is being captured: the launch reports that
+    return false;
+}
+
 int compute_units() {
     static int cached[64] = {};
     int dev = 0;

@@ -14,7 +14,7 @@
 // At the sizes this path is used at, a call lasts about as long as its chain of memory latencies, so
 // the work of a tile is spread over the four waves of a workgroup (16-key blocks, or query blocks, dealt round-robin; the waves'
 // partial results meet once in LDS), operands go straight from memory to registers, and what can
-// share a launch does: D_i is formed by the dQ kernel, and the far keys' partial sums are added by the
+// share a launch does: dQ and dK/dV (launch_backward_shape), and the far keys' partial sums are added by the
 // last workgroup to finish a list tile instead of by a kernel of their own.
 //
 // A masked pair enters the contractions over streamed rows with weight 0, and 0 times an infinity or a NaN is NaN: a
@@ -69,6 +69,11 @@ __device__ inline float group_sum(float v) {
     return v + __shfl_xor(v, 32);
 }
 
+// Divisors that a launch has in common.
+struct Fp32Plan {
+    FastDiv by_tiles, by_hq, by_g, by_bkv, by_hkv, by_min_slice;
+    int n_tiles, G, min_slice;
+};
 // A query tile: 16 positions from i0 on of one query head, and its key stream (key_stream.h).
 struct QueryTile {
     int b, h, kv, i0;
@@ -78,16 +83,16 @@ struct QueryTile {
     Stream st;
     int de;
 };
-__device__ inline QueryTile query_tile(const sepattn_params &p, const HeadWin &hw, const int32_t *sep_idx,
+template <bool HW>
+__device__ inline QueryTile query_tile(const sepattn_params &p, const Fp32Plan &pl, const HeadArgs<HW> &ha, int block, const int32_t *sep_idx,
                                        const int32_t *sep_prefix, const int32_t *doc_start, const int32_t *doc_end) {
     QueryTile t;
-    const int n_tiles = (p.L + kT - 1) / kT;
-    const int bh = blockIdx.x / n_tiles;
-    t.b = bh / p.Hq, t.h = bh % p.Hq, t.kv = t.h / (p.Hq / p.Hkv);
-    t.i0 = (blockIdx.x % n_tiles) * kT;
+    const int bh = quotient(block, pl.by_tiles);
+    t.b = quotient(bh, pl.by_hq), t.h = bh - t.b * p.Hq, t.kv = quotient(t.h, pl.by_g);
+    t.i0 = (block - bh * pl.n_tiles) * kT;
     t.row0 = (long)bh * p.L;
     t.p = p;
-    t.p.n = p.n - head_delta(hw, t.h);
+    t.p.n = p.n - ha.of_head(t.h);
     t.prefix = sep_prefix + (long)t.b * (p.L + 1);
     t.idx = sep_idx + (long)t.b * p.cap;
     t.dend = doc_end ? doc_end + (long)t.b * p.L : nullptr;
@@ -165,20 +170,20 @@ __device__ inline void add_visible(f32x4 (&acc)[D / 16], const f32x4 &w, const b
 }
 
 // ---- forward -----------------------------------------------------------------------------------
-template <int D>
+template <int D, bool HW>
 __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 3) void fwd_fp32_kernel(sepattn_params p, const float *__restrict__ Q,
                                                                const float *__restrict__ K, const float *__restrict__ V,
                                                                const int32_t *__restrict__ sep_idx,
                                                                const int32_t *__restrict__ sep_prefix,
                                                                const int32_t *__restrict__ doc_start,
                                                                const int32_t *__restrict__ doc_end,
-                                                               float *__restrict__ O, float *__restrict__ LSE, HeadWin hw) {
+                                                               float *__restrict__ O, float *__restrict__ LSE, Fp32Plan pl, HeadArgs<HW> ha) {
     constexpr int C = D / 16;
     __shared__ float os[kWaves][kT][D + 4];
     __shared__ float ms[kWaves][kT], ls[kWaves][kT];
     const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: scalar loads and branches
-    const QueryTile t = query_tile(p, hw, sep_idx, sep_prefix, doc_start, doc_end);
+    const QueryTile t = query_tile<HW>(p, pl, ha, blockIdx.x, sep_idx, sep_prefix, doc_start, doc_end);
     const long kv0 = ((long)t.b * p.Hkv + t.kv) * (long)p.L * D;
     const float *Kh = K + kv0, *Vh = V + kv0;
     const int iq = t.i0 + m;
@@ -251,24 +256,18 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 3) void fwd_fp32_kernel(
     }
 }
 
-// ---- dQ, and D_i = <dO_i, O_i> for the dK/dV kernel, whose counters it clears too ---------------------
-template <int D>
-__global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void dq_fp32_kernel(sepattn_params p, const float *__restrict__ Q,
-                                                              const float *__restrict__ K, const float *__restrict__ V,
-                                                              const float *__restrict__ O, const float *__restrict__ LSE,
-                                                              const float *__restrict__ dO,
-                                                              const int32_t *__restrict__ sep_idx,
-                                                              const int32_t *__restrict__ sep_prefix,
-                                                              const int32_t *__restrict__ doc_start,
-                                                              const int32_t *__restrict__ doc_end,
-                                                              float *__restrict__ dQ, float *__restrict__ Dws,
-                                                              int32_t *__restrict__ counters, long n_counters, HeadWin hw) {
+// ---- dQ, and D_i = <dO_i, O_i> (stored where Dws is given) ------------------------------------------
+template <int D, bool HW>
+__device__ inline void dq_tile(float (&xs)[kWaves][kT][D + 4], int block, const sepattn_params &p, const float *__restrict__ Q,
+                               const float *__restrict__ K, const float *__restrict__ V, const float *__restrict__ O,
+                               const float *__restrict__ LSE, const float *__restrict__ dO, const int32_t *__restrict__ sep_idx,
+                               const int32_t *__restrict__ sep_prefix, const int32_t *__restrict__ doc_start,
+                               const int32_t *__restrict__ doc_end, float *__restrict__ dQ, float *__restrict__ Dws,
+                               const Fp32Plan &pl, const HeadArgs<HW> &ha) {
     constexpr int C = D / 16;
-    __shared__ float xs[kWaves][kT][D + 4];
-    for (long c = (long)blockIdx.x * (64 * kWaves) + threadIdx.x; c < n_counters; c += (long)gridDim.x * (64 * kWaves)) counters[c] = 0;
     const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: scalar loads and branches
-    const QueryTile t = query_tile(p, hw, sep_idx, sep_prefix, doc_start, doc_end);
+    const QueryTile t = query_tile<HW>(p, pl, ha, block, sep_idx, sep_prefix, doc_start, doc_end);
     const long kv0 = ((long)t.b * p.Hkv + t.kv) * (long)p.L * D;
     const float *Kh = K + kv0, *Vh = V + kv0;
     const int iq = t.i0 + m;
@@ -287,7 +286,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void dq_fp32_kernel(s
         Di = group_sum(Di);
     }
     const float lse = LSE[row];
-    if (wave == 0 && g == 0 && iq < p.L) Dws[row] = Di;
+    if (Dws && wave == 0 && g == 0 && iq < p.L) Dws[row] = Di;
     auto run = [&](auto VISIBLE_ONLY) __attribute__((always_inline)) {
 #pragma unroll
         for (int c = 0; c < C; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -337,25 +336,22 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void dq_fp32_kernel(s
 // list tile that lies in one slice is finished there, otherwise each slice writes a partial (slot
 // slice + tile) and the workgroup that is the last to count itself in adds them in slice order.
 // Every wave of a workgroup keeps the tile's K and V rows and its own dK and dV sums in registers.
-template <int D>
-__global__ __launch_bounds__(64 * kWaves) void dkv_fp32_kernel(sepattn_params p, const float *__restrict__ Q,
-                                                               const float *__restrict__ K, const float *__restrict__ V,
-                                                               const float *__restrict__ LSE, const float *__restrict__ dO,
-                                                               const float *__restrict__ Drow,
-                                                               const int32_t *__restrict__ sep_idx,
-                                                               const int32_t *__restrict__ sep_prefix,
-                                                               const int32_t *__restrict__ doc_end, float *__restrict__ dK,
-                                                               float *__restrict__ dV, float *__restrict__ partials,
-                                                               int32_t *__restrict__ counters, int n_far_tiles, int wpg,
-                                                               HeadWin hw) {
+// OWN_D: D_i is formed here, from the rows of dO, which an item reads anyway, and of O, so that the launch need not wait for dQ;
+// and slices are counted in words that nobody has to clear (common.h; `one`) instead of in counters.
+template <int D, bool HW, bool OWN_D>
+__device__ inline void dkv_unit(float (&xs)[kWaves][kT][D + 4], const sepattn_params &p, const float *__restrict__ Q, const float *__restrict__ K,
+                                const float *__restrict__ V, const float *__restrict__ O, const float *__restrict__ LSE,
+                                const float *__restrict__ dO, const float *__restrict__ Drow, const int32_t *__restrict__ sep_idx,
+                                const int32_t *__restrict__ sep_prefix, const int32_t *__restrict__ doc_end, float *__restrict__ dK,
+                                float *__restrict__ dV, float *__restrict__ partials, void *__restrict__ counters, int n_far_tiles, int wpg,
+                                int word_stride, uint64_t one, const Fp32Plan &pl, const HeadArgs<HW> &ha) {
     constexpr int C = D / 16;
-    __shared__ float xs[kWaves][kT][D + 4];
     __shared__ int last_s, js[kT];  // js: the keys of a list tile
     const int lane = threadIdx.x & 63, m = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: scalar loads and branches
-    const int G = p.Hq / p.Hkv, n_bkv = p.B * p.Hkv;
-    const int bkv = blockIdx.x % n_bkv, unit = blockIdx.x / n_bkv;  // units: wpg far slices, then the band units
-    const int kv = bkv % p.Hkv, b = bkv / p.Hkv;
+    const int G = pl.G, n_bkv = p.B * p.Hkv;
+    const int unit = quotient(blockIdx.x, pl.by_bkv), bkv = blockIdx.x - unit * n_bkv;  // units: wpg far slices, then the band units
+    const int b = quotient(bkv, pl.by_hkv), kv = bkv - b * p.Hkv;
     const int32_t *prefix = sep_prefix + (long)b * (p.L + 1);
     const int32_t *idx = sep_idx + (long)b * p.cap;
     const int32_t *dend = doc_end ? doc_end + (long)b * p.L : nullptr;
@@ -368,13 +364,15 @@ __global__ __launch_bounds__(64 * kWaves) void dkv_fp32_kernel(sepattn_params p,
         const int jr = valid ? j : 0;
         load_row<D>(kf, K + (kvrow0 + jr) * D, g);
         load_row<D>(vf, V + (kvrow0 + jr) * D, g);
+        const float by_qb = reciprocal(n_qb);
         auto run = [&](auto VISIBLE_ONLY) __attribute__((always_inline)) {
 #pragma unroll
             for (int c = 0; c < C; ++c) ak[c] = av[c] = f32x4{0.f, 0.f, 0.f, 0.f};
             for (int it = first + wave; it < last; it += kWaves) {
-                const int h = kv * G + it / n_qb, q0 = q_lo + (it % n_qb) * kT;
+                const int head = last < kSmallQuotient ? __builtin_amdgcn_readfirstlane(small_quotient(it, by_qb)) : it / n_qb;
+                const int h = kv * G + head, q0 = q_lo + (it - head * n_qb) * kT;
                 // last query that sees the key: end of the sequence (document), or of head h's window
-                const int hi = valid ? (far ? end : (int)min((long)end, (long)j + p.n - head_delta(hw, h))) - 1 : -1;
+                const int hi = valid ? (far ? end : (int)min((long)end, (long)j + p.n - ha.of_head(h))) - 1 : -1;
                 if (__ballot(hi >= q0) == 0ull) continue;
                 const long hrow = ((long)b * p.Hq + h) * p.L;
                 f32x4 qf[C], gf[C];
@@ -387,8 +385,10 @@ __global__ __launch_bounds__(64 * kWaves) void dkv_fp32_kernel(sepattn_params p,
                 for (int i = 0; i < 4; ++i) {
                     qi[i] = min(q0 + 4 * g + i, p.L - 1);
                     lse[i] = LSE[hrow + qi[i]];
-                    Dq[i] = Drow[hrow + qi[i]];
+                    if constexpr (!OWN_D) Dq[i] = Drow[hrow + qi[i]];
                 }
+                f32x4 of[C];
+                if constexpr (OWN_D) load_row<D>(of, O + qrow * D, g);
                 // requested with the rows: one memory round trip per item
                 float gt[C][4], qt[C][4];
                 if constexpr (!VISIBLE_ONLY) {
@@ -396,6 +396,16 @@ __global__ __launch_bounds__(64 * kWaves) void dkv_fp32_kernel(sepattn_params p,
                     load_columns<D>(qt, Q + hrow * D, qi, m);
                 }
                 const f32x4 s = row_product<D>(qf, kf), dp = row_product<D>(gf, vf);
+                if constexpr (OWN_D) {  // as in dq_tile, handed to the lanes that hold the row's scores
+                    float Di = 0.f;
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) Di = fmaf(gf[c][e], of[c][e], Di);
+                    Di = group_sum(Di);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) Dq[i] = __shfl(Di, 4 * g + i);
+                }
                 f32x4 pr, ds;
                 bool vis[4];
 #pragma unroll
@@ -464,29 +474,30 @@ __global__ __launch_bounds__(64 * kWaves) void dkv_fp32_kernel(sepattn_params p,
         fq = far_pos(fl, t * kT, idx, p.L) & ~(kT - 1);
         return max(0, G * ((far_last_query(fl, t * kT, idx, p, dend, kT) - fq + kT - 1) / kT));
     };
-    auto inclusive_scan = [&](int v) {
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int u = __shfl_up(v, off);
-            if (lane >= off) v += u;
-        }
-        return v;
-    };
     // the first group of 64 list tiles (all of them up to 1024 list entries) is worked out once for both passes
-    int fq, nq = tile_items(lane, fq), inc = inclusive_scan(nq);
+    int fq, nq = tile_items(lane, fq), inc = lanes_scan(nq);
     long total = __shfl(inc, 63);
     for (int t0 = 64; t0 < NFT; t0 += 64) {
         int unused;
-        total += __shfl(inclusive_scan(tile_items(t0 + lane, unused)), 63);
+        total += __shfl(lanes_scan(tile_items(t0 + lane, unused)), 63);
     }
-    const long slices = min((long)wpg, max(1l, quotient(total, max(kMinItems, G * ((p.L + kT - 1) / kT) / kMaxShare))));
+    const long least = total >> 31 ? total / pl.min_slice : (long)quotient((int)total, pl.by_min_slice);
+    const long slices = min((long)wpg, max(1l, least));
     if (unit >= slices || total == 0) return;
-    const long s0 = quotient(unit * total, slices), s1 = quotient((unit + 1) * total, slices);
+    // slice u is [u total / slices, (u + 1) total / slices); u < slices <= wpg
+    const long whole = quotient(total, slices), over = total - whole * slices;
+    const float by_slices = reciprocal((int)slices), by_total = reciprocal((int)min(total, (long)kSmallQuotient));
+    auto slice_start = [&](long u) { return u * whole + (u * over < kSmallQuotient ? (long)small_quotient((int)(u * over), by_slices) : u * over / slices); };
+    const long s0 = slice_start(unit), s1 = slice_start(unit + 1);
+    auto slice_of = [&](long item) {  // the slice that holds an item
+        const long x = (item + 1) * slices - 1;
+        return (int)(x < kSmallQuotient ? (long)small_quotient((int)x, by_total) : quotient(x, total));
+    };
     long cum = 0;
     for (int t0 = 0; t0 < NFT && cum < s1; t0 += 64) {
         if (t0 > 0) {
             nq = tile_items(t0 + lane, fq);
-            inc = inclusive_scan(nq);
+            inc = lanes_scan(nq);
         }
         unsigned long long pend = __ballot(nq > 0 && cum + inc > s0 && cum + inc - nq < s1);
         for (; pend; pend &= pend - 1) {
@@ -498,9 +509,14 @@ __global__ __launch_bounds__(64 * kWaves) void dkv_fp32_kernel(sepattn_params p,
             const int end = dend ? min(dend[j], p.L) : p.L;
             __syncthreads();  // the tile before has been written out
             if (threadIdx.x < kT) js[m] = j;
-            run_items((int)(max(s0, F) - F), (int)(min(s1, F + items) - F), q_lo, items / G, j, valid, end, true);
+            uint64_t *const word = OWN_D ? reinterpret_cast<uint64_t *>(static_cast<char *>(counters) + ((long)bkv * n_far_tiles + ft) * word_stride) : nullptr;
+            uint64_t seen = 0;
+            if constexpr (OWN_D) {
+                if (threadIdx.x == 0) seen = arrival_seen(word);
+            }
+            run_items((int)(max(s0, F) - F), (int)(min(s1, F + items) - F), q_lo, quotient(items, pl.by_g), j, valid, end, true);
             // slices w0 .. w1 hold the tile
-            const int w0 = (int)quotient((F + 1) * slices - 1, total), w1 = (int)quotient((F + items) * slices - 1, total);
+            const int w0 = slice_of(F), w1 = slice_of(F + items - 1);
             auto to_row = [&](float *dst, float fac) {
                 return [=](int r, int col, f32x4 v) {
                     if (ft * kT + r < fl.NF)
@@ -526,30 +542,70 @@ __global__ __launch_bounds__(64 * kWaves) void dkv_fp32_kernel(sepattn_params p,
             add_waves(av, to_slot(1));
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's part of the slot is where every XCD sees it
             __syncthreads();
-            if (threadIdx.x == 0) last_s = atomicAdd(&counters[(long)bkv * n_far_tiles + ft], 1) == w1 - w0;
+            if constexpr (OWN_D) {
+                if (threadIdx.x == 0) {
+                    arrival_ready(word, seen, one, w1 - w0 + 1);
+                    last_s = arrives_last(word, one, w1 - w0 + 1);
+                    if (last_s) arrival_reset(word);
+                }
+            } else {
+                if (threadIdx.x == 0) last_s = atomicAdd(static_cast<int32_t *>(counters) + (long)bkv * n_far_tiles + ft, 1) == w1 - w0;
+            }
             __syncthreads();
             if (!last_s) continue;
-            for (int e = threadIdx.x; e < 2 * kT * D / 4; e += 64 * kWaves) {
-                const int which = e / (kT * D / 4), r = (e / (D / 4)) % kT, col = (e % (D / 4)) * 4;
-                f32x4 v = {0.f, 0.f, 0.f, 0.f};
-                constexpr int NB = 8;  // slots requested together
+            for (int e = threadIdx.x; e < kT * D / 4; e += 64 * kWaves) {
+                const int r = e / (D / 4), col = (e % (D / 4)) * 4;
+                f32x4 v[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+                constexpr int NB = 8;  // slots requested together, dK and dV
                 for (int w = w0; w <= w1; w += NB) {
-                    float2 x[NB], y[NB];
-#pragma unroll
-                    for (int k = 0; k < NB; ++k) {
-                        const float *src = slot_of(min(w + k, w1), which) + r * D + col;
-                        x[k] = fetch_published(src), y[k] = fetch_published(src + 2);
-                    }
+                    float2 x[NB][2], y[NB][2];
 #pragma unroll
                     for (int k = 0; k < NB; ++k)
-                        if (w + k <= w1) v += f32x4{x[k].x, x[k].y, y[k].x, y[k].y};
+#pragma unroll
+                        for (int which = 0; which < 2; ++which) {
+                            const float *src = slot_of(min(w + k, w1), which) + r * D + col;
+                            x[k][which] = fetch_published(src), y[k][which] = fetch_published(src + 2);
+                        }
+#pragma unroll
+                    for (int k = 0; k < NB; ++k)
+                        if (w + k <= w1)
+#pragma unroll
+                            for (int which = 0; which < 2; ++which)
+                                v[which] += f32x4{x[k][which].x, x[k][which].y, y[k][which].x, y[k][which].y};
                 }
-                if (which == 0) to_row(dK, p.scale)(r, col, v);
-                else to_row(dV, 1.f)(r, col, v);
+                to_row(dK, p.scale)(r, col, v[0]);
+                to_row(dV, 1.f)(r, col, v[1]);
             }
         }
         cum += __shfl(inc, 63);
     }
+}
+
+// dQ by itself, with D_i for the dK/dV kernel, whose counters it clears too
+template <int D, bool HW>
+__global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void dq_fp32_kernel(
+    sepattn_params p, const float *__restrict__ Q, const float *__restrict__ K, const float *__restrict__ V, const float *__restrict__ O,
+    const float *__restrict__ LSE, const float *__restrict__ dO, const int32_t *__restrict__ sep_idx,
+    const int32_t *__restrict__ sep_prefix, const int32_t *__restrict__ doc_start, const int32_t *__restrict__ doc_end,
+    float *__restrict__ dQ, float *__restrict__ Dws, int32_t *__restrict__ counters, long n_counters, Fp32Plan pl, HeadArgs<HW> ha) {
+    __shared__ float xs[kWaves][kT][D + 4];
+    for (long c = (long)blockIdx.x * (64 * kWaves) + threadIdx.x; c < n_counters; c += (long)gridDim.x * (64 * kWaves)) counters[c] = 0;
+    dq_tile<D, HW>(xs, blockIdx.x, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, pl, ha);
+}
+// MERGED: the blocks behind the dK/dV units are dQ tiles (see launch_backward_fp32).
+template <int D, bool HW, bool MERGED>
+__global__ __launch_bounds__(64 * kWaves, D == 64 ? 2 : 1) void dkv_fp32_kernel(
+    sepattn_params p, const float *__restrict__ Q, const float *__restrict__ K, const float *__restrict__ V, const float *__restrict__ O,
+    const float *__restrict__ LSE, const float *__restrict__ dO, const float *__restrict__ Drow, const int32_t *__restrict__ sep_idx,
+    const int32_t *__restrict__ sep_prefix, const int32_t *__restrict__ doc_start, const int32_t *__restrict__ doc_end,
+    float *__restrict__ dQ, float *__restrict__ dK, float *__restrict__ dV, float *__restrict__ partials, void *__restrict__ counters,
+    int n_far_tiles, int wpg, int word_stride, uint64_t one, int n_units, Fp32Plan pl, HeadArgs<HW> ha) {
+    __shared__ float xs[kWaves][kT][D + 4];
+    if (MERGED && (int)blockIdx.x >= n_units)
+        dq_tile<D, HW>(xs, blockIdx.x - n_units, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, nullptr, pl, ha);
+    else
+        dkv_unit<D, HW, MERGED>(xs, p, Q, K, V, O, LSE, dO, Drow, sep_idx, sep_prefix, doc_end, dK, dV, partials, counters, n_far_tiles, wpg,
+                                word_stride, one, pl, ha);
 }
 
 // backward workspace: D_i [B,Hq,L] | one counter per list tile | the slots of the partial sums
@@ -574,14 +630,67 @@ Fp32Workspace fp32_workspace(const sepattn_params &p) {
 
 size_t backward_fp32_workspace(const sepattn_params &p) { return fp32_workspace(p).total; }
 
+static Fp32Plan fp32_plan(const sepattn_params &p) {
+    Fp32Plan pl;
+    pl.n_tiles = (p.L + kT - 1) / kT;
+    pl.G = p.Hq / p.Hkv;
+    pl.min_slice = (int)(pl.G * (long)pl.n_tiles / kMaxShare > kMinItems ? pl.G * (long)pl.n_tiles / kMaxShare : kMinItems);
+    pl.by_tiles = fast_div((uint32_t)pl.n_tiles);
+    pl.by_hq = fast_div((uint32_t)p.Hq);
+    pl.by_g = fast_div((uint32_t)pl.G);
+    pl.by_bkv = fast_div((uint32_t)(p.B * p.Hkv));
+    pl.by_hkv = fast_div((uint32_t)p.Hkv);
+    pl.by_min_slice = fast_div((uint32_t)pl.min_slice);
+    return pl;
+}
+
 int launch_forward_fp32(const sepattn_params &p, const HeadWin &hw, const float *Q, const float *K, const float *V,
                         const int32_t *sep_idx, const int32_t *sep_prefix, const int32_t *doc_start,
                         const int32_t *doc_end, float *O, float *LSE, hipStream_t st) {
     const long tiles = (long)p.B * p.Hq * ((p.L + kT - 1) / kT);
     if (tiles > 0x7FFFFFFFL) return SEPATTN_ERR_SHAPE;
-    auto kernel = p.d == 64 ? fwd_fp32_kernel<64> : fwd_fp32_kernel<128>;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * kWaves), 0, st, p, Q, K, V, sep_idx, sep_prefix, doc_start,
-                       doc_end, O, LSE, hw);
+    auto go = [&](auto kernel, auto ha) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * kWaves), 0, st, p, Q, K, V, sep_idx, sep_prefix, doc_start, doc_end, O, LSE,
+                           fp32_plan(p), ha);
+    };
+    if (any_delta(hw)) go(p.d == 64 ? fwd_fp32_kernel<64, true> : fwd_fp32_kernel<128, true>, HeadArgs<true>{hw, {}});
+    else go(p.d == 64 ? fwd_fp32_kernel<64, false> : fwd_fp32_kernel<128, false>, HeadArgs<false>{});
+    return launch_status();
+}
+
+// One launch or two.  dK/dV needs nothing of dQ but D_i.  Where the blocks are few, both kinds run side by side in one launch and
+// dK/dV forms D_i itself (one more row per item); where they fill the chip anyway, dQ comes first, by itself.  The line, in dQ
+// tiles and band units per compute unit, of which the joint kernel has two at a time at d = 64 and one at d = 128 (registers):
+// backward in us, two launches / one.  d = 64: 2/1 heads, L = 512 (0.4) 21.3 / 15.0, 4 x 4/1 heads, L = 1000 (1.2) 48.0 / 38.1, 8/2
+// heads, L = 1024 (2.5) 49.8 / 40.0, 32/32 heads, L = 200 (3.3) 30.6 / 27.9, 2/2 heads, L = 4000 (3.9) 53.5 / 51.1, 1/1 heads, L = 8192 (4)
+// 90.1 / 93.6, 2 x 8/8 heads, L = 1024 (8) 59.8 / 61.9, 4 x 12/12 heads 167 / 190.  d = 128: 4/4 heads, L = 300 (0.6) 33.7 / 21.2, L = 1024 (2)
+// 34.3 / 31.9, 8/2 heads, L = 1024 (2.5) 89.9 / 79.4, 32/32 heads, L = 200 (3.3) 56.2 / 63.0, 8/8 heads, L = 1024 (4) 79.8 / 88.9.
+template <int D, bool HW>
+int launch_backward_shape(const sepattn_params &p, const HeadArgs<HW> &ha, const float *Q, const float *K, const float *V,
+                          const float *O, const float *LSE, const float *dO, const int32_t *sep_idx, const int32_t *sep_prefix,
+                          const int32_t *doc_start, const int32_t *doc_end, float *dQ, float *dK, float *dV, void *ws, hipStream_t st) {
+    const Fp32Workspace w = fp32_workspace(p);
+    const Fp32Plan pl = fp32_plan(p);
+    char *base = static_cast<char *>(ws);
+    float *Dws = reinterpret_cast<float *>(base);
+    int32_t *counters = reinterpret_cast<int32_t *>(base + w.d_bytes);
+    float *partials = reinterpret_cast<float *>(base + w.d_bytes + w.counter_bytes);
+    const long q_tiles = (long)p.B * p.Hq * pl.n_tiles, k_units = (long)p.B * p.Hkv * (w.wpg + pl.n_tiles);
+    if (q_tiles > 0x7FFFFFFFL || k_units > 0x7FFFFFFFL) return SEPATTN_ERR_SHAPE;
+    const dim3 block(64 * kWaves);
+    // the words in which slices are counted take the place of D_i, a cache line each where there is room
+    const int stride = (size_t)w.n_counters * 128 <= w.d_bytes ? 128 : 8;
+    const long most = (D == 64 ? 15 : 10) * (long)compute_units() / 4;
+    if (q_tiles + (long)p.B * p.Hkv * pl.n_tiles <= most && (size_t)w.n_counters * stride <= w.d_bytes && !being_captured(st)) {
+        hipLaunchKernelGGL((dkv_fp32_kernel<D, HW, true>), dim3((unsigned)(k_units + q_tiles)), block, 0, st, p, Q, K, V, O, LSE, dO, nullptr, sep_idx,
+                           sep_prefix, doc_start, doc_end, dQ, dK, dV, partials, Dws, w.n_far_tiles, w.wpg, stride, launch_number(), (int)k_units, pl, ha);
+        return launch_status();
+    }
+    hipLaunchKernelGGL((dq_fp32_kernel<D, HW>), dim3((unsigned)q_tiles), block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start,
+                       doc_end, dQ, Dws, counters, w.n_counters, pl, ha);
+    if (hipGetLastError() != hipSuccess) return SEPATTN_ERR_HIP;
+    hipLaunchKernelGGL((dkv_fp32_kernel<D, HW, false>), dim3((unsigned)k_units), block, 0, st, p, Q, K, V, O, LSE, dO, Dws, sep_idx, sep_prefix,
+                       doc_start, doc_end, dQ, dK, dV, partials, counters, w.n_far_tiles, w.wpg, 0, 0ull, (int)k_units, pl, ha);
     return launch_status();
 }
 
@@ -589,22 +698,11 @@ int launch_backward_fp32(const sepattn_params &p, const HeadWin &hw, const float
                          const float *O, const float *LSE, const float *dO, const int32_t *sep_idx,
                          const int32_t *sep_prefix, const int32_t *doc_start, const int32_t *doc_end, float *dQ,
                          float *dK, float *dV, void *ws, hipStream_t st) {
-    const Fp32Workspace w = fp32_workspace(p);
-    char *base = static_cast<char *>(ws);
-    float *Dws = reinterpret_cast<float *>(base);
-    int32_t *counters = reinterpret_cast<int32_t *>(base + w.d_bytes);
-    float *partials = reinterpret_cast<float *>(base + w.d_bytes + w.counter_bytes);
-    const long tiles = (p.L + kT - 1) / kT, q_tiles = (long)p.B * p.Hq * tiles, k_units = (long)p.B * p.Hkv * (w.wpg + tiles);
-    if (q_tiles > 0x7FFFFFFFL || k_units > 0x7FFFFFFFL) return SEPATTN_ERR_SHAPE;
-    const dim3 block(64 * kWaves);
-    auto dq = p.d == 64 ? dq_fp32_kernel<64> : dq_fp32_kernel<128>;
-    hipLaunchKernelGGL(dq, dim3((unsigned)q_tiles), block, 0, st, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start,
-                       doc_end, dQ, Dws, counters, w.n_counters, hw);
-    if (hipGetLastError() != hipSuccess) return SEPATTN_ERR_HIP;
-    auto dkv = p.d == 64 ? dkv_fp32_kernel<64> : dkv_fp32_kernel<128>;
-    hipLaunchKernelGGL(dkv, dim3((unsigned)k_units), block, 0, st, p, Q, K, V, LSE, dO, Dws, sep_idx, sep_prefix, doc_end, dK,
-                       dV, partials, counters, w.n_far_tiles, w.wpg, hw);
-    return launch_status();
+    auto go = [&](auto launch, auto ha) {
+        return launch(p, ha, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, dK, dV, ws, st);
+    };
+    if (any_delta(hw)) return go(p.d == 64 ? launch_backward_shape<64, true> : launch_backward_shape<128, true>, HeadArgs<true>{hw, {}});
+    return go(p.d == 64 ? launch_backward_shape<64, false> : launch_backward_shape<128, false>, HeadArgs<false>{});
 }
 
 }  // namespace sepattn

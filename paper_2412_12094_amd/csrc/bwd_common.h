@@ -39,6 +39,17 @@ __host__ __device__ inline int align_down32(int x) { return x & ~31; }
 // dK/dV kernel
 __device__ inline long quotient(long x, long y) { return ((x | y) >> 31) ? x / y : (long)((uint32_t)x / (uint32_t)y); }
 
+// Inclusive sums over the lanes of a wave, in registers (row_shr by 1, 2, 4, 8, then the rows' last lanes handed on).
+__device__ inline int lanes_scan(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15 to rows 1 and 3
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31 to rows 2 and 3
+    return v;
+}
+
 // The far work of one (batch, KV head): for list tile ft (bk = 32 KW consecutive list entries) the
 // "items" (query tile, query head) from the first query that can see the tile's first key
 // to the end of the sequence.  The items of all list tiles, in this order, are cut into slices, at

@@ -188,18 +188,12 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
         }
         return fq < qe ? G * ((qe - fq + BQ - 1) / BQ) : 0;
     };
-    auto inclusive_scan = [&](int v) __attribute__((always_inline)) {
-        static_for<4>([&](auto I) { v += __builtin_amdgcn_update_dpp(0, v, 0x110 | (1 << decltype(I)::value), 0xF, 0xF, false); });  // row_shr
-        v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);  // row_bcast:15: rows 1, 3
-        v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);  // row_bcast:31: rows 2, 3
-        return v;
-    };
     // the first group of 64 list tiles is worked out once, for the total and for the pieces
-    int first_fq, first_nq = tile_items(lane, first_fq), first_inc = inclusive_scan(first_nq);
+    int first_fq, first_nq = tile_items(lane, first_fq), first_inc = lanes_scan(first_nq);
     long far_total = __builtin_amdgcn_readlane(first_inc, 63);
     for (int base = 64; base < NFT; base += 64) {
         int fq;
-        far_total += __builtin_amdgcn_readlane(inclusive_scan(tile_items(base + lane, fq)), 63);
+        far_total += __builtin_amdgcn_readlane(lanes_scan(tile_items(base + lane, fq)), 63);
     }
     // Slices.  Where the band units do not divide among the workgroups, the first `heavy` have one more than the others,
     // and far work goes to those others first, as much as a band unit costs (in items, with its start).  Without that
@@ -254,7 +248,7 @@ __global__ __launch_bounds__(128 * KW, KW == 4 ? 1 : (D == 64 ? 3 : 2)) void dkv
                     int inc = first_inc;
                     if (HW || grp_base > 0) {  // head-wise: once more, rather than registers that d = 64 does not have
                         g_nq = tile_items(grp_base + lane, g_fq);
-                        inc = inclusive_scan(g_nq);
+                        inc = lanes_scan(g_nq);
                     }
                     g_excl = inc - g_nq;
                     pend = __ballot(g_nq > 0 && grp_cum + inc > s0 && grp_cum + g_excl < s1);

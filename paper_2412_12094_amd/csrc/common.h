@@ -46,6 +46,28 @@ __device__ inline float2 fetch_published(const float *src) {
     return __builtin_bit_cast(float2, __hip_atomic_load(reinterpret_cast<const uint64_t *>(src), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 
+// How many slices of one piece of work (the caches of a (sequence, KV head), a list tile) have published their records: a word in
+// the caller's workspace, which nobody clears.  Each slice adds `one`, the number of this launch in the upper 56 bits and 1 in the lower 8; the last one finds
+// (slices - 1) of them and sets the word to 0, so that the next launch finds it so.  Whatever else may stand there
+// (memory never used for this, the sum that calls left which overlapped on one workspace) is no multiple of this
+// launch's `one`: every slice looks at the word before it counts itself in and, if it saw such a value, replaces that by 0;
+// if the exchange fails, another slice of this launch has done so.  Nobody waits for another workgroup.  (A word that
+// every launch has to set first: 0.1 to 0.2 us more.)
+__device__ inline uint64_t arrival_seen(uint64_t *word) { return __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ inline void arrival_ready(uint64_t *word, uint64_t seen, uint64_t one, int nsplit) {
+    const uint64_t n = seen & 0xFF;
+    if (n >= (uint64_t)nsplit || seen != n * one)
+        __hip_atomic_compare_exchange_strong(word, &seen, 0ull, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline bool arrives_last(uint64_t *word, uint64_t one, int nsplit) {
+    return __hip_atomic_fetch_add(word, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint64_t)(nsplit - 1) * one;
+}
+__device__ inline void arrival_reset(uint64_t *word) { __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+uint64_t launch_number();  // `one` of a launch (api.hip)
+// A captured launch runs with the same arguments at every replay, so it has no number of its own to count its slices under.
+bool being_captured(hipStream_t st);
+
 // number of compute units of the current device (queried once per device; 256 if the query fails)
 int compute_units();
 

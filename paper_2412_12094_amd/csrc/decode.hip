@@ -327,15 +327,6 @@ size_t decode_workspace(const sepkv_params &p) {
     return arrival + align_up((size_t)p.S * p.Hq * nsplit * (p.d + 2) * sizeof(float), 256);
 }
 
-// A captured launch runs with the same arguments at every replay, so it has no number of its own to count its slices under
-// (decode_wide.hip); its slices are added by a merge launch.
-static bool being_captured(hipStream_t st) {
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
-    discard_stale_hip_error();  // the null stream while another stream is being captured: the launch reports that
-    return false;
-}
-
 template <typename T>
 int launch_decode_valu(const sepkv_params &p, const void *q, const void *Kc, const void *Vc, const int32_t *sizes,
                        const float *rope, int n_pos, void *out, float *lse, float *part, hipStream_t st) {
@@ -356,7 +347,7 @@ int launch_decode(const sepkv_params &p, const void *q, const void *Kc, const vo
         DecodeWideShape shape = {1, 0, false};
         if (wide) {
             shape = decode_wide_shape(p, rope != nullptr, compute_units());
-            shape.add = shape.add && !being_captured(st);
+            shape.add = shape.add && !being_captured(st);  // else a merge launch adds the slices
         }
         const int nsplit = wide ? shape.nsplit : decode_mfma_nsplit(p);
         const int rc = wide ? launch_decode_wide(p, shape, (const T *)q, (const T *)Kc, (const T *)Vc, sizes, rope, n_pos, (T *)out, lse, part, st)

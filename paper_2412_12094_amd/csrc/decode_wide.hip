@@ -35,9 +35,6 @@
 // column l%16, rows 4g..4g+3.  Row 4g+i of score tile t (t = 0, 1) is row 8g+4t+i of the block, so that
 // the two tiles' registers of lane group g are rows 8g..8g+7, exactly the k-slots the group holds of the
 // probabilities as B operand of the output contraction: no exchange between lanes.
-#include <atomic>
-#include <chrono>
-
 #include "common.h"
 #include "mfma_common.h"
 #include "decode_common.h"
@@ -86,24 +83,6 @@ __device__ inline float half_row_max(float x) {
 #pragma clang diagnostic ignored "-Wint-to-pointer-cast"
 __device__ inline f32x4 lds_read_f4(uint32_t addr) { return *(const f32x4 __attribute__((address_space(3))) *)addr; }
 #pragma clang diagnostic pop
-
-// How many slices of a (sequence, KV head) have published their records: a word in the caller's workspace, which nobody
-// clears.  Each slice adds `one`, the number of this launch in the upper 56 bits and 1 in the lower 8; the last one finds
-// (slices - 1) of them and sets the word to 0, so that the next launch finds it so.  Whatever else may stand there
-// (memory never used for this, the sum that calls left which overlapped on one workspace) is no multiple of this
-// launch's `one`: every slice looks at the word before it counts itself in and, if it saw such a value, replaces that by 0;
-// if the exchange fails, another slice of this launch has done so.  Nobody waits for another workgroup.  (A word that
-// every launch has to set first: 0.1 to 0.2 us more.)
-__device__ inline uint64_t arrival_seen(uint64_t *word) { return __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-__device__ inline void arrival_ready(uint64_t *word, uint64_t seen, uint64_t one, int nsplit) {
-    const uint64_t n = seen & 0xFF;
-    if (n >= (uint64_t)nsplit || seen != n * one)
-        __hip_atomic_compare_exchange_strong(word, &seen, 0ull, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ inline bool arrives_last(uint64_t *word, uint64_t one, int nsplit) {
-    return __hip_atomic_fetch_add(word, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint64_t)(nsplit - 1) * one;
-}
-__device__ inline void arrival_reset(uint64_t *word) { __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // ADD: several slices, added by the workgroup that finishes last.  Otherwise one slice, or the records are left to a merge launch.
 // The arguments fill 120 bytes, so that what the kernel reads of them, the grid's size behind them included, is two cache
@@ -556,13 +535,6 @@ DecodeWideShape decode_wide_shape(const sepkv_params &p, bool rope, int units) {
         if (nb - per >= pays) return {ns, d64 == 1 || per <= 4 ? 4 : 8, ns <= kDwMostAdded && row <= 1024 && ns * row <= 8192};
     }
     return {1, nb <= 4 || pairs > (long)units * d64 ? 4 : 8, false};
-}
-
-// What each slice of one launch adds to its word: a number in the upper 56 bits that no two launches of a process share (those of
-// another process, or whatever else memory may hold, meet it with probability 2^-56), and 1.
-static uint64_t launch_number() {
-    static std::atomic<uint64_t> number{(uint64_t)std::chrono::system_clock::now().time_since_epoch().count()};
-    return (number.fetch_add(1, std::memory_order_relaxed) * 0x9E3779B97F4A7C15ull) << 8 | 1;
 }
 
 int launch_decode_wide(const sepkv_params &p, const DecodeWideShape &shape, const uint16_t *q, const uint16_t *Kc, const uint16_t *Vc,
