@@ -183,6 +183,20 @@ __device__ inline int far_last_query(const FarList &fl, int f, const int32_t *__
     return min(max(dend[far_pos(fl, last, idx, p.L)], 0), p.L);
 }
 
+// Adds the partials of a dK/dV pass of the four-wave shape with `wpg` workgroups per (batch, KV head).
+int launch_dkv_combine_bf16(const sepattn_params &p, const int32_t *sep_idx, const int32_t *sep_prefix, const int32_t *doc_end,
+                            uint16_t *dK, uint16_t *dV, const float *farK, const float *farV, const int32_t *piece_tab, int wpg, int split,
+                            hipStream_t st);
+
+// The backward of a small call: dQ and dK/dV in one launch (bwd_joint.h).  dq_wpg: workgroups per group of the dQ part, 0: not such a call.
+int joint_dq_workgroups(const sepattn_params &p, const HeadWin &hw, bool docs);
+int launch_joint_64(const sepattn_params &p, int dq_wpg, const uint16_t *Q, const uint16_t *K, const uint16_t *V, const uint16_t *O, const float *LSE,
+                    const uint16_t *dO, const int32_t *sep_idx, const int32_t *sep_prefix, const int32_t *doc_start, const int32_t *doc_end,
+                    uint16_t *dQ, uint16_t *dK, uint16_t *dV, float *Dws, float *Lws, float *farK, float *farV, int32_t *piece_tab, hipStream_t st);
+int launch_joint_128(const sepattn_params &p, int dq_wpg, const uint16_t *Q, const uint16_t *K, const uint16_t *V, const uint16_t *O, const float *LSE,
+                     const uint16_t *dO, const int32_t *sep_idx, const int32_t *sep_prefix, const int32_t *doc_start, const int32_t *doc_end,
+                     uint16_t *dQ, uint16_t *dK, uint16_t *dV, float *Dws, float *Lws, float *farK, float *farV, int32_t *piece_tab, hipStream_t st);
+
 // doc_end: packed documents ([B, L], p.a == 0), or nullptr
 int launch_dkv_bf16(const sepattn_params &p, const HeadWin &hw, const uint16_t *Q, const uint16_t *K, const uint16_t *V,
                     const float *lse2, const uint16_t *dO, const float *Dws, const int32_t *sep_idx,
