@@ -85,8 +85,7 @@ struct DkvLds {
     static constexpr int kRows = KW == 2 ? 32 : 64, kTiles = 4;
     alignas(1024) uint16_t Qs[kTiles][kRows * D];
     alignas(1024) uint16_t dOs[kTiles][kRows * D];
-    alignas(256) float lse_s[kTiles][kRows];
-    alignas(256) float d_s[kTiles][kRows];
+    alignas(256) float row_s[2][kTiles][2][64];  // LSE*log2e, -D of a tile's one or two blocks: 32 values twice
     alignas(1024) uint16_t Pex[KW][2][2][64 * 8];  // [key block][step parity][k-half][lane*8], bf16
 };
 // bkv, w_id: (batch, KV head) and number of the workgroup (head-wise windows: bkv is the block's number)
@@ -114,17 +113,14 @@ __device__ __forceinline__ void dkv_work(
     // (dS-waves behind the barrier 163, P-waves 169); 28/4 heads, 3 x L = 3077 152 / 152 (154, 160); packed 163 / 162.
     constexpr int LOADER = KW == 4 ? 0 : 1;
     constexpr int LOADS = BQ / (RPL * KW);   // wave-wide loads per loading wave per tensor per tile
-    constexpr int RVL = (2 * BQ / 16) / KW;  // loads of sixteen row values (LSE*log2e or -D) per loading wave per tile
     constexpr int KSTEPS = D / 16;
     constexpr int DB = D / 32;
     constexpr int TILE = BQ * D;
     constexpr int NBUF = DkvLds<D, KW>::kTiles;
-    static_assert(LOADS >= 1 && LOADS * RPL * KW == BQ && RVL >= 1 && RVL * 16 * KW == 2 * BQ, "tile must divide among the waves");
+    static_assert(LOADS * RPL * KW == BQ && 2 * BPT == KW, "tile must divide among the waves");
 
     auto &Qs = lds.Qs;
     auto &dOs = lds.dOs;
-    auto &lse_s = lds.lse_s;
-    auto &d_s = lds.d_s;
     auto &Pex = lds.Pex;
 
     const int tid = threadIdx.x, lane = tid & 63;
@@ -176,7 +172,7 @@ __device__ __forceinline__ void dkv_work(
     // index 2*ks + hh and the k-step only enters through bits 1..3 of it, so fragment ks sits at
     // (fragment 0) ^ (32 * ks); tile and block bases are multiples of 1 KB, so the XOR commutes with
     // adding them.
-    const uint32_t q_base = lds_addr(&Qs[0][0]), do_base = lds_addr(&dOs[0][0]);
+    const uint32_t q_base = lds_addr(&Qs[0][0]), do_base = lds_addr(&dOs[0][0]), row_base = lds_addr(&lds.row_s[0][0][0][0]);
     const uint32_t t1_base = (role == 0 ? q_base : do_base) + lds_off_a<kSwzBoth, D>(a_row, hh);
     const uint32_t t2_base = role == 0 ? do_base : q_base;
     uint32_t ktr0[DB], ktr1[DB];
@@ -396,64 +392,66 @@ __device__ __forceinline__ void dkv_work(
 
         // tile tt -> LDS buffer tt%4: the loading wave of key block kbw fills rows (LOADS*kbw + u)*RPL ..
         // +RPL-1 with one wave-wide direct load per tensor; a lane owns physical chunk lane%CH of its row and
-        // fetches the logical chunk the permutation maps there.  Rows past the sequence end are clamped (they
-        // are masked by the [lo, hi] test: hi <= L-1).  Tiles are issued in order, head by head: the next one
-        // is query tile iss_qt of the head whose rows begin at iss_head (iss_g: the head of the first).
+        // fetches the logical chunk the permutation maps there, and the 32 row values (LSE*log2e or -D) of one block with one
+        // load.  Tiles are issued in order, head by head: the next one is query tile iss_qt of the head iss_g (at first) and
+        // begins iss_off bytes into Q and dO.  Its address is the same for all lanes, the lanes' parts are constants: 40
+        // instructions a tile, where one address per load took 125, on the path of the wave that the others wait for.  A tile that reaches past the sequence's end clamps its rows (they are masked by the [lo, hi] test: hi <= L-1).
+        // dK/dV in us, before / now: 32/8 heads, d = 128, n = 256, L = 8192 218 / 210, L = 4096 86.5 / 83.7, n = 512, L = 16384 681 / 662; 28/4
+        // heads, 3 x L = 3077 137.7 / 132.4; 8 x 12/12 heads, L = 2048, d = 64 61.2 / 59.4.
         int iss_tt = 0, iss_g = item0 < kSmallQuotient ? __builtin_amdgcn_readfirstlane(small_quotient(item0, reciprocal(n_qt))) : item0 / n_qt;
         const int q0_tile = item0 - iss_g * n_qt;
         int iss_qt = q0_tile;
         if (PARTS && !FAR) iss_g = (unit - quotient(unit, sl.by_split) * split) * Gs;  // the part's first head
-        size_t iss_head = (((long)b * p.Hq + kv * G + iss_g) * (long)p.L) * ROWB;  // byte offset of the head's rows in Q and dO
+        size_t iss_off = ((((long)b * p.Hq + kv * G + iss_g) * (long)p.L) + q_lo + iss_qt * BQ) * ROWB;
+        const int n_whole = (p.L - q_lo) / BQ;  // tiles of a head that end within the sequence
+        const size_t to_next_head = ((size_t)p.L - (size_t)(n_qt - 1) * BQ) * ROWB;
         auto issue_tile = [&]() {
             if (role == LOADER) {
-                const int buf = iss_tt % NBUF;
-                const int qbase = q_lo + iss_qt * BQ;
-                static_for<LOADS>([&](auto U) {
-                    constexpr int u = U;
-                    // (uniform base of the head) + 32-bit byte offset; the loads go through inline assembly
-                    // so that the compiler does not make every LDS read wait for all of them
-                    uint32_t off = my_off;
-                    asm volatile("" : "+v"(off));  // one register for all rows, not one each
-                    off = (uint32_t)qbase * ROWB + ((off ^ (u * (D == 128 ? 16u : 32u))) + u * RPL * ROWB);
-                    off = min(off, ((uint32_t)(p.L - 1) * ROWB) | (off & (ROWB - 1)));
-                    const int wave_off = (LOADS * kbw + u) * RPL * D;
-                    dma_to_lds_16(reinterpret_cast<const char *>(Q) + iss_head, off, lds_addr(&Qs[buf][wave_off]));
-                    dma_to_lds_16(reinterpret_cast<const char *>(dO) + iss_head, off, lds_addr(&dOs[buf][wave_off]));
-                });
-                // the BQ + BQ row values (LSE*log2e, -D) in groups of sixteen: group g holds rows
-                // 16 (g % (BQ/16)) .. +15 of LSE*log2e (g < BQ/16) or of -D
+                const uint32_t buf = iss_tt & (NBUF - 1);
+                const uint32_t to = buf * (TILE * 2) + kbw * (LOADS * RPL * ROWB);
+                const int which = kbw / BPT, half = kbw % BPT;
+                const char *qp = reinterpret_cast<const char *>(Q) + iss_off, *dop = reinterpret_cast<const char *>(dO) + iss_off;
+                const char *rp = reinterpret_cast<const char *>(which ? Dws : LSE2) + iss_off / (ROWB / 4);
+                uint32_t off[LOADS], row = 4u * (32 * half + kj);
 #pragma unroll
-                for (int v = 0; v < RVL; ++v) {
-                    constexpr int GPT = BQ / 16;  // groups per tensor
-                    const int g = kbw * RVL + v, part = g % GPT;
-                    const char *src = reinterpret_cast<const char *>(g < GPT ? LSE2 : Dws) + iss_head / (ROWB / 4);
-                    float *dst = g < GPT ? &lse_s[buf][16 * part] : &d_s[buf][16 * part];
-                    if (lane < 16) dma_to_lds_4(src, (uint32_t)min(qbase + 16 * part + lane, p.L - 1) * 4u, lds_addr(dst));
+                for (int u = 0; u < LOADS; ++u) off[u] = my_off ^ (u * (D == 128 ? 16u : 32u));
+                if (iss_qt < n_whole) {
+                    dma_to_lds_16_rows(qp, off, q_base + to);
+                    dma_to_lds_16_rows(dop, off, do_base + to);
+                } else {
+                    const uint32_t last = p.L - q_lo - iss_qt * BQ - 1;  // row of the tile that is the sequence's last
+                    static_for<LOADS>([&](auto U) {
+                        constexpr int u = U;
+                        off[u] = min(off[u] + u * 1024u, last * ROWB | (off[u] & (ROWB - 1)));
+                        dma_to_lds_16(qp, off[u], q_base + to + u * 1024u);
+                        dma_to_lds_16(dop, off[u], do_base + to + u * 1024u);
+                    });
+                    row = min(row, 4u * last);
                 }
+                dma_to_lds_4(rp, row, row_base + ((which * NBUF + buf) * 2 + half) * 256);
             }
             ++iss_tt;
-            if (++iss_qt == n_qt) {
-                iss_qt = 0;
-                iss_head += (size_t)p.L * ROWB;
-            }
+            ++iss_qt;
+            iss_off += iss_qt == n_qt ? to_next_head : (size_t)(BQ * ROWB);
+            if (iss_qt == n_qt) iss_qt = 0;
         };
         // wait until at most the wave's loads of the n_out newest tiles are still in flight: loads complete in the
-        // order they were issued, and a wave of the loading role issues LW = 2*LOADS + RVL of them per tile.  The
+        // order they were issued, and a wave of the loading role issues LW = 2*LOADS + 1 of them per tile.  The
         // other waves issue none (at the start of a piece they wait for their resident rows here).
         auto wait_tiles = [&](int n_out) __attribute__((always_inline)) {
-            constexpr int LW = 2 * LOADS + RVL;
-            static_assert(LW == 6 || LW == 10, "wait counts below are written for 6 or 10 loads per wave and tile");
+            constexpr int LW = 2 * LOADS + 1;
+            static_assert(LW == 5 || LW == 9, "wait counts below are written for 5 or 9 loads per wave and tile");
             if (n_out <= 0 || role != LOADER) {
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             } else if (n_out == 1) {
-                if constexpr (LW == 6) asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
-                else asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
+                if constexpr (LW == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(9)" ::: "memory");
             } else if (n_out == 2) {
-                if constexpr (LW == 6) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
-                else asm volatile("s_waitcnt vmcnt(20)" ::: "memory");
+                if constexpr (LW == 5) asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(18)" ::: "memory");
             } else {
-                if constexpr (LW == 6) asm volatile("s_waitcnt vmcnt(18)" ::: "memory");
-                else asm volatile("s_waitcnt vmcnt(30)" ::: "memory");
+                if constexpr (LW == 5) asm volatile("s_waitcnt vmcnt(15)" ::: "memory");
+                else asm volatile("s_waitcnt vmcnt(27)" ::: "memory");
             }
         };
 
@@ -525,7 +523,7 @@ __device__ __forceinline__ void dkv_work(
             const int tp = __builtin_amdgcn_readlane(sch_t, l);
             k.r0 = r0p & ~31;
             k.full = r0p & 1;
-            k.rv = ((r0p >> 2) & 3) * BQ + ((r0p >> 1) & 1) * 32;
+            k.rv = (r0p & 14) << 5;
             k.ps = st_n & 1;
             k.dlt = HW ? __builtin_amdgcn_readlane(sch_d, l) : 0;
             lo_cur = tp >> 2;
@@ -629,7 +627,7 @@ __device__ __forceinline__ void dkv_work(
         };
         // the sixteen per-row values (LSE*log2e or D) of the block's rows held by this lane
         auto read_rowvals = [&](const Blk &k, f32x16 &rv) __attribute__((always_inline)) {
-            const float *rowval = (role == 0 ? &lse_s[0][0] : &d_s[0][0]) + k.rv;
+            const float *rowval = &lds.row_s[role == 0 ? 0 : 1][0][0][0] + k.rv;
 #pragma unroll
             for (int half = 0; half < 2; ++half) {
                 const int base = 16 * half + 8 * hh;
@@ -685,10 +683,12 @@ __device__ __forceinline__ void dkv_work(
         // interval after it reads the blocks of that step (second contraction) and of the next one
         // (first contraction): every wave first waits for its share of the tiles the next step needs,
         // and in that interval the buffers of the tiles below the lowest one still in use are refilled.
-        auto block_barrier = [&]() __attribute__((always_inline)) {
-            if (hi_next != hi_landed) {
-                wait_tiles(iss_tt - 1 - hi_next);
-                hi_landed = hi_next;
+        auto block_barrier = [&](auto ROLE) __attribute__((always_inline)) {
+            if constexpr (decltype(ROLE)::value == LOADER) {
+                if (hi_next != hi_landed) {
+                    wait_tiles(iss_tt - 1 - hi_next);
+                    hi_landed = hi_next;
+                }
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
             __builtin_amdgcn_s_barrier();
@@ -733,7 +733,7 @@ __device__ __forceinline__ void dkv_work(
                 gemm1(afr, x);
                 if constexpr (R == 0) softmax_and_publish(cur, x, xb);
             }
-            block_barrier();
+            block_barrier(ROLE);
             // one step of the dS-wave: xc holds dP - D of block cur, xn receives that of block nxt
             auto ds_step = [&](f32x16 &xc, f32x16 &xn) __attribute__((always_inline)) {
                 const Blk nxt = next_block();
@@ -754,7 +754,7 @@ __device__ __forceinline__ void dkv_work(
                 __builtin_amdgcn_sched_barrier(0);
                 gemm1_then_gemm2(nxt, a0, a1, xn, cur, xb);
                 refill();
-                block_barrier();
+                block_barrier(ROLE);
                 cur = nxt;
             };
             if constexpr (R == 0) {
@@ -763,7 +763,7 @@ __device__ __forceinline__ void dkv_work(
                     gemm2_then_gemm1(cur, xb, nxt, x);
                     refill();
                     softmax_and_publish(nxt, x, xb);
-                    block_barrier();
+                    block_barrier(ROLE);
                     cur = nxt;
                 }
             } else {

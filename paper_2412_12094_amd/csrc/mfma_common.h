@@ -120,6 +120,24 @@ __device__ inline void dma_to_lds_16_nt(const void *base, uint32_t voff, uint32_
                  : "s"(lds_addr), "v"(voff), "s"(base)
                  : "memory");
 }
+// N such loads of consecutive kilobytes: load u fetches from base + voff[u] + 1024 u (the instruction's offset counts for both
+// addresses) and lands 1024 u behind lds_addr
+template <int N>
+__device__ inline void dma_to_lds_16_rows(const void *base, const uint32_t (&voff)[N], uint32_t lds_addr) {
+    static_assert(N == 2 || N == 4, "");
+    if constexpr (N == 4)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\t"
+                     "global_load_lds_dwordx4 %1, %5\n\tglobal_load_lds_dwordx4 %2, %5 offset:1024\n\t"
+                     "global_load_lds_dwordx4 %3, %5 offset:2048\n\tglobal_load_lds_dwordx4 %4, %5 offset:3072"
+                     :
+                     : "s"(lds_addr), "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(base)
+                     : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\tglobal_load_lds_dwordx4 %2, %3 offset:1024"
+                     :
+                     : "s"(lds_addr), "v"(voff[0]), "v"(voff[1]), "s"(base)
+                     : "memory");
+}
 __device__ inline void dma_to_lds_4(const void *base, uint32_t voff, uint32_t lds_addr) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
                  :
