@@ -395,7 +395,8 @@ __device__ __forceinline__ void dkv_work(
         // fetches the logical chunk the permutation maps there, and the 32 row values (LSE*log2e or -D) of one block with one
         // load.  Tiles are issued in order, head by head: the next one is query tile iss_qt of the head iss_g (at first) and
         // begins iss_off bytes into Q and dO.  Its address is the same for all lanes, the lanes' parts are constants: 40
-        // instructions a tile, where one address per load took 125, on the path of the wave that the others wait for.  A tile that reaches past the sequence's end clamps its rows (they are masked by the [lo, hi] test: hi <= L-1).
+        // instructions a tile, where one address per load took 125, on the path of the wave that the others wait for.  A tile that
+        // reaches past the sequence's end clamps its rows (they are masked by the [lo, hi] test: hi <= L-1).
         // dK/dV in us, before / now: 32/8 heads, d = 128, n = 256, L = 8192 218 / 210, L = 4096 86.5 / 83.7, n = 512, L = 16384 681 / 662; 28/4
         // heads, 3 x L = 3077 137.7 / 132.4; 8 x 12/12 heads, L = 2048, d = 64 61.2 / 59.4.
         int iss_tt = 0, iss_g = item0 < kSmallQuotient ? __builtin_amdgcn_readfirstlane(small_quotient(item0, reciprocal(n_qt))) : item0 / n_qt;
@@ -798,43 +799,53 @@ __device__ __forceinline__ void dkv_work(
         // partial (slot w + ft, row = entry within the list tile); a band unit finishes keys that are
         // not on the far list and writes the band partial (one row per list entry, after the slots)
         // of those that are.
+        // The sums go through LDS (the ring, 32 fp32 rows per wave, chunks of 16 bytes permuted by the row) and leave as whole
+        // rows: stored as they lie in the accumulators, an instruction is 64 scattered pieces of 16 bytes, which took 3400 to
+        // 9400 cycles a piece and held up the next piece's loads behind them.
+        // @FIG2@
         const float oscale = role == 0 ? 1.f : p.scale;
         float *farX = role == 0 ? farV : farK;
-        long part_row = (long)(w_id + ft) * BK + 32 * kbw + kj;
-        bool to_partial = FAR;
-        if (PARTS && !FAR) {
-            to_partial = true;
-            part_row = (long)fg.NP * BK + (long)unit * BK + 32 * kbw + kj;
-        } else if (!FAR && valid) {
+        uint16_t *outX = role == 0 ? dV : dK;
+        int row = -1;  // band unit: twice the row, plus one where it is a partial
+        if (!FAR && !PARTS && valid) {
             const int f = far_index(fl, prefix, j);
-            if (f >= 0 && far_first_query(fl, f, idx, p, BK) < far_last_query(fl, f, idx, p, dend, BK)) {
-                to_partial = true;
-                part_row = (long)fg.NP * BK + f;
-            }
+            const bool partial = f >= 0 && far_first_query(fl, f, idx, p, BK) < far_last_query(fl, f, idx, p, dend, BK);
+            row = partial ? 2 * (fg.NP * BK + f) + 1 : 2 * j;
         }
-        if (valid) {
-            if (to_partial) {
-                const long prow = (part0 + part_row) * D;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        {
+            constexpr int RCH = D / 4, RPI = 64 / RCH;  // chunks of a row, rows per instruction
+            const uint32_t stage = q_base + wave * (32 * D * 4);
+            int ln = lane;
+            asm volatile("" : "+v"(ln));  // the addresses are formed here, not kept through the loop above
+            const uint32_t to = stage + (ln & 31) * (D * 4) + (((ln >> 5) ^ (ln & 31 & (RCH - 1))) * 16);
 #pragma unroll
-                for (int db = 0; db < DB; ++db)
+            for (int db = 0; db < DB; ++db)
 #pragma unroll
-                    for (int i4 = 0; i4 < 4; ++i4) {
-                        const int col = db * 32 + 8 * i4 + 4 * hh;
-                        const float4 a = {acc[db][4 * i4] * oscale, acc[db][4 * i4 + 1] * oscale,
-                                          acc[db][4 * i4 + 2] * oscale, acc[db][4 * i4 + 3] * oscale};
-                        *reinterpret_cast<float4 *>(farX + prow + col) = a;
-                    }
+                for (int i4 = 0; i4 < 4; ++i4)
+                    lds_write_b128_at(to ^ ((db * 8 + 2 * i4) * 16), f32x4{acc[db][4 * i4] * oscale, acc[db][4 * i4 + 1] * oscale,
+                                                                           acc[db][4 * i4 + 2] * oscale, acc[db][4 * i4 + 3] * oscale});
+            const int sub = ln / RCH, c = ln % RCH;
+            const uint32_t from = stage + sub * (D * 4) + ((c ^ sub) * 16);
+            auto rows_at = [&](int it) __attribute__((always_inline)) {  // rows RPI it .. of the wave's 32
+                return lds_read_f32x4_at((from ^ (RPI * it % RCH * 16)) + it * 1024);
+            };
+            if (FAR || PARTS) {
+                // whole slots: rows of no key are written with them and read by nobody
+                float *dst = farX + (part0 + (FAR ? (long)(w_id + ft) * BK : ((long)fg.NP + unit) * BK) + 32 * kbw) * D + 4 * ln;
+#pragma unroll
+                for (int it = 0; it < 32 / RPI; ++it) *reinterpret_cast<f32x4 *>(dst + it * 256) = rows_at(it);
             } else {
-                uint16_t *orow = (role == 0 ? dV : dK) + (kvrow0 + j) * D;
 #pragma unroll
-                for (int db = 0; db < DB; ++db)
-#pragma unroll
-                    for (int i4 = 0; i4 < 4; ++i4) {
-                        const int col = db * 32 + 8 * i4 + 4 * hh;
-                        *reinterpret_cast<uint2 *>(orow + col) =
-                            pack_bf16x4(acc[db][4 * i4] * oscale, acc[db][4 * i4 + 1] * oscale,
-                                        acc[db][4 * i4 + 2] * oscale, acc[db][4 * i4 + 3] * oscale);
+                for (int it = 0; it < 32 / RPI; ++it) {
+                    const f32x4 x = rows_at(it);
+                    const int r = __shfl(row, it * RPI + sub);
+                    if (r >= 0) {
+                        if (r & 1) *reinterpret_cast<f32x4 *>(farX + (part0 + (r >> 1)) * D + 4 * c) = x;
+                        else *reinterpret_cast<uint2 *>(outX + (kvrow0 + (r >> 1)) * D + 4 * c) = pack_bf16x4(x[0], x[1], x[2], x[3]);
                     }
+                }
             }
         }
     }  // pieces

@@ -191,6 +191,12 @@ __device__ inline uint32_t lds_addr(const void *p) {
 __device__ inline bf16x8 lds_read_b128_at(uint32_t addr) {
     return *(const bf16x8 __attribute__((address_space(3))) *)addr;
 }
+__device__ inline f32x4 lds_read_f32x4_at(uint32_t addr) {
+    return *(const f32x4 __attribute__((address_space(3))) *)addr;
+}
+__device__ inline void lds_write_b128_at(uint32_t addr, f32x4 x) {
+    *(f32x4 __attribute__((address_space(3))) *)addr = x;
+}
 // two transposed 64-bit reads, `second` bytes apart (the rows r and r+4 of lds_read_a_tr_swz)
 __device__ inline bf16x8 lds_read_tr_at(uint32_t addr, uint32_t second) {
     s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3))) *)addr);
