@@ -801,16 +801,15 @@ __device__ __forceinline__ void dkv_work(
         // of those that are.
         // The sums go through LDS (the ring, 32 fp32 rows per wave, chunks of 16 bytes permuted by the row) and leave as whole
         // rows: stored as they lie in the accumulators, an instruction is 64 scattered pieces of 16 bytes, which took 3400 to
-        // 9400 cycles a piece and held up the next piece's loads behind them.
-        // @FIG2@
+        // 9400 cycles a piece and held up the next piece's loads behind them.  dK/dV in us, scattered / whole rows: 32/8 heads,
+        // d = 128, n = 256, L = 8192 212 / 206, 28/4 heads, 3 x L = 3077 133.4 / 131.2, 8 x 12/12 heads, L = 2048, d = 64 59.6 / 55.8.
         const float oscale = role == 0 ? 1.f : p.scale;
         float *farX = role == 0 ? farV : farK;
         uint16_t *outX = role == 0 ? dV : dK;
-        int row = -1;  // band unit: twice the row, plus one where it is a partial
+        int f = -1;  // entry of the far list whose band partial this key's row is
         if (!FAR && !PARTS && valid) {
-            const int f = far_index(fl, prefix, j);
-            const bool partial = f >= 0 && far_first_query(fl, f, idx, p, BK) < far_last_query(fl, f, idx, p, dend, BK);
-            row = partial ? 2 * (fg.NP * BK + f) + 1 : 2 * j;
+            f = far_index(fl, prefix, j);
+            if (f >= 0 && far_first_query(fl, f, idx, p, BK) >= far_last_query(fl, f, idx, p, dend, BK)) f = -1;
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
@@ -826,25 +825,33 @@ __device__ __forceinline__ void dkv_work(
                 for (int i4 = 0; i4 < 4; ++i4)
                     lds_write_b128_at(to ^ ((db * 8 + 2 * i4) * 16), f32x4{acc[db][4 * i4] * oscale, acc[db][4 * i4 + 1] * oscale,
                                                                            acc[db][4 * i4 + 2] * oscale, acc[db][4 * i4 + 3] * oscale});
-            const int sub = ln / RCH, c = ln % RCH;
-            const uint32_t from = stage + sub * (D * 4) + ((c ^ sub) * 16);
-            auto rows_at = [&](int it) __attribute__((always_inline)) {  // rows RPI it .. of the wave's 32
-                return lds_read_f32x4_at((from ^ (RPI * it % RCH * 16)) + it * 1024);
-            };
             if (FAR || PARTS) {
                 // whole slots: rows of no key are written with them and read by nobody
+                const uint32_t from = stage + ln / RCH * (D * 4) + ((ln % RCH ^ ln / RCH) * 16);  // row ln / RCH
                 float *dst = farX + (part0 + (FAR ? (long)(w_id + ft) * BK : ((long)fg.NP + unit) * BK) + 32 * kbw) * D + 4 * ln;
 #pragma unroll
-                for (int it = 0; it < 32 / RPI; ++it) *reinterpret_cast<f32x4 *>(dst + it * 256) = rows_at(it);
+                for (int it = 0; it < 32 / RPI; ++it)
+                    *reinterpret_cast<f32x4 *>(dst + it * 256) = lds_read_f32x4_at((from ^ (RPI * it % RCH * 16)) + it * 1024);
             } else {
+                // all rows but those of keys on the list (and past the end) as bf16, eight columns a lane
+                constexpr int RB = 512 / D;  // rows per instruction
+                const int sub = ln / (D / 8), c = ln % (D / 8);
+                const uint32_t from = stage + sub * (D * 4) + ((2 * c ^ sub) * 16);
+                uint16_t *dst = outX + (kvrow0 + unit * BK + 32 * kbw) * D + 8 * ln;
+                const uint32_t listed = (uint32_t)__ballot(f >= 0), own = (uint32_t)__ballot(valid && f < 0) >> sub;
 #pragma unroll
-                for (int it = 0; it < 32 / RPI; ++it) {
-                    const f32x4 x = rows_at(it);
-                    const int r = __shfl(row, it * RPI + sub);
-                    if (r >= 0) {
-                        if (r & 1) *reinterpret_cast<f32x4 *>(farX + (part0 + (r >> 1)) * D + 4 * c) = x;
-                        else *reinterpret_cast<uint2 *>(outX + (kvrow0 + (r >> 1)) * D + 4 * c) = pack_bf16x4(x[0], x[1], x[2], x[3]);
+                for (int it = 0; it < 32 / RB; ++it) {
+                    const uint32_t at = (from ^ (RB * it % RCH * 16)) + it * (RB * D * 4);
+                    const f32x4 x = lds_read_f32x4_at(at), y = lds_read_f32x4_at(at ^ 16);
+                    if ((own >> (RB * it)) & 1) {
+                        const uint2 u = pack_bf16x4(x[0], x[1], x[2], x[3]), v = pack_bf16x4(y[0], y[1], y[2], y[3]);
+                        *reinterpret_cast<uint4 *>(dst + it * 512) = uint4{u.x, u.y, v.x, v.y};
                     }
+                }
+                for (uint32_t m = listed; m; m &= m - 1) {
+                    const int r = __ffs(m) - 1;
+                    float *row = farX + (part0 + (long)fg.NP * BK + __builtin_amdgcn_readlane(f, r)) * D;
+                    if (ln < RCH) *reinterpret_cast<f32x4 *>(row + 4 * ln) = lds_read_f32x4_at(stage + r * (D * 4) + ((ln ^ (r % RCH)) * 16));
                 }
             }
         }
