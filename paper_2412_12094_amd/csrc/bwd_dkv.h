@@ -212,13 +212,22 @@ __device__ __forceinline__ void dkv_work(
     auto by = [](long x, FastDiv f, int d) { return x >> 31 ? x / d : (long)quotient((int)x, f); };
     const int heavy = sl.heavy, light = wpg - heavy, min_slice = sl.min_slice;
     const long unit_items = sl.unit_items;
-    long per_heavy = 0;
+    // What is left when the others have that much goes to all in equal parts; where these would be shorter than min_slice,
+    // slices of min_slice go to as many of the first (`n_heavy`, the last of them) as it takes to leave the others no more than
+    // one beyond a unit's cost.  All of it to the others, one workgroup of sixteen got the far work of 47 units' keys: dK/dV and
+    // combine in us, so / now: 32/32 heads, L = 3000, n = 512 178 / 103, 16/8 heads, L = 3856, n = 156 174 / 57, 4 x 32/8 heads, L = 3000,
+    // n = 1024 605 / 483; over 240 calls 1.02 times as fast, level where the units divide evenly.
+    long per_heavy = 0, n_heavy = 0;
     if (heavy) {
         const long rest = max(far_total - unit_items * light, 0l);
         per_heavy = HW ? quotient(rest, wpg) : by(rest, sl.by_wpg, wpg);
+        n_heavy = heavy;
+        if (per_heavy < min_slice) {
+            per_heavy = min_slice;
+            n_heavy = min(max((HW ? quotient(rest, min_slice) : by(rest, sl.by_min_slice, min_slice)) - light, 0l), (long)heavy);
+        }
     }
-    if (per_heavy < min_slice) per_heavy = 0;
-    const long far_light = far_total - per_heavy * heavy;
+    const long far_light = far_total - per_heavy * n_heavy;
     const long n_light = min(max(HW ? quotient(far_light, min_slice) : by(far_light, sl.by_min_slice, min_slice), 1l), (long)light);
     const int w_light = w_id - heavy;
     // the first of the slices w of n_light equal ones: floor(w far_light / n_light), w <= n_light <= wpg, from one division
@@ -227,8 +236,8 @@ __device__ __forceinline__ void dkv_work(
         const long x = w * over;  // < n_light^2
         return w * whole + (x < kSmallQuotient ? (long)small_quotient((int)x, reciprocal((int)n_light)) : x / n_light);
     };
-    const long s0 = w_light < 0 ? w_id * per_heavy : per_heavy * heavy + slice_start(min((long)w_light, n_light));
-    const long s1 = w_light < 0 ? s0 + per_heavy : per_heavy * heavy + slice_start(min(w_light + 1l, n_light));
+    const long s0 = w_light < 0 ? max(w_light + n_heavy, 0l) * per_heavy : per_heavy * n_heavy + slice_start(min((long)w_light, n_light));
+    const long s1 = w_light < 0 ? (w_light + n_heavy < 0 ? 0l : s0 + per_heavy) : per_heavy * n_heavy + slice_start(min(w_light + 1l, n_light));
 
     // iteration state over the pieces: first the far pieces of the slice (list tiles in groups of 64,
     // `pend` = tiles of the current group that overlap the slice and are still to be visited), then
