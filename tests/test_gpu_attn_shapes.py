@@ -118,6 +118,30 @@ def test_bf16_band_units_in_parts(B, Hq, Hkv, L, d, a, n, p):
     run(B, Hq, Hkv, L, d, a, n, p, "bf16")
 
 
+@pytest.mark.parametrize("B,Hq,Hkv,L,d,a,n,p", [
+    (1, 32, 32, 1970, 128, 4, 189, 0.1),  # 31 units, 16 workgroups: one has a unit less and not all far work
+    (1, 32, 32, 1970, 128, 4, 64, 0.9),   # ... enough of it for a slice each
+    (1, 32, 32, 1970, 128, 0, 900, 0.01),  # ... so little that one workgroup has it all
+    (1, 32, 32, 1090, 128, 4, 60, 0.1),   # 18 units: fourteen share it
+    (2, 16, 16, 3000, 64, 4, 100, 0.2),   # 47 units, 24 workgroups
+    (2, 16, 16, 3000, 64, 4, [100] * 8 + [300] * 8, 0.2),
+])
+def test_bf16_far_work_beside_uneven_band_units(B, Hq, Hkv, L, d, a, n, p):
+    run(B, Hq, Hkv, L, d, a, n, p, "bf16")
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,d,a,n,p", [
+    (1, 32, 8, 768, 128, 4, 100, 0.1),  # four heads, 192 query tiles: the last call that runs dQ and dK/dV in one launch
+    (1, 32, 8, 769, 128, 4, 100, 0.1),  # one position more: two launches
+    (2, 8, 4, 1536, 64, 0, 33, 0.1),    # two heads
+    (2, 8, 4, 1537, 64, 0, 33, 0.1),
+    (2, 8, 8, 1536, 64, 4, 70, 0.1),    # one head
+    (2, 8, 8, 1537, 128, 4, 70, 0.1),
+])
+def test_bf16_backward_in_one_launch_and_in_two(B, Hq, Hkv, L, d, a, n, p):
+    run(B, Hq, Hkv, L, d, a, n, p, "bf16")
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("B,Hq,Hkv,L,a,n,p", [
     (1, 4, 1, 2560, 4, 2560, 0.1),                         # four heads; the shortest window that may end before the sequence
