@@ -104,14 +104,16 @@ __device__ __forceinline__ void dkv_work(
     constexpr int RPL = 64 / CH;             // rows covered by one wave-wide 1 KB load
     constexpr int BQ = DkvLds<D, KW>::kRows;  // query rows per LDS tile
     constexpr int BPT = BQ / 32;             // blocks of 32 query rows per tile
-    // The loads of a tile (40 wave-wide ones per compute unit, 16 cycles each, and the waves that issue them stand still
-    // meanwhile) are issued by the waves of one role, and where these have time to spare: with eight waves by the P-waves
-    // in front of their softmax, while the dS-waves multiply; with four, where the P-waves come last to the barrier, by
-    // the dS-waves in front of it (see refill).  By all waves right behind the barrier, where every wave has the longest way
-    // to go, they cost 325 - 590 of 2400 cycles per step.  dK/dV, us, before / now: 32/8 heads, d = 128, L = 8192,
-    // n = 256 (eight waves) 227 / 213, with the dS-waves loading 222; four waves: every fourth KV head full at L = 4096 167 / 158
-    // (dS-waves behind the barrier 163, P-waves 169); 28/4 heads, 3 x L = 3077 152 / 152 (154, 160); packed 163 / 162.
-    constexpr int LOADER = KW == 4 ? 0 : 1;
+    // The loads of a tile (36 wave-wide ones per compute unit, 16 cycles each, and the waves that issue them stand still
+    // meanwhile) are issued where there is time to spare.  With eight waves each role loads the tensor that it reads first, the
+    // P-waves in front of their softmax, the dS-waves in front of the barrier: with all loads on the P-waves these came 300 cycles later to
+    // the barrier of a step of 2000.  With four waves the dS-waves load, in front of the barrier (see refill), although they are the later
+    // ones: the two workgroups of a compute unit fill each other's gaps.  By all waves right behind the barrier, where every wave has
+    // the longest way to go, the loads cost 325 - 590 of 2400 cycles per step.  dK/dV, us, P-waves / each its own: 32/8 heads, d = 128, L = 8192,
+    // n = 256 205.4 / 202.5, L = 12000, n = 128 312 / 300, L = 16384, n = 512 655 / 645, 28/4 heads, L = 8192, n = 1024 297 / 291.  Four waves,
+    // dS-waves / each its own: 28/4 heads, 3 x L = 3077 133 / 136, 32/8 heads, L = 4096, n = 256 82.3 / 83.1.
+    constexpr bool EACH = KW == 4;           // each role loads its own tensor, else the dS-waves both
+    constexpr int TILE_LOADS[2] = {EACH ? 16 / RPL : 0, (EACH ? 1 : 2) * (16 / RPL) + 1};  // wave-wide loads per tile, by role
     constexpr int LOADS = BQ / (RPL * KW);   // wave-wide loads per loading wave per tensor per tile
     constexpr int KSTEPS = D / 16;
     constexpr int DB = D / 32;
@@ -399,7 +401,7 @@ __device__ __forceinline__ void dkv_work(
         const int n_blocks = (st_G - 1) * st_P + nbh;            // steps of the piece
         const int tiles_per_head = FAR ? 0 : n_qt;
 
-        // tile tt -> LDS buffer tt%4: the loading wave of key block kbw fills rows (LOADS*kbw + u)*RPL ..
+        // tile tt -> LDS buffer tt%4: a loading wave of key block kbw fills rows (LOADS*kbw + u)*RPL ..
         // +RPL-1 with one wave-wide direct load per tensor; a lane owns physical chunk lane%CH of its row and
         // fetches the logical chunk the permutation maps there, and the 32 row values (LSE*log2e or -D) of one block with one
         // load.  Tiles are issued in order, head by head: the next one is query tile iss_qt of the head iss_g (at first) and
@@ -416,29 +418,32 @@ __device__ __forceinline__ void dkv_work(
         const int n_whole = (p.L - q_lo) / BQ;  // tiles of a head that end within the sequence
         const size_t to_next_head = ((size_t)p.L - (size_t)(n_qt - 1) * BQ) * ROWB;
         auto issue_tile = [&]() {
-            if (role == LOADER) {
+            if (EACH || role == 1) {
                 const uint32_t buf = iss_tt & (NBUF - 1);
                 const uint32_t to = buf * (TILE * 2) + kbw * (LOADS * RPL * ROWB);
-                const int which = kbw / BPT, half = kbw % BPT;
                 const char *qp = reinterpret_cast<const char *>(Q) + iss_off, *dop = reinterpret_cast<const char *>(dO) + iss_off;
-                const char *rp = reinterpret_cast<const char *>(which ? Dws : LSE2) + iss_off / (ROWB / 4);
-                uint32_t off[LOADS], row = 4u * (32 * half + kj);
+                uint32_t off[LOADS];
 #pragma unroll
                 for (int u = 0; u < LOADS; ++u) off[u] = my_off ^ (u * (D == 128 ? 16u : 32u));
-                if (iss_qt < n_whole) {
-                    dma_to_lds_16_rows(qp, off, q_base + to);
-                    dma_to_lds_16_rows(dop, off, do_base + to);
+                const bool whole = iss_qt < n_whole;
+                const uint32_t last = p.L - q_lo - iss_qt * BQ - 1;  // not whole: row of the tile that is the sequence's last
+                if (whole) {
+                    if (!EACH || role == 0) dma_to_lds_16_rows(qp, off, q_base + to);
+                    if (role == 1) dma_to_lds_16_rows(dop, off, do_base + to);
                 } else {
-                    const uint32_t last = p.L - q_lo - iss_qt * BQ - 1;  // row of the tile that is the sequence's last
                     static_for<LOADS>([&](auto U) {
                         constexpr int u = U;
                         off[u] = min(off[u] + u * 1024u, last * ROWB | (off[u] & (ROWB - 1)));
-                        dma_to_lds_16(qp, off[u], q_base + to + u * 1024u);
-                        dma_to_lds_16(dop, off[u], do_base + to + u * 1024u);
+                        if (!EACH || role == 0) dma_to_lds_16(qp, off[u], q_base + to + u * 1024u);
+                        if (role == 1) dma_to_lds_16(dop, off[u], do_base + to + u * 1024u);
                     });
-                    row = min(row, 4u * last);
                 }
-                dma_to_lds_4(rp, row, row_base + ((which * NBUF + buf) * 2 + half) * 256);
+                if (role == 1) {
+                    const int which = kbw / BPT, half = kbw % BPT;
+                    const char *rp = reinterpret_cast<const char *>(which ? Dws : LSE2) + iss_off / (ROWB / 4);
+                    const uint32_t row = 4u * (32 * half + kj);
+                    dma_to_lds_4(rp, whole ? row : min(row, 4u * last), row_base + ((which * NBUF + buf) * 2 + half) * 256);
+                }
             }
             ++iss_tt;
             ++iss_qt;
@@ -446,23 +451,18 @@ __device__ __forceinline__ void dkv_work(
             if (iss_qt == n_qt) iss_qt = 0;
         };
         // wait until at most the wave's loads of the n_out newest tiles are still in flight: loads complete in the
-        // order they were issued, and a wave of the loading role issues LW = 2*LOADS + 1 of them per tile.  The
-        // other waves issue none (at the start of a piece they wait for their resident rows here).
+        // order they were issued, TILE_LOADS of them per tile.  (A wave that issues none waits here for its resident rows at the
+        // start of a piece.)
         auto wait_tiles = [&](int n_out) __attribute__((always_inline)) {
-            constexpr int LW = 2 * LOADS + 1;
-            static_assert(LW == 5 || LW == 9, "wait counts below are written for 5 or 9 loads per wave and tile");
-            if (n_out <= 0 || role != LOADER) {
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            } else if (n_out == 1) {
-                if constexpr (LW == 5) asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
-                else asm volatile("s_waitcnt vmcnt(9)" ::: "memory");
-            } else if (n_out == 2) {
-                if constexpr (LW == 5) asm volatile("s_waitcnt vmcnt(10)" ::: "memory");
-                else asm volatile("s_waitcnt vmcnt(18)" ::: "memory");
-            } else {
-                if constexpr (LW == 5) asm volatile("s_waitcnt vmcnt(15)" ::: "memory");
-                else asm volatile("s_waitcnt vmcnt(27)" ::: "memory");
-            }
+            auto of = [&](auto LW) __attribute__((always_inline)) {  // LW: the wave's loads of a tile
+                constexpr int lw = decltype(LW)::value;
+                if (n_out <= 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                else if (n_out == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(lw) : "memory");
+                else if (n_out == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * lw) : "memory");
+                else asm volatile("s_waitcnt vmcnt(%0)" ::"n"(3 * lw) : "memory");
+            };
+            if (role == 0) of(IntC<TILE_LOADS[0]>{});
+            else of(IntC<TILE_LOADS[1]>{});
         };
 
         // ---- per-step pieces.  What a wave needs to know about a step (the LDS offset of its block, the
@@ -694,7 +694,7 @@ __device__ __forceinline__ void dkv_work(
         // (first contraction): every wave first waits for its share of the tiles the next step needs,
         // and in that interval the buffers of the tiles below the lowest one still in use are refilled.
         auto block_barrier = [&](auto ROLE) __attribute__((always_inline)) {
-            if constexpr (decltype(ROLE)::value == LOADER) {
+            if constexpr (TILE_LOADS[decltype(ROLE)::value] != 0) {
                 if (hi_next != hi_landed) {
                     wait_tiles(iss_tt - 1 - hi_next);
                     hi_landed = hi_next;
