@@ -40,11 +40,11 @@ PEAK_HBM_GBS = 8000.0      # MI355X HBM3E
 CALIB_BYTES = 256 << 20
 MEASURED_TRAFFIC_BYTES = {
     "forward": 175.6e6,      # cfg3: read 107.4 MB + written 68.2 MB   (algorithmic: 168.8 MB)
-    "bwd_dq": 317.4e6,       # cfg3: read 248.0 MB + written 69.4 MB
-    "bwd_dkv": 551.2e6,      # cfg3: read 476.9 MB (Q, dO tiles re-read by every list tile and band unit) + written 74.3 MB
-    "bwd_combine": 46.6e6,   # cfg3: read 43.9 MB + written 2.8 MB
-    "cfg2_step": 612.2e6,    # mark+compact 0.2 + forward 108.4 + dQ 165.3 + dK/dV 291.1 + combine 47.2 MB (algorithmic: 303.6 MB)
-    "cfg4_forward": 1825.4e6,  # read 1280.2 MB + written 545.3 MB    (algorithmic: 1351 MB)
+    "bwd_dq": 317.3e6,       # cfg3: read 247.9 MB + written 69.4 MB
+    "bwd_dkv": 552.7e6,      # cfg3: read 477.6 MB (Q, dO tiles re-read by every list tile and band unit) + written 75.1 MB
+    "bwd_combine": 46.4e6,   # cfg3: read 43.6 MB + written 2.8 MB
+    "cfg2_step": 612.7e6,    # mark+compact 0.2 + forward 108.2 + dQ 164.0 + dK/dV 293.2 + combine 47.1 MB (algorithmic: 303.6 MB)
+    "cfg4_forward": 1783.5e6,  # read 1238.2 MB + written 545.3 MB    (algorithmic: 1351 MB)
     "evict_move": 42.1e6,    # cfg5: read 21.3 MB + written 20.8 MB by the counters; the kernel loads and stores 10.4 MB each
                              # (a build that counts its stores: 40 704 rows of 256 B), i.e. the counters read twice the bytes of
                              # these scattered 256-byte rows

@@ -135,8 +135,8 @@ int launch_bwd(const sepattn_params &p, const uint16_t *Q, const uint16_t *K, co
 // are at most three eighths as many as the workgroups that fit the chip.  Beyond that, the tiles take from dK/dV the workgroups that its longest
 // units and slices need.  Backward, two launches' time over one's, over 110 calls of two head sizes: up to 64 tiles 1.12 to 1.62 (1.34 in
 // the mean), up to 128 1.19 to 1.55 (1.32), up to 192 1.10 to 1.43 (1.25), up to 256 0.75 to 1.29 (1.04), up to 320 0.84 to 1.04, beyond
-// less.  In us, two / one: 8/2 heads, L = 600, n = 96, d = 128 (38 tiles) 25.6 / 19.2; 2 x 32/32 heads, L = 265, n = 85, d = 64 (192)
-// 24.2 / 22.1; 4 x 8/2 heads, L = 936, n = 657, d = 128 (240) 60.0 / 80.2.
+// less.  In us, two / one: 8/2 heads, L = 600, n = 96, d = 128 (38 tiles) 26.9 / 20.2, d = 64 21.8 / 16.8; 32/8 heads, L = 768, n = 100 (192)
+// 33.3 / 31.1, d = 64 24.3 / 24.3; 12/12 heads, L = 2011, n = 64 (192) 41.4 / 37.1; 4 x 8/2 heads, L = 936, n = 657 (240) 60.0 / 80.2.
 int joint_dq_workgroups(const sepattn_params &p, const HeadWin &hw, bool docs) {
     const QueryShape shape = query_shape(p);
     if (any_delta(hw) || shape.nw != 4 || dkv_key_blocks(p, docs) != 2) return 0;

@@ -12,11 +12,11 @@ namespace sepattn {
 // of two shapes:
 //   KW = 4: 8 waves, one workgroup per compute unit.  Fewest tile loads per matrix instruction; the
 //           better shape when a workgroup's pieces are long: d = 128, sequences from 8K on with
-//           grouped heads.  A step in us, KW = 4 / 2 (two runs of one side differ by up to 0.5 %): 32/8 heads, n = 256, L = 8192
-//           430.8 / 433.7, two of them 884 / 906, L = 12000 783 / 801; 28/4 heads, L = 8192, n = 256 380 / 386, n = 1024 688 / 719;
-//           8/2 heads, L = 16384, n = 256 331 / 346, n = 1024 516 / 540.  Short windows at 8K, where pieces are shorter, are on the wrong side of
-//           the line: 32/8 heads, n = 64 351 / 346 (28/4 heads 307 / 310).  Beyond it: 16/4 heads, L = 4096, n = 64 102.6 / 96.6, n = 256 119.7 /
-//           115.4; 32/8 heads 196.8 / 197.4, but n = 1024 360 / 377; 32/32 heads, L = 8192, n = 64 465 / 459, n = 256 556 / 559.
+//           grouped heads.  dK/dV and the sum of its partials in us, KW = 4 / 2 (means of two runs, 1 to 2 % apart): 32/8 heads, L = 8192,
+//           n = 256 196.7 / 198.5, n = 1024 348 / 382, two of them 408 / 418; 28/4 heads, L = 8192, n = 256 168 / 174, n = 1024 305 / 333; 16/4
+//           heads, L = 8192, n = 256 109 / 112; 32/8 heads, L = 16384, n = 512 (dK/dV) 674 / 710; 8/2 heads, L = 16384 (dK/dV) 138 / 150.  Short
+//           windows at 8K, where pieces are shorter, are on the wrong side of the line: 32/8 heads, n = 64 (dK/dV) 150 / 145.  Beyond
+//           it: 16/4 heads, L = 4096, n = 256 52.7 / 47.5; 32/8 heads 89.1 / 89.2, but n = 1024 161 / 177; 32/32 heads, L = 8192, n = 256 265 / 255.
 //   KW = 2: 4 waves, two workgroups per compute unit (three at d = 64, where the registers and the ring
 //           of query tiles allow it) that run independently: one's piece start-up and partial stores
 //           overlap the others' matrix work, the split of a (batch, KV head) is finer (it fills the
