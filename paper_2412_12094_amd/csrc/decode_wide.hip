@@ -435,7 +435,8 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
     if (!last_s) return;
     // The lanes of a head (64, or 32 at d = 64) have two columns each.  Maximum and sum of slice k are fetched by the head's lane k
     // and handed around as scalars: fetched by every lane, they are half of the requests, whose number is what the
-    // fetch costs.  The arithmetic, and so every bit, is that of decode_merge_kernel: eight records at a time, in slice order.
+    // fetch costs.  The arithmetic, and so every bit, is that of decode_merge_kernel: eight records at a time, in slice order, and
+    // exp2f, whose results reach below 2^-126 where the bare instruction's end (one per lane and batch).
     static_assert(kDwMostAdded <= 16 && kDwMostAdded <= D / 2, "a slice per lane of a row of sixteen");
     const int lk = lane % (D / 2);
     for (int item = tid; item < G * (D / 2); item += 64 * NW) {
@@ -462,10 +463,10 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
                 else return lane < 32 ? a : __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), 32 + k));
             };
             const float Mn = fmaxf(M, of_head(m8, s0));
-            const float keep = (M == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(M - Mn);
+            const float keep = (M == -INFINITY) ? 0.f : exp2f(M - Mn);
             lsum *= keep, o0 *= keep, o1 *= keep;
             M = Mn;
-            const float wgt = (ml.x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml.x - M);  // used of the batch's lanes
+            const float wgt = (ml.x == -INFINITY) ? 0.f : exp2f(ml.x - M);  // used of the batch's lanes
 #pragma unroll
             for (int k = 0; k < 8; ++k) {
                 const float w = of_head(wgt, s0 + k);
@@ -477,7 +478,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
         const long sh = (long)sq * p.Hq + h0 + h;
         const uint32_t b0 = decode_f32_to_bf16(lsum > 0.f ? o0 / lsum : 0.f), b1 = decode_f32_to_bf16(lsum > 0.f ? o1 / lsum : 0.f);
         *reinterpret_cast<uint32_t *>(out + sh * D + 2 * c2) = b0 | (b1 << 16);
-        if (lse && c2 == 0) lse[sh] = (lsum > 0.f) ? (M + __builtin_amdgcn_logf(lsum)) * kLn2_f : -INFINITY;
+        if (lse && c2 == 0) lse[sh] = (lsum > 0.f) ? (M + log2f(lsum)) * kLn2_f : -INFINITY;
     }
 }
 

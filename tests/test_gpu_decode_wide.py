@@ -196,3 +196,34 @@ def test_decode_captured_slices_replay():
         torch.cuda.synchronize()
         for x, y in zip(out, ref):
             assert torch.equal(x, y), k
+
+
+@pytest.mark.parametrize("S,Hq,Hkv,d,a,s,w,c,blocks", [  # blocks: of the first slice; seven, eight and sixteen slices
+    (4, 32, 8, 128, 4, 64, 256, 800, 4), (4, 8, 8, 64, 4, 900, 256, 2300, 9), (1, 4, 2, 64, 4, 2500, 256, 5200, 11)])
+def test_decode_slices_far_apart(S, Hq, Hkv, d, a, s, w, c, blocks):
+    """Slices whose maxima lie 130 octaves apart: their weights, below the smallest normal number, reach the output where
+    the values are as large, and in a captured call as in an eager one, bit for bit.  Scores in octaves: 90 log2(e) at one entry of the
+    first slice, 0 at all others, which hold 2^115 (the first slice zeros): each weight of 2^-129.84 keeps 19 bits, so the bf16
+    result is within 2^-8 of the exact sum."""
+    import paper_2412_12094_amd as sp
+
+    per = 32 * blocks
+    sizes = np.array([[a, s, c - a - s - w, w, 0, 0]] * S, dtype=np.int32)
+    q, K, V = np.zeros((S, Hq, d), np.float32), np.zeros((S, Hkv, c, d), np.float32), np.full((S, Hkv, c, d), 2.0 ** 115, np.float32)
+    q[..., 0], K[:, :, 0, 0], V[:, :, :per] = 1.0, 90.0, 0.0
+    bf = lambda x: torch.from_numpy(x).cuda().to(torch.bfloat16)
+    args = [bf(q), bf(K), bf(V), torch.from_numpy(sizes).cuda(), a, s, w, 1.0]
+    ws = torch.zeros(4 << 20, dtype=torch.uint8, device="cuda")
+    eager = [t.clone() for t in sp.sepattn_decode(*args, ws=ws)]
+    out = (torch.empty_like(eager[0]), torch.empty_like(eager[1]))
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        sp.sepattn_decode(*args, out=out, ws=ws)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        for x, y in zip(out, eager):
+            assert torch.equal(x, y)
+    want = (c - per) * 2.0 ** 115 * math.exp(-90.0)
+    assert np.abs(eager[0].float().cpu().numpy() / want - 1).max() <= 2.0 ** -8
