@@ -213,8 +213,9 @@ __global__ __launch_bounds__(kCompactThreads) void compact_write_kernel(
 #pragma unroll
     for (int it = 0; it < kCompactIters; ++it) {
         const int g = it * kCompactWaves + wave, j = base + it * kCompactThreads + tid;
+        const int group_base = chunk_base + __builtin_amdgcn_readlane(incl - v, g);  // in front of the branch: lane g may lie past L
         if (j < L) {
-            const int r = chunk_base + __builtin_amdgcn_readlane(incl - v, g) + rank_in_wave[it];
+            const int r = group_base + rank_in_wave[it];
             if (sep_prefix) sep_prefix[(long)b * (L + 1) + j] = r;
             // token j is separator r, or one of the others, j - r of which lie in front of it: these take the entries behind
             // the list's last, from L - 1 downwards, so that nobody needs to know how long the list is

@@ -28,8 +28,9 @@ def ptr(t):
     return ctypes.c_void_p(t.data_ptr())
 
 
-# a token, a wave, a chunk of 2048 and its halves, the one-launch limits of 8192 and 32768 tokens, each with its neighbours
-@pytest.mark.parametrize("B,L,p", [(1, 1, 0.5), (2, 63, 0.3), (3, 1023, 0.1), (2, 1025, 0.0), (2, 2048, 1.0), (3, 2049, 0.1), (2, 4095, 0.08),
+# a token, a wave, a chunk of 2048 and its halves, the one-launch limits of 8192 and 32768 tokens, each with its neighbours; a wave with one
+# token of its own (1025 and 3073)
+@pytest.mark.parametrize("B,L,p", [(1, 1, 0.5), (2, 63, 0.3), (3, 1023, 0.1), (2, 1025, 0.0), (2, 1025, 0.5), (2, 3073, 0.4), (2, 2048, 1.0), (3, 2049, 0.1), (2, 4095, 0.08),
                                    (3, 6145, 0.2), (2, 8192, 0.08), (2, 8193, 0.08), (1, 32768, 0.1), (2, 32769, 0.1)])
 def test_list_is_filled_behind_its_last_separator(sp, B, L, p):
     lib = sp.load()
