@@ -185,30 +185,40 @@ __device__ __forceinline__ void dq_work(
             c.next = open_segment(c.round + 1);
         }
     };
-    // entries of tile t (global number g) of stream ss
-    auto issue_entries = [&](const Stream &ss, int t, int g) __attribute__((always_inline)) {
+    // where a lane's entries of tile t of stream ss stand
+    struct EntryAt {
+        const int32_t *of_row, *behind, *doc_end;
+    };
+    auto entry_at = [&](const Stream &ss, int t) __attribute__((always_inline)) {
         const int k = t * kBN + lane;
         const int e = min(max(ss.sep_lo - ss.n_init + k, 0), p.cap - 1);
         const int j = min(max(ss.bs - ss.n_dense + k, 0), p.L - 1);
-        const uint32_t dst = lds_addr(&ent_s[g & 3][0][0]);
-        dma_to_lds_4_addr(k < ss.n_dense ? idx + e : prefix + j, dst);
-        dma_to_lds_4_addr(prefix + j + 1, dst + kBN * 4);
-        if constexpr (DOCS) dma_to_lds_4_addr(dend + j, dst + 2 * kBN * 4);  // where the key's document ends
+        return EntryAt{k < ss.n_dense ? idx + e : prefix + j, prefix + j + 1, DOCS ? dend + j : nullptr};
     };
-    auto write_rows = [&](const Cursor &c, int g) __attribute__((always_inline)) {
+    // entries of tile t (global number g) of stream ss
+    auto issue_entries = [&](const Stream &ss, int t, int g) __attribute__((always_inline)) {
+        const EntryAt at = entry_at(ss, t);
+        const uint32_t dst = lds_addr(&ent_s[g & 3][0][0]);
+        dma_to_lds_4_addr(at.of_row, dst);
+        dma_to_lds_4_addr(at.behind, dst + kBN * 4);
+        if constexpr (DOCS) dma_to_lds_4_addr(at.doc_end, dst + 2 * kBN * 4);  // where the key's document ends
+    };
+    auto write_entries = [&](const Cursor &c, int g, int e0, int e1, int doc_end) __attribute__((always_inline)) {
         const Stream &ss = c.cur.st;
         const int k = c.t * kBN + lane;
-        const int e0 = ent_s[g & 3][0][lane], e1 = ent_s[g & 3][1][lane];
         const bool dense = k < ss.n_dense, pad = k >= ss.n_total;
         const int jb = ss.bs + (k - ss.n_dense);
         // the clamp keeps a stale list tail (caller broke sep_count <= cap) from faulting
         int j = dense ? min(max(e0, 0), p.L - 1) : jb;
         j = k < ss.n_init ? k : j;
         int hi = (dense | (jb < p.a) | (e1 != e0)) ? kIntMax : jb + p.n - 1;
-        if constexpr (DOCS) hi = min(hi, (dense ? c.cur.de : ent_s[g & 3][2][lane]) - 1);
+        if constexpr (DOCS) hi = min(hi, (dense ? c.cur.de : doc_end) - 1);
         lo_s[g % MKS][lane] = pad ? kIntMax : j;
         hi_s[g % MKS][lane] = pad ? -1 : hi;
         off_s[g & 3][lane] = pad ? 0u : (uint32_t)j * (uint32_t)(D * 2);
+    };
+    auto write_rows = [&](const Cursor &c, int g) __attribute__((always_inline)) {
+        write_entries(c, g, ent_s[g & 3][0][lane], ent_s[g & 3][1][lane], DOCS ? ent_s[g & 3][DOCS ? 2 : 0][lane] : 0);
     };
     // start of tile step g: positions of a tile four further on, entries of one six further on (AH = 2: of two
     // tiles every other step)
@@ -413,16 +423,19 @@ __device__ __forceinline__ void dq_work(
     };
     // ---- start-up, once per workgroup, as in the forward: positions of tiles 0 .. 3, a wave each, then the first rows (the entries
     // of tiles 4 and 5 are on their way).  The first segment's rows of Q, dO and O are requested behind the entries,
-    // which are waited for alone.
+    // which alone are waited for (they come into registers: the compiler counts the loads that it has placed behind them).
     Seg cseg = segment_at(rank0);
     {
         Seg next = segment_at(min(rank_of(1), n_pieces - 1));
         if (rank_of(1) >= n_pieces) next = past_the_last();
         lc = {cseg, next, 0, cseg.t0};
     }
+    int e0 = 0, e1 = 0, e_doc = 0;
     if (wave < 4) {
         for (int t = 0; t < wave; ++t) advance(lc);
-        issue_entries(lc.cur.st, lc.t, wave);
+        const EntryAt at = entry_at(lc.cur.st, lc.t);
+        e0 = *at.of_row, e1 = *at.behind;
+        if constexpr (DOCS) e_doc = *at.doc_end;
     }
     __builtin_amdgcn_sched_barrier(0);
     fetch_rows(cseg);
@@ -431,16 +444,9 @@ __device__ __forceinline__ void dq_work(
         const Cursor own = lc;
         if (wave < 2)
             for (int t = 0; t < 4; ++t) advance(lc);
-        static_assert(CB == 2 || CB == 4, "all but the loads of fetch_rows are waited for");
-        if constexpr (ROWS) {  // 4 CB and one
-            if constexpr (CB == 2) asm volatile("s_waitcnt vmcnt(9)" ::: "memory");
-            if constexpr (CB == 4) asm volatile("s_waitcnt vmcnt(17)" ::: "memory");
-        } else {
-            if constexpr (CB == 2) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
-            if constexpr (CB == 4) asm volatile("s_waitcnt vmcnt(24)" ::: "memory");
-        }
-        write_rows(own, wave);
-        if (wave < 2) issue_entries(lc.cur.st, lc.t, 4 + wave);  // where those of tile `wave` have just been read
+        asm volatile("" : "+v"(e0), "+v"(e1), "+v"(e_doc));  // looked at from here on
+        write_entries(own, wave, e0, e1, e_doc);
+        if (wave < 2) issue_entries(lc.cur.st, lc.t, 4 + wave);
     }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // only what write_rows wrote is published here
     __builtin_amdgcn_s_barrier();
