@@ -433,18 +433,25 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     if (!last_s) return;
-    // The lanes of a head (64, or 32 at d = 64) have two columns each.  Maximum and sum of slice k are fetched by the head's lane k
-    // and handed around as scalars: fetched by every lane, they are half of the requests, whose number is what the
-    // fetch costs.  The arithmetic, and so every bit, is that of decode_merge_kernel: eight records at a time, in slice order, and
-    // exp2f, whose results reach below 2^-126 where the bare instruction's end (one per lane and batch).
-    static_assert(kDwMostAdded <= 16 && kDwMostAdded <= D / 2, "a slice per lane of a row of sixteen");
-    const int lk = lane % (D / 2);
+    // The lanes of a head (64, or 32 at d = 64) have two columns each.  Maximum and sum of slice k are fetched by lane k of the
+    // head's lanes (d = 128), of every row of sixteen (d = 64, where a wave has two heads), and handed around, as scalars or along the
+    // row: fetched by every lane, they are half of the requests, whose number is what the
+    // fetch costs.  (A call at d = 64, us, with two scalars per value and a choice between them / fetched by every lane / along the row: 7 x
+    // 12/12 heads, 1750 entries 9.38 / 9.17 / 9.11; 1 x 4/2 heads, 5200 entries 6.83 / 6.56 / 6.19; 4 x 32/8 heads, 1999 entries 6.84 / 7.29 / 6.58.)  The arithmetic, and so every bit, is that of decode_merge_kernel:
+    // eight records at a time, in slice order, and exp2f, whose results reach below 2^-126 where the bare instruction's end (one per lane and batch).
+    static_assert(kDwMostAdded <= 16, "a slice per lane of a row of sixteen, in two batches");
+    const int lk = lane % (D == 128 ? 64 : 16);
+    // what lane S0 + K of this lane's head or row holds
+    auto of_slice = [&](float x, auto S0, auto K) __attribute__((always_inline)) {
+        if constexpr (D == 128) return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), S0 + K));
+        else return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x150 + S0 + K, 0xF, 0xF, false));  // row_newbcast
+    };
     for (int item = tid; item < G * (D / 2); item += 64 * NW) {
         const int h = item / (D / 2), c2 = item % (D / 2);
         const uint32_t at = (uint32_t)(h * nsplit) * (PF * 4);
         float2 ml = {-INFINITY, 0.f};
         float M = -INFINITY, lsum = 0.f, o0 = 0.f, o1 = 0.f;
-        for (int s0 = 0; s0 < nsplit; s0 += 8) {
+        auto batch = [&](auto s0) __attribute__((always_inline)) {  // the slices s0 .. s0 + 7
             float2 o[8];
 #pragma unroll
             for (int k = 0; k < 8; ++k)  // slices past the last repeat it with weight 0
@@ -453,32 +460,34 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
             if (s0 == 0) {  // the last of the requests, because its answer is waited for first
                 ml = fetch_published(reinterpret_cast<const float *>(recs + (at + (uint32_t)(min(lk, nsplit - 1) * (PF * 4)))));
                 if (lk >= nsplit) ml = float2{-INFINITY, 0.f};
+                if (tid == 0) arrival_reset(arrived);
             }
-            if (s0 == 0 && tid == 0) arrival_reset(arrived);
             // the largest of the batch, in all of its eight lanes
             const float m8 = half_row_max(ml.x);
-            auto of_head = [&](float x, int k) __attribute__((always_inline)) {  // lane k of this lane's head
-                const float a = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), k));
-                if constexpr (D == 128) return a;
-                else return lane < 32 ? a : __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), 32 + k));
-            };
-            const float Mn = fmaxf(M, of_head(m8, s0));
+            const float Mn = fmaxf(M, of_slice(m8, s0, IntC<0>{}));
             const float keep = (M == -INFINITY) ? 0.f : exp2f(M - Mn);
             lsum *= keep, o0 *= keep, o1 *= keep;
             M = Mn;
             const float wgt = (ml.x == -INFINITY) ? 0.f : exp2f(ml.x - M);  // used of the batch's lanes
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const float w = of_head(wgt, s0 + k);
-                lsum = fmaf(w, of_head(ml.y, s0 + k), lsum);
+            static_for<8>([&](auto KK) __attribute__((always_inline)) {
+                constexpr int k = decltype(KK)::value;
+                const float w = of_slice(wgt, s0, KK);
+                lsum = fmaf(w, of_slice(ml.y, s0, KK), lsum);
                 o0 = fmaf(w, o[k].x, o0);
                 o1 = fmaf(w, o[k].y, o1);
-            }
+            });
+        };
+        if constexpr (D == 128) {
+            for (int s0 = 0; s0 < nsplit; s0 += 8) batch(s0);
+        } else {  // the lane is part of the instruction
+            batch(IntC<0>{});
+            if (nsplit > 8) batch(IntC<8>{});
         }
         const long sh = (long)sq * p.Hq + h0 + h;
         const uint32_t b0 = decode_f32_to_bf16(lsum > 0.f ? o0 / lsum : 0.f), b1 = decode_f32_to_bf16(lsum > 0.f ? o1 / lsum : 0.f);
         *reinterpret_cast<uint32_t *>(out + sh * D + 2 * c2) = b0 | (b1 << 16);
-        if (lse && c2 == 0) lse[sh] = (lsum > 0.f) ? (M + log2f(lsum)) * kLn2_f : -INFINITY;
+        // (the bare logarithm: the largest slice counts with weight 1, so the sum is no denormal number)
+        if (lse && c2 == 0) lse[sh] = (lsum > 0.f) ? (M + __builtin_amdgcn_logf(lsum)) * kLn2_f : -INFINITY;
     }
 }
 
