@@ -392,6 +392,8 @@ int sepkv_fill_from_prefill_zeroed(const sepkv_params *p, int L, int nw, const v
  * The handle and everything it records belong to the caller; the library keeps no process-wide state,
  * only, per thread, which handle is attached.  Different threads may use different handles at the
  * same time; one handle must not be attached to two threads.
+ * Every launch is recorded under one id.  Where the backward of a small bf16 call runs dQ and dK/dV side by side in one launch, that
+ * launch counts as SEPATTN_K_BWD_DKV, and SEPATTN_K_BWD_DQ is the short one in front of it that forms the row values.
  *   sepattn_profile_create   kernel: a sepattn_kernel_id; max_records: events are created up front
  *                            for this many launches, further launches are not recorded;
  *                            *out receives the handle (HOST)

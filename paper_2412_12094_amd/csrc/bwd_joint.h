@@ -90,9 +90,11 @@ int launch_joint(const sepattn_params &p, int dq_wpg, const uint16_t *Q, const u
     jp.by_dq_wpg = fast_div((uint32_t)dq_wpg);
     const DkvSlices sl = dkv_slices(p, 2, jp.kv_wpg, jp.split, false);
     {
-        // both of the kernels that this launch stands for
-        ProfScope prof_q(SEPATTN_K_BWD_DQ, st), prof_kv(SEPATTN_K_BWD_DKV, st);
+        ProfScope prof(SEPATTN_K_BWD_DQ, st);
         hipLaunchKernelGGL((row_values_kernel<D>), dim3((unsigned)((rows + 63) / 64)), dim3(256), 0, st, rows, O, LSE, dO, Dws, Lws);
+    }
+    {
+        ProfScope prof(SEPATTN_K_BWD_DKV, st);
         auto go = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3((unsigned)(jp.n_kv + n_dq)), dim3(256), 0, st, p, Q, K, V, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, dK,
                                dV, Dws, Lws, farK, farV, piece_tab, jp, qg, sl);

@@ -142,6 +142,29 @@ def test_bf16_backward_in_one_launch_and_in_two(B, Hq, Hkv, L, d, a, n, p):
     run(B, Hq, Hkv, L, d, a, n, p, "bf16")
 
 
+def test_bf16_backward_in_one_launch_is_recorded_once():
+    """Two handles do not both cover the launch that has dQ and dK/dV side by side: that counts as dK/dV, and the row values in front
+    of it, which read and write a fraction of its bytes, as dQ."""
+    import paper_2412_12094_amd as sp
+
+    B, H, L, d, a, n = 1, 12, 2011, 128, 4, 64
+    tok, Q, K, V, dO = make_case(B, H, H, L, d, 0.1, "bf16", 1)
+    q, k, v, do = (dev(x, "bf16") for x in (Q, K, V, dO))
+    _, idx, cnt, pre = gpu_index(sp, tok)
+    scale = 1.0 / math.sqrt(d)
+    O, LSE = sp.sepattn_forward(q, k, v, idx, cnt, pre, a, n, scale)
+    us = {}
+    for name in ("bwd_dq", "bwd_dkv"):
+        prof = sp.sepattn_profile_begin(sp.KERNEL_IDS[name], 40)
+        for _ in range(40):
+            sp.sepattn_backward(q, k, v, O, LSE, do, idx, cnt, pre, a, n, scale)
+        torch.cuda.synchronize()
+        ms = sp.sepattn_profile_end(prof)
+        assert len(ms) == 40
+        us[name] = 1e3 * float(np.median(ms))
+    assert us["bwd_dq"] <= 0.6 * us["bwd_dkv"], us
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("B,Hq,Hkv,L,a,n,p", [
     (1, 4, 1, 2560, 4, 2560, 0.1),                         # four heads; the shortest window that may end before the sequence
