@@ -160,10 +160,11 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
     char *const arrived_at = reinterpret_cast<char *>(part) + pair * ((long)sizeof(uint64_t) + pair_bytes);
     uint64_t *const arrived = reinterpret_cast<uint64_t *>(arrived_at);
     char *const recs = ADD ? arrived_at + sizeof(uint64_t) : reinterpret_cast<char *>(part) + decode_wide_arrival_bytes(p) + pair * pair_bytes;
-    // requested in front of the rows, looked at when the wave's blocks are done
+    // requested in front of the rows, by the wave with the fewest of them, and looked at while the records are on their way (requested behind
+    // the rows, 0.1 us more)
     uint64_t seen = 0;
     if constexpr (ADD) {
-        if (tid == 0) seen = arrival_seen(arrived);
+        if (tid == 64 * (NW - 1)) seen = arrival_seen(arrived);
     }
     const CacheMap cm = cache_map(p, sz);
     const int nv = cm.n_init + cm.n_sep + cm.n_past + cm.n_loc;
@@ -367,9 +368,6 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
         }
     }
 
-    if constexpr (ADD) {
-        if (tid == 0) arrival_ready(arrived, seen, one, nsplit);
-    }
     // ---- merge the waves' states through LDS: D outputs, max, sum of a head.  A wave's records lie in its own stage, whose rows
     // nobody else reads: heads 0 .. 7 in the K half, the others in the V half
     const float l_tot = groups_sum(l_run);
@@ -425,6 +423,7 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
 
     // ---- the workgroup that finishes last adds the slices' records, in slice order, whichever it is
     __shared__ int last_s;
+    if (tid == 64 * (NW - 1)) arrival_ready(arrived, seen, one, nsplit);  // while the record is on its way
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's part of the record is where every XCD sees it
     __syncthreads();
     if (tid == 0) last_s = arrives_last(arrived, one, nsplit);
@@ -433,12 +432,14 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     if (!last_s) return;
-    // The lanes of a head (64, or 32 at d = 64) have two columns each.  Maximum and sum of slice k are fetched by lane k of the
-    // head's lanes (d = 128), of every row of sixteen (d = 64, where a wave has two heads), and handed around, as scalars or along the
-    // row: fetched by every lane, they are half of the requests, whose number is what the
-    // fetch costs.  (A call at d = 64, us, with two scalars per value and a choice between them / fetched by every lane / along the row: 7 x
-    // 12/12 heads, 1750 entries 9.38 / 9.17 / 9.11; 1 x 4/2 heads, 5200 entries 6.83 / 6.56 / 6.19; 4 x 32/8 heads, 1999 entries 6.84 / 7.29 / 6.58.)  The arithmetic, and so every bit, is that of decode_merge_kernel:
-    // eight records at a time, in slice order, and exp2f, whose results reach below 2^-126 where the bare instruction's end (one per lane and batch).
+    // The lanes of a head (64, or 32 at d = 64) have two columns each.  Maximum and sum of slice k are fetched by lane k of the head's
+    // lanes (d = 128) or of every row of sixteen (d = 64, where a wave has two heads) and handed on, as scalars or along the row:
+    // fetched by every lane, they are half of the requests, whose number is what the fetch costs.  A call in us, every lane for itself / handed
+    // on: d = 128, one head per KV head, 2 x 8 KV heads, 1130 entries 6.66 / 6.63, two heads 6.85 / 6.78, four (4 x 8 KV heads, 800 entries)
+    // 6.71 / 6.51, seven (2 x 2 KV heads, 1400 entries) 7.36 / 7.00; d = 64, 7 x 12/12 heads, 1750 entries 9.17 / 9.11, 1 x 4/2 heads, 5200
+    // entries 6.56 / 6.19 (there as scalars, two and a choice per value: 9.38, 6.83).
+    // The arithmetic, and so every bit, is that of decode_merge_kernel: eight records at a time, in slice order, and exp2f, whose results
+    // reach below 2^-126 where the bare instruction's end.
     static_assert(kDwMostAdded <= 16, "a slice per lane of a row of sixteen, in two batches");
     const int lk = lane % (D == 128 ? 64 : 16);
     // what lane S0 + K of this lane's head or row holds
@@ -451,20 +452,20 @@ __global__ __launch_bounds__(64 * NW, D == 64 ? 4 : 2) void decode_wide_kernel(
         const uint32_t at = (uint32_t)(h * nsplit) * (PF * 4);
         float2 ml = {-INFINITY, 0.f};
         float M = -INFINITY, lsum = 0.f, o0 = 0.f, o1 = 0.f;
-        auto batch = [&](auto s0) __attribute__((always_inline)) {  // the slices s0 .. s0 + 7
+        // the slices s0 .. s0 + 7, those past the last as the last again with weight 0
+        auto batch = [&](auto s0) __attribute__((always_inline)) {
             float2 o[8];
+            auto record_at = [&](int slice) { return at + (uint32_t)(min(slice, nsplit - 1) * (PF * 4)); };
 #pragma unroll
-            for (int k = 0; k < 8; ++k)  // slices past the last repeat it with weight 0
-                o[k] = fetch_published(reinterpret_cast<const float *>(recs + (at + 8u + 8u * c2 + (uint32_t)(min(s0 + k, nsplit - 1) * (PF * 4)))));
+            for (int k = 0; k < 8; ++k) o[k] = fetch_published(reinterpret_cast<const float *>(recs + (record_at(s0 + k) + 8u + 8u * c2)));
             __builtin_amdgcn_sched_barrier(0);
             if (s0 == 0) {  // the last of the requests, because its answer is waited for first
-                ml = fetch_published(reinterpret_cast<const float *>(recs + (at + (uint32_t)(min(lk, nsplit - 1) * (PF * 4)))));
+                ml = fetch_published(reinterpret_cast<const float *>(recs + record_at(lk)));
                 if (lk >= nsplit) ml = float2{-INFINITY, 0.f};
-                if (tid == 0) arrival_reset(arrived);
             }
-            // the largest of the batch, in all of its eight lanes
-            const float m8 = half_row_max(ml.x);
-            const float Mn = fmaxf(M, of_slice(m8, s0, IntC<0>{}));
+            // (the largest of the batch is in all of its eight lanes)
+            const float Mn = fmaxf(M, of_slice(half_row_max(ml.x), s0, IntC<0>{}));
+            if (s0 == 0 && tid == 0) arrival_reset(arrived);  // (in front of the maximum: 0.1 us more)
             const float keep = (M == -INFINITY) ? 0.f : exp2f(M - Mn);
             lsum *= keep, o0 *= keep, o1 *= keep;
             M = Mn;
