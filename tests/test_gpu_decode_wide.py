@@ -131,7 +131,8 @@ def test_decode_heals_from_counts_that_overlapping_calls_left(left):
 
     S, Hkv, c, sizes = 4, 8, 800, [[4, 64, 476, 256, 3, 5]]
     ws = torch.zeros(4 << 20, dtype=torch.uint8, device="cuda")
-    words = ws[: 8 * S * Hkv].view(torch.int64)
+    # a word in front of the records of its (sequence, KV head): four heads, seven slices, 130 floats each
+    words = ws.view(torch.int64).as_strided((S * Hkv,), (1 + 4 * 7 * 130 // 2,))
     g = torch.Generator(device="cuda").manual_seed(left)
     sz = torch.tensor(sizes * S, dtype=torch.int32, device="cuda")
     for call in range(4):
@@ -141,6 +142,7 @@ def test_decode_heals_from_counts_that_overlapping_calls_left(left):
         got = sp.sepattn_decode(q, K, V, sz, 4, 64, 256, 0.09, ws=ws)
         for x, y in zip(got, ref):
             assert torch.equal(x, y), call
+        assert not words.any(), call  # set back, for the next call to find it so
         words += left + (call << 40)  # the lower 8 bits count, the upper ones tell launches apart
 
 
