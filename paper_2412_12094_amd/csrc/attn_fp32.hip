@@ -14,7 +14,7 @@
 // At the sizes this path is used at, a call lasts about as long as its chain of memory latencies, so
 // the work of a tile is spread over the four waves of a workgroup (16-key blocks, or query blocks, dealt round-robin; the waves'
 // partial results meet once in LDS), operands go straight from memory to registers, and what can
-// share a launch does: dQ and dK/dV (launch_backward_shape), and the far keys' partial sums are added by the
+// share a launch does: dQ and dK/dV (fp32_one_launch), and the far keys' partial sums are added by the
 // last workgroup to finish a list tile instead of by a kernel of their own.
 //
 // A masked pair enters the contractions over streamed rows with weight 0, and 0 times an infinity or a NaN is NaN: a
@@ -24,6 +24,7 @@
 // below; B=1, 32/8 heads, L=4096, d=128, n=256 451 us forward and 1858 backward with it, 452 and 1866 without.
 // B=1, 2 heads per KV head, L=512, d=64, n=64: forward 22 -> 7 us, D_i and dQ 5 + 23 -> 8, dK/dV 168 -> 16, against one
 // wave per row on the vector ALU.
+#include "attn_fp32.h"
 #include "bwd_common.h"
 #include "key_stream.h"
 #include "mfma_common.h"
@@ -32,8 +33,7 @@ namespace sepattn {
 
 namespace {
 
-constexpr int kT = 16;      // queries / keys per block
-constexpr int kWaves = 4;   // waves per workgroup
+constexpr int kWaves = 4;  // waves per workgroup
 // (query block, head) items per far slice: one per wave, more where a list tile of the whole sequence would be shared among
 // more than kMaxShare slices, whose sums one workgroup adds.  Backward, us, with 4 / 8 / the rule: 2 heads per KV head,
 // L=512, d=64 23.0 / 23.9 / 23.0; 4 and 4 heads, 2 x L=300, d=128 32.7 / 36.4 / 32.7; 4 heads per KV head, 2 x L=1000, d=64
@@ -592,7 +592,7 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 4 : 2) void dq_fp32_kernel(
     for (long c = (long)blockIdx.x * (64 * kWaves) + threadIdx.x; c < n_counters; c += (long)gridDim.x * (64 * kWaves)) counters[c] = 0;
     dq_tile<D, HW>(xs, blockIdx.x, p, Q, K, V, O, LSE, dO, sep_idx, sep_prefix, doc_start, doc_end, dQ, Dws, pl, ha);
 }
-// MERGED: the blocks behind the dK/dV units are dQ tiles (see launch_backward_fp32).
+// MERGED: the blocks behind the dK/dV units are dQ tiles (see fp32_one_launch).
 template <int D, bool HW, bool MERGED>
 __global__ __launch_bounds__(64 * kWaves, D == 64 ? 2 : 1) void dkv_fp32_kernel(
     sepattn_params p, const float *__restrict__ Q, const float *__restrict__ K, const float *__restrict__ V, const float *__restrict__ O,
@@ -606,24 +606,6 @@ __global__ __launch_bounds__(64 * kWaves, D == 64 ? 2 : 1) void dkv_fp32_kernel(
     else
         dkv_unit<D, HW, MERGED>(xs, p, Q, K, V, O, LSE, dO, Drow, sep_idx, sep_prefix, doc_end, dK, dV, partials, counters, n_far_tiles, wpg,
                                 word_stride, one, pl, ha);
-}
-
-// backward workspace: D_i [B,Hq,L] | one counter per list tile | the slots of the partial sums
-struct Fp32Workspace {
-    int wpg, n_far_tiles;
-    long n_counters;
-    size_t d_bytes, counter_bytes, total;
-};
-Fp32Workspace fp32_workspace(const sepattn_params &p) {
-    Fp32Workspace w;
-    const long n_bkv = (long)p.B * p.Hkv, wpg = 2 * (long)compute_units() / n_bkv;
-    w.wpg = (int)(wpg < 1 ? 1 : wpg);
-    w.n_far_tiles = (p.a + p.cap + kT - 1) / kT;
-    w.n_counters = n_bkv * w.n_far_tiles;
-    w.d_bytes = align_up((size_t)p.B * p.Hq * p.L * sizeof(float), 256);
-    w.counter_bytes = align_up((size_t)w.n_counters * sizeof(int32_t), 256);
-    w.total = w.d_bytes + w.counter_bytes + (size_t)n_bkv * (w.wpg + w.n_far_tiles) * (2 * kT * p.d) * sizeof(float);
-    return w;
 }
 
 }  // namespace
@@ -658,13 +640,6 @@ int launch_forward_fp32(const sepattn_params &p, const HeadWin &hw, const float 
     return launch_status();
 }
 
-// One launch or two.  dK/dV needs nothing of dQ but D_i.  Where the blocks are few, both kinds run side by side in one launch and
-// dK/dV forms D_i itself (one more row per item); where they fill the chip anyway, dQ comes first, by itself.  The line, in dQ
-// tiles and band units per compute unit, of which the joint kernel has two at a time at d = 64 and one at d = 128 (registers):
-// backward in us, two launches / one.  d = 64: 2/1 heads, L = 512 (0.4) 21.3 / 15.0, 4 x 4/1 heads, L = 1000 (1.2) 48.0 / 38.1, 8/2
-// heads, L = 1024 (2.5) 49.8 / 40.0, 32/32 heads, L = 200 (3.3) 30.6 / 27.9, 2/2 heads, L = 4000 (3.9) 53.5 / 51.1, 1/1 heads, L = 8192 (4)
-// 90.1 / 93.6, 2 x 8/8 heads, L = 1024 (8) 59.8 / 61.9, 4 x 12/12 heads 167 / 190.  d = 128: 4/4 heads, L = 300 (0.6) 33.7 / 21.2, L = 1024 (2)
-// 34.3 / 31.9, 8/2 heads, L = 1024 (2.5) 89.9 / 79.4, 32/32 heads, L = 200 (3.3) 56.2 / 63.0, 8/8 heads, L = 1024 (4) 79.8 / 88.9.
 template <int D, bool HW>
 int launch_backward_shape(const sepattn_params &p, const HeadArgs<HW> &ha, const float *Q, const float *K, const float *V,
                           const float *O, const float *LSE, const float *dO, const int32_t *sep_idx, const int32_t *sep_prefix,
@@ -678,10 +653,8 @@ int launch_backward_shape(const sepattn_params &p, const HeadArgs<HW> &ha, const
     const long q_tiles = (long)p.B * p.Hq * pl.n_tiles, k_units = (long)p.B * p.Hkv * (w.wpg + pl.n_tiles);
     if (q_tiles > 0x7FFFFFFFL || k_units > 0x7FFFFFFFL) return SEPATTN_ERR_SHAPE;
     const dim3 block(64 * kWaves);
-    // the words in which slices are counted take the place of D_i, a cache line each where there is room
-    const int stride = (size_t)w.n_counters * 128 <= w.d_bytes ? 128 : 8;
-    const long most = (D == 64 ? 15 : 10) * (long)compute_units() / 4;
-    if (q_tiles + (long)p.B * p.Hkv * pl.n_tiles <= most && (size_t)w.n_counters * stride <= w.d_bytes && !being_captured(st)) {
+    const int stride = fp32_one_launch(p, w);
+    if (stride && !being_captured(st)) {
         hipLaunchKernelGGL((dkv_fp32_kernel<D, HW, true>), dim3((unsigned)(k_units + q_tiles)), block, 0, st, p, Q, K, V, O, LSE, dO, nullptr, sep_idx,
                            sep_prefix, doc_start, doc_end, dQ, dK, dV, partials, Dws, w.n_far_tiles, w.wpg, stride, launch_number(), (int)k_units, pl, ha);
         return launch_status();

@@ -131,24 +131,6 @@ int launch_bwd(const sepattn_params &p, const uint16_t *Q, const uint16_t *K, co
 
 }  // namespace
 
-// Whether dQ and dK/dV share a launch: four-wave shapes without split streams and without a list of all keys, whose query tiles
-// are at most three eighths as many as the workgroups that fit the chip.  Beyond that, the tiles take from dK/dV the workgroups that its longest
-// units and slices need.  Backward, two launches' time over one's, over 110 calls of two head sizes: up to 64 tiles 1.12 to 1.62 (1.34 in
-// the mean), up to 128 1.19 to 1.55 (1.32), up to 192 1.10 to 1.43 (1.25), up to 256 0.75 to 1.29 (1.04), up to 320 0.84 to 1.04, beyond
-// less.  In us, two / one: 8/2 heads, L = 600, n = 96, d = 128 (38 tiles) 26.9 / 20.2, d = 64 21.8 / 16.8; 32/8 heads, L = 768, n = 100 (192)
-// 33.3 / 31.1, d = 64 24.3 / 24.3; 12/12 heads, L = 2011, n = 64 (192) 41.4 / 37.1; 4 x 8/2 heads, L = 936, n = 657 (240) 60.0 / 80.2.
-int joint_dq_workgroups(const sepattn_params &p, const HeadWin &hw, bool docs) {
-    const QueryShape shape = query_shape(p);
-    if (any_delta(hw) || shape.nw != 4 || dkv_key_blocks(p, docs) != 2) return 0;
-    const int TP = 32 * shape.nw / shape.gp, tiles = (p.L + TP - 1) / TP;
-    const long slots = 2l * compute_units(), n_groups = (long)p.B * (p.Hq / shape.gp), n_bkv = (long)p.B * p.Hkv;
-    if (n_groups * tiles > slots * 3 / 8 || n_groups * tiles + n_bkv > slots) return 0;
-    if (!docs && split_keys(p, hw, shape.gp, TP, slots, (size_t)-1)) return 0;
-    const int wpg = dkv_workgroups_per_head(p, 2);
-    if (!docs && p.n >= p.L && list_of_all_keys(p, 2, wpg, far_geom(p, wpg, 2), false)) return 0;
-    return tiles;
-}
-
 size_t backward_bf16_workspace(const sepattn_params &p) { return bwd_workspace(p).total; }
 
 int launch_backward_bf16(const sepattn_params &p, const HeadWin &hw, const void *Q, const void *K, const void *V,

@@ -4,6 +4,7 @@
 #pragma once
 
 #include "common.h"
+#include "key_stream.h"
 #include "work_share.h"
 
 namespace sepattn {
@@ -136,6 +137,44 @@ inline BwdWorkspace bwd_workspace(const sepattn_params &p) {
     return w;
 }
 
+// Whether KV heads that see every earlier key work through the list of all keys (see dkv_kernel).  As band units their
+// work is q = units / workgroups walks per workgroup, the longest about 1 + 1/q times the mean; as slices it is even, but
+// every key's gradients pass through fp32 partials.  That pays where a workgroup has about one unit (eight waves,
+// with nothing beside it on the compute unit to fill the gap: two) and the walks are long, with grouped heads, or
+// next to KV heads with shorter windows, which leave the full ones more workgroups.
+// Measured, a step in us, band units / slices, n = L.  Taken: 32/8 heads, d = 128, L = 8192 (q = 2, eight waves) 2716 / 2311,
+// L = 2048 (q = 1/2) 339 / 235, 16/8 heads, d = 64, L = 4096 (q = 2/3) 320 / 270 and twice that batch (q = 4/3) 442 / 429, every
+// other of 8/8 heads full, d = 64, L = 4096 246 / 205.  Not taken: 4 x 32/8 heads, L = 2048 (q = 2) 694 / 716, 2 x 12/12
+// heads, d = 64, L = 4096 (q = 2) 367 / 399 and one (q = 1) 242 / 247; every other of 8 x 12/12 heads full, L = 300 54 / 82.
+inline bool list_of_all_keys(const sepattn_params &p, int kw, int wpg, const FarGeom &fg, bool headwise) {
+    const long units = (p.L + fg.bk - 1) / fg.bk, G = p.Hq / p.Hkv;
+    const bool fits = p.cap + p.a >= p.L;  // the list has to fit where the far list does
+    return fits && 3 * units <= (kw == 4 ? 6 : 4) * (long)wpg && G * p.L >= 4096 && (G >= 2 || headwise);
+}
+
+// Whether dQ and dK/dV of a call share a launch (bwd_joint.h), and with how many dQ workgroups per group; 0: they do not.  They do in
+// four-wave shapes without split streams and without a list of all keys, whose query tiles are at most three eighths as many
+// as the workgroups that fit the chip.  Beyond that, the tiles take from dK/dV the workgroups that its longest units and slices need.  Backward, two launches' time over one's, over 110 calls of two head sizes: up to 64 tiles 1.12 to 1.62 (1.34 in
+// the mean), up to 128 1.19 to 1.55 (1.32), up to 192 1.10 to 1.43 (1.25), up to 256 0.75 to 1.29 (1.04), up to 320 0.84 to 1.04, beyond
+// less.  In us, two / one: 8/2 heads, L = 600, n = 96, d = 128 (38 tiles) 26.9 / 20.2, d = 64 21.8 / 16.8; 32/8 heads, L = 768, n = 100 (192)
+// 33.3 / 31.1, d = 64 24.3 / 24.3; 12/12 heads, L = 2011, n = 64 (192) 41.4 / 37.1; 4 x 8/2 heads, L = 936, n = 657 (240) 60.0 / 80.2.
+inline int joint_dq_workgroups(const sepattn_params &p, const HeadWin &hw, bool docs) {
+    const QueryShape shape = query_shape(p);
+    if (any_delta(hw) || shape.nw != 4 || dkv_key_blocks(p, docs) != 2) return 0;
+    const int TP = 32 * shape.nw / shape.gp, tiles = (p.L + TP - 1) / TP;
+    const long slots = 2l * compute_units(), n_groups = (long)p.B * (p.Hq / shape.gp), n_bkv = (long)p.B * p.Hkv;
+    if (n_groups * tiles > slots * 3 / 8 || n_groups * tiles + n_bkv > slots) return 0;
+    if (!docs && split_keys(p, hw, shape.gp, TP, slots, (size_t)-1)) return 0;
+    const int wpg = dkv_workgroups_per_head(p, 2);
+    if (!docs && p.n >= p.L && list_of_all_keys(p, 2, wpg, far_geom(p, wpg, 2), false)) return 0;
+    return tiles;
+}
+// Workgroups per (batch, KV head) that dQ leaves dK/dV there: no more than dK/dV has by itself, which the workspace is laid out for.
+inline int joint_dkv_workgroups(const sepattn_params &p, int dq_wpg) {
+    const long n_dq = (long)p.B * (p.Hq / query_shape(p).gp) * dq_wpg, wpg = (2l * compute_units() - n_dq) / ((long)p.B * p.Hkv);
+    return (int)(wpg < 1 ? 1 : wpg);
+}
+
 struct FarList {
     int a_eff, sep_base, NF;
 };
@@ -188,8 +227,7 @@ int launch_dkv_combine_bf16(const sepattn_params &p, const int32_t *sep_idx, con
                             uint16_t *dK, uint16_t *dV, const float *farK, const float *farV, const int32_t *piece_tab, int wpg, int split,
                             hipStream_t st);
 
-// The backward of a small call: dQ and dK/dV in one launch (bwd_joint.h).  dq_wpg: workgroups per group of the dQ part, 0: not such a call.
-int joint_dq_workgroups(const sepattn_params &p, const HeadWin &hw, bool docs);
+// The backward of a small call: dQ and dK/dV in one launch (bwd_joint.h).  dq_wpg: workgroups per group of the dQ part.
 int launch_joint_64(const sepattn_params &p, int dq_wpg, const uint16_t *Q, const uint16_t *K, const uint16_t *V, const uint16_t *O, const float *LSE,
                     const uint16_t *dO, const int32_t *sep_idx, const int32_t *sep_prefix, const int32_t *doc_start, const int32_t *doc_end,
                     uint16_t *dQ, uint16_t *dK, uint16_t *dV, float *Dws, float *Lws, float *farK, float *farV, int32_t *piece_tab, hipStream_t st);

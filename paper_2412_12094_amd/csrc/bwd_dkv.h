@@ -62,21 +62,6 @@ inline DkvSlices dkv_slices(const sepattn_params &p, int kw, int wpg, int split,
     return sl;
 }
 
-// Whether KV heads that see every earlier key work through the list of all keys (see dkv_kernel).  As band units their
-// work is q = units / workgroups walks per workgroup, the longest about 1 + 1/q times the mean; as slices it is even, but
-// every key's gradients pass through fp32 partials.  That pays where a workgroup has about one unit (eight waves,
-// with nothing beside it on the compute unit to fill the gap: two) and the walks are long, with grouped heads, or
-// next to KV heads with shorter windows, which leave the full ones more workgroups.
-// Measured, a step in us, band units / slices, n = L.  Taken: 32/8 heads, d = 128, L = 8192 (q = 2, eight waves) 2716 / 2311,
-// L = 2048 (q = 1/2) 339 / 235, 16/8 heads, d = 64, L = 4096 (q = 2/3) 320 / 270 and twice that batch (q = 4/3) 442 / 429, every
-// other of 8/8 heads full, d = 64, L = 4096 246 / 205.  Not taken: 4 x 32/8 heads, L = 2048 (q = 2) 694 / 716, 2 x 12/12
-// heads, d = 64, L = 4096 (q = 2) 367 / 399 and one (q = 1) 242 / 247; every other of 8 x 12/12 heads full, L = 300 54 / 82.
-inline bool list_of_all_keys(const sepattn_params &p, int kw, int wpg, const FarGeom &fg, bool headwise) {
-    const long units = (p.L + fg.bk - 1) / fg.bk, G = p.Hq / p.Hkv;
-    const bool fits = p.cap + p.a >= p.L;  // the list has to fit where the far list does
-    return fits && 3 * units <= (kw == 4 ? 6 : 4) * (long)wpg && G * p.L >= 4096 && (G >= 2 || headwise);
-}
-
 // Query rows per LDS tile.  Workgroups that share a compute unit (two at d = 128 with 80 KB each,
 // three at d = 64 with 53 KB and 168 registers) stream tiles of 32 rows (one block) through the
 // ring of four, the single workgroup tiles of 64 rows (two blocks).

@@ -80,8 +80,7 @@ int launch_joint(const sepattn_params &p, int dq_wpg, const uint16_t *Q, const u
     const long n_groups = (long)p.B * (p.Hq / shape.gp), n_dq = n_groups * dq_wpg, n_bkv = (long)p.B * p.Hkv, rows = (long)p.B * p.Hq * p.L;
     const QueryGrid qg = query_grid(p, shape.gp, n_groups);
     JointPlan jp;
-    jp.kv_wpg = (int)((2l * compute_units() - n_dq) / n_bkv);
-    jp.kv_wpg = jp.kv_wpg < 1 ? 1 : jp.kv_wpg;
+    jp.kv_wpg = joint_dkv_workgroups(p, dq_wpg);
     jp.n_kv = (int)(n_bkv * jp.kv_wpg);
     jp.dq_wpg = dq_wpg;
     jp.split = band_split(p, jp.kv_wpg, 2);

@@ -7,7 +7,7 @@ import pytest
 
 import oracle
 import workloads as wl
-from test_gpu_parity import assert_close, assert_grads_close, dev, gpu_index, host, make_case
+from test_gpu_parity import assert_close, assert_grads_close, dev, gpu_index, host, make_case, packed_index
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -33,6 +33,21 @@ def run(B, Hq, Hkv, L, d, a, n, p, dtype, seed=1):
     assert_close(host(O), rO, dtype, "O")
     assert np.abs(host(LSE) - rL).max() <= (1e-4 if dtype == "fp32" else 2e-3)
     assert_grads_close(grads, refs, dtype)
+
+
+def run_packed(L, Hq, Hkv, d, a, n, p, cu, seed=1):
+    import paper_2412_12094_amd as sp
+
+    tok, Q, K, V, dO = make_case(1, Hq, Hkv, L, d, p, "bf16", seed)
+    scale = 1.0 / math.sqrt(d)
+    cus = [np.array(cu, dtype=np.int32)]
+    flags = oracle.mark_separators(tok, wl.SEPARATOR_IDS)
+    _, ds, de, idx, cnt, pre = packed_index(sp, tok, cus, a)
+    q, k, v, do = (dev(x, "bf16") for x in (Q, K, V, dO))
+    O, LSE = sp.sepattn_forward_packed(q, k, v, ds, de, idx, cnt, pre, n, scale)
+    grads = sp.sepattn_backward_packed(q, k, v, O, LSE, do, ds, de, idx, cnt, pre, n, scale)
+    torch.cuda.synchronize()
+    assert_grads_close(grads, oracle.backward_packed(Q, K, V, dO, flags, cus, a, n, scale, return_term_rss=True), "bf16")
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,L,d,a,n,p", [
@@ -113,6 +128,7 @@ def test_bf16_waves_whose_streams_end_apart(B, Hq, Hkv, L, d, a, n, p):
     (21, 4, 1, 384, 128, 4, 360, 0.1),  # as many parts as workgroups
     (21, 4, 1, 385, 128, 4, 360, 0.1),  # one key more: two parts
     (1, 8, 1, 8200, 128, 4, 2000, 0.05),  # eight-wave workgroups
+    (1, 8, 2, 8201, 128, 4, 256, 0.05),   # whole units: eight waves, the last unit has nine keys
 ])
 def test_bf16_band_units_in_parts(B, Hq, Hkv, L, d, a, n, p):
     run(B, Hq, Hkv, L, d, a, n, p, "bf16")
@@ -130,16 +146,51 @@ def test_bf16_far_work_beside_uneven_band_units(B, Hq, Hkv, L, d, a, n, p):
     run(B, Hq, Hkv, L, d, a, n, p, "bf16")
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,L,d,a,n,p", [
-    (1, 32, 8, 768, 128, 4, 100, 0.1),  # four heads, 192 query tiles: the last call that runs dQ and dK/dV in one launch
-    (1, 32, 8, 769, 128, 4, 100, 0.1),  # one position more: two launches
-    (2, 8, 4, 1536, 64, 0, 33, 0.1),    # two heads
-    (2, 8, 4, 1537, 64, 0, 33, 0.1),
-    (2, 8, 8, 1536, 64, 4, 70, 0.1),    # one head
-    (2, 8, 8, 1537, 128, 4, 70, 0.1),
-])
-def test_bf16_backward_in_one_launch_and_in_two(B, Hq, Hkv, L, d, a, n, p):
-    run(B, Hq, Hkv, L, d, a, n, p, "bf16")
+# B, Hq, Hkv, L, d, a, n, p, packed from documents, dQ and dK/dV in one launch (asserted where the rule is tested on the host)
+JOINT_CASES = [
+    (1, 32, 8, 768, 128, 4, 100, 0.1, False, True),  # four heads, 192 query tiles: the last call with one launch
+    (1, 32, 8, 769, 128, 4, 100, 0.1, False, False),  # one position more
+    (2, 8, 4, 1536, 64, 0, 33, 0.1, False, True),    # two heads
+    (2, 8, 4, 1537, 64, 0, 33, 0.1, False, False),
+    (2, 8, 8, 1536, 64, 4, 70, 0.1, False, True),    # one head
+    (2, 8, 8, 1537, 128, 4, 70, 0.1, False, False),
+    (1, 32, 8, 768, 128, 4, 100, 0.1, True, True),
+    (1, 32, 8, 769, 64, 4, 100, 0.1, True, False),
+    (1, 8, 8, 3072, 64, 3, 70, 0.1, True, True),
+    (1, 8, 8, 3073, 128, 3, 70, 0.1, True, False),
+]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,d,a,n,p,docs,one", JOINT_CASES)
+def test_bf16_backward_in_one_launch_and_in_two(B, Hq, Hkv, L, d, a, n, p, docs, one):
+    if docs:
+        run_packed(L, Hq, Hkv, d, a, n, p, [0, L // 3, L // 3 + 5, L // 2, L])
+    else:
+        run(B, Hq, Hkv, L, d, a, n, p, "bf16")
+
+
+# one row: dQ and dK/dV in one launch; four: in two (asserted where the rule is tested on the host)
+JOINT_ROWS = [(32, 8, 700, 128, 4, 100), (32, 8, 700, 64, 4, 30), (8, 4, 3000, 128, 0, 33), (12, 12, 2011, 64, 4, 64)]
+
+
+@pytest.mark.parametrize("Hq,Hkv,L,d,a,n", JOINT_ROWS)
+def test_bf16_dq_of_one_launch_and_of_two(Hq, Hkv, L, d, a, n):
+    """A row's dQ is the same bits in a call that runs dQ beside dK/dV and as part of a batch that does not; dK and dV, whose far work is
+    cut for other numbers of workgroups, differ by no more than two roundings to bf16 and the order of fp32 sums."""
+    import paper_2412_12094_amd as sp
+
+    B, scale = 4, 1.0 / math.sqrt(d)
+    tok, Q, K, V, dO = make_case(B, Hq, Hkv, L, d, 0.1, "bf16", 1)
+    q, k, v, do = (dev(x, "bf16") for x in (Q, K, V, dO))
+    _, idx, cnt, pre = gpu_index(sp, tok)
+    O, LSE = sp.sepattn_forward(q, k, v, idx, cnt, pre, a, n, scale)
+    call = lambda b: sp.sepattn_backward(*(x[b].contiguous() for x in (q, k, v, O, LSE, do, idx, cnt, pre)), a, n, scale)
+    two = call(slice(0, B))
+    for b in range(B):
+        one = call(slice(b, b + 1))
+        assert torch.equal(one[0][0], two[0][b])
+        for x, y in zip(one[1:], two[1:]):
+            assert np.abs(host(x[0]) - host(y[b])).max() <= 2.0 ** -7 * np.abs(host(y[b])).max()
 
 
 def test_bf16_backward_in_one_launch_is_recorded_once():

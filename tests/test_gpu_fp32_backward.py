@@ -17,12 +17,16 @@ def sp():
     return sp_
 
 
-# one launch: a tile, a ragged row, list tiles in many slices, the last size below the line at d = 64 and 128; two: the first above
-@pytest.mark.parametrize("B,Hq,Hkv,L,d,a,n,p", [
-    (1, 1, 1, 1, 64, 0, 1, 0.0), (1, 2, 1, 17, 128, 4, 3, 0.5), (1, 2, 1, 512, 64, 4, 64, 0.125), (2, 4, 1, 999, 64, 3, 40, 0.3),
-    (1, 4, 4, 300, 128, 0, 100, 0.1), (1, 14, 14, 544, 64, 4, 64, 0.1),
-    (1, 8, 2, 1024, 128, 4, 64, 0.1), (1, 8, 8, 1024, 64, 4, 16, 0.1), (1, 8, 8, 656, 128, 4, 16, 0.1)])
-def test_one_launch_and_two_give_the_same_bits(sp, B, Hq, Hkv, L, d, a, n, p):
+# one launch (the last column: yes): a tile, a ragged row, list tiles in many slices, the last size below the line at d = 64 and 128; two:
+# the first above
+CASES = [
+    (1, 1, 1, 1, 64, 0, 1, 0.0, True), (1, 2, 1, 17, 128, 4, 3, 0.5, True), (1, 2, 1, 512, 64, 4, 64, 0.125, True),
+    (2, 4, 1, 999, 64, 3, 40, 0.3, True), (1, 4, 4, 300, 128, 0, 100, 0.1, True), (1, 14, 14, 544, 64, 4, 64, 0.1, True),
+    (1, 8, 2, 1024, 128, 4, 64, 0.1, True), (1, 8, 8, 1024, 64, 4, 16, 0.1, False), (1, 8, 8, 656, 128, 4, 16, 0.1, False)]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,L,d,a,n,p,one", CASES)
+def test_one_launch_and_two_give_the_same_bits(sp, B, Hq, Hkv, L, d, a, n, p, one):  # one: asserted where the rule is tested on the host
     g = torch.Generator(device="cuda").manual_seed(L)
     tok = torch.from_numpy(wl.make_token_ids(B, L, p, L).astype("int32")).cuda()
     _, idx, cnt, pre = sp.sepattn_mark_compact(tok, wl.SEPARATOR_IDS.tolist())
