@@ -154,10 +154,10 @@ inline bool list_of_all_keys(const sepattn_params &p, int kw, int wpg, const Far
 
 // Whether dQ and dK/dV of a call share a launch (bwd_joint.h), and with how many dQ workgroups per group; 0: they do not.  They do in
 // four-wave shapes without split streams and without a list of all keys, whose query tiles are at most three eighths as many
-// as the workgroups that fit the chip.  Beyond that, the tiles take from dK/dV the workgroups that its longest units and slices need.  Backward, two launches' time over one's, over 110 calls of two head sizes: up to 64 tiles 1.12 to 1.62 (1.34 in
-// the mean), up to 128 1.19 to 1.55 (1.32), up to 192 1.10 to 1.43 (1.25), up to 256 0.75 to 1.29 (1.04), up to 320 0.84 to 1.04, beyond
-// less.  In us, two / one: 8/2 heads, L = 600, n = 96, d = 128 (38 tiles) 26.9 / 20.2, d = 64 21.8 / 16.8; 32/8 heads, L = 768, n = 100 (192)
-// 33.3 / 31.1, d = 64 24.3 / 24.3; 12/12 heads, L = 2011, n = 64 (192) 41.4 / 37.1; 4 x 8/2 heads, L = 936, n = 657 (240) 60.0 / 80.2.
+// as the workgroups that fit the chip.  Beyond that, the tiles take from dK/dV the workgroups that its longest units and slices need.  Backward, two launches' time over one's, over 137 calls of two head sizes: up to 64 tiles 1.22 to 1.59 (1.34 in
+// the mean), up to 128 1.22 to 1.56 (1.33), up to 192 1.01 to 1.36 (1.20), up to 256 0.74 to 1.29 (1.08), up to 320 0.48 to 1.22 (1.01).
+// In us, two / one: 8/2 heads, L = 600, n = 96, d = 128 (38 tiles) 27.1 / 20.6, d = 64 22.2 / 17.2; 32/8 heads, L = 768, n = 100 (192) 40.0 /
+// 31.9, d = 64 24.5 / 24.2; 12/12 heads, L = 2011, n = 64 (192) 42.1 / 37.7; 4 x 8/2 heads, L = 936, n = 657 (240) 59.4 / 80.3.
 inline int joint_dq_workgroups(const sepattn_params &p, const HeadWin &hw, bool docs) {
     const QueryShape shape = query_shape(p);
     if (any_delta(hw) || shape.nw != 4 || dkv_key_blocks(p, docs) != 2) return 0;

@@ -204,7 +204,11 @@ __device__ __forceinline__ void dkv_work(
     // one beyond a unit's cost.  All of it to the others, one workgroup of sixteen got the far work of 47 units' keys: dK/dV and
     // combine in us, so / now: 32/32 heads, L = 3000, n = 512 178 / 103, 16/8 heads, L = 3856, n = 156 174 / 57, 4 x 32/8 heads, L = 3000,
     // n = 1024 605 / 483; over 240 calls 1.02 times as fast, level where the units divide evenly.
+    // Of what the equal parts leave over, the others get an item each, and as many of the first (`extra`) as there are more: all of it
+    // to the others, one workgroup of 43 got 39 items where the rest had a unit (10 items) and four.  Backward in us, so / now: 8/8 heads, n = 22, L = 2646,
+    // d = 64 35 to 45 (with the separators) / 27 to 28, L = 2611, d = 128 47.3 / 39.1; where units divide evenly nothing changes.
     long per_heavy = 0, n_heavy = 0;
+    int extra = 0;
     if (heavy) {
         const long rest = max(far_total - unit_items * light, 0l);
         per_heavy = HW ? quotient(rest, wpg) : by(rest, sl.by_wpg, wpg);
@@ -212,9 +216,12 @@ __device__ __forceinline__ void dkv_work(
         if (per_heavy < min_slice) {
             per_heavy = min_slice;
             n_heavy = min(max((HW ? quotient(rest, min_slice) : by(rest, sl.by_min_slice, min_slice)) - light, 0l), (long)heavy);
+        } else {
+            extra = max((int)(rest - per_heavy * wpg) - light, 0);
         }
     }
-    const long far_light = far_total - per_heavy * n_heavy;
+    auto heavy_start = [&](int v) __attribute__((always_inline)) { return v * per_heavy + min(v, extra); };  // of workgroup v of those n_heavy
+    const long all_heavy = per_heavy * n_heavy + extra, far_light = far_total - all_heavy;
     const long n_light = min(max(HW ? quotient(far_light, min_slice) : by(far_light, sl.by_min_slice, min_slice), 1l), (long)light);
     const int w_light = w_id - heavy;
     // the first of the slices w of n_light equal ones: floor(w far_light / n_light), w <= n_light <= wpg, from one division
@@ -223,8 +230,9 @@ __device__ __forceinline__ void dkv_work(
         const long x = w * over;  // < n_light^2
         return w * whole + (x < kSmallQuotient ? (long)small_quotient((int)x, reciprocal((int)n_light)) : x / n_light);
     };
-    const long s0 = w_light < 0 ? max(w_light + n_heavy, 0l) * per_heavy : per_heavy * n_heavy + slice_start(min((long)w_light, n_light));
-    const long s1 = w_light < 0 ? (w_light + n_heavy < 0 ? 0l : s0 + per_heavy) : per_heavy * n_heavy + slice_start(min(w_light + 1l, n_light));
+    const int v_heavy = w_light + (int)n_heavy;
+    const long s0 = w_light < 0 ? heavy_start(max(v_heavy, 0)) : all_heavy + slice_start(min((long)w_light, n_light));
+    const long s1 = w_light < 0 ? (v_heavy < 0 ? 0l : heavy_start(v_heavy + 1)) : all_heavy + slice_start(min(w_light + 1l, n_light));
 
     // iteration state over the pieces: first the far pieces of the slice (list tiles in groups of 64,
     // `pend` = tiles of the current group that overlap the slice and are still to be visited), then

@@ -141,6 +141,9 @@ def test_bf16_band_units_in_parts(B, Hq, Hkv, L, d, a, n, p):
     (1, 32, 32, 1090, 128, 4, 60, 0.1),   # 18 units: fourteen share it
     (2, 16, 16, 3000, 64, 4, 100, 0.2),   # 47 units, 24 workgroups
     (2, 16, 16, 3000, 64, 4, [100] * 8 + [300] * 8, 0.2),
+    (1, 8, 8, 2646, 64, 4, 22, 0.1),      # 42 units, 43 workgroups: all but one share it, in parts that differ by an item
+    (1, 32, 32, 1000, 128, 4, 20, 0.3),   # 16 units, 16 workgroups: none has a unit less
+    (1, 16, 16, 2000, 64, 4, [20] * 15 + [30], 0.3),
 ])
 def test_bf16_far_work_beside_uneven_band_units(B, Hq, Hkv, L, d, a, n, p):
     run(B, Hq, Hkv, L, d, a, n, p, "bf16")
