@@ -15,7 +15,7 @@
  *   - Pointers marked DEVICE address memory of the current HIP device; HOST pointers address
  *     ordinary host memory.  The caller owns every buffer, including workspaces; the library
  *     allocates no device memory and keeps no state between calls (the fixed scratch array of
- *     sepattn_decode_noalloc aside).
+ *     sepattn_decode_noalloc and a counter that numbers launches aside).
  *   - Alignment: token_ids, Q, K, V, O, dO, dQ, dK, dV, q, Kc, Vc, out, k_new, v_new and rope tables
  *     must be 16-byte aligned, is_sep 4-byte aligned, workspaces 256-byte aligned; a misaligned
  *     buffer is refused with SEPATTN_ERR_PARAM (workspaces: SEPATTN_ERR_WORKSPACE).

@@ -4,12 +4,13 @@
 //   dS_ij = P_ij (dP_ij - D_i),  dQ_i = scale sum_j dS_ij K_j,  dK_j = scale sum_i dS_ij Q_i,
 //   dV_j = sum_i P_ij dO_i   (dK, dV summed over the query heads of the KV head).
 //
-// Three launches, no floating-point atomics (results are bit-reproducible):
-//  1. dq_kernel (this file): persistent workgroups over the query tiles, same dense key stream as the forward
+// Three launches, no floating-point atomics (results are bit-reproducible; a small call has 1. and 2. side by side in one launch behind a
+// kernel that forms -D_i and LSE_i*log2(e) of all rows: bwd_joint.h, joint_dq_workgroups):
+//  1. dq_kernel (this file; its work: bwd_dq.h): persistent workgroups over the query tiles, same dense key stream as the forward
 //     [initial | separators older than the window | band].  Also writes -D_i and LSE_i*log2(e).
 //     (Where few tiles have long streams, these go in two parts to two workgroups and dq_parts_kernel adds their
 //     fp32 sums: see split_tiles.)
-//  2. dkv_kernel (bwd_dkv_bf16.hip): the visible pairs split into band pairs (i-j < n) and far
+//  2. dkv_kernel (bwd_dkv_bf16.hip; its work: bwd_dkv.h): the visible pairs split into band pairs (i-j < n) and far
 //     pairs (i-j >= n, j an initial token or a separator); far units work on the COMPACTED list of
 //     such keys and write fp32 partials, band units finish the keys that are not on that list.
 //  3. dkv_combine_kernel: adds, in fixed order, the partials of every far-list key and rounds once.

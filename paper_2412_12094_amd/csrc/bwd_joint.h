@@ -7,7 +7,8 @@
 // rows of O.  The sums and their order are those of the separate kernels, so the results are the same bits up to where dK/dV is
 // cut: its slices follow the number of workgroups that dQ leaves it.
 // Bounds: the latency of its chains (row values -> a unit's or slice's rows and tiles -> its steps -> partials).  The backward at 8/2 heads,
-// L = 600, n = 96, d = 128: 26.9 us in two launches (dQ 12, dK/dV 14, sum of the parts 5), 20.2 here (row values 3, this 14, sum 5).
+// L = 600, n = 96, d = 128: 27.1 us with two launches (in a trace, which adds a few tenths to each kernel: dQ 11.3, dK/dV 12.1, sum of the parts
+// 5.1), 20.6 here (row values 2.7, this 13.5, sum 5.2).
 #pragma once
 
 #include "bwd_dq.h"

@@ -30,6 +30,8 @@
 // 10.5 -> 7.6 / 9.0.  Where the 13100 cycles of such a workgroup with ROPE go that adds (one block per wave, 4 sequences): sizes and
 // table's requests 1050, rows' requests 700, table in registers 1200, K rows 900, turned and multiplied 1800, V 800,
 // waves' records 1400, slices' records published 900, counted 1000, added 2700.
+// Then: the counting word looked at while the records are on their way and set back behind the slices' maximum, at d = 64 the slices' pairs along
+// rows of lanes.  Calls with slices 0.1 to 0.2 us less, at d = 64 0.3 to 0.6 (4 x 32/8 heads, 1999 entries 6.84 -> 6.43).
 //
 // Operand layouts of 16x16x32 (lane l, g = l / 16): A row l%16, k = 8g..8g+7; B column l%16, same k; C
 // column l%16, rows 4g..4g+3.  Row 4g+i of score tile t (t = 0, 1) is row 8g+4t+i of the block, so that
