@@ -204,9 +204,10 @@ __device__ __forceinline__ void dkv_work(
     // one beyond a unit's cost.  All of it to the others, one workgroup of sixteen got the far work of 47 units' keys: dK/dV and
     // combine in us, so / now: 32/32 heads, L = 3000, n = 512 178 / 103, 16/8 heads, L = 3856, n = 156 174 / 57, 4 x 32/8 heads, L = 3000,
     // n = 1024 605 / 483; over 240 calls 1.02 times as fast, level where the units divide evenly.
-    // Of what the equal parts leave over, the others get an item each, and as many of the first (`extra`) as there are more: all of it
-    // to the others, one workgroup of 43 got 39 items where the rest had a unit (10 items) and four.  Backward in us, so / now: 8/8 heads, n = 22, L = 2646,
-    // d = 64 35 to 45 (with the separators) / 27 to 28, L = 2611, d = 128 47.3 / 39.1; where units divide evenly nothing changes.
+    // What the equal parts leave over goes to the others too, unless that would be more than two items each: then they get one, and as many
+    // of the first (`extra`) as there are more.  All of it to the others, one workgroup of 43 got 39 items where the rest had a unit (10
+    // items) and four.  Backward in us, so / now: 8/8 heads, n = 22, L = 2646, d = 64 35 to 45 (with the separators) / 27 to 28, L = 2611,
+    // d = 128 47.3 / 39.1.
     long per_heavy = 0, n_heavy = 0;
     int extra = 0;
     if (heavy) {
@@ -217,7 +218,8 @@ __device__ __forceinline__ void dkv_work(
             per_heavy = min_slice;
             n_heavy = min(max((HW ? quotient(rest, min_slice) : by(rest, sl.by_min_slice, min_slice)) - light, 0l), (long)heavy);
         } else {
-            extra = max((int)(rest - per_heavy * wpg) - light, 0);
+            const int over = (int)(rest - per_heavy * wpg) - light;
+            extra = over > light ? over : 0;
         }
     }
     auto heavy_start = [&](int v) __attribute__((always_inline)) { return v * per_heavy + min(v, extra); };  // of workgroup v of those n_heavy
